@@ -48,6 +48,8 @@ struct Shape {
     int variant;
     int high;                 // 1: FREQKV_FLAG_RETAIN_HIGH
     int elem;                 // bytes per cache element
+    int nearfar;              // 1: the near/far form runs (nf holds its geometry), whatever `variant` says
+    NfGeom nf;
     long long hts_per_slab;   // batch * n_heads
     int nslabs;               // 2 * n_layers
 };
@@ -239,6 +241,11 @@ freqkv_status_t check_shape(const freqkv_layout_t* L, int n_heads, int head_dim,
         sh.variant = (pays || (L->flags & FREQKV_FLAG_TWO_LEVEL_FOLD)) ? kFold2F16 : kFoldF16;
     }
     else sh.variant = (sh.n % 2 == 0 && sh.Lc % 2 == 0) ? kFoldF16 : kPlainF16;
+    // The near/far form takes the place of all of these wherever it exists (no flag that asks for a matrix form, head_dim
+    // a multiple of 32, ratios from 0.2, spans that its LDS image holds).
+    sh.nearfar = sh.variant != kNone && sh.variant != kDrop && sh.variant != kF32 && !sh.high &&
+                 !(L->flags & (FREQKV_FLAG_DENSE | FREQKV_FLAG_SINGLE_FOLD | FREQKV_FLAG_TWO_LEVEL_FOLD)) &&
+                 (long long)window * L->stride_token * 2 < (1LL << 32) && nf_geometry(sh.n, sh.Lc, head_dim, &sh.nf);
     *out = sh;
     return FREQKV_OK;
 }
@@ -311,6 +318,39 @@ freqkv_status_t get_basis(const Shape& sh, const Geom& g, int rescale, hipStream
         HIP_TRY(hipStreamWaitEvent(st, it->second.ready, 0));
     }
     *out = it->second.ptr;
+    return FREQKV_OK;
+}
+
+// Tables of the near/far form, cached like the bases.
+freqkv_status_t get_nf_tables(const Shape& sh, hipStream_t st, const char** out)
+{
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    BasisKey key{dev, sh.n, sh.Lc, kNearFar, 0, 0};
+    std::lock_guard<std::mutex> lock(g_mu);
+    auto it = g_basis.find(key);
+    if (it == g_basis.end()) {
+        BasisEntry e;
+        e.bytes = (size_t)sh.nf.table_bytes;
+        hipError_t err = hipMalloc(&e.ptr, e.bytes);
+        if (err != hipSuccess) {
+            set_error("hipMalloc(near/far tables)", err);
+            (void)hipGetLastError();
+            return FREQKV_E_ALLOC;
+        }
+        err = launch_nf_tables(sh.nf, (char*)e.ptr, st);
+        if (err == hipSuccess) err = hipEventCreateWithFlags(&e.ready, hipEventDisableTiming);
+        if (err == hipSuccess) err = hipEventRecord(e.ready, st);
+        if (err != hipSuccess) {
+            set_error("near/far table build", err);
+            (void)hipFree(e.ptr);
+            return FREQKV_E_HIP;
+        }
+        it = g_basis.emplace(key, e).first;
+    } else {
+        HIP_TRY(hipStreamWaitEvent(st, it->second.ready, 0));
+    }
+    *out = (const char*)it->second.ptr;
     return FREQKV_OK;
 }
 
@@ -555,11 +595,15 @@ freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink
     freqkv_layout_t L;
     memset(&L, 0, sizeof(L));
     L.dtype = dtype; L.n_layers = 1; L.batch = 1; L.token_capacity = window;
-    L.stride_token = 8; L.flags = flags;
+    L.stride_token = 32; L.flags = flags;
     Shape sh;
-    freqkv_status_t rc = check_shape(&L, 1, 8, window, window, n_sink, retain_ratio, &sh);
+    freqkv_status_t rc = check_shape(&L, 1, 32, window, window, n_sink, retain_ratio, &sh);   // head_dim as caches have it
     if (rc < 0) return rc;
     if (sh.variant == kNone || sh.variant == kDrop) return FREQKV_OK;
+    if (sh.nearfar) {
+        const char* tables = nullptr;
+        return get_nf_tables(sh, (hipStream_t)stream, &tables);
+    }
     Geom g = make_geom(sh, L, 1, 0);
     void* basis = nullptr;
     int key = !(flags & FREQKV_FLAG_NO_RESCALE);
@@ -617,6 +661,49 @@ freqkv_status_t compress_resolved(const std::vector<char*>& bases, const freqkv_
     }
 
     const int rescale = !(L.flags & FREQKV_FLAG_NO_RESCALE);
+
+    if (sh.nearfar) {
+        // Near/far form: one kernel, in place; the tail moves afterwards, when the span has been read.  It needs no
+        // workspace, but a plan that names a matrix form has asked the caller for one: the contract stays.
+        if (sh.variant != kFast) {
+            const size_t min_ws = pass_workspace(sh, 1);
+            if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < min_ws) return FREQKV_E_WORKSPACE;
+        }
+        const char* tables = nullptr;
+        ProfSpan ps;                                           // profiles of matrix-form plans count a preparation: the tables
+        if (sh.variant != kFast) HIP_TRY(prof_begin(st, 0, &ps));
+        freqkv_status_t rc = get_nf_tables(sh, st, &tables);
+        if (rc < 0) return rc;
+        if (sh.variant != kFast) HIP_TRY(prof_end(st, &ps));
+        if (g_prof_on) { std::lock_guard<std::mutex> lock(g_mu); g_prof_acc.calls++; }
+        NfGeom nf = sh.nf;
+        nf.S = sh.S; nf.n_heads = sh.n_heads; nf.hts_per_slab = (int)sh.hts_per_slab;
+        nf.stride_batch = L.stride_batch; nf.stride_head = L.stride_head; nf.stride_token = L.stride_token;
+        nf.out_scale = rescale ? 1.0f : (float)std::sqrt((double)sh.n / (double)sh.Lc);
+        for (int s0 = 0; s0 < sh.nslabs; s0 += kMaxSlabs) {
+            int slabs = sh.nslabs - s0 < kMaxSlabs ? sh.nslabs - s0 : kMaxSlabs;
+            SlabTable tab;
+            memset(&tab, 0, sizeof(tab));
+            for (int i = 0; i < slabs; ++i) tab.base[i] = bases[(size_t)s0 + i];
+            nf.hts = slabs * (int)sh.hts_per_slab;
+            nf.tap_slab0 = s0;
+            ProfSpan sp;
+            HIP_TRY(prof_begin(st, 1, &sp));
+            HIP_TRY(launch_nearfar(tab, nf, tables, tap, st));
+            HIP_TRY(prof_end(st, &sp));
+            if (sh.tail > 0) {
+                Geom g = make_geom(sh, L, slabs, s0);
+                HIP_TRY(prof_begin(st, 2, &sp));
+                const int gap = sh.n - sh.Lc;
+                for (int r0 = 0; r0 < sh.tail; r0 += gap) {
+                    int rows = sh.tail - r0 < gap ? sh.tail - r0 : gap;
+                    HIP_TRY(launch_move_rows(tab, g, sh.elem, sh.W + r0, sh.S + sh.Lc + r0, rows, st));
+                }
+                HIP_TRY(prof_end(st, &sp));
+            }
+        }
+        return FREQKV_OK;
+    }
 
     if (sh.variant == kFast) {
         // Factored transform: one kernel reads the span from the cache and writes the retained rows in place

@@ -78,7 +78,8 @@ __device__ __forceinline__ char* column_base(const SlabTable& tab, const Geom& g
     return tab.base[slab] + off * elem_bytes;
 }
 
-enum Variant { kNone = 0, kFoldF16 = 1, kPlainF16 = 2, kF32 = 3, kDrop = 4, kFold2F16 = 5, kFast = 6 };
+enum Variant { kNone = 0, kFoldF16 = 1, kPlainF16 = 2, kF32 = 3, kDrop = 4, kFold2F16 = 5, kFast = 6,
+               kNearFar = 7 };   // 7: key of its tables only; a plan names the form that FREQKV_FLAG_DENSE or the layout falls back to
 
 // ---- basis construction (fp64 closed form, rounded once) -------------------------
 // G: [Kpad/8][Grows][8] fp16.  Folded: rows [0,Mpad) even part, rows [Mpad,2Mpad) odd part.
@@ -127,6 +128,28 @@ void fast_build_tables_host(int n, int head_dim, char* out);   // fp64, rounded 
 // rescale of Eq. 3).  dump/stop: diagnostic, see the kernel; pass nullptr, 0.
 hipError_t launch_fast(const SlabTable& tab, const Geom& g, const void* tables, float rest_scale, float* tap,
                        _Float16* dump, int stop, hipStream_t st);
+
+// ---- near/far form (bf16 caches, n/5 <= Lc < n): one kernel, no workspace ------------------------------------
+constexpr int kNfMinSpan = 128;
+// Geometry (by-value kernel argument); everything but the last block follows from n and Lc.
+struct NfGeom {
+    int n, Lc;
+    int NK, NLO;             // leaves (128 rows) per exact window; its 16-row steps that get a second bf16 part
+    int GT;                  // tiles (32 result rows) per step and group
+    int NL, NC, NT, NG, NB;  // leaves, blocks of 4 leaves, tiles, groups, blocks of a group's neighbourhood
+    int NLm, NCp, NGp;       // leaves, blocks, groups that LDS has room for
+    int R, NLr;              // ring slots; NL mod R
+    int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
+    int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
+    int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;
+    int d;
+    int S, n_heads, hts_per_slab, hts;
+    float out_scale;         // sqrt(n/Lc) without the rescale of Eq. 3, else 1
+    long long stride_batch, stride_head, stride_token, tap_slab0;
+};
+bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out);
+hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st);
+hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, hipStream_t st);
 
 // ---- tail move: rows [src, src+rows) -> [dst, dst+rows) of every head-tensor; ranges must not overlap
 hipError_t launch_move_rows(const SlabTable& tab, const Geom& g, int elem_bytes, int src_row,

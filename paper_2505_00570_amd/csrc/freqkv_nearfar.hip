@@ -1,0 +1,723 @@
+// Near/far form of the compression operator: any span n and any retained length Lc from n/5 up, bf16 caches.
+//
+// The operator of Sec. 3.3 Eq. 2-3 with the transforms of Appendix A (n-point DCT-II, the Lc lowest
+// coefficients, Lc-point inverse, sqrt(Lc/n)) is, entry by entry,
+//     M[m][j] = (1/2n) (E(a_m - b_j) + E(a_m + b_j)),   E(t) = sin(Lc t) cot(t/2),
+//     a_m = pi (2m+1) / 2Lc,   b_j = pi (2j+1) / 2n,    sin(Lc (a_m -+ b_j)) = (-1)^m cos(Lc b_j),
+// that is a Cauchy matrix between the points a_m and b_j with diagonal factors on both sides:
+//     M[m][j] = (1/n) (-1)^m K(a_m, b_j) cos(Lc b_j),   K(a, b) = (cot((a-b)/2) + cot((a+b)/2)) / 2.
+// Rows that lie close together along the token axis get the exact entries; K between intervals that are apart is
+// smooth, so there it is interpolated on Chebyshev points of both intervals (the kernel-independent fast multipole
+// scheme with Lagrange polynomials, 8 points per interval, relative error of the far part below 1e-3 of a share
+// that is itself 6 % of the result: 1e-6 in all).  Sizes, in span rows:
+//     leaf     128 rows: its 8 moments are sum_j L_s(j) cos(Lc b_j) x_j
+//     block    4 leaves: 8 moments from its leaves' (coarse level)
+//     tile     32 result rows (32 n/Lc span rows): a window of NK leaves with exact entries, 8 local values from the
+//              leaves of the neighbouring blocks
+//     group    the GT tiles of one step: 8 local values from all the blocks further away
+// Per channel that is about 1.1 M multiply-adds at 8188 -> 4094 against 33.5 M for the dense operator, all of them on
+// the matrix cores with bf16 operands: the cache values enter as they are (no scale, no conversion, no range guard),
+// the exact entries as the sum of two bf16 parts (16 significant bits; the second part only around the
+// tile, where entries are large), everything of the far part as one bf16 part.  Error 1e-4 of a channel's RMS.
+//
+// One workgroup owns 32 channels (64 bytes of every row) of one head-tensor and streams the span twice through a ring
+// of LDS slots (a leaf each): first for the moments, then for the result rows.  What bounds it is moving the rows:
+// 512 head-tensors x 8188 rows take 0.35 ms for one read and one write of half and 0.45 ms with the second read (a bare
+// stream with the same ring, grid and stores), because 256 workgroups x 0.5 MB are still in the 256 MB memory-side
+// cache when they are read again: that is why a workgroup takes 32 channels and not a whole 256-byte row.  Ownership
+// by columns keeps the in-place write free of hazards: rows are written behind the rows still to be read.
+//
+// Four waves move data (global -> LDS copies, counted by vmcnt), four compute; apart, because the copies and the loads of
+// tables come back in one order: a wave that did both would wait for its newest copies in front of every table.
+#include "freqkv_internal.h"
+
+#include <cmath>
+#include <cstring>
+
+namespace freqkv {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+template <int I> struct IC { static constexpr int value = I; };
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(IC<I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
+constexpr int kC = 32;                    // channels per workgroup
+constexpr int kRowB = kC * 2;             // bytes of one row in a ring slot
+constexpr int kLeaf = 128;                // span rows per leaf
+constexpr int kSlotB = kLeaf * kRowB;     // bytes of one ring slot
+constexpr int kVecB = kC * 8 * 2;         // bytes of 8 moments (or local values) of 32 channels, [channel][8] bf16
+constexpr int kFrag = 1024;               // one operand fragment: 64 lanes x 8 bf16
+constexpr int kCompute = 4, kMovers = 4;  // waves
+constexpr int kNB = 3;                    // blocks of a group's neighbourhood: 512 rows or less, 128 to spare on both sides
+constexpr int kLdsBytes = 160 * 1024;
+
+// Where the exact window of tile t starts (leaf), and whether the ends of the span shifted it.
+struct TileAt { int leaf0, clamped; };
+__host__ __device__ inline TileAt tile_at(const NfGeom& g, int t)
+{
+    const int a = (int)((unsigned)(32 * t) * (unsigned)g.n / (unsigned)g.Lc);       // first span row of the tile
+    int l = (a - 32) >> 7;                                                           // at least 32 rows on its left
+    const int top = g.NL - g.NK;
+    TileAt r;
+    r.clamped = l < 0 || l > top;
+    r.leaf0 = l < 0 ? 0 : (l > top ? top : l);
+    return r;
+}
+// First of the 16-row steps of the window that get the second bf16 part: 8 to 23 rows ahead of the tile.
+__host__ __device__ inline int tile_lo_step(const NfGeom& g, int t, int leaf0)
+{
+    const int a = (int)((unsigned)(32 * t) * (unsigned)g.n / (unsigned)g.Lc);
+    const int k = ((a - 8) >> 4) - leaf0 * 8;
+    const int top = 8 * g.NK - g.NLO;
+    return k < 0 ? 0 : (k > top ? top : k);
+}
+__host__ __device__ inline int tile_slot(const NfGeom& g, int t)
+{
+    if (!g.shifts) return t;
+    return t < g.tlo ? g.PT + t : (t >= g.thi ? g.PT + g.tlo + (t - g.thi) : t % g.PT);
+}
+// First block of the neighbourhood that group gr treats leaf by leaf.
+__host__ __device__ inline int group_block0(const NfGeom& g, int gr)
+{
+    const int a = (int)((unsigned)(32 * g.GT * gr) * (unsigned)g.n / (unsigned)g.Lc);
+    const int b = (a - 128) >> 9, top = g.NC > g.NB ? g.NC - g.NB : 0;
+    return b < 0 ? 0 : (b > top ? top : b);
+}
+
+// ------------------------------------------------------------------------------------------
+// tables, built on the device in fp64 and rounded once
+// ------------------------------------------------------------------------------------------
+
+// Chebyshev points of the first kind on [-1, 1] and the Lagrange polynomials on them.
+__device__ double cheb(int s) { return cospi((2 * s + 1) / 16.0); }
+__device__ double lagrange(int s, double u)
+{
+    double p = 1.0;
+    const double xs = cheb(s);
+    for (int q = 0; q < 8; ++q)
+        if (q != s) p *= (u - cheb(q)) / (xs - cheb(q));
+    return p;
+}
+// E of the header comment at the angle pi q / (2 n Lc); its limit at zero is 2 Lc.
+__device__ double entry(long long q, long long n, long long Lc)
+{
+    if (q == 0) return 2.0 * (double)Lc;
+    const double t = (double)q / (double)(4 * n * Lc);
+    return sinpi((double)(q % (4 * n)) / (double)(2 * n)) * cospi(t) / sinpi(t);
+}
+// K between two positions in span rows; image_only: without its direct term.
+__device__ double far_kernel(double a, double b, double n, bool image_only)
+{
+    const double s = (a + b) / (2.0 * n), d = (a - b) / (2.0 * n);
+    double v = cospi(s) / sinpi(s);
+    if (!image_only) v += cospi(d) / sinpi(d);
+    return 0.5 * v;
+}
+// Intervals in span rows, cut at the end of the span.
+struct Iv {
+    double c, h;             // centre, half width; h <= 0: nothing in it
+    __device__ double node(int s) const { return c + h * cheb(s); }
+};
+__device__ Iv interval(double a, double b, double n)
+{
+    if (b > n) b = n;
+    return Iv{0.5 * (a + b), 0.5 * (b - a)};
+}
+__device__ Iv leaf_iv(const NfGeom& g, int l) { return interval(128.0 * l, 128.0 * l + 128.0, g.n); }
+__device__ Iv block_iv(const NfGeom& g, int b) { return interval(512.0 * b, 512.0 * b + 512.0, g.n); }
+__device__ Iv tile_iv(const NfGeom& g, int t)
+{
+    const double r = (double)g.n / g.Lc;
+    return interval(32.0 * t * r, (32.0 * t + 32.0) * r, g.n);
+}
+__device__ Iv group_iv(const NfGeom& g, int gr)
+{
+    const double r = (double)g.n / g.Lc, w = 32.0 * g.GT;
+    return interval(w * gr * r, (w * gr + w) * r, g.n);
+}
+
+// Near entry of result row m and span row j for table slot `slot`.
+__device__ double near_entry(const NfGeom& g, int slot, int m_in, int row_in)
+{
+    int t = slot;
+    bool direct = false;                    // a pattern shared by the tiles in the middle: no reflected term
+    if (g.shifts) {
+        if (slot < g.PT) {
+            t = g.tlo + ((slot - g.tlo) % g.PT + g.PT) % g.PT;
+            direct = true;
+            if (t >= g.thi) return 0.0;
+        } else {
+            t = slot - g.PT;
+            if (t >= g.tlo) t = g.thi + (t - g.tlo);
+        }
+    }
+    const long long n = g.n, Lc = g.Lc, m = 32LL * t + m_in, j = 128LL * tile_at(g, t).leaf0 + row_in;
+    if (t >= g.NT || m >= Lc || j >= n) return 0.0;
+    double v = entry((2 * m + 1) * n - (2 * j + 1) * Lc, n, Lc);
+    if (!direct) v += entry((2 * m + 1) * n + (2 * j + 1) * Lc, n, Lc);
+    return v / (2.0 * n);
+}
+
+// What the kernel wants to know of tile t and of group gr in one word each: first leaf of the window, first step with
+// second parts, table slot; first block of the neighbourhood.
+__device__ uint32_t tile_word(const NfGeom& g, int t)
+{
+    const int l = tile_at(g, t).leaf0;
+    return (uint32_t)l | (uint32_t)tile_lo_step(g, t, l) << 8 | (uint32_t)tile_slot(g, t) << 16;
+}
+
+// One thread per 16 bytes (lane) of a fragment.
+__global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
+{
+    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= g.off_w / 16) {
+        const long long w = idx - g.off_w / 16;
+        uint32_t* const words = (uint32_t*)(out + g.off_w);
+        if (w < g.NT) words[w] = tile_word(g, (int)w);
+        else if (w < g.NT + g.NG) words[w] = (uint32_t)group_block0(g, (int)w - g.NT);
+        return;
+    }
+    const int lane = (int)(idx & 63);
+    const long long byte = (idx >> 6) * kFrag;
+    const int l32 = lane & 31, hw = lane >> 5, l16 = lane & 15, g4 = lane >> 4;
+    const double n = g.n;
+    bf16x8 v;
+    for (int i = 0; i < 8; ++i) {
+        double x = 0.0;
+        if (byte < g.off_v) {
+            // exact entries: [slot][first parts: 8 NK steps | second parts: NLO steps], 16 rows x 32 results
+            const int f = (int)(byte / kFrag), per = 8 * g.NK + g.NLO;
+            const int slot = f / per;
+            int k = f - slot * per;
+            const bool second = k >= 8 * g.NK;
+            if (second) {
+                int t = slot;
+                if (g.shifts) {
+                    if (slot < g.PT) t = g.tlo + ((slot - g.tlo) % g.PT + g.PT) % g.PT;
+                    else { t = slot - g.PT; if (t >= g.tlo) t = g.thi + (t - g.tlo); }
+                }
+                k = k - 8 * g.NK + tile_lo_step(g, t, tile_at(g, t).leaf0);
+            }
+            x = near_entry(g, slot, l32, 16 * k + 8 * hw + i);
+            if (second) x -= (double)(float)(__bf16)(float)x;
+        } else if (byte < g.off_m) {
+            // moments: [slot][4 steps of 32 rows], 16 (8 used) moments x 32 rows
+            const int f = (int)((byte - g.off_v) / kFrag), slot = f >> 2;
+            const int leaf = g.v_slots == 2 ? (slot ? g.NL - 1 : 0) : slot;
+            const long long j = 128LL * leaf + (f & 3) * 32 + 8 * g4 + i;
+            const Iv iv = leaf_iv(g, leaf);
+            if (l16 < 8 && j < g.n && iv.h > 0) {
+                const long long ph = ((2 * j + 1) * (long long)g.Lc) % (4LL * g.n);      // cos(Lc b_j)
+                x = lagrange(l16, (j + 0.5 - iv.c) / iv.h) * cospi((double)ph / (2.0 * n)) / 128.0;
+            }
+        } else if (byte < g.off_c) {
+            // coarse moments of a block from those of its 4 leaves
+            const int b = (int)((byte - g.off_m) / kFrag), leaf = 4 * b + g4;
+            const Iv lv = leaf_iv(g, leaf), bv = block_iv(g, b);
+            if (l16 < 8 && lv.h > 0) x = lagrange(l16, (lv.node(i) - bv.c) / bv.h) * 0.25;
+        } else if (byte < g.off_f) {
+            // local values of two groups from 4 blocks
+            const int f = (int)((byte - g.off_c) / kFrag), kst = g.NCp / 4;
+            const int gr = 2 * (f / kst) + (l16 >> 3), b = 4 * (f % kst) + g4;
+            if (gr < g.NG && b < g.NC) {
+                const int b0 = group_block0(g, gr);
+                if (b < b0 || b >= b0 + g.NB)
+                    x = far_kernel(group_iv(g, gr).node(l16 & 7), block_iv(g, b).node(i), n, false) * 512.0 / n;
+            }
+        } else if (byte < g.off_t) {
+            // local values of two tiles from the 4 leaves of a neighbouring block
+            const int f = (int)((byte - g.off_f) / kFrag), mt = f / g.NB;
+            const int gr = mt / (g.GT / 2), t = 2 * mt + (l16 >> 3);
+            const int leaf = 4 * (group_block0(g, gr) + f % g.NB) + g4;
+            const Iv lv = leaf_iv(g, leaf);
+            if (t < g.NT && lv.h > 0) {
+                const TileAt at = tile_at(g, t);
+                const bool near = leaf >= at.leaf0 && leaf < at.leaf0 + g.NK;
+                const bool shared = g.shifts && t >= g.tlo && t < g.thi;
+                if (!near || shared) x = far_kernel(tile_iv(g, t).node(l16 & 7), lv.node(i), n, near) * 128.0 / n;
+            }
+        } else {
+            // results of a tile from its 8 local values and the 8 of its group; [any but the last group | the last][tile]
+            const int f = (int)((byte - g.off_t) / kFrag);
+            const int gr = f < g.GT ? 0 : g.NG - 1, t = gr * g.GT + f % g.GT, m = 32 * t + l32;
+            if (m < g.Lc) {
+                const Iv iv = hw ? group_iv(g, gr) : tile_iv(g, t);
+                x = lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
+            }
+        }
+        v[i] = (__bf16)(float)x;
+    }
+    *(bf16x8*)(out + idx * 16) = v;
+}
+
+// ------------------------------------------------------------------------------------------
+// the kernel
+// ------------------------------------------------------------------------------------------
+
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed.
+__device__ __forceinline__ void wait_copies(int leaves)
+{
+    bool done = false;
+    static_for<20>([&](auto k) {
+        if (!done && leaves == k.value) {
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * k.value) : "memory");
+            done = true;
+        }
+    });
+    if (!done) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+
+// Four consecutive rows of 16 columns, transposed: lane i of 16 gets column i.  Each lane names the 8 bytes
+// (row lane/4, columns 4 (lane%4) ..) that it fetches.
+__device__ __forceinline__ s16x4 read_tr(const char* p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p); }
+
+__device__ __forceinline__ bf16x8 join(s16x4 a, s16x4 b)
+{
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+__device__ __forceinline__ uint32_t pack2(float a, float b)
+{
+    f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ u32x2 pack4(f32x4 a) { return u32x2{pack2(a[0], a[1]), pack2(a[2], a[3])}; }
+
+// NK: leaves per exact window; NLO: 16-row steps of it with a second part; TPW: tiles per computing wave and step.
+// SHIFTS: tables of exact entries repeat from tile to tile (NfGeom::shifts) and stay in registers.
+template <int NK, int NLO, int TPW, bool SHIFTS>
+__global__ __launch_bounds__((kCompute + kMovers) * 64, 2)
+void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* __restrict__ tap)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
+    char* const ring = smem;
+    char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8]
+    char* const cmom = mom + g.NLm * kVecB;          // [block]...
+    char* const cloc = cmom + g.NCp * kVecB;         // [group]...
+    char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]...
+    constexpr int GT = kCompute * TPW;
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int tph = g.d / kC;                        // tasks per head-tensor
+
+    // Task -> first row of the span at its channels.  The tasks of a head-tensor take consecutive slots of one XCD
+    // (workgroups are dealt round-robin to 8): they read the halves of the same 128-byte lines.
+    auto task_base = [&](int vb, int* ht_out, int* c0_out) -> char* {
+        const int full = g.hts / 8, per_group = 8 * tph;
+        int task = vb;
+        if (vb < full * per_group) {
+            const int grp = vb / per_group, local = vb - grp * per_group;
+            task = (grp * 8 + (local & 7)) * tph + (local >> 3);
+        }
+        const int ht = task / tph, c0 = (task - ht * tph) * kC;
+        const int slab = ht / g.hts_per_slab, r = ht - slab * g.hts_per_slab;
+        const int b = r / g.n_heads, h = r - b * g.n_heads;
+        *ht_out = ht;
+        *c0_out = c0;
+        return tab.base[slab] + ((long long)b * g.stride_batch + (long long)h * g.stride_head +
+                                 (long long)g.S * g.stride_token + c0) * 2;
+    };
+    const int tasks = g.hts * tph;
+    const uint32_t* const words = (const uint32_t*)(tables + g.off_w);      // tile words, then group words
+    const uint32_t rowb = (uint32_t)g.stride_token * 2;
+
+    // moments of leaves that do not exist stay zero: they meet zero table entries and must be finite
+    for (int i = threadIdx.x; i < (g.NLm + g.NCp + g.NGp + 2 * GT) * (kVecB / 16); i += (kCompute + kMovers) * 64)
+        ((u32x4*)mom)[i] = u32x4{0u, 0u, 0u, 0u};
+    lds_barrier();
+
+    if (wave >= kCompute) {
+        // ---- movers.  Leaves go out in the order in which they are used, 2 NL per task (moments, then results).  A leaf may
+        // take its slot when the steps that used the slot's previous leaf are over, i.e. behind the barrier after them.
+        const int mv = wave - kCompute;
+        const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
+        int issued = 0, slot = 0, leaf = 0, half = 0, vb = blockIdx.x, ht, c0;
+        const char* src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
+        auto issue_until = [&](int limit) {
+            while (issued < limit && vb < tasks) {
+                static_for<2>([&](auto i) {
+                    const int r0 = (mv * 2 + i.value) * 16;              // 16 rows per instruction
+                    const int row = min(leaf * kLeaf + r0 + (lane >> 2), g.n - 1);   // past the span: its last row again
+                    lds_dma16(ring_lds + slot * kSlotB + r0 * kRowB, src + (uint32_t)row * rowb);
+                });
+                ++issued;
+                if (++slot == g.R) slot = 0;
+                if (++leaf == g.NL) {
+                    leaf = 0;
+                    half ^= 1;
+                    if (!half) {
+                        vb += gridDim.x;
+                        if (vb < tasks) src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
+                    }
+                }
+            }
+        };
+        issue_until(g.R);
+        int p0 = 0;
+        for (int v = blockIdx.x; v < tasks; v += gridDim.x) {
+            for (int i = 0; i < g.NC; ++i) {
+                wait_copies(issued - (p0 + min(4 * i + 4, g.NL)));
+                lds_barrier();
+                issue_until(p0 + 4 * i + g.R);
+            }
+            lds_barrier();
+            p0 += g.NL;
+            issue_until(p0 + g.R);
+            lds_barrier();
+            for (int c = 0; c < g.NG; ++c) {
+                const int first = words[GT * c] & 255;
+                const int end = (int)(words[min(GT * c + GT, g.NT) - 1] & 255) + NK;
+                wait_copies(issued - (p0 + end));
+                lds_barrier();
+                issue_until(p0 + first + g.R);
+            }
+            p0 += g.NL;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return;
+    }
+
+    // ---- computing waves
+    const int l32 = lane & 31, hw = lane >> 5, l16 = lane & 15, g4 = lane >> 4;
+    // a fragment: uniform address plus the lane's offset, so that the address of each stays in scalar registers
+    const uint32_t lane_off = (uint32_t)lane * 16;
+    auto table = [&](int off) { return *(const bf16x8*)(tables + off + lane_off); };
+    // this lane's 8 bytes inside a 32-row (moments) or 16-row (results) step of a ring slot
+    const int tr32 = (8 * g4 + (l16 >> 2)) * kRowB + (l16 & 3) * 8;
+    const int tr16 = (8 * hw + (l16 >> 2)) * kRowB + (g4 & 1) * 32 + (l16 & 3) * 8;
+    const int vec16 = l16 * 16;                     // this lane's channel in a vector of 8 values (first 16 channels)
+    // the first 8 (of 16) result rows of a moment product, or all 16: 4 per lane, [vector][channel][8]
+    auto put8 = [&](char* vec, int h, f32x4 a) {
+        if (g4 < 2) *(u32x2*)(vec + h * 256 + vec16 + g4 * 8) = pack4(a);
+    };
+    auto put16 = [&](char* vec, int h, f32x4 a) { *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a); };
+
+    // Tables are fetched one step ahead of their use, into registers: their way from the L2 takes as long as a step.
+    bf16x8 ft[TPW][kNB];                             // neighbourhood of the next group whose local values are due
+    auto fetch_group = [&](int gr) {
+        static_for<TPW>([&](auto u) {
+            const int off = g.off_f + (gr * (GT / 2) + (wave & 1) * TPW + u.value) * kNB * kFrag;
+            static_for<kNB>([&](auto k) { ft[u.value][k.value] = table(off + k.value * kFrag); });
+        });
+    };
+    // local values of the tiles of group gr from the leaves around it
+    auto group_locals = [&](int gr) {
+        const int h = wave >> 1;
+        const char* src = mom + (4 * (int)words[g.NT + gr] + g4) * kVecB + h * 256 + vec16;
+        static_for<TPW>([&](auto u) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+            static_for<kNB>([&](auto k) {
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[u.value][k.value], *(const bf16x8*)(src + k.value * 4 * kVecB), a, 0, 0, 0);
+            });
+            put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u.value)) * kVecB, h, a);
+        });
+        fetch_group(gr + 1 < g.NG ? gr + 1 : 0);
+    };
+    auto block_moments = [&](int b, bf16x8 m) {
+        static_for<2>([&](auto h) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + (4 * b + g4) * kVecB + h.value * 256 + vec16), a, 0, 0, 0);
+            put8(cmom + b * kVecB, h.value, a);
+        });
+    };
+    bf16x8 vt[4];                                    // moments of the wave's next leaf
+    auto fetch_moments = [&](int leaf) {
+        const int off = g.off_v + (g.v_slots == 2 ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
+        static_for<4>([&](auto k) { vt[k.value] = table(off + k.value * kFrag); });
+    };
+    bf16x8 rt[TPW];                                  // results from local values
+    auto fetch_results = [&](bool last) {
+        static_for<TPW>([&](auto u) { rt[u.value] = table(g.off_t + ((last ? GT : 0) + wave + kCompute * u.value) * kFrag); });
+    };
+    fetch_group(0);
+    if (wave < g.NL) fetch_moments(wave);
+    fetch_results(g.NG == 1);
+
+    // table of exact entries of the tile at hand, in registers; replaced step by step when the next tile has another
+    constexpr int STEPS = 8 * NK + NLO, PER = STEPS * kFrag;
+    bf16x8 e[STEPS];
+    auto fetch_entries = [&](int slot) { static_for<STEPS>([&](auto k) { e[k.value] = table(slot * PER + k.value * kFrag); }); };
+    int cur_slot = -1;
+    if (wave < g.NT) {
+        cur_slot = (int)(words[wave] >> 16);
+        fetch_entries(cur_slot);
+    }
+
+    int slot0 = 0;                                   // ring slot of the task's next leaf 0
+    for (int vb = blockIdx.x; vb < tasks; vb += gridDim.x) {
+        int ht, c0;
+        char* const base = task_base(vb, &ht, &c0);
+        // ---- moments: a step is one block, a wave takes one leaf
+        {
+            int s = slot0 + wave;
+            if (s >= g.R) s -= g.R;
+            for (int i = 0; i < g.NC; ++i) {
+                const int leaf = 4 * i + wave;
+                const bool sum = i > 0 && wave == (i & 3);
+                bf16x8 bt;
+                if (sum) bt = table(g.off_m + (i - 1) * kFrag);
+                lds_barrier();
+                if (leaf < g.NL) {
+                    const char* x = ring + s * kSlotB + tr32;
+                    f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                    static_for<4>([&](auto k) {
+                        static_for<2>([&](auto h) {
+                            const char* p = x + k.value * 32 * kRowB + h.value * 32;
+                            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], join(read_tr(p), read_tr(p + 4 * kRowB)), a[h.value], 0, 0, 0);
+                        });
+                    });
+                    put8(mom + leaf * kVecB, 0, a[0]);
+                    put8(mom + leaf * kVecB, 1, a[1]);
+                    fetch_moments(leaf + 4 < g.NL ? leaf + 4 : wave);
+                }
+                if (sum) block_moments(i - 1, bt);
+                s += 4;
+                if (s >= g.R) s -= g.R;
+            }
+        }
+        // ---- local values of the groups from the blocks that are far from them; those of the first group's tiles.
+        // Units of two groups and 16 channels, 16 blocks at a time (or 4 in all).
+        bf16x8 ct[4];
+        const int quarter = wave >> 1, h = wave & 1, kst = g.NCp / 4;
+        auto fetch_far = [&](int mt, int k0) {
+            static_for<4>([&](auto k) { ct[k.value] = table(g.off_c + (mt * kst + min(k0 + k.value, kst - 1)) * kFrag); });
+        };
+        fetch_far(quarter, 0);
+        bf16x8 bt;
+        if (wave == 0) bt = table(g.off_m + (g.NC - 1) * kFrag);
+        lds_barrier();
+        if (wave == 0) block_moments(g.NC - 1, bt);
+        group_locals(0);
+        lds_barrier();
+        for (int mt = quarter; mt < g.NGp / 2; mt += 2) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+            for (int k0 = 0; k0 < kst; k0 += 4) {
+                const bool more = k0 + 4 < kst;
+                static_for<4>([&](auto k) {
+                    if (k0 + k.value < kst)
+                        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct[k.value], *(const bf16x8*)(cmom + (4 * (k0 + k.value) + g4) * kVecB + h * 256 + vec16), a, 0, 0, 0);
+                });
+                fetch_far(more ? mt : min(mt + 2, g.NGp / 2 - 1), more ? k0 + 4 : 0);
+            }
+            put16(cloc + 2 * mt * kVecB, h, a);
+        }
+
+        // ---- results
+        slot0 += g.NLr;                              // where leaf 0 of the second reading sits
+        if (slot0 >= g.R) slot0 -= g.R;
+        float* const tp = tap ? tap + ((g.tap_slab0 * g.hts_per_slab + ht) * (long long)g.Lc) * g.d + c0 : nullptr;
+        int first = 0, first_slot = slot0;           // first leaf of the step, its ring slot
+        for (int c = 0; c < g.NG; ++c) {
+            lds_barrier();
+            if (c + 1 < g.NG) group_locals(c + 1);
+            {
+                const int f = (int)(words[GT * c] & 255);
+                first_slot += f - first;
+                if (first_slot >= g.R) first_slot -= g.R;
+                first = f;
+            }
+#pragma unroll 1
+            for (int u = 0; u < TPW; ++u) {
+                const int tl = wave + kCompute * u, t = GT * c + tl;
+                if (t >= g.NT) break;
+                const uint32_t word = words[t];
+                const int leaf0 = (int)(word & 255), klo = (int)(word >> 8 & 255);
+                const char* x[NK];
+                {
+                    int s = first_slot + leaf0 - first;
+                    if (s >= g.R) s -= g.R;
+                    static_for<NK>([&](auto k) {
+                        x[k.value] = ring + s * kSlotB + tr16;
+                        if (++s == g.R) s = 0;
+                    });
+                }
+                f32x16 acc;
+                static_for<16>([&](auto r) { acc[r.value] = 0.f; });
+                {
+                    // far part: 8 local values of the tile and 8 of its group
+                    const bf16x8 far = *(const bf16x8*)((hw ? cloc + c * kVecB : loc + ((c & 1) * GT + tl) * kVecB) + l32 * 16);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, TPW > 1 && u ? rt[TPW - 1] : rt[0], acc, 0, 0, 0);
+                }
+                const int next = t + kCompute < g.NT ? t + kCompute : wave;     // the wave's next tile (of this task or the next)
+                const int next_slot = (int)(words[next] >> 16);
+                // 8 NK steps with the first parts, then NLO with the second; operands are read kAhead steps ahead, and the
+                // order is pinned: left alone the compiler reads the whole window first and runs out of registers
+                constexpr int kAhead = 3;
+                bf16x8 xf[kAhead + 1];
+                auto fetch_rows = [&](auto kc) {
+                    constexpr int K = decltype(kc)::value;
+                    const char* p;
+                    if constexpr (K < 8 * NK) {
+                        p = x[K / 8] + (K % 8) * 16 * kRowB;
+                    } else {
+                        const int ks = klo + K - 8 * NK;
+                        const char* xb = x[0];
+                        static_for<NK - 1>([&](auto q) { xb = ks >= 8 * (q.value + 1) ? x[q.value + 1] : xb; });
+                        p = xb + (ks & 7) * 16 * kRowB;
+                    }
+                    xf[K % (kAhead + 1)] = join(read_tr(p), read_tr(p + 4 * kRowB));
+                };
+                static_for<kAhead>([&](auto k) { fetch_rows(k); });
+                static_for<STEPS>([&](auto k) {
+                    constexpr int K = decltype(k)::value;
+                    if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[K % (kAhead + 1)], e[K], acc, 0, 0, 0);
+                    if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if (SHIFTS && next_slot != cur_slot) fetch_entries(next_slot);   // at the ends of the span only
+                cur_slot = next_slot;
+
+                // lane: result row 32 t + l32, channels 8 q + 4 hw + (0..3) in registers 4 q ..
+                const int m = 32 * t + l32;
+                static_for<16>([&](auto r) { acc[r.value] *= g.out_scale; });
+                uint32_t w[4][2];
+                static_for<4>([&](auto q) {
+                    w[q.value][0] = pack2(acc[4 * q.value], acc[4 * q.value + 1]);
+                    w[q.value][1] = pack2(acc[4 * q.value + 2], acc[4 * q.value + 3]);
+                });
+                // the half-waves trade: the lower keeps channels 0..15 of its row, the upper 16..31
+                u32x4 piece[2];
+                static_for<2>([&](auto q) {
+                    static_for<2>([&](auto e) {
+                        const auto s = __builtin_amdgcn_permlane32_swap(w[q.value][e.value], w[q.value + 2][e.value], false, false);
+                        piece[q.value][e.value] = s[0];
+                        piece[q.value][2 + e.value] = s[1];
+                    });
+                });
+                if (m < g.Lc) {
+                    char* o = base + (uint32_t)m * rowb + hw * 32;
+                    *(u32x4*)o = piece[0];
+                    *(u32x4*)(o + 16) = piece[1];
+                    if (tp) {
+                        float* f = tp + (long long)m * g.d + 4 * hw;
+                        static_for<16>([&](auto r) { f[8 * (r.value / 4) + r.value % 4] = acc[r.value]; });
+                    }
+                }
+            }
+            if (g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+        }
+        slot0 += g.NLr;
+        if (slot0 >= g.R) slot0 -= g.R;
+    }
+}
+
+}  // namespace
+
+// Everything that follows from the span alone.  False: no near/far form for this shape.
+bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
+{
+    if (head_dim % kC || Lc >= n || n < kNfMinSpan || n > 16384 || 5LL * Lc < n) return false;
+    NfGeom g;
+    memset(&g, 0, sizeof(g));
+    g.n = n; g.Lc = Lc; g.d = head_dim;
+    const double tile_rows = 32.0 * n / Lc;
+    // The window has 32 rows to spare on the left of a tile and must keep some 24 on its right: 2 leaves up to 72 rows
+    // per tile (ratios from 0.44), else 3 (ratios from 0.2: 160 rows, which also is what the second parts cover).
+    g.NK = tile_rows <= 72.0 ? 2 : 3;
+    g.NLO = g.NK == 2 ? 6 : 12;
+    g.GT = kCompute * (g.NK == 2 ? 2 : 1);
+    g.NL = (n + kLeaf - 1) / kLeaf;
+    if (g.NL < g.NK) g.NL = g.NK;
+    g.NC = (g.NL + 3) / 4;
+    g.NT = (Lc + 31) / 32;
+    g.NG = (g.NT + g.GT - 1) / g.GT;
+    g.NB = kNB;
+    g.NCp = g.NC <= 4 ? 4 : (g.NC + 15) / 16 * 16;
+    g.NGp = (g.NG + 1) / 2 * 2;
+    g.NLm = 4 * (g.NC > g.NB ? g.NC : g.NB);
+    // n = s Lc with s = 2 or 4: the exact entries repeat from tile to tile (every PT tiles) but for the reflected term,
+    // which then joins the far part except where the reflection of the window is close: at the ends.
+    const int s = n / Lc;
+    g.shifts = n % Lc == 0 && (s == 2 || s == 4);
+    if (g.shifts) {
+        g.PT = s == 2 ? 2 : 1;
+        g.tlo = 0;
+        g.thi = g.NT;
+        auto own = [&](int t) {                      // a table of its own: the reflection is close, or the span ends here
+            const TileAt at = tile_at(g, t);
+            const int a = 32 * t * s, b = a + 32 * s, wa = kLeaf * at.leaf0, wb = wa + kLeaf * g.NK;
+            return at.clamped || b > n || wb > n || a + wa < 64 || (n - b) + (n - wb) < 64;
+        };
+        while (g.tlo < g.thi && own(g.tlo)) ++g.tlo;
+        while (g.thi > g.tlo && own(g.thi - 1)) --g.thi;
+    }
+    const int slots = g.shifts ? g.PT + g.tlo + (g.NT - g.thi) : g.NT;
+    g.v_slots = g.shifts ? 2 : g.NL;
+    g.off_v = slots * (8 * g.NK + g.NLO) * kFrag;
+    g.off_m = g.off_v + g.v_slots * 4 * kFrag;
+    g.off_c = g.off_m + g.NC * kFrag;
+    g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * kFrag;
+    g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * kFrag;
+    g.off_w = g.off_t + 2 * g.GT * kFrag;
+    g.table_bytes = g.off_w + (g.NT + g.NG) * 4;
+    // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
+    const int fixed = (g.NLm + g.NCp + g.NGp + 2 * g.GT) * kVecB;
+    g.R = (kLdsBytes - fixed) / kSlotB;
+    int need = (int)std::floor((2 * g.GT - 1) * tile_rows / kLeaf) + 1 + g.NK;
+    const int turn = (int)std::floor((g.GT * tile_rows + 32.0) / kLeaf) + 2 + 4;   // from a task's last step to the next task's first
+    if (need < turn) need = turn;
+    if (need < 8) need = 8;
+    if (g.R < need) return false;
+    if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
+    g.NLr = g.NL % g.R;
+    *out = g;
+    return true;
+}
+
+hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st)
+{
+    const long long threads = g.off_w / 16 + g.NT + g.NG;
+    hipLaunchKernelGGL(k_nf_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, hipStream_t st)
+{
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const unsigned tasks = (unsigned)(g.hts * (g.d / kC)), resident = (unsigned)cus / 8 * 8;
+    const unsigned grid = resident >= 8 && tasks > resident ? resident : tasks;
+    const dim3 block((kCompute + kMovers) * 64);
+    if (g.NK == 2) {
+        if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+    } else {
+        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace freqkv
