@@ -138,7 +138,7 @@ struct NfGeom {
     int GT;                  // tiles (32 result rows) per step and group
     int NL, NC, NT, NG, NB;  // leaves, blocks of 4 leaves, tiles, groups, blocks of a group's neighbourhood
     int NLm, NCp, NGp;       // leaves, blocks, groups that LDS has room for
-    int R, NLr;              // ring slots; NL mod R
+    int R, NLr;              // ring slots; (NL - 1) mod R
     int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
     int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;

@@ -350,17 +350,23 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     const uint32_t* const words = (const uint32_t*)(tables + g.off_w);      // tile words, then group words
     const uint32_t rowb = (uint32_t)g.stride_token * 2;
 
+    auto wrap = [&](int s) { return s < 0 ? s + g.R : (s >= g.R ? s - g.R : s); };
+
     // moments of leaves that do not exist stay zero: they meet zero table entries and must be finite
     for (int i = threadIdx.x; i < (g.NLm + g.NCp + g.NGp + 2 * GT) * (kVecB / 16); i += (kCompute + kMovers) * 64)
         ((u32x4*)mom)[i] = u32x4{0u, 0u, 0u, 0u};
     lds_barrier();
 
     if (wave >= kCompute) {
-        // ---- movers.  Leaves go out in the order in which they are used, 2 NL per task (moments, then results).  A leaf may
-        // take its slot when the steps that used the slot's previous leaf are over, i.e. behind the barrier after them.
+        // ---- movers.  Leaves go out in the order in which they are used: last to first for the moments, then, since the
+        // first R of them are still in the ring, R, R+1, ... for the results (20 % of the second reading saved at 8188 rows, 40
+        // % at 4092).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
+        // the barrier after them.  Slots are taken in one direction round the ring on the way down and in the other on
+        // the way up, so that leaf l and leaf l + R share one.
         const int mv = wave - kCompute;
         const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
-        int issued = 0, slot = 0, leaf = 0, half = 0, vb = blockIdx.x, ht, c0;
+        int issued = 0, slot = 0, dir = 1, leaf = g.NL - 1, vb = blockIdx.x, ht, c0;
+        bool down = true;
         const char* src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
         auto issue_until = [&](int limit) {
             while (issued < limit && vb < tasks) {
@@ -370,37 +376,46 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     lds_dma16(ring_lds + slot * kSlotB + r0 * kRowB, src + (uint32_t)row * rowb);
                 });
                 ++issued;
-                if (++slot == g.R) slot = 0;
-                if (++leaf == g.NL) {
-                    leaf = 0;
-                    half ^= 1;
-                    if (!half) {
-                        vb += gridDim.x;
-                        if (vb < tasks) src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
-                    }
+                bool done = false;
+                if (down && leaf == 0) {
+                    if (g.NL >= g.R) dir = -dir;             // turn round: leaf R goes where leaf 0 is
+                    else slot = wrap(slot + dir);
+                    down = false;
+                    leaf = g.R;
+                    done = g.NL <= g.R;
+                } else {
+                    slot = wrap(slot + dir);
+                    leaf += down ? -1 : 1;
+                    done = !down && leaf == g.NL;
+                }
+                if (done) {
+                    down = true;
+                    leaf = g.NL - 1;
+                    vb += gridDim.x;
+                    if (vb < tasks) src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
                 }
             }
         };
-        issue_until(g.R);
+        const bool whole = g.NL < g.R;                       // the span and part of the next one fit the ring
+        issue_until(min(g.R, g.NL));
         int p0 = 0;
         for (int v = blockIdx.x; v < tasks; v += gridDim.x) {
-            for (int i = 0; i < g.NC; ++i) {
-                wait_copies(issued - (p0 + min(4 * i + 4, g.NL)));
+            for (int i = g.NC - 1; i >= 0; --i) {
+                wait_copies(issued - (p0 + g.NL - 4 * i));
                 lds_barrier();
-                issue_until(p0 + 4 * i + g.R);
+                issue_until(p0 + min((i == g.NC - 1 ? 0 : g.NL - 4 * (i + 1)) + g.R, g.NL));
             }
             lds_barrier();
-            p0 += g.NL;
-            issue_until(p0 + g.R);
+            if (whole) issue_until(p0 + g.R);
             lds_barrier();
-            for (int c = 0; c < g.NG; ++c) {
-                const int first = words[GT * c] & 255;
-                const int end = (int)(words[min(GT * c + GT, g.NT) - 1] & 255) + NK;
-                wait_copies(issued - (p0 + end));
+            for (int t = 0; t < g.NT; t += kCompute) {
+                const int first = words[t] & 255;
+                const int end = (int)(words[min(t + kCompute, g.NT) - 1] & 255) + NK;
+                wait_copies(issued - (p0 + g.NL + max(0, end - g.R)));
                 lds_barrier();
-                issue_until(p0 + first + g.R);
+                issue_until(p0 + (whole ? g.R : g.NL + first));
             }
-            p0 += g.NL;
+            p0 += g.NL + max(0, g.NL - g.R);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
@@ -422,25 +437,22 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto put16 = [&](char* vec, int h, f32x4 a) { *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a); };
 
     // Tables are fetched one step ahead of their use, into registers: their way from the L2 takes as long as a step.
-    bf16x8 ft[TPW][kNB];                             // neighbourhood of the next group whose local values are due
-    auto fetch_group = [&](int gr) {
-        static_for<TPW>([&](auto u) {
-            const int off = g.off_f + (gr * (GT / 2) + (wave & 1) * TPW + u.value) * kNB * kFrag;
-            static_for<kNB>([&](auto k) { ft[u.value][k.value] = table(off + k.value * kFrag); });
-        });
+    bf16x8 ft[kNB];                                  // neighbourhood of the tiles whose local values are due next
+    auto fetch_locals = [&](int gr, int u) {
+        const int off = g.off_f + (gr * (GT / 2) + (wave & 1) * TPW + u) * kNB * kFrag;
+        static_for<kNB>([&](auto k) { ft[k.value] = table(off + k.value * kFrag); });
     };
-    // local values of the tiles of group gr from the leaves around it
-    auto group_locals = [&](int gr) {
+    // local values of the tiles of group gr (one part in TPW of them) from the leaves around it
+    auto locals = [&](int gr, int u) {
         const int h = wave >> 1;
         const char* src = mom + (4 * (int)words[g.NT + gr] + g4) * kVecB + h * 256 + vec16;
-        static_for<TPW>([&](auto u) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            static_for<kNB>([&](auto k) {
-                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[u.value][k.value], *(const bf16x8*)(src + k.value * 4 * kVecB), a, 0, 0, 0);
-            });
-            put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u.value)) * kVecB, h, a);
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        static_for<kNB>([&](auto k) {
+            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], *(const bf16x8*)(src + k.value * 4 * kVecB), a, 0, 0, 0);
         });
-        fetch_group(gr + 1 < g.NG ? gr + 1 : 0);
+        put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u)) * kVecB, h, a);
+        if (u + 1 < TPW) fetch_locals(gr, u + 1);
+        else fetch_locals(gr + 1 < g.NG ? gr + 1 : 0, 0);
     };
     auto block_moments = [&](int b, bf16x8 m) {
         static_for<2>([&](auto h) {
@@ -458,8 +470,9 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto fetch_results = [&](bool last) {
         static_for<TPW>([&](auto u) { rt[u.value] = table(g.off_t + ((last ? GT : 0) + wave + kCompute * u.value) * kFrag); });
     };
-    fetch_group(0);
-    if (wave < g.NL) fetch_moments(wave);
+    const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
+    fetch_locals(0, 0);
+    if (top_leaf >= 0) fetch_moments(top_leaf);
     fetch_results(g.NG == 1);
 
     // table of exact entries of the tile at hand, in registers; replaced step by step when the next tile has another
@@ -472,19 +485,18 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         fetch_entries(cur_slot);
     }
 
-    int slot0 = 0;                                   // ring slot of the task's next leaf 0
+    int ptr = 0, dir = 1;                            // ring slot of the task's first leaf (the span's last), and where to go from there
     for (int vb = blockIdx.x; vb < tasks; vb += gridDim.x) {
         int ht, c0;
         char* const base = task_base(vb, &ht, &c0);
-        // ---- moments: a step is one block, a wave takes one leaf
+        // ---- moments, from the last leaf to the first: a step is one block, a wave takes one leaf
         {
-            int s = slot0 + wave;
-            if (s >= g.R) s -= g.R;
-            for (int i = 0; i < g.NC; ++i) {
+            int s = wrap(ptr + dir * (g.NL - 1 - 4 * (g.NC - 1) - wave));
+            for (int i = g.NC - 1; i >= 0; --i) {
                 const int leaf = 4 * i + wave;
-                const bool sum = i > 0 && wave == (i & 3);
+                const bool sum = i < g.NC - 1 && wave == (i & 3);
                 bf16x8 bt;
-                if (sum) bt = table(g.off_m + (i - 1) * kFrag);
+                if (sum) bt = table(g.off_m + (i + 1) * kFrag);
                 lds_barrier();
                 if (leaf < g.NL) {
                     const char* x = ring + s * kSlotB + tr32;
@@ -497,11 +509,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     });
                     put8(mom + leaf * kVecB, 0, a[0]);
                     put8(mom + leaf * kVecB, 1, a[1]);
-                    fetch_moments(leaf + 4 < g.NL ? leaf + 4 : wave);
+                    fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
                 }
-                if (sum) block_moments(i - 1, bt);
-                s += 4;
-                if (s >= g.R) s -= g.R;
+                if (sum) block_moments(i + 1, bt);
+                s = wrap(s + 4 * dir);
             }
         }
         // ---- local values of the groups from the blocks that are far from them; those of the first group's tiles.
@@ -513,10 +524,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         };
         fetch_far(quarter, 0);
         bf16x8 bt;
-        if (wave == 0) bt = table(g.off_m + (g.NC - 1) * kFrag);
+        if (wave == 0) bt = table(g.off_m);
         lds_barrier();
-        if (wave == 0) block_moments(g.NC - 1, bt);
-        group_locals(0);
+        if (wave == 0) block_moments(0, bt);
+        locals(0, 0);
         lds_barrier();
         for (int mt = quarter; mt < g.NGp / 2; mt += 2) {
             f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -531,33 +542,36 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             put16(cloc + 2 * mt * kVecB, h, a);
         }
 
-        // ---- results
-        slot0 += g.NLr;                              // where leaf 0 of the second reading sits
-        if (slot0 >= g.R) slot0 -= g.R;
+        if (TPW > 1) locals(0, 1);
+
+        // ---- results: a step is one tile per wave, a group TPW steps
+        int at_leaf = 0, at_slot = wrap(ptr + dir * g.NLr);      // a leaf and its slot (leaf 0: the last one read)
+        if (g.NL >= g.R) {                               // the next task goes on from here: where the leaf behind the last would be
+            ptr = wrap(ptr - dir);
+            dir = -dir;
+        } else {
+            ptr = wrap(ptr + dir * g.NL);
+        }
+        const int up = g.NL >= g.R ? dir : -dir;         // leaf l + 1 sits one slot further on this way
         float* const tp = tap ? tap + ((g.tap_slab0 * g.hts_per_slab + ht) * (long long)g.Lc) * g.d + c0 : nullptr;
-        int first = 0, first_slot = slot0;           // first leaf of the step, its ring slot
         for (int c = 0; c < g.NG; ++c) {
-            lds_barrier();
-            if (c + 1 < g.NG) group_locals(c + 1);
-            {
-                const int f = (int)(words[GT * c] & 255);
-                first_slot += f - first;
-                if (first_slot >= g.R) first_slot -= g.R;
-                first = f;
-            }
 #pragma unroll 1
             for (int u = 0; u < TPW; ++u) {
                 const int tl = wave + kCompute * u, t = GT * c + tl;
-                if (t >= g.NT) break;
+                if (GT * c + kCompute * u >= g.NT) break;        // nobody has a tile
+                lds_barrier();
+                if (c + 1 < g.NG) locals(c + 1, u);
+                if (t >= g.NT) continue;
                 const uint32_t word = words[t];
                 const int leaf0 = (int)(word & 255), klo = (int)(word >> 8 & 255);
+                at_slot = wrap(at_slot + up * (leaf0 - at_leaf));
+                at_leaf = leaf0;
                 const char* x[NK];
                 {
-                    int s = first_slot + leaf0 - first;
-                    if (s >= g.R) s -= g.R;
+                    int s = at_slot;
                     static_for<NK>([&](auto k) {
                         x[k.value] = ring + s * kSlotB + tr16;
-                        if (++s == g.R) s = 0;
+                        s = wrap(s + up);
                     });
                 }
                 f32x16 acc;
@@ -614,20 +628,24 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                         piece[q.value][2 + e.value] = s[1];
                     });
                 });
-                if (m < g.Lc) {
-                    char* o = base + (uint32_t)m * rowb + hw * 32;
-                    *(u32x4*)o = piece[0];
-                    *(u32x4*)(o + 16) = piece[1];
-                    if (tp) {
-                        float* f = tp + (long long)m * g.d + 4 * hw;
-                        static_for<16>([&](auto r) { f[8 * (r.value / 4) + r.value % 4] = acc[r.value]; });
-                    }
+                if (tp && m < g.Lc) {
+                    float* f = tp + (long long)m * g.d + 4 * hw;
+                    static_for<16>([&](auto r) { f[8 * (r.value / 4) + r.value % 4] = acc[r.value]; });
                 }
+                // then lanes 16 apart, so that one store writes whole 64-byte rows (16 of them): 4 % of the kernel's time
+                u32x4 row[2];
+                static_for<4>([&](auto e) {
+                    const auto s = __builtin_amdgcn_permlane16_swap(piece[0][e.value], piece[1][e.value], false, false);
+                    row[0][e.value] = s[0];
+                    row[1][e.value] = s[1];
+                });
+                static_for<2>([&](auto i) {
+                    const int mr = 32 * t + 16 * i.value + l16;
+                    if (mr < g.Lc) *(u32x4*)(base + (uint32_t)mr * rowb + g4 * 16) = row[i.value];
+                });
             }
             if (g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
         }
-        slot0 += g.NLr;
-        if (slot0 >= g.R) slot0 -= g.R;
     }
 }
 
@@ -683,13 +701,14 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
     const int fixed = (g.NLm + g.NCp + g.NGp + 2 * g.GT) * kVecB;
     g.R = (kLdsBytes - fixed) / kSlotB;
-    int need = (int)std::floor((2 * g.GT - 1) * tile_rows / kLeaf) + 1 + g.NK;
-    const int turn = (int)std::floor((g.GT * tile_rows + 32.0) / kLeaf) + 2 + 4;   // from a task's last step to the next task's first
+    int need = (int)std::floor((2 * kCompute - 1) * tile_rows / kLeaf) + 1 + g.NK;
+    const int turn = (int)std::floor((kCompute * tile_rows + 32.0) / kLeaf) + 2 + 4;   // from a task's last step to the next task's first
     if (need < turn) need = turn;
     if (need < 8) need = 8;
     if (g.R < need) return false;
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
-    g.NLr = g.NL % g.R;
+    if (g.NL < g.R && g.R < g.NL + 4) g.R = g.NL;    // no slots over for part of the next task only
+    g.NLr = (g.NL - 1) % g.R;
     *out = g;
     return true;
 }
