@@ -137,7 +137,7 @@ struct NfGeom {
     int NK, NLO;             // leaves (128 rows) per exact window; its 16-row steps that get a second bf16 part
     int GT;                  // tiles (32 result rows) per step and group
     int NL, NC, NT, NG, NB;  // leaves, blocks of 4 leaves, tiles, groups, blocks of a group's neighbourhood
-    int NLm, NCp, NGp;       // leaves, blocks, groups that LDS has room for
+    int NLm, NCp, NGp, NX;   // leaves, blocks, groups that LDS has room for; vectors where blocks and later tiles go
     int R, NLr;              // ring slots; (NL - 1) mod R
     int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
     int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf

@@ -66,6 +66,7 @@ constexpr int kVecB = kC * 8 * 2;         // bytes of 8 moments (or local values
 constexpr int kFrag = 1024;               // one operand fragment: 64 lanes x 8 bf16
 constexpr int kCompute = 4, kMovers = 4;  // waves
 constexpr int kNB = 3;                    // blocks of a group's neighbourhood: 512 rows or less, 128 to spare on both sides
+constexpr int kTabFrags = 6;              // table fragments kept in LDS
 constexpr int kLdsBytes = 160 * 1024;
 
 // Where the exact window of tile t starts (leaf), and whether the ends of the span shifted it.
@@ -291,6 +292,10 @@ __device__ __forceinline__ void wait_copies(int leaves)
     if (!done) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// A load that only some passes through a loop issue is awaited where it is issued: otherwise the compiler has to expect it in
+// flight at every use, and waits there for whatever is really in flight, copies and stores.
+__device__ __forceinline__ void pin(bf16x8& v) { asm volatile("" : "+v"(v)); }
+
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 
 // Four consecutive rows of 16 columns, transposed: lane i of 16 gets column i.  Each lane names the 8 bytes
@@ -320,9 +325,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
     char* const ring = smem;
     char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8]
-    char* const cmom = mom + g.NLm * kVecB;          // [block]...
-    char* const cloc = cmom + g.NCp * kVecB;         // [group]...
+    char* const cloc = mom + g.NLm * kVecB;          // [group]...
     char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]...
+    char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come
+    char* const ltab = loc + g.NX * kVecB;           // moments of an inner leaf (SHIFTS) | of an inner block | of the last block
     constexpr int GT = kCompute * TPW;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -353,8 +359,13 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto wrap = [&](int s) { return s < 0 ? s + g.R : (s >= g.R ? s - g.R : s); };
 
     // moments of leaves that do not exist stay zero: they meet zero table entries and must be finite
-    for (int i = threadIdx.x; i < (g.NLm + g.NCp + g.NGp + 2 * GT) * (kVecB / 16); i += (kCompute + kMovers) * 64)
+    for (int i = threadIdx.x; i < (g.NLm + g.NGp + g.NX) * (kVecB / 16); i += (kCompute + kMovers) * 64)
         ((u32x4*)mom)[i] = u32x4{0u, 0u, 0u, 0u};
+    for (int i = threadIdx.x; i < kTabFrags * 64; i += (kCompute + kMovers) * 64) {
+        const int f = i >> 6;
+        const int off = f < 4 ? g.off_v + f * kFrag : g.off_m + (f == 4 ? 0 : g.NC - 1) * kFrag;
+        ((u32x4*)ltab)[i] = *(const u32x4*)(tables + off + (i & 63) * 16);
+    }
     lds_barrier();
 
     if (wave >= kCompute) {
@@ -408,6 +419,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             lds_barrier();
             if (whole) issue_until(p0 + g.R);
             lds_barrier();
+            lds_barrier();
             for (int t = 0; t < g.NT; t += kCompute) {
                 const int first = words[t] & 255;
                 const int end = (int)(words[min(t + kCompute, g.NT) - 1] & 255) + NK;
@@ -422,39 +434,52 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     }
 
     // ---- computing waves
-    const int l32 = lane & 31, hw = lane >> 5, l16 = lane & 15, g4 = lane >> 4;
+    // What a lane derives from its index is recomputed in every step (an opaque copy of the index): kept across the steps, all
+    // of it together does not fit the register file, and a spilled register comes back behind the copies in flight.
+    int lane_v = lane;
+#define NF_LANE()                                                                                                       \
+    asm volatile("" : "+v"(lane_v));                                                                                    \
+    [[maybe_unused]] const int l32 = lane_v & 31, hw = lane_v >> 5, l16 = lane_v & 15, g4 = lane_v >> 4, vec16 = l16 * 16
     // a fragment: uniform address plus the lane's offset, so that the address of each stays in scalar registers
-    const uint32_t lane_off = (uint32_t)lane * 16;
-    auto table = [&](int off) { return *(const bf16x8*)(tables + off + lane_off); };
-    // this lane's 8 bytes inside a 32-row (moments) or 16-row (results) step of a ring slot
-    const int tr32 = (8 * g4 + (l16 >> 2)) * kRowB + (l16 & 3) * 8;
-    const int tr16 = (8 * hw + (l16 >> 2)) * kRowB + (g4 & 1) * 32 + (l16 & 3) * 8;
-    const int vec16 = l16 * 16;                     // this lane's channel in a vector of 8 values (first 16 channels)
+    auto table = [&](int off) { return *(const bf16x8*)(tables + off + (uint32_t)lane * 16); };
+    auto lds_table = [&](int f) { return *(const bf16x8*)(ltab + f * kFrag + lane * 16); };
     // the first 8 (of 16) result rows of a moment product, or all 16: 4 per lane, [vector][channel][8]
     auto put8 = [&](char* vec, int h, f32x4 a) {
+        NF_LANE();
         if (g4 < 2) *(u32x2*)(vec + h * 256 + vec16 + g4 * 8) = pack4(a);
     };
-    auto put16 = [&](char* vec, int h, f32x4 a) { *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a); };
+    auto put16 = [&](char* vec, int h, f32x4 a) {
+        NF_LANE();
+        *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a);
+    };
 
-    // Tables are fetched one step ahead of their use, into registers: their way from the L2 takes as long as a step.
+    // Tables that change from step to step are fetched one step ahead of their use, into registers: a load queues behind
+    // the copies in flight, a step's worth of time.  What does not change sits in LDS or stays in registers.
     bf16x8 ft[kNB];                                  // neighbourhood of the tiles whose local values are due next
     auto fetch_locals = [&](int gr, int u) {
         const int off = g.off_f + (gr * (GT / 2) + (wave & 1) * TPW + u) * kNB * kFrag;
         static_for<kNB>([&](auto k) { ft[k.value] = table(off + k.value * kFrag); });
     };
-    // local values of the tiles of group gr (one part in TPW of them) from the leaves around it
-    auto locals = [&](int gr, int u) {
-        const int h = wave >> 1;
-        const char* src = mom + (4 * (int)words[g.NT + gr] + g4) * kVecB + h * 256 + vec16;
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        static_for<kNB>([&](auto k) {
-            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], *(const bf16x8*)(src + k.value * 4 * kVecB), a, 0, 0, 0);
-        });
-        put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u)) * kVecB, h, a);
+    // Local values of the tiles of group gr (part u in TPW of them) from the leaves around it, in three parts: operands, product, result.
+    bf16x8 lf[kNB];
+    f32x4 la;
+    auto locals_read = [&](int block0) {
+        NF_LANE();
+        const char* src = mom + (4 * block0 + g4) * kVecB + (wave >> 1) * 256 + vec16;
+        static_for<kNB>([&](auto k) { lf[k.value] = *(const bf16x8*)(src + k.value * 4 * kVecB); });
+    };
+    auto locals_mac = [&](auto k) {
+        if constexpr (decltype(k)::value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
+        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf[k.value], la, 0, 0, 0);
+    };
+    auto locals_put = [&](int gr, int u) {
+        put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u)) * kVecB, wave >> 1, la);
         if (u + 1 < TPW) fetch_locals(gr, u + 1);
         else fetch_locals(gr + 1 < g.NG ? gr + 1 : 0, 0);
     };
-    auto block_moments = [&](int b, bf16x8 m) {
+    auto block_moments = [&](int b) {
+        NF_LANE();
+        const bf16x8 m = lds_table(b == g.NC - 1 ? 5 : 4);
         static_for<2>([&](auto h) {
             f32x4 a = {0.f, 0.f, 0.f, 0.f};
             a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + (4 * b + g4) * kVecB + h.value * 256 + vec16), a, 0, 0, 0);
@@ -463,16 +488,18 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     };
     bf16x8 vt[4];                                    // moments of the wave's next leaf
     auto fetch_moments = [&](int leaf) {
-        const int off = g.off_v + (g.v_slots == 2 ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
+        const int off = g.off_v + (SHIFTS ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
         static_for<4>([&](auto k) { vt[k.value] = table(off + k.value * kFrag); });
     };
     bf16x8 rt[TPW];                                  // results from local values
     auto fetch_results = [&](bool last) {
         static_for<TPW>([&](auto u) { rt[u.value] = table(g.off_t + ((last ? GT : 0) + wave + kCompute * u.value) * kFrag); });
+        static_for<TPW>([&](auto u) { pin(rt[u.value]); });
     };
     const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
     fetch_locals(0, 0);
     if (top_leaf >= 0) fetch_moments(top_leaf);
+    if (SHIFTS) static_for<4>([&](auto k) { pin(vt[k.value]); });
     fetch_results(g.NG == 1);
 
     // table of exact entries of the tile at hand, in registers; replaced step by step when the next tile has another
@@ -484,6 +511,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         cur_slot = (int)(words[wave] >> 16);
         fetch_entries(cur_slot);
     }
+    static_for<STEPS>([&](auto k) { pin(e[k.value]); });
 
     int ptr = 0, dir = 1;                            // ring slot of the task's first leaf (the span's last), and where to go from there
     for (int vb = blockIdx.x; vb < tasks; vb += gridDim.x) {
@@ -494,55 +522,76 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             int s = wrap(ptr + dir * (g.NL - 1 - 4 * (g.NC - 1) - wave));
             for (int i = g.NC - 1; i >= 0; --i) {
                 const int leaf = 4 * i + wave;
-                const bool sum = i < g.NC - 1 && wave == (i & 3);
-                bf16x8 bt;
-                if (sum) bt = table(g.off_m + (i + 1) * kFrag);
+                if (SHIFTS && leaf != top_leaf)
+                    static_for<4>([&](auto k) { vt[k.value] = lds_table(k.value); });
                 lds_barrier();
                 if (leaf < g.NL) {
-                    const char* x = ring + s * kSlotB + tr32;
+                    NF_LANE();
+                    const char* x = ring + s * kSlotB + (8 * g4 + (l16 >> 2)) * kRowB + (l16 & 3) * 8;   // the lane's 8 bytes of a 32-row step
                     f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                    bf16x8 xa[4][2];                         // all of the leaf first: one wait for LDS instead of eight
                     static_for<4>([&](auto k) {
                         static_for<2>([&](auto h) {
                             const char* p = x + k.value * 32 * kRowB + h.value * 32;
-                            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], join(read_tr(p), read_tr(p + 4 * kRowB)), a[h.value], 0, 0, 0);
+                            xa[k.value][h.value] = join(read_tr(p), read_tr(p + 4 * kRowB));
+                        });
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                    static_for<4>([&](auto k) {
+                        static_for<2>([&](auto h) {
+                            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], xa[k.value][h.value], a[h.value], 0, 0, 0);
                         });
                     });
                     put8(mom + leaf * kVecB, 0, a[0]);
                     put8(mom + leaf * kVecB, 1, a[1]);
-                    fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
+                    if (!SHIFTS) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
                 }
-                if (sum) block_moments(i + 1, bt);
+                if (i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
                 s = wrap(s + 4 * dir);
             }
         }
-        // ---- local values of the groups from the blocks that are far from them; those of the first group's tiles.
-        // Units of two groups and 16 channels, 16 blocks at a time (or 4 in all).
-        bf16x8 ct[4];
-        const int quarter = wave >> 1, h = wave & 1, kst = g.NCp / 4;
-        auto fetch_far = [&](int mt, int k0) {
-            static_for<4>([&](auto k) { ct[k.value] = table(g.off_c + (mt * kst + min(k0 + k.value, kst - 1)) * kFrag); });
-        };
-        fetch_far(quarter, 0);
-        bf16x8 bt;
-        if (wave == 0) bt = table(g.off_m);
-        lds_barrier();
-        if (wave == 0) block_moments(0, bt);
-        locals(0, 0);
-        lds_barrier();
-        for (int mt = quarter; mt < g.NGp / 2; mt += 2) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            for (int k0 = 0; k0 < kst; k0 += 4) {
-                const bool more = k0 + 4 < kst;
-                static_for<4>([&](auto k) {
-                    if (k0 + k.value < kst)
-                        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct[k.value], *(const bf16x8*)(cmom + (4 * (k0 + k.value) + g4) * kVecB + h * 256 + vec16), a, 0, 0, 0);
+        // ---- local values of the groups from the blocks that are far from them: units of two groups and 16 channels, 2 units
+        // of a wave and 4 x 4 blocks at a time, their tables requested together
+        {
+            NF_LANE();
+            const int q0 = wave >> 1, h = wave & 1, kst = g.NCp / 4, mts = g.NGp / 2;
+            bf16x8 ct[2][4];
+            auto fetch_far = [&](int m0, int k0) {
+                static_for<2>([&](auto j) {
+                    static_for<4>([&](auto k) {
+                        ct[j.value][k.value] = table(g.off_c + (min(m0 + 2 * j.value, mts - 1) * kst + min(k0 + k.value, kst - 1)) * kFrag);
+                    });
                 });
-                fetch_far(more ? mt : min(mt + 2, g.NGp / 2 - 1), more ? k0 + 4 : 0);
+            };
+            fetch_far(q0, 0);
+            lds_barrier();
+            if (wave == 0) block_moments(0);
+            lds_barrier();
+            for (int m0 = q0; m0 < mts; m0 += 4) {
+                f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                for (int k0 = 0; k0 < kst; k0 += 4) {
+                    static_for<4>([&](auto k) {
+                        if (k0 + k.value < kst) {
+                            bf16x8 c = {};                       // (behind the last block lies other data, perhaps not finite)
+                            if (4 * (k0 + k.value) + g4 < g.NC) c = *(const bf16x8*)(cmom + (4 * (k0 + k.value) + g4) * kVecB + h * 256 + vec16);
+                            static_for<2>([&](auto j) { a[j.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct[j.value][k.value], c, a[j.value], 0, 0, 0); });
+                        }
+                    });
+                    if (k0 + 4 < kst) fetch_far(m0, k0 + 4);
+                    else if (m0 + 4 < mts) fetch_far(m0 + 4, 0);
+                }
+                static_for<2>([&](auto j) {
+                    if (m0 + 2 * j.value < mts) put16(cloc + 2 * (m0 + 2 * j.value) * kVecB, h, a[j.value]);
+                });
             }
-            put16(cloc + 2 * mt * kVecB, h, a);
+            lds_barrier();
+            // ... and those of the first group's tiles
+            static_for<TPW>([&](auto u) {
+                locals_read((int)words[g.NT]);
+                static_for<kNB>([&](auto k) { locals_mac(k); });
+                locals_put(0, u.value);
+            });
         }
-
-        if (TPW > 1) locals(0, 1);
 
         // ---- results: a step is one tile per wave, a group TPW steps
         int at_leaf = 0, at_slot = wrap(ptr + dir * g.NLr);      // a leaf and its slot (leaf 0: the last one read)
@@ -554,100 +603,148 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         }
         const int up = g.NL >= g.R ? dir : -dir;         // leaf l + 1 sits one slot further on this way
         float* const tp = tap ? tap + ((g.tap_slab0 * g.hts_per_slab + ht) * (long long)g.Lc) * g.d + c0 : nullptr;
-        for (int c = 0; c < g.NG; ++c) {
-#pragma unroll 1
-            for (int u = 0; u < TPW; ++u) {
-                const int tl = wave + kCompute * u, t = GT * c + tl;
-                if (GT * c + kCompute * u >= g.NT) break;        // nobody has a tile
-                lds_barrier();
-                if (c + 1 < g.NG) locals(c + 1, u);
-                if (t >= g.NT) continue;
-                const uint32_t word = words[t];
-                const int leaf0 = (int)(word & 255), klo = (int)(word >> 8 & 255);
-                at_slot = wrap(at_slot + up * (leaf0 - at_leaf));
-                at_leaf = leaf0;
-                const char* x[NK];
-                {
-                    int s = at_slot;
-                    static_for<NK>([&](auto k) {
-                        x[k.value] = ring + s * kSlotB + tr16;
-                        s = wrap(s + up);
-                    });
-                }
-                f32x16 acc;
-                static_for<16>([&](auto r) { acc[r.value] = 0.f; });
-                {
-                    // far part: 8 local values of the tile and 8 of its group
-                    const bf16x8 far = *(const bf16x8*)((hw ? cloc + c * kVecB : loc + ((c & 1) * GT + tl) * kVecB) + l32 * 16);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, TPW > 1 && u ? rt[TPW - 1] : rt[0], acc, 0, 0, 0);
-                }
-                const int next = t + kCompute < g.NT ? t + kCompute : wave;     // the wave's next tile (of this task or the next)
-                const int next_slot = (int)(words[next] >> 16);
-                // 8 NK steps with the first parts, then NLO with the second; operands are read kAhead steps ahead, and the
-                // order is pinned: left alone the compiler reads the whole window first and runs out of registers
-                constexpr int kAhead = 3;
-                bf16x8 xf[kAhead + 1];
-                auto fetch_rows = [&](auto kc) {
-                    constexpr int K = decltype(kc)::value;
-                    const char* p;
-                    if constexpr (K < 8 * NK) {
-                        p = x[K / 8] + (K % 8) * 16 * kRowB;
-                    } else {
-                        const int ks = klo + K - 8 * NK;
-                        const char* xb = x[0];
-                        static_for<NK - 1>([&](auto q) { xb = ks >= 8 * (q.value + 1) ? x[q.value + 1] : xb; });
-                        p = xb + (ks & 7) * 16 * kRowB;
-                    }
-                    xf[K % (kAhead + 1)] = join(read_tr(p), read_tr(p + 4 * kRowB));
-                };
-                static_for<kAhead>([&](auto k) { fetch_rows(k); });
-                static_for<STEPS>([&](auto k) {
-                    constexpr int K = decltype(k)::value;
-                    if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[K % (kAhead + 1)], e[K], acc, 0, 0, 0);
-                    if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-                if (SHIFTS && next_slot != cur_slot) fetch_entries(next_slot);   // at the ends of the span only
-                cur_slot = next_slot;
 
-                // lane: result row 32 t + l32, channels 8 q + 4 hw + (0..3) in registers 4 q ..
-                const int m = 32 * t + l32;
-                static_for<16>([&](auto r) { acc[r.value] *= g.out_scale; });
-                uint32_t w[4][2];
-                static_for<4>([&](auto q) {
-                    w[q.value][0] = pack2(acc[4 * q.value], acc[4 * q.value + 1]);
-                    w[q.value][1] = pack2(acc[4 * q.value + 2], acc[4 * q.value + 3]);
-                });
-                // the half-waves trade: the lower keeps channels 0..15 of its row, the upper 16..31
-                u32x4 piece[2];
+        // Rounding and storing a tile, in 7 parts that the next tile's matrix instructions cover.  A lane has result row
+        // 32 t + l32, channels 8 q + 4 hw + (0..3) in registers 4 q ..; the half-waves trade, so that the lower keeps channels 0..15
+        // of its row and the upper 16..31, then lanes 16 apart, so that one store writes 16 whole 64-byte rows.
+        uint32_t w[4][2];
+        u32x4 row[2];
+        auto finish = [&](f32x16& acc, int t, auto part) {
+            NF_LANE();
+            constexpr int P = decltype(part)::value;
+            if constexpr (P < 4) {
+                static_for<4>([&](auto i) { acc[4 * P + i.value] *= g.out_scale; });
+                w[P][0] = pack2(acc[4 * P], acc[4 * P + 1]);
+                w[P][1] = pack2(acc[4 * P + 2], acc[4 * P + 3]);
+                if (tp && 32 * t + l32 < g.Lc) {
+                    float* f = tp + (long long)(32 * t + l32) * g.d + 8 * P + 4 * hw;
+                    static_for<4>([&](auto i) { f[i.value] = acc[4 * P + i.value]; });
+                }
+            } else if constexpr (P == 4) {
                 static_for<2>([&](auto q) {
-                    static_for<2>([&](auto e) {
-                        const auto s = __builtin_amdgcn_permlane32_swap(w[q.value][e.value], w[q.value + 2][e.value], false, false);
-                        piece[q.value][e.value] = s[0];
-                        piece[q.value][2 + e.value] = s[1];
+                    static_for<2>([&](auto i) {
+                        const auto s = __builtin_amdgcn_permlane32_swap(w[q.value][i.value], w[q.value + 2][i.value], false, false);
+                        row[q.value][i.value] = s[0];
+                        row[q.value][2 + i.value] = s[1];
                     });
                 });
-                if (tp && m < g.Lc) {
-                    float* f = tp + (long long)m * g.d + 4 * hw;
-                    static_for<16>([&](auto r) { f[8 * (r.value / 4) + r.value % 4] = acc[r.value]; });
-                }
-                // then lanes 16 apart, so that one store writes whole 64-byte rows (16 of them): 4 % of the kernel's time
-                u32x4 row[2];
-                static_for<4>([&](auto e) {
-                    const auto s = __builtin_amdgcn_permlane16_swap(piece[0][e.value], piece[1][e.value], false, false);
-                    row[0][e.value] = s[0];
-                    row[1][e.value] = s[1];
+            } else if constexpr (P == 5) {
+                static_for<4>([&](auto i) {
+                    const auto s = __builtin_amdgcn_permlane16_swap(row[0][i.value], row[1][i.value], false, false);
+                    row[0][i.value] = s[0];
+                    row[1][i.value] = s[1];
                 });
+            } else {
                 static_for<2>([&](auto i) {
                     const int mr = 32 * t + 16 * i.value + l16;
                     if (mr < g.Lc) *(u32x4*)(base + (uint32_t)mr * rowb + g4 * 16) = row[i.value];
                 });
             }
-            if (g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+        };
+        // One step of group c, part u: tile t into acc, while the tile before it (tp_, in prev; none: a tile past the end) is stored
+        // and the local values of the next group's tiles are computed.
+        // (Windows of 3 leaves leave no registers for that: there a tile is stored at the end of its own step.)
+        constexpr bool LATE = NK == 2;
+        int before = g.NT + kCompute;                    // a tile past the end: nothing to store
+        auto step = [&](int c, auto uc, f32x16& acc, f32x16& prev) {
+            constexpr int U = decltype(uc)::value;
+            const int tl = wave + kCompute * U, t = GT * c + tl;
+            // what the step needs to know of its tiles: scalar loads, ahead of the barrier (behind it their wait would take in LDS reads)
+            const bool more = c + 1 < g.NG;
+            const int next = t + kCompute < g.NT ? t + kCompute : wave;     // the wave's next tile (of this task or the next)
+            const uint32_t word = words[min(t, g.NT - 1)], next_word = words[min(next, g.NT - 1)];
+            const int block0 = (int)words[g.NT + min(c + 1, g.NG - 1)];
+            lds_barrier();
+            if (t >= g.NT) {                             // no tile for this wave in the last step of the task
+                if constexpr (LATE) static_for<7>([&](auto p) { finish(prev, before, p); });
+                before = t;
+                return;
+            }
+            const int leaf0 = (int)(word & 255), klo = (int)(word >> 8 & 255);
+            const int next_slot = (int)(next_word >> 16);
+            at_slot = wrap(at_slot + up * (leaf0 - at_leaf));
+            at_leaf = leaf0;
+            NF_LANE();
+            const int tr16 = (8 * hw + (l16 >> 2)) * kRowB + (g4 & 1) * 32 + (l16 & 3) * 8;    // the lane's 8 bytes of a 16-row step
+            const char* x[NK];
+            {
+                int s = at_slot;
+                static_for<NK>([&](auto k) {
+                    x[k.value] = ring + s * kSlotB + tr16;
+                    s = wrap(s + up);
+                });
+            }
+            // 8 NK matrix instructions with the first parts, then NLO with the second; operands are read kAhead instructions
+            // ahead, and the order is pinned: left alone the compiler reads the whole window first and runs out of registers
+            constexpr int kAhead = NK == 2 ? 4 : 2;
+            bf16x8 xf[kAhead + 1], far;
+            auto fetch_rows = [&](auto kc) {
+                constexpr int K = decltype(kc)::value;
+                const char* p;
+                if constexpr (K < 8 * NK) {
+                    p = x[K / 8] + (K % 8) * 16 * kRowB;
+                } else {
+                    const int ks = klo + K - 8 * NK;
+                    const char* xb = x[0];
+                    static_for<NK - 1>([&](auto q) { xb = ks >= 8 * (q.value + 1) ? x[q.value + 1] : xb; });
+                    p = xb + (ks & 7) * 16 * kRowB;
+                }
+                xf[K % (kAhead + 1)] = join(read_tr(p), read_tr(p + 4 * kRowB));
+            };
+            static_for<16>([&](auto r) { acc[r.value] = 0.f; });
+            static_for<kAhead>([&](auto k) { fetch_rows(k); });
+            static_for<STEPS>([&](auto k) {
+                constexpr int K = decltype(k)::value;
+                if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[K % (kAhead + 1)], e[K], acc, 0, 0, 0);
+                if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
+                if constexpr (K == 0) { if (more) locals_read(block0); }
+                if constexpr (K >= 7 && K < 7 + kNB) { if (more) locals_mac(IC<K - 7>{}); }
+                if constexpr (K == 17) { if (more) locals_put(c + 1, U); }
+                if constexpr (LATE) {
+                    if constexpr (K >= 2 && K < 6) finish(prev, before, IC<K - 2>{});
+                    if constexpr (K == 10) finish(prev, before, IC<4>{});
+                    if constexpr (K == 12) finish(prev, before, IC<5>{});
+                    if constexpr (K == 14) finish(prev, before, IC<6>{});
+                }
+                // far part: 8 local values of the tile and 8 of its group
+                if constexpr (K == STEPS - 5) far = *(const bf16x8*)((hw ? cloc + c * kVecB : loc + ((c & 1) * GT + tl) * kVecB) + l32 * 16);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, rt[U], acc, 0, 0, 0);
+            if (SHIFTS && next_slot != cur_slot) {           // at the ends of the span only
+                fetch_entries(next_slot);
+                static_for<STEPS>([&](auto k) { pin(e[k.value]); });
+            }
+            cur_slot = next_slot;
+            before = t;
+            if constexpr (!LATE) static_for<7>([&](auto p) { finish(acc, t, p); });
+        };
+        f32x16 acc0, acc1;
+        static_for<16>([&](auto r) { acc0[r.value] = 0.f; acc1[r.value] = 0.f; });
+        const int steps = (g.NT + kCompute - 1) / kCompute;
+        for (int i = 0; i < steps; i += 2) {
+            const int c = TPW == 2 ? i / 2 : i;
+            step(c, IC<0>{}, acc0, acc1);
+            if (TPW == 1 && g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+            if (i + 1 < steps) {
+                step(TPW == 2 ? c : c + 1, IC<TPW - 1>{}, acc1, acc0);
+                if (TPW == 1 && c + 1 >= g.NG - 2) fetch_results(c + 1 == g.NG - 2);
+            }
+            if (TPW == 2 && g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+        }
+        if constexpr (LATE) {
+            if (steps & 1) static_for<7>([&](auto p) { finish(acc0, before, p); });
+            else           static_for<7>([&](auto p) { finish(acc1, before, p); });
+        }
+        if (SHIFTS && top_leaf >= 0) {
+            fetch_moments(top_leaf);
+            static_for<4>([&](auto k) { pin(vt[k.value]); });
         }
     }
 }
+
+#undef NF_LANE
 
 }  // namespace
 
@@ -662,7 +759,7 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     // The window has 32 rows to spare on the left of a tile and must keep some 24 on its right: 2 leaves up to 72 rows
     // per tile (ratios from 0.44), else 3 (ratios from 0.2: 160 rows, which also is what the second parts cover).
     g.NK = tile_rows <= 72.0 ? 2 : 3;
-    g.NLO = g.NK == 2 ? 6 : 12;
+    g.NLO = g.NK == 2 ? 6 : (tile_rows <= 136.0 ? 10 : 12);
     g.GT = kCompute * (g.NK == 2 ? 2 : 1);
     g.NL = (n + kLeaf - 1) / kLeaf;
     if (g.NL < g.NK) g.NL = g.NK;
@@ -699,7 +796,8 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     g.off_w = g.off_t + 2 * g.GT * kFrag;
     g.table_bytes = g.off_w + (g.NT + g.NG) * 4;
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
-    const int fixed = (g.NLm + g.NCp + g.NGp + 2 * g.GT) * kVecB;
+    g.NX = g.NCp > 2 * g.GT ? g.NCp : 2 * g.GT;
+    const int fixed = (g.NLm + g.NGp + g.NX) * kVecB + kTabFrags * kFrag;
     g.R = (kLdsBytes - fixed) / kSlotB;
     int need = (int)std::floor((2 * kCompute - 1) * tile_rows / kLeaf) + 1 + g.NK;
     const int turn = (int)std::floor((kCompute * tile_rows + 32.0) / kLeaf) + 2 + 4;   // from a task's last step to the next task's first
@@ -732,9 +830,11 @@ hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tab
     if (g.NK == 2) {
         if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
         else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+    } else if (g.NLO == 10) {
+        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 10, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        else          hipLaunchKernelGGL((k_nearfar<3, 10, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
     } else {
-        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
-        else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
     }
     return hipGetLastError();
 }
