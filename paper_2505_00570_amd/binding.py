@@ -87,60 +87,61 @@ def lib_path() -> str:
 def load() -> C.CDLL:
     """Load libfreqkv.so; fails loudly when it has not been built (no fallback path exists)."""
     global _lib
-    if _lib is None:
-        if not os.path.exists(_LIB_PATH):
-            raise FreqKVError(E_HIP, f"{_LIB_PATH} is missing: run `python -m paper_2505_00570_amd.build`")
-        lib = C.CDLL(_LIB_PATH)
-        LP, PP = C.POINTER(Layout), C.POINTER(Plan)
-        lib.freqkv_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, PP]
-        lib.freqkv_plan.restype = C.c_int
-        lib.freqkv_compress.argtypes = [C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.c_int, C.c_int,
-                                        C.c_int, C.c_double, C.c_void_p]
-        lib.freqkv_compress.restype = C.c_int
-        lib.freqkv_attend_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(AttendPlan)]
-        lib.freqkv_attend_plan.restype = C.c_int
-        lib.freqkv_attend_decode.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
-                                             C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, C.c_void_p]
-        lib.freqkv_attend_decode.restype = C.c_int
-        lib.freqkv_attend_decode_noalloc.argtypes = lib.freqkv_attend_decode.argtypes
-        lib.freqkv_attend_decode_noalloc.restype = C.c_int
-        lib.freqkv_noalloc_scratch_bytes.argtypes = []
-        lib.freqkv_noalloc_scratch_bytes.restype = C.c_size_t
-        lib.freqkv_attend_decode_ragged.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
-                                                    C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_double,
-                                                    C.c_void_p]
-        lib.freqkv_attend_decode_ragged.restype = C.c_int
-        lib.freqkv_compress_ragged.argtypes = [C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.POINTER(C.c_int32),
-                                               C.POINTER(C.c_int32), C.c_int, C.c_int, C.c_double, C.c_void_p]
-        lib.freqkv_compress_ragged.restype = C.c_int
-        lib.freqkv_power_spectrum.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.c_int,
-                                              C.c_int, C.c_void_p]
-        lib.freqkv_power_spectrum.restype = C.c_int
-        lib.freqkv_attend_prefill_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(PrefillPlan)]
-        lib.freqkv_attend_prefill_plan.restype = C.c_int
-        lib.freqkv_attend_prefill.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
-                                              C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, C.c_void_p]
-        lib.freqkv_attend_prefill.restype = C.c_int
-        lib.freqkv_prepare.argtypes = [C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_double, C.c_void_p]
-        lib.freqkv_prepare.restype = C.c_int
-        lib.freqkv_status_string.argtypes = [C.c_int]
-        lib.freqkv_status_string.restype = C.c_char_p
-        lib.freqkv_last_error.argtypes = []
-        lib.freqkv_last_error.restype = C.c_char_p
-        lib.freqkv_shutdown.argtypes = []
-        lib.freqkv_shutdown.restype = None
-        lib.freqkv_version.argtypes = []
-        lib.freqkv_version.restype = C.c_int
-        lib.freqkv_profile_enable.argtypes = [C.c_int]
-        lib.freqkv_profile_enable.restype = C.c_int
-        lib.freqkv_profile_read.argtypes = [C.POINTER(Profile)]
-        lib.freqkv_profile_read.restype = C.c_int
-        lib.freqkv_calibrate_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_int, C.c_void_p,
-                                              C.POINTER(C.c_double)]
-        lib.freqkv_calibrate_copy.restype = C.c_int
-        lib.freqkv_calibrate_mfma.argtypes = [C.c_int, C.c_void_p, C.POINTER(C.c_double)]
-        lib.freqkv_calibrate_mfma.restype = C.c_int
-        _lib = lib
+    if _lib is not None:
+        return _lib
+    if not os.path.exists(_LIB_PATH):
+        raise FreqKVError(E_HIP, f"{_LIB_PATH} is missing: run `python -m paper_2505_00570_amd.build`")
+    lib = C.CDLL(_LIB_PATH)
+    LP, PP = C.POINTER(Layout), C.POINTER(Plan)
+    lib.freqkv_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, PP]
+    lib.freqkv_plan.restype = C.c_int
+    lib.freqkv_compress.argtypes = [C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.c_int, C.c_int,
+                                    C.c_int, C.c_double, C.c_void_p]
+    lib.freqkv_compress.restype = C.c_int
+    lib.freqkv_attend_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(AttendPlan)]
+    lib.freqkv_attend_plan.restype = C.c_int
+    lib.freqkv_attend_decode.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
+                                         C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, C.c_void_p]
+    lib.freqkv_attend_decode.restype = C.c_int
+    lib.freqkv_attend_decode_noalloc.argtypes = lib.freqkv_attend_decode.argtypes
+    lib.freqkv_attend_decode_noalloc.restype = C.c_int
+    lib.freqkv_noalloc_scratch_bytes.argtypes = []
+    lib.freqkv_noalloc_scratch_bytes.restype = C.c_size_t
+    lib.freqkv_attend_decode_ragged.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
+                                                C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_double,
+                                                C.c_void_p]
+    lib.freqkv_attend_decode_ragged.restype = C.c_int
+    lib.freqkv_compress_ragged.argtypes = [C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.POINTER(C.c_int32),
+                                           C.POINTER(C.c_int32), C.c_int, C.c_int, C.c_double, C.c_void_p]
+    lib.freqkv_compress_ragged.restype = C.c_int
+    lib.freqkv_power_spectrum.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, LP, C.c_int, C.c_int, C.c_int,
+                                          C.c_int, C.c_void_p]
+    lib.freqkv_power_spectrum.restype = C.c_int
+    lib.freqkv_attend_prefill_plan.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(PrefillPlan)]
+    lib.freqkv_attend_prefill_plan.restype = C.c_int
+    lib.freqkv_attend_prefill.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, LP,
+                                          C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double, C.c_void_p]
+    lib.freqkv_attend_prefill.restype = C.c_int
+    lib.freqkv_prepare.argtypes = [C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_double, C.c_void_p]
+    lib.freqkv_prepare.restype = C.c_int
+    lib.freqkv_status_string.argtypes = [C.c_int]
+    lib.freqkv_status_string.restype = C.c_char_p
+    lib.freqkv_last_error.argtypes = []
+    lib.freqkv_last_error.restype = C.c_char_p
+    lib.freqkv_shutdown.argtypes = []
+    lib.freqkv_shutdown.restype = None
+    lib.freqkv_version.argtypes = []
+    lib.freqkv_version.restype = C.c_int
+    lib.freqkv_profile_enable.argtypes = [C.c_int]
+    lib.freqkv_profile_enable.restype = C.c_int
+    lib.freqkv_profile_read.argtypes = [C.POINTER(Profile)]
+    lib.freqkv_profile_read.restype = C.c_int
+    lib.freqkv_calibrate_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_int, C.c_void_p,
+                                          C.POINTER(C.c_double)]
+    lib.freqkv_calibrate_copy.restype = C.c_int
+    lib.freqkv_calibrate_mfma.argtypes = [C.c_int, C.c_void_p, C.POINTER(C.c_double)]
+    lib.freqkv_calibrate_mfma.restype = C.c_int
+    _lib = lib
     return _lib
 
 
@@ -300,24 +301,22 @@ def calibrate_mfma(iters: int = 20000, stream=None) -> float:
 
 # ---------------------------------------------------------------- marshalling helpers
 
+# Called five times per attention call: plain integers (ctypes converts them itself), tensors first.
 def _dev_ptr(x):
     if x is None:
         return None
-    if isinstance(x, int):
-        return C.c_void_p(x)
+    ptr = getattr(x, "data_ptr", None)
+    if ptr is not None:
+        return ptr()
     if isinstance(x, C.Array):
         return C.cast(x, C.c_void_p)
-    if hasattr(x, "data_ptr"):
-        return C.c_void_p(x.data_ptr())
-    return x
+    return x                                       # a device address
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        return None
-    if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)          # torch.cuda.Stream
+    if stream is None or isinstance(stream, int):
+        return stream
+    return stream.cuda_stream                      # torch.cuda.Stream
 
 
 def layout_for(k, *, batch_dim: bool = True, workspace=None, tap=None, flags: int = 0) -> Layout:

@@ -262,12 +262,28 @@ struct BasisKey {
 struct BasisEntry {
     void* ptr = nullptr;
     size_t bytes = 0;
-    hipEvent_t ready = nullptr;   // recorded after the build kernel; other streams wait on it
+    hipEvent_t ready = nullptr;   // recorded after the build kernel; streams wait on it until it has been seen to be over
+    bool built = false;
     void* host = nullptr;         // pinned staging copy of tables built on the host (kept until shutdown)
 };
 
 std::mutex g_mu;
 std::map<BasisKey, BasisEntry> g_basis;
+
+// Orders `st` behind the build of a cached table.  Once the build is known to be over there is nothing to wait for, and
+// calls spare themselves a wait in the stream (held g_mu; a capturing stream keeps to what may be recorded).
+hipError_t order_after(BasisEntry& e, hipStream_t st)
+{
+    if (e.built) return hipSuccess;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t err = hipStreamIsCapturing(st, &cap);
+    if (err == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        err = hipEventQuery(e.ready);
+        if (err == hipSuccess) { e.built = true; return hipSuccess; }
+        (void)hipGetLastError();                      // not ready
+    }
+    return hipStreamWaitEvent(st, e.ready, 0);
+}
 
 freqkv_status_t get_basis(const Shape& sh, const Geom& g, int rescale, hipStream_t st, void** out)
 {
@@ -315,7 +331,7 @@ freqkv_status_t get_basis(const Shape& sh, const Geom& g, int rescale, hipStream
         it = g_basis.emplace(key, e).first;
     } else {
         // built on some stream earlier: order this stream after the build
-        HIP_TRY(hipStreamWaitEvent(st, it->second.ready, 0));
+        HIP_TRY(order_after(it->second, st));
     }
     *out = it->second.ptr;
     return FREQKV_OK;
@@ -348,14 +364,45 @@ freqkv_status_t get_nf_tables(const Shape& sh, hipStream_t st, const char** out)
         }
         it = g_basis.emplace(key, e).first;
     } else {
-        HIP_TRY(hipStreamWaitEvent(st, it->second.ready, 0));
+        HIP_TRY(order_after(it->second, st));
     }
     *out = (const char*)it->second.ptr;
     return FREQKV_OK;
 }
 
 // ---------------------------------------------------------------- attention: shape, plan, rotary table
-constexpr long long kAttendTargetWgs = 768;   // 256 compute units x 3 resident workgroups
+// Row chunks per KV head.  All workgroups of a launch are resident at once (up to 3 or 4 per compute unit), so what counts is
+// how many sit on the busiest of the 256 compute units.  Measured (bf16, d = 128, 4 query heads per workgroup): one
+// workgroup alone on its compute unit takes 0.0239 us per row, several of them 0.020 each; 0.013 with 2 heads, 0.0095 with
+// 1, in proportion to d; a workgroup's set-up adds 1 us for each on the compute unit, merging 1.5 us and 0.04 for each
+// chunk; nothing runs faster than the rows come from memory (6 TB/s).  Tried are the chunk counts that fill 1, 2, 3 or 4
+// workgroups per compute unit; the fewest chunks within 1 us of the best are taken.  8 KV heads x 6147 rows: 28 chunks 15.1
+// us (22 chunks 16.5, 16 19.5); 128 x 8192: 4 chunks 86 us (6: 97); 32 heads of 1 query head x 4096: 8 chunks 16.1 us (22: 17.5).
+int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int rows, int min_rows)
+{
+    constexpr int kCus = 256, kMost = 4;
+    const double per_row = (GT == 4 ? 0.0239 : GT == 2 ? 0.013 : 0.0095) * d / 128.0 * (elem == 4 ? 1.3 : 1.0);
+    const double floor_us = 2.0 * units * rows * d * elem / 6e6;
+    int ns_of[kMost + 1];
+    double cost[kMost + 1], best = 1e30;
+    for (int r = 0; r <= kMost; ++r) {
+        long long ns = r ? (long long)kCus * r / wgs : 1;
+        if (ns > rows / min_rows) ns = rows / min_rows;
+        if (ns < 1) ns = 1;
+        const double chunk = (double)rows / ns;
+        const double deep = std::ceil((double)wgs * ns / kCus);
+        double us = chunk * deep * per_row * (deep > 1 ? 0.83 : 1.0);
+        // compute units with fewer workgroups than the busiest leave half of their share of the bandwidth unused
+        const double least = floor_us * (0.5 + 0.5 * deep * kCus / ((double)wgs * ns));
+        if (us < least) us = least;
+        ns_of[r] = (int)ns;
+        cost[r] = us + deep + (ns > 1 ? 1.5 + 0.04 * ns : 0.0);
+        if (cost[r] < best) best = cost[r];
+    }
+    for (int r = 0; r <= kMost; ++r)
+        if (cost[r] <= best + 1.0) return ns_of[r];
+    return 1;
+}
 
 struct AttShape {
     int d, n_q, n_kv, G, GT, batch, n_layers, cur_len, elem;
@@ -391,15 +438,9 @@ freqkv_status_t check_attend(const freqkv_layout_t* L, int n_q, int n_kv, int d,
     a.batch = L->batch; a.n_layers = L->n_layers; a.cur_len = cur_len;
     a.elem = L->dtype == FREQKV_BF16 ? 2 : 4;
     a.units_all = units;
-    // Row chunks: a chunk is at least eight loop steps long; the number of chunks is chosen so that the
-    // workgroups fill the resident slots of the 256 compute units about once (few, long workgroups: the
-    // set-up and the final combination of a workgroup cost several microseconds).
     const int step = attend_row_step(d);
     const long long wgs_per_split = units * (a.G / a.GT);
-    long long ns = (kAttendTargetWgs + wgs_per_split / 2) / wgs_per_split;
-    long long ns_max = cur_len / (16 * step);
-    if (ns > ns_max) ns = ns_max;
-    if (ns < 1) ns = 1;
+    long long ns = attend_chunks(wgs_per_split, units, a.GT, d, a.elem, cur_len, 2 * step);
     long long chunk = round_up(((long long)cur_len + ns - 1) / ns, 2 * step);
     ns = ((long long)cur_len + chunk - 1) / chunk;
     if (wgs_per_split * ns > (1LL << 30)) return FREQKV_E_UNSUPPORTED;
@@ -444,7 +485,7 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
         }
         it = g_rope.emplace(key, e).first;
     } else {
-        HIP_TRY(hipStreamWaitEvent(st, it->second.ready, 0));
+        HIP_TRY(order_after(it->second, st));
     }
     *out = (RopeEntry*)it->second.ptr;
     return FREQKV_OK;
@@ -1049,7 +1090,7 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         ProfSpan sp;
         sp.a = sp.b = nullptr;
         if (!use_static) HIP_TRY(prof_begin(st, 3, &sp));       // timing events are created per call: not here
-        HIP_TRY(launch_attend_partial(tab, g, a.elem, qp, rt, pa, pm, st));
+        HIP_TRY(launch_attend_partial(tab, g, a.elem, qp, rt, pa, pm, op, lse ? lse + head0 : nullptr, st));
         if (!use_static) HIP_TRY(prof_end(st, &sp));
         HIP_TRY(launch_attend_merge(g, a.elem, pa, pm, op, lse ? lse + head0 : nullptr, st));
     }

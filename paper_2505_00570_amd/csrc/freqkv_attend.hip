@@ -15,7 +15,7 @@
 //                     max / sum / weighted-V state (online softmax).  cos/sin of the row position are
 //                     advanced by a fixed rotation per step from seeds computed with an fp64 range
 //                     reduction, so no table is read in the loop.
-//   k_attend_merge    combines the per-chunk states of a query head and writes the output row.
+//   k_attend_merge    combines the per-chunk states of a query head and writes the output row (not needed for one chunk).
 #include "freqkv_internal.h"
 
 namespace freqkv {
@@ -83,6 +83,14 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x)
     return x;
 }
 
+// Two adjacent results, rounded once.
+__device__ __forceinline__ void store2(uint16_t* p, float a, float b)
+{
+    f32x2 v = {a, b};
+    *(uint32_t*)p = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ void store2(float* p, float a, float b) { *(f32x2*)p = f32x2{a, b}; }
+
 // cos and sin of pos * theta.  The product, its reduction to [-pi/4, pi/4] plus a quadrant and the two
 // short Taylor sums (truncation below 2e-9 on that interval) are all in fp64; the results are rounded once.
 struct CosSin { float c, s; };
@@ -138,11 +146,15 @@ __global__ void k_rope_table(RopeEntry* rt, int d, double base, int step)
 // T: storage type of the cache, the query and the output (uint16_t = bfloat16 bits, or float).
 // D: head_dim.  GT: query heads handled together (they share the KV head).  P: rotary pairs per lane
 // (the lane owns channels P*l .. P*l+P-1 and their partners D/2 + P*l ..), so D/(2P) lanes share a row.
-template <typename T, int D, int GT, int P>
+// ONE: there is one chunk only; the workgroup writes the results itself and no merge kernel runs.
+// (Two forms were built and taken back.  Merging by the workgroup that arrives last: the arrival counter of a launch is an
+// atomic of many workgroups on 8 XCDs, 28 us for 16 chunks of 8 heads against 19.5 with the second kernel.  Workgroups of
+// eight waves: half as many loop steps, but the same time, 14.9 against 15.1 us at 32 chunks.)
+template <typename T, int D, int GT, int P, bool ONE>
 __global__ __launch_bounds__(kWaves * 64, attend_min_waves(sizeof(T), GT, P))
 void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict__ q,
                       const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
-                      float* __restrict__ part_ml)
+                      float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse)
 {
     constexpr int LPR = D / (2 * P);       // lanes per cache row
     constexpr int RPW = 64 / LPR;          // rows per wave per load
@@ -351,7 +363,8 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
     __syncthreads();
     static_for<GT>([&](auto gg) {
         constexpr int gi = decltype(gg)::value;
-        float M = fmaxf(fmaxf(xm[gi][0], xm[gi][1]), fmaxf(xm[gi][2], xm[gi][3]));
+        float M = xm[gi][0];
+        static_for<kWaves - 1>([&](auto w) { M = fmaxf(M, xm[gi][w.value + 1]); });
         float f = exp2_fast(m[gi] - M);
         m[gi] = M;
         float ls = lsum[gi] * f;
@@ -376,51 +389,105 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
     });
     __syncthreads();
 
-    // 2. sum over the parked lane groups; one (query head, channel) per thread and pass
-    const long long pidx = ((long long)unit * g.G + g0) * g.n_split + split;   // + gi * n_split below
-    for (int idx = tid; idx < GT * D; idx += kWaves * 64) {
-        int gi = idx / D;
-        int ch = idx - gi * D;
-        float sum = 0.f;
+    // 2. sum over the parked lane groups; two channels of one query head per thread and pass
+    auto group_ml = [&](int gi, float* M, float* L) {
+        *M = xm[gi][0];
+        *L = xl[gi][0];
+        static_for<kWaves - 1>([&](auto w) { *M = fmaxf(*M, xm[gi][w.value + 1]); *L += xl[gi][w.value + 1]; });
+    };
+    const long long head0 = (long long)unit * g.G + g0;                        // dense query head of gi = 0
+    const long long pidx = head0 * g.n_split + split;                          // + gi * n_split below
+    for (int idx = tid; idx < GT * D / 2; idx += kWaves * 64) {
+        const int gi = idx / (D / 2), ch = 2 * (idx - gi * (D / 2));
+        f32x2 sum = {0.f, 0.f};
 #pragma unroll
-        for (int hs = 0; hs < HSLOTS; ++hs) sum += red[(hs * GT + gi) * D + ch];
-        part_acc[(pidx + (long long)gi * g.n_split) * D + ch] = sum;
+        for (int hs = 0; hs < HSLOTS; ++hs) sum += *(const f32x2*)(red + (hs * GT + gi) * D + ch);
+        if constexpr (ONE) {
+            float M, L;
+            group_ml(gi, &M, &L);
+            store2(out + (head0 + gi) * D + ch, sum[0] / L, sum[1] / L);
+        } else {
+            *(f32x2*)(part_acc + (pidx + (long long)gi * g.n_split) * D + ch) = sum;
+        }
     }
     if (tid < GT) {
-        float M = fmaxf(fmaxf(xm[tid][0], xm[tid][1]), fmaxf(xm[tid][2], xm[tid][3]));
-        float Lsum = xl[tid][0] + xl[tid][1] + xl[tid][2] + xl[tid][3];
-        float* ml = part_ml + (pidx + (long long)tid * g.n_split) * 2;
-        ml[0] = M;
-        ml[1] = Lsum;
+        float M, L;
+        group_ml(tid, &M, &L);
+        f32x2* ml = (f32x2*)(part_ml + (pidx + (long long)tid * g.n_split) * 2);
+        if constexpr (ONE) {
+            if (lse) lse[head0 + tid] = 0.6931471805599453f * (M + log2f(L));
+        } else {
+            *ml = f32x2{M, L};
+        }
     }
 }
 
-// One workgroup of D threads per query head: merge the chunk states, normalise, store.
-template <typename T>
-__global__ void k_attend_merge(const AttGeom g, const float* __restrict__ part_acc,
-                               const float* __restrict__ part_ml, T* __restrict__ out,
-                               float* __restrict__ lse)
+// One workgroup per query head merges the chunk states, normalises, stores.  D/2 threads cover the channels (two each), and
+// kMergeShare such groups of threads take the chunks in turn: what the kernel costs is the chain of loads, so that all of them
+// should be in flight (22 chunks of one head: 8.2 us with one load behind the other, see the figures in k_attend_partial).
+constexpr int kMergeShare = 4;
+template <typename T, int D>
+__global__ __launch_bounds__(kMergeShare * D / 2)
+void k_attend_merge(const AttGeom g, const float* __restrict__ part_acc, const float* __restrict__ part_ml,
+                    T* __restrict__ out, float* __restrict__ lse)
 {
+    constexpr int NT = kMergeShare * D / 2, NWV = NT / 64;
+    __shared__ float wm[NWV], wl[NWV], sh_w[NT];
+    __shared__ f32x2 sh_sum[kMergeShare][D / 2];
     const long long head = blockIdx.x;                    // (layer, batch, query head), dense
-    const int ch = threadIdx.x;
-    const float* ml = part_ml + head * g.n_split * 2;
-    float M = kMinusBig;
-    for (int sp = 0; sp < g.n_split; ++sp) M = fmaxf(M, ml[2 * sp]);
-    float o = 0.f, L = 0.f;
-    for (int sp = 0; sp < g.n_split; ++sp) {
-        float f = exp2_fast(ml[2 * sp] - M);
-        L = fmaf(ml[2 * sp + 1], f, L);
-        o = fmaf(part_acc[(head * g.n_split + sp) * g.d + ch], f, o);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int pr = tid % (D / 2), part = tid / (D / 2);
+    const f32x2* ml = (const f32x2*)(part_ml + head * g.n_split * 2);
+    const float* acc = part_acc + head * g.n_split * D + 2 * pr;
+    f32x2 sum = {0.f, 0.f};
+    float M = kMinusBig, L = 0.f;
+    for (int s0 = 0; s0 < g.n_split; s0 += NT) {          // NT chunks at a time (one pass but for tiny head counts)
+        const int here = min(NT, g.n_split - s0);
+        // the accumulators of the first chunks are requested ahead of everything else
+        f32x2 v[8] = {};
+        static_for<8>([&](auto i) {
+            if (i.value * kMergeShare < here)
+                v[i.value] = *(const f32x2*)(acc + (long long)min(s0 + part + i.value * kMergeShare, g.n_split - 1) * D);
+        });
+        const f32x2 mine = tid < here ? ml[s0 + tid] : f32x2{kMinusBig, 0.f};
+        float mx = mine[0];
+        for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        if (lane == 0) wm[wave] = mx;
+        __syncthreads();
+        float Mn = M;
+        static_for<NWV>([&](auto w) { Mn = fmaxf(Mn, wm[w.value]); });
+        const float w = tid < here ? exp2_fast(mine[0] - Mn) : 0.f;
+        sh_w[tid] = w;
+        float ls = mine[1] * w;
+        for (int o = 1; o < 64; o <<= 1) ls += __shfl_xor(ls, o);
+        if (lane == 0) wl[wave] = ls;
+        __syncthreads();
+        const float f = exp2_fast(M - Mn);
+        L *= f;
+        static_for<NWV>([&](auto i) { L += wl[i.value]; });
+        sum[0] *= f;
+        sum[1] *= f;
+        M = Mn;
+        for (int sp0 = part; sp0 < here; sp0 += 8 * kMergeShare) {
+            if (sp0 != part)
+                static_for<8>([&](auto i) { v[i.value] = *(const f32x2*)(acc + (long long)min(s0 + sp0 + i.value * kMergeShare, g.n_split - 1) * D); });
+            static_for<8>([&](auto i) {
+                const int sp = sp0 + i.value * kMergeShare;
+                if (sp >= here) return;
+                const float x = sh_w[sp];
+                sum[0] = fmaf(v[i.value][0], x, sum[0]);
+                sum[1] = fmaf(v[i.value][1], x, sum[1]);
+            });
+        }
+        __syncthreads();
     }
-    float r = o / L;
-    if constexpr (sizeof(T) == 2) {
-        f32x2 v = {r, 0.f};
-        bf16x2 bv = __builtin_convertvector(v, bf16x2);
-        out[head * g.d + ch] = (T)(__builtin_bit_cast(uint32_t, bv) & 0xffffu);
-    } else {
-        out[head * g.d + ch] = r;
+    sh_sum[part][pr] = sum;
+    __syncthreads();
+    if (part == 0) {
+        static_for<kMergeShare - 1>([&](auto i) { sum[0] += sh_sum[i.value + 1][pr][0]; sum[1] += sh_sum[i.value + 1][pr][1]; });
+        store2(out + head * D + 2 * pr, sum[0] / L, sum[1] / L);
+        if (lse && pr == 0) lse[head] = 0.6931471805599453f * (M + log2f(L));
     }
-    if (lse && ch == 0) lse[head] = 0.6931471805599453f * (M + log2f(L));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -434,16 +501,31 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, int D, int P>
-static hipError_t launch_partial_p(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt,
-                                   float* part_acc, float* part_ml, hipStream_t st)
+template <typename T, int D, int GT, bool ONE>
+static void launch_partial_o(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
+                             float* part_ml, void* out, float* lse, hipStream_t st)
 {
-    dim3 grid((unsigned)(g.units * g.n_split), (unsigned)(g.G / g.GT));
-    dim3 block(kWaves * 64);
+    const dim3 grid((unsigned)(g.units * g.n_split), (unsigned)(g.G / g.GT));
+    hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE>), grid, dim3(kWaves * 64), 0, st, tab, g, (const T*)q, rt,
+                       part_acc, part_ml, (T*)out, lse);
+}
+
+template <typename T, int D, int GT>
+static void launch_partial_g(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
+                             float* part_ml, void* out, float* lse, hipStream_t st)
+{
+    if (g.n_split == 1) launch_partial_o<T, D, GT, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+    else                launch_partial_o<T, D, GT, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+}
+
+template <typename T, int D>
+static hipError_t launch_partial_d(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
+                                   float* part_ml, void* out, float* lse, hipStream_t st)
+{
     switch (g.GT) {
-        case 4: hipLaunchKernelGGL((k_attend_partial<T, D, 4, P>), grid, block, 0, st, tab, g, (const T*)q, rt, part_acc, part_ml); break;
-        case 2: hipLaunchKernelGGL((k_attend_partial<T, D, 2, P>), grid, block, 0, st, tab, g, (const T*)q, rt, part_acc, part_ml); break;
-        case 1: hipLaunchKernelGGL((k_attend_partial<T, D, 1, P>), grid, block, 0, st, tab, g, (const T*)q, rt, part_acc, part_ml); break;
+        case 4: launch_partial_g<T, D, 4>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
+        case 2: launch_partial_g<T, D, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
+        case 1: launch_partial_g<T, D, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -451,38 +533,45 @@ static hipError_t launch_partial_p(const SlabTable& tab, const AttGeom& g, const
 
 template <typename T>
 static hipError_t launch_partial_t(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt,
-                                   float* part_acc, float* part_ml, hipStream_t st)
+                                   float* part_acc, float* part_ml, void* out, float* lse, hipStream_t st)
 {
     if (g.P != attend_pairs_per_lane(g.d)) return hipErrorInvalidValue;
     switch (g.d) {
-        case 64:  return launch_partial_p<T, 64, attend_pairs_per_lane(64)>(tab, g, q, rt, part_acc, part_ml, st);
-        case 128: return launch_partial_p<T, 128, attend_pairs_per_lane(128)>(tab, g, q, rt, part_acc, part_ml, st);
-        case 256: return launch_partial_p<T, 256, attend_pairs_per_lane(256)>(tab, g, q, rt, part_acc, part_ml, st);
+        case 64:  return launch_partial_d<T, 64>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+        case 128: return launch_partial_d<T, 128>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+        case 256: return launch_partial_d<T, 256>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
         default:  return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_attend_partial(const SlabTable& tab, const AttGeom& g, int elem_bytes, const void* q,
-                                 const RopeEntry* rt, float* part_acc, float* part_ml, hipStream_t st)
+                                 const RopeEntry* rt, float* part_acc, float* part_ml, void* out, float* lse, hipStream_t st)
 {
     if (g.units < 1 || g.n_split < 1 || g.chunk < 1 || g.cur_len < 1) return hipErrorInvalidValue;
     if ((long long)(g.n_split - 1) * g.chunk >= g.cur_len) return hipErrorInvalidValue;   // no chunk beyond the longest cache
     if ((long long)g.n_split * g.chunk < g.cur_len) return hipErrorInvalidValue;          // chunks cover the cache
     if (g.G % g.GT) return hipErrorInvalidValue;
     if (g.chunk % (kUnroll * attend_row_step(g.d))) return hipErrorInvalidValue;
-    return elem_bytes == 2 ? launch_partial_t<uint16_t>(tab, g, q, rt, part_acc, part_ml, st)
-                           : launch_partial_t<float>(tab, g, q, rt, part_acc, part_ml, st);
+    return elem_bytes == 2 ? launch_partial_t<uint16_t>(tab, g, q, rt, part_acc, part_ml, out, lse, st)
+                           : launch_partial_t<float>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
 }
 
 hipError_t launch_attend_merge(const AttGeom& g, int elem_bytes, const float* part_acc, const float* part_ml,
                                void* out, float* lse, hipStream_t st)
 {
-    dim3 grid((unsigned)((long long)g.units * g.G));
-    dim3 block(g.d);
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(k_attend_merge<uint16_t>, grid, block, 0, st, g, part_acc, part_ml, (uint16_t*)out, lse);
-    else
-        hipLaunchKernelGGL(k_attend_merge<float>, grid, block, 0, st, g, part_acc, part_ml, (float*)out, lse);
+    if (g.n_split < 2) return hipSuccess;                 // the one chunk's workgroup has written the results
+    const dim3 grid((unsigned)((long long)g.units * g.G)), block(kMergeShare * g.d / 2);
+    auto launch = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        if (elem_bytes == 2) hipLaunchKernelGGL((k_attend_merge<uint16_t, D>), grid, block, 0, st, g, part_acc, part_ml, (uint16_t*)out, lse);
+        else                 hipLaunchKernelGGL((k_attend_merge<float, D>), grid, block, 0, st, g, part_acc, part_ml, (float*)out, lse);
+    };
+    switch (g.d) {
+        case 64:  launch(IC<64>{}); break;
+        case 128: launch(IC<128>{}); break;
+        case 256: launch(IC<256>{}); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

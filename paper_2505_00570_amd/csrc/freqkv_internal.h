@@ -196,7 +196,7 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st);
 // tab.base[2*i] / [2*i+1]: K / V slab of the pass's i-th layer.  part_acc: [units*G][n_split][d] fp32,
 // part_ml: [units*G][n_split][2] fp32 (running maximum in the exp2 domain, sum of weights).
 hipError_t launch_attend_partial(const SlabTable& tab, const AttGeom& g, int elem_bytes, const void* q,
-                                 const RopeEntry* rt, float* part_acc, float* part_ml, hipStream_t st);
+                                 const RopeEntry* rt, float* part_acc, float* part_ml, void* out, float* lse, hipStream_t st);
 hipError_t launch_attend_merge(const AttGeom& g, int elem_bytes, const float* part_acc, const float* part_ml,
                                void* out, float* lse, hipStream_t st);
 
