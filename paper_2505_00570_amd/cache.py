@@ -40,6 +40,12 @@ class CompressedKVCache:
         self.can_prefill = rc == fk.OK
         if self.can_prefill:
             need = max(need, pp.workspace_bytes)
+            # chunks shorter than the cache are cut along the keys as well, which takes room of its own
+            q_len = 1
+            while q_len < self.capacity:
+                _, pp = fk.attend_prefill_plan(self.layout, self.n_q_heads, n_heads, head_dim, self.capacity, q_len)
+                need = max(need, pp.workspace_bytes)
+                q_len *= 2
         self.workspace = torch.empty(need, dtype=torch.uint8, device=device)
         self.layout.workspace = self.workspace.data_ptr()
         self.layout.workspace_bytes = self.workspace.numel()

@@ -491,6 +491,57 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
     return FREQKV_OK;
 }
 
+// Cos/sin of every row position for chunk-wise attention (512 bytes per row at d = 128), cached per (device, d, base) like the
+// other tables: 5 us of every short call otherwise.  A call that needs more rows than the table has gets a new one of the next
+// power of two; the old one stays until shutdown, since enqueued work and captured graphs may still read it.  While a
+// stream is being captured nothing is allocated, and neither are tables beyond kCsMaxRows rows or kCsMaxTables in number:
+// such calls fill the table into their own workspace.
+constexpr int kCsMaxRows = 1 << 16;
+constexpr size_t kCsMaxTables = 16;
+struct CsTable { RopeKey key; int rows; BasisEntry e; };
+std::vector<CsTable> g_cs;
+
+freqkv_status_t get_cs_table(int rows, int d, double base, hipStream_t st, float2* ws, const float2** out)
+{
+    const int rope = base > 0.0;
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> lock(g_mu);
+        for (CsTable& t : g_cs)
+            if (t.key.device == dev && t.key.d == d && t.key.base == base && t.rows >= rows) {
+                HIP_TRY(order_after(t.e, st));
+                *out = (const float2*)t.e.ptr;
+                return FREQKV_OK;
+            }
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(st, &cap));
+        if (cap == hipStreamCaptureStatusNone && rows <= kCsMaxRows && g_cs.size() < kCsMaxTables) {
+            CsTable t{RopeKey{dev, d, base}, 4096, BasisEntry()};
+            while (t.rows < rows) t.rows *= 2;
+            t.e.bytes = (size_t)t.rows * (d / 2) * sizeof(float2);
+            hipError_t err = hipMalloc(&t.e.ptr, t.e.bytes);
+            if (err == hipSuccess) {
+                err = launch_prefill_cs((float2*)t.e.ptr, t.rows, d, rope ? base : 1.0, rope, st);
+                if (err == hipSuccess) err = hipEventCreateWithFlags(&t.e.ready, hipEventDisableTiming);
+                if (err == hipSuccess) err = hipEventRecord(t.e.ready, st);
+                if (err != hipSuccess) {
+                    set_error("cos/sin table build", err);
+                    (void)hipFree(t.e.ptr);
+                    return FREQKV_E_HIP;
+                }
+                g_cs.push_back(t);
+                *out = (const float2*)t.e.ptr;
+                return FREQKV_OK;
+            }
+            (void)hipGetLastError();                      // no memory for it: as above, in the workspace
+        }
+    }
+    HIP_TRY(launch_prefill_cs(ws, rows, d, rope ? base : 1.0, rope, st));
+    *out = ws;
+    return FREQKV_OK;
+}
+
 // ---------------------------------------------------------------- static scratch of the entry point that allocates nothing
 // freqkv_attend_decode_noalloc keeps the per-chunk softmax states and the rotary table here instead of in a
 // caller's workspace and a cached allocation.  Every device the library runs on holds its own copy of the
@@ -1179,8 +1230,25 @@ namespace {
 struct PrefillShape {
     AttShape a;
     int q_len, q_pad, key_tiles, layers_per_pass;
-    size_t off_kr, off_vt, workspace_bytes;
+    size_t off_kr, off_vt, off_part, workspace_bytes, workspace_min;
+    size_t part_bytes;          // states of one part of the key range
+    int n_split;                // parts of the key range, given a workspace of workspace_bytes
 };
+
+// Parts that the key tiles of every workgroup are cut into when there are fewer workgroups than compute units (one holds
+// one workgroup).  A tile takes a workgroup 0.73 us; a part's states (16.6 KB per task) are written and read at about 7
+// TB/s; merging adds 4 us.  301 queries on 5001 rows, 8 KV heads: 40 workgroups x 157 tiles, 115 us in one part.
+int prefill_splits(long long wgs, long long tasks, int tiles)
+{
+    const double tile_us = 0.73;
+    int best = 1;
+    double best_us = std::ceil(wgs / 256.0) * tiles * tile_us;
+    for (int s = 2; s <= 32 && s * 4 <= tiles; ++s) {
+        const double us = std::ceil((double)wgs * s / 256.0) * std::ceil((double)tiles / s) * tile_us + 4.0 + (double)tasks * s * 16640.0 * 2.0 / 7e6;
+        if (us < 0.97 * best_us) { best = s; best_us = us; }
+    }
+    return best;
+}
 
 freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d, int cur_len, int q_len,
                               PrefillShape* out)
@@ -1200,7 +1268,12 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     size_t kv_bytes = (size_t)units * p.key_tiles * 32 * d * 2;
     p.off_kr = cs_bytes;
     p.off_vt = p.off_kr + kv_bytes;
-    p.workspace_bytes = p.off_vt + kv_bytes;
+    p.off_part = p.off_vt + kv_bytes;
+    p.workspace_min = p.off_part;
+    const long long tasks = units * p.a.G * (p.q_pad / 32);
+    p.part_bytes = (size_t)tasks * (32 * d * sizeof(float) + 32 * sizeof(float2));
+    p.n_split = prefill_splits(units * ((p.a.G * (p.q_pad / 32) + 7) / 8), tasks, p.key_tiles);
+    p.workspace_bytes = p.workspace_min + (p.n_split > 1 ? p.n_split * p.part_bytes : 0);
     *out = p;
     return FREQKV_OK;
 }
@@ -1248,11 +1321,19 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
             bases[(size_t)2 * l + kv] = bp;
         }
     }
-    if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < p.workspace_bytes)
+    if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < p.workspace_min)
         return FREQKV_E_WORKSPACE;
+    // a workspace sized for a longer chunk may hold fewer parts than would be best, or no room for any
+    int n_split = p.n_split;
+    while (n_split > 1 && p.workspace_min + n_split * p.part_bytes > L.workspace_bytes) --n_split;
+    const int split_tiles = (p.key_tiles + n_split - 1) / n_split;
+    n_split = (p.key_tiles + split_tiles - 1) / split_tiles;
 
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)L.workspace;
+    const float2* cs = nullptr;
+    rc = get_cs_table(cur_len, a.d, rope_base, st, (float2*)ws, &cs);
+    if (rc < 0) return rc;
     const int upl = a.batch * a.n_kv;
     for (int l0 = 0; l0 < a.n_layers; l0 += p.layers_per_pass) {
         int layers = a.n_layers - l0 < p.layers_per_pass ? a.n_layers - l0 : p.layers_per_pass;
@@ -1264,7 +1345,7 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
         g.d = a.d; g.G = a.G; g.n_kv = a.n_kv;
         g.units = layers * upl; g.units_per_layer = upl;
         g.cur_len = cur_len; g.q_len = q_len; g.q_pad = p.q_pad; g.q_blocks = p.q_pad / 32;
-        g.key_tiles = p.key_tiles; g.rope = rope_base > 0.0;
+        g.key_tiles = p.key_tiles; g.n_split = n_split; g.split_tiles = split_tiles;
         g.stride_batch = L.stride_batch; g.stride_head = L.stride_head; g.stride_token = L.stride_token;
         g.qscale = (float)(1.4426950408889634 / std::sqrt((double)a.d));
         const long long head0 = (long long)l0 * upl * a.G;
@@ -1272,12 +1353,14 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
         char* op = (char*)out + head0 * q_len * a.d * a.elem;
         ProfSpan sp;
         HIP_TRY(prof_begin(st, 0, &sp));
-        HIP_TRY(launch_prefill_prepare(tab, g, rope_base > 0.0 ? rope_base : 1.0, (float2*)ws,
-                                       (_Float16*)(ws + p.off_kr), (_Float16*)(ws + p.off_vt), st));
+        HIP_TRY(launch_prefill_prepare(tab, g, cs, (_Float16*)(ws + p.off_kr), (_Float16*)(ws + p.off_vt), st));
         HIP_TRY(prof_end(st, &sp));
         HIP_TRY(prof_begin(st, 3, &sp));
-        HIP_TRY(launch_attend_prefill(g, (const _Float16*)(ws + p.off_kr), (const _Float16*)(ws + p.off_vt), qp,
-                                      (const float2*)ws, op, lse ? lse + head0 * q_len : nullptr, st));
+        const long long tasks = (long long)g.units * a.G * g.q_blocks;
+        float* part_acc = n_split > 1 ? (float*)(ws + p.off_part) : nullptr;
+        float2* part_ml = n_split > 1 ? (float2*)(part_acc + tasks * n_split * 32 * a.d) : nullptr;
+        HIP_TRY(launch_attend_prefill(g, (const _Float16*)(ws + p.off_kr), (const _Float16*)(ws + p.off_vt), qp, cs, op,
+                                      lse ? lse + head0 * q_len : nullptr, part_acc, part_ml, st));
         HIP_TRY(prof_end(st, &sp));
     }
     return FREQKV_OK;
@@ -1307,6 +1390,15 @@ void freqkv_shutdown(void)
         (void)hipFree(kv.second.ptr);
     }
     g_rope.clear();
+    for (CsTable& t : g_cs) {
+        if (hipSetDevice(t.key.device) != hipSuccess) continue;
+        if (t.e.ready) {
+            (void)hipEventSynchronize(t.e.ready);
+            (void)hipEventDestroy(t.e.ready);
+        }
+        (void)hipFree(t.e.ptr);
+    }
+    g_cs.clear();
     for (auto& sp : g_prof_spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
     g_prof_spans.clear();
     if (have_dev) (void)hipSetDevice(cur);

@@ -212,16 +212,19 @@ struct PrefillGeom {
     int q_pad;             // q_len rounded up to 32
     int q_blocks;          // q_pad / 32
     int key_tiles;         // ceil(cur_len / 32)
-    int rope;
+    int n_split;           // parts that the key tiles of a workgroup are cut into, of split_tiles tiles each
+    int split_tiles;
     long long stride_batch, stride_head, stride_token;   // elements
     float qscale;          // log2(e) / sqrt(d)
 };
 
-// cs: [cur_len][d/2] (cos, sin); Kr, Vt: [units][key_tiles] tiles of 32 keys x d fp16 in fragment order.
-// q: dense [units*G][q_len][d] bf16, rotated inside the attention kernel.
-hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, double rope_base, float2* cs,
-                                  _Float16* Kr, _Float16* Vt, hipStream_t st);
+// cs: [rows][d/2] (cos, sin).
+hipError_t launch_prefill_cs(float2* cs, int rows, int d, double rope_base, int rope, hipStream_t st);
+// Kr, Vt: [units][key_tiles] tiles of 32 keys x d fp16 in fragment order.
+hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, const float2* cs, _Float16* Kr, _Float16* Vt, hipStream_t st);
+// q: dense [units*G][q_len][d] bf16, rotated inside the attention kernel.  part_acc, part_ml (n_split > 1): per (task, part)
+// 32 x d fp32 and 32 x (reference point, sum).
 hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
-                                 void* out, float* lse, hipStream_t st);
+                                 void* out, float* lse, float* part_acc, float2* part_ml, hipStream_t st);
 
 }  // namespace freqkv

@@ -6,14 +6,14 @@
 // row index when they are read; queries take the one of p_i (closing paragraph of Sec. 3.4).
 //
 // Unlike the one-token case this is a dense contraction (q_len x cur_len x d per head, twice), so it runs
-// on the matrix cores, as a streaming-softmax attention kernel.  Three small passes put the cached operands
+// on the matrix cores, as a streaming-softmax attention kernel.  Small passes put the cached operands
 // into MFMA fragment order first (all fp16: a bf16 cache value is exact in fp16, and the rotated keys and
 // queries keep 11 significant bits instead of 8):
-//   k_prefill_cs      cos/sin of (row * theta_j) for every cached row, fp64 angle reduction, fp32 table
-//   k_prefill_prep_k  Kr = rotate(K) in tiles of 32 keys, [tile][group of 8 channels][key][8]
-//   k_prefill_prep_v  Vt = V transposed in tiles of 32 keys, [tile][channel block][k-step][half][channel][8 keys],
-//                     keys permuted so that a softmax tile, as the matrix core leaves it in registers, is
-//                     already the second operand of the weighted sum
+//   k_prefill_cs      cos/sin of (row * theta_j) for every cached row, fp64 angle reduction, fp32 table (kept by the library)
+//   k_prefill_prep    Kr = rotate(K) in tiles of 32 keys, [tile][group of 8 channels][key][8]; Vt = V transposed in
+//                     tiles of 32 keys, [tile][channel block][k-step][half][channel][8 keys], keys permuted so that a
+//                     softmax tile, as the matrix core leaves it in registers, is already the second operand of
+//                     the weighted sum
 // and k_attend_prefill first builds, per wave, Qr = rotate(q) * log2(e)/sqrt(d) for its 32 queries in
 // registers (once), then computes S^T = Kr Qr^T for 32 keys x 32 queries at a time, the running softmax per
 // query (a query is a column, so its sum is an in-lane reduction plus one exchange between the two
@@ -27,6 +27,7 @@ namespace {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -94,82 +95,82 @@ __global__ void k_prefill_cs(float2* __restrict__ cs, int rows, int d, double ba
     cs[idx] = o;
 }
 
-// One thread per (unit, key row, group of 8 rotary pairs): rotate and store in fragment order; the group of
-// the lower half and its partner group of the upper half come from the same two 16-byte loads.
-// Kr tile layout (fp16): [group of 8 channels g8 = 0..15][key 0..31][8].
-__global__ void k_prefill_prep_k(const SlabTable tab, const PrefillGeom g, const float2* __restrict__ cs,
-                                 _Float16* __restrict__ Kr)
-{
-    long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    constexpr int half = kD / 2;
-    constexpr int pgn = half / 8;                             // groups of 8 pairs per row
-    long long total = (long long)g.units * g.key_tiles * kKeyTile * pgn;
-    if (idx >= total) return;
-    int pg = (int)(idx % pgn);
-    long long rest = idx / pgn;
-    int p = (int)(rest % ((long long)g.key_tiles * kKeyTile));
-    int unit = (int)(rest / ((long long)g.key_tiles * kKeyTile));
-    half8 lo8 = {}, up8 = {};                                 // rows beyond cur_len are zero
-    if (p < g.cur_len) {
-        int layer = unit / g.units_per_layer;
-        int rem = unit - layer * g.units_per_layer;
-        int b = rem / g.n_kv, kvh = rem - b * g.n_kv;
-        const uint16_t* row = (const uint16_t*)tab.base[2 * layer] + (long long)b * g.stride_batch +
-                              (long long)kvh * g.stride_head + (long long)p * g.stride_token;
-        const int j0 = pg * 8;                                // first rotary pair of this group
-        const u32x4 lo = *(const u32x4*)(row + j0), up = *(const u32x4*)(row + half + j0);
-        const float2* c = cs + (long long)p * half + j0;
-        for (int i = 0; i < 4; ++i) {
-            float a0 = bf16_lo(lo[i]), a1 = bf16_hi(lo[i]);
-            float b0 = bf16_lo(up[i]), b1 = bf16_hi(up[i]);
-            float2 c0 = c[2 * i], c1 = c[2 * i + 1];
-            // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
-            lo8[2 * i]     = (_Float16)(a0 * c0.x - b0 * c0.y);
-            lo8[2 * i + 1] = (_Float16)(a1 * c1.x - b1 * c1.y);
-            up8[2 * i]     = (_Float16)(b0 * c0.x + a0 * c0.y);
-            up8[2 * i + 1] = (_Float16)(b1 * c1.x + a1 * c1.y);
-        }
-    }
-    int tile = p / kKeyTile, key = p % kKeyTile;
-    _Float16* dst = Kr + ((long long)unit * g.key_tiles + tile) * (kKeyTile * kD) + ((long long)pg * kKeyTile + key) * 8;
-    *(half8*)dst = lo8;
-    *(half8*)(dst + (long long)pgn * kKeyTile * 8) = up8;
-}
-
-// One workgroup per (unit, tile of 32 keys): the 32 x 128 bf16 block of V is read row by row with 16-byte
-// loads, turned through LDS, and written as the Vt tile.
+// One workgroup per (unit, tile of 32 keys) writes the tile's rotated keys and its transposed values (one launch for both: short
+// calls are bound by the launches, and the loads of the two halves overlap).
+// Keys: a thread rotates a group of 8 pairs of one row; the group of the lower half and its partner group of the upper half
+// come from the same two 16-byte loads.  Kr tile layout (fp16): [group of 8 channels g8 = 0..15][key 0..31][8].
+// Values: the 32 x 128 bf16 block is read row by row with 16-byte loads, turned through LDS, and written as the Vt tile.
 // Vt tile layout (fp16): [channel block db = 0..3][k-step t = 0..1][half-wave hw = 0..1][channel 0..31][8 keys].
-__global__ __launch_bounds__(256) void k_prefill_prep_v(const SlabTable tab, const PrefillGeom g, _Float16* __restrict__ Vt)
+__global__ __launch_bounds__(256) void k_prefill_prep(const SlabTable tab, const PrefillGeom g, const float2* __restrict__ cs,
+                                                      _Float16* __restrict__ Kr, _Float16* __restrict__ Vt)
 {
     __shared__ uint32_t sm[kKeyTile][kD / 2 + 1];             // [key][pair of channels], one word of padding per row
+    constexpr int half = kD / 2, pgn = half / 8;              // groups of 8 pairs per row
     const int tile = blockIdx.x % g.key_tiles;
     const int unit = blockIdx.x / g.key_tiles;
     const int layer = unit / g.units_per_layer;
     const int rem = unit - layer * g.units_per_layer;
     const int b = rem / g.n_kv, kvh = rem - b * g.n_kv;
-    const uint16_t* head = (const uint16_t*)tab.base[2 * layer + 1] + (long long)b * g.stride_batch +
-                           (long long)kvh * g.stride_head;
-    for (int piece = threadIdx.x; piece < kKeyTile * (kD / 8); piece += 256) {
-        const int key = piece / (kD / 8), seg = piece % (kD / 8);
-        const int row = tile * kKeyTile + key;
-        u32x4 w = {0u, 0u, 0u, 0u};                           // rows beyond cur_len are zero
-        if (row < g.cur_len) w = *(const u32x4*)(head + (long long)row * g.stride_token + seg * 8);
-        static_for<4>([&](auto i) { sm[key][seg * 4 + i.value] = w[i.value]; });
+    const long long head = (long long)b * g.stride_batch + (long long)kvh * g.stride_head;
+    const uint16_t* khead = (const uint16_t*)tab.base[2 * layer] + head;
+    const uint16_t* vhead = (const uint16_t*)tab.base[2 * layer + 1] + head;
+    static_assert(kKeyTile * pgn == 256 && kKeyTile * (kD / 8) == 512, "pieces per thread");
+    const int key = threadIdx.x / pgn, pg = threadIdx.x % pgn, j0 = pg * 8;    // the thread's key piece
+    const int krow = tile * kKeyTile + key;
+    u32x4 lo = {0u, 0u, 0u, 0u}, up = lo, vw[2] = {lo, lo};  // rows beyond cur_len are zero
+    float2 c[8];
+    if (krow < g.cur_len) {
+        const uint16_t* row = khead + (long long)krow * g.stride_token;
+        lo = *(const u32x4*)(row + j0);
+        up = *(const u32x4*)(row + half + j0);
+        const f32x4* cr = (const f32x4*)(cs + (long long)krow * half + j0);
+        static_for<4>([&](auto i) {
+            const f32x4 x = cr[i.value];
+            c[2 * i.value] = {x[0], x[1]};
+            c[2 * i.value + 1] = {x[2], x[3]};
+        });
+    }
+    static_for<2>([&](auto i) {
+        const int piece = threadIdx.x + 256 * i.value;
+        const int row = tile * kKeyTile + piece / (kD / 8);
+        if (row < g.cur_len) vw[i.value] = *(const u32x4*)(vhead + (long long)row * g.stride_token + piece % (kD / 8) * 8);
+    });
+    static_for<2>([&](auto i) {
+        const int piece = threadIdx.x + 256 * i.value;
+        static_for<4>([&](auto w) { sm[piece / (kD / 8)][piece % (kD / 8) * 4 + w.value] = vw[i.value][w.value]; });
+    });
+    const long long tile0 = ((long long)unit * g.key_tiles + tile) * (kKeyTile * kD);
+    {
+        half8 lo8 = {}, up8 = {};
+        if (krow < g.cur_len) {
+            static_for<4>([&](auto i) {
+                const float a0 = bf16_lo(lo[i.value]), a1 = bf16_hi(lo[i.value]);
+                const float b0 = bf16_lo(up[i.value]), b1 = bf16_hi(up[i.value]);
+                const float2 c0 = c[2 * i.value], c1 = c[2 * i.value + 1];
+                // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
+                lo8[2 * i.value]     = (_Float16)(a0 * c0.x - b0 * c0.y);
+                lo8[2 * i.value + 1] = (_Float16)(a1 * c1.x - b1 * c1.y);
+                up8[2 * i.value]     = (_Float16)(b0 * c0.x + a0 * c0.y);
+                up8[2 * i.value + 1] = (_Float16)(b1 * c1.x + a1 * c1.y);
+            });
+        }
+        _Float16* dst = Kr + tile0 + ((long long)pg * kKeyTile + key) * 8;
+        *(half8*)dst = lo8;
+        *(half8*)(dst + pgn * kKeyTile * 8) = up8;
     }
     __syncthreads();
     // thread = (k-step t, half-wave hw, pair of channels): two adjacent 16-byte groups of the tile
     const int cp = threadIdx.x & 63, hw = (threadIdx.x >> 6) & 1, t = threadIdx.x >> 7;
-    half8 lo, hi;
+    half8 lov, hiv;
     static_for<8>([&](auto e) {
         const uint32_t w = sm[vt_key(16 * t + 8 * hw + e.value)][cp];
-        lo[e.value] = (_Float16)bf16_lo(w);
-        hi[e.value] = (_Float16)bf16_hi(w);
+        lov[e.value] = (_Float16)bf16_lo(w);
+        hiv[e.value] = (_Float16)bf16_hi(w);
     });
     const int ch = 2 * cp, db = ch >> 5, dl = ch & 31;
-    _Float16* dst = Vt + ((long long)unit * g.key_tiles + tile) * (kKeyTile * kD) +
-                    (long long)(((db * 2 + t) * 2 + hw) * 32 + dl) * 8;
-    *(half8*)dst = lo;
-    *(half8*)(dst + 8) = hi;
+    _Float16* dst = Vt + tile0 + (long long)(((db * 2 + t) * 2 + hw) * 32 + dl) * 8;
+    *(half8*)dst = lov;
+    *(half8*)(dst + 8) = hiv;
 }
 
 // Workgroup = 8 waves = 8 tasks of one KV unit, two waves per SIMD; a task is (query head of the KV group,
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(256) void k_prefill_prep_v(const SlabTable tab, con
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
 void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,
                       const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
-                      float* __restrict__ lse)
+                      float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml)
 {
     __shared__ __attribute__((aligned(1024))) char ksm[4][kTileBytes];   // Kr tiles t+1, t+2, t+3 of step t (ring)
     __shared__ __attribute__((aligned(1024))) char vsm[4][kTileBytes];   // Vt tiles t .. t+3 (ring)
@@ -195,9 +196,10 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // group of 8 units the XCD index picks the unit: all workgroups of a unit run on one XCD and share its L2
     // for the unit's K/V tiles (dealt unit by unit, every XCD fetched every unit: 12.7 GB of fabric reads per
     // launch against 2.2 GB of operands).  The units left over after the last full group are dealt plainly.
-    int unit, wg_seq;
+    int unit, wg_seq, split;
     {
-        const int per_group = 8 * wgs_per_unit;
+        const int wgs_per_unit_split = wgs_per_unit * g.n_split;
+        const int per_group = 8 * wgs_per_unit_split;
         const int grp = blockIdx.x / per_group;
         if (grp < g.units / 8) {
             const int local = blockIdx.x - grp * per_group;
@@ -205,9 +207,11 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
             wg_seq = local >> 3;
         } else {
             const int local = blockIdx.x - (g.units / 8) * per_group;
-            unit = (g.units / 8) * 8 + local / wgs_per_unit;
-            wg_seq = local % wgs_per_unit;
+            unit = (g.units / 8) * 8 + local / wgs_per_unit_split;
+            wg_seq = local % wgs_per_unit_split;
         }
+        split = wg_seq % g.n_split;
+        wg_seq /= g.n_split;
     }
     // later query blocks see more keys: hand them out first so that the long workgroups start early
     const int wg_in_unit = wgs_per_unit - 1 - wg_seq;
@@ -221,7 +225,7 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
 
     // keys this wave needs: [0, pos0 + 31] cut at cur_len; the workgroup loads up to its largest need
     const int my_last = active ? min(pos0 + kQPerWave - 1, g.cur_len - 1) : -1;
-    const int my_tiles = (my_last + kKeyTile) / kKeyTile;
+    int my_tiles = (my_last + kKeyTile) / kKeyTile;
     const int full_tiles = active ? (pos0 + 1) / kKeyTile : 0;     // tiles every query of the wave sees whole
     int wg_tiles;
     {
@@ -229,6 +233,13 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         const int last_qb = last_task / g.G;
         const int wg_last = min(g.cur_len - g.q_len + last_qb * kQPerWave + kQPerWave - 1, g.cur_len - 1);
         wg_tiles = (wg_last + kKeyTile) / kKeyTile;
+    }
+    // few workgroups: the key tiles of each are cut into n_split parts, whose states k_prefill_merge brings together
+    const int t0 = split * g.split_tiles;
+    if (g.n_split > 1) {
+        if (t0 >= wg_tiles) return;                                // nobody here sees keys of this part
+        wg_tiles = min(wg_tiles, t0 + g.split_tiles);
+        my_tiles = min(my_tiles, wg_tiles);
     }
 
     // ---- queries of this wave: second operand of S^T = Kr Qr^T, lane = query column, 8 channels per k-step half.
@@ -291,8 +302,8 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // reads any more, which keeps the loop free of branches.
     const int last_tile = wg_tiles - 1;
     static_for<3>([&](auto i) {
-        dma_k(min(i.value, last_tile), i.value);
-        dma_v(min(i.value, last_tile), i.value);
+        dma_k(min(t0 + i.value, last_tile), t0 + i.value);
+        dma_v(min(t0 + i.value, last_tile), t0 + i.value);
     });
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -304,13 +315,13 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // exponent needs no subtraction; nxt receives S(t+1) - m during step t; the two swap roles every step.
     f32x16 cur, nxt;
     static_for<16>([&](auto r) { cur[r.value] = 0.f; });
-    if (my_tiles > 0) {
-        const char* kt = ksm[0] + frag;
+    if (my_tiles > t0) {
+        const char* kt = ksm[t0 & 3] + frag;
         static_for<8>([&](auto s8) {
             read_k(s8, kt);
             cur = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s8.value], qf[s8.value], cur, 0, 0, 0);
         });
-        static_for<2>([&](auto s8) { read_k(s8, ksm[1] + frag); });
+        static_for<2>([&](auto s8) { read_k(s8, ksm[(t0 + 1) & 3] + frag); });
     }
 
     // Causal mask of a tile that reaches past the first query of the wave.
@@ -331,7 +342,8 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         float v = s[0];
         static_for<16>([&](auto r) { v = fmaxf(v, s[r.value]); });
         const float mx = fmaxf(v, __shfl_xor(v, 32));
-        const bool grow = all || mx > kSlack;
+        // (a query may see nothing of the first tile of its part: its point stays where it is)
+        const bool grow = all ? mx > -INFINITY : mx > kSlack;
         const float delta = grow ? mx : 0.f;
         const float f = exp2_fast(-delta);
         m += delta;
@@ -412,13 +424,28 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // their loads on every path, instead of in front of the first matrix instruction of each step (where the
     // wait would also cover the tile loads just issued).
     asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7]));
-    for (int t = 0; t < wg_tiles; t += 2) {
+    for (int t = t0; t < wg_tiles; t += 2) {
         step(t, cur, nxt);
         if (t + 1 < wg_tiles) step(t + 1, nxt, cur);
     }
 
     // ---- normalise and store: lane = query, registers = channels 8*(r/4) + 4*hw + r%4 of each block
     lsum += __shfl_xor(lsum, 32);
+    if (g.n_split > 1) {
+        // the state as it is, in the order of the registers (1 KB per store): [task][part][channel block][register / 4][lane][4]
+        if (my_tiles > t0) {
+            const long long st = ((long long)unit * tasks_per_unit + task) * g.n_split + split;
+            f32x4* o = (f32x4*)part_acc + st * (16 * 64) + lane;
+            static_for<4>([&](auto db) {
+                static_for<4>([&](auto r4) {
+                    constexpr int R = 4 * decltype(r4)::value;
+                    o[(db.value * 4 + r4.value) * 64] = f32x4{acc[db.value][R], acc[db.value][R + 1], acc[db.value][R + 2], acc[db.value][R + 3]};
+                });
+            });
+            if (hw == 0) part_ml[st * 32 + l32] = {lsum > 0.f ? m : -1e30f, lsum};
+        }
+        return;
+    }
     const int qi = q0 + l32;
     if (active && qi < g.q_len) {
         const float inv = 1.0f / lsum;
@@ -438,35 +465,76 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     }
 }
 
+// Merges the parts of the key range (n_split > 1): one workgroup per task, a wave per block of 32 channels, the same lane layout.
+__global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom g, const float* __restrict__ part_acc,
+                                                       const float2* __restrict__ part_ml, uint16_t* __restrict__ out,
+                                                       float* __restrict__ lse)
+{
+    const int tasks_per_unit = g.G * g.q_blocks;
+    const int unit = blockIdx.x / tasks_per_unit, task = blockIdx.x - unit * tasks_per_unit;
+    const int db = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, hw = lane >> 5;
+    const int qb = task / g.G, gh = task - qb * g.G, q0 = qb * kQPerWave;
+    const int last = min(g.cur_len - g.q_len + q0 + kQPerWave - 1, g.cur_len - 1);
+    const int parts = ((last + kKeyTile) / kKeyTile + g.split_tiles - 1) / g.split_tiles;     // parts that some query of the task sees
+    const long long st = (long long)blockIdx.x * g.n_split;
+    float M = -1e30f, L = 0.f;
+    for (int s = 0; s < parts; ++s) M = fmaxf(M, part_ml[(st + s) * 32 + l32].x);
+    f32x4 o[4] = {};
+    for (int s = 0; s < parts; ++s) {
+        const float2 ml = part_ml[(st + s) * 32 + l32];
+        const float f = exp2_fast(ml.x - M);
+        L = fmaf(ml.y, f, L);
+        const f32x4* a = (const f32x4*)part_acc + (st + s) * (16 * 64) + db * (4 * 64) + lane;
+        static_for<4>([&](auto r4) {
+            const f32x4 x = a[r4.value * 64];
+            static_for<4>([&](auto i) { o[r4.value][i.value] = fmaf(x[i.value], f, o[r4.value][i.value]); });
+        });
+    }
+    const int qi = q0 + l32;
+    if (qi >= g.q_len) return;
+    const long long head = (long long)unit * g.G + gh;
+    const float inv = 1.0f / L;
+    uint16_t* orow = out + (head * g.q_len + qi) * kD + db * 32 + 4 * hw;
+    static_for<4>([&](auto r4) {
+        f32x2 a = {o[r4.value][0] * inv, o[r4.value][1] * inv}, b = {o[r4.value][2] * inv, o[r4.value][3] * inv};
+        u32x2 w;
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(b, bf16x2));
+        *(u32x2*)(orow + 8 * r4.value) = w;
+    });
+    if (lse && db == 0 && hw == 0) lse[head * g.q_len + qi] = 0.6931471805599453f * (M + log2f(L));
+}
+
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
 
-hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, double rope_base, float2* cs,
-                                  _Float16* Kr, _Float16* Vt, hipStream_t st)
+hipError_t launch_prefill_cs(float2* cs, int rows, int d, double rope_base, int rope, hipStream_t st)
+{
+    const long long total = (long long)rows * (d / 2);
+    hipLaunchKernelGGL(k_prefill_cs, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, cs, rows, d, rope_base, rope);
+    return hipGetLastError();
+}
+
+hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, const float2* cs, _Float16* Kr, _Float16* Vt, hipStream_t st)
 {
     if (g.d != kD || g.cur_len < 1 || g.q_len < 1 || g.q_len > g.cur_len) return hipErrorInvalidValue;
     if (g.key_tiles * kKeyTile < g.cur_len || g.q_pad < g.q_len || g.q_pad % kQPerWave) return hipErrorInvalidValue;
-    {
-        long long total = (long long)g.cur_len * (kD / 2);
-        hipLaunchKernelGGL(k_prefill_cs, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, cs, g.cur_len, kD,
-                           rope_base, g.rope);
-    }
-    {
-        long long total = (long long)g.units * g.key_tiles * kKeyTile * (kD / 16);
-        hipLaunchKernelGGL(k_prefill_prep_k, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, tab, g, cs, Kr);
-        hipLaunchKernelGGL(k_prefill_prep_v, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, tab, g, Vt);
-    }
+    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, tab, g, cs, Kr, Vt);
     return hipGetLastError();
 }
 
 hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
-                                 void* out, float* lse, hipStream_t st)
+                                 void* out, float* lse, float* part_acc, float2* part_ml, hipStream_t st)
 {
     if (g.d != kD || g.q_blocks * kQPerWave != g.q_pad) return hipErrorInvalidValue;
+    if (g.n_split < 1 || (g.n_split > 1 && (!part_acc || !part_ml || (long long)g.n_split * g.split_tiles < g.key_tiles))) return hipErrorInvalidValue;
     const int wgs_per_unit = (g.G * g.q_blocks + kPrefillWaves - 1) / kPrefillWaves;
-    hipLaunchKernelGGL(k_attend_prefill, dim3((unsigned)((long long)g.units * wgs_per_unit)), dim3(kPrefillWaves * 64), 0,
-                       st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse);
+    hipLaunchKernelGGL(k_attend_prefill, dim3((unsigned)((long long)g.units * wgs_per_unit * g.n_split)), dim3(kPrefillWaves * 64), 0,
+                       st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    if (g.n_split > 1)
+        hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)((long long)g.units * g.G * g.q_blocks)), dim3(256), 0, st, g, part_acc, part_ml,
+                           (uint16_t*)out, lse);
     return hipGetLastError();
 }
 
