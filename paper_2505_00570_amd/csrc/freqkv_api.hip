@@ -1235,16 +1235,27 @@ struct PrefillShape {
     int n_split;                // parts of the key range, given a workspace of workspace_bytes
 };
 
-// Parts that the key tiles of every workgroup are cut into when there are fewer workgroups than compute units (one holds
-// one workgroup).  A tile takes a workgroup 0.73 us; a part's states (16.6 KB per task) are written and read at about 7
-// TB/s; merging adds 4 us.  301 queries on 5001 rows, 8 KV heads: 40 workgroups x 157 tiles, 115 us in one part.
-int prefill_splits(long long wgs, long long tasks, int tiles)
+// Parts that the key tiles of the workgroups are cut into when these are too few for the 256 compute units (one holds one
+// workgroup).  tiles: of the longest workgroup; first: of the shortest (causal: the lengths rise evenly in between).  A tile
+// takes a workgroup 0.72 us, 0.9 when there is more than one for each (the clock falls); a part's states (16.6 KB per task) are
+// written and read at about 7 TB/s; merging adds 4 us and 0.25 per part.  The time is the longest of: one workgroup; all
+// tiles evenly spread; the whole rounds that equal workgroups make.  8 KV heads of 4 query heads: 301 queries on 5001 rows
+// 125 us in one part, 53 in 6, 69 in 12; 1 query on 8192 rows 131, 43 (6), 38 (12), 48 (32); 600 queries on 2 x 4096
+// rows 111 in one part, 119 in 3; 7088 queries on as many rows 395 in one part, 530 in 3.
+int prefill_splits(long long wgs, long long tasks, int tiles, int first)
 {
-    const double tile_us = 0.73;
     int best = 1;
-    double best_us = std::ceil(wgs / 256.0) * tiles * tile_us;
-    for (int s = 2; s <= 32 && s * 4 <= tiles; ++s) {
-        const double us = std::ceil((double)wgs * s / 256.0) * std::ceil((double)tiles / s) * tile_us + 4.0 + (double)tasks * s * 16640.0 * 2.0 / 7e6;
+    double best_us = 1e30;
+    const double avg = 0.5 * (tiles + first);
+    for (int s = 1; s <= 32 && (s == 1 || s * 4 <= tiles); ++s) {
+        const double part = std::ceil((double)tiles / s);
+        const double busy = s == 1 ? wgs / 256.0 : wgs * std::ceil(avg / part) / 256.0, tile_us = busy > 1.0 ? 0.9 : 0.72;
+        double us = part;
+        if (us < wgs * avg / 256.0) us = wgs * avg / 256.0;
+        const double rounds = std::ceil(busy) * (s == 1 ? first : part);
+        if (us < rounds) us = rounds;
+        us *= tile_us;
+        if (s > 1) us += 4.0 + 0.25 * s + (double)tasks * s * 16640.0 * 2.0 / 7e6;
         if (us < 0.97 * best_us) { best = s; best_us = us; }
     }
     return best;
@@ -1272,7 +1283,7 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     p.workspace_min = p.off_part;
     const long long tasks = units * p.a.G * (p.q_pad / 32);
     p.part_bytes = (size_t)tasks * (32 * d * sizeof(float) + 32 * sizeof(float2));
-    p.n_split = prefill_splits(units * ((p.a.G * (p.q_pad / 32) + 7) / 8), tasks, p.key_tiles);
+    p.n_split = prefill_splits(units * ((p.a.G * (p.q_pad / 32) + 7) / 8), tasks, p.key_tiles, (cur_len - q_len) / 32 + 1);
     p.workspace_bytes = p.workspace_min + (p.n_split > 1 ? p.n_split * p.part_bytes : 0);
     *out = p;
     return FREQKV_OK;

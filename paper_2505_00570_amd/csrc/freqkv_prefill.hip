@@ -478,8 +478,10 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom g, cons
     const int parts = ((last + kKeyTile) / kKeyTile + g.split_tiles - 1) / g.split_tiles;     // parts that some query of the task sees
     const long long st = (long long)blockIdx.x * g.n_split;
     float M = -1e30f, L = 0.f;
+#pragma unroll 4
     for (int s = 0; s < parts; ++s) M = fmaxf(M, part_ml[(st + s) * 32 + l32].x);
     f32x4 o[4] = {};
+#pragma unroll 4
     for (int s = 0; s < parts; ++s) {
         const float2 ml = part_ml[(st + s) * 32 + l32];
         const float f = exp2_fast(ml.x - M);
