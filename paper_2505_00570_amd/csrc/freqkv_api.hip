@@ -71,6 +71,13 @@ Geom make_geom(const Shape& sh, const freqkv_layout_t& L, int slabs, int slab0)
         g.Mpad = (int)round_up(g.Mh, kRowsFold);
         g.Grows = 2 * g.Mpad;
         g.nmtiles = g.Mpad / kRowsFold;
+    } else if (sh.variant == kF32) {
+        g.fold = sh.n % 2 == 0 && sh.Lc % 2 == 0;
+        g.Kh = g.fold ? sh.n / 2 : sh.n;
+        g.Mh = g.fold ? sh.Lc / 2 : sh.Lc;
+        g.Mpad = (int)round_up(g.Mh, 32);
+        g.Grows = (g.fold ? 2 : 1) * g.Mpad;
+        g.nmtiles = g.Mpad / 32;
     } else {
         g.Kh = sh.n; g.Mh = sh.Lc;
         g.Mpad = (int)round_up(g.Mh, kRowsPlain);
@@ -151,7 +158,7 @@ size_t basis_bytes(const Shape& sh, const Geom& g)
         const long long MpA = round_up((sh.Lc / 2 + 1) / 2, kRowsFold), MpB = round_up(sh.Lc / 2, kRowsPlain);
         return (size_t)((H / 8) * (2 * MpA) * 16 + (2 * H / 8) * MpB * 16);
     }
-    if (sh.variant == kF32) return (size_t)sh.n * sh.Lc * sizeof(float);
+    if (sh.variant == kF32) return (size_t)g.Kh * g.Grows * sizeof(float);
     if (sh.variant == kNone) return 0;
     if (sh.variant == kFast) return fast_table_bytes(sh.n, sh.d);
     return (size_t)(g.Kpad / 8) * g.Grows * 16;
@@ -309,7 +316,7 @@ freqkv_status_t get_basis(const Shape& sh, const Geom& g, int rescale, hipStream
                 err = hipMemcpyAsync(e.ptr, e.host, e.bytes, hipMemcpyHostToDevice, st);
             }
         } else if (sh.variant == kF32) {
-            err = launch_basis_f32((float*)e.ptr, sh.n, sh.Lc, rescale, sh.high, st);
+            err = launch_basis_f32((float*)e.ptr, g, rescale, st);
         } else if (sh.variant == kFold2F16) {
             freqkv_layout_t L0;
             memset(&L0, 0, sizeof(L0));

@@ -84,8 +84,8 @@ enum Variant { kNone = 0, kFoldF16 = 1, kPlainF16 = 2, kF32 = 3, kDrop = 4, kFol
 // ---- basis construction (fp64 closed form, rounded once) -------------------------
 // G: [Kpad/8][Grows][8] fp16.  Folded: rows [0,Mpad) even part, rows [Mpad,2Mpad) odd part.
 hipError_t launch_basis_f16(_Float16* G, const Geom& g, int rescale, hipStream_t st);
-// Mf: [Lc][n] fp32 row-major.
-hipError_t launch_basis_f32(float* Mf, int n, int Lc, int rescale, int band, hipStream_t st);
+// Gt: [parity][Kh][Mpad] fp32 (plain: one parity).
+hipError_t launch_basis_f32(float* Gt, const Geom& g, int rescale, hipStream_t st);
 
 // Power of two that brings a head-tensor whose largest bf16 magnitude has the bit pattern `amax` into
 // [2^11, 2^12): sums of four such values stay far below the fp16 limit, and nothing but values 2^-25 of the
@@ -114,7 +114,7 @@ hipError_t launch_fill_zero(float* p, size_t count, hipStream_t st);
 
 // ---- fp32 cache ------------------------------------------------------------------------
 hipError_t launch_prepare_f32(const SlabTable& tab, const Geom& g, float* ws, hipStream_t st);
-hipError_t launch_contract_f32(const SlabTable& tab, const Geom& g, const float* Mf,
+hipError_t launch_contract_f32(const SlabTable& tab, const Geom& g, const float* Gt,
                                const float* ws, float* tap, hipStream_t st);
 
 // ---- factored transform (spans n = 4pq, Lc = n/2, bf16 caches): one kernel, no workspace ------------------

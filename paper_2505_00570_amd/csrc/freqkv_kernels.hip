@@ -170,12 +170,23 @@ __global__ void k_basis_f16(_Float16* __restrict__ G, Geom g, double scale)
     *(half8*)(G + idx * 8) = out;
 }
 
-__global__ void k_basis_f32(float* __restrict__ Mf, int n, int Lc, double scale, int band)
+// fp32 operator, transposed for the contraction: [parity][Kh][Mpad] (plain: one parity), zero in the pad columns.
+__global__ void k_basis_f32(float* __restrict__ Gt, Geom g, double scale)
 {
-    long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (long long)n * Lc) return;
-    int m = (int)(idx / n), j = (int)(idx - (long long)m * n);
-    Mf[idx] = (float)operator_entry(m, j, n, Lc, scale, band);
+    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (long long)(g.fold ? 2 : 1) * g.Kh * g.Mpad) return;
+    const int m = (int)(idx % g.Mpad);
+    const long long rest = idx / g.Mpad;
+    const int j = (int)(rest % g.Kh), parity = (int)(rest / g.Kh);
+    double v = 0.0;
+    if (m < g.Mh) {
+        v = operator_entry(m, j, g.n, g.Lc, scale, g.high);
+        if (g.fold) {
+            const double b = operator_entry(g.Lc - 1 - m, j, g.n, g.Lc, scale, g.high);
+            v = parity ? v - b : v + b;                               // the halves are in the span
+        }
+    }
+    Gt[idx] = (float)v;
 }
 
 hipError_t launch_basis_f16(_Float16* G, const Geom& g, int rescale, hipStream_t st)
@@ -187,12 +198,11 @@ hipError_t launch_basis_f16(_Float16* G, const Geom& g, int rescale, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_basis_f32(float* Mf, int n, int Lc, int rescale, int band, hipStream_t st)
+hipError_t launch_basis_f32(float* Gt, const Geom& g, int rescale, hipStream_t st)
 {
-    double scale = rescale ? 1.0 : sqrt((double)n / (double)Lc);
-    long long total = (long long)n * Lc;
-    unsigned blocks = (unsigned)((total + 255) / 256);
-    hipLaunchKernelGGL(k_basis_f32, dim3(blocks), dim3(256), 0, st, Mf, n, Lc, scale, band);
+    const double scale = rescale ? 1.0 : sqrt((double)g.n / (double)g.Lc);
+    const long long total = (long long)(g.fold ? 2 : 1) * g.Kh * g.Mpad;
+    hipLaunchKernelGGL(k_basis_f32, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Gt, g, scale);
     return hipGetLastError();
 }
 
@@ -803,93 +813,113 @@ hipError_t launch_contract_f16(const SlabTable& tab, const Geom& g, const _Float
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 cache: copy the span out, then a plain LDS-tiled fp32 FMA contraction y = Mf * x
-// workspace: xs[n][ncolsf] fp32, ncolsf = ncols rounded up to 64 (pad columns are zero)
+// fp32 cache: fold (or copy) the span out, then contract on the fp32 matrix instructions (fp32 products and sums)
+// workspace: xs[parity][Kh][ncolsf] fp32, ncolsf = ncols rounded up to 64 (pad columns are zero)
 // ------------------------------------------------------------------------------------------
 
 __device__ __forceinline__ int f32_cols_padded(const Geom& g) { return (g.ncols + 63) & ~63; }
 
+template <bool FOLD>
 __global__ __launch_bounds__(256) void k_prepare_f32(SlabTable tab, Geom g, float* __restrict__ ws)
 {
     const int ncp = f32_cols_padded(g);
     const int vcol = blockIdx.x * 256 + threadIdx.x;
     if (vcol >= ncp) return;
-    const char* base = vcol < g.ncols ? column_base(tab, g, vcol, 4, nullptr) : nullptr;
-    for (int j = blockIdx.y; j < g.n; j += gridDim.y) {
-        float v = base ? *(const float*)(base + (long long)(g.S + j) * g.stride_token * 4) : 0.f;
-        ws[(size_t)j * ncp + vcol] = v;
+    const char* base = vcol < g.ncols ? column_base(tab, g, vcol, 4, nullptr) + (long long)g.S * g.stride_token * 4 : nullptr;
+    for (int j = blockIdx.y; j < g.Kh; j += gridDim.y) {
+        float a = 0.f, b = 0.f;
+        if (base) a = *(const float*)(base + (long long)j * g.stride_token * 4);
+        if (FOLD && base) b = *(const float*)(base + (long long)(g.n - 1 - j) * g.stride_token * 4);
+        if (FOLD) a *= 0.5f, b *= 0.5f;                               // as large as the values themselves: no overflow
+        ws[(size_t)j * ncp + vcol] = FOLD ? a + b : a;
+        if (FOLD) ws[(size_t)(g.Kh + j) * ncp + vcol] = a - b;
     }
 }
 
-__global__ __launch_bounds__(256) void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Mf,
-                                                      const float* __restrict__ ws, float* __restrict__ tap)
+// A workgroup owns 32 result rows (of each parity) x 32 columns; its four waves take a quarter of the contraction each, with
+// the operands straight from the L2 (32 consecutive rows or columns of two contraction indices in a 4-byte load per lane: at
+// 64 cycles per matrix instruction that is little traffic), and are added up in LDS.  The chain of one wave is what a small
+// cache costs: 254 x 508 on 64 columns of K and of V took 80 us as 8 workgroups of a 64 x 64 tile with vector multiply-adds
+// behind a barrier every 16 indices, and takes 5 us; 1022 x 2044 on 8192 columns took 810 us and takes 290 us.  Eight waves
+// to a tile lose 2 us on the former and 50 us on the latter, 32 x 64 tiles 5 us and 40 us, tiles of one wave 17 us and 12 us.
+constexpr int kWavesF32 = 4;
+
+template <bool FOLD>
+__global__ __launch_bounds__(kWavesF32 * 64)
+void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const float* __restrict__ ws, float* __restrict__ tap)
 {
-    __shared__ float As[16][65];   // [k][m]
-    __shared__ float Bs[16][64];   // [k][col]
-    const int ncp = f32_cols_padded(g);
-    const int c0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < g.n; k0 += 16) {
-        for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-            int mm = e >> 4, kk = e & 15;
-            int m = m0 + mm, j = k0 + kk;
-            As[kk][mm] = (m < g.Lc && j < g.n) ? Mf[(size_t)m * g.n + j] : 0.f;
-        }
-        for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-            int kk = e >> 6, cc = e & 63;
-            int j = k0 + kk;
-            Bs[kk][cc] = (j < g.n) ? ws[(size_t)j * ncp + c0 + cc] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) b[i] = Bs[kk][tx * 4 + i];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[i][q] = fmaf(a[i], b[q], acc[i][q]);
-        }
-        __syncthreads();
+    constexpr int P = FOLD ? 2 : 1, U = 8;                            // U steps have their loads in flight together
+    __shared__ float red[kWavesF32][P][16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hw = lane >> 5;
+    const int ncp = f32_cols_padded(g), rtiles = g.Mpad / 32;
+    const int m0 = (int)(blockIdx.x % rtiles) * 32, c0 = (int)(blockIdx.x / rtiles) * 32;
+    const int steps = (g.Kh + 1) / 2;                                 // of two contraction indices each
+    const int per = (steps + kWavesF32 - 1) / kWavesF32, s0 = wave * per, s1 = min(s0 + per, steps);
+    f32x16 acc[P];
+    static_for<P>([&](auto p) { static_for<16>([&](auto r) { acc[p.value][r.value] = 0.f; }); });
+    const float* ga = Gt + m0 + l32;
+    const float* xb = ws + c0 + l32;
+    for (int s = s0; s < s1; s += U) {
+        float a[U][P], b[U][P];
+        static_for<U>([&](auto u) {
+            const int k = min(2 * (s + u.value) + hw, g.Kh - 1);      // past the end: the last index again, times zero
+            static_for<P>([&](auto p) {
+                a[u.value][p.value] = ga[((size_t)p.value * g.Kh + k) * g.Mpad];
+                b[u.value][p.value] = xb[((size_t)p.value * g.Kh + k) * ncp];
+            });
+        });
+        static_for<U>([&](auto u) {
+            const bool in = s + u.value < s1 && 2 * (s + u.value) + hw < g.Kh;
+            static_for<P>([&](auto p) {
+                acc[p.value] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[u.value][p.value] : 0.f, in ? b[u.value][p.value] : 0.f,
+                                                                    acc[p.value], 0, 0, 0);
+            });
+        });
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        int vcol = c0 + tx * 4 + q;
-        if (vcol >= g.ncols) continue;
-        int ht;
-        char* base = column_base(tab, g, vcol, 4, &ht);
-        int c = vcol - ht * g.d;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int m = m0 + ty * 4 + i;
-            if (m >= g.Lc) continue;
-            *(float*)(base + (long long)(g.S + m) * g.stride_token * 4) = acc[i][q];
-            if (tap) {
-                long long ht_global = g.tap_slab0 * g.hts_per_slab + ht;
-                tap[(ht_global * g.Lc + m) * g.d + c] = acc[i][q];
-            }
+    static_for<P>([&](auto p) { static_for<16>([&](auto r) { red[wave][p.value][r.value][lane] = acc[p.value][r.value]; }); });
+    __syncthreads();
+
+    const int vcol = c0 + l32;
+    if (vcol >= g.ncols) return;
+    int ht;
+    char* base = column_base(tab, g, vcol, 4, &ht);
+    float* tp = tap ? tap + ((g.tap_slab0 * g.hts_per_slab + ht) * (long long)g.Lc) * g.d + (vcol - ht * g.d) : nullptr;
+    auto put = [&](int row, float v) {
+        *(float*)(base + (long long)(g.S + row) * g.stride_token * 4) = v;
+        if (tp) tp[(long long)row * g.d] = v;
+    };
+    for (int r = wave; r < 16; r += kWavesF32) {
+        const int m = m0 + 8 * (r / 4) + 4 * hw + r % 4;              // row of result register r in this half of the wave
+        if (m >= g.Mh) continue;
+        float v[P];
+        static_for<P>([&](auto p) {
+            v[p.value] = 0.f;
+            static_for<kWavesF32>([&](auto w) { v[p.value] += red[w.value][p.value][r][lane]; });
+        });
+        if constexpr (FOLD) {
+            put(m, v[0] + v[1]);
+            put(g.Lc - 1 - m, v[0] - v[1]);
+        } else {
+            put(m, v[0]);
         }
     }
 }
 
 hipError_t launch_prepare_f32(const SlabTable& tab, const Geom& g, float* ws, hipStream_t st)
 {
-    int ncp = (g.ncols + 63) & ~63;
-    dim3 grid((ncp + 255) / 256, g.n < 65535 ? g.n : 65535);
-    hipLaunchKernelGGL(k_prepare_f32, grid, dim3(256), 0, st, tab, g, ws);
+    const int ncp = (g.ncols + 63) & ~63;
+    const dim3 grid((ncp + 255) / 256, g.Kh < 65535 ? g.Kh : 65535);
+    if (g.fold) hipLaunchKernelGGL(k_prepare_f32<true>, grid, dim3(256), 0, st, tab, g, ws);
+    else        hipLaunchKernelGGL(k_prepare_f32<false>, grid, dim3(256), 0, st, tab, g, ws);
     return hipGetLastError();
 }
 
-hipError_t launch_contract_f32(const SlabTable& tab, const Geom& g, const float* Mf, const float* ws,
+hipError_t launch_contract_f32(const SlabTable& tab, const Geom& g, const float* Gt, const float* ws,
                                float* tap, hipStream_t st)
 {
-    int ncp = (g.ncols + 63) & ~63;
-    dim3 grid(ncp / 64, (g.Lc + 63) / 64);
-    hipLaunchKernelGGL(k_contract_f32, grid, dim3(256), 0, st, tab, g, Mf, ws, tap);
+    const dim3 grid(g.Mpad / 32 * (((g.ncols + 63) & ~63) / 32));
+    if (g.fold) hipLaunchKernelGGL(k_contract_f32<true>, grid, dim3(kWavesF32 * 64), 0, st, tab, g, Gt, ws, tap);
+    else        hipLaunchKernelGGL(k_contract_f32<false>, grid, dim3(kWavesF32 * 64), 0, st, tab, g, Gt, ws, tap);
     return hipGetLastError();
 }
 
