@@ -24,6 +24,9 @@ constexpr int kMaxSlabs = 192;
 struct SlabTable {
     char* base[kMaxSlabs];
 };
+struct TailTable {
+    int rows[kMaxSlabs];
+};
 
 // Tile constants of the fp16-MFMA contraction.
 constexpr int kColTile   = 128;   // virtual columns per workgroup tile
@@ -154,6 +157,10 @@ hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tab
 // ---- tail move: rows [src, src+rows) -> [dst, dst+rows) of every head-tensor; ranges must not overlap
 hipError_t launch_move_rows(const SlabTable& tab, const Geom& g, int elem_bytes, int src_row,
                             int dst_row, int rows, hipStream_t st);
+// the first tails.rows[slab] rows from src on -> dst on, for every slab its own count (at most `most`); the ranges of one
+// slab may overlap, but not rows that are less than `gap` apart
+hipError_t launch_move_tails(const SlabTable& tab, const TailTable& tails, const Geom& g, int elem_bytes, int src_row,
+                             int dst_row, int most, int gap, hipStream_t st);
 
 // ---- calibration: plain 16-byte copy; register-only MFMA loop (16 x 32x32x16 f16 per iteration per wave)
 hipError_t launch_calib_copy(void* dst, const void* src, size_t bytes, hipStream_t st);

@@ -960,6 +960,35 @@ hipError_t launch_move_rows(const SlabTable& tab, const Geom& g, int elem_bytes,
     return hipSuccess;
 }
 
+// The tails of slabs that hold different numbers of tokens, in one launch: as many rows of workgroups as the longest needs.
+__global__ __launch_bounds__(256) void k_move_tails(SlabTable tab, TailTable tails, Geom g, int elem_bytes, int src_row,
+                                                    int dst_row, int row0, int per16)
+{
+    const long long grp = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (grp >= (long long)g.ncols / per16) return;
+    const int row = row0 + blockIdx.y, vcol = (int)(grp * per16);
+    int ht;
+    char* base = column_base(tab, g, vcol, elem_bytes, &ht);
+    if (row >= tails.rows[ht / g.hts_per_slab]) return;
+    const long long rowb = g.stride_token * elem_bytes;
+    *(u32x4*)(base + (long long)(dst_row + row) * rowb) = *(const u32x4*)(base + (long long)(src_row + row) * rowb);
+}
+
+hipError_t launch_move_tails(const SlabTable& tab, const TailTable& tails, const Geom& g, int elem_bytes, int src_row,
+                             int dst_row, int most, int gap, hipStream_t st)
+{
+    const int per16 = 16 / elem_bytes;
+    const unsigned wgs = (unsigned)(((long long)g.ncols / per16 + 255) / 256);
+    const int step = gap < 65535 ? gap : 65535;                       // no chunk overlaps its own source; limit of gridDim.y
+    for (int r0 = 0; r0 < most; r0 += step) {
+        const dim3 grid(wgs, most - r0 < step ? most - r0 : step);
+        hipLaunchKernelGGL(k_move_tails, grid, dim3(256), 0, st, tab, tails, g, elem_bytes, src_row, dst_row, r0, per16);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ------------------------------------------------------------------------------------------
 // calibration kernels: what this device sustains for a plain copy and for a register-only MFMA
 // loop on random (power-realistic) operands; rooflines are quoted against both nominal and these

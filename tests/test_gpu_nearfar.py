@@ -3,7 +3,8 @@
 import pytest
 import torch
 
-from paper_2505_00570_amd import synth
+import paper_2505_00570_amd as fk
+from paper_2505_00570_amd import binding, synth
 
 from _util import TOL_BF16
 from test_gpu_parity import _check_all_heads, _mk, _run, _say
@@ -53,3 +54,24 @@ def test_nearfar_nan_stays_in_its_channel():
     ok = [c for c in range(64) if c not in (17, 40)]
     assert not torch.isfinite(got[:, 17]).any() and not torch.isfinite(got[:, 40]).any()
     assert torch.equal(got[:, ok], clean[0, 0, 0, 4:p.new_len].float()[:, ok])
+
+
+@pytest.mark.parametrize("layers,lens", [(1, [140, 133, 400, 132, 12]), (33, [132, 133, 250, 3, 132])])
+def test_nearfar_ragged_is_each_sequence_alone(layers, lens):
+    """One pass over all due sequences: tails longer than the rows set free, more slabs than one pass holds."""
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=layers, batch=5, n_heads=3, head_dim=32, window=132)
+    k, v = _mk(wl, seed=5, capacity=max(lens) + 3, cur_len=max(lens) + 3)
+    k0, v0 = k.clone(), v.clone()
+    L = binding.layout_for(k)
+    _, p = fk.plan(L, 3, 32, 132, 132, wl.n_sink, 0.5)
+    ws = torch.empty(max(p.workspace_bytes, 256), dtype=torch.uint8, device=k.device)
+    L.workspace, L.workspace_bytes = ws.data_ptr(), p.workspace_bytes
+    _, new = fk.compress_ragged(k, v, L, 3, 32, lens, 132, wl.n_sink, 0.5)
+    for b, n in enumerate(lens):
+        kb, vb = k0[:, b:b + 1].clone(), v0[:, b:b + 1].clone()
+        if n >= 132:
+            _run(kb, vb, synth.small(wl, batch=1), n, tap=False)
+        assert new[b] == (n if n < 132 else n - 132 + wl.n_sink + p.retained_len)
+        for got, want, before in ((k, kb, k0), (v, vb, v0)):
+            assert torch.equal(got[:, b, :, :new[b]], want[:, 0, :, :new[b]])
+            assert torch.equal(got[:, b, :, n:], before[:, b, :, n:])
