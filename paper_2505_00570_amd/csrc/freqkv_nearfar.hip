@@ -602,6 +602,9 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             ptr = wrap(ptr + dir * g.NL);
         }
         const int up = g.NL >= g.R ? dir : -dir;         // leaf l + 1 sits one slot further on this way
+        // Result rows go out through a buffer that ends with the last of them: rows past it are dropped without a branch, which
+        // would make every wait for a table expect the stores to be missing and so wait for them too.
+        const auto out = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)((uint32_t)g.Lc * rowb), 0x00020000);
         float* const tp = tap ? tap + ((g.tap_slab0 * g.hts_per_slab + ht) * (long long)g.Lc) * g.d + c0 : nullptr;
 
         // Rounding and storing a tile, in 7 parts that the next tile's matrix instructions cover.  A lane has result row
@@ -637,7 +640,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             } else {
                 static_for<2>([&](auto i) {
                     const int mr = 32 * t + 16 * i.value + l16;
-                    if (mr < g.Lc) *(u32x4*)(base + (uint32_t)mr * rowb + g4 * 16) = row[i.value];
+                    __builtin_amdgcn_raw_buffer_store_b128(row[i.value], out, mr < g.Lc ? (uint32_t)mr * rowb + g4 * 16 : ~15u, 0, 0);
                 });
             }
         };
@@ -685,9 +688,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     p = x[K / 8] + (K % 8) * 16 * kRowB;
                 } else {
                     const int ks = klo + K - 8 * NK;
-                    const char* xb = x[0];
-                    static_for<NK - 1>([&](auto q) { xb = ks >= 8 * (q.value + 1) ? x[q.value + 1] : xb; });
-                    p = xb + (ks & 7) * 16 * kRowB;
+                    if constexpr (NK == 2)
+                        p = (ks >= 8 ? x[1] : x[0]) + (ks & 7) * 16 * kRowB;
+                    else                                         // (a choice among three x would become an array in scratch memory)
+                        p = ring + wrap(at_slot + up * (ks >> 3)) * kSlotB + (ks & 7) * 16 * kRowB + tr16;
                 }
                 xf[K % (kAhead + 1)] = join(read_tr(p), read_tr(p + 4 * kRowB));
             };
