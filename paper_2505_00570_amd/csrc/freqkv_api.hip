@@ -345,11 +345,11 @@ freqkv_status_t get_basis(const Shape& sh, const Geom& g, int rescale, hipStream
 }
 
 // Tables of the near/far form, cached like the bases.
-freqkv_status_t get_nf_tables(const Shape& sh, hipStream_t st, const char** out)
+freqkv_status_t get_nf_tables(const Shape& sh, int rescale, hipStream_t st, const char** out)
 {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    BasisKey key{dev, sh.n, sh.Lc, kNearFar, 0, 0};
+    BasisKey key{dev, sh.n, sh.Lc, kNearFar, rescale, 0};
     std::lock_guard<std::mutex> lock(g_mu);
     auto it = g_basis.find(key);
     if (it == g_basis.end()) {
@@ -361,7 +361,9 @@ freqkv_status_t get_nf_tables(const Shape& sh, hipStream_t st, const char** out)
             (void)hipGetLastError();
             return FREQKV_E_ALLOC;
         }
-        err = launch_nf_tables(sh.nf, (char*)e.ptr, st);
+        NfGeom nf = sh.nf;
+        nf.out_scale = rescale ? 1.0f : (float)std::sqrt((double)sh.n / (double)sh.Lc);
+        err = launch_nf_tables(nf, (char*)e.ptr, st);
         if (err == hipSuccess) err = hipEventCreateWithFlags(&e.ready, hipEventDisableTiming);
         if (err == hipSuccess) err = hipEventRecord(e.ready, st);
         if (err != hipSuccess) {
@@ -701,7 +703,7 @@ freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink
     if (sh.variant == kNone || sh.variant == kDrop) return FREQKV_OK;
     if (sh.nearfar) {
         const char* tables = nullptr;
-        return get_nf_tables(sh, (hipStream_t)stream, &tables);
+        return get_nf_tables(sh, !(flags & FREQKV_FLAG_NO_RESCALE), (hipStream_t)stream, &tables);
     }
     Geom g = make_geom(sh, L, 1, 0);
     void* basis = nullptr;
@@ -737,14 +739,13 @@ freqkv_status_t compress_nearfar(const std::vector<char*>& bases, const std::vec
     const char* tables = nullptr;
     ProfSpan ps;                                               // profiles of matrix-form plans count a preparation: the tables
     if (sh.variant != kFast) HIP_TRY(prof_begin(st, 0, &ps));
-    freqkv_status_t rc = get_nf_tables(sh, st, &tables);
+    freqkv_status_t rc = get_nf_tables(sh, !(L.flags & FREQKV_FLAG_NO_RESCALE), st, &tables);
     if (rc < 0) return rc;
     if (sh.variant != kFast) HIP_TRY(prof_end(st, &ps));
     if (g_prof_on) { std::lock_guard<std::mutex> lock(g_mu); g_prof_acc.calls++; }
     NfGeom nf = sh.nf;
     nf.S = sh.S; nf.n_heads = sh.n_heads; nf.hts_per_slab = (int)sh.hts_per_slab;
     nf.stride_batch = L.stride_batch; nf.stride_head = L.stride_head; nf.stride_token = L.stride_token;
-    nf.out_scale = L.flags & FREQKV_FLAG_NO_RESCALE ? (float)std::sqrt((double)sh.n / (double)sh.Lc) : 1.0f;
     for (int s0 = 0; s0 < sh.nslabs; s0 += kMaxSlabs) {
         const int slabs = sh.nslabs - s0 < kMaxSlabs ? sh.nslabs - s0 : kMaxSlabs;
         SlabTable tab;

@@ -147,7 +147,7 @@ struct NfGeom {
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;
     int d;
     int S, n_heads, hts_per_slab, hts;
-    float out_scale;         // sqrt(n/Lc) without the rescale of Eq. 3, else 1
+    float out_scale;         // sqrt(n/Lc) without the rescale of Eq. 3, else 1 (in the tables)
     long long stride_batch, stride_head, stride_token, tap_slab0;
 };
 bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out);

@@ -176,12 +176,13 @@ __device__ double near_entry(const NfGeom& g, int slot, int m_in, int row_in)
     return v / (2.0 * n);
 }
 
-// What the kernel wants to know of tile t and of group gr in one word each: first leaf of the window, first step with
-// second parts, table slot; first block of the neighbourhood.
-__device__ uint32_t tile_word(const NfGeom& g, int t)
+// What the kernel wants to know of tile t, in one scalar load: first leaf of the window, first step with second parts, table
+// slot | slot of the wave's next tile (of this task or the next), first block of the next group's neighbourhood.
+__device__ u32x2 tile_words(const NfGeom& g, int t)
 {
-    const int l = tile_at(g, t).leaf0;
-    return (uint32_t)l | (uint32_t)tile_lo_step(g, t, l) << 8 | (uint32_t)tile_slot(g, t) << 16;
+    const int l = tile_at(g, t).leaf0, next = t + kCompute < g.NT ? t + kCompute : t % kCompute;
+    return u32x2{(uint32_t)l | (uint32_t)tile_lo_step(g, t, l) << 8 | (uint32_t)tile_slot(g, t) << 16,
+                 (uint32_t)tile_slot(g, next) | (uint32_t)group_block0(g, min(t / g.GT + 1, g.NG - 1)) << 16};
 }
 
 // One thread per 16 bytes (lane) of a fragment.
@@ -190,9 +191,9 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= g.off_w / 16) {
         const long long w = idx - g.off_w / 16;
-        uint32_t* const words = (uint32_t*)(out + g.off_w);
-        if (w < g.NT) words[w] = tile_word(g, (int)w);
-        else if (w < g.NT + g.NG) words[w] = (uint32_t)group_block0(g, (int)w - g.NT);
+        u32x2* const words = (u32x2*)(out + g.off_w);
+        if (w < g.NT) words[w] = tile_words(g, (int)w);
+        else if (w == g.NT) words[w] = u32x2{(uint32_t)group_block0(g, 0), 0u};
         return;
     }
     const int lane = (int)(idx & 63);
@@ -216,7 +217,7 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
                 }
                 k = k - 8 * g.NK + tile_lo_step(g, t, tile_at(g, t).leaf0);
             }
-            x = near_entry(g, slot, l32, 16 * k + 8 * hw + i);
+            x = g.out_scale * near_entry(g, slot, l32, 16 * k + 8 * hw + i);
             if (second) x -= (double)(float)(__bf16)(float)x;
         } else if (byte < g.off_m) {
             // moments: [slot][4 steps of 32 rows], 16 (8 used) moments x 32 rows
@@ -260,7 +261,7 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
             const int gr = f < g.GT ? 0 : g.NG - 1, t = gr * g.GT + f % g.GT, m = 32 * t + l32;
             if (m < g.Lc) {
                 const Iv iv = hw ? group_iv(g, gr) : tile_iv(g, t);
-                x = lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
+                x = g.out_scale * lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
             }
         }
         v[i] = (__bf16)(float)x;
@@ -353,7 +354,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                                  (long long)g.S * g.stride_token + c0) * 2;
     };
     const int tasks = g.hts * tph;
-    const uint32_t* const words = (const uint32_t*)(tables + g.off_w);      // tile words, then group words
+    const u32x2* const words = (const u32x2*)(tables + g.off_w);            // of tiles, then the first group's first block
     const uint32_t rowb = (uint32_t)g.stride_token * 2;
 
     auto wrap = [&](int s) { return s < 0 ? s + g.R : (s >= g.R ? s - g.R : s); };
@@ -421,8 +422,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             lds_barrier();
             lds_barrier();
             for (int t = 0; t < g.NT; t += kCompute) {
-                const int first = words[t] & 255;
-                const int end = (int)(words[min(t + kCompute, g.NT) - 1] & 255) + NK;
+                const int first = words[t][0] & 255;
+                const int end = (int)(words[min(t + kCompute, g.NT) - 1][0] & 255) + NK;
                 wait_copies(issued - (p0 + g.NL + max(0, end - g.R)));
                 lds_barrier();
                 issue_until(p0 + (whole ? g.R : g.NL + first));
@@ -440,8 +441,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 #define NF_LANE()                                                                                                       \
     asm volatile("" : "+v"(lane_v));                                                                                    \
     [[maybe_unused]] const int l32 = lane_v & 31, hw = lane_v >> 5, l16 = lane_v & 15, g4 = lane_v >> 4, vec16 = l16 * 16
-    // a fragment: uniform address plus the lane's offset, so that the address of each stays in scalar registers
-    auto table = [&](int off) { return *(const bf16x8*)(tables + off + (uint32_t)lane * 16); };
+    // a fragment: one scalar offset each
+    const auto tabs = __builtin_amdgcn_make_buffer_rsrc((void*)tables, 0, g.table_bytes, 0x00020000);
+    const int lane16 = lane * 16;
+    auto table = [&](int off) { return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(tabs, lane16, off, 0)); };
     auto lds_table = [&](int f) { return *(const bf16x8*)(ltab + f * kFrag + lane * 16); };
     // the first 8 (of 16) result rows of a moment product, or all 16: 4 per lane, [vector][channel][8]
     auto put8 = [&](char* vec, int h, f32x4 a) {
@@ -455,28 +458,23 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 
     // Tables that change from step to step are fetched one step ahead of their use, into registers: a load queues behind
     // the copies in flight, a step's worth of time.  What does not change sits in LDS or stays in registers.
-    bf16x8 ft[kNB];                                  // neighbourhood of the tiles whose local values are due next
-    auto fetch_locals = [&](int gr, int u) {
-        const int off = g.off_f + (gr * (GT / 2) + (wave & 1) * TPW + u) * kNB * kFrag;
-        static_for<kNB>([&](auto k) { ft[k.value] = table(off + k.value * kFrag); });
-    };
-    // Local values of the tiles of group gr (part u in TPW of them) from the leaves around it, in three parts: operands, product, result.
-    bf16x8 lf[kNB];
+    // Local values of the tiles of a group from the leaves around it: a wave takes two tiles and a half of the channels, with TPW == 2
+    // one half in each of the group's steps (u) from the same tables.  A table is requested again right after its last use.
+    bf16x8 ft[kNB];
+    const int mt = TPW == 2 ? wave : wave & 1;
+    auto fetch_local = [&](int gr, auto k) { ft[k.value] = table(g.off_f + ((gr * (GT / 2) + mt) * kNB + k.value) * kFrag); };
+    bf16x8 lf;
     f32x4 la;
-    auto locals_read = [&](int block0) {
-        NF_LANE();
-        const char* src = mom + (4 * block0 + g4) * kVecB + (wave >> 1) * 256 + vec16;
-        static_for<kNB>([&](auto k) { lf[k.value] = *(const bf16x8*)(src + k.value * 4 * kVecB); });
+    const char* const local_in = mom + (lane >> 4) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16;
+    char* const local_out = loc + 2 * mt * kVecB + (lane >> 5) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16 + (lane >> 4 & 1) * 8;
+    auto locals_read = [&](int block0, auto u, auto k) {
+        lf = *(const bf16x8*)(local_in + block0 * 4 * kVecB + (TPW == 2 ? u.value * 256 : 0) + k.value * 4 * kVecB);
     };
     auto locals_mac = [&](auto k) {
         if constexpr (decltype(k)::value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
-        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf[k.value], la, 0, 0, 0);
+        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf, la, 0, 0, 0);
     };
-    auto locals_put = [&](int gr, int u) {
-        put16(loc + ((gr & 1) * GT + 2 * ((wave & 1) * TPW + u)) * kVecB, wave >> 1, la);
-        if (u + 1 < TPW) fetch_locals(gr, u + 1);
-        else fetch_locals(gr + 1 < g.NG ? gr + 1 : 0, 0);
-    };
+    auto locals_put = [&](int gr, auto u) { *(u32x2*)(local_out + (gr & 1) * (GT * kVecB) + (TPW == 2 ? u.value * 256 : 0)) = pack4(la); };
     auto block_moments = [&](int b) {
         NF_LANE();
         const bf16x8 m = lds_table(b == g.NC - 1 ? 5 : 4);
@@ -497,7 +495,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         static_for<TPW>([&](auto u) { pin(rt[u.value]); });
     };
     const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
-    fetch_locals(0, 0);
+    static_for<kNB>([&](auto k) { fetch_local(0, k); });
     if (top_leaf >= 0) fetch_moments(top_leaf);
     if (SHIFTS) static_for<4>([&](auto k) { pin(vt[k.value]); });
     fetch_results(g.NG == 1);
@@ -508,10 +506,16 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto fetch_entries = [&](int slot) { static_for<STEPS>([&](auto k) { e[k.value] = table(slot * PER + k.value * kFrag); }); };
     int cur_slot = -1;
     if (wave < g.NT) {
-        cur_slot = (int)(words[wave] >> 16);
+        cur_slot = (int)(words[wave][0] >> 16);
         fetch_entries(cur_slot);
     }
     static_for<STEPS>([&](auto k) { pin(e[k.value]); });
+
+    // parts of addresses that depend on the lane
+    const char* const tr16 = ring + (8 * (lane >> 5) + (lane >> 2 & 3)) * kRowB + (lane >> 4 & 1) * 32 + (lane & 3) * 8;    // its 8 bytes of a 16-row step
+    const char* const far_tile = loc + wave * kVecB + (lane & 31) * 16;
+    const char* const far_group = cloc + (lane & 31) * 16;
+    const uint32_t row_lane = (uint32_t)(lane & 15) * rowb + (lane >> 4) * 16;
 
     int ptr = 0, dir = 1;                            // ring slot of the task's first leaf (the span's last), and where to go from there
     for (int vb = blockIdx.x; vb < tasks; vb += gridDim.x) {
@@ -587,9 +591,12 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             lds_barrier();
             // ... and those of the first group's tiles
             static_for<TPW>([&](auto u) {
-                locals_read((int)words[g.NT]);
-                static_for<kNB>([&](auto k) { locals_mac(k); });
-                locals_put(0, u.value);
+                static_for<kNB>([&](auto k) {
+                    locals_read((int)words[g.NT][0], u, k);
+                    locals_mac(k);
+                    if (u.value == TPW - 1) fetch_local(g.NG > 1, k);
+                });
+                locals_put(0, u);
             });
         }
 
@@ -613,16 +620,17 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         uint32_t w[4][2];
         u32x4 row[2];
         auto finish = [&](f32x16& acc, int t, auto part) {
-            NF_LANE();
             constexpr int P = decltype(part)::value;
+            if constexpr (P == 0) {
+                if (tp) {
+                    NF_LANE();
+                    if (32 * t + l32 < g.Lc)
+                        static_for<16>([&](auto i) { tp[(long long)(32 * t + l32) * g.d + 8 * (i.value / 4) + 4 * hw + i.value % 4] = acc[i.value]; });
+                }
+            }
             if constexpr (P < 4) {
-                static_for<4>([&](auto i) { acc[4 * P + i.value] *= g.out_scale; });
                 w[P][0] = pack2(acc[4 * P], acc[4 * P + 1]);
                 w[P][1] = pack2(acc[4 * P + 2], acc[4 * P + 3]);
-                if (tp && 32 * t + l32 < g.Lc) {
-                    float* f = tp + (long long)(32 * t + l32) * g.d + 8 * P + 4 * hw;
-                    static_for<4>([&](auto i) { f[i.value] = acc[4 * P + i.value]; });
-                }
             } else if constexpr (P == 4) {
                 static_for<2>([&](auto q) {
                     static_for<2>([&](auto i) {
@@ -638,9 +646,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     row[1][i.value] = s[1];
                 });
             } else {
+                // one path for all tiles: behind a branch, the waits for tables would have to expect the stores to be missing
                 static_for<2>([&](auto i) {
-                    const int mr = 32 * t + 16 * i.value + l16;
-                    __builtin_amdgcn_raw_buffer_store_b128(row[i.value], out, mr < g.Lc ? (uint32_t)mr * rowb + g4 * 16 : ~15u, 0, 0);
+                    const int m = 32 * t + 16 * i.value;
+                    __builtin_amdgcn_raw_buffer_store_b128(row[i.value], out, (lane & 15) < g.Lc - m ? row_lane + (uint32_t)m * rowb : ~15u, 0, 0);
                 });
             }
         };
@@ -652,46 +661,35 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         auto step = [&](int c, auto uc, f32x16& acc, f32x16& prev) {
             constexpr int U = decltype(uc)::value;
             const int tl = wave + kCompute * U, t = GT * c + tl;
-            // what the step needs to know of its tiles: scalar loads, ahead of the barrier (behind it their wait would take in LDS reads)
-            const bool more = c + 1 < g.NG;
-            const int next = t + kCompute < g.NT ? t + kCompute : wave;     // the wave's next tile (of this task or the next)
-            const uint32_t word = words[min(t, g.NT - 1)], next_word = words[min(next, g.NT - 1)];
-            const int block0 = (int)words[g.NT + min(c + 1, g.NG - 1)];
+            // what the step needs to know of its tile: a scalar load, ahead of the barrier (behind it its wait would take in LDS reads)
+            const u32x2 word = words[min(t, g.NT - 1)];
             lds_barrier();
             if (t >= g.NT) {                             // no tile for this wave in the last step of the task
                 if constexpr (LATE) static_for<7>([&](auto p) { finish(prev, before, p); });
                 before = t;
                 return;
             }
-            const int leaf0 = (int)(word & 255), klo = (int)(word >> 8 & 255);
-            const int next_slot = (int)(next_word >> 16);
+            const int leaf0 = (int)(word[0] & 255), klo = (int)(word[0] >> 8 & 255);
+            const int next_slot = (int)(word[1] & 0xffff), block0 = (int)(word[1] >> 16);
             at_slot = wrap(at_slot + up * (leaf0 - at_leaf));
             at_leaf = leaf0;
-            NF_LANE();
-            const int tr16 = (8 * hw + (l16 >> 2)) * kRowB + (g4 & 1) * 32 + (l16 & 3) * 8;    // the lane's 8 bytes of a 16-row step
-            const char* x[NK];
-            {
-                int s = at_slot;
-                static_for<NK>([&](auto k) {
-                    x[k.value] = ring + s * kSlotB + tr16;
-                    s = wrap(s + up);
-                });
-            }
+            const int s0 = at_slot * kSlotB, s1 = wrap(at_slot + up) * kSlotB, s2 = NK == 3 ? wrap(at_slot + 2 * up) * kSlotB : 0;
+            const char *const x0 = tr16 + s0, *const x1 = tr16 + s1, *const x2 = NK == 3 ? tr16 + s2 : nullptr;
             // 8 NK matrix instructions with the first parts, then NLO with the second; operands are read kAhead instructions
             // ahead, and the order is pinned: left alone the compiler reads the whole window first and runs out of registers
-            constexpr int kAhead = NK == 2 ? 4 : 2;
+            constexpr int kAhead = 3;
             bf16x8 xf[kAhead + 1], far;
             auto fetch_rows = [&](auto kc) {
                 constexpr int K = decltype(kc)::value;
                 const char* p;
                 if constexpr (K < 8 * NK) {
-                    p = x[K / 8] + (K % 8) * 16 * kRowB;
+                    p = (K < 8 ? x0 : K < 16 ? x1 : x2) + (K % 8) * 16 * kRowB;
                 } else {
                     const int ks = klo + K - 8 * NK;
                     if constexpr (NK == 2)
-                        p = (ks >= 8 ? x[1] : x[0]) + (ks & 7) * 16 * kRowB;
-                    else                                         // (a choice among three x would become an array in scratch memory)
-                        p = ring + wrap(at_slot + up * (ks >> 3)) * kSlotB + (ks & 7) * 16 * kRowB + tr16;
+                        p = tr16 + ((ks >= 8 ? s1 : s0) + (ks & 7) * 16 * kRowB);
+                    else                                         // (a choice among three would become an array in scratch memory)
+                        p = tr16 + (wrap(at_slot + up * (ks >> 3)) * kSlotB + (ks & 7) * 16 * kRowB);
                 }
                 xf[K % (kAhead + 1)] = join(read_tr(p), read_tr(p + 4 * kRowB));
             };
@@ -702,9 +700,15 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[K % (kAhead + 1)], e[K], acc, 0, 0, 0);
                 if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
-                if constexpr (K == 0) { if (more) locals_read(block0); }
-                if constexpr (K >= 7 && K < 7 + kNB) { if (more) locals_mac(IC<K - 7>{}); }
-                if constexpr (K == 17) { if (more) locals_put(c + 1, U); }
+                // Local values of the next group (behind the last: of no use, but a branch costs more): reads, products and the result,
+                // a few instructions apart.  The tables are requested ahead of the step's stores: their wait then passes over them.
+                constexpr int A = TPW == 2 && U == 0 ? 9 : 2;
+                if constexpr (K >= A && (K - A) % 3 == 0 && (K - A) / 3 < kNB) locals_read(block0, uc, IC<(K - A) / 3>{});
+                if constexpr (K >= A + 2 && (K - A) % 3 == 2 && (K - A) / 3 < kNB) {
+                    locals_mac(IC<(K - A) / 3>{});
+                    if constexpr (U == TPW - 1) fetch_local(c + 2 < g.NG ? c + 2 : 0, IC<(K - A) / 3>{});
+                }
+                if constexpr (K == A + 3 * kNB) locals_put(c + 1, uc);
                 if constexpr (LATE) {
                     if constexpr (K >= 2 && K < 6) finish(prev, before, IC<K - 2>{});
                     if constexpr (K == 10) finish(prev, before, IC<4>{});
@@ -712,7 +716,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     if constexpr (K == 14) finish(prev, before, IC<6>{});
                 }
                 // far part: 8 local values of the tile and 8 of its group
-                if constexpr (K == STEPS - 5) far = *(const bf16x8*)((hw ? cloc + c * kVecB : loc + ((c & 1) * GT + tl) * kVecB) + l32 * 16);
+                if constexpr (K == STEPS - 5) far = *(const bf16x8*)(lane < 32 ? far_tile + (c & 1) * (GT * kVecB) + U * (kCompute * kVecB) : far_group + c * kVecB);
                 __builtin_amdgcn_sched_barrier(0);
             });
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, rt[U], acc, 0, 0, 0);
@@ -798,7 +802,7 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * kFrag;
     g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * kFrag;
     g.off_w = g.off_t + 2 * g.GT * kFrag;
-    g.table_bytes = g.off_w + (g.NT + g.NG) * 4;
+    g.table_bytes = g.off_w + (g.NT + 1) * 8;
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
     g.NX = g.NCp > 2 * g.GT ? g.NCp : 2 * g.GT;
     const int fixed = (g.NLm + g.NGp + g.NX) * kVecB + kTabFrags * kFrag;
@@ -817,7 +821,7 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
 
 hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st)
 {
-    const long long threads = g.off_w / 16 + g.NT + g.NG;
+    const long long threads = g.off_w / 16 + g.NT + 1;
     hipLaunchKernelGGL(k_nf_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, out);
     return hipGetLastError();
 }
