@@ -16,6 +16,11 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, const void* src)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory");
 }
+// ... from a scalar address and an offset of the lane's own
+__device__ __forceinline__ void lds_dma16(uint32_t lds, const void* base, uint32_t offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(offset), "s"(base) : "memory");
+}
 
 // One launch group addresses at most this many (layer, K|V) slabs; their base
 // pointers travel by value in the kernel arguments.

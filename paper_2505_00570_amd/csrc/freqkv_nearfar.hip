@@ -280,17 +280,18 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed.
+// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed: one of 32 immediates, found
+// by halves.
+template <int LO = 0, int HI = 32>
 __device__ __forceinline__ void wait_copies(int leaves)
 {
-    bool done = false;
-    static_for<20>([&](auto k) {
-        if (!done && leaves == k.value) {
-            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * k.value) : "memory");
-            done = true;
-        }
-    });
-    if (!done) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (HI - LO == 1) {
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LO) : "memory");
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (leaves < MID) wait_copies<LO, MID>(leaves);
+        else wait_copies<MID, HI>(leaves);
+    }
 }
 
 // A load that only some passes through a loop issue is awaited where it is issued: otherwise the compiler has to expect it in
@@ -375,37 +376,48 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         // % at 4092).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
         // the barrier after them.  Slots are taken in one direction round the ring on the way down and in the other on
         // the way up, so that leaf l and leaf l + R share one.
+        // A mover issues little besides copies: its own instructions, branches above all, are what bounds the first reading when
+        // rows come from the memory-side cache.  So leaves go out in runs (down, up), from a scalar base.
         const int mv = wave - kCompute;
-        const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
-        int issued = 0, slot = 0, dir = 1, leaf = g.NL - 1, vb = blockIdx.x, ht, c0;
+        const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + mv * 32 * kRowB;
+        const int row0 = mv * 32 + (lane >> 2);                                               // its row in the first of its two copies
+        const uint32_t part = (lane & 3) * 16;
+        int issued = 0, slot = 0, dir = 1, vb = blockIdx.x, ht, c0;
         bool down = true;
-        const char* src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
+        int leaf = g.NL - 1, left = g.NL;                                                     // next leaf, leaves left in the run
+        const char* src = task_base(vb, &ht, &c0);
         auto issue_until = [&](int limit) {
             while (issued < limit && vb < tasks) {
-                static_for<2>([&](auto i) {
-                    const int r0 = (mv * 2 + i.value) * 16;              // 16 rows per instruction
-                    const int row = min(leaf * kLeaf + r0 + (lane >> 2), g.n - 1);   // past the span: its last row again
-                    lds_dma16(ring_lds + slot * kSlotB + r0 * kRowB, src + (uint32_t)row * rowb);
-                });
-                ++issued;
-                bool done = false;
-                if (down && leaf == 0) {
-                    if (g.NL >= g.R) dir = -dir;             // turn round: leaf R goes where leaf 0 is
-                    else slot = wrap(slot + dir);
-                    down = false;
-                    leaf = g.R;
-                    done = g.NL <= g.R;
-                } else {
+                const int count = min(limit - issued, left);
+                for (int k = 0; k < count; ++k) {
+                    const uint32_t to = ring_lds + slot * kSlotB;
+                    static_for<2>([&](auto i) {                  // 16 rows each; past the span: its last row again
+                        const uint32_t row = (uint32_t)min(leaf * kLeaf + row0 + 16 * i.value, g.n - 1);
+                        lds_dma16(to + i.value * 16 * kRowB, src, row * rowb + part);
+                    });
                     slot = wrap(slot + dir);
                     leaf += down ? -1 : 1;
-                    done = !down && leaf == g.NL;
                 }
-                if (done) {
+                issued += count;
+                left -= count;
+                if (left) break;
+                if (down && g.NL > g.R) {                    // turn round: leaf R goes where leaf 0 is
+                    slot = wrap(slot - dir);
+                    dir = -dir;
+                    down = false;
+                    leaf = g.R;
+                    left = g.NL - g.R;
+                } else {
+                    if (down && g.NL == g.R) {
+                        slot = wrap(slot - dir);
+                        dir = -dir;
+                    }
                     down = true;
                     leaf = g.NL - 1;
+                    left = g.NL;
                     vb += gridDim.x;
-                    if (vb < tasks) src = task_base(vb, &ht, &c0) + (lane & 3) * 16;
                 }
+                if (down && vb < tasks) src = task_base(vb, &ht, &c0);
             }
         };
         const bool whole = g.NL < g.R;                       // the span and part of the next one fit the ring
