@@ -58,6 +58,19 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
+// f(IC<i>) for a uniform i in [0, N).  The cases end in different (empty) assembly: merged into one, what they do to the elements of
+// an array would keep that array in scratch memory.
+template <int N, class F>
+__device__ __forceinline__ void dispatch(int i, F&& f)
+{
+    static_for<N>([&](auto c) {
+        if (i == c.value) {
+            f(c);
+            asm volatile("; %0" :: "n"(c.value));
+        }
+    });
+}
+
 constexpr int kC = 32;                    // channels per workgroup
 constexpr int kRowB = kC * 2;             // bytes of one row in a ring slot
 constexpr int kLeaf = 128;                // span rows per leaf
@@ -66,6 +79,7 @@ constexpr int kVecB = kC * 8 * 2;         // bytes of 8 moments (or local values
 constexpr int kFrag = 1024;               // one operand fragment: 64 lanes x 8 bf16
 constexpr int kCompute = 4, kMovers = 4;  // waves
 constexpr int kNB = 3;                    // blocks of a group's neighbourhood: 512 rows or less, 128 to spare on both sides
+constexpr int kHeld = 4;                  // blocks that the movers keep in registers
 constexpr int kTabFrags = 6;              // table fragments kept in LDS
 constexpr int kLdsBytes = 160 * 1024;
 
@@ -382,6 +396,14 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + mv * 32 * kRowB;
         const int row0 = mv * 32 + (lane >> 2);                                               // its row in the first of its two copies
         const uint32_t part = (lane & 3) * 16;
+        // Most of a mover's registers are free, and four movers hold 4 blocks in them: the first whole ones behind the leaves that stay
+        // in the ring are read from it on the way down (each mover its part) and written back on the way up.  8188 rows: 495 ->
+        // 482 us, 6083 rows: 127 -> 121 (5 or 6 blocks need more registers than there are); with less to read again than that and a
+        // half (spans up to some 4600 rows) the instructions cost what the copies did: 31.5 -> 32.3 us at 4092.
+        const bool hold = g.NL - g.R >= 6 * kHeld;
+        const int hold0 = hold ? (g.R + 3) / 4 * 4 : g.NL, hold1 = hold ? hold0 + 4 * kHeld : g.NL;
+        u32x4 held[kHeld][4][2];
+        int copies = 0;                                      // leaves that came from memory
         int issued = 0, slot = 0, dir = 1, vb = blockIdx.x, ht, c0;
         bool down = true;
         int leaf = g.NL - 1, left = g.NL;                                                     // next leaf, leaves left in the run
@@ -391,10 +413,20 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 const int count = min(limit - issued, left);
                 for (int k = 0; k < count; ++k) {
                     const uint32_t to = ring_lds + slot * kSlotB;
-                    static_for<2>([&](auto i) {                  // 16 rows each; past the span: its last row again
-                        const uint32_t row = (uint32_t)min(leaf * kLeaf + row0 + 16 * i.value, g.n - 1);
-                        lds_dma16(to + i.value * 16 * kRowB, src, row * rowb + part);
-                    });
+                    if (!down && leaf >= hold0 && leaf < hold1) {
+                        char* const p = ring + slot * kSlotB + mv * 32 * kRowB + lane * 16;
+                        dispatch<kHeld>((leaf - hold0) >> 2, [&](auto b) {
+                            dispatch<4>(leaf & 3, [&](auto l) {
+                                static_for<2>([&](auto i) { *(u32x4*)(p + i.value * 16 * kRowB) = held[b.value][l.value][i.value]; });
+                            });
+                        });
+                    } else {
+                        static_for<2>([&](auto i) {                  // 16 rows each; past the span: its last row again
+                            const uint32_t row = (uint32_t)min(leaf * kLeaf + row0 + 16 * i.value, g.n - 1);
+                            lds_dma16(to + i.value * 16 * kRowB, src, row * rowb + part);
+                        });
+                        ++copies;
+                    }
                     slot = wrap(slot + dir);
                     leaf += down ? -1 : 1;
                 }
@@ -422,12 +454,26 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         };
         const bool whole = g.NL < g.R;                       // the span and part of the next one fit the ring
         issue_until(min(g.R, g.NL));
-        int p0 = 0;
+        // of the task: counts at its start; slot of its last leaf and where to go from there; copies up to leaf `end` of the results
+        int p0 = 0, d0 = 0, at0 = 0, at_dir = 1;
+        auto copied = [&](int end) { return d0 + g.NL + max(0, min(end, hold0) - g.R) + max(0, end - hold1); };
         for (int v = blockIdx.x; v < tasks; v += gridDim.x) {
+            int at = wrap(at0 - at_dir * (4 * g.NC - g.NL));         // slot of the block's last leaf
             for (int i = g.NC - 1; i >= 0; --i) {
-                wait_copies(issued - (p0 + g.NL - 4 * i));
+                wait_copies(copies - (d0 + g.NL - 4 * i));
                 lds_barrier();
                 issue_until(p0 + min((i == g.NC - 1 ? 0 : g.NL - 4 * (i + 1)) + g.R, g.NL));
+                // (there before the next barrier, and so before a copy can take their slots)
+                if (4 * i >= hold0 && 4 * i < hold1) {
+                    const char* p[4];
+                    static_for<4>([&](auto l) { p[l.value] = ring + wrap(at + at_dir * (3 - l.value)) * kSlotB + mv * 32 * kRowB + lane * 16; });
+                    dispatch<kHeld>(i - hold0 / 4, [&](auto b) {
+                        static_for<4>([&](auto l) {
+                            static_for<2>([&](auto k) { held[b.value][l.value][k.value] = *(const u32x4*)(p[l.value] + k.value * 16 * kRowB); });
+                        });
+                    });
+                }
+                at = wrap(at + 4 * at_dir);
             }
             lds_barrier();
             if (whole) issue_until(p0 + g.R);
@@ -436,11 +482,14 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             for (int t = 0; t < g.NT; t += kCompute) {
                 const int first = words[t][0] & 255;
                 const int end = (int)(words[min(t + kCompute, g.NT) - 1][0] & 255) + NK;
-                wait_copies(issued - (p0 + g.NL + max(0, end - g.R)));
+                wait_copies(copies - copied(end));
                 lds_barrier();
                 issue_until(p0 + (whole ? g.R : g.NL + first));
             }
             p0 += g.NL + max(0, g.NL - g.R);
+            d0 = copied(g.NL);
+            at0 = wrap(at0 - at_dir);
+            at_dir = -at_dir;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;

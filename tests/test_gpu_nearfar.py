@@ -17,8 +17,8 @@ CASES = [
     (1, 1, 2, 32, 257, 0.25), (1, 1, 1, 32, 383, 0.2), (1, 1, 1, 32, 384, 0.25), (1, 1, 1, 32, 511, 0.44),
     (1, 1, 1, 32, 512, 0.45), (1, 1, 1, 32, 513, 0.6), (2, 1, 9, 32, 640, 0.5), (1, 1, 1, 32, 1000, 0.999),
     (1, 1, 1, 96, 1024, 0.5), (1, 1, 1, 32, 1025, 0.5), (1, 1, 1, 32, 2048, 0.25), (1, 1, 1, 32, 2100, 0.375),
-    (1, 1, 1, 32, 4096, 0.5), (1, 1, 1, 32, 6083, 0.5), (1, 1, 1, 32, 8192, 0.2), (1, 1, 1, 32, 8192, 0.9),
-    (1, 1, 1, 32, 12284, 0.5), (1, 3, 100, 32, 1536, 0.5),
+    (1, 1, 1, 32, 4096, 0.5), (1, 1, 1, 32, 4864, 0.5), (1, 1, 1, 32, 4993, 0.5), (1, 1, 1, 32, 6083, 0.5), (1, 1, 1, 32, 8192, 0.2), (1, 1, 1, 32, 8192, 0.9),
+    (1, 1, 1, 32, 12284, 0.5), (1, 3, 100, 32, 1536, 0.5), (1, 3, 60, 32, 5377, 0.6),
 ]
 
 
