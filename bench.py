@@ -2,7 +2,7 @@
 """Benchmark of the FreqKV compression hot path on one MI355X.
 
 A step = one compression trigger over the whole cache of the workload (all layers' K and V: DCT -> keep the
-low half -> inverse -> in-place write, as one factored transform kernel, or fold/convert -> contraction with
+low half -> inverse -> in-place write, as one kernel (near/far form), or fold/convert -> contraction with
 --dense) through the C ABI, inputs resident in HBM.
 Default workload: the LLaMA-3-8B GQA cache of the 128K iterative prefill (32 layers x 8 KV heads
 x head_dim 128, bf16, window 8192, 4 sinks, ratio 0.5): 512 head-tensors, span 8188 -> 4094.
@@ -25,11 +25,11 @@ MFMA_F16_PEAK_TFLOPS = 2500.0      # MI355X dense fp16/bf16 MFMA
 HBM_PEAK_GBS = 8000.0
 # HBM bytes (read + write) of the contraction of one trigger (two launches with the two-level fold), from
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled by what the same counters read for the library's plain copy
-# kernel (profiles/contract_llama3_8b_128k_pmc.txt).
+# kernel (profiles/compress_llama3_8b_128k_pmc.txt).
 TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * (5.244e5 + 9.187e5) + 1.0 * (2.62e5 + 5.24e5)) * 1024}
 TRAFFIC_BYTES_SINGLE_FOLD = {"llama3_8b_128k": (2.0 * 2.622e6 + 1.0 * 5.24e5) * 1024}
-# the same for the factored transform's single kernel (profiles/fast_llama3_8b_128k_pmc.txt)
-FAST_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.4e5 + 1.0 * 5.24e5) * 1024}
+# the same for the near/far form's single kernel (profiles/compress_llama3_8b_128k_pmc.txt)
+NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.278e5 + 1.0 * 5.24e5) * 1024}
 # the same for k_attend_partial (profiles/attend_llama3_8b_128k_pmc.txt)
 ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.248e5 + 1.0 * 1608) * 1024}
 # the same for k_attend_prefill (profiles/prefill_llama3_8b_128k.txt)
@@ -378,7 +378,7 @@ def main():
     ap.add_argument("--two-level", action="store_true",
                     help="use the two-level fold wherever it applies, also for spans below its default threshold")
     ap.add_argument("--dense", action="store_true",
-                    help="use the matrix form (fp16 MFMA contraction) where the factored transform would be chosen (comparison)")
+                    help="use the matrix form (fp16 MFMA contraction) where the near/far form would be chosen (comparison)")
     ap.add_argument("--stream", action="store_true",
                     help="run the workload's whole trigger schedule (total_tokens through the window), every trigger timed")
     ap.add_argument("--sustain-seconds", type=float, default=2.0,
@@ -518,17 +518,16 @@ def main():
                 "bytes_per_launch": p.bytes_algorithmic, "measured_copy_gbs": copy_gbs,
                 "frac_of_measured_copy": gbs / copy_gbs if copy_gbs else None}
     elif variant == 6:
-        # the factored transform: one kernel per trigger that reads the span and writes the retained rows; its
-        # matrix work is a small fraction of the dense count, so HBM is the roofline it is held against
+        # the near/far form (what runs at these head sizes): one kernel per trigger that reads the span and writes the retained
+        # rows; its matrix work is a small fraction of the dense count, so HBM is the roofline it is held against
         bytes_launch = p.bytes_algorithmic / per_trigger
         gbs = bytes_launch / (ms_contract * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "k_fast", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": gbs / HBM_PEAK_GBS, "traffic": FAST_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload),
+        roof = {"bound": "hbm", "kernel": "k_nearfar", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": gbs / HBM_PEAK_GBS, "traffic": NEARFAR_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload),
                 "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run of this kernel (profiles/), "
                                   "not measured by this run",
                 "launches_per_trigger": per_trigger, "ms_per_launch": ms_contract, "bytes_per_launch": bytes_launch,
                 "measured_copy_gbs": copy_gbs, "frac_of_measured_copy": gbs / copy_gbs,
-                "executed_tflops": flops_launch / (ms_contract * 1e-3) / 1e12,
                 "sustained_frac": (p.bytes_algorithmic / (sustained["ms_main_kernel_per_trigger"] * 1e-3) / 1e9 / HBM_PEAK_GBS)
                 if sustained else None}
     else:
@@ -550,13 +549,14 @@ def main():
         sustained["gbs_algorithmic"] = p.bytes_algorithmic / (sustained["ms_per_step"] * 1e-3) / 1e9
 
     names = {1: "one-level folded matrix form", 2: "plain matrix form", 3: "fp32 matrix form", 4: "dropping",
-             5: "two-level folded matrix form", 6: "factored transform"}
+             5: "two-level folded matrix form", 6: "near/far form"}
     out = {
         "metric": "KV compression throughput (GB/s KV in)",
         "value": value, "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f16" if elem == 2 else "f32",
-        "dtype_note": "bf16 cache; fp16 MFMA operands, fp32 accumulation" if elem == 2 else "fp32 cache, fp32 FMA",
+        "dtype": "f32" if elem == 4 else "bf16" if variant == 6 else "f16",
+        "dtype_note": ("fp32 cache, fp32 MFMA" if elem == 4 else "bf16 cache and MFMA operands, fp32 accumulation" if variant == 6
+                       else "bf16 cache; fp16 MFMA operands, fp32 accumulation"),
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.n_layers} layers x {wl.batch} x {wl.n_heads} KV heads x "
                                f"head_dim {wl.head_dim}, window {wl.window}, {wl.n_sink} sinks, ratio "
@@ -564,7 +564,8 @@ def main():
                                f"per trigger; one trigger per step",
                    "variant": variant, "form": names.get(variant, "?"),
                    "operator": "dropping" if args.dropping else "freqkv"},
-        "tflops_executed": p.flops_executed / (dt / args.steps) / 1e12,
+        # (the plan's count is that of the form it names, not of the near/far form)
+        "tflops_executed": p.flops_executed / (dt / args.steps) / 1e12 if variant != 6 else None,
         "tflops_dense_equivalent": p.flops_dense / (dt / args.steps) / 1e12,
         "gbs_algorithmic": p.bytes_algorithmic / (dt / args.steps) / 1e9,
         "frac_hbm_roofline": p.bytes_algorithmic / (dt / args.steps) / 1e9 / HBM_PEAK_GBS,

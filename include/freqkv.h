@@ -65,10 +65,19 @@ typedef enum {
 #define FREQKV_FLAG_TWO_LEVEL_FOLD 0x10u /* use the two-level fold wherever it applies (span a multiple of 4, even
                                          retained length), whatever the sizes.  Not with SINGLE_FOLD */
 
-#define FREQKV_FLAG_DENSE 0x20u      /* never use the factored transform (variant 6); the matrix forms (variants 1, 2, 5)
-                                         run instead (SINGLE_FOLD and TWO_LEVEL_FOLD imply it).  Default: spans n = 4pq with a compiled factorization (8188 = 4*23*89,
-                                         4092 = 4*11*93, 2044 = 4*7*73, 1020 = 4*3*85, and 1260, 140 for tests) at retain_ratio 0.5 on bf16 caches take the
-                                         factored form, which needs no workspace */
+#define FREQKV_FLAG_DENSE 0x20u      /* use neither the near/far form nor the factored transform (variant 6); the matrix forms
+                                         (variants 1, 2, 5) run instead (SINGLE_FOLD and TWO_LEVEL_FOLD imply it) */
+
+/*
+ * Forms of the compression on bf16 caches, without the flags above:
+ *   near/far   head_dim a multiple of 32, retain_ratio >= 0.2, spans of 128 to some 12000 rows, a span of less than
+ *              4 GiB: exact entries close to the diagonal, interpolated ones further away (error below 5e-3 of the
+ *              RMS).  freqkv_plan keeps naming the form that the shape would have otherwise, with that form's
+ *              sizes and counts; the workspace that it asks for has to be there, but stays unused.
+ *   variant 6  the factored transform, head_dim not a multiple of 32, retain_ratio 0.5, spans n = 4pq with a compiled
+ *              factorization (8188 = 4*23*89, 4092 = 4*11*93, 2044 = 4*7*73, 1020 = 4*3*85, and 1260, 140 for tests)
+ *   variants 1, 2, 5  the matrix forms: everything else, and what the flags ask for
+ */
 
 /*
  * Memory description of the cache ("layout"): everything the scalar arguments of
@@ -107,7 +116,7 @@ typedef struct freqkv_plan {
     int32_t retained_len;       /* Lc = clamp(floor(retain_ratio*n + 1e-9), 1, n)                */
     int32_t new_len;            /* cache length after the call: n_sink + Lc + (cur_len - window) */
     int32_t head_tensors;       /* 2 * n_layers * batch * n_heads                                */
-    int32_t variant;            /* 0 none (no-op or ratio 1), 1 folded fp16-MFMA, 2 plain fp16-MFMA, 3 fp32 FMA,
+    int32_t variant;            /* 0 none (no-op or ratio 1), 1 folded fp16-MFMA, 2 plain fp16-MFMA, 3 fp32,
                                    4 dropping (row moves only), 5 two-level folded fp16-MFMA,
                                    6 factored transform (prime-factor DFT stages on the matrix cores, LDS resident) */
     int32_t reserved;
@@ -115,7 +124,7 @@ typedef struct freqkv_plan {
     size_t  workspace_min_bytes;/* smallest scratch accepted (one (layer,K|V) slab per pass)     */
     size_t  basis_bytes;        /* device memory the library itself holds for this (n, Lc)       */
     double  flops_dense;        /* 2*Lc*n*d per head-tensor, summed: the fused operator as one contraction */
-    double  flops_executed;     /* what the chosen variant executes (no padding counted)         */
+    double  flops_executed;     /* what the named variant executes (no padding counted)          */
     double  bytes_algorithmic;  /* (n + Lc)*d*e per head-tensor + 2*(cur_len-window)*d*e, summed */
 } freqkv_plan_t;
 
@@ -169,8 +178,9 @@ FREQKV_API freqkv_status_t freqkv_plan(const freqkv_layout_t* layout, int n_head
  *            synchronise the device and never reads results back.  The first call for a new
  *            (device, n, Lc, dtype, flags) builds and caches the basis table (one allocation).
  * retain_ratio == 1 (Lc == n) is the identity and enqueues nothing (FREQKV_OK).
- * Value range (bf16 caches): the matrix cores take fp16 operands, whose range is narrower than bfloat16's.
- * Every head-tensor (every 8- or 16-channel slice of one in the factored form) is therefore scaled by an exact
+ * Value range (bf16 caches): the near/far form takes the cache values as they are, bfloat16, and accumulates in fp32: any
+ * finite magnitude, and an inf or nan stays in its channel.  The other forms take fp16 operands, whose range is narrower.
+ * There every head-tensor (every 8- or 16-channel slice of one in the factored form) is scaled by an exact
  * power of two, chosen from the largest magnitude of its span, on its way in and back on its way out, so
  * finite cache values of any magnitude neither overflow nor sink into fp16 subnormals; only values more
  * than 2^24 times smaller than the largest of their head-tensor (slice) lose precision.  An inf or
@@ -295,7 +305,7 @@ FREQKV_API freqkv_status_t freqkv_power_spectrum(const void* k, const void* v, f
 
 /* Result of the chunk-attention buffer-plan query (host arithmetic only). */
 typedef struct freqkv_prefill_plan {
-    size_t  workspace_bytes;    /* rotary table (fp32), rotated keys and transposed values (fp16)             */
+    size_t  workspace_bytes;    /* rotary table (fp32), rotated keys and transposed values (fp16), results of parts */
     int32_t key_tiles;          /* ceil(cur_len / 32)                                                         */
     int32_t query_blocks;       /* ceil(q_len / 32)                                                           */
     double  flops;              /* 4 * head_dim per (query, visible row), summed                              */
@@ -314,7 +324,8 @@ FREQKV_API freqkv_status_t freqkv_attend_prefill_plan(const freqkv_layout_t* lay
  * freqkv_attend_decode (its last query is this call's last query).
  *   q, out   [n_layers][batch][n_q_heads][q_len][head_dim], dense, bfloat16
  *   lse      optional [n_layers][batch][n_q_heads][q_len] fp32
- *   layout.workspace  at least freqkv_attend_prefill_plan(...).workspace_bytes, 256-byte aligned
+ *   layout.workspace  freqkv_attend_prefill_plan(...).workspace_bytes, 256-byte aligned; with less the key range is cut into
+ *                     fewer parts (few queries are then slower), down to what the operands alone need
  * head_dim 128 and bfloat16 caches only (FREQKV_E_UNSUPPORTED otherwise).  Operands of the matrix cores are
  * fp16 (cache values are exact in fp16; rotated keys and queries keep 11 significant bits), accumulation,
  * softmax and the running sums are fp32.  The call only enqueues work on `stream`.
