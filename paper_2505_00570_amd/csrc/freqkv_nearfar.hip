@@ -17,8 +17,14 @@
 //     group    the GT tiles of one step: 8 local values from all the blocks further away
 // Per channel that is about 1.1 M multiply-adds at 8188 -> 4094 against 33.5 M for the dense operator, all of them on
 // the matrix cores with bf16 operands: the cache values enter as they are (no scale, no conversion, no range guard),
-// the exact entries as the sum of two bf16 parts (16 significant bits; the second part only around the
-// tile, where entries are large), everything of the far part as one bf16 part.  Error 1e-4 of a channel's RMS.
+// the exact entries as the sum of two bf16 parts (16 significant bits; the second part only around the tile, where
+// entries are large).  The far part has two parts where they cost little, and one elsewhere: the moment tables (a product
+// of 8 moments has 16 result rows: the second parts take the other 8), the tables from local values to results (one more
+// product per tile) and, with windows of 3 leaves, the tiles' local values (the same product).  So the rms error stays
+// below that of a matrix of the operator in fp16, at every ratio: before the result is rounded, on white rows,
+// 8188 -> 4094 1.5e-4 of the RMS (fp16 matrix 1.6e-4), 8188 -> 2047 1.4e-4 (1.6e-4), 6083 -> 2737 1.6e-4 (1.8e-4); with
+// one part throughout the far field 1.8e-4, 2.0e-4 and 1.9e-4.  These second parts take 0.5 % of the time of 512 head-tensors
+// x 8188 rows at ratio 1/2, 1.7 % at 1/4 (two steps more of exact entries among them).
 //
 // One workgroup owns 32 channels (64 bytes of every row) of one head-tensor and streams the span twice through a ring
 // of LDS slots (a leaf each): first for the moments, then for the result rows.  What bounds it is moving the rows:
@@ -95,11 +101,11 @@ __host__ __device__ inline TileAt tile_at(const NfGeom& g, int t)
     r.leaf0 = l < 0 ? 0 : (l > top ? top : l);
     return r;
 }
-// First of the 16-row steps of the window that get the second bf16 part: 8 to 23 rows ahead of the tile.
+// First of the 16-row steps of the window that get the second bf16 part: the tile in their middle.
 __host__ __device__ inline int tile_lo_step(const NfGeom& g, int t, int leaf0)
 {
-    const int a = (int)((unsigned)(32 * t) * (unsigned)g.n / (unsigned)g.Lc);
-    const int k = ((a - 8) >> 4) - leaf0 * 8;
+    const int a = (int)((unsigned)(32 * t) * (unsigned)g.n / (unsigned)g.Lc), rows = 32 * g.n / g.Lc;
+    const int k = (2 * (a - leaf0 * kLeaf) + rows - 16 * g.NLO + 16) >> 5;
     const int top = 8 * g.NK - g.NLO;
     return k < 0 ? 0 : (k > top ? top : k);
 }
@@ -190,6 +196,9 @@ __device__ double near_entry(const NfGeom& g, int slot, int m_in, int row_in)
     return v / (2.0 * n);
 }
 
+// What a bf16 holds of x; the rest, rounded in its turn, is its second part.
+__device__ double first_part(double x) { return (double)(float)(__bf16)(float)x; }
+
 // What the kernel wants to know of tile t, in one scalar load: first leaf of the window, first step with second parts, table
 // slot | slot of the wave's next tile (of this task or the next), first block of the next group's neighbourhood.
 __device__ u32x2 tile_words(const NfGeom& g, int t)
@@ -232,22 +241,26 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
                 k = k - 8 * g.NK + tile_lo_step(g, t, tile_at(g, t).leaf0);
             }
             x = g.out_scale * near_entry(g, slot, l32, 16 * k + 8 * hw + i);
-            if (second) x -= (double)(float)(__bf16)(float)x;
+            if (second) x -= first_part(x);
         } else if (byte < g.off_m) {
-            // moments: [slot][4 steps of 32 rows], 16 (8 used) moments x 32 rows
+            // moments: [slot][4 steps of 32 rows], 8 moments (then the second parts of their entries) x 32 rows
             const int f = (int)((byte - g.off_v) / kFrag), slot = f >> 2;
             const int leaf = g.v_slots == 2 ? (slot ? g.NL - 1 : 0) : slot;
             const long long j = 128LL * leaf + (f & 3) * 32 + 8 * g4 + i;
             const Iv iv = leaf_iv(g, leaf);
-            if (l16 < 8 && j < g.n && iv.h > 0) {
+            if (j < g.n && iv.h > 0) {
                 const long long ph = ((2 * j + 1) * (long long)g.Lc) % (4LL * g.n);      // cos(Lc b_j)
-                x = lagrange(l16, (j + 0.5 - iv.c) / iv.h) * cospi((double)ph / (2.0 * n)) / 128.0;
+                x = lagrange(l16 & 7, (j + 0.5 - iv.c) / iv.h) * cospi((double)ph / (2.0 * n)) / 128.0;
+                if (l16 >= 8) x -= first_part(x);
             }
         } else if (byte < g.off_c) {
-            // coarse moments of a block from those of its 4 leaves
+            // coarse moments of a block from those of its 4 leaves, and their second parts
             const int b = (int)((byte - g.off_m) / kFrag), leaf = 4 * b + g4;
             const Iv lv = leaf_iv(g, leaf), bv = block_iv(g, b);
-            if (l16 < 8 && lv.h > 0) x = lagrange(l16, (lv.node(i) - bv.c) / bv.h) * 0.25;
+            if (lv.h > 0) {
+                x = lagrange(l16 & 7, (lv.node(i) - bv.c) / bv.h) * 0.25;
+                if (l16 >= 8) x -= first_part(x);
+            }
         } else if (byte < g.off_f) {
             // local values of two groups from 4 blocks
             const int f = (int)((byte - g.off_c) / kFrag), kst = g.NCp / 4;
@@ -270,12 +283,15 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
                 if (!near || shared) x = far_kernel(tile_iv(g, t).node(l16 & 7), lv.node(i), n, near) * 128.0 / n;
             }
         } else {
-            // results of a tile from its 8 local values and the 8 of its group; [any but the last group | the last][tile]
-            const int f = (int)((byte - g.off_t) / kFrag);
+            // results of a tile from its 8 local values and the 8 of its group; [any but the last group | the last][tile], then the
+            // same again for the second product: with windows of 2 leaves the second parts of all 16; with 3 the second parts of
+            // the tile's 8 and, for the second parts of the local values themselves, its first parts once more
+            const int ff = (int)((byte - g.off_t) / kFrag), second = ff >= 2 * g.GT, f = ff - second * 2 * g.GT;
             const int gr = f < g.GT ? 0 : g.NG - 1, t = gr * g.GT + f % g.GT, m = 32 * t + l32;
             if (m < g.Lc) {
-                const Iv iv = hw ? group_iv(g, gr) : tile_iv(g, t);
+                const Iv iv = hw && !(second && g.NK == 3) ? group_iv(g, gr) : tile_iv(g, t);
                 x = g.out_scale * lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
+                if (second && !(hw && g.NK == 3)) x -= first_part(x);
             }
         }
         v[i] = (__bf16)(float)x;
@@ -342,10 +358,11 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     char* const ring = smem;
     char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8]
     char* const cloc = mom + g.NLm * kVecB;          // [group]...
-    char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]...
+    char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]..., with TWO_LOC the second parts behind them
     char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come
     char* const ltab = loc + g.NX * kVecB;           // moments of an inner leaf (SHIFTS) | of an inner block | of the last block
     constexpr int GT = kCompute * TPW;
+    constexpr bool TWO_LOC = NK == 3;                // local values of tiles in two parts
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -507,11 +524,18 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     const int lane16 = lane * 16;
     auto table = [&](int off) { return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(tabs, lane16, off, 0)); };
     auto lds_table = [&](int f) { return *(const bf16x8*)(ltab + f * kFrag + lane * 16); };
-    // the first 8 (of 16) result rows of a moment product, or all 16: 4 per lane, [vector][channel][8]
-    auto put8 = [&](char* vec, int h, f32x4 a) {
+    // Moment products have the first parts of the table in result rows 0..7 and the second parts in 8..15: the half-waves add
+    // them up, the lower for channels 0..15 (a0), the upper for 16..31 (a1).  [channel][8], 4 per lane.
+    auto put_moments = [&](char* vec, f32x4 a0, f32x4 a1) {
         NF_LANE();
-        if (g4 < 2) *(u32x2*)(vec + h * 256 + vec16 + g4 * 8) = pack4(a);
+        f32x4 sum;
+        static_for<4>([&](auto i) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0[i.value]), __float_as_uint(a1[i.value]), false, false);
+            sum[i.value] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        });
+        *(u32x2*)(vec + hw * 256 + vec16 + (g4 & 1) * 8) = pack4(sum);
     };
+    // all 16 result rows of a product: two vectors
     auto put16 = [&](char* vec, int h, f32x4 a) {
         NF_LANE();
         *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a);
@@ -535,25 +559,39 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         if constexpr (decltype(k)::value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
         la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf, la, 0, 0, 0);
     };
-    auto locals_put = [&](int gr, auto u) { *(u32x2*)(local_out + (gr & 1) * (GT * kVecB) + (TPW == 2 ? u.value * 256 : 0)) = pack4(la); };
+    auto locals_put = [&](int gr, auto u) {
+        char* const p = local_out + (gr & 1) * (GT * kVecB) + (TPW == 2 ? u.value * 256 : 0);
+        const u32x2 first = pack4(la);
+        *(u32x2*)p = first;
+        if constexpr (TWO_LOC) {
+            static_for<4>([&](auto i) {
+                la[i.value] -= __uint_as_float(i.value & 1 ? first[i.value / 2] & 0xffff0000u : first[i.value / 2] << 16);
+            });
+            *(u32x2*)(p + 2 * GT * kVecB) = pack4(la);
+        }
+    };
     auto block_moments = [&](int b) {
         NF_LANE();
         const bf16x8 m = lds_table(b == g.NC - 1 ? 5 : 4);
+        f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         static_for<2>([&](auto h) {
-            f32x4 a = {0.f, 0.f, 0.f, 0.f};
-            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + (4 * b + g4) * kVecB + h.value * 256 + vec16), a, 0, 0, 0);
-            put8(cmom + b * kVecB, h.value, a);
+            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + (4 * b + g4) * kVecB + h.value * 256 + vec16), a[h.value], 0, 0, 0);
         });
+        put_moments(cmom + b * kVecB, a[0], a[1]);
     };
     bf16x8 vt[4];                                    // moments of the wave's next leaf
     auto fetch_moments = [&](int leaf) {
         const int off = g.off_v + (SHIFTS ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
         static_for<4>([&](auto k) { vt[k.value] = table(off + k.value * kFrag); });
     };
-    bf16x8 rt[TPW];                                  // results from local values
+    bf16x8 rt[TPW], rt2[TPW];                        // results from local values: first and second product
     auto fetch_results = [&](bool last) {
-        static_for<TPW>([&](auto u) { rt[u.value] = table(g.off_t + ((last ? GT : 0) + wave + kCompute * u.value) * kFrag); });
-        static_for<TPW>([&](auto u) { pin(rt[u.value]); });
+        static_for<TPW>([&](auto u) {
+            const int off = g.off_t + ((last ? GT : 0) + wave + kCompute * u.value) * kFrag;
+            rt[u.value] = table(off);
+            rt2[u.value] = table(off + 2 * GT * kFrag);
+        });
+        static_for<TPW>([&](auto u) { pin(rt[u.value]); pin(rt2[u.value]); });
     };
     const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
     static_for<kNB>([&](auto k) { fetch_local(0, k); });
@@ -607,8 +645,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                             a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], xa[k.value][h.value], a[h.value], 0, 0, 0);
                         });
                     });
-                    put8(mom + leaf * kVecB, 0, a[0]);
-                    put8(mom + leaf * kVecB, 1, a[1]);
+                    put_moments(mom + leaf * kVecB, a[0], a[1]);
                     if (!SHIFTS) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
                 }
                 if (i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
@@ -739,7 +776,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             // 8 NK matrix instructions with the first parts, then NLO with the second; operands are read kAhead instructions
             // ahead, and the order is pinned: left alone the compiler reads the whole window first and runs out of registers
             constexpr int kAhead = 3;
-            bf16x8 xf[kAhead + 1], far;
+            bf16x8 xf[kAhead + 1], far, far2;
             auto fetch_rows = [&](auto kc) {
                 constexpr int K = decltype(kc)::value;
                 const char* p;
@@ -776,11 +813,16 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     if constexpr (K == 12) finish(prev, before, IC<5>{});
                     if constexpr (K == 14) finish(prev, before, IC<6>{});
                 }
-                // far part: 8 local values of the tile and 8 of its group
-                if constexpr (K == STEPS - 5) far = *(const bf16x8*)(lane < 32 ? far_tile + (c & 1) * (GT * kVecB) + U * (kCompute * kVecB) : far_group + c * kVecB);
+                // far part: 8 local values of the tile and 8 of its group; for the second product the tile's, first and second parts
+                if constexpr (K == STEPS - 5) {
+                    const char* const p = far_tile + (c & 1) * (GT * kVecB) + U * (kCompute * kVecB);
+                    far = *(const bf16x8*)(lane < 32 ? p : far_group + c * kVecB);
+                    if constexpr (TWO_LOC) far2 = *(const bf16x8*)(p + (lane < 32 ? 0 : 2 * GT * kVecB));
+                }
                 __builtin_amdgcn_sched_barrier(0);
             });
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, rt[U], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TWO_LOC ? far2 : far, rt2[U], acc, 0, 0, 0);
             if (SHIFTS && next_slot != cur_slot) {           // at the ends of the span only
                 fetch_entries(next_slot);
                 static_for<STEPS>([&](auto k) { pin(e[k.value]); });
@@ -826,9 +868,11 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     g.n = n; g.Lc = Lc; g.d = head_dim;
     const double tile_rows = 32.0 * n / Lc;
     // The window has 32 rows to spare on the left of a tile and must keep some 24 on its right: 2 leaves up to 72 rows
-    // per tile (ratios from 0.44), else 3 (ratios from 0.2: 160 rows, which also is what the second parts cover).
+    // per tile (ratios from 0.44), else 3 (ratios from 0.2: 160 rows).  Second parts around the tile: 8 to 24 rows beyond it on
+    // both sides with 6 and 12 steps, 20 or more with 10 (tiles of up to 104 rows, ratios from 0.31).  At ratio 0.25 the
+    // rms error on autoregressive rows (0.9) is 0.83e-4 with 10 steps and 0.61e-4 with 12, 0.81e-4 in the fp16 matrix form.
     g.NK = tile_rows <= 72.0 ? 2 : 3;
-    g.NLO = g.NK == 2 ? 6 : (tile_rows <= 136.0 ? 10 : 12);
+    g.NLO = g.NK == 2 ? 6 : (tile_rows <= 104.0 ? 10 : 12);
     g.GT = kCompute * (g.NK == 2 ? 2 : 1);
     g.NL = (n + kLeaf - 1) / kLeaf;
     if (g.NL < g.NK) g.NL = g.NK;
@@ -862,10 +906,11 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     g.off_c = g.off_m + g.NC * kFrag;
     g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * kFrag;
     g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * kFrag;
-    g.off_w = g.off_t + 2 * g.GT * kFrag;
+    g.off_w = g.off_t + 4 * g.GT * kFrag;
     g.table_bytes = g.off_w + (g.NT + 1) * 8;
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
-    g.NX = g.NCp > 2 * g.GT ? g.NCp : 2 * g.GT;
+    const int loc_vectors = (g.NK == 2 ? 2 : 4) * g.GT;
+    g.NX = g.NCp > loc_vectors ? g.NCp : loc_vectors;
     const int fixed = (g.NLm + g.NGp + g.NX) * kVecB + kTabFrags * kFrag;
     g.R = (kLdsBytes - fixed) / kSlotB;
     int need = (int)std::floor((2 * kCompute - 1) * tile_rows / kLeaf) + 1 + g.NK;
@@ -900,10 +945,10 @@ hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tab
         if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
         else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
     } else if (g.NLO == 10) {
-        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 10, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
-        else          hipLaunchKernelGGL((k_nearfar<3, 10, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        hipLaunchKernelGGL((k_nearfar<3, 10, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
     } else {
-        hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
     }
     return hipGetLastError();
 }

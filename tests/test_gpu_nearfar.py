@@ -1,12 +1,15 @@
 """GPU parity of the near/far form against the fp64 CPU oracle, every element: spans around the edges of its leaves
 (128 rows), blocks (512) and ring, ratios on both sides of its window sizes, odd lengths, shared and separate tables."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2505_00570_amd as fk
 from paper_2505_00570_amd import binding, synth
 
-from _util import TOL_BF16
+from oracle import freqkv_oracle as orc
+
+from _util import TOL_BF16, f64
 from test_gpu_parity import _check_all_heads, _mk, _run, _say
 
 pytestmark = pytest.mark.gpu
@@ -54,6 +57,29 @@ def test_nearfar_nan_stays_in_its_channel():
     ok = [c for c in range(64) if c not in (17, 40)]
     assert not torch.isfinite(got[:, 17]).any() and not torch.isfinite(got[:, 40]).any()
     assert torch.equal(got[:, ok], clean[0, 0, 0, 4:p.new_len].float()[:, ok])
+
+
+@pytest.mark.parametrize("rho", [0.0, 0.9])
+@pytest.mark.parametrize("span,ratio", [(1020, 0.25), (2044, 0.25), (8188, 0.25), (6083, 0.25), (4095, 0.2), (2996, 0.3125), (6083, 0.45),
+                                        (4999, 0.5), (4092, 0.5), (3000, 0.9)])
+def test_nearfar_is_no_further_off_than_the_matrix_forms(span, ratio, rho):
+    """Before the result is rounded to bf16: rms distance from 64 bits, white rows and rows that are correlated along the
+    tokens.  The matrix forms round every entry once to fp16."""
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=1, head_dim=64, window=span, n_sink=0, retain_ratio=ratio,
+                     total_tokens=span)
+    x = np.random.default_rng(span).standard_normal((2, span, 64))
+    for t in range(1, span):
+        x[:, t] += rho * x[:, t - 1]
+    rows = torch.from_numpy(x).to(torch.bfloat16)
+    err = []
+    for flags in (0, fk.FLAG_DENSE):
+        k, v = (rows[i].to("cuda").reshape(1, 1, 1, span, 64).clone() for i in range(2))
+        rc, p, tap = _run(k, v, wl, span, flags=flags)
+        assert rc == 0
+        ref = np.stack([orc.compress_span(f64(rows[i]), p.retained_len) for i in range(2)])
+        err.append(np.sqrt(((f64(tap).reshape(ref.shape) - ref) ** 2).mean() / (ref ** 2).mean()))
+    _say(f"near/far span {span} ratio {ratio} rho {rho}: rms error {err[0]:.3e}, matrix form {err[1]:.3e}")
+    assert err[0] <= err[1]
 
 
 @pytest.mark.parametrize("layers,lens", [(1, [140, 133, 400, 132, 12]), (33, [132, 133, 250, 3, 132])])
