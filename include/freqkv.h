@@ -147,7 +147,8 @@ typedef struct freqkv_attend_plan {
     int32_t chunk_rows;         /* rows per chunk                                                    */
     int32_t heads_together;     /* query heads of one KV group that one workgroup serves (1, 2 or 4) */
     int32_t reserved;
-    size_t  workspace_bytes;    /* scratch for the per-chunk softmax states                          */
+    size_t  workspace_bytes;    /* scratch for the per-chunk softmax states; a longer cache may need less (fewer
+                                   chunks suit it better)                                            */
     double  bytes_algorithmic;  /* K and V rows [0, cur_len) read once, q read, out written          */
     double  flops;              /* 4 * cur_len * head_dim per query head (scores and weighted sum)   */
 } freqkv_attend_plan_t;
@@ -241,7 +242,8 @@ FREQKV_API freqkv_status_t freqkv_attend_plan(const freqkv_layout_t* layout, int
  *            exp(score); lets a caller merge results over caches sharded by token
  *   q_pos    in-cache position of the query, or -1 for cur_len - 1
  *   rope_base  e.g. 10000 (LLaMA-2) or 500000 (LLaMA-3); 0 applies no rotary embedding
- *   layout.workspace  at least freqkv_attend_plan(...).workspace_bytes, 256-byte aligned
+ *   layout.workspace  freqkv_attend_plan(...).workspace_bytes, 256-byte aligned; with less (a workspace planned at another
+ *                     length) the rows are cut into fewer chunks, down to one, whose states any plan of these heads has room for
  * q, out and lse must be 16-byte aligned.  The call only enqueues work on `stream`.  The first call
  * for a new (device, head_dim, rope_base) builds a small cached table (one allocation).
  * On a negative status no device memory has been written.

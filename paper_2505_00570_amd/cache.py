@@ -32,9 +32,11 @@ class CompressedKVCache:
         self.n_q_heads = n_heads if n_q_heads is None else n_q_heads
         self.rope_base = rope_base
         need = max(p.workspace_bytes, 256)
-        rc, ap = fk.attend_plan(self.layout, self.n_q_heads, n_heads, head_dim, self.capacity, check=False)
-        if rc == fk.OK:
-            need = max(need, ap.workspace_bytes)
+        # a shorter cache may want more row chunks than a full one
+        for n in range(self.capacity, 0, -max(64, self.capacity // 256)):
+            rc, ap = fk.attend_plan(self.layout, self.n_q_heads, n_heads, head_dim, n, check=False)
+            if rc == fk.OK:
+                need = max(need, ap.workspace_bytes)
         rc, pp = fk.attend_prefill_plan(self.layout, self.n_q_heads, n_heads, head_dim, self.capacity, self.capacity,
                                         check=False)
         self.can_prefill = rc == fk.OK

@@ -419,6 +419,16 @@ struct AttShape {
     long long units_all;        // n_layers * batch * n_kv
     size_t ml_offset;           // byte offset of the (max, sum) region inside the workspace
     size_t workspace_bytes;
+
+    // Cuts the rows into (at most) ns chunks of whole steps.
+    void cut(long long ns)
+    {
+        chunk = (int)round_up(((long long)cur_len + ns - 1) / ns, 2 * attend_row_step(d));
+        n_split = (cur_len + chunk - 1) / chunk;
+        const size_t states = (size_t)units_all * G * n_split;
+        ml_offset = (size_t)round_up((long long)(states * d * sizeof(float)), 256);
+        workspace_bytes = ml_offset + states * 2 * sizeof(float);
+    }
 };
 
 freqkv_status_t check_attend(const freqkv_layout_t* L, int n_q, int n_kv, int d, int cur_len, AttShape* out)
@@ -449,14 +459,8 @@ freqkv_status_t check_attend(const freqkv_layout_t* L, int n_q, int n_kv, int d,
     a.units_all = units;
     const int step = attend_row_step(d);
     const long long wgs_per_split = units * (a.G / a.GT);
-    long long ns = attend_chunks(wgs_per_split, units, a.GT, d, a.elem, cur_len, 2 * step);
-    long long chunk = round_up(((long long)cur_len + ns - 1) / ns, 2 * step);
-    ns = ((long long)cur_len + chunk - 1) / chunk;
-    if (wgs_per_split * ns > (1LL << 30)) return FREQKV_E_UNSUPPORTED;
-    a.n_split = (int)ns; a.chunk = (int)chunk;
-    size_t acc_bytes = (size_t)units * a.G * ns * d * sizeof(float);
-    a.ml_offset = (size_t)round_up((long long)acc_bytes, 256);
-    a.workspace_bytes = a.ml_offset + (size_t)units * a.G * ns * 2 * sizeof(float);
+    a.cut(attend_chunks(wgs_per_split, units, a.GT, d, a.elem, cur_len, 2 * step));
+    if (wgs_per_split * a.n_split > (1LL << 30)) return FREQKV_E_UNSUPPORTED;
     *out = a;
     return FREQKV_OK;
 }
@@ -1151,6 +1155,9 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         HIP_TRY(launch_rope_table(rt, a.d, rope ? rope_base : 1.0, st));
         ws = (char*)sp + kScratchRopeBytes;
     } else {
+        // The best chunk count is not monotone in cur_len, so a workspace planned at another length (a longer one, as a loop over
+        // a growing cache holds it) may have room for fewer chunks: fewer it is then, down to one.
+        while (a.n_split > 1 && a.workspace_bytes > L.workspace_bytes) a.cut(a.n_split - 1);
         if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < a.workspace_bytes)
             return FREQKV_E_WORKSPACE;
         rc = get_rope_table(a.d, rope ? rope_base : 1.0, st, &rt);

@@ -7,6 +7,7 @@ import subprocess
 import tempfile
 
 import pytest
+import torch
 
 import paper_2505_00570_amd as fk
 from paper_2505_00570_amd import binding
@@ -281,6 +282,21 @@ def test_attend_decode_validates_without_gpu():
     assert f(16, 16, 16, 16, None, C.byref(L), 4, 2, 128, 100, -1, -5.0, None) == -1          # rotary base
     assert f(16, 16, 16, 16, None, C.byref(L), 4, 2, 128, 100, -1, 10000.0, None) == -3       # no workspace
     assert f(24, 16, 16, 16, None, C.byref(L), 4, 2, 128, 100, -1, 10000.0, None) == -1       # q misaligned
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="passes made-up addresses: must end before a device is found")
+@pytest.mark.parametrize("batch,hkv,hq,d,planned", [(1, 8, 32, 128, 6147), (1, 8, 32, 64, 8192), (1, 2, 8, 256, 4096), (4, 8, 32, 128, 8192),
+                                                    (1, 32, 32, 128, 16384), (16, 8, 32, 64, 3000)])
+def test_attend_decode_takes_a_workspace_planned_at_a_longer_length(batch, hkv, hq, d, planned):
+    L = _layout(n_layers=1, batch=batch, n_heads=hkv, d=d, cap=planned)
+    _, p = fk.attend_plan(L, hq, hkv, d, planned)
+    L.workspace, L.workspace_bytes = 0x7F0000000000, p.workspace_bytes
+    fake = 0x7F0000100000
+    for cur in range(planned, 0, -89):
+        rc = fk.attend_decode(fake, fake, fake, fake, None, L, hq, hkv, d, cur, check=False)
+        assert rc == binding.E_HIP, cur                 # as far as the missing device
+    L.workspace_bytes = batch * hq * (d + 2) * 4 - 1    # not even one chunk's states
+    assert fk.attend_decode(fake, fake, fake, fake, None, L, hq, hkv, d, planned, check=False) == binding.E_WORKSPACE
 
 
 def test_compress_ragged_validates_without_gpu():

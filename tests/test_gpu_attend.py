@@ -191,6 +191,29 @@ def test_errors_leave_output_untouched():
     assert bool((out == 5.0).all())
 
 
+@pytest.mark.parametrize("d,hq,batch,cur,planned", [(128, 8, 1, 3000, 6147), (64, 2, 3, 1999, 4096), (256, 4, 1, 700, 2048)])
+def test_smaller_workspace_runs_in_fewer_chunks(d, hq, batch, cur, planned):
+    """Workspaces planned at another length, and down to one chunk's states; the last is refused."""
+    wl = _wl(d=d, hkv=2, hq=hq, batch=batch, cap=planned)
+    q, k, v = _mk(wl, cur, seed=d)
+    L = binding.layout_for(k)
+    _, best = fk.attend_plan(L, hq, 2, d, cur)
+    _, other = fk.attend_plan(L, hq, 2, d, planned)
+    one = batch * hq * (d + 2) * 4
+    assert best.n_split > 2
+    for size in (other.workspace_bytes, best.workspace_bytes - 1, best.workspace_bytes // 2, one + 256, one - 1):
+        ws = torch.empty(size + 512, dtype=torch.uint8, device=DEV)
+        ws[size:] = 7
+        L.workspace, L.workspace_bytes = ws.data_ptr(), size
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device=DEV)
+        rc = fk.attend_decode(q, k, v, out, lse, L, hq, 2, d, cur, -1, wl.rope_base, check=False)
+        torch.cuda.synchronize()
+        assert rc == (binding.E_WORKSPACE if size < one else 0)
+        assert bool((ws[size:] == 7).all())
+        if rc == 0:
+            _check(q, k, v, out, lse, wl, cur)
+
+
 def test_compress_then_attend():
     """The step after a trigger: attention over [sinks | compressed rows | tail] of the cache the library
     itself compacted, checked against the oracle on those same bits, and against the all-oracle path."""
