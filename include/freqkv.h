@@ -210,8 +210,11 @@ FREQKV_API freqkv_status_t freqkv_compress_ragged(void* k, void* v, const freqkv
                                        double retain_ratio, void* stream);
 
 /*
- * Build and cache the basis table for (window - n_sink, retain_ratio, dtype, flags) on the current
- * device ahead of the first trigger (Appendix A cosine bases fused into one operator).  Optional.
+ * Build and cache the tables for (window - n_sink, retain_ratio, dtype, flags) on the current device ahead of the
+ * first trigger (Appendix A cosine bases fused into one operator): those of every form that some head_dim takes (near/far,
+ * factored, matrix), so that the first trigger allocates nothing.  Optional.  Not among them: the two-level fold, which
+ * caches of many head-tensors take where there is no near/far form (FREQKV_FLAG_TWO_LEVEL_FOLD asks for it), and at
+ * spans that have a factored form the matrix form for rows that span 4 GiB or more.
  */
 FREQKV_API freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink,
                                double retain_ratio, void* stream);

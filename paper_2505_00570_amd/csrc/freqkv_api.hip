@@ -701,19 +701,25 @@ freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink
     memset(&L, 0, sizeof(L));
     L.dtype = dtype; L.n_layers = 1; L.batch = 1; L.token_capacity = window;
     L.stride_token = 32; L.flags = flags;
-    Shape sh;
-    freqkv_status_t rc = check_shape(&L, 1, 32, window, window, n_sink, retain_ratio, &sh);   // head_dim as caches have it
-    if (rc < 0) return rc;
-    if (sh.variant == kNone || sh.variant == kDrop) return FREQKV_OK;
-    if (sh.nearfar) {
-        const char* tables = nullptr;
-        return get_nf_tables(sh, !(flags & FREQKV_FLAG_NO_RESCALE), (hipStream_t)stream, &tables);
+    // head_dim decides which form runs (near/far: multiples of 32; factored: multiples of 16 or of 8): tables for all of them
+    for (int d : {32, 16, 8}) {
+        Shape sh;
+        freqkv_status_t rc = check_shape(&L, 1, d, window, window, n_sink, retain_ratio, &sh);
+        if (rc < 0) return rc;
+        if (sh.variant == kNone || sh.variant == kDrop) return FREQKV_OK;
+        int key = !(flags & FREQKV_FLAG_NO_RESCALE);
+        if (sh.nearfar) {
+            const char* tables = nullptr;
+            rc = get_nf_tables(sh, key, (hipStream_t)stream, &tables);
+        } else {
+            Geom g = make_geom(sh, L, 1, 0);
+            void* basis = nullptr;
+            if (sh.variant == kFast) fast_supported(sh.n, sh.Lc, d, nullptr, nullptr, &key);   // keyed by channels per workgroup
+            rc = get_basis(sh, g, key, (hipStream_t)stream, &basis);
+        }
+        if (rc < 0) return rc;
     }
-    Geom g = make_geom(sh, L, 1, 0);
-    void* basis = nullptr;
-    int key = !(flags & FREQKV_FLAG_NO_RESCALE);
-    if (sh.variant == kFast) fast_supported(sh.n, sh.Lc, sh.d, nullptr, nullptr, &key);   // keyed by channels per workgroup
-    return get_basis(sh, g, key, (hipStream_t)stream, &basis);
+    return FREQKV_OK;
 }
 
 namespace {

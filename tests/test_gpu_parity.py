@@ -693,6 +693,34 @@ def test_graph_capture_of_trigger_and_attention(window):
         assert torch.equal(outc, outc_ref), i
 
 
+@pytest.mark.parametrize("d,window,ratio", [(40, 1024, 0.5), (80, 2048, 0.5), (72, 700, 0.5), (112, 701, 0.4), (128, 1500, 0.5)])
+def test_prepared_tables_serve_the_first_call(d, window, ratio):
+    """After freqkv_prepare the first trigger of any head size allocates nothing, so that it may be captured.  Factored
+    transform with 8 and 16 channels per workgroup, folded and plain matrix form, near/far form."""
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=2, head_dim=d, window=window, retain_ratio=ratio, total_tokens=window)
+    k, v = _mk(wl, seed=d)
+    k0, v0 = k.clone(), v.clone()
+    L = binding.layout_for(k)
+    _, p = fk.plan(L, 2, d, window, window, 4, ratio)
+    ws = torch.empty(max(p.workspace_bytes, 256), dtype=torch.uint8, device=DEV)
+    L.workspace, L.workspace_bytes = ws.data_ptr(), ws.numel()
+    torch.cuda.synchronize()
+    fk.shutdown()                                     # no table of an earlier call
+    fk.prepare(fk.BF16, 0, window, 4, ratio)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fk.compress(k, v, L, 2, d, window, window, 4, ratio, torch.cuda.current_stream())
+    for _ in range(3):
+        k.copy_(k0)
+        v.copy_(v0)
+        graph.replay()
+        torch.cuda.synchronize()
+        _check_all_heads(wl, k0.cpu(), v0.cpu(), k.cpu(), v.cpu(), None, p, window, TOL_BF16)
+    del graph
+    torch.cuda.synchronize()
+
+
 def test_two_level_fold_in_several_passes():
     """A workspace that holds one (layer, K|V) slab at a time: the two-level fold runs slab by slab, its fp32
     even-part buffer indexed per pass, the optional tap per cache; same bits as the single pass."""
