@@ -508,7 +508,7 @@ def main():
     ms_prepare = prof.ms_prepare / max(int(prof.launches_prepare), 1)
     flops_launch = p.flops_executed * args.steps / launches
     achieved = flops_launch / max(ms_contract * 1e-3, 1e-12) / 1e12
-    variant = int(p.variant)
+    variant, runs = int(p.variant), int(p.runs)
     if args.dropping:
         # the whole step is k_move_rows launches (timed as one span per call by the library)
         ms_move = prof.ms_tail / max(int(prof.calls), 1)
@@ -517,13 +517,14 @@ def main():
                 "frac": gbs / HBM_PEAK_GBS, "traffic": None, "ms_per_launch": ms_move,
                 "bytes_per_launch": p.bytes_algorithmic, "measured_copy_gbs": copy_gbs,
                 "frac_of_measured_copy": gbs / copy_gbs if copy_gbs else None}
-    elif variant == 6:
-        # the near/far form (what runs at these head sizes): one kernel per trigger that reads the span and writes the retained
+    elif runs in (6, 7):
+        # the factored and the near/far form: one kernel per trigger that reads the span and writes the retained
         # rows; its matrix work is a small fraction of the dense count, so HBM is the roofline it is held against
         bytes_launch = p.bytes_algorithmic / per_trigger
         gbs = bytes_launch / (ms_contract * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "k_nearfar", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": gbs / HBM_PEAK_GBS, "traffic": NEARFAR_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload),
+        roof = {"bound": "hbm", "kernel": "k_nearfar" if runs == 7 else "k_fast", "achieved": gbs, "peak": HBM_PEAK_GBS,
+                "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
+                "traffic": NEARFAR_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload) if runs == 7 else None,
                 "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run of this kernel (profiles/), "
                                   "not measured by this run",
                 "launches_per_trigger": per_trigger, "ms_per_launch": ms_contract, "bytes_per_launch": bytes_launch,
@@ -549,23 +550,23 @@ def main():
         sustained["gbs_algorithmic"] = p.bytes_algorithmic / (sustained["ms_per_step"] * 1e-3) / 1e9
 
     names = {1: "one-level folded matrix form", 2: "plain matrix form", 3: "fp32 matrix form", 4: "dropping",
-             5: "two-level folded matrix form", 6: "near/far form"}
+             5: "two-level folded matrix form", 6: "factored transform", 7: "near/far form"}
     out = {
         "metric": "KV compression throughput (GB/s KV in)",
         "value": value, "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32" if elem == 4 else "bf16" if variant == 6 else "f16",
-        "dtype_note": ("fp32 cache, fp32 MFMA" if elem == 4 else "bf16 cache and MFMA operands, fp32 accumulation" if variant == 6
+        "dtype": "f32" if elem == 4 else "bf16" if runs == 7 else "f16",
+        "dtype_note": ("fp32 cache, fp32 MFMA" if elem == 4 else "bf16 cache and MFMA operands, fp32 accumulation" if runs == 7
                        else "bf16 cache; fp16 MFMA operands, fp32 accumulation"),
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.n_layers} layers x {wl.batch} x {wl.n_heads} KV heads x "
                                f"head_dim {wl.head_dim}, window {wl.window}, {wl.n_sink} sinks, ratio "
                                f"{wl.retain_ratio}; span {n} -> {p.retained_len}; {p.head_tensors} head-tensors "
                                f"per trigger; one trigger per step",
-                   "variant": variant, "form": names.get(variant, "?"),
+                   "variant": variant, "form": names.get(runs, "?"),
                    "operator": "dropping" if args.dropping else "freqkv"},
         # (the plan's count is that of the form it names, not of the near/far form)
-        "tflops_executed": p.flops_executed / (dt / args.steps) / 1e12 if variant != 6 else None,
+        "tflops_executed": p.flops_executed / (dt / args.steps) / 1e12 if runs != 7 else None,
         "tflops_dense_equivalent": p.flops_dense / (dt / args.steps) / 1e12,
         "gbs_algorithmic": p.bytes_algorithmic / (dt / args.steps) / 1e9,
         "frac_hbm_roofline": p.bytes_algorithmic / (dt / args.steps) / 1e9 / HBM_PEAK_GBS,
@@ -613,7 +614,7 @@ def bench_stream(args, wl, k, v, L, p, step):
         "metric": "KV compression throughput over the whole schedule (GB/s KV in)",
         "value": bytes_in * len(times) / (total_ms * 1e-3) / 1e9, "unit": "GB/s", "n_gpus": 1, "steps": len(times),
         "warmup": args.warmup, "ms_per_step": total_ms / len(times), "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "f16", "data": "synthetic",
+        "vs_baseline": None, "dtype": "f32" if elem == 4 else "bf16" if p.runs == 7 else "f16", "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.total_tokens} tokens per sequence through a window of {W} "
                                f"({wl.n_layers} layers x {wl.batch} x {wl.n_heads} KV heads x head_dim {wl.head_dim}): "
                                f"{len(times)} triggers of {p.head_tensors} head-tensors, span {p.span_len} -> {p.retained_len}",

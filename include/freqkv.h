@@ -72,8 +72,9 @@ typedef enum {
  * Forms of the compression on bf16 caches, without the flags above:
  *   near/far   head_dim a multiple of 32, retain_ratio >= 0.2, spans of 128 to some 12000 rows, a span of less than
  *              4 GiB: exact entries close to the diagonal, interpolated ones further away (error below 5e-3 of the
- *              RMS).  freqkv_plan keeps naming the form that the shape would have otherwise, with that form's
- *              sizes and counts; the workspace that it asks for has to be there, but stays unused.
+ *              RMS).  freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
+ *              have otherwise, with that form's sizes and counts; of the workspace that it asks for
+ *              workspace_min_bytes have to be there, but stay unused.
  *   variant 6  the factored transform, head_dim not a multiple of 32, retain_ratio 0.5, spans n = 4pq with a compiled
  *              factorization (8188 = 4*23*89, 4092 = 4*11*93, 2044 = 4*7*73, 1020 = 4*3*85, and 1260, 140 for tests)
  *   variants 1, 2, 5  the matrix forms: everything else, and what the flags ask for
@@ -119,10 +120,12 @@ typedef struct freqkv_plan {
     int32_t variant;            /* 0 none (no-op or ratio 1), 1 folded fp16-MFMA, 2 plain fp16-MFMA, 3 fp32,
                                    4 dropping (row moves only), 5 two-level folded fp16-MFMA,
                                    6 factored transform (prime-factor DFT stages on the matrix cores, LDS resident) */
-    int32_t reserved;
-    size_t  workspace_bytes;    /* scratch for all head-tensors in one pass (fastest)            */
+    int32_t runs;               /* the form that a call really takes: 7 near/far form, else the same as variant */
+    size_t  workspace_bytes;    /* scratch for all head-tensors in one pass (fastest); where runs is 7
+                                   workspace_min_bytes does as well                              */
     size_t  workspace_min_bytes;/* smallest scratch accepted (one (layer,K|V) slab per pass)     */
-    size_t  basis_bytes;        /* device memory the library itself holds for this (n, Lc)       */
+    size_t  basis_bytes;        /* device memory the library itself holds for this (n, Lc) and the named variant;
+                                   the tables of the near/far form take 0.1 to 9 MB instead      */
     double  flops_dense;        /* 2*Lc*n*d per head-tensor, summed: the fused operator as one contraction */
     double  flops_executed;     /* what the named variant executes (no padding counted)          */
     double  bytes_algorithmic;  /* (n + Lc)*d*e per head-tensor + 2*(cur_len-window)*d*e, summed */

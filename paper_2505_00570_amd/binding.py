@@ -48,7 +48,7 @@ class Plan(C.Structure):
     """struct freqkv_plan (include/freqkv.h)."""
     _fields_ = [
         ("span_len", C.c_int32), ("retained_len", C.c_int32), ("new_len", C.c_int32),
-        ("head_tensors", C.c_int32), ("variant", C.c_int32), ("reserved", C.c_int32),
+        ("head_tensors", C.c_int32), ("variant", C.c_int32), ("runs", C.c_int32),
         ("workspace_bytes", C.c_size_t), ("workspace_min_bytes", C.c_size_t), ("basis_bytes", C.c_size_t),
         ("flops_dense", C.c_double), ("flops_executed", C.c_double), ("bytes_algorithmic", C.c_double),
     ]

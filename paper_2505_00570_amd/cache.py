@@ -31,7 +31,8 @@ class CompressedKVCache:
         self.plan = p
         self.n_q_heads = n_heads if n_q_heads is None else n_q_heads
         self.rope_base = rope_base
-        need = max(p.workspace_bytes, 256)
+        # the near/far form (7) wants the least that the library accepts, the matrix forms run faster with more
+        need = max(p.workspace_min_bytes if p.runs == 7 else p.workspace_bytes, 256)
         # a shorter cache may want more row chunks than a full one
         for n in range(self.capacity, 0, -max(64, self.capacity // 256)):
             rc, ap = fk.attend_plan(self.layout, self.n_q_heads, n_heads, head_dim, n, check=False)

@@ -668,6 +668,7 @@ freqkv_status_t freqkv_plan(const freqkv_layout_t* layout, int n_heads, int head
     out->new_len = sh.S + sh.Lc + sh.tail;
     out->head_tensors = (int)(sh.nslabs * sh.hts_per_slab);
     out->variant = sh.variant;
+    out->runs = sh.nearfar ? kNearFar : sh.variant;
     double hts = (double)sh.nslabs * (double)sh.hts_per_slab;
     if (sh.variant == kDrop) {
         out->bytes_algorithmic = (2.0 * sh.Lc + 2.0 * sh.tail) * sh.d * sh.elem * hts;

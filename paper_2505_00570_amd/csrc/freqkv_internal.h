@@ -87,7 +87,7 @@ __device__ __forceinline__ char* column_base(const SlabTable& tab, const Geom& g
 }
 
 enum Variant { kNone = 0, kFoldF16 = 1, kPlainF16 = 2, kF32 = 3, kDrop = 4, kFold2F16 = 5, kFast = 6,
-               kNearFar = 7 };   // 7: key of its tables only; a plan names the form that FREQKV_FLAG_DENSE or the layout falls back to
+               kNearFar = 7 };   // 7: in the key of its tables and in freqkv_plan_t::runs; Shape::variant is the form without it
 
 // ---- basis construction (fp64 closed form, rounded once) -------------------------
 // G: [Kpad/8][Grows][8] fp16.  Folded: rows [0,Mpad) even part, rows [Mpad,2Mpad) odd part.

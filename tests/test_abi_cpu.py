@@ -129,6 +129,16 @@ def test_plan_agrees_with_oracle_rules(window, sink, ratio, cur):
         assert p.variant == 2
 
 
+@pytest.mark.parametrize("d,window,ratio,flags,variant,runs", [
+    (128, 8192, 0.5, 0, 6, 7), (128, 8192, 0.25, 0, 2, 7), (96, 516, 0.5, 0, 1, 7), (40, 8192, 0.5, 0, 6, 6), (128, 8192, 0.5, fk.FLAG_DENSE, 5, 5),
+    (128, 8192, 0.19, 0, 2, 2), (128, 131, 0.5, 0, 2, 2), (128, 8192, 1.0, 0, 0, 0), (128, 8192, 0.5, fk.FLAG_DROPPING, 4, 4)])
+def test_plan_names_the_form_that_runs(d, window, ratio, flags, variant, runs):
+    L = _layout(d=d)
+    L.flags = flags
+    _, p = fk.plan(L, 8, d, window, window, 4, ratio)
+    assert (p.variant, p.runs) == (variant, runs)
+
+
 def test_plan_noop_below_window():
     rc, p = fk.plan(_layout(), 8, 128, 100, 8192, 4, 0.5)
     assert rc == 1 and p.retained_len == 4094
