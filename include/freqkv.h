@@ -134,8 +134,9 @@ typedef struct freqkv_plan {
 /* Per-kernel GPU time, accumulated by HIP events while profiling is on. */
 typedef struct freqkv_profile {
     int64_t calls;              /* freqkv_compress calls that enqueued work                      */
-    int64_t launches_prepare;   /* fold/convert (or copy) launches                               */
-    int64_t launches_contract;  /* contraction launches                                          */
+    int64_t launches_prepare;   /* fold/convert (or copy) launches of the matrix forms and of fp32 caches; chunk-wise
+                                   attention: its preparation                                    */
+    int64_t launches_contract;  /* contraction launches; near/far and factored form: their one kernel */
     int64_t launches_tail;      /* tail-move launches                                            */
     double  ms_prepare;
     double  ms_contract;

@@ -748,11 +748,8 @@ freqkv_status_t compress_nearfar(const std::vector<char*>& bases, const std::vec
                                  const Shape& sh, float* tap, hipStream_t st)
 {
     const char* tables = nullptr;
-    ProfSpan ps;                                               // profiles of matrix-form plans count a preparation: the tables
-    if (sh.variant != kFast) HIP_TRY(prof_begin(st, 0, &ps));
     freqkv_status_t rc = get_nf_tables(sh, !(L.flags & FREQKV_FLAG_NO_RESCALE), st, &tables);
     if (rc < 0) return rc;
-    if (sh.variant != kFast) HIP_TRY(prof_end(st, &ps));
     if (g_prof_on) { std::lock_guard<std::mutex> lock(g_mu); g_prof_acc.calls++; }
     NfGeom nf = sh.nf;
     nf.S = sh.S; nf.n_heads = sh.n_heads; nf.hts_per_slab = (int)sh.hts_per_slab;

@@ -354,14 +354,15 @@ def test_runs_on_the_callers_stream_and_prepare_is_idempotent(W):
 def test_profile_and_calibration_helpers():
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=4, window=516)
     k, v = _mk(wl, seed=13)
-    fk.profile_enable(True)
-    for _ in range(3):
-        rc, p, _ = _run(k, v, wl, 516, tap=False)
-        assert rc == 0
-    prof = fk.profile_read()
-    fk.profile_enable(False)
-    assert prof.calls == 3 and prof.launches_contract == 3 and prof.launches_prepare == 3
-    assert prof.launches_tail == 0 and prof.ms_contract > 0 and prof.ms_prepare > 0
+    for flags in (fk.FLAG_DENSE, 0):                  # the matrix form prepares its operands, the near/far form is one kernel
+        fk.profile_enable(True)
+        for _ in range(3):
+            rc, p, _ = _run(k, v, wl, 516, tap=False, flags=flags)
+            assert rc == 0
+        prof = fk.profile_read()
+        fk.profile_enable(False)
+        assert prof.calls == 3 and prof.launches_contract == 3 and prof.launches_prepare == (3 if flags else 0)
+        assert prof.launches_tail == 0 and prof.ms_contract > 0 and (prof.ms_prepare > 0) == (flags != 0)
     a = torch.empty(1 << 26, dtype=torch.uint8, device=DEV)
     b = torch.randint(0, 255, (1 << 26,), dtype=torch.uint8, device=DEV)
     gbs = fk.calibrate_copy(a, b, 1 << 26, 5)
