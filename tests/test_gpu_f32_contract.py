@@ -1,5 +1,5 @@
 """GPU parity of the fp32 contraction against the fp64 CPU oracle, every element: folded and plain spans, remainders of its
-tiles (32 rows, 32 columns) and of its contraction slices, one wave or eight waves to a tile, a whole pass of both kinds."""
+tiles (32 rows, 32 columns) and of its contraction slices, four waves to a tile, a whole pass of both kinds."""
 import pytest
 
 from paper_2505_00570_amd import synth

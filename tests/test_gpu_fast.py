@@ -1,7 +1,9 @@
-"""GPU parity of the factored transform (plan variant 6) against the fp64 CPU oracle, element by element.
+"""GPU parity of triggers whose plan names the factored transform (variant 6) against the fp64 CPU oracle, element by element.
 
 Spans n = 4pq with a compiled factorization: 140 = 4*5*7 and 1260 = 4*7*45 (small, every head-tensor whole),
-4092 = 4*11*93 and 8188 = 4*23*89 (the paper's windows minus 4 sinks).  Same inputs, same tolerance
+1020 = 4*3*85, 2044 = 4*7*73, 4092 = 4*11*93 and 8188 = 4*23*89 (windows minus 4 sinks).  Head sizes that are a
+multiple of 32 run the near/far form there, others the factored transform itself, with 16 channels per workgroup
+where head_dim is a multiple of 16 and the span below 8188, else with 8.  Same inputs, same tolerance
 (tests/_util.py) and same checks as the matrix forms; the oracle runs on the bits the GPU sees.
 """
 import math
@@ -26,6 +28,10 @@ def _wl(layers, batch, heads, d, window, sink=4):
                        window=window, n_sink=sink, total_tokens=window)
 
 
+def _runs(d):
+    return 7 if d % 32 == 0 else 6
+
+
 FAST_SMALL = [
     # (layers, batch, heads, d, window, sink)
     (1, 1, 1, 8, 144, 4),        # n = 140: one task
@@ -38,6 +44,19 @@ FAST_SMALL = [
     (1, 1, 2, 128, 4096, 4),     # n = 4092
     (1, 1, 2, 128, 8192, 4),     # n = 8188
     (1, 1, 1, 256, 8196, 8),     # 8 sinks, head_dim 256
+    # the factored transform, each compiled form of it
+    (2, 2, 3, 72, 144, 4),       # several layers / sequences / heads, 9 tasks per head-tensor
+    (1, 1, 9, 40, 140, 0),       # no sinks; 9 head-tensors per slab: the XCD-aware block map has a remainder
+    (1, 2, 5, 112, 1262, 2),     # 2 sinks
+    (1, 2, 2, 40, 1024, 4),      # n = 1020, 8 channels
+    (2, 1, 3, 80, 1024, 4),      # n = 1020, 16 channels
+    (1, 1, 2, 72, 2048, 4),      # n = 2044, 8
+    (1, 1, 2, 112, 2048, 4),     # n = 2044, 16
+    (1, 1, 2, 40, 4096, 4),      # n = 4092, 8
+    (1, 1, 2, 80, 4096, 4),      # n = 4092, 16
+    (1, 1, 1, 112, 8192, 4),     # n = 8188
+    (4, 2, 60, 40, 1024, 4),     # more tasks than workgroups (960 head-tensors, 5 tasks each): the last heads
+    (4, 2, 60, 80, 1024, 4),     # as many, 16 channels
 ]
 
 
@@ -49,26 +68,33 @@ def test_fast_every_element(case):
     k, v = _mk(wl, seed=window + d)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, window)
-    assert rc == 0 and p.variant == 6 and p.workspace_bytes == 0
+    assert rc == 0 and p.variant == 6 and p.workspace_bytes == 0 and p.runs == _runs(d)
     assert p.retained_len * 2 == p.span_len == window - sink
+    if heads > 50:
+        pick = (slice(layers - 1, layers), slice(1, 2), slice(heads - 3, heads))
+        _check_all_heads(_wl(1, 1, 3, d, window, sink), k0[pick], v0[pick], k.cpu()[pick], v.cpu()[pick],
+                         tap.cpu()[(slice(None),) + pick], p, window, TOL_BF16)
+        return
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, window, TOL_BF16)
 
 
+@pytest.mark.parametrize("d", [128, 72])
 @pytest.mark.parametrize("extra", [1, 17, 700])
-def test_fast_tail_and_canaries(extra):
+def test_fast_tail_and_canaries(extra, d):
     """cur_len > window: the tail moves bit for bit behind the retained rows, rows beyond cur_len keep
     their canary (both checked inside _check_all_heads)."""
-    wl = _wl(1, 2, 2, 128, 1264)
+    wl = _wl(1, 2, 2, d, 1264)
     cur = wl.window + extra
     k, v = _mk(wl, seed=extra, capacity=cur + 5, cur_len=cur)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, cur)
-    assert rc == 0 and p.variant == 6 and p.new_len == 4 + 630 + extra
+    assert rc == 0 and p.variant == 6 and p.runs == _runs(d) and p.new_len == 4 + 630 + extra
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, cur, TOL_BF16)
 
 
-def test_fast_without_workspace_and_without_tap():
-    wl = _wl(1, 1, 3, 128, 1264)
+@pytest.mark.parametrize("d", [128, 40])
+def test_fast_without_workspace_and_without_tap(d):
+    wl = _wl(1, 1, 3, d, 1264)
     k, v = _mk(wl, seed=9)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     L = binding.layout_for(k)                      # workspace NULL: the factored form needs none
@@ -78,8 +104,9 @@ def test_fast_without_workspace_and_without_tap():
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), None, p, wl.window, TOL_BF16)
 
 
-def test_fast_flags_rescale_off_and_dense_agree_with_the_oracle():
-    wl = _wl(1, 1, 2, 128, 1264)
+@pytest.mark.parametrize("d", [128, 112])
+def test_fast_flags_rescale_off_and_dense_agree_with_the_oracle(d):
+    wl = _wl(1, 1, 2, d, 1264)
     k, v = _mk(wl, seed=21)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, wl.window, flags=fk.FLAG_NO_RESCALE)
@@ -99,9 +126,10 @@ def test_fast_flags_rescale_off_and_dense_agree_with_the_oracle():
     assert p4.variant in (1, 2, 5)
 
 
-def test_fast_token_major_strides_and_pointer_table():
+@pytest.mark.parametrize("head_dim,window", [(64, 1264), (72, 1264), (80, 1024)])
+def test_fast_token_major_strides_and_pointer_table(head_dim, window):
     import ctypes as C
-    wl = _wl(2, 1, 3, 64, 1264)
+    wl = _wl(2, 1, 3, head_dim, window)
     S, W, d, H = wl.n_sink, wl.window, wl.head_dim, wl.n_heads
     # token-major storage [layer][batch][token][head][dim], viewed as [layer][batch][head][token][dim]
     src = synth.KVSource(wl, 31, DEV)
@@ -113,7 +141,7 @@ def test_fast_token_major_strides_and_pointer_table():
     k0, v0 = kt.cpu().clone(), vt.cpu().clone()
     L = binding.layout_for(kt)
     _, p = fk.plan(L, H, d, W, W, S, 0.5)
-    assert p.variant == 6
+    assert p.variant == 6 and p.runs == _runs(d)
     assert fk.compress(kt, vt, L, H, d, W, W, S, 0.5) == 0
     torch.cuda.synchronize()
     _check_all_heads(wl, k0, v0, kt.cpu(), vt.cpu(), None, p, W, TOL_BF16)
@@ -129,13 +157,14 @@ def test_fast_token_major_strides_and_pointer_table():
     _check_all_heads(wl, kk.cpu(), vv.cpu(), torch.cat(ks).cpu(), torch.cat(vs).cpu(), None, p, W, TOL_BF16)
 
 
-@pytest.mark.parametrize("flags", [0, binding.FLAG_DENSE, binding.FLAG_SINGLE_FOLD])
-def test_large_and_tiny_values_keep_the_tolerance(flags):
+@pytest.mark.parametrize("flags,d,window", [(0, 128, 1264), (binding.FLAG_DENSE, 128, 1264), (binding.FLAG_SINGLE_FOLD, 128, 1264),
+                                            (0, 72, 1264), (0, 80, 1024)])
+def test_large_and_tiny_values_keep_the_tolerance(flags, d, window):
     """Cache values far outside the fp16 range of the matrix-core operands: a K head whose outlier channels
     reach 6e4, a head of magnitude 1e-6, a head of magnitude 3e37 and an all-zero head.  Every head-tensor is
     scaled by an exact power of two on its way in and back on its way out, so none of them overflows to
     inf or drowns in fp16 subnormals."""
-    wl = _wl(1, 1, 5, 128, 1264)
+    wl = _wl(1, 1, 5, d, window)
     k, v = _mk(wl, seed=77)
     S, W = wl.n_sink, wl.window
     with torch.no_grad():

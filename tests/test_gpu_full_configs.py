@@ -83,7 +83,7 @@ def _one_trigger_full(wl, n_pick, seed, with_tap, extra_picks=(), expect=None, f
     L = binding.layout_for(k, flags=flags)
     _, p = fk.plan(L, wl.n_heads, wl.head_dim, wl.window, wl.window, wl.n_sink, wl.retain_ratio)
     if variant is not None:
-        assert p.variant == variant
+        assert p.variant == variant and p.runs == (variant if flags else 7)
     if expect is not None:
         assert (p.span_len, p.retained_len, p.head_tensors) == expect
     ws = torch.empty(max(p.workspace_bytes, 256), dtype=torch.uint8, device=DEV)
@@ -131,8 +131,9 @@ def test_llama2_7b_one_layer_full():
     _check_sample(wl, before, after, tap, p, picks)
 
 
-# the full-size triggers run twice: the factored transform (the default for these spans) and the matrix form
-FORMS = [pytest.param(0, 6, id="factored"), pytest.param(binding.FLAG_DENSE, 5, id="matrix")]
+# the full-size triggers run twice: the near/far form (the default, though the plan's variant is the factored transform) and
+# the matrix form
+FORMS = [pytest.param(0, 6, id="nearfar"), pytest.param(binding.FLAG_DENSE, 5, id="matrix")]
 
 
 @pytest.mark.parametrize("flags,variant", FORMS)
@@ -287,11 +288,12 @@ def _free_running(wl, seed, n_cols=16):
     return cache.triggers, worst_rel, last
 
 
-@pytest.mark.parametrize("name,layers,count", [("llama2_7b_32k", 2, 15), ("llama3_8b_128k", 2, 31),
-                                               ("decode_b8_256k", 1, 127)])
-def test_free_running_drift_over_the_whole_schedule(name, layers, count):
-    """Configs 3, 4, 5: all 15 / 31 / 127 triggers of the schedule, two head-tensors free running in fp64."""
-    wl = synth.small(synth.WORKLOADS[name], n_layers=layers)
+@pytest.mark.parametrize("name,layers,d,count", [("llama2_7b_32k", 2, 128, 15), ("llama3_8b_128k", 2, 128, 31),
+                                                 ("decode_b8_256k", 1, 128, 127), ("llama2_7b_32k", 2, 80, 15)])
+def test_free_running_drift_over_the_whole_schedule(name, layers, d, count):
+    """Configs 3, 4, 5: all 15 / 31 / 127 triggers of the schedule, two head-tensors free running in fp64; once with a head size
+    that takes the factored transform."""
+    wl = synth.small(synth.WORKLOADS[name], n_layers=layers, head_dim=d)
     triggers, worst, bound_rel = _free_running(wl, seed=90 + count)
     assert triggers == count == orc.trigger_count(wl.total_tokens, wl.window, wl.n_sink, wl.retain_ratio)
     _say(f"free running {name}: {triggers} triggers, worst max-abs drift / RMS {worst:.3e}; "

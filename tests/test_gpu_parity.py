@@ -109,6 +109,10 @@ def test_tiny_fp32_full():
 # bf16, small shapes: several tiles, ragged tails, every pipeline tail length, both variants
 # ------------------------------------------------------------------------------------------
 
+# near/far form (head_dim a multiple of 32, spans of 128 rows or more, ratios from 0.2; else what the plan names) and, on
+# request, the matrix forms
+FORMS = [pytest.param(0, id="default"), pytest.param(binding.FLAG_DENSE, id="matrix")]
+
 SMALL = [
     # (layers, batch, heads, d, window, sink, ratio)        what it exercises
     (1, 1, 1, 128, 68, 4, 0.5),      # one pipeline stage (n/2 = 32)
@@ -154,16 +158,17 @@ def test_bf16_two_level_fold(cfg):
 
 
 
+@pytest.mark.parametrize("flags", FORMS)
 @pytest.mark.parametrize("cfg", SMALL, ids=[str(c) for c in SMALL])
-def test_bf16_small_full(cfg):
+def test_bf16_small_full(cfg, flags):
     nl, b, h, d, W, S, ratio = cfg
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=nl, batch=b, n_heads=h, head_dim=d,
                      window=W, n_sink=S, retain_ratio=ratio, total_tokens=W)
     _say(f"bf16 small {cfg}")
     k, v = _mk(wl, seed=3, capacity=W + 9)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
-    rc, p, tap = _run(k, v, wl, W)
-    assert rc == 0
+    rc, p, tap = _run(k, v, wl, W, flags=flags)
+    assert rc == 0 and p.runs == (7 if not flags and W - S >= 128 and ratio >= 0.2 else p.variant) and p.variant in (1, 2)
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, W, TOL_BF16)
 
 
@@ -188,14 +193,15 @@ def test_noop_below_window_leaves_cache_untouched():
 # recent tail (cur_len > window), including a tail longer than the freed gap (chunked move)
 # ------------------------------------------------------------------------------------------
 
+@pytest.mark.parametrize("flags", FORMS)
 @pytest.mark.parametrize("extra", [1, 37, 148, 149, 400])
-def test_tail_is_moved_bit_for_bit(extra):
+def test_tail_is_moved_bit_for_bit(extra, flags):
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=2, n_heads=2, window=300, n_sink=4)
     cur = 300 + extra
     _say(f"tail extra={extra}")
     k, v = _mk(wl, seed=5, capacity=cur + 7, cur_len=cur)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
-    rc, p, tap = _run(k, v, wl, cur)
+    rc, p, tap = _run(k, v, wl, cur, flags=flags)
     assert rc == 0 and p.new_len == 4 + 148 + extra
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, cur, TOL_BF16)
 
@@ -204,7 +210,8 @@ def test_tail_is_moved_bit_for_bit(extra):
 # layouts: token-major strides, pointer table, small workspace (several passes)
 # ------------------------------------------------------------------------------------------
 
-def test_token_major_strides():
+@pytest.mark.parametrize("flags", FORMS)
+def test_token_major_strides(flags):
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=2, n_heads=3, window=260)
     W = wl.window
     # storage [L, B, token, H, d] viewed as [L, B, H, token, d]
@@ -213,12 +220,13 @@ def test_token_major_strides():
     k, v = ks.permute(0, 1, 3, 2, 4), vs.permute(0, 1, 3, 2, 4)
     synth.KVSource(wl, 2, DEV).fill(k, v, 0, W)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
-    rc, p, tap = _run(k, v, wl, W)
+    rc, p, tap = _run(k, v, wl, W, flags=flags)
     assert rc == 0
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, W, TOL_BF16)
 
 
-def test_pointer_table_and_multi_pass_match_single_pass():
+@pytest.mark.parametrize("flags", FORMS)
+def test_pointer_table_and_multi_pass_match_single_pass(flags):
     import ctypes as C
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=3, n_heads=2, window=516)
     W = wl.window
@@ -226,12 +234,12 @@ def test_pointer_table_and_multi_pass_match_single_pass():
     ka, va = k.clone(), v.clone()       # single pass, base pointers
     kb, vb = k.clone(), v.clone()       # minimum workspace -> one slab per pass
     kc, vc = k.clone(), v.clone()       # per-layer pointer table
-    rc, p, _ = _run(ka, va, wl, W, tap=False)
+    rc, p, _ = _run(ka, va, wl, W, tap=False, flags=flags)
     assert rc == 0
-    rc, _, _ = _run(kb, vb, wl, W, tap=False, ws_bytes=p.workspace_min_bytes)
+    rc, _, _ = _run(kb, vb, wl, W, tap=False, ws_bytes=p.workspace_min_bytes, flags=flags)
     assert rc == 0
     assert torch.equal(ka, kb) and torch.equal(va, vb)
-    L = binding.layout_for(kc)
+    L = binding.layout_for(kc, flags=flags)
     ws = torch.empty(p.workspace_bytes, dtype=torch.uint8, device=DEV)
     L.workspace, L.workspace_bytes, L.pointer_table = ws.data_ptr(), p.workspace_bytes, 1
     kt = (C.c_void_p * 3)(*[kc[l].data_ptr() for l in range(3)])
@@ -255,11 +263,12 @@ def test_errors_leave_memory_untouched():
     assert torch.equal(k, k0) and torch.equal(v, v0)
 
 
-def test_no_rescale_flag():
+@pytest.mark.parametrize("flags", FORMS)
+def test_no_rescale_flag(flags):
     wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=2, window=260)
     k, v = _mk(wl, seed=6)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
-    rc, p, tap = _run(k, v, wl, 260, flags=fk.FLAG_NO_RESCALE)
+    rc, p, tap = _run(k, v, wl, 260, flags=flags | fk.FLAG_NO_RESCALE)
     assert rc == 0
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, 260, TOL_BF16, rescale=False)
 
@@ -268,10 +277,11 @@ def test_no_rescale_flag():
 # iterative schedule (Sec. 3.4): teacher-forced parity at every trigger + free-running drift
 # ------------------------------------------------------------------------------------------
 
-def test_iterative_schedule_small():
+@pytest.mark.parametrize("flags", FORMS)
+def test_iterative_schedule_small(flags):
     wl = synth.small(synth.WORKLOADS["llama2_7b_32k"], n_layers=2, n_heads=2, window=516, total_tokens=516 * 8)
     W, S = wl.window, wl.n_sink
-    cache = CompressedKVCache(wl.n_layers, wl.batch, wl.n_heads, wl.head_dim, W, S, wl.retain_ratio, wl.dtype, DEV)
+    cache = CompressedKVCache(wl.n_layers, wl.batch, wl.n_heads, wl.head_dim, W, S, wl.retain_ratio, wl.dtype, DEV, flags=flags)
     src = synth.KVSource(wl, 11, DEV)
     lc = cache.plan.retained_len
     free = cache.free_after_trigger
@@ -320,21 +330,21 @@ def test_iterative_schedule_small():
 # launch plan: more (layer, K|V) slabs than one pointer table holds; caller's stream; helpers
 # ------------------------------------------------------------------------------------------
 
-@pytest.mark.parametrize("window,variant", [(132, 1), (144, 6)])
-def test_many_layers_split_into_passes(window, variant):
-    """100 layers = 200 slabs > 192 per launch group: the call makes two passes (matrix form and factored form)."""
-    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=100, n_heads=1, head_dim=64, window=window)
-    _say(f"100 layers x 1 head x 64, window {window}")
+@pytest.mark.parametrize("window,d,variant,runs", [(132, 64, 1, 7), (144, 64, 6, 7), (132, 72, 1, 1), (144, 72, 6, 6)])
+def test_many_layers_split_into_passes(window, d, variant, runs):
+    """100 layers = 200 slabs > 192 per launch group: the call makes two passes (near/far, matrix and factored form)."""
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=100, n_heads=1, head_dim=d, window=window)
+    _say(f"100 layers x 1 head x {d}, window {window}")
     k, v = _mk(wl, seed=8, capacity=window + 8)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, window)
-    assert rc == 0 and p.head_tensors == 200 and p.variant == variant
+    assert rc == 0 and p.head_tensors == 200 and (p.variant, p.runs) == (variant, runs)
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, window, TOL_BF16)
 
 
-@pytest.mark.parametrize("W", [516, 1264])
-def test_runs_on_the_callers_stream_and_prepare_is_idempotent(W):
-    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=2, window=W)
+@pytest.mark.parametrize("W,d", [(516, 128), (1264, 128), (516, 72), (1264, 72)])
+def test_runs_on_the_callers_stream_and_prepare_is_idempotent(W, d):
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_heads=2, head_dim=d, window=W)
     k, v = _mk(wl, seed=12)
     ka, va = k.clone(), v.clone()
     rc, p, _ = _run(ka, va, wl, W, tap=False)              # default stream
@@ -346,7 +356,7 @@ def test_runs_on_the_callers_stream_and_prepare_is_idempotent(W):
     L.workspace, L.workspace_bytes = ws.data_ptr(), p.workspace_bytes
     torch.cuda.synchronize()
     with torch.cuda.stream(side):
-        assert fk.compress(k, v, L, 2, 128, W, W, 4, 0.5, side) == 0
+        assert fk.compress(k, v, L, 2, d, W, W, 4, 0.5, side) == 0
     side.synchronize()
     assert torch.equal(k, ka) and torch.equal(v, va)        # same bits whichever stream ran it
 
@@ -402,12 +412,15 @@ def test_dropping_variant(window, sink, ratio, extra, dtype):
 # batches whose sequences hold different numbers of tokens
 # ------------------------------------------------------------------------------------------
 
-@pytest.mark.parametrize("lens,flags", [([300, 290, 307, 300], 0), ([300, 300, 301, 301], 0), ([10, 299, 0, 42], 0),
-                                        ([300, 290, 307, 300], fk.FLAG_DROPPING), ([340, 300, 300, 340], 0),
-                                        ([144, 140, 151, 144], 0), ([184, 144, 144, 184], 0)])
-def test_ragged_batch(lens, flags):
-    window = 144 if max(lens) < 200 else 300             # 144: span 140, the factored form
-    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=2, batch=4, n_heads=2, window=window)
+# head_dim 72: no near/far form; window 144: span 140, the factored form
+@pytest.mark.parametrize("lens,flags,d", [([300, 290, 307, 300], 0, 128), ([300, 300, 301, 301], 0, 128), ([10, 299, 0, 42], 0, 128),
+                                          ([300, 290, 307, 300], fk.FLAG_DROPPING, 128), ([340, 300, 300, 340], 0, 128),
+                                          ([144, 140, 151, 144], 0, 128), ([184, 144, 144, 184], 0, 128),
+                                          ([300, 290, 307, 300], fk.FLAG_DENSE, 128), ([300, 300, 301, 301], 0, 72),
+                                          ([144, 140, 151, 144], 0, 72), ([184, 144, 144, 184], 0, 72)])
+def test_ragged_batch(lens, flags, d):
+    window = 144 if max(lens) < 200 else 300
+    wl = synth.small(synth.WORKLOADS["llama2_7b_layer"], n_layers=2, batch=4, n_heads=2, head_dim=d, window=window)
     cap = window + 60
     _say(f"ragged compress lens={lens} flags={flags}")
     k, v = _mk(wl, seed=77, capacity=cap, cur_len=cap)
@@ -642,14 +655,14 @@ def test_power_spectrum_errors():
 # and chunk-wise attention can be captured once and replayed
 # ------------------------------------------------------------------------------------------
 
-@pytest.mark.parametrize("window", [516, 1264])
-def test_graph_capture_of_trigger_and_attention(window):
-    """Trigger (matrix form at 516, factored form at 1264) + decode attention + chunk attention in one HIP graph."""
+@pytest.mark.parametrize("window,flags", [(516, 0), (1264, 0), (516, binding.FLAG_DENSE)])
+def test_graph_capture_of_trigger_and_attention(window, flags):
+    """Trigger (near/far form, matrix form) + decode attention + chunk attention in one HIP graph."""
     wl = synth.small(synth.WORKLOADS["llama3_8b_128k"], n_layers=2, n_heads=2, n_q_heads=8, window=window)
     k0, v0 = _mk(wl, seed=17)
     k, v = k0.clone(), v0.clone()
     q = synth.queries(wl, 17, DEV)
-    L = binding.layout_for(k)
+    L = binding.layout_for(k, flags=flags)
     _, p = fk.plan(L, wl.n_heads, wl.head_dim, wl.window, wl.window, wl.n_sink, wl.retain_ratio)
     _, ap = fk.attend_plan(L, wl.q_heads, wl.n_heads, wl.head_dim, p.new_len)
     q_len = 100                                       # chunk-wise attention of the last 100 compacted rows
