@@ -507,10 +507,11 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
 // Cos/sin of every row position for chunk-wise attention (512 bytes per row at d = 128), cached per (device, d, base) like the
 // other tables: 5 us of every short call otherwise.  A call that needs more rows than the table has gets a new one of the next
 // power of two; the old one stays until shutdown, since enqueued work and captured graphs may still read it.  While a
-// stream is being captured nothing is allocated, and neither are tables beyond kCsMaxRows rows or kCsMaxTables in number:
-// such calls fill the table into their own workspace.
+// stream is being captured nothing is allocated, and neither are tables beyond kCsMaxRows rows or kCsMaxTables per device
+// (three rotary bases that grow from 4096 to kCsMaxRows rows, 64 MB each in all, and one more): such calls fill the table into
+// their own workspace.
 constexpr int kCsMaxRows = 1 << 16;
-constexpr size_t kCsMaxTables = 16;
+constexpr int kCsMaxTables = 16;
 struct CsTable { RopeKey key; int rows; BasisEntry e; };
 std::vector<CsTable> g_cs;
 
@@ -521,15 +522,19 @@ freqkv_status_t get_cs_table(int rows, int d, double base, hipStream_t st, float
     HIP_TRY(hipGetDevice(&dev));
     {
         std::lock_guard<std::mutex> lock(g_mu);
-        for (CsTable& t : g_cs)
-            if (t.key.device == dev && t.key.d == d && t.key.base == base && t.rows >= rows) {
+        int held = 0;                                     // tables of this device
+        for (CsTable& t : g_cs) {
+            if (t.key.device != dev) continue;
+            ++held;
+            if (t.key.d == d && t.key.base == base && t.rows >= rows) {
                 HIP_TRY(order_after(t.e, st));
                 *out = (const float2*)t.e.ptr;
                 return FREQKV_OK;
             }
+        }
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         HIP_TRY(hipStreamIsCapturing(st, &cap));
-        if (cap == hipStreamCaptureStatusNone && rows <= kCsMaxRows && g_cs.size() < kCsMaxTables) {
+        if (cap == hipStreamCaptureStatusNone && rows <= kCsMaxRows && held < kCsMaxTables) {
             CsTable t{RopeKey{dev, d, base}, 4096, BasisEntry()};
             while (t.rows < rows) t.rows *= 2;
             t.e.bytes = (size_t)t.rows * (d / 2) * sizeof(float2);

@@ -48,6 +48,23 @@ def test_smaller_workspace_runs_in_fewer_parts():
     assert fk.attend_prefill(q, k, v, again, None, L, 4, 1, 128, 2048, 50, wl.rope_base, check=False) == -3
 
 
+def test_more_rotary_bases_than_tables():
+    """From the 17th table of a device on, calls keep the cos/sin in their own workspace: the same results."""
+    wl = _wl(1, 2, 70)
+    q, k, v = _mk(wl, 70, 20, seed=3)
+    torch.cuda.synchronize()
+    fk.shutdown()                                     # the tables of other tests
+    for i in range(20):
+        out, lse, _ = _run(q, k, v, wl, 70, base=1000.0 + i)
+        if i in (0, 17, 19):
+            assert _check(q, k, v, out, lse, wl, 70, base=1000.0 + i) <= TOL_PREFILL
+    again, _, _ = _run(q, k, v, wl, 70, base=1000.0)
+    first, _, _ = _run(q, k, v, wl, 70, base=1019.0)
+    assert _check(q, k, v, again, None, wl, 70, base=1000.0) <= TOL_PREFILL and torch.equal(first, out)
+    torch.cuda.synchronize()
+    fk.shutdown()
+
+
 def test_cos_sin_table_grows():
     for cur in (100, 5000, 300):
         wl = _wl(1, 2, cur)
