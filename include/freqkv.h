@@ -71,8 +71,10 @@ typedef enum {
 /*
  * Forms of the compression on bf16 caches, without the flags above:
  *   near/far   head_dim a multiple of 32, retain_ratio >= 0.2, spans of 128 to some 12000 rows, a span of less than
- *              4 GiB: exact entries close to the diagonal, interpolated ones further away (error below 5e-3 of the
- *              RMS).  freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
+ *              4 GiB: exact entries close to the diagonal, interpolated ones further away.  Before the result is
+ *              rounded the largest error is below 5e-3 of the RMS of the channel's span (rms 3e-4), as in the
+ *              other forms; the error does not shrink with the result, so that relative to a result that is
+ *              much smaller than its span (nearly all of it in the discarded band) it is larger.  freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
  *              have otherwise, with that form's sizes and counts; of the workspace that it asks for
  *              workspace_min_bytes have to be there, but stay unused.
  *   variant 6  the factored transform, head_dim not a multiple of 32, retain_ratio 0.5, spans n = 4pq with a compiled

@@ -403,8 +403,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 
     if (wave >= kCompute) {
         // ---- movers.  Leaves go out in the order in which they are used: last to first for the moments, then, since the
-        // first R of them are still in the ring, R, R+1, ... for the results (20 % of the second reading saved at 8188 rows, 40
-        // % at 4092).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
+        // first R of them are still in the ring, R, R+1, ... for the results (of 64 leaves at 8188 rows 13 stay in the
+        // ring, and 16 in registers, see below; of 32 at 4092 rows 15).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
         // the barrier after them.  Slots are taken in one direction round the ring on the way down and in the other on
         // the way up, so that leaf l and leaf l + R share one.
         // A mover issues little besides copies: its own instructions, branches above all, are what bounds the first reading when
