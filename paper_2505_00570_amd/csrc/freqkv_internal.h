@@ -148,6 +148,8 @@ struct NfGeom {
     int NLm, NCp, NGp, NX;   // leaves, blocks, groups that LDS has room for; vectors where blocks and later tiles go
     int R, NLr;              // ring slots; (NL - 1) mod R
     int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
+    int TU, NU;              // the form by units (freqkv_nearfar_units.hip): tiles per unit, units; TU 0: not that form
+    int held, held0, held_every;  // ... blocks that its movers hold in registers: how many, the first, their distance
     int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;
     int d;
@@ -156,6 +158,9 @@ struct NfGeom {
     long long stride_batch, stride_head, stride_token, tap_slab0;
 };
 bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out);
+bool nf_unit_geometry(int n, int Lc, int head_dim, NfGeom* out);
+hipError_t launch_nf_unit_tables(const NfGeom& g, char* out, hipStream_t st);
+hipError_t launch_nearfar_units(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, unsigned grid, hipStream_t st);
 hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st);
 hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, hipStream_t st);
 

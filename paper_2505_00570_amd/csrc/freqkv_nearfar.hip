@@ -35,7 +35,7 @@
 //
 // Four waves move data (global -> LDS copies, counted by vmcnt), four compute; apart, because the copies and the loads of
 // tables come back in one order: a wave that did both would wait for its newest copies in front of every table.
-#include "freqkv_internal.h"
+#include "freqkv_nearfar.h"
 
 #include <cmath>
 #include <cstring>
@@ -43,51 +43,6 @@
 namespace freqkv {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-template <int I> struct IC { static constexpr int value = I; };
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (I < N) {
-        f(IC<I>{});
-        static_for<N, I + 1>(f);
-    }
-}
-
-// f(IC<i>) for a uniform i in [0, N).  The cases end in different (empty) assembly: merged into one, what they do to the elements of
-// an array would keep that array in scratch memory.
-template <int N, class F>
-__device__ __forceinline__ void dispatch(int i, F&& f)
-{
-    static_for<N>([&](auto c) {
-        if (i == c.value) {
-            f(c);
-            asm volatile("; %0" :: "n"(c.value));
-        }
-    });
-}
-
-constexpr int kC = 32;                    // channels per workgroup
-constexpr int kRowB = kC * 2;             // bytes of one row in a ring slot
-constexpr int kLeaf = 128;                // span rows per leaf
-constexpr int kSlotB = kLeaf * kRowB;     // bytes of one ring slot
-constexpr int kVecB = kC * 8 * 2;         // bytes of 8 moments (or local values) of 32 channels, [channel][8] bf16
-constexpr int kFrag = 1024;               // one operand fragment: 64 lanes x 8 bf16
-constexpr int kCompute = 4, kMovers = 4;  // waves
-constexpr int kNB = 3;                    // blocks of a group's neighbourhood: 512 rows or less, 128 to spare on both sides
-constexpr int kHeld = 4;                  // blocks that the movers keep in registers
-constexpr int kTabFrags = 6;              // table fragments kept in LDS
-constexpr int kLdsBytes = 160 * 1024;
 
 // Where the exact window of tile t starts (leaf), and whether the ends of the span shifted it.
 struct TileAt { int leaf0, clamped; };
@@ -126,23 +81,6 @@ __host__ __device__ inline int group_block0(const NfGeom& g, int gr)
 // tables, built on the device in fp64 and rounded once
 // ------------------------------------------------------------------------------------------
 
-// Chebyshev points of the first kind on [-1, 1] and the Lagrange polynomials on them.
-__device__ double cheb(int s) { return cospi((2 * s + 1) / 16.0); }
-__device__ double lagrange(int s, double u)
-{
-    double p = 1.0;
-    const double xs = cheb(s);
-    for (int q = 0; q < 8; ++q)
-        if (q != s) p *= (u - cheb(q)) / (xs - cheb(q));
-    return p;
-}
-// E of the header comment at the angle pi q / (2 n Lc); its limit at zero is 2 Lc.
-__device__ double entry(long long q, long long n, long long Lc)
-{
-    if (q == 0) return 2.0 * (double)Lc;
-    const double t = (double)q / (double)(4 * n * Lc);
-    return sinpi((double)(q % (4 * n)) / (double)(2 * n)) * cospi(t) / sinpi(t);
-}
 // K between two positions in span rows; image_only: without its direct term.
 __device__ double far_kernel(double a, double b, double n, bool image_only)
 {
@@ -151,11 +89,7 @@ __device__ double far_kernel(double a, double b, double n, bool image_only)
     if (!image_only) v += cospi(d) / sinpi(d);
     return 0.5 * v;
 }
-// Intervals in span rows, cut at the end of the span.
-struct Iv {
-    double c, h;             // centre, half width; h <= 0: nothing in it
-    __device__ double node(int s) const { return c + h * cheb(s); }
-};
+// Intervals are cut at the end of the span.
 __device__ Iv interval(double a, double b, double n)
 {
     if (b > n) b = n;
@@ -195,9 +129,6 @@ __device__ double near_entry(const NfGeom& g, int slot, int m_in, int row_in)
     if (!direct) v += entry((2 * m + 1) * n + (2 * j + 1) * Lc, n, Lc);
     return v / (2.0 * n);
 }
-
-// What a bf16 holds of x; the rest, rounded in its turn, is its second part.
-__device__ double first_part(double x) { return (double)(float)(__bf16)(float)x; }
 
 // What the kernel wants to know of tile t, in one scalar load: first leaf of the window, first step with second parts, table
 // slot | slot of the wave's next tile (of this task or the next), first block of the next group's neighbourhood.
@@ -302,51 +233,6 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
 // ------------------------------------------------------------------------------------------
 // the kernel
 // ------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed: one of 32 immediates, found
-// by halves.
-template <int LO = 0, int HI = 32>
-__device__ __forceinline__ void wait_copies(int leaves)
-{
-    if constexpr (HI - LO == 1) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LO) : "memory");
-    } else {
-        constexpr int MID = (LO + HI) / 2;
-        if (leaves < MID) wait_copies<LO, MID>(leaves);
-        else wait_copies<MID, HI>(leaves);
-    }
-}
-
-// A load that only some passes through a loop issue is awaited where it is issued: otherwise the compiler has to expect it in
-// flight at every use, and waits there for whatever is really in flight, copies and stores.
-__device__ __forceinline__ void pin(bf16x8& v) { asm volatile("" : "+v"(v)); }
-
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
-
-// Four consecutive rows of 16 columns, transposed: lane i of 16 gets column i.  Each lane names the 8 bytes
-// (row lane/4, columns 4 (lane%4) ..) that it fetches.
-__device__ __forceinline__ s16x4 read_tr(const char* p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p); }
-
-__device__ __forceinline__ bf16x8 join(s16x4 a, s16x4 b)
-{
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-__device__ __forceinline__ uint32_t pack2(float a, float b)
-{
-    f32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-__device__ __forceinline__ u32x2 pack4(f32x4 a) { return u32x2{pack2(a[0], a[1]), pack2(a[2], a[3])}; }
 
 // NK: leaves per exact window; NLO: 16-row steps of it with a second part; TPW: tiles per computing wave and step.
 // SHIFTS: tables of exact entries repeat from tile to tile (NfGeom::shifts) and stay in registers.
@@ -863,6 +749,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
 {
     if (head_dim % kC || Lc >= n || n < kNfMinSpan || n > 16384 || 5LL * Lc < n) return false;
+    if (nf_unit_geometry(n, Lc, head_dim, out)) return true;
     NfGeom g;
     memset(&g, 0, sizeof(g));
     g.n = n; g.Lc = Lc; g.d = head_dim;
@@ -927,6 +814,7 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
 
 hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st)
 {
+    if (g.TU) return launch_nf_unit_tables(g, out, st);
     const long long threads = g.off_w / 16 + g.NT + 1;
     hipLaunchKernelGGL(k_nf_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, out);
     return hipGetLastError();
@@ -940,6 +828,7 @@ hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tab
     if (e != hipSuccess) return e;
     const unsigned tasks = (unsigned)(g.hts * (g.d / kC)), resident = (unsigned)cus / 8 * 8;
     const unsigned grid = resident >= 8 && tasks > resident ? resident : tasks;
+    if (g.TU) return launch_nearfar_units(tab, g, tables, tap, grid, st);
     const dim3 block((kCompute + kMovers) * 64);
     if (g.NK == 2) {
         if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
