@@ -186,6 +186,8 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     __shared__ __attribute__((aligned(1024))) char ksm[4][kTileBytes];   // Kr tiles t+1, t+2, t+3 of step t (ring)
     __shared__ __attribute__((aligned(1024))) char vsm[4][kTileBytes];   // Vt tiles t .. t+3 (ring)
 
+    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves][32 * 256];
+
     static_assert(kTileBytes == kPrefillWaves * 64 * 16, "one 16-byte piece of a tile per thread");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: the loop bounds below are per wave
     const int lane = threadIdx.x & 63;
@@ -242,38 +244,6 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         my_tiles = min(my_tiles, wg_tiles);
     }
 
-    // ---- queries of this wave: second operand of S^T = Kr Qr^T, lane = query column, 8 channels per k-step half.
-    // Qr = rotate(q at its in-cache position) * log2(e)/sqrt(d), computed here once per wave: the lane's groups
-    // of 8 channels in the lower half (k-steps 0..3) and their rotary partners in the upper half (k-steps 4..7)
-    // come from the same two 16-byte loads.  Rows of the block beyond q_len are zero.
-    half8 qf[8];
-    {
-        const bool have = active && q0 + l32 < g.q_len;
-        const uint16_t* qrow = q + (head * g.q_len + (have ? q0 + l32 : 0)) * kD;
-        const float2* crow = cs + (long long)(have ? pos0 + l32 : 0) * (kD / 2);
-        static_for<4>([&](auto sc) {
-            constexpr int S = decltype(sc)::value;
-            const int j0 = S * 16 + hw * 8;                   // first rotary pair of the group
-            half8 lo8 = {}, up8 = {};
-            if (have) {
-                const u32x4 lo = *(const u32x4*)(qrow + j0), up = *(const u32x4*)(qrow + kD / 2 + j0);
-                static_for<4>([&](auto ec) {
-                    constexpr int E = decltype(ec)::value;
-                    const float a0 = bf16_lo(lo[E]), a1 = bf16_hi(lo[E]);
-                    const float b0 = bf16_lo(up[E]), b1 = bf16_hi(up[E]);
-                    const float2 c0 = crow[j0 + 2 * E], c1 = crow[j0 + 2 * E + 1];
-                    // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
-                    lo8[2 * E]     = (_Float16)((a0 * c0.x - b0 * c0.y) * g.qscale);
-                    lo8[2 * E + 1] = (_Float16)((a1 * c1.x - b1 * c1.y) * g.qscale);
-                    up8[2 * E]     = (_Float16)((b0 * c0.x + a0 * c0.y) * g.qscale);
-                    up8[2 * E + 1] = (_Float16)((b1 * c1.x + a1 * c1.y) * g.qscale);
-                });
-            }
-            qf[S] = lo8;
-            qf[S + 4] = up8;
-        });
-    }
-
     f32x16 acc[4];              // O^T: [channel block], 32 channels x 32 queries each
     static_for<4>([&](auto db) { static_for<16>([&](auto r) { acc[db.value][r.value] = 0.f; }); });
     float m = 0.f, lsum = 0.f;  // m: reference point of the lane's query (both half-waves agree); lsum: this half-wave's share
@@ -305,7 +275,54 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         dma_k(min(t0 + i.value, last_tile), t0 + i.value);
         dma_v(min(t0 + i.value, last_tile), t0 + i.value);
     });
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // ---- queries of this wave: second operand of S^T = Kr Qr^T, lane = query column, 8 channels per k-step half.
+    // Qr = rotate(q at its in-cache position) * log2(e)/sqrt(d), computed here once per wave: the lane's groups
+    // of 8 channels in the lower half (k-steps 0..3) and their rotary partners in the upper half (k-steps 4..7) are
+    // in its registers together.  A lane wants 16 bytes here and there of a query's row and of its row of cos and sin: asked for
+    // like that, 64 lines to a load, the start of a workgroup took 7 us.  So rows come in whole, all of them in flight at once, and
+    // turn through 8 KB of LDS per wave, three times: 16 pieces of 16 bytes of 32 rows, piece p of row r in place p ^ (r & 15).
+    // Rows of the block beyond q_len are zero (another row is loaded for them).
+    half8 qf[8];
+    {
+        char* const turn = qsm[wave];
+        const int r0 = lane >> 4, piece = lane & 15;
+        auto put = [&](auto j, u32x4 x) { *(u32x4*)(turn + (4 * j.value + r0) * 256 + ((piece ^ (4 * j.value + r0)) & 15) * 16) = x; };
+        auto get = [&](int pc) { return *(const u32x4*)(turn + l32 * 256 + ((pc ^ l32) & 15) * 16); };
+        const uint16_t* const qrows = q + (head * g.q_len + (active ? q0 : 0)) * kD + piece * 8;
+        const float2* const crows = cs + (long long)(active ? pos0 : 0) * (kD / 2) + piece * 2;
+        const int most = active ? g.q_len - 1 - q0 : 0;       // last row of the block that there is
+        u32x4 x[8], c[2][8];
+        static_for<8>([&](auto j) { x[j.value] = *(const u32x4*)(qrows + (long long)min(4 * j.value + r0, most) * kD); });
+        static_for<2>([&](auto h) {
+            static_for<8>([&](auto j) { c[h.value][j.value] = *(const u32x4*)(crows + (long long)min(4 * j.value + r0, most) * (kD / 2) + h.value * 32); });
+        });
+        u32x4 lo[4], up[4];
+        static_for<8>([&](auto j) { put(j, x[j.value]); });
+        static_for<4>([&](auto s) { lo[s.value] = get(2 * s.value + hw); up[s.value] = get(8 + 2 * s.value + hw); });
+        static_for<2>([&](auto h) {
+            static_for<8>([&](auto j) { put(j, c[h.value][j.value]); });
+            static_for<2>([&](auto s) {
+                constexpr int S = 2 * h.value + s.value;
+                half8 lo8, up8;
+                static_for<4>([&](auto ec) {
+                    constexpr int E = decltype(ec)::value;
+                    const u32x4 w = get(8 * s.value + 4 * hw + E);
+                    const float2 c0 = {__uint_as_float(w[0]), __uint_as_float(w[1])}, c1 = {__uint_as_float(w[2]), __uint_as_float(w[3])};
+                    const float a0 = bf16_lo(lo[S][E]), a1 = bf16_hi(lo[S][E]);
+                    const float b0 = bf16_lo(up[S][E]), b1 = bf16_hi(up[S][E]);
+                    // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
+                    lo8[2 * E]     = (_Float16)((a0 * c0.x - b0 * c0.y) * g.qscale);
+                    lo8[2 * E + 1] = (_Float16)((a1 * c1.x - b1 * c1.y) * g.qscale);
+                    up8[2 * E]     = (_Float16)((b0 * c0.x + a0 * c0.y) * g.qscale);
+                    up8[2 * E + 1] = (_Float16)((b1 * c1.x + a1 * c1.y) * g.qscale);
+                });
+                qf[S] = lo8;
+                qf[S + 4] = up8;
+            });
+        });
+        if (!active || l32 > most) static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);                // all loads and copies have landed (in a form that the compiler takes into account)
     __syncthreads();
 
     half8 kf[8], vf[8];         // fragments of Kr(t+1) and Vt(t), read from LDS a few matrix instructions ahead
@@ -420,10 +437,6 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
-    // The queries are consumed above only by waves that have tiles; using them here makes the compiler wait for
-    // their loads on every path, instead of in front of the first matrix instruction of each step (where the
-    // wait would also cover the tile loads just issued).
-    asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7]));
     for (int t = t0; t < wg_tiles; t += 2) {
         step(t, cur, nxt);
         if (t + 1 < wg_tiles) step(t + 1, nxt, cur);
