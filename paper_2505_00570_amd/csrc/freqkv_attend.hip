@@ -83,6 +83,39 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x)
     return x;
 }
 
+// x op (x of the lane O further or nearer), in every lane; O = 8, 16 or 32.  On the vector units: a shuffle goes through LDS, and
+// a chain of them is what the end of a short call waits for.
+template <int O, class F> __device__ __forceinline__ float fold(float x, F&& op)
+{
+    if constexpr (O == 8) {
+        return op(x, dpp<0x128>(x));             // the row of 16 turned by 8
+    } else if constexpr (O == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    } else {
+        static_assert(O == 32);
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    }
+}
+// ... over the lanes O, 2 O, ... 32 apart
+template <int O, class F> __device__ __forceinline__ float fold_from(float x, F&& op)
+{
+    x = fold<O>(x, op);
+    if constexpr (O < 32) x = fold_from<2 * O>(x, op);
+    return x;
+}
+// ... over all 64 lanes
+template <class F> __device__ __forceinline__ float wave_fold(float x, F&& op)
+{
+    x = op(x, dpp<0xB1>(x));                     // lanes 1, 2 and 4 apart (quads exchange halves, half rows of 8 mirror)
+    x = op(x, dpp<0x4E>(x));
+    x = op(x, dpp<0x141>(x));
+    return fold_from<8>(x, op);
+}
+struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
 // Two adjacent results, rounded once.
 __device__ __forceinline__ void store2(uint16_t* p, float a, float b)
 {
@@ -150,7 +183,8 @@ __global__ void k_rope_table(RopeEntry* rt, int d, double base, int step)
 // (Two forms were built and taken back.  Merging by the workgroup that arrives last: the arrival counter of a launch is an
 // atomic of many workgroups on 8 XCDs, 28 us for 16 chunks of 8 heads against 19.5 with the second kernel.  Workgroups of
 // eight waves: half as many loop steps, but the same time, 14.9 against 15.1 us at 32 chunks.)
-template <typename T, int D, int GT, int P, bool ONE>
+// EXACT: no surplus loop step where a chunk has an odd number of them.
+template <typename T, int D, int GT, int P, bool ONE, bool EXACT>
 __global__ __launch_bounds__(kWaves * 64, attend_min_waves(sizeof(T), GT, P))
 void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict__ q,
                       const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
@@ -343,21 +377,22 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
             });
         });
     };
-    // Two register sets take turns: while one step is consumed the loads of the next are in flight.  The step
+    // Two register sets take turns: while one step is consumed the loads of the next are in flight.  Without EXACT the step
     // count is rounded up to even; a surplus step sees only rows past the end (weights exactly zero).
     for (int it = 0; it < nit; it += 2) {
         issue(rb);
         consume(ra, it);
+        if (EXACT && it + 1 >= nit) break;
         issue(ra);
         consume(rb, it + 1);
     }
 
     // ---- combine the lane groups of the workgroup
-    // 1. common maximum per query head: over the lane groups of a wave by shuffles, over waves through LDS
+    // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS
     static_for<GT>([&](auto gg) {
         constexpr int gi = decltype(gg)::value;
         float mx = m[gi];
-        for (int o = LPR; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        mx = fold_from<LPR>(mx, Max{});
         if (lane == 0) xm[gi][wave] = mx;
     });
     __syncthreads();
@@ -368,14 +403,12 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
         float f = exp2_fast(m[gi] - M);
         m[gi] = M;
         float ls = lsum[gi] * f;
-        for (int o = LPR; o < 64; o <<= 1) ls += __shfl_xor(ls, o);
+        ls = fold_from<LPR>(ls, Add{});
         if (lane == 0) xl[gi][wave] = ls;
         // rescale, fold the neighbouring lane group in, park the even groups' sums in LDS
         static_for<2 * P>([&](auto cc) {
             constexpr int ci = decltype(cc)::value;
-            float v = acc[gi][ci] * f;
-            v += __shfl_xor(v, LPR);
-            acc[gi][ci] = v;
+            acc[gi][ci] = fold<LPR>(acc[gi][ci] * f, Add{});
         });
         if ((slot & 1) == 0) {
             float* dst = red + ((wave * (RPW / 2) + (slot >> 1)) * GT + gi) * D;
@@ -451,7 +484,7 @@ void k_attend_merge(const AttGeom g, const float* __restrict__ part_acc, const f
         });
         const f32x2 mine = tid < here ? ml[s0 + tid] : f32x2{kMinusBig, 0.f};
         float mx = mine[0];
-        for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        mx = wave_fold(mx, Max{});
         if (lane == 0) wm[wave] = mx;
         __syncthreads();
         float Mn = M;
@@ -459,7 +492,7 @@ void k_attend_merge(const AttGeom g, const float* __restrict__ part_acc, const f
         const float w = tid < here ? exp2_fast(mine[0] - Mn) : 0.f;
         sh_w[tid] = w;
         float ls = mine[1] * w;
-        for (int o = 1; o < 64; o <<= 1) ls += __shfl_xor(ls, o);
+        ls = wave_fold(ls, Add{});
         if (lane == 0) wl[wave] = ls;
         __syncthreads();
         const float f = exp2_fast(M - Mn);
@@ -501,12 +534,12 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, int D, int GT, bool ONE>
+template <typename T, int D, int GT, bool ONE, bool EXACT>
 static void launch_partial_o(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
                              float* part_ml, void* out, float* lse, hipStream_t st)
 {
     const dim3 grid((unsigned)(g.units * g.n_split), (unsigned)(g.G / g.GT));
-    hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE>), grid, dim3(kWaves * 64), 0, st, tab, g, (const T*)q, rt,
+    hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE, EXACT>), grid, dim3(kWaves * 64), 0, st, tab, g, (const T*)q, rt,
                        part_acc, part_ml, (T*)out, lse);
 }
 
@@ -514,8 +547,14 @@ template <typename T, int D, int GT>
 static void launch_partial_g(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
                              float* part_ml, void* out, float* lse, hipStream_t st)
 {
-    if (g.n_split == 1) launch_partial_o<T, D, GT, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
-    else                launch_partial_o<T, D, GT, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+    // Odd numbers of steps up to 23: leaving the last one out gives 4 % and more (7 steps, 28 chunks of 224 rows: 15.1 -> 13.8 us per
+    // call); the branch in the loop costs 0.4 % of long chunks.
+    const int steps = g.chunk / (kUnroll * attend_row_step(D));
+    const bool exact = (steps & 1) && steps < 24;
+    if (g.n_split == 1) exact ? launch_partial_o<T, D, GT, true, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st)
+                              : launch_partial_o<T, D, GT, true, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+    else                exact ? launch_partial_o<T, D, GT, false, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st)
+                              : launch_partial_o<T, D, GT, false, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
 }
 
 template <typename T, int D>
