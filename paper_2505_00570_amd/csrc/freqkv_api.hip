@@ -1289,31 +1289,44 @@ struct PrefillShape {
     int q_len, q_pad, key_tiles, layers_per_pass;
     size_t off_kr, off_vt, off_part, workspace_bytes, workspace_min;
     size_t part_bytes;          // states of one part of the key range
-    int n_split;                // parts of the key range, given a workspace of workspace_bytes
+    int halves, n_split;        // shares of a workgroup, parts of the key range, given a workspace of workspace_bytes
 };
 
-// Parts that the key tiles of the workgroups are cut into when these are too few for the 256 compute units (one holds one
-// workgroup).  tiles: of the longest workgroup; first: of the shortest (causal: the lengths rise evenly in between).  A tile
-// takes a workgroup 0.72 us, 0.9 when there is more than one for each (the clock falls); a part's states (16.6 KB per task) are
-// written and read at about 7 TB/s; merging adds 4 us and 0.25 per part.  The time is the longest of: one workgroup; all
-// tiles evenly spread; the whole rounds that equal workgroups make.  8 KV heads of 4 query heads: 301 queries on 5001 rows
-// 125 us in one part, 53 in 6, 69 in 12; 1 query on 8192 rows 131, 43 (6), 38 (12), 48 (32); 600 queries on 2 x 4096
-// rows 111 in one part, 119 in 3; 7088 queries on as many rows 395 in one part, 530 in 3.
-int prefill_splits(long long wgs, long long tasks, int tiles, int first)
+// How the keys of a chunk-wise call are shared out when its workgroups are too few for the 256 compute units: among the two halves of a
+// workgroup (which then has 4 tasks instead of 8), and into parts of the key range that k_prefill_merge brings together.
+// tiles: of the longest workgroup; first: of the shortest (causal: the lengths rise evenly in between).  What is estimated, in
+// microseconds: the longest of one workgroup, all tiles evenly spread, and the whole rounds that equal workgroups make, at 0.9 per tile
+// and stream of keys (0.72 where a workgroup of one stream has its compute unit to itself; with halves two streams of copies run
+// there); 5 for each further start of a workgroup on a compute unit; for parts, 3, 1 per part, and a write and a read of
+// their states (16.6 KB per task) at 7 TB/s.  The halves' own meeting, in LDS, is next to nothing; with up to 4 tasks they would only
+// give work to waves that are idle in a workgroup of one stream, and parts alone measure the same.
+// Measured with 8 KV heads of 4 query heads, as (halves x parts): 1000 queries on 1000 rows 35.0 us (1x1), 27.4 (2x1), 41.5 (2x2); 300 on
+// 300 18.8 (1x1), 15.9 (2x1); 100 on 1000 26.4 (1x3), 23.9 (2x3); 301 on 5001 123 (1x1), 51.4 (1x6), 51.5 (2x3), 66 (1x8 and 2x4: a
+// second round); 1 on 8192 134 (1x1), 41.6 (1x10), 40.7 (2x10), 43.4 (1x16); 600 on 2 x 4096 109 (1x1), 128 (2x1); 2000 on 8192 238
+// (1x1), 246 (2x1), 250 (1x2); 200 on 200 in 8 layers 23.1 (1x1), 28.9 (2x1).
+struct PrefillCut { int halves, n_split; };
+PrefillCut prefill_cut(long long units, long long tasks_per_unit, int tiles, int first)
 {
-    int best = 1;
+    PrefillCut best = {1, 1};
     double best_us = 1e30;
-    const double avg = 0.5 * (tiles + first);
-    for (int s = 1; s <= 32 && (s == 1 || s * 4 <= tiles); ++s) {
+    const double avg = 0.5 * (tiles + first), tasks = (double)(units * tasks_per_unit);
+    auto consider = [&](int halves, int s) {
+        const double wgs = (double)(units * ((tasks_per_unit * halves + 7) / 8));
         const double part = std::ceil((double)tiles / s);
-        const double busy = s == 1 ? wgs / 256.0 : wgs * std::ceil(avg / part) / 256.0, tile_us = busy > 1.0 ? 0.9 : 0.72;
+        const double busy = s == 1 ? wgs / 256.0 : wgs * std::ceil(avg / part) / 256.0;
         double us = part;
         if (us < wgs * avg / 256.0) us = wgs * avg / 256.0;
         const double rounds = std::ceil(busy) * (s == 1 ? first : part);
         if (us < rounds) us = rounds;
-        us *= tile_us;
-        if (s > 1) us += 4.0 + 0.25 * s + (double)tasks * s * 16640.0 * 2.0 / 7e6;
-        if (us < 0.97 * best_us) { best = s; best_us = us; }
+        us *= (halves == 1 && busy <= 1.0 ? 0.72 : 0.9) / halves;
+        if (busy > 1.0) us += 5.0 * (busy - 1.0);
+        if (s > 1) us += 3.0 + s + tasks * s * 16640.0 * 2.0 / 7e6;
+        if (us < 0.97 * best_us) { best = {halves, s}; best_us = us; }
+    };
+    // (in the order of the streams of keys that a task is cut into: more of them have to gain something)
+    for (int n = 1; n <= 64 && (n <= 2 || n * 4 <= tiles); ++n) {
+        if (n == 1 || (n <= 32 && n * 4 <= tiles)) consider(1, n);
+        if (n % 2 == 0 && tasks_per_unit > 4 && tiles > 1) consider(2, n / 2);
     }
     return best;
 }
@@ -1340,7 +1353,9 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     p.workspace_min = p.off_part;
     const long long tasks = units * p.a.G * (p.q_pad / 32);
     p.part_bytes = (size_t)tasks * (32 * d * sizeof(float) + 32 * sizeof(float2));
-    p.n_split = prefill_splits(units * ((p.a.G * (p.q_pad / 32) + 7) / 8), tasks, p.key_tiles, (cur_len - q_len) / 32 + 1);
+    const PrefillCut cut = prefill_cut(units, (long long)p.a.G * (p.q_pad / 32), p.key_tiles, (cur_len - q_len) / 32 + 1);
+    p.halves = cut.halves;
+    p.n_split = cut.n_split;
     p.workspace_bytes = p.workspace_min + (p.n_split > 1 ? p.n_split * p.part_bytes : 0);
     *out = p;
     return FREQKV_OK;
@@ -1413,7 +1428,7 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
         g.d = a.d; g.G = a.G; g.n_kv = a.n_kv;
         g.units = layers * upl; g.units_per_layer = upl;
         g.cur_len = cur_len; g.q_len = q_len; g.q_pad = p.q_pad; g.q_blocks = p.q_pad / 32;
-        g.key_tiles = p.key_tiles; g.n_split = n_split; g.split_tiles = split_tiles;
+        g.key_tiles = p.key_tiles; g.n_split = n_split; g.split_tiles = split_tiles; g.halves = p.halves;
         g.stride_batch = L.stride_batch; g.stride_head = L.stride_head; g.stride_token = L.stride_token;
         g.qscale = (float)(1.4426950408889634 / std::sqrt((double)a.d));
         const long long head0 = (long long)l0 * upl * a.G;

@@ -231,6 +231,7 @@ struct PrefillGeom {
     int key_tiles;         // ceil(cur_len / 32)
     int n_split;           // parts that the key tiles of a workgroup are cut into, of split_tiles tiles each
     int split_tiles;
+    int halves;            // 2: the waves of a workgroup share out the keys of its part in two halves (4 tasks instead of 8)
     long long stride_batch, stride_head, stride_token;   // elements
     float qscale;          // log2(e) / sqrt(d)
 };

@@ -178,22 +178,30 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const SlabTable tab, const
 // A wave keeps its 32 queries, their 128 x 32 output block and two 32 x 32 score blocks in vector registers
 // (under 256 in all, so that two waves share a SIMD and the matrix instructions take all operands from the
 // vector registers).
+// HALVES == 2, for short calls: a workgroup has 4 tasks, and its first and last four waves (two to a SIMD) take the two halves of the
+// keys, each with rings of its own; the halves meet in LDS at the end.  So half as many states go through memory as with as many parts
+// of the key range more, or none, and no merging kernel.  (halves, parts) with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 35.0 us
+// (1, 1) -> 27.4 (2, 1); 100 on 1000 26.4 (1, 3) -> 23.9 (2, 3); 256 on 4000 50.8 -> 49.4.  A step of one tile of each half takes 0.985
+// us against 0.907 for a step of eight tasks (twice the copies).
+template <int HALVES>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
 void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,
                       const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
                       float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml)
 {
-    __shared__ __attribute__((aligned(1024))) char ksm[4][kTileBytes];   // Kr tiles t+1, t+2, t+3 of step t (ring)
-    __shared__ __attribute__((aligned(1024))) char vsm[4][kTileBytes];   // Vt tiles t .. t+3 (ring)
+    constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
+    __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
+    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];   // (two halves: and the slots not yet used)
 
-    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves][32 * 256];
-
-    static_assert(kTileBytes == kPrefillWaves * 64 * 16, "one 16-byte piece of a tile per thread");
+    static_assert(kTileBytes % (TASKS * 64 * 16) == 0, "whole 16-byte pieces of a tile per thread");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: the loop bounds below are per wave
     const int lane = threadIdx.x & 63;
+    const int half = wave / TASKS, tw = wave % TASKS;
+    auto& ksm = ring[half][0];
+    auto& vsm = ring[half][1];
     const int l32 = lane & 31, hw = lane >> 5;
     const int tasks_per_unit = g.G * g.q_blocks;
-    const int wgs_per_unit = (tasks_per_unit + kPrefillWaves - 1) / kPrefillWaves;
+    const int wgs_per_unit = (tasks_per_unit + TASKS - 1) / TASKS;
     // blockIdx -> (KV unit, workgroup of the unit).  Workgroups are dealt round-robin to the 8 XCDs, so inside a
     // group of 8 units the XCD index picks the unit: all workgroups of a unit run on one XCD and share its L2
     // for the unit's K/V tiles (dealt unit by unit, every XCD fetched every unit: 12.7 GB of fabric reads per
@@ -217,7 +225,7 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     }
     // later query blocks see more keys: hand them out first so that the long workgroups start early
     const int wg_in_unit = wgs_per_unit - 1 - wg_seq;
-    const int task = wg_in_unit * kPrefillWaves + wave;
+    const int task = wg_in_unit * TASKS + tw;
     const bool active = task < tasks_per_unit;
     const int qb = active ? task / g.G : 0;
     const int gh = active ? task - qb * g.G : 0;
@@ -231,18 +239,23 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     const int full_tiles = active ? (pos0 + 1) / kKeyTile : 0;     // tiles every query of the wave sees whole
     int wg_tiles;
     {
-        const int last_task = min(wg_in_unit * kPrefillWaves + kPrefillWaves - 1, tasks_per_unit - 1);
+        const int last_task = min(wg_in_unit * TASKS + TASKS - 1, tasks_per_unit - 1);
         const int last_qb = last_task / g.G;
         const int wg_last = min(g.cur_len - g.q_len + last_qb * kQPerWave + kQPerWave - 1, g.cur_len - 1);
         wg_tiles = (wg_last + kKeyTile) / kKeyTile;
     }
     // few workgroups: the key tiles of each are cut into n_split parts, whose states k_prefill_merge brings together
-    const int t0 = split * g.split_tiles;
+    const int part0 = split * g.split_tiles;
     if (g.n_split > 1) {
-        if (t0 >= wg_tiles) return;                                // nobody here sees keys of this part
-        wg_tiles = min(wg_tiles, t0 + g.split_tiles);
+        if (part0 >= wg_tiles) return;                             // nobody here sees keys of this part
+        wg_tiles = min(wg_tiles, part0 + g.split_tiles);
         my_tiles = min(my_tiles, wg_tiles);
     }
+    const bool seen = my_tiles > part0;                            // the task sees keys of this part
+    // this half's tiles: t0 .. t0 + steps - 1, of which there may be one less for the second half
+    const int steps = HALVES == 1 ? wg_tiles - part0 : (wg_tiles - part0 + 1) / 2;
+    const int t0 = part0 + half * steps, t1 = min(t0 + steps, wg_tiles);
+    my_tiles = min(my_tiles, t1);
 
     f32x16 acc[4];              // O^T: [channel block], 32 channels x 32 queries each
     static_for<4>([&](auto db) { static_for<16>([&](auto r) { acc[db.value][r.value] = 0.f; }); });
@@ -252,7 +265,8 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
 
     const char* ksrc = (const char*)(Kr + (long long)unit * g.key_tiles * (kKeyTile * kD));
     const char* vsrc = (const char*)(Vt + (long long)unit * g.key_tiles * (kKeyTile * kD));
-    const int tid16 = threadIdx.x * 16;
+    constexpr int PIECE = kTileBytes / TASKS;          // of a tile, per wave
+    const int tid16 = tw * PIECE + lane * 16;
     const int frag = (hw * kKeyTile + l32) * 16;       // this lane's 16 bytes inside a k-step of a tile
 
     // Step t consumes tile t: it computes S(t+1) = Kr(t+1) Qr^T while the softmax of S(t) runs, then
@@ -264,13 +278,18 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // compiler, which cannot tell the ring slots apart, would wait for a copy issued through its builtin in
     // front of the next LDS read; the waits are placed by hand, before each barrier).
     typedef __attribute__((address_space(3))) char* lptr_t;
-    const uint32_t k_lds = (uint32_t)(uintptr_t)(lptr_t)ksm[0] + wave * 1024;
-    const uint32_t v_lds = (uint32_t)(uintptr_t)(lptr_t)vsm[0] + wave * 1024;
-    auto dma_k = [&](int tile, int slot) { lds_dma16(k_lds + (slot & 3) * kTileBytes, ksrc + (long long)tile * kTileBytes + tid16); };
-    auto dma_v = [&](int tile, int slot) { lds_dma16(v_lds + (slot & 3) * kTileBytes, vsrc + (long long)tile * kTileBytes + tid16); };
+    const uint32_t k_lds = (uint32_t)(uintptr_t)(lptr_t)ksm[0] + tw * PIECE;
+    const uint32_t v_lds = (uint32_t)(uintptr_t)(lptr_t)vsm[0] + tw * PIECE;
+    auto dma = [&](uint32_t lds, const char* src, int tile, int slot) {
+        static_for<PIECE / 1024>([&](auto i) {
+            lds_dma16(lds + (slot & 3) * kTileBytes + i.value * 1024, src + (long long)tile * kTileBytes + tid16 + i.value * 1024);
+        });
+    };
+    auto dma_k = [&](int tile, int slot) { dma(k_lds, ksrc, tile, slot); };
+    auto dma_v = [&](int tile, int slot) { dma(v_lds, vsrc, tile, slot); };
     // Copies past the last tile are not branched around: they repeat the last tile into a slot that nobody
     // reads any more, which keeps the loop free of branches.
-    const int last_tile = wg_tiles - 1;
+    const int last_tile = (t1 > t0 ? t1 : wg_tiles) - 1;
     static_for<3>([&](auto i) {
         dma_k(min(t0 + i.value, last_tile), t0 + i.value);
         dma_v(min(t0 + i.value, last_tile), t0 + i.value);
@@ -281,16 +300,18 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // in its registers together.  A lane wants 16 bytes here and there of a query's row and of its row of cos and sin: asked for
     // like that, 64 lines to a load, the start of a workgroup took 7 us.  So rows come in whole, all of them in flight at once, and
     // turn through 8 KB of LDS per wave, three times: 16 pieces of 16 bytes of 32 rows, piece p of row r in place p ^ (r & 15).
-    // Rows of the block beyond q_len are zero (another row is loaded for them).
+    // Rows of the block beyond q_len are zero (another row is loaded for them).  A wave without a task asks for nothing: the loads of
+    // seven such waves held up the eighth by 1 us (1 query of 4 heads on 200 rows: 13.8 -> 12.0 us).
     half8 qf[8];
-    {
-        char* const turn = qsm[wave];
+    static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
+    if (active) {
+        char* const turn = HALVES == 1 ? qsm[wave % TASKS] : tw < 2 ? ring[half][tw][(t0 + 3) & 3] : qsm[half * 2 + tw - 2];
         const int r0 = lane >> 4, piece = lane & 15;
         auto put = [&](auto j, u32x4 x) { *(u32x4*)(turn + (4 * j.value + r0) * 256 + ((piece ^ (4 * j.value + r0)) & 15) * 16) = x; };
         auto get = [&](int pc) { return *(const u32x4*)(turn + l32 * 256 + ((pc ^ l32) & 15) * 16); };
-        const uint16_t* const qrows = q + (head * g.q_len + (active ? q0 : 0)) * kD + piece * 8;
-        const float2* const crows = cs + (long long)(active ? pos0 : 0) * (kD / 2) + piece * 2;
-        const int most = active ? g.q_len - 1 - q0 : 0;       // last row of the block that there is
+        const uint16_t* const qrows = q + (head * g.q_len + q0) * kD + piece * 8;
+        const float2* const crows = cs + (long long)pos0 * (kD / 2) + piece * 2;
+        const int most = g.q_len - 1 - q0;                    // last row of the block that there is
         u32x4 x[8], c[2][8];
         static_for<8>([&](auto j) { x[j.value] = *(const u32x4*)(qrows + (long long)min(4 * j.value + r0, most) * kD); });
         static_for<2>([&](auto h) {
@@ -320,7 +341,7 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
                 qf[S + 4] = up8;
             });
         });
-        if (!active || l32 > most) static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
+        if (l32 > most) static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);                // all loads and copies have landed (in a form that the compiler takes into account)
     __syncthreads();
@@ -437,16 +458,46 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
-    for (int t = t0; t < wg_tiles; t += 2) {
+    for (int t = t0; t < t0 + steps; t += 2) {
         step(t, cur, nxt);
-        if (t + 1 < wg_tiles) step(t + 1, nxt, cur);
+        if (t + 1 < t0 + steps) step(t + 1, nxt, cur);
     }
 
     // ---- normalise and store: lane = query, registers = channels 8*(r/4) + 4*hw + r%4 of each block
     lsum += __shfl_xor(lsum, 32);
+    if constexpr (HALVES == 2) {
+        // (behind the last step's barrier nobody reads or copies into the rings any more)
+        f32x4* const meet = (f32x4*)(&ring[0][0][0][0] + tw * 18 * 1024) + lane;
+        float2* const meet_ml = (float2*)(&ring[0][0][0][0] + tw * 18 * 1024 + 16 * 1024) + lane;
+        if (half == 1) {
+            static_for<4>([&](auto db) {
+                static_for<4>([&](auto r4) {
+                    constexpr int R = 4 * decltype(r4)::value;
+                    meet[(db.value * 4 + r4.value) * 64] = f32x4{acc[db.value][R], acc[db.value][R + 1], acc[db.value][R + 2], acc[db.value][R + 3]};
+                });
+            });
+            *meet_ml = {m, lsum};
+        }
+        __syncthreads();
+        if (half == 1) return;
+        const float2 o = *meet_ml;
+        const float m0 = lsum > 0.f ? m : -1e30f, m1 = o.y > 0.f ? o.x : -1e30f, M = fmaxf(m0, m1);
+        const float f0 = exp2_fast(m0 - M), f1 = exp2_fast(m1 - M);
+        m = M;
+        lsum = lsum * f0 + o.y * f1;
+        static_for<4>([&](auto db) {
+            static_for<4>([&](auto r4) {
+                const f32x4 x = meet[(db.value * 4 + r4.value) * 64];
+                static_for<4>([&](auto i) {
+                    constexpr int R = 4 * decltype(r4)::value + decltype(i)::value;
+                    acc[db.value][R] = acc[db.value][R] * f0 + x[i.value] * f1;
+                });
+            });
+        });
+    }
     if (g.n_split > 1) {
         // the state as it is, in the order of the registers (1 KB per store): [task][part][channel block][register / 4][lane][4]
-        if (my_tiles > t0) {
+        if (seen) {
             const long long st = ((long long)unit * tasks_per_unit + task) * g.n_split + split;
             f32x4* o = (f32x4*)part_acc + st * (16 * 64) + lane;
             static_for<4>([&](auto db) {
@@ -543,10 +594,12 @@ hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const
                                  void* out, float* lse, float* part_acc, float2* part_ml, hipStream_t st)
 {
     if (g.d != kD || g.q_blocks * kQPerWave != g.q_pad) return hipErrorInvalidValue;
+    if (g.halves != 1 && g.halves != 2) return hipErrorInvalidValue;
     if (g.n_split < 1 || (g.n_split > 1 && (!part_acc || !part_ml || (long long)g.n_split * g.split_tiles < g.key_tiles))) return hipErrorInvalidValue;
-    const int wgs_per_unit = (g.G * g.q_blocks + kPrefillWaves - 1) / kPrefillWaves;
-    hipLaunchKernelGGL(k_attend_prefill, dim3((unsigned)((long long)g.units * wgs_per_unit * g.n_split)), dim3(kPrefillWaves * 64), 0,
-                       st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    const int tasks = kPrefillWaves / g.halves, wgs_per_unit = (g.G * g.q_blocks + tasks - 1) / tasks;
+    const dim3 grid((unsigned)((long long)g.units * wgs_per_unit * g.n_split)), block(kPrefillWaves * 64);
+    if (g.halves == 2) hipLaunchKernelGGL(k_attend_prefill<2>, grid, block, 0, st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    else               hipLaunchKernelGGL(k_attend_prefill<1>, grid, block, 0, st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
     if (g.n_split > 1)
         hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)((long long)g.units * g.G * g.q_blocks)), dim3(256), 0, st, g, part_acc, part_ml,
                            (uint16_t*)out, lse);
