@@ -249,10 +249,11 @@ freqkv_status_t check_shape(const freqkv_layout_t* L, int n_heads, int head_dim,
     }
     else sh.variant = (sh.n % 2 == 0 && sh.Lc % 2 == 0) ? kFoldF16 : kPlainF16;
     // The near/far form takes the place of all of these wherever it exists (no flag that asks for a matrix form, head_dim
-    // a multiple of 32, ratios from 0.2, spans that its LDS image holds).
+    // a multiple of 32, ratios from 0.2, spans of 128 to 16384 rows).
     sh.nearfar = sh.variant != kNone && sh.variant != kDrop && sh.variant != kF32 && !sh.high &&
                  !(L->flags & (FREQKV_FLAG_DENSE | FREQKV_FLAG_SINGLE_FOLD | FREQKV_FLAG_TWO_LEVEL_FOLD)) &&
-                 (long long)window * L->stride_token * 2 < (1LL << 32) && nf_geometry(sh.n, sh.Lc, head_dim, &sh.nf);
+                 (long long)window * L->stride_token * 2 < (1LL << 32) && nf_geometry(sh.n, sh.Lc, head_dim, &sh.nf) &&
+                 !(sh.nf.spills && sh.variant == kFast);                          // (that form's plan asks for no workspace)
     *out = sh;
     return FREQKV_OK;
 }
@@ -747,8 +748,8 @@ freqkv_status_t resolve_bases(void* k, void* v, const freqkv_layout_t& L, const 
     return FREQKV_OK;
 }
 
-// Near/far form over sh.nslabs slabs, each with a tail of its own: one kernel, in place and without a workspace; the tails move
-// afterwards, when the spans have been read.
+// Near/far form over sh.nslabs slabs, each with a tail of its own: one kernel, in place; spans whose leaves' moments do not fit LDS keep
+// these in the workspace.  The tails move afterwards, when the spans have been read.
 freqkv_status_t compress_nearfar(const std::vector<char*>& bases, const std::vector<int>& tails, const freqkv_layout_t& L,
                                  const Shape& sh, float* tap, hipStream_t st)
 {
@@ -759,6 +760,12 @@ freqkv_status_t compress_nearfar(const std::vector<char*>& bases, const std::vec
     NfGeom nf = sh.nf;
     nf.S = sh.S; nf.n_heads = sh.n_heads; nf.hts_per_slab = (int)sh.hts_per_slab;
     nf.stride_batch = L.stride_batch; nf.stride_head = L.stride_head; nf.stride_token = L.stride_token;
+    unsigned most_wgs = ~0u;
+    if (nf.spills) {                                          // the workspace of the matrix form, at least one slab's image, holds many
+        nf.spill = (char*)L.workspace;
+        most_wgs = (unsigned)std::min<size_t>(L.workspace_bytes / (size_t)nf.spill_bytes, 1u << 20);
+        if (!nf.spill || !most_wgs) return FREQKV_E_WORKSPACE;
+    }
     for (int s0 = 0; s0 < sh.nslabs; s0 += kMaxSlabs) {
         const int slabs = sh.nslabs - s0 < kMaxSlabs ? sh.nslabs - s0 : kMaxSlabs;
         SlabTable tab;
@@ -775,7 +782,7 @@ freqkv_status_t compress_nearfar(const std::vector<char*>& bases, const std::vec
         nf.tap_slab0 = s0;
         ProfSpan sp;
         HIP_TRY(prof_begin(st, 1, &sp));
-        HIP_TRY(launch_nearfar(tab, nf, tables, tap, st));
+        HIP_TRY(launch_nearfar(tab, nf, tables, tap, most_wgs, st));
         HIP_TRY(prof_end(st, &sp));
         if (most > 0) {
             HIP_TRY(prof_begin(st, 2, &sp));

@@ -150,6 +150,9 @@ struct NfGeom {
     int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
     int TU, NU;              // the form by units (freqkv_nearfar_units.hip): tiles per unit, units; TU 0: not that form
     int held, held0, held_every;  // ... blocks that its movers hold in registers: how many, the first, their distance
+    int spills;              // the leaves' moments do not fit LDS: they go through spill, spill_bytes per workgroup
+    int spill_bytes;
+    char* spill;
     int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;
     int d;
@@ -162,7 +165,8 @@ bool nf_unit_geometry(int n, int Lc, int head_dim, NfGeom* out);
 hipError_t launch_nf_unit_tables(const NfGeom& g, char* out, hipStream_t st);
 hipError_t launch_nearfar_units(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, unsigned grid, hipStream_t st);
 hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st);
-hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, hipStream_t st);
+// most_wgs: workgroups that g.spill has room for (if g.spills)
+hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, unsigned most_wgs, hipStream_t st);
 
 // ---- tail move: rows [src, src+rows) -> [dst, dst+rows) of every head-tensor; ranges must not overlap
 hipError_t launch_move_rows(const SlabTable& tab, const Geom& g, int elem_bytes, int src_row,

@@ -39,6 +39,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 namespace freqkv {
 
@@ -236,13 +237,18 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
 
 // NK: leaves per exact window; NLO: 16-row steps of it with a second part; TPW: tiles per computing wave and step.
 // SHIFTS: tables of exact entries repeat from tile to tile (NfGeom::shifts) and stay in registers.
-template <int NK, int NLO, int TPW, bool SHIFTS>
+// SPILL, for long spans: 512 bytes of moments per leaf would leave the ring too few slots.  LDS keeps those of the last two blocks, for the
+// blocks' own; all of them go to memory too (64 KB per workgroup, which its L2 keeps) and come back 12 leaves at a time for the tiles'
+// local values, requested at the start of the step that uses them at its end.  Against the matrix form, which such spans took before:
+// 14813 -> 8887 rows of 336 head-tensors 14099 -> 1544 us, 16384 -> 14745 of 32 2189 -> 194, 11787 -> 2946 of 8 229 -> 78.  Only where it
+// must be: 10000 -> 2500 of 128, which fit LDS, 132 without it and 135 with it, 4092 -> 2455 of 256 156 and 171.
+template <int NK, int NLO, int TPW, bool SHIFTS, bool SPILL>
 __global__ __launch_bounds__((kCompute + kMovers) * 64, 2)
 void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* __restrict__ tap)
 {
     __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
     char* const ring = smem;
-    char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8]
+    char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8] (SPILL: of 8 leaves)
     char* const cloc = mom + g.NLm * kVecB;          // [group]...
     char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]..., with TWO_LOC the second parts behind them
     char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come
@@ -412,14 +418,22 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto lds_table = [&](int f) { return *(const bf16x8*)(ltab + f * kFrag + lane * 16); };
     // Moment products have the first parts of the table in result rows 0..7 and the second parts in 8..15: the half-waves add
     // them up, the lower for channels 0..15 (a0), the upper for 16..31 (a1).  [channel][8], 4 per lane.
-    auto put_moments = [&](char* vec, f32x4 a0, f32x4 a1) {
+    auto put_moments = [&](char* vec, f32x4 a0, f32x4 a1) -> u32x2 {
         NF_LANE();
         f32x4 sum;
         static_for<4>([&](auto i) {
             const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0[i.value]), __float_as_uint(a1[i.value]), false, false);
             sum[i.value] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
         });
-        *(u32x2*)(vec + hw * 256 + vec16 + (g4 & 1) * 8) = pack4(sum);
+        const u32x2 packed = pack4(sum);
+        *(u32x2*)(vec + hw * 256 + vec16 + (g4 & 1) * 8) = packed;
+        return packed;
+    };
+    [[maybe_unused]] const auto spill = __builtin_amdgcn_make_buffer_rsrc(SPILL ? g.spill + (long long)blockIdx.x * g.spill_bytes : nullptr, 0,
+                                                                         SPILL ? g.spill_bytes : 0, 0x00020000);
+    auto spill_moments = [&](int leaf, u32x2 packed) {
+        NF_LANE();
+        __builtin_amdgcn_raw_buffer_store_b64(packed, spill, hw * 256 + vec16 + (g4 & 1) * 8, leaf * kVecB, 0);
     };
     // all 16 result rows of a product: two vectors
     auto put16 = [&](char* vec, int h, f32x4 a) {
@@ -434,16 +448,19 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     bf16x8 ft[kNB];
     const int mt = TPW == 2 ? wave : wave & 1;
     auto fetch_local = [&](int gr, auto k) { ft[k.value] = table(g.off_f + ((gr * (GT / 2) + mt) * kNB + k.value) * kFrag); };
-    bf16x8 lf;
+    bf16x8 lf[SPILL ? kNB : 1];
     f32x4 la;
-    const char* const local_in = mom + (lane >> 4) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16;
+    const int local_at = (lane >> 4) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16;
+    const char* const local_in = mom + local_at;
     char* const local_out = loc + 2 * mt * kVecB + (lane >> 5) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16 + (lane >> 4 & 1) * 8;
     auto locals_read = [&](int block0, auto u, auto k) {
-        lf = *(const bf16x8*)(local_in + block0 * 4 * kVecB + (TPW == 2 ? u.value * 256 : 0) + k.value * 4 * kVecB);
+        const int at = block0 * 4 * kVecB + (TPW == 2 ? u.value * 256 : 0) + k.value * 4 * kVecB;
+        if constexpr (SPILL) lf[k.value] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(spill, local_at, at, 0));
+        else                 lf[0] = *(const bf16x8*)(local_in + at);
     };
     auto locals_mac = [&](auto k) {
         if constexpr (decltype(k)::value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
-        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf, la, 0, 0, 0);
+        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf[SPILL ? k.value : 0], la, 0, 0, 0);
     };
     auto locals_put = [&](int gr, auto u) {
         char* const p = local_out + (gr & 1) * (GT * kVecB) + (TPW == 2 ? u.value * 256 : 0);
@@ -461,7 +478,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         const bf16x8 m = lds_table(b == g.NC - 1 ? 5 : 4);
         f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         static_for<2>([&](auto h) {
-            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + (4 * b + g4) * kVecB + h.value * 256 + vec16), a[h.value], 0, 0, 0);
+            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + ((SPILL ? 4 * b & 7 : 4 * b) + g4) * kVecB + h.value * 256 + vec16), a[h.value], 0, 0, 0);
         });
         put_moments(cmom + b * kVecB, a[0], a[1]);
     };
@@ -531,8 +548,12 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                             a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], xa[k.value][h.value], a[h.value], 0, 0, 0);
                         });
                     });
-                    put_moments(mom + leaf * kVecB, a[0], a[1]);
+                    const u32x2 packed = put_moments(mom + (SPILL ? leaf & 7 : leaf) * kVecB, a[0], a[1]);
+                    if constexpr (SPILL) spill_moments(leaf, packed);
                     if (!SHIFTS) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
+                } else if constexpr (SPILL) {                // (a leaf that does not exist: see above)
+                    const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+                    spill_moments(leaf, put_moments(mom + (leaf & 7) * kVecB, none, none));
                 }
                 if (i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
                 s = wrap(s + 4 * dir);
@@ -551,6 +572,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     });
                 });
             };
+            if constexpr (SPILL) settle_memory();            // the moments are in memory, for all waves behind the barrier
             fetch_far(q0, 0);
             lds_barrier();
             if (wave == 0) block_moments(0);
@@ -575,8 +597,9 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             lds_barrier();
             // ... and those of the first group's tiles
             static_for<TPW>([&](auto u) {
+                if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read((int)words[g.NT][0], u, k); });
                 static_for<kNB>([&](auto k) {
-                    locals_read((int)words[g.NT][0], u, k);
+                    if constexpr (!SPILL) locals_read((int)words[g.NT][0], u, k);
                     locals_mac(k);
                     if (u.value == TPW - 1) fetch_local(g.NG > 1, k);
                 });
@@ -679,6 +702,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             };
             static_for<16>([&](auto r) { acc[r.value] = 0.f; });
             static_for<kAhead>([&](auto k) { fetch_rows(k); });
+            if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read(block0, uc, k); });
             static_for<STEPS>([&](auto k) {
                 constexpr int K = decltype(k)::value;
                 if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
@@ -686,8 +710,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
                 // Local values of the next group (behind the last: of no use, but a branch costs more): reads, products and the result,
                 // a few instructions apart.  The tables are requested ahead of the step's stores: their wait then passes over them.
-                constexpr int A = TPW == 2 && U == 0 ? 9 : 2;
-                if constexpr (K >= A && (K - A) % 3 == 0 && (K - A) / 3 < kNB) locals_read(block0, uc, IC<(K - A) / 3>{});
+                constexpr int A = SPILL ? STEPS - 13 : TPW == 2 && U == 0 ? 9 : 2;
+                if constexpr (!SPILL && K >= A && (K - A) % 3 == 0 && (K - A) / 3 < kNB) locals_read(block0, uc, IC<(K - A) / 3>{});
                 if constexpr (K >= A + 2 && (K - A) % 3 == 2 && (K - A) / 3 < kNB) {
                     locals_mac(IC<(K - A) / 3>{});
                     if constexpr (U == TPW - 1) fetch_local(c + 2 < g.NG ? c + 2 : 0, IC<(K - A) / 3>{});
@@ -798,12 +822,18 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
     const int loc_vectors = (g.NK == 2 ? 2 : 4) * g.GT;
     g.NX = g.NCp > loc_vectors ? g.NCp : loc_vectors;
-    const int fixed = (g.NLm + g.NGp + g.NX) * kVecB + kTabFrags * kFrag;
-    g.R = (kLdsBytes - fixed) / kSlotB;
     int need = (int)std::floor((2 * kCompute - 1) * tile_rows / kLeaf) + 1 + g.NK;
     const int turn = (int)std::floor((kCompute * tile_rows + 32.0) / kLeaf) + 2 + 4;   // from a task's last step to the next task's first
     if (need < turn) need = turn;
     if (need < 8) need = 8;
+    auto slots_left = [&] { return (kLdsBytes - (g.NLm + g.NGp + g.NX) * kVecB - kTabFrags * kFrag) / kSlotB; };
+    g.R = slots_left();
+    if (g.R < need && g.NC >= g.NB) {
+        g.spills = 1;
+        g.spill_bytes = 4 * g.NC * kVecB;
+        g.NLm = 8;
+        g.R = slots_left();
+    }
     if (g.R < need) return false;
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
     if (g.NL < g.R && g.R < g.NL + 4) g.R = g.NL;    // no slots over for part of the next task only
@@ -820,25 +850,32 @@ hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, hipStream_t st)
+hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tables, float* tap, unsigned most_wgs, hipStream_t st)
 {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     const unsigned tasks = (unsigned)(g.hts * (g.d / kC)), resident = (unsigned)cus / 8 * 8;
-    const unsigned grid = resident >= 8 && tasks > resident ? resident : tasks;
+    unsigned grid = resident >= 8 && tasks > resident ? resident : tasks;
+    if (g.spills && grid > most_wgs) grid = most_wgs;
+    if (!grid || (g.spills && !g.spill)) return hipErrorInvalidValue;
     if (g.TU) return launch_nearfar_units(tab, g, tables, tap, grid, st);
     const dim3 block((kCompute + kMovers) * 64);
-    if (g.NK == 2) {
-        if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
-        else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
-    } else if (g.NLO == 10) {
-        hipLaunchKernelGGL((k_nearfar<3, 10, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
-    } else {
-        if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true>), dim3(grid), block, 0, st, tab, g, tables, tap);
-        else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false>), dim3(grid), block, 0, st, tab, g, tables, tap);
-    }
+    auto launch = [&](auto spills) {
+        constexpr bool SPILL = decltype(spills)::value;
+        if (g.NK == 2) {
+            if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        } else if (g.NLO == 10) {
+            hipLaunchKernelGGL((k_nearfar<3, 10, 1, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        } else {
+            if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+        }
+    };
+    if (g.spills) launch(std::true_type{});
+    else          launch(std::false_type{});
     return hipGetLastError();
 }
 
