@@ -848,7 +848,11 @@ template <bool FOLD>
 __global__ __launch_bounds__(kWavesF32 * 64)
 void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const float* __restrict__ ws, float* __restrict__ tap)
 {
-    constexpr int P = FOLD ? 2 : 1, U = 8;                            // U steps have their loads in flight together
+    // U steps have their loads in flight together.  Without a fold half the matrix instructions stand behind a load, and one chain: there
+    // twice as many steps, and a second set requested ahead of the products of the first (8 steps in one set | 16 in two: 253 x 507 on
+    // 64 columns of K and of V 20.4 | 12.2 us, 510 x 2043 on 256 columns 72 | 27, 1021 x 2043 on 8192 508 | 493).  With a fold a second
+    // set loses (508 -> 254 12.1 -> 14.8, 2044 -> 1022 on 8192 columns 281 -> 304), and so do 16 steps in one (16.4, 330).
+    constexpr int P = FOLD ? 2 : 1, U = FOLD ? 8 : 16, SETS = FOLD ? 1 : 2;
     __shared__ float red[kWavesF32][P][16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hw = lane >> 5;
     const int ncp = f32_cols_padded(g), rtiles = g.Mpad / 32;
@@ -859,8 +863,7 @@ void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const f
     static_for<P>([&](auto p) { static_for<16>([&](auto r) { acc[p.value][r.value] = 0.f; }); });
     const float* ga = Gt + m0 + l32;
     const float* xb = ws + c0 + l32;
-    for (int s = s0; s < s1; s += U) {
-        float a[U][P], b[U][P];
+    auto fetch = [&](float (&a)[U][P], float (&b)[U][P], int s) __attribute__((always_inline)) {
         static_for<U>([&](auto u) {
             const int k = min(2 * (s + u.value) + hw, g.Kh - 1);      // past the end: the last index again, times zero
             static_for<P>([&](auto p) {
@@ -868,6 +871,8 @@ void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const f
                 b[u.value][p.value] = xb[((size_t)p.value * g.Kh + k) * ncp];
             });
         });
+    };
+    auto multiply = [&](const float (&a)[U][P], const float (&b)[U][P], int s) __attribute__((always_inline)) {
         static_for<U>([&](auto u) {
             const bool in = s + u.value < s1 && 2 * (s + u.value) + hw < g.Kh;
             static_for<P>([&](auto p) {
@@ -875,6 +880,22 @@ void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const f
                                                                     acc[p.value], 0, 0, 0);
             });
         });
+    };
+    if constexpr (SETS == 2) {
+        float a[2][U][P], b[2][U][P];
+        fetch(a[0], b[0], s0);
+        for (int s = s0; s < s1; s += 2 * U) {
+            fetch(a[1], b[1], s + U);
+            multiply(a[0], b[0], s);
+            fetch(a[0], b[0], s + 2 * U);
+            multiply(a[1], b[1], s + U);
+        }
+    } else {
+        for (int s = s0; s < s1; s += U) {
+            float a[U][P], b[U][P];
+            fetch(a, b, s);
+            multiply(a, b, s);
+        }
     }
     static_for<P>([&](auto p) { static_for<16>([&](auto r) { red[wave][p.value][r.value][lane] = acc[p.value][r.value]; }); });
     __syncthreads();
