@@ -29,7 +29,7 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * (5.244e5 + 9.187e5) + 1.0 * (2.62e5 + 5.24e5)) * 1024}
 TRAFFIC_BYTES_SINGLE_FOLD = {"llama3_8b_128k": (2.0 * 2.622e6 + 1.0 * 5.24e5) * 1024}
 # the same for the near/far form's single kernel (profiles/compress_llama3_8b_128k_pmc.txt)
-NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.280e5 + 1.0 * 5.24e5) * 1024}
+NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.638e5 + 1.0 * 5.24e5) * 1024}
 # the same for k_attend_partial (profiles/attend_llama3_8b_128k_pmc.txt)
 ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.248e5 + 1.0 * 1608) * 1024}
 # the same for k_attend_prefill (profiles/prefill_llama3_8b_128k.txt)
@@ -522,7 +522,8 @@ def main():
         # rows; its matrix work is a small fraction of the dense count, so HBM is the roofline it is held against
         bytes_launch = p.bytes_algorithmic / per_trigger
         gbs = bytes_launch / (ms_contract * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "k_nearfar" if runs == 7 else "k_fast", "achieved": gbs, "peak": HBM_PEAK_GBS,
+        roof = {"bound": "hbm", "kernel": "k_fast" if runs != 7 else "k_nearfar_units" if p.span_len in (2 * p.retained_len, 4 * p.retained_len) else "k_nearfar",
+                "achieved": gbs, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                 "traffic": NEARFAR_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload) if runs == 7 else None,
                 "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run of this kernel (profiles/), "

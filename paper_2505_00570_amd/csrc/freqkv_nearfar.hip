@@ -1,4 +1,5 @@
-// Near/far form of the compression operator: any span n and any retained length Lc from n/5 up, bf16 caches.
+// Near/far form of the compression operator: any span n and any retained length Lc from n/5 up, bf16 caches.  Where n is 2 Lc or 4 Lc
+// most spans take the form by units instead (freqkv_nearfar_units.hip), for which figures at 8188 and 4092 rows below no longer hold.
 //
 // The operator of Sec. 3.3 Eq. 2-3 with the transforms of Appendix A (n-point DCT-II, the Lc lowest
 // coefficients, Lc-point inverse, sqrt(Lc/n)) is, entry by entry,
