@@ -243,7 +243,10 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
 // local values, requested at the start of the step that uses them at its end.  Against the matrix form, which such spans took before:
 // 14813 -> 8887 rows of 336 head-tensors 14099 -> 1544 us, 16384 -> 14745 of 32 2189 -> 194, 11787 -> 2946 of 8 229 -> 78.  Only where it
 // must be: 10000 -> 2500 of 128, which fit LDS, 132 without it and 135 with it, 4092 -> 2455 of 256 156 and 171.
-template <int NK, int NLO, int TPW, bool SHIFTS, bool SPILL>
+// ALL_NEAR, for spans of up to 3 blocks: no block is far from any group, so there are no blocks' moments and the groups' local values stay
+// zero.  Two barriers, a load of tables and the blocks' products less between the readings of a task, which takes 3 to 9 us: 255 -> 127 rows of
+// 1728 head-tensors 93.5 -> 72.6 us, 469 -> 117 114 -> 98, 599 -> 299 of 480 57.6 -> 50.0, 1020 -> 918 of 1920 455 -> 438.
+template <int NK, int NLO, int TPW, bool SHIFTS, bool SPILL, bool ALL_NEAR>
 __global__ __launch_bounds__((kCompute + kMovers) * 64, 2)
 void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* __restrict__ tap)
 {
@@ -387,8 +390,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             }
             lds_barrier();
             if (whole) issue_until(p0 + g.R);
-            lds_barrier();
-            lds_barrier();
+            if constexpr (!ALL_NEAR) {
+                lds_barrier();
+                lds_barrier();
+            }
             for (int t = 0; t < g.NT; t += kCompute) {
                 const int first = words[t][0] & 255;
                 const int end = (int)(words[min(t + kCompute, g.NT) - 1][0] & 255) + NK;
@@ -556,13 +561,13 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     const f32x4 none = {0.f, 0.f, 0.f, 0.f};
                     spill_moments(leaf, put_moments(mom + (leaf & 7) * kVecB, none, none));
                 }
-                if (i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
+                if (!ALL_NEAR && i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
                 s = wrap(s + 4 * dir);
             }
         }
         // ---- local values of the groups from the blocks that are far from them: units of two groups and 16 channels, 2 units
         // of a wave and 4 x 4 blocks at a time, their tables requested together
-        {
+        if constexpr (!ALL_NEAR) {
             NF_LANE();
             const int q0 = wave >> 1, h = wave & 1, kst = g.NCp / 4, mts = g.NGp / 2;
             bf16x8 ct[2][4];
@@ -595,18 +600,18 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     if (m0 + 2 * j.value < mts) put16(cloc + 2 * (m0 + 2 * j.value) * kVecB, h, a[j.value]);
                 });
             }
-            lds_barrier();
-            // ... and those of the first group's tiles
-            static_for<TPW>([&](auto u) {
-                if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read((int)words[g.NT][0], u, k); });
-                static_for<kNB>([&](auto k) {
-                    if constexpr (!SPILL) locals_read((int)words[g.NT][0], u, k);
-                    locals_mac(k);
-                    if (u.value == TPW - 1) fetch_local(g.NG > 1, k);
-                });
-                locals_put(0, u);
-            });
         }
+        lds_barrier();
+        // ... and those of the first group's tiles
+        static_for<TPW>([&](auto u) {
+            if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read((int)words[g.NT][0], u, k); });
+            static_for<kNB>([&](auto k) {
+                if constexpr (!SPILL) locals_read((int)words[g.NT][0], u, k);
+                locals_mac(k);
+                if (u.value == TPW - 1) fetch_local(g.NG > 1, k);
+            });
+            locals_put(0, u);
+        });
 
         // ---- results: a step is one tile per wave, a group TPW steps
         int at_leaf = 0, at_slot = wrap(ptr + dir * g.NLr);      // a leaf and its slot (leaf 0: the last one read)
@@ -863,20 +868,21 @@ hipError_t launch_nearfar(const SlabTable& tab, const NfGeom& g, const char* tab
     if (!grid || (g.spills && !g.spill)) return hipErrorInvalidValue;
     if (g.TU) return launch_nearfar_units(tab, g, tables, tap, grid, st);
     const dim3 block((kCompute + kMovers) * 64);
-    auto launch = [&](auto spills) {
-        constexpr bool SPILL = decltype(spills)::value;
+    auto launch = [&](auto spills, auto all_near) {
+        constexpr bool SPILL = decltype(spills)::value, ALL_NEAR = decltype(all_near)::value;
         if (g.NK == 2) {
-            if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
-            else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            if (g.shifts) hipLaunchKernelGGL((k_nearfar<2, 6, 2, true, SPILL, ALL_NEAR>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            else          hipLaunchKernelGGL((k_nearfar<2, 6, 2, false, SPILL, ALL_NEAR>), dim3(grid), block, 0, st, tab, g, tables, tap);
         } else if (g.NLO == 10) {
-            hipLaunchKernelGGL((k_nearfar<3, 10, 1, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            hipLaunchKernelGGL((k_nearfar<3, 10, 1, false, SPILL, ALL_NEAR>), dim3(grid), block, 0, st, tab, g, tables, tap);
         } else {
-            if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
-            else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false, SPILL>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            if (g.shifts) hipLaunchKernelGGL((k_nearfar<3, 12, 1, true, SPILL, ALL_NEAR>), dim3(grid), block, 0, st, tab, g, tables, tap);
+            else          hipLaunchKernelGGL((k_nearfar<3, 12, 1, false, SPILL, ALL_NEAR>), dim3(grid), block, 0, st, tab, g, tables, tap);
         }
     };
-    if (g.spills) launch(std::true_type{});
-    else          launch(std::false_type{});
+    if (g.spills)          launch(std::true_type{}, std::false_type{});
+    else if (g.NC <= kNB)  launch(std::false_type{}, std::true_type{});
+    else                   launch(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 
