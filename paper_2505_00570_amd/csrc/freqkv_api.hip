@@ -1302,31 +1302,35 @@ struct PrefillShape {
 // How the keys of a chunk-wise call are shared out when its workgroups are too few for the 256 compute units: among the two halves of a
 // workgroup (which then has 4 tasks instead of 8), and into parts of the key range that k_prefill_merge brings together.
 // tiles: of the longest workgroup; first: of the shortest (causal: the lengths rise evenly in between).  What is estimated, in
-// microseconds: the longest of one workgroup, all tiles evenly spread, and the whole rounds that equal workgroups make, at 0.9 per tile
-// and stream of keys (0.72 where a workgroup of one stream has its compute unit to itself; with halves two streams of copies run
-// there); 5 for each further start of a workgroup on a compute unit; for parts, 3, 1 per part, and a write and a read of
-// their states (16.6 KB per task) at 7 TB/s.  The halves' own meeting, in LDS, is next to nothing; with up to 4 tasks they would only
-// give work to waves that are idle in a workgroup of one stream, and parts alone measure the same.
-// Measured with 8 KV heads of 4 query heads, as (halves x parts): 1000 queries on 1000 rows 35.0 us (1x1), 27.4 (2x1), 41.5 (2x2); 300 on
-// 300 18.8 (1x1), 15.9 (2x1); 100 on 1000 26.4 (1x3), 23.9 (2x3); 301 on 5001 123 (1x1), 51.4 (1x6), 51.5 (2x3), 66 (1x8 and 2x4: a
+// microseconds: the longest of one workgroup, all tiles evenly spread, and the whole rounds that the workgroups make (a little over one
+// is one where many are short; a later round's parts are 0.6 full), at 0.9 per tile (0.72 where a workgroup has its compute unit to itself, 0.96 for a tile of each half, with two
+// streams of copies); 7 for each further round, whose workgroups start from nothing; for parts, 3, 1 per part, and a
+// write and a read of their states (16.6 KB per task) at 7 TB/s.  The halves' own meeting, in LDS, is next to nothing; with up to 4 tasks
+// they would only give work to waves that are idle in a workgroup of one stream, and parts alone measure the same.  The
+// constants are those that choose best over 36 shapes timed in every cut (0.5 % above the best cut on average).
+// Measured, as (halves x parts), with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 35.0 us (1x1), 26.9 (2x1), 41.5 (2x2); 300
+// on 300 18.8 (1x1), 16.3 (2x1); 100 on 1000 26.4 (1x3), 23.7 (2x3); 301 on 5001 123 (1x1), 51.4 (1x6), 50.3 (2x3), 66 (1x8 and 2x4: a
 // second round); 1 on 8192 134 (1x1), 41.6 (1x10), 40.7 (2x10), 43.4 (1x16); 600 on 2 x 4096 109 (1x1), 128 (2x1); 2000 on 8192 238
-// (1x1), 246 (2x1), 250 (1x2); 200 on 200 in 8 layers 23.1 (1x1), 28.9 (2x1).
+// (1x1), 246 (2x1), 250 (1x2); 363 on 727 in 4 layers 36.8 (1x1), 42.8 (2x1).
 struct PrefillCut { int halves, n_split; };
-PrefillCut prefill_cut(long long units, long long tasks_per_unit, int tiles, int first)
+PrefillCut prefill_cut(long long units, int G, int cur_len, int q_len)
 {
+    const int tiles = (cur_len + 31) / 32, first = (cur_len - q_len) / 32 + 1, tasks_per_unit = G * ((q_len + 31) / 32);
     PrefillCut best = {1, 1};
     double best_us = 1e30;
-    const double avg = 0.5 * (tiles + first), tasks = (double)(units * tasks_per_unit);
+    const double avg = 0.5 * (tiles + first), tasks = (double)units * tasks_per_unit;
     auto consider = [&](int halves, int s) {
-        const double wgs = (double)(units * ((tasks_per_unit * halves + 7) / 8));
-        const double part = std::ceil((double)tiles / s);
-        const double busy = s == 1 ? wgs / 256.0 : wgs * std::ceil(avg / part) / 256.0;
+        const int of_unit = (tasks_per_unit * halves + 7) / 8, part = (tiles + s - 1) / s;
+        int launched = 0;                                     // of a unit
+        for (int t = 0; t < tiles; t += part) launched += of_unit - prefill_first_wg(cur_len, q_len, G, of_unit, 8 / halves, t);
+        const double wgs = (double)units * of_unit, full = of_unit * avg / ((double)launched * part);
+        const double busy = (double)units * launched / 256.0 - 0.2 * (1.0 - full);
         double us = part;
         if (us < wgs * avg / 256.0) us = wgs * avg / 256.0;
-        const double rounds = std::ceil(busy) * (s == 1 ? first : part);
+        const double rounds = std::ceil(busy) * (s == 1 ? first : 0.6 * part);
         if (us < rounds) us = rounds;
-        us *= (halves == 1 && busy <= 1.0 ? 0.72 : 0.9) / halves;
-        if (busy > 1.0) us += 5.0 * (busy - 1.0);
+        us *= halves == 2 ? 0.48 : busy <= 1.0 ? 0.72 : 0.9;
+        if (busy > 1.0) us += 7.0 * (std::ceil(busy) - 1.0);
         if (s > 1) us += 3.0 + s + tasks * s * 16640.0 * 2.0 / 7e6;
         if (us < 0.97 * best_us) { best = {halves, s}; best_us = us; }
     };
@@ -1360,7 +1364,7 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     p.workspace_min = p.off_part;
     const long long tasks = units * p.a.G * (p.q_pad / 32);
     p.part_bytes = (size_t)tasks * (32 * d * sizeof(float) + 32 * sizeof(float2));
-    const PrefillCut cut = prefill_cut(units, (long long)p.a.G * (p.q_pad / 32), p.key_tiles, (cur_len - q_len) / 32 + 1);
+    const PrefillCut cut = prefill_cut(units, p.a.G, cur_len, q_len);
     p.halves = cut.halves;
     p.n_split = cut.n_split;
     p.workspace_bytes = p.workspace_min + (p.n_split > 1 ? p.n_split * p.part_bytes : 0);

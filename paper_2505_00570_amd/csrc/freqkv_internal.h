@@ -236,9 +236,18 @@ struct PrefillGeom {
     int n_split;           // parts that the key tiles of a workgroup are cut into, of split_tiles tiles each
     int split_tiles;
     int halves;            // 2: the waves of a workgroup share out the keys of its part in two halves (4 tasks instead of 8)
+    int wgs;               // workgroups of a unit, over all parts: those that see keys of them
     long long stride_batch, stride_head, stride_token;   // elements
     float qscale;          // log2(e) / sqrt(d)
 };
+// First of a unit's `wgs` workgroups of `tasks` tasks each (in the order of their query blocks) that sees the key tile `tile`; the
+// later ones do too.
+__host__ __device__ inline int prefill_first_wg(int cur_len, int q_len, int G, int wgs, int tasks, int tile)
+{
+    if (32 * tile >= cur_len) return wgs;
+    const int beyond = 32 * tile - (cur_len - q_len);         // of the first query's row
+    return beyond > 0 ? beyond / 32 * G / tasks : 0;
+}
 
 // cs: [rows][d/2] (cos, sin).
 hipError_t launch_prefill_cs(float2* cs, int rows, int d, double rope_base, int rope, hipStream_t st);

@@ -206,22 +206,27 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // group of 8 units the XCD index picks the unit: all workgroups of a unit run on one XCD and share its L2
     // for the unit's K/V tiles (dealt unit by unit, every XCD fetched every unit: 12.7 GB of fabric reads per
     // launch against 2.2 GB of operands).  The units left over after the last full group are dealt plainly.
-    int unit, wg_seq, split;
+    // With the key range in parts, only workgroups that see keys of a part are there, part by part, so that every XCD gets as many
+    // (those that saw none used to be launched too, side by side with the others: with an even number of parts some XCDs got
+    // two rounds and some half of one: 2118 queries on 4237 rows, 2 KV heads of 2, in 4 parts of 2 halves 56.6 -> 37.7 us).
+    int unit, wg_seq, split = 0;
     {
-        const int wgs_per_unit_split = wgs_per_unit * g.n_split;
-        const int per_group = 8 * wgs_per_unit_split;
-        const int grp = blockIdx.x / per_group;
+        const int grp = blockIdx.x / (8 * g.wgs);
+        int local = blockIdx.x - grp * 8 * g.wgs;
         if (grp < g.units / 8) {
-            const int local = blockIdx.x - grp * per_group;
             unit = grp * 8 + (local & 7);
             wg_seq = local >> 3;
         } else {
-            const int local = blockIdx.x - (g.units / 8) * per_group;
-            unit = (g.units / 8) * 8 + local / wgs_per_unit_split;
-            wg_seq = local % wgs_per_unit_split;
+            local = blockIdx.x - (g.units / 8) * 8 * g.wgs;
+            unit = (g.units / 8) * 8 + local / g.wgs;
+            wg_seq = local % g.wgs;
         }
-        split = wg_seq % g.n_split;
-        wg_seq /= g.n_split;
+        while (split + 1 < g.n_split) {
+            const int here = wgs_per_unit - prefill_first_wg(g.cur_len, g.q_len, g.G, wgs_per_unit, TASKS, split * g.split_tiles);
+            if (wg_seq < here) break;
+            wg_seq -= here;
+            ++split;
+        }
     }
     // later query blocks see more keys: hand them out first so that the long workgroups start early
     const int wg_in_unit = wgs_per_unit - 1 - wg_seq;
@@ -247,7 +252,6 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
     // few workgroups: the key tiles of each are cut into n_split parts, whose states k_prefill_merge brings together
     const int part0 = split * g.split_tiles;
     if (g.n_split > 1) {
-        if (part0 >= wg_tiles) return;                             // nobody here sees keys of this part
         wg_tiles = min(wg_tiles, part0 + g.split_tiles);
         my_tiles = min(my_tiles, wg_tiles);
     }
@@ -597,9 +601,12 @@ hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const
     if (g.halves != 1 && g.halves != 2) return hipErrorInvalidValue;
     if (g.n_split < 1 || (g.n_split > 1 && (!part_acc || !part_ml || (long long)g.n_split * g.split_tiles < g.key_tiles))) return hipErrorInvalidValue;
     const int tasks = kPrefillWaves / g.halves, wgs_per_unit = (g.G * g.q_blocks + tasks - 1) / tasks;
-    const dim3 grid((unsigned)((long long)g.units * wgs_per_unit * g.n_split)), block(kPrefillWaves * 64);
-    if (g.halves == 2) hipLaunchKernelGGL(k_attend_prefill<2>, grid, block, 0, st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
-    else               hipLaunchKernelGGL(k_attend_prefill<1>, grid, block, 0, st, g, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    PrefillGeom gw = g;
+    gw.wgs = 0;
+    for (int s = 0; s < g.n_split; ++s) gw.wgs += wgs_per_unit - prefill_first_wg(g.cur_len, g.q_len, g.G, wgs_per_unit, tasks, s * g.split_tiles);
+    const dim3 grid((unsigned)((long long)g.units * gw.wgs)), block(kPrefillWaves * 64);
+    if (g.halves == 2) hipLaunchKernelGGL(k_attend_prefill<2>, grid, block, 0, st, gw, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    else               hipLaunchKernelGGL(k_attend_prefill<1>, grid, block, 0, st, gw, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
     if (g.n_split > 1)
         hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)((long long)g.units * g.G * g.q_blocks)), dim3(256), 0, st, g, part_acc, part_ml,
                            (uint16_t*)out, lse);
