@@ -72,12 +72,16 @@ typedef enum {
  * Forms of the compression on bf16 caches, without the flags above:
  *   near/far   head_dim a multiple of 32, retain_ratio >= 0.2, spans of 128 to 16384 rows, a span of less than
  *              4 GiB: exact entries close to the diagonal, interpolated ones further away.  Before the result is
- *              rounded the largest error is below 5e-3 of the RMS of the channel's span (rms 3e-4), as in the
- *              other forms; the error does not shrink with the result, so that relative to a result that is
- *              much smaller than its span (nearly all of it in the discarded band) it is larger.  freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
+ *              rounded the largest error is below 5e-3 of the RMS of the channel's span; the rms error is 0.4e-4 to
+ *              1.6e-4 of it, as in the other forms or less, but on channels with nearly all their energy in a
+ *              few frequencies at the retained length up to 9.5e-4 (1.8e-4 in the matrix forms; spans long enough to
+ *              use the workspace, see below: 0.8e-4).  The error does not shrink with the result, so that relative
+ *              to a result that is much smaller than its span (nearly all of it in the discarded band) it is larger.
+ *              freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
  *              have otherwise, with that form's sizes and counts; of the workspace that it asks for
- *              workspace_min_bytes have to be there; spans from 10000 to 15000 rows up
- *              (by ratio) keep intermediate values in it, the others leave it unused.
+ *              workspace_min_bytes have to be there; spans from 9000 to 15000 rows up
+ *              (by ratio) keep intermediate values in it, a share for each compute unit that works (with the least
+ *              workspace fewer of them may), the others leave it unused.
  *   variant 6  the factored transform, head_dim not a multiple of 32, retain_ratio 0.5, spans n = 4pq with a compiled
  *              factorization (8188 = 4*23*89, 4092 = 4*11*93, 2044 = 4*7*73, 1020 = 4*3*85, and 1260, 140 for tests)
  *   variants 1, 2, 5  the matrix forms: everything else, and what the flags ask for

@@ -151,7 +151,8 @@ struct NfGeom {
     int TU, NU;              // the form by units (freqkv_nearfar_units.hip): tiles per unit, units; TU 0: not that form
     int held, held0, held_every;  // ... blocks that its movers hold in registers: how many, the first, their distance
     int spills;              // the leaves' moments do not fit LDS: they go through spill, spill_bytes per workgroup
-    int spill_bytes;
+    int spill_bytes;         // (a multiple of 16)
+    int spill_cloc;          // ... of these: where the second parts of the groups' local values begin
     char* spill;
     int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;

@@ -48,6 +48,7 @@ constexpr int kVecB = kC * 8 * 2;         // bytes of 8 moments (or local values
 constexpr int kFrag = 1024;               // one operand fragment: 64 lanes x 8 bf16
 constexpr int kCompute = 4, kMovers = 4;  // waves
 constexpr int kNB = 3;                    // blocks of a group's neighbourhood: 512 rows or less, 128 to spare on both sides
+constexpr int kWin = kNB + 2;             // blocks whose moments are back in LDS where they go through memory: a group's and those ahead
 constexpr int kHeld = 4;                  // blocks that the movers keep in registers
 constexpr int kTabFrags = 6;              // table fragments kept in LDS
 constexpr int kLdsBytes = 160 * 1024;
@@ -128,6 +129,14 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 __device__ __forceinline__ u32x2 pack4(f32x4 a) { return u32x2{pack2(a[0], a[1]), pack2(a[2], a[3])}; }
+// What rounding to `first` left of a.
+__device__ __forceinline__ f32x4 rest(f32x4 a, u32x2 first)
+{
+    static_for<4>([&](auto i) {
+        a[i.value] -= __uint_as_float(i.value & 1 ? first[i.value / 2] & 0xffff0000u : first[i.value / 2] << 16);
+    });
+    return a;
+}
 
 }  // namespace
 

@@ -195,17 +195,18 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
                 if (l16 >= 8) x -= first_part(x);
             }
         } else if (byte < g.off_f) {
-            // local values of two groups from 4 blocks
-            const int f = (int)((byte - g.off_c) / kFrag), kst = g.NCp / 4;
-            const int gr = 2 * (f / kst) + (l16 >> 3), b = 4 * (f % kst) + g4;
+            // local values of two groups from 4 blocks; with spills the second parts behind the first of each pair of groups
+            const int kst = g.NCp / 4, kst2 = g.spills ? 2 * kst : kst, f = (int)((byte - g.off_c) / kFrag), fk = f % kst2;
+            const int gr = 2 * (f / kst2) + (l16 >> 3), b = 4 * (fk % kst) + g4;
             if (gr < g.NG && b < g.NC) {
                 const int b0 = group_block0(g, gr);
                 if (b < b0 || b >= b0 + g.NB)
                     x = far_kernel(group_iv(g, gr).node(l16 & 7), block_iv(g, b).node(i), n, false) * 512.0 / n;
+                if (fk >= kst) x -= first_part(x);
             }
         } else if (byte < g.off_t) {
-            // local values of two tiles from the 4 leaves of a neighbouring block
-            const int f = (int)((byte - g.off_f) / kFrag), mt = f / g.NB;
+            // local values of two tiles from the 4 leaves of a neighbouring block; with spills the second parts behind each fragment
+            const int ff = (int)((byte - g.off_f) / kFrag), f = g.spills ? ff / 2 : ff, mt = f / g.NB;
             const int gr = mt / (g.GT / 2), t = 2 * mt + (l16 >> 3);
             const int leaf = 4 * (group_block0(g, gr) + f % g.NB) + g4;
             const Iv lv = leaf_iv(g, leaf);
@@ -214,17 +215,19 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
                 const bool near = leaf >= at.leaf0 && leaf < at.leaf0 + g.NK;
                 const bool shared = g.shifts && t >= g.tlo && t < g.thi;
                 if (!near || shared) x = far_kernel(tile_iv(g, t).node(l16 & 7), lv.node(i), n, near) * 128.0 / n;
+                if (g.spills && (ff & 1)) x -= first_part(x);
             }
         } else {
             // results of a tile from its 8 local values and the 8 of its group; [any but the last group | the last][tile], then the
-            // same again for the second product: with windows of 2 leaves the second parts of all 16; with 3 the second parts of
-            // the tile's 8 and, for the second parts of the local values themselves, its first parts once more
+            // same again for the second product: with windows of 2 leaves, and with spills, the second parts of all 16; else the second
+            // parts of the tile's 8 and, for the second parts of the local values themselves, its first parts once more
             const int ff = (int)((byte - g.off_t) / kFrag), second = ff >= 2 * g.GT, f = ff - second * 2 * g.GT;
             const int gr = f < g.GT ? 0 : g.NG - 1, t = gr * g.GT + f % g.GT, m = 32 * t + l32;
             if (m < g.Lc) {
-                const Iv iv = hw && !(second && g.NK == 3) ? group_iv(g, gr) : tile_iv(g, t);
+                const bool tile_twice = second && g.NK == 3 && !g.spills;
+                const Iv iv = hw && !tile_twice ? group_iv(g, gr) : tile_iv(g, t);
                 x = g.out_scale * lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
-                if (second && !(hw && g.NK == 3)) x -= first_part(x);
+                if (second && !(hw && tile_twice)) x -= first_part(x);
             }
         }
         v[i] = (__bf16)(float)x;
@@ -239,10 +242,14 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
 // NK: leaves per exact window; NLO: 16-row steps of it with a second part; TPW: tiles per computing wave and step.
 // SHIFTS: tables of exact entries repeat from tile to tile (NfGeom::shifts) and stay in registers.
 // SPILL, for long spans: 512 bytes of moments per leaf would leave the ring too few slots.  LDS keeps those of the last two blocks, for the
-// blocks' own; all of them go to memory too (64 KB per workgroup, which its L2 keeps) and come back 12 leaves at a time for the tiles'
-// local values, requested at the start of the step that uses them at its end.  Against the matrix form, which such spans took before:
-// 14813 -> 8887 rows of 336 head-tensors 14099 -> 1544 us, 16384 -> 14745 of 32 2189 -> 194, 11787 -> 2946 of 8 229 -> 78.  Only where it
-// must be: 10000 -> 2500 of 128, which fit LDS, 132 without it and 135 with it, 4092 -> 2455 of 256 156 and 171.
+// blocks' own; all of them go to memory too, and come back a block at a time into a window of kWin blocks, ahead of the tiles' local
+// values.  Such spans have a matrix form of fp16 entries and fp32 sums beside this one, so everything of the far part has two bf16 parts
+// here, tables, moments and local values: on channels of one frequency close to the retained length, where the far rows add up in
+// phase, the rms error is 0.44e-4 to 0.64e-4 of the span's rms against 0.87e-4 to 1.8e-4 there (with one part 4.9e-4 to 6.5e-4), on white
+// rows 0.44e-4 to 0.68e-4 against 0.87e-4 to 1.8e-4.  The second parts cost 10 to 23 % of the time: half of it the products (three for one),
+// the groups' local values above all, half the moments' way back and the ring slots that they take.  Against the matrix form: 14813 -> 8887
+// rows of 336 head-tensors 14099 -> 1381 us, 16384 -> 14745 of 32 2189 -> 215, 11787 -> 2946 of 8 229 -> 86.  (Without the window, each wave
+// requesting what it needs of a group's 12 leaves: 1429, 224 and 90 us.)
 // ALL_NEAR, for spans of up to 3 blocks: no block is far from any group, so there are no blocks' moments and the groups' local values stay
 // zero.  Two barriers, a load of tables and the blocks' products less between the readings of a task, which takes 3 to 9 us: 255 -> 127 rows of
 // 1728 head-tensors 93.5 -> 72.6 us, 469 -> 117 114 -> 98, 599 -> 299 of 480 57.6 -> 50.0, 1020 -> 918 of 1920 455 -> 438.
@@ -255,10 +262,12 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8] (SPILL: of 8 leaves)
     char* const cloc = mom + g.NLm * kVecB;          // [group]...
     char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]..., with TWO_LOC the second parts behind them
-    char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come
+    char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come (SPILL: two parts each)
     char* const ltab = loc + g.NX * kVecB;           // moments of an inner leaf (SHIFTS) | of an inner block | of the last block
     constexpr int GT = kCompute * TPW;
-    constexpr bool TWO_LOC = NK == 3;                // local values of tiles in two parts
+    char* const win = loc + 4 * GT * kVecB;          // SPILL: moments of kWin blocks [block mod kWin][leaf]..., in the place of cmom as well
+    constexpr bool TWO_LOC = NK == 3 || SPILL;       // local values of tiles in two parts
+    constexpr int MV = SPILL ? 2 : 1;                // vectors of the moments of a leaf or a block: with SPILL first and second parts
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -394,6 +403,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 lds_barrier();
                 lds_barrier();
             }
+            if constexpr (SPILL) lds_barrier();
             for (int t = 0; t < g.NT; t += kCompute) {
                 const int first = words[t][0] & 255;
                 const int end = (int)(words[min(t + kCompute, g.NT) - 1][0] & 255) + NK;
@@ -424,69 +434,91 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     auto lds_table = [&](int f) { return *(const bf16x8*)(ltab + f * kFrag + lane * 16); };
     // Moment products have the first parts of the table in result rows 0..7 and the second parts in 8..15: the half-waves add
     // them up, the lower for channels 0..15 (a0), the upper for 16..31 (a1).  [channel][8], 4 per lane.
-    auto put_moments = [&](char* vec, f32x4 a0, f32x4 a1) -> u32x2 {
+    [[maybe_unused]] const auto spill = __builtin_amdgcn_make_buffer_rsrc(SPILL ? g.spill + (long long)blockIdx.x * g.spill_bytes : nullptr, 0,
+                                                                         SPILL ? g.spill_bytes : 0, 0x00020000);
+    // spill_at: where they go in memory as well (SPILL; negative: nowhere)
+    auto put_moments = [&](char* vec, f32x4 a0, f32x4 a1, [[maybe_unused]] int spill_at) {
         NF_LANE();
         f32x4 sum;
         static_for<4>([&](auto i) {
             const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0[i.value]), __float_as_uint(a1[i.value]), false, false);
             sum[i.value] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
         });
-        const u32x2 packed = pack4(sum);
-        *(u32x2*)(vec + hw * 256 + vec16 + (g4 & 1) * 8) = packed;
-        return packed;
+        const int at = hw * 256 + vec16 + (g4 & 1) * 8;
+        const u32x2 first = pack4(sum);
+        *(u32x2*)(vec + at) = first;
+        if constexpr (SPILL) {
+            const u32x2 second = pack4(rest(sum, first));
+            *(u32x2*)(vec + kVecB + at) = second;
+            if (spill_at >= 0) {
+                __builtin_amdgcn_raw_buffer_store_b64(first, spill, at, spill_at, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(second, spill, at + kVecB, spill_at, 0);
+            }
+        }
     };
-    [[maybe_unused]] const auto spill = __builtin_amdgcn_make_buffer_rsrc(SPILL ? g.spill + (long long)blockIdx.x * g.spill_bytes : nullptr, 0,
-                                                                         SPILL ? g.spill_bytes : 0, 0x00020000);
-    auto spill_moments = [&](int leaf, u32x2 packed) {
+    // all 16 result rows of a product: two vectors (SPILL: their second parts in memory)
+    auto put16 = [&](char* vec, int h, f32x4 a, [[maybe_unused]] int spill_at) {
         NF_LANE();
-        __builtin_amdgcn_raw_buffer_store_b64(packed, spill, hw * 256 + vec16 + (g4 & 1) * 8, leaf * kVecB, 0);
-    };
-    // all 16 result rows of a product: two vectors
-    auto put16 = [&](char* vec, int h, f32x4 a) {
-        NF_LANE();
-        *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a);
+        const int at = (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8;
+        const u32x2 first = pack4(a);
+        *(u32x2*)(vec + at) = first;
+        if constexpr (SPILL) __builtin_amdgcn_raw_buffer_store_b64(pack4(rest(a, first)), spill, at, spill_at, 0);
     };
 
     // Tables that change from step to step are fetched one step ahead of their use, into registers: a load queues behind
     // the copies in flight, a step's worth of time.  What does not change sits in LDS or stays in registers.
     // Local values of the tiles of a group from the leaves around it: a wave takes two tiles and a half of the channels, with TPW == 2
     // one half in each of the group's steps (u) from the same tables.  A table is requested again right after its last use.
-    bf16x8 ft[kNB];
+    // SPILL with TPW == 1: a block's tables at a time, first and second parts of all would not fit the registers.
+    constexpr bool ROLL = SPILL && TPW == 1;
+    bf16x8 ft[ROLL ? 1 : kNB], ft2[SPILL && !ROLL ? kNB : 1];
     const int mt = TPW == 2 ? wave : wave & 1;
-    auto fetch_local = [&](int gr, auto k) { ft[k.value] = table(g.off_f + ((gr * (GT / 2) + mt) * kNB + k.value) * kFrag); };
-    bf16x8 lf[SPILL ? kNB : 1];
-    f32x4 la;
-    const int local_at = (lane >> 4) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16;
-    const char* const local_in = mom + local_at;
-    char* const local_out = loc + 2 * mt * kVecB + (lane >> 5) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16 + (lane >> 4 & 1) * 8;
-    auto locals_read = [&](int block0, auto u, auto k) {
-        const int at = block0 * 4 * kVecB + (TPW == 2 ? u.value * 256 : 0) + k.value * 4 * kVecB;
-        if constexpr (SPILL) lf[k.value] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(spill, local_at, at, 0));
-        else                 lf[0] = *(const bf16x8*)(local_in + at);
+    auto fetch_local = [&](int gr, auto k) {
+        constexpr int I = ROLL ? 0 : k.value;
+        const int off = g.off_f + ((gr * (GT / 2) + mt) * kNB + k.value) * (MV * kFrag);
+        ft[I] = table(off);
+        if constexpr (SPILL) ft2[I] = table(off + kFrag);
     };
-    auto locals_mac = [&](auto k) {
-        if constexpr (decltype(k)::value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
-        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[k.value], lf[SPILL ? k.value : 0], la, 0, 0, 0);
+    bf16x8 lf;
+    f32x4 la;
+    const int local_at = (lane >> 4) * MV * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16;
+    const char* const local_in = (SPILL ? win : mom) + local_at;
+    char* const local_out = loc + 2 * mt * kVecB + (lane >> 5) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16 + (lane >> 4 & 1) * 8;
+    // part: of a block's moments (SPILL: the first parts meet both parts of the table, the second the first)
+    auto locals_read = [&](int block0, auto u, auto k, auto part) {
+        const int block = block0 + k.value, at = SPILL ? block - block / kWin * kWin : block;
+        lf = *(const bf16x8*)(local_in + at * 4 * MV * kVecB + (TPW == 2 ? u.value * 256 : 0) + part.value * kVecB);
+    };
+    auto locals_mac = [&](auto k, auto part) {
+        constexpr int I = ROLL ? 0 : k.value;
+        if constexpr (decltype(k)::value == 0 && part.value == 0) la = f32x4{0.f, 0.f, 0.f, 0.f};
+        la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft[I], lf, la, 0, 0, 0);
+        if constexpr (SPILL && part.value == 0) la = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ft2[I], lf, la, 0, 0, 0);
+    };
+    // SPILL: a block's moments come back from memory, a leaf to each wave, into a place of the window that holds none in use
+    auto window_load = [&](int block) {
+        return __builtin_amdgcn_raw_buffer_load_b128(spill, lane * 16, (min(block, g.NC - 1) * 4 + wave) * (2 * kVecB), 0);
+    };
+    auto window_put = [&](int block, u32x4 x) {
+        block = min(block, g.NC - 1);
+        *(u32x4*)(win + ((block - block / kWin * kWin) * 4 + wave) * (2 * kVecB) + lane * 16) = x;
     };
     auto locals_put = [&](int gr, auto u) {
         char* const p = local_out + (gr & 1) * (GT * kVecB) + (TPW == 2 ? u.value * 256 : 0);
         const u32x2 first = pack4(la);
         *(u32x2*)p = first;
-        if constexpr (TWO_LOC) {
-            static_for<4>([&](auto i) {
-                la[i.value] -= __uint_as_float(i.value & 1 ? first[i.value / 2] & 0xffff0000u : first[i.value / 2] << 16);
-            });
-            *(u32x2*)(p + 2 * GT * kVecB) = pack4(la);
-        }
+        if constexpr (TWO_LOC) *(u32x2*)(p + 2 * GT * kVecB) = pack4(rest(la, first));
     };
     auto block_moments = [&](int b) {
         NF_LANE();
         const bf16x8 m = lds_table(b == g.NC - 1 ? 5 : 4);
         f32x4 a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         static_for<2>([&](auto h) {
-            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(mom + ((SPILL ? 4 * b & 7 : 4 * b) + g4) * kVecB + h.value * 256 + vec16), a[h.value], 0, 0, 0);
+            const char* const in = mom + ((SPILL ? 4 * b & 7 : 4 * b) + g4) * (MV * kVecB) + h.value * 256 + vec16;
+            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)in, a[h.value], 0, 0, 0);
+            if constexpr (SPILL) a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m, *(const bf16x8*)(in + kVecB), a[h.value], 0, 0, 0);
         });
-        put_moments(cmom + b * kVecB, a[0], a[1]);
+        put_moments(cmom + b * (MV * kVecB), a[0], a[1], -1);
     };
     bf16x8 vt[4];                                    // moments of the wave's next leaf
     auto fetch_moments = [&](int leaf) {
@@ -503,7 +535,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         static_for<TPW>([&](auto u) { pin(rt[u.value]); pin(rt2[u.value]); });
     };
     const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
-    static_for<kNB>([&](auto k) { fetch_local(0, k); });
+    if constexpr (!ROLL) static_for<kNB>([&](auto k) { fetch_local(0, k); });
     if (top_leaf >= 0) fetch_moments(top_leaf);
     if (SHIFTS) static_for<4>([&](auto k) { pin(vt[k.value]); });
     fetch_results(g.NG == 1);
@@ -554,12 +586,11 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                             a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], xa[k.value][h.value], a[h.value], 0, 0, 0);
                         });
                     });
-                    const u32x2 packed = put_moments(mom + (SPILL ? leaf & 7 : leaf) * kVecB, a[0], a[1]);
-                    if constexpr (SPILL) spill_moments(leaf, packed);
+                    put_moments(mom + (SPILL ? leaf & 7 : leaf) * (MV * kVecB), a[0], a[1], leaf * (MV * kVecB));
                     if (!SHIFTS) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
                 } else if constexpr (SPILL) {                // (a leaf that does not exist: see above)
                     const f32x4 none = {0.f, 0.f, 0.f, 0.f};
-                    spill_moments(leaf, put_moments(mom + (leaf & 7) * kVecB, none, none));
+                    put_moments(mom + (leaf & 7) * (MV * kVecB), none, none, leaf * (MV * kVecB));
                 }
                 if (!ALL_NEAR && i < g.NC - 1 && wave == (i & 3)) block_moments(i + 1);
                 s = wrap(s + 4 * dir);
@@ -569,7 +600,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         // of a wave and 4 x 4 blocks at a time, their tables requested together
         if constexpr (!ALL_NEAR) {
             NF_LANE();
-            const int q0 = wave >> 1, h = wave & 1, kst = g.NCp / 4, mts = g.NGp / 2;
+            // (SPILL: the tables' first parts meet both parts of the blocks' moments, their second parts, kst fragments on, the first)
+            const int q0 = wave >> 1, h = wave & 1, blocks4 = g.NCp / 4, kst = MV * blocks4, mts = g.NGp / 2;
             bf16x8 ct[2][4];
             auto fetch_far = [&](int m0, int k0) {
                 static_for<2>([&](auto j) {
@@ -588,27 +620,47 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 for (int k0 = 0; k0 < kst; k0 += 4) {
                     static_for<4>([&](auto k) {
                         if (k0 + k.value < kst) {
-                            bf16x8 c = {};                       // (behind the last block lies other data, perhaps not finite)
-                            if (4 * (k0 + k.value) + g4 < g.NC) c = *(const bf16x8*)(cmom + (4 * (k0 + k.value) + g4) * kVecB + h * 256 + vec16);
+                            bf16x8 c = {}, c2 = {};              // (behind the last block lies other data, perhaps not finite)
+                            const bool second = SPILL && k0 + k.value >= blocks4;
+                            const int b = 4 * (second ? k0 + k.value - blocks4 : k0 + k.value) + g4;
+                            if (b < g.NC) {
+                                const char* const in = cmom + b * (MV * kVecB) + h * 256 + vec16;
+                                c = *(const bf16x8*)in;
+                                if constexpr (SPILL) c2 = *(const bf16x8*)(in + kVecB);
+                            }
                             static_for<2>([&](auto j) { a[j.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct[j.value][k.value], c, a[j.value], 0, 0, 0); });
+                            if constexpr (SPILL) {
+                                if (!second)
+                                    static_for<2>([&](auto j) { a[j.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ct[j.value][k.value], c2, a[j.value], 0, 0, 0); });
+                            }
                         }
                     });
                     if (k0 + 4 < kst) fetch_far(m0, k0 + 4);
                     else if (m0 + 4 < mts) fetch_far(m0 + 4, 0);
                 }
                 static_for<2>([&](auto j) {
-                    if (m0 + 2 * j.value < mts) put16(cloc + 2 * (m0 + 2 * j.value) * kVecB, h, a[j.value]);
+                    const int gr = 2 * (m0 + 2 * j.value);
+                    if (gr < g.NGp) put16(cloc + gr * kVecB, h, a[j.value], g.spill_cloc + gr * kVecB);
                 });
             }
+            if constexpr (SPILL) settle_memory();            // the groups' second parts are in memory
         }
         lds_barrier();
+        if constexpr (SPILL) {                               // the first kWin blocks that the groups' neighbourhoods take
+            u32x4 x[kWin];
+            static_for<kWin>([&](auto i) { x[i.value] = window_load((int)words[g.NT][0] + i.value); });
+            static_for<kWin>([&](auto i) { window_put((int)words[g.NT][0] + i.value, x[i.value]); });
+            lds_barrier();
+        }
         // ... and those of the first group's tiles
         static_for<TPW>([&](auto u) {
-            if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read((int)words[g.NT][0], u, k); });
             static_for<kNB>([&](auto k) {
-                if constexpr (!SPILL) locals_read((int)words[g.NT][0], u, k);
-                locals_mac(k);
-                if (u.value == TPW - 1) fetch_local(g.NG > 1, k);
+                if constexpr (ROLL) fetch_local(0, k);
+                static_for<MV>([&](auto part) {
+                    locals_read((int)words[g.NT][0], u, k, part);
+                    locals_mac(k, part);
+                });
+                if constexpr (!ROLL) { if (u.value == TPW - 1) fetch_local(g.NG > 1, k); }
             });
             locals_put(0, u);
         });
@@ -676,6 +728,16 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             const int tl = wave + kCompute * U, t = GT * c + tl;
             // what the step needs to know of its tile: a scalar load, ahead of the barrier (behind it its wait would take in LDS reads)
             const u32x2 word = words[min(t, g.NT - 1)];
+            const int next_slot = (int)(word[1] & 0xffff), block0 = (int)(word[1] >> 16), next_group = c + 1 < g.NG ? c + 1 : 0;
+            // SPILL: requested ahead of the barrier, where the wave waits anyhow: the second parts of the group's values, for the upper
+            // half-wave; the block that the window takes in (TPW == 1: the first of two); ROLL: the first block's tables
+            [[maybe_unused]] bf16x8 glo;
+            [[maybe_unused]] u32x4 incoming;
+            if constexpr (SPILL) {
+                if constexpr (ROLL) fetch_local(next_group, IC<0>{});
+                glo = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(spill, (lane & 31) * 16, g.spill_cloc + c * kVecB, 0));
+                incoming = window_load(block0 + kNB + U);
+            }
             lds_barrier();
             if (t >= g.NT) {                             // no tile for this wave in the last step of the task
                 if constexpr (LATE) static_for<7>([&](auto p) { finish(prev, before, p); });
@@ -683,7 +745,6 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 return;
             }
             const int leaf0 = (int)(word[0] & 255), klo = (int)(word[0] >> 8 & 255);
-            const int next_slot = (int)(word[1] & 0xffff), block0 = (int)(word[1] >> 16);
             at_slot = wrap(at_slot + up * (leaf0 - at_leaf));
             at_leaf = leaf0;
             const int s0 = at_slot * kSlotB, s1 = wrap(at_slot + up) * kSlotB, s2 = NK == 3 ? wrap(at_slot + 2 * up) * kSlotB : 0;
@@ -708,7 +769,6 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             };
             static_for<16>([&](auto r) { acc[r.value] = 0.f; });
             static_for<kAhead>([&](auto k) { fetch_rows(k); });
-            if constexpr (SPILL) static_for<kNB>([&](auto k) { locals_read(block0, uc, k); });
             static_for<STEPS>([&](auto k) {
                 constexpr int K = decltype(k)::value;
                 if constexpr (K + kAhead < STEPS) fetch_rows(IC<K + kAhead>{});
@@ -716,29 +776,58 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 if constexpr (!SHIFTS) e[K] = table(next_slot * PER + K * kFrag);
                 // Local values of the next group (behind the last: of no use, but a branch costs more): reads, products and the result,
                 // a few instructions apart.  The tables are requested ahead of the step's stores: their wait then passes over them.
-                constexpr int A = SPILL ? STEPS - 13 : TPW == 2 && U == 0 ? 9 : 2;
-                if constexpr (!SPILL && K >= A && (K - A) % 3 == 0 && (K - A) / 3 < kNB) locals_read(block0, uc, IC<(K - A) / 3>{});
-                if constexpr (K >= A + 2 && (K - A) % 3 == 2 && (K - A) / 3 < kNB) {
-                    locals_mac(IC<(K - A) / 3>{});
-                    if constexpr (U == TPW - 1) fetch_local(c + 2 < g.NG ? c + 2 : 0, IC<(K - A) / 3>{});
+                if constexpr (SPILL) {
+                    // a third of the step for each block: reads, products, reads, products; then its tables for the step after (ROLL:
+                    // the next block's)
+                    constexpr int THIRD = STEPS / kNB, B = K / THIRD, AT = K % THIRD;
+                    if constexpr (B < kNB) {
+                        if constexpr (AT == THIRD - 6) locals_read(block0, uc, IC<B>{}, IC<0>{});
+                        if constexpr (AT == THIRD - 4) locals_mac(IC<B>{}, IC<0>{});
+                        if constexpr (AT == THIRD - 3) locals_read(block0, uc, IC<B>{}, IC<1>{});
+                        if constexpr (AT == THIRD - 1) {
+                            locals_mac(IC<B>{}, IC<1>{});
+                            if constexpr (ROLL && B + 1 < kNB) fetch_local(next_group, IC<B + 1>{});
+                            if constexpr (!ROLL && U == TPW - 1) fetch_local(c + 2 < g.NG ? c + 2 : 0, IC<B>{});
+                            if constexpr (B == kNB - 1) locals_put(c + 1, uc);
+                        }
+                    }
+                    if constexpr (K == STEPS / 2) {
+                        window_put(block0 + kNB + U, incoming);
+                        if constexpr (TPW == 1) incoming = window_load(block0 + kNB + 1);
+                    }
+                    if constexpr (TPW == 1 && K == STEPS - 1) window_put(block0 + kNB + 1, incoming);
+                } else {
+                    constexpr int A = TPW == 2 && U == 0 ? 9 : 2;
+                    if constexpr (K >= A && (K - A) % 3 == 0 && (K - A) / 3 < kNB) locals_read(block0, uc, IC<(K - A) / 3>{}, IC<0>{});
+                    if constexpr (K >= A + 2 && (K - A) % 3 == 2 && (K - A) / 3 < kNB) {
+                        locals_mac(IC<(K - A) / 3>{}, IC<0>{});
+                        if constexpr (U == TPW - 1) fetch_local(c + 2 < g.NG ? c + 2 : 0, IC<(K - A) / 3>{});
+                    }
+                    if constexpr (K == A + 3 * kNB) locals_put(c + 1, uc);
                 }
-                if constexpr (K == A + 3 * kNB) locals_put(c + 1, uc);
                 if constexpr (LATE) {
                     if constexpr (K >= 2 && K < 6) finish(prev, before, IC<K - 2>{});
                     if constexpr (K == 10) finish(prev, before, IC<4>{});
                     if constexpr (K == 12) finish(prev, before, IC<5>{});
                     if constexpr (K == 14) finish(prev, before, IC<6>{});
                 }
-                // far part: 8 local values of the tile and 8 of its group; for the second product the tile's, first and second parts
+                // far part: 8 local values of the tile and 8 of its group; for the second product the tile's, first and second parts (SPILL:
+                // the same again, and the second parts of all 16 for a third)
                 if constexpr (K == STEPS - 5) {
                     const char* const p = far_tile + (c & 1) * (GT * kVecB) + U * (kCompute * kVecB);
                     far = *(const bf16x8*)(lane < 32 ? p : far_group + c * kVecB);
-                    if constexpr (TWO_LOC) far2 = *(const bf16x8*)(p + (lane < 32 ? 0 : 2 * GT * kVecB));
+                    if constexpr (SPILL) {
+                        far2 = *(const bf16x8*)(p + 2 * GT * kVecB);
+                        if (lane >= 32) far2 = glo;
+                    } else if constexpr (TWO_LOC) {
+                        far2 = *(const bf16x8*)(p + (lane < 32 ? 0 : 2 * GT * kVecB));
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far, rt[U], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TWO_LOC ? far2 : far, rt2[U], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TWO_LOC && !SPILL ? far2 : far, rt2[U], acc, 0, 0, 0);
+            if constexpr (SPILL) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(far2, rt[U], acc, 0, 0, 0);
             if (SHIFTS && next_slot != cur_slot) {           // at the ends of the span only
                 fetch_entries(next_slot);
                 static_for<STEPS>([&](auto k) { pin(e[k.value]); });
@@ -816,15 +905,6 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
         while (g.tlo < g.thi && own(g.tlo)) ++g.tlo;
         while (g.thi > g.tlo && own(g.thi - 1)) --g.thi;
     }
-    const int slots = g.shifts ? g.PT + g.tlo + (g.NT - g.thi) : g.NT;
-    g.v_slots = g.shifts ? 2 : g.NL;
-    g.off_v = slots * (8 * g.NK + g.NLO) * kFrag;
-    g.off_m = g.off_v + g.v_slots * 4 * kFrag;
-    g.off_c = g.off_m + g.NC * kFrag;
-    g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * kFrag;
-    g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * kFrag;
-    g.off_w = g.off_t + 4 * g.GT * kFrag;
-    g.table_bytes = g.off_w + (g.NT + 1) * 8;
     // ring: what LDS leaves, and at least the leaves from the first one a step still uses to the last one the next needs
     const int loc_vectors = (g.NK == 2 ? 2 : 4) * g.GT;
     g.NX = g.NCp > loc_vectors ? g.NCp : loc_vectors;
@@ -834,13 +914,26 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     if (need < 8) need = 8;
     auto slots_left = [&] { return (kLdsBytes - (g.NLm + g.NGp + g.NX) * kVecB - kTabFrags * kFrag) / kSlotB; };
     g.R = slots_left();
-    if (g.R < need && g.NC >= g.NB) {
+    if (g.R < need && g.NC >= g.NB) {                // in two parts throughout, see the kernel
         g.spills = 1;
-        g.spill_bytes = 4 * g.NC * kVecB;
-        g.NLm = 8;
+        g.spill_cloc = 4 * g.NC * 2 * kVecB;
+        g.spill_bytes = g.spill_cloc + g.NGp * kVecB;
+        g.NLm = 8 * 2;
+        g.NCp = (g.NC + 3) / 4 * 4;
+        const int later = 4 * g.GT + kWin * 4 * 2;   // tiles' local values, the window of moments
+        g.NX = 2 * g.NCp > later ? 2 * g.NCp : later;
         g.R = slots_left();
     }
     if (g.R < need) return false;
+    const int slots = g.shifts ? g.PT + g.tlo + (g.NT - g.thi) : g.NT, parts = g.spills ? 2 : 1;
+    g.v_slots = g.shifts ? 2 : g.NL;
+    g.off_v = slots * (8 * g.NK + g.NLO) * kFrag;
+    g.off_m = g.off_v + g.v_slots * 4 * kFrag;
+    g.off_c = g.off_m + g.NC * kFrag;
+    g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * parts * kFrag;
+    g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * parts * kFrag;
+    g.off_w = g.off_t + 4 * g.GT * kFrag;
+    g.table_bytes = g.off_w + (g.NT + 1) * 8;
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
     if (g.NL < g.R && g.R < g.NL + 4) g.R = g.NL;    // no slots over for part of the next task only
     g.NLr = (g.NL - 1) % g.R;

@@ -39,7 +39,7 @@ def test_spill_every_element(span, ratio):
 
 @pytest.mark.parametrize("span,ratio", [(10397, 0.25), (14813, 0.6), (16384, 0.5)])
 def test_spill_many_tasks(span, ratio):
-    """4 heads in 40 slabs, 160 tasks of 32 channels: with the least workspace a plan names, which holds the moments of some 50
+    """4 heads in 40 slabs, 160 tasks of 32 channels: with the least workspace a plan names, which holds the moments of some 30
     workgroups, and with a workgroup for each."""
     wl = _workload(span, ratio, n_heads=4, n_layers=20)
     k, v = _mk(wl, seed=7)
