@@ -74,8 +74,8 @@ typedef enum {
  *              4 GiB: exact entries close to the diagonal, interpolated ones further away.  Before the result is
  *              rounded the largest error is below 5e-3 of the RMS of the channel's span; the rms error is 0.4e-4 to
  *              1.6e-4 of it, as in the other forms or less, but on channels with nearly all their energy in a
- *              few frequencies at the retained length up to 9.5e-4 (1.8e-4 in the matrix forms; spans long enough to
- *              use the workspace, see below: 0.8e-4).  The error does not shrink with the result, so that relative
+ *              few frequencies at the retained length up to 9.5e-4 (2.8e-4 where four times the retained length is the
+ *              span, 0.8e-4 where spans use the workspace, see below; matrix forms 1.8e-4).  The error does not shrink with the result, so that relative
  *              to a result that is much smaller than its span (nearly all of it in the discarded band) it is larger.
  *              freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
  *              have otherwise, with that form's sizes and counts; of the workspace that it asks for

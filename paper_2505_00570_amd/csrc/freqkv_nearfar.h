@@ -129,6 +129,18 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 __device__ __forceinline__ u32x2 pack4(f32x4 a) { return u32x2{pack2(a[0], a[1]), pack2(a[2], a[3])}; }
+// The same with what each rounding leaves passed on to the next: the sum keeps its precision.
+__device__ __forceinline__ u32x2 pack4_carry(f32x4 a)
+{
+    uint32_t q[4];
+    float left = 0.f;
+    static_for<4>([&](auto i) {
+        const float x = a[i.value] + left;
+        q[i.value] = __builtin_bit_cast(uint16_t, (__bf16)x);
+        left = x - __uint_as_float(q[i.value] << 16);
+    });
+    return u32x2{q[0] | q[1] << 16, q[2] | q[3] << 16};
+}
 // What rounding to `first` left of a.
 __device__ __forceinline__ f32x4 rest(f32x4 a, u32x2 first)
 {

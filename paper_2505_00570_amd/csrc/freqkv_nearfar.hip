@@ -868,7 +868,6 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
 {
     if (head_dim % kC || Lc >= n || n < kNfMinSpan || n > 16384 || 5LL * Lc < n) return false;
-    if (nf_unit_geometry(n, Lc, head_dim, out)) return true;
     NfGeom g;
     memset(&g, 0, sizeof(g));
     g.n = n; g.Lc = Lc; g.d = head_dim;
@@ -925,6 +924,10 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
         g.R = slots_left();
     }
     if (g.R < need) return false;
+    // By units, where that form exists; but not where this one has two parts throughout, for the error that the matrix form of such
+    // spans has: by units 11132 -> 2783 rows would be 5.1e-4 off at the retained length (0.45e-4 here, matrix form 0.9e-4), in 69 us for 84
+    // at 12284 -> 3071 of 64 head-tensors (matrix form 687).
+    if (!g.spills && nf_unit_geometry(n, Lc, head_dim, out)) return true;
     const int slots = g.shifts ? g.PT + g.tlo + (g.NT - g.thi) : g.NT, parts = g.spills ? 2 : 1;
     g.v_slots = g.shifts ? 2 : g.NL;
     g.off_v = slots * (8 * g.NK + g.NLO) * kFrag;

@@ -24,8 +24,16 @@
 // inner groups too, because there the images of the neighbourhood are taken with the blocks.  And the compiler must know that none is in
 // flight (settle_memory): a wait that it adds for a load on some other path is one for the copies, or for the stores of the last step.
 //
-// 512 head-tensors x 8188 rows: 476 -> 445 us, 2048 x 4092 1023 -> 905 (bare streams of the same rows and results, with the re-read
-// part: 403 and 730), 512 x 8188 -> 2047 417 -> 388.  What bounds it: the rows that come in for the moments (10 bytes per cycle and compute
+// *Error.*  What stands 64 rows from a result already goes through the far part, where the form with a tile at a time has up to 128
+// rows more of exact entries.  So the moments' roundings take each other over (pack4_carry), and at ratio 1/4 the groups' local values have
+// second parts, for a third product: on channels of one frequency close to the retained length, where the far rows add up in phase, the rms
+// error is then 5.7e-4 of the span's rms at 8188 -> 4094 (a tile at a time 6.0e-4), 5.0e-4 (5.3e-4) at 4092 -> 2046, 1.7e-4 (4.2e-4) at 8188 -> 2047
+// and 1.8e-4 (2.9e-4) at 4092 -> 1023, on white rows 0.90e-4 (1.04e-4), 0.92e-4 (1.04e-4), 0.43e-4 (0.69e-4) and 0.44e-4 (0.70e-4).  The third product
+// and the LDS of the second parts cost 0.5 to 3 % at ratio 1/4, the carries up to 1 %.
+//
+// Against a tile at a time, same device: 512 head-tensors x 8188 rows 473 -> 448 us, 2048 x 4092 946 -> 863 (bare streams of the same rows
+// and results, with the re-read part, take 0.9 and 0.8 of that), 512 x 8188 -> 2047 413 -> 383, 512 x 4092 -> 1023 210 -> 198, but 64 x 4092 ->
+// 1023, one task to each compute unit, 26.8 -> 27.3.  What bounds it: the rows that come in for the moments (10 bytes per cycle and compute
 // unit, what HBM gives), then rows, results and matrix instructions together; in between 3000 to 4400 cycles of every 55000 or 108000 in
 // which the far part is prepared and little moves.
 #include "freqkv_nearfar.h"
@@ -140,11 +148,11 @@ __global__ void k_nf_unit_tables(NfGeom g, char* __restrict__ out)
         } else {
             // results of a tile of a group from its 8 local values and the 8 of its group; then the same again for the second product:
             // with two tiles to a unit the second parts of all 16; with one the second parts of the tile's 8 and, for the second parts of
-            // the local values themselves, its first parts once more
-            const int ff = (int)((byte - g.off_t) / kFrag), second = ff >= g.GT, t = ff - second * g.GT, m = 32 * t + l32;
-            const Iv iv = hw && !(second && TU == 1) ? group_rows(0) : tile_rows<TU>(t);
+            // the local values themselves, its first parts once more, and for a third product the group's first and second parts
+            const int ff = (int)((byte - g.off_t) / kFrag), product = ff / g.GT, t = ff % g.GT, m = 32 * t + l32;
+            const Iv iv = product == 2 || (hw && !(product == 1 && TU == 1)) ? group_rows(0) : tile_rows<TU>(t);
             x = g.out_scale * lagrange(i, ((m + 0.5) * n / g.Lc - iv.c) / iv.h) * ((m & 1) ? -1.0 : 1.0);
-            if (second && !(hw && TU == 1)) x -= first_part(x);
+            if ((product == 1 && !(hw && TU == 1)) || (product == 2 && hw)) x -= first_part(x);
         }
         v[i] = (__bf16)(float)x;
     }
@@ -162,7 +170,8 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
     char* const ring = smem;
     char* const mom = smem + g.R * kSlotB;           // [leaf][channel][8]
     char* const cloc = mom + g.NLm * kVecB;          // [group]...
-    char* const loc = cloc + g.NGp * kVecB;          // [even group | odd | last][tile of the group]..., with TWO_LOC second parts behind each
+    constexpr bool TWO_GROUP = TU == 1;              // local values of groups in two parts: all second parts behind all first
+    char* const loc = cloc + (TWO_GROUP ? 2 : 1) * g.NGp * kVecB;      // [even group | odd | last][tile of the group]..., with TWO_LOC second parts behind each
     char* const cmom = loc;                          // [block | first leaf | last]..., gone before the first local values of tiles come
     char* const ltab = loc + g.NX * kVecB;           // moments | block moments | with LDS_TABS results from local values
     constexpr int GT = GTiles<TU>, LO = kLo<TU>, kWaves = GT, kThreads = (kWaves + kMovers) * 64;
@@ -198,7 +207,7 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
     auto wrap = [&](int s) { return s < 0 ? s + g.R : (s >= g.R ? s - g.R : s); };
 
     // moments of leaves that do not exist stay zero: they meet zero table entries and must be finite
-    for (int i = threadIdx.x; i < (g.NLm + g.NGp + g.NX) * (kVecB / 16); i += kThreads)
+    for (int i = threadIdx.x; i < (g.NLm + (TWO_GROUP ? 2 : 1) * g.NGp + g.NX) * (kVecB / 16); i += kThreads)
         ((u32x4*)mom)[i] = u32x4{0u, 0u, 0u, 0u};
     for (int i = threadIdx.x; i < kTab * 64; i += kThreads) ((u32x4*)ltab)[i] = *(const u32x4*)(tables + g.off_v + i * 16);
     char* const rt_tab = ltab + kTab * kFrag;        // [first product | second][the tile's part, the same for all | the group's part of each tile]
@@ -382,14 +391,17 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(tabs, lane_v * 16, off, 0));
     };
     // Moment products have the first parts of the table in result rows 0..7 and the second parts in 8..15: the half-waves add
-    // them up, the lower for a0, the upper for a1.  [channel][8], 4 per lane.
+    // them up, the lower for a0, the upper for a1.  [channel][8], 4 per lane.  Of the four roundings each takes over what the one before
+    // left: what the moments meet next varies little from one to its neighbour, so that the errors cancel where they used to add up.
+    // (25 frequencies from 60 below to 60 above the retained length, rms error over the span's rms: 8188 -> 4094 5.9e-4 -> 5.6e-4, 4092 ->
+    // 2046 5.2e-4 -> 4.9e-4, a tile at a time 5.9e-4 and 5.2e-4; white rows 1.0e-4 -> 0.9e-4; no difference in time.)
     auto add_parts = [&](f32x4 a0, f32x4 a1) {
         f32x4 sum;
         static_for<4>([&](auto i) {
             const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0[i.value]), __float_as_uint(a1[i.value]), false, false);
             sum[i.value] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
         });
-        return pack4(sum);
+        return pack4_carry(sum);
     };
     auto block_moments = [&](int b) {
         NF_LANE();
@@ -416,15 +428,10 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         char* const p = loc + (2 * mt + hw) * kVecB + half0 * 256 + vec16 + (g4 & 1) * 8 + buf * LOCB;
         const u32x2 first = pack4(a);
         *(u32x2*)p = first;
-        if constexpr (TWO_LOC) {
-            static_for<4>([&](auto i) {
-                a[i.value] -= __uint_as_float(i.value & 1 ? first[i.value / 2] & 0xffff0000u : first[i.value / 2] << 16);
-            });
-            *(u32x2*)(p + GT * kVecB) = pack4(a);
-        }
+        if constexpr (TWO_LOC) *(u32x2*)(p + GT * kVecB) = pack4(rest(a, first));
     };
     const int tile = wave % TU;                      // of the unit
-    bf16x8 ft[kNB], rt, rt2;                         // local values of an inner group; results from local values: first and second product
+    bf16x8 ft[kNB], rt, rt2, rt3;                    // local values of an inner group; results from local values: first, second and third product
     bf16x8 e[16], lo[LO];                            // exact entries, second parts
     static_for<kNB>([&](auto k) { ft[k.value] = local_table(1, k.value); });
     static_for<16>([&](auto k) { e[k.value] = table((tile * 16 + k.value) * kFrag); });
@@ -432,8 +439,10 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
     if constexpr (!LDS_TABS) {
         rt = table(g.off_t + wave * kFrag);
         rt2 = table(g.off_t + (GT + wave) * kFrag);
+        rt3 = table(g.off_t + (2 * GT + wave) * kFrag);
         pin(rt);
         pin(rt2);
+        pin(rt3);
     }
     static_for<kNB>([&](auto k) { pin(ft[k.value]); });
     static_for<16>([&](auto k) { pin(e[k.value]); });
@@ -525,7 +534,10 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                 });
                 if (it + BUFS < items) fetch_far(buf, it + BUFS);
                 if (k0 + KC >= kst) {                        // all 16 result rows: two groups
-                    *(u32x2*)(cloc + (2 * m + (g4 >> 1)) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = pack4(a);
+                    char* const p = cloc + (2 * m + (g4 >> 1)) * kVecB + h * 256 + vec16 + (g4 & 1) * 8;
+                    const u32x2 first = pack4(a);
+                    *(u32x2*)p = first;
+                    if constexpr (TWO_GROUP) *(u32x2*)(p + g.NGp * kVecB) = pack4(rest(a, first));
                     a = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             };
@@ -599,7 +611,7 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                 // Row fragments are read kAhead steps ahead, and the order is pinned: left alone the compiler reads the whole window first
                 // and runs out of registers.
                 constexpr int kAhead = 2;
-                bf16x8 xf[kAhead + 1], lf[kNB], far, far2, ra, rb;
+                bf16x8 xf[kAhead + 1], lf[kNB], far, far2, far3, ra, rb;
                 f32x16 acc;
                 f32x4 la;
                 auto fetch_rows = [&](auto kc) {
@@ -616,13 +628,15 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                     if constexpr (K + kAhead < 16) fetch_rows(IC<K + kAhead>{});
                     mac(xf[K % (kAhead + 1)], e[K]);
                     if constexpr (K >= K0 && K < K0 + LO) mac(xf[K % (kAhead + 1)], lo[K - K0]);
-                    // far part: 8 local values of the tile and 8 of its group; for the second product the tile's, first and second parts
+                    // far part: 8 local values of the tile and 8 of its group; for the second product the tile's, first and second parts; for
+                    // the third the group's, second and first
                     if constexpr (K == 4) {
                         NF_LANE();
                         const char* const p = loc + (c == g.NG - 1 && c ? 2 : c & 1) * LOCB + wave * kVecB + l32 * 16;
                         far = *(const bf16x8*)(hw ? cloc + c * kVecB + l32 * 16 : p);
                         far2 = far;
                         if constexpr (TWO_LOC) far2 = *(const bf16x8*)(p + (hw ? GT * kVecB : 0));
+                        if constexpr (TWO_GROUP) far3 = *(const bf16x8*)(cloc + (hw ? c : c + g.NGp) * kVecB + l32 * 16);
                         ra = rt;
                         rb = rt2;
                         if constexpr (LDS_TABS) {
@@ -634,6 +648,7 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                     if constexpr (K == 7) {
                         mac(far, ra);
                         mac(far2, rb);
+                        if constexpr (TWO_GROUP) mac(far3, rt3);
                     }
                     // local values of the next group (an end group has its own already: of no use there, but a branch costs more)
                     if constexpr (K == 9) {
@@ -664,10 +679,11 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
 // Everything that follows from the span alone.  False: no such form (then that of freqkv_nearfar.hip, perhaps).
 bool nf_unit_geometry(int n, int Lc, int head_dim, NfGeom* out)
 {
-    // From 1000 rows at ratio 1/2 and 1400 at 1/4: there the error is no larger than that of a tile at a time, whose end tiles have
-    // both terms of K in one rounded entry, and the time less (1 x 8 heads of 512 rows 8.4 -> 9.2 us, of 1024 rows 11.0 -> 10.9, of 2044
+    // From 1000 rows at ratio 1/2 and 1500 at 1/4: there the error is no larger than that of a tile at a time, whose end tiles have
+    // both terms of K in one rounded entry (1404 -> 351: 1.46e-4 on frequencies close to the retained length against 1.39e-4, 1532 -> 383
+    // 1.32e-4 against 1.50e-4), and the time less (1 x 8 heads of 512 rows 8.4 -> 9.2 us, of 1024 rows 11.0 -> 10.9, of 2044
     // 16.6 -> 15.2; 32 x 8 heads of 1024 rows 77 -> 65).
-    if (head_dim % kC || n > 16384 || !(n == 2 * Lc ? n >= 1000 : n == 4 * Lc && n >= 1400)) return false;
+    if (head_dim % kC || n > 16384 || !(n == 2 * Lc ? n >= 1000 : n == 4 * Lc && n >= 1500)) return false;
     const int units = (n + kLeaf - 1) / kLeaf, beyond = units * kLeaf - n;
     if (beyond > 16) return false;                   // 48 to 64 rows of the last leaf are in the span: no other image comes closer to a tile than 32 rows
     NfGeom g;
@@ -691,10 +707,10 @@ bool nf_unit_geometry(int n, int Lc, int head_dim, NfGeom* out)
     g.off_c = g.off_m + 3 * kFrag;
     g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * kFrag;
     g.off_t = g.off_f + 3 * (g.GT / 2) * kNB * kFrag;
-    g.off_w = g.table_bytes = g.off_t + 2 * g.GT * kFrag;
+    g.off_w = g.table_bytes = g.off_t + (g.TU == 1 ? 3 : 2) * g.GT * kFrag;
     // ring: what LDS leaves, and at least the five leaves of a step and the four of the next or of the next task's first
     g.NX = g.NCp > 24 ? g.NCp : 24;                  // (three groups' local values take 8 vectors each)
-    const int fixed = (g.NLm + g.NGp + g.NX) * kVecB + kTab * kFrag + (g.TU == 2 ? 2 * 512 * (1 + g.GT) : 0);
+    const int fixed = (g.NLm + (g.TU == 1 ? 2 : 1) * g.NGp + g.NX) * kVecB + kTab * kFrag + (g.TU == 2 ? 2 * 512 * (1 + g.GT) : 0);
     g.R = (kLdsBytes - fixed) / kSlotB;
     if (g.R < 9) return false;
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight

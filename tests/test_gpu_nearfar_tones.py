@@ -44,7 +44,7 @@ def _rms(e):
     return float(np.sqrt((e ** 2).mean()))
 
 
-@pytest.mark.parametrize("span,ratio", [(14850, 0.5), (14813, 0.6), (16384, 0.5), (16384, 0.9), (13800, 0.4), (11787, 0.25), (16384, 0.25),
+@pytest.mark.parametrize("span,ratio", [(14850, 0.5), (14813, 0.6), (16384, 0.5), (16384, 0.9), (13800, 0.4), (11787, 0.25), (16384, 0.25), (11260, 0.25),
                                         (10300, 0.21)])
 def test_long_spans_are_no_worse_than_the_matrix_form(span, ratio):
     """Spans whose moments go through the workspace took a matrix form of fp16 entries and fp32 sums before there was a near/far form for
@@ -54,3 +54,17 @@ def test_long_spans_are_no_worse_than_the_matrix_form(span, ratio):
     _say(f"tones {span} {ratio}: near/far {_rms(near[:t]):.2e} (max {near[:t].max():.2e}), white {_rms(near[t:]):.2e}; "
          f"matrix {_rms(matrix[:t]):.2e} (max {matrix[:t].max():.2e}), white {_rms(matrix[t:]):.2e}")
     assert (near <= matrix).all()
+
+
+# rms over the frequencies and over the white channels that the form with a tile at a time reaches at these spans
+TILE_AT_A_TIME = [(1008, 0.5, 3.00e-4, 0.955e-4), (1020, 0.5, 3.24e-4, 0.910e-4), (2044, 0.5, 4.01e-4, 0.987e-4), (4092, 0.5, 5.32e-4, 1.042e-4),
+                  (6130, 0.5, 5.64e-4, 1.047e-4), (8188, 0.5, 6.00e-4, 1.040e-4), (11260, 0.5, 6.11e-4, 1.036e-4),
+                  (1404, 0.25, 1.39e-4, 0.577e-4), (1532, 0.25, 1.51e-4, 0.591e-4), (2048, 0.25, 2.00e-4, 0.662e-4), (4092, 0.25, 2.89e-4, 0.697e-4),
+                  (6140, 0.25, 3.54e-4, 0.673e-4), (8188, 0.25, 4.24e-4, 0.687e-4)]
+
+
+@pytest.mark.parametrize("span,ratio,tones,white", TILE_AT_A_TIME)
+def test_units_are_no_worse_than_a_tile_at_a_time(span, ratio, tones, white):
+    e, t = _errors(span, ratio), len(OFFSETS)
+    _say(f"tones {span} {ratio}: {_rms(e[:t]):.3e} of {tones:.2e} (max {e[:t].max():.2e}), white {_rms(e[t:]):.3e} of {white:.2e}")
+    assert _rms(e[:t]) <= tones and _rms(e[t:]) <= white
