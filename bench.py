@@ -522,7 +522,7 @@ def main():
         # rows; its matrix work is a small fraction of the dense count, so HBM is the roofline it is held against
         bytes_launch = p.bytes_algorithmic / per_trigger
         gbs = bytes_launch / (ms_contract * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "k_fast" if runs != 7 else "k_nearfar_units" if p.span_len in (2 * p.retained_len, 4 * p.retained_len) else "k_nearfar",
+        roof = {"bound": "hbm", "kernel": fk.compress_kernel(L, wl.n_heads, wl.head_dim, wl.window, wl.n_sink, wl.retain_ratio),
                 "achieved": gbs, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                 "traffic": NEARFAR_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload) if runs == 7 else None,

@@ -124,6 +124,11 @@ def load() -> C.CDLL:
     lib.freqkv_attend_prefill.restype = C.c_int
     lib.freqkv_prepare.argtypes = [C.c_int, C.c_uint32, C.c_int, C.c_int, C.c_double, C.c_void_p]
     lib.freqkv_prepare.restype = C.c_int
+    lib.freqkv_debug_compress_kernel.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double]
+    lib.freqkv_debug_compress_kernel.restype = C.c_char_p
+    lib.freqkv_debug_prefill_cut.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int32),
+                                             C.POINTER(C.c_int32)]
+    lib.freqkv_debug_prefill_cut.restype = C.c_int
     lib.freqkv_status_string.argtypes = [C.c_int]
     lib.freqkv_status_string.restype = C.c_char_p
     lib.freqkv_last_error.argtypes = []
@@ -252,6 +257,20 @@ def power_spectrum(k, v, out, layout: Layout, n_heads: int, head_dim: int, row0:
     rc = load().freqkv_power_spectrum(_dev_ptr(k), _dev_ptr(v), _dev_ptr(out), C.byref(layout), n_heads, head_dim,
                                       row0, n_rows, _stream_ptr(stream))
     return _check(rc) if check else rc
+
+
+def compress_kernel(layout: Layout, n_heads: int, head_dim: int, window: int, n_sink: int, retain_ratio: float):
+    """freqkv_debug_compress_kernel: name of the kernel that the spans go through; None for invalid arguments."""
+    name = load().freqkv_debug_compress_kernel(C.byref(layout), n_heads, head_dim, window, n_sink, float(retain_ratio))
+    return name.decode() if name is not None else None
+
+
+def prefill_cut(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, cur_len: int, q_len: int, workspace_bytes: int):
+    """freqkv_debug_prefill_cut: (halves, parts) of a chunk-wise call with such a workspace."""
+    halves, parts = C.c_int32(), C.c_int32()
+    _check(load().freqkv_debug_prefill_cut(C.byref(layout), n_q_heads, n_kv_heads, head_dim, cur_len, q_len, workspace_bytes,
+                                           C.byref(halves), C.byref(parts)))
+    return halves.value, parts.value
 
 
 def attend_prefill_plan(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, cur_len: int, q_len: int,

@@ -701,6 +701,21 @@ freqkv_status_t freqkv_plan(const freqkv_layout_t* layout, int n_heads, int head
     return cur_len < window ? FREQKV_NOOP : FREQKV_OK;
 }
 
+const char* freqkv_debug_compress_kernel(const freqkv_layout_t* layout, int n_heads, int head_dim, int window, int n_sink,
+                                         double retain_ratio)
+{
+    Shape sh;
+    if (!layout || check_shape(layout, n_heads, head_dim, 0, window, n_sink, retain_ratio, &sh) < 0) return nullptr;
+    if (sh.nearfar) return sh.nf.TU ? "k_nearfar_units" : sh.nf.spills ? "k_nearfar (workspace)" : "k_nearfar";
+    switch (sh.variant) {
+        case kNone: return "none";
+        case kDrop: return "k_move_rows";
+        case kF32: return "k_contract_f32";
+        case kFast: return "k_fast";
+        default: return "k_contract_f16";
+    }
+}
+
 freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink, double retain_ratio,
                                void* stream)
 {
@@ -1371,7 +1386,31 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     *out = p;
     return FREQKV_OK;
 }
+
+// Parts that a workspace holds, and their tiles: one sized for a longer chunk may hold fewer parts than would be best, or none.
+freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_tiles)
+{
+    if (workspace_bytes < p->workspace_min) return FREQKV_E_WORKSPACE;
+    while (p->n_split > 1 && p->workspace_min + p->n_split * p->part_bytes > workspace_bytes) --p->n_split;
+    *split_tiles = (p->key_tiles + p->n_split - 1) / p->n_split;
+    p->n_split = (p->key_tiles + *split_tiles - 1) / *split_tiles;
+    return FREQKV_OK;
+}
 }  // namespace
+
+freqkv_status_t freqkv_debug_prefill_cut(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads, int head_dim,
+                                         int cur_len, int q_len, size_t workspace_bytes, int32_t* halves, int32_t* parts)
+{
+    if (!halves || !parts) return FREQKV_E_INVALID;
+    PrefillShape p;
+    int split_tiles = 0;
+    freqkv_status_t rc = check_prefill(layout, n_q_heads, n_kv_heads, head_dim, cur_len, q_len, &p);
+    if (rc == FREQKV_OK) rc = fit_prefill(&p, workspace_bytes, &split_tiles);
+    if (rc < 0) return rc;
+    *halves = p.halves;
+    *parts = p.n_split;
+    return FREQKV_OK;
+}
 
 freqkv_status_t freqkv_attend_prefill_plan(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads,
                                            int head_dim, int cur_len, int q_len, freqkv_prefill_plan_t* out)
@@ -1415,13 +1454,11 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
             bases[(size_t)2 * l + kv] = bp;
         }
     }
-    if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < p.workspace_min)
-        return FREQKV_E_WORKSPACE;
-    // a workspace sized for a longer chunk may hold fewer parts than would be best, or no room for any
-    int n_split = p.n_split;
-    while (n_split > 1 && p.workspace_min + n_split * p.part_bytes > L.workspace_bytes) --n_split;
-    const int split_tiles = (p.key_tiles + n_split - 1) / n_split;
-    n_split = (p.key_tiles + split_tiles - 1) / split_tiles;
+    if (!L.workspace || ((uintptr_t)L.workspace & 255)) return FREQKV_E_WORKSPACE;
+    int split_tiles = 0;
+    rc = fit_prefill(&p, L.workspace_bytes, &split_tiles);
+    if (rc < 0) return rc;
+    const int n_split = p.n_split;
 
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)L.workspace;

@@ -368,3 +368,36 @@ def test_build_rejects_packed_fp32_in_device_code(tmp_path):
         asm = os.path.join(hb.OBJ_DIR, name.replace(".hip", "-hip-amdgcn-amd-amdhsa-gfx950.s"))
         if os.path.exists(asm):
             assert hb.check_device_asm(asm) == (0, 0), name
+
+
+def test_kernel_names():
+    """freqkv_debug_compress_kernel agrees with the plan's `runs`, and tells the kernels of the near/far form apart."""
+    def kernel(span, ratio, d=128, dtype=fk.BF16, flags=0, cap=None):
+        L = _layout(dtype=dtype, cap=span + 4, d=d)
+        L.flags = flags
+        return fk.compress_kernel(L, 8, d, span + 4, 4, ratio), fk.plan(L, 8, d, 0, span + 4, 4, ratio)[1].runs
+    assert kernel(8188, 0.5) == ("k_nearfar_units", 7)
+    assert kernel(6083, 0.5) == ("k_nearfar", 7)
+    assert kernel(900, 0.5) == ("k_nearfar", 7)
+    assert kernel(16384, 0.5) == ("k_nearfar (workspace)", 7)
+    assert kernel(1260, 0.5, d=40) == ("k_fast", 6)
+    assert kernel(8188, 0.5, flags=fk.FLAG_DENSE)[0] == "k_contract_f16"
+    assert kernel(508, 0.5, dtype=fk.F32) == ("k_contract_f32", 3)
+    assert kernel(508, 0.5, flags=fk.FLAG_DROPPING) == ("k_move_rows", 4)
+    assert kernel(508, 1.0) == ("none", 0)
+    assert fk.compress_kernel(_layout(), 8, 128, 8192, 4, 1.5) is None
+
+
+def test_prefill_cut_follows_the_workspace():
+    """freqkv_debug_prefill_cut: the planned cut in the planned workspace, fewer parts in less, an error without room for the operands."""
+    L = _layout(n_layers=1, cap=8192)
+    _, p = fk.attend_prefill_plan(L, 32, 8, 128, 5001, 301)
+    halves, parts = fk.prefill_cut(L, 32, 8, 128, 5001, 301, p.workspace_bytes)
+    assert parts > 1
+    states = 8 * 4 * 10 * 32 * (128 * 4 + 8)
+    operands = p.workspace_bytes - parts * states
+    for have in range(parts):
+        assert fk.prefill_cut(L, 32, 8, 128, 5001, 301, operands + have * states)[1] <= max(have, 1)
+    with pytest.raises(fk.FreqKVError) as e:
+        fk.prefill_cut(L, 32, 8, 128, 5001, 301, operands - 256)
+    assert e.value.status == -3

@@ -20,15 +20,22 @@ def _workload(span, ratio, **kw):
     return synth.small(synth.WORKLOADS["llama2_7b_layer"], **args)
 
 
+def _spills(wl):
+    L = binding.Layout()
+    L.dtype, L.n_layers, L.batch, L.token_capacity, L.stride_token = fk.BF16, 1, 1, wl.window, wl.head_dim
+    assert fk.compress_kernel(L, 1, wl.head_dim, wl.window, wl.n_sink, wl.retain_ratio) == "k_nearfar (workspace)"
+
+
 @pytest.mark.parametrize("span,ratio", [
-    (14801, 0.5), (14850, 0.6), (16384, 0.9), (13953, 0.75),       # 2 leaves; 116, 117, 128 and 110 of them in all
+    (14849, 0.5), (15231, 0.5), (14850, 0.6), (16384, 0.9), (13953, 0.75),     # 2 leaves; 117, 119, 117, 128 and 110 of them in all
     (16384, 0.5), (15104, 0.5),                                    # ... with tables that repeat
     (13800, 0.4), (16383, 0.33),                                   # 3 leaves, 10 steps with a second part
-    (10300, 0.25), (11787, 0.21), (16384, 0.25),                   # 3 leaves, 12 steps; the last with tables that repeat
+    (8705, 0.2), (10300, 0.25), (11787, 0.21), (16384, 0.25),      # 3 leaves, 12 steps; the last with tables that repeat
 ])
 def test_spill_every_element(span, ratio):
     wl = _workload(span, ratio)
     _say(f"spill {span} {ratio}")
+    _spills(wl)
     k, v = _mk(wl, seed=span, capacity=span + 20, cur_len=span + 9)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, span + 9)
@@ -42,6 +49,7 @@ def test_spill_many_tasks(span, ratio):
     """4 heads in 40 slabs, 160 tasks of 32 channels: with the least workspace a plan names, which holds the moments of some 30
     workgroups, and with a workgroup for each."""
     wl = _workload(span, ratio, n_heads=4, n_layers=20)
+    _spills(wl)
     k, v = _mk(wl, seed=7)
     k1, v1 = k.clone(), v.clone()
     L = binding.layout_for(k)
@@ -62,6 +70,7 @@ def test_spill_tasks_of_one_workgroup():
     """More tasks than compute units: every head alone gives the same bits."""
     heads = 150
     wl = _workload(10300, 0.25, n_heads=heads)
+    _spills(wl)
     k, v = _mk(wl, seed=9)
     k0, v0 = k.clone(), v.clone()
     rc, p, _ = _run(k, v, wl, wl.window, tap=False)
@@ -75,6 +84,7 @@ def test_spill_tasks_of_one_workgroup():
 
 def test_spill_ragged():
     wl = _workload(14813, 0.6, batch=3, n_heads=2, n_layers=2)
+    _spills(wl)
     lens = [wl.window + 5, wl.window - 1, wl.window]
     k, v = _mk(wl, seed=2, capacity=wl.window + 5, cur_len=wl.window + 5)
     k0, v0 = k.clone(), v.clone()
@@ -93,8 +103,10 @@ def test_spill_ragged():
     assert torch.equal(k[:, 1], k0[:, 1]) and torch.equal(v[:, 1], v0[:, 1])
 
 
-def test_spill_nan_stays_in_its_channel():
-    wl = _workload(14801, 0.5, head_dim=64)
+@pytest.mark.parametrize("span,ratio", [(14849, 0.5), (14813, 0.6), (10397, 0.25)])
+def test_spill_nan_stays_in_its_channel(span, ratio):
+    wl = _workload(span, ratio, head_dim=64)
+    _spills(wl)
     k, v = _mk(wl, seed=4)
     clean = k.clone()
     k[0, 0, 0, 4 + 9000, 17] = float("nan")

@@ -29,13 +29,19 @@ def test_rounds(hkv, hq, cur, q_len):
     L = binding.layout_for(k)
     _, plan = fk.attend_prefill_plan(L, hq, hkv, 128, cur, q_len)
     states = hkv * (hq // hkv) * ((q_len + 31) // 32) * 32 * (128 * 4 + 8)          # of a part
-    least = plan.workspace_bytes
-    for _ in range(3):
-        least -= states
-        ws = torch.empty(max(least, 256), dtype=torch.uint8, device="cuda")
-        L.workspace, L.workspace_bytes = ws.data_ptr(), least
+    parts = fk.prefill_cut(L, hq, hkv, 128, cur, q_len, plan.workspace_bytes)[1]
+    assert parts >= 3
+    operands = plan.workspace_bytes - parts * states
+    for have in range(parts - 1, -2, -1):
+        size = operands + max(have, 0) * states - (256 if have < 0 else 0)           # at last: no room for the operands themselves
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        L.workspace, L.workspace_bytes = ws.data_ptr(), size
         again = torch.full_like(q, float("nan"))
-        if fk.attend_prefill(q, k, v, again, None, L, hq, hkv, 128, cur, q_len, wl.rope_base, check=False) != 0:
-            break                                                                    # no room for the operands themselves
+        rc = fk.attend_prefill(q, k, v, again, None, L, hq, hkv, 128, cur, q_len, wl.rope_base, check=False)
         torch.cuda.synchronize()
+        assert rc == (0 if have >= 0 else -3)
+        if have < 0:
+            assert again.isnan().all()
+            continue
+        assert fk.prefill_cut(L, hq, hkv, 128, cur, q_len, size)[1] <= max(have, 1)
         assert (again.float() - out.float()).abs().max().item() <= 2 ** -7 * out.float().abs().max().item()
