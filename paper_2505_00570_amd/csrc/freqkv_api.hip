@@ -1336,17 +1336,25 @@ PrefillCut prefill_cut(long long units, int G, int cur_len, int q_len)
     const double avg = 0.5 * (tiles + first), tasks = (double)units * tasks_per_unit;
     auto consider = [&](int halves, int s) {
         const int of_unit = (tasks_per_unit * halves + 7) / 8, part = (tiles + s - 1) / s;
-        int launched = 0;                                     // of a unit
-        for (int t = 0; t < tiles; t += part) launched += of_unit - prefill_first_wg(cur_len, q_len, G, of_unit, 8 / halves, t);
-        const double wgs = (double)units * of_unit, full = of_unit * avg / ((double)launched * part);
-        const double busy = (double)units * launched / 256.0 - 0.2 * (1.0 - full);
+        const double wgs = (double)units * of_unit;
         double us = part;
         if (us < wgs * avg / 256.0) us = wgs * avg / 256.0;
+        const double of_parts = s > 1 ? 3.0 + s + tasks * s * 16640.0 * 2.0 / 7e6 : 0.0;
+        // No cut that this rules out would be taken: what follows only adds to it.  (Most are: a plan of 4094 queries on 8192 rows takes
+        // 2.1 us through ctypes, 1.6 of them for the call; with all of them worked out and divisions in the loop below 4.0.)
+        if (us * (halves == 2 ? 0.48 : wgs > 308.0 ? 0.9 : 0.72) + of_parts >= 0.97 * best_us) return;
+        int launched = 0;                                     // of a unit: prefill_first_wg, whose divisors here are powers of two
+        for (int t = 0; t < tiles; t += part) {
+            const int beyond = 32 * t - (cur_len - q_len);
+            launched += of_unit - (beyond > 0 ? (beyond >> 5) * G >> (halves == 2 ? 2 : 3) : 0);
+        }
+        const double full = of_unit * avg / ((double)launched * part);
+        const double busy = (double)units * launched / 256.0 - 0.2 * (1.0 - full);
         const double rounds = std::ceil(busy) * (s == 1 ? first : 0.6 * part);
         if (us < rounds) us = rounds;
         us *= halves == 2 ? 0.48 : busy <= 1.0 ? 0.72 : 0.9;
         if (busy > 1.0) us += 7.0 * (std::ceil(busy) - 1.0);
-        if (s > 1) us += 3.0 + s + tasks * s * 16640.0 * 2.0 / 7e6;
+        us += of_parts;
         if (us < 0.97 * best_us) { best = {halves, s}; best_us = us; }
     };
     // (in the order of the streams of keys that a task is cut into: more of them have to gain something)

@@ -401,3 +401,22 @@ def test_prefill_cut_follows_the_workspace():
     with pytest.raises(fk.FreqKVError) as e:
         fk.prefill_cut(L, 32, 8, 128, 5001, 301, operands - 256)
     assert e.value.status == -3
+
+
+def test_prefill_plan_time_hardly_depends_on_the_sizes():
+    """Every chunk-wise call plans its cut: the least of many repeats, long rows against short ones (cuts that cannot win are passed over;
+    with all of them worked out 2.5 times the time)."""
+    import time
+
+    def least(cur_len, q_len):
+        L = _layout(n_layers=1, cap=cur_len)
+        best = 1.0
+        for _ in range(60):
+            t0 = time.perf_counter()
+            for _ in range(100):
+                fk.attend_prefill_plan(L, 32, 8, 128, cur_len, q_len)
+            best = min(best, time.perf_counter() - t0)
+        return best
+    short = least(200, 100)
+    for cur_len, q_len in [(5001, 301), (8192, 4094), (8192, 8192), (16384, 300)]:
+        assert least(cur_len, q_len) <= 1.8 * short
