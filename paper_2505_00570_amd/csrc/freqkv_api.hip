@@ -1308,6 +1308,7 @@ freqkv_status_t freqkv_power_spectrum(const void* k, const void* v, float* out, 
 namespace {
 struct PrefillShape {
     AttShape a;
+    long long units;            // of a pass
     int q_len, q_pad, key_tiles, layers_per_pass;
     size_t off_kr, off_vt, off_part, workspace_bytes, workspace_min;
     size_t part_bytes;          // states of one part of the key range
@@ -1317,24 +1318,27 @@ struct PrefillShape {
 // How the keys of a chunk-wise call are shared out when its workgroups are too few for the 256 compute units: among the two halves of a
 // workgroup (which then has 4 tasks instead of 8), and into parts of the key range that k_prefill_merge brings together.
 // tiles: of the longest workgroup; first: of the shortest (causal: the lengths rise evenly in between).  What is estimated, in
-// microseconds: the longest of one workgroup, all tiles evenly spread, and the whole rounds that the workgroups make (a little over one
-// is one where many are short; a later round's parts are 0.6 full), at 0.9 per tile (0.72 where a workgroup has its compute unit to itself, 0.96 for a tile of each half, with two
-// streams of copies); 7 for each further round, whose workgroups start from nothing; for parts, 3, 1 per part, and a
+// microseconds, is the most of three: a part of the longest workgroup; all tiles, evenly spread; and the whole rounds that the workgroups
+// make, each the shortest workgroup, or 0.6 of a part where there are parts.  Their number is that of the workgroups launched per compute unit, less a
+// fifth of the share of their tiles that they do not have (`full`: a little over one round is one where many are short), rounded up.
+// A tile takes 0.9 (0.72 where a workgroup has its compute unit to itself, 0.96 for a tile of each half, with two
+// streams of copies); 7 more for each further round, whose workgroups start from nothing; for parts, 3, 1 per part, and a
 // write and a read of their states (16.6 KB per task) at 7 TB/s.  The halves' own meeting, in LDS, is next to nothing; with up to 4 tasks
 // they would only give work to waves that are idle in a workgroup of one stream, and parts alone measure the same.  The
-// constants are those that choose best over 36 shapes timed in every cut (0.5 % above the best cut on average).
+// constants are fitted: those that choose best over 36 shapes timed in every cut (0.5 % above the best cut on average, no bound for others).
 // Measured, as (halves x parts), with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 35.0 us (1x1), 26.9 (2x1), 41.5 (2x2); 300
 // on 300 18.8 (1x1), 16.3 (2x1); 100 on 1000 26.4 (1x3), 23.7 (2x3); 301 on 5001 123 (1x1), 51.4 (1x6), 50.3 (2x3), 66 (1x8 and 2x4: a
 // second round); 1 on 8192 134 (1x1), 41.6 (1x10), 40.7 (2x10), 43.4 (1x16); 600 on 2 x 4096 109 (1x1), 128 (2x1); 2000 on 8192 238
 // (1x1), 246 (2x1), 250 (1x2); 363 on 727 in 4 layers 36.8 (1x1), 42.8 (2x1).
 struct PrefillCut { int halves, n_split; };
-PrefillCut prefill_cut(long long units, int G, int cur_len, int q_len)
+PrefillCut prefill_cut(long long units, int G, int cur_len, int q_len, int most_parts)
 {
     const int tiles = (cur_len + 31) / 32, first = (cur_len - q_len) / 32 + 1, tasks_per_unit = G * ((q_len + 31) / 32);
     PrefillCut best = {1, 1};
     double best_us = 1e30;
     const double avg = 0.5 * (tiles + first), tasks = (double)units * tasks_per_unit;
     auto consider = [&](int halves, int s) {
+        if (s > most_parts) return;
         const int of_unit = (tasks_per_unit * halves + 7) / 8, part = (tiles + s - 1) / s;
         const double wgs = (double)units * of_unit;
         double us = part;
@@ -1387,7 +1391,8 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     p.workspace_min = p.off_part;
     const long long tasks = units * p.a.G * (p.q_pad / 32);
     p.part_bytes = (size_t)tasks * (32 * d * sizeof(float) + 32 * sizeof(float2));
-    const PrefillCut cut = prefill_cut(units, p.a.G, cur_len, q_len);
+    p.units = units;
+    const PrefillCut cut = prefill_cut(units, p.a.G, cur_len, q_len, 64);
     p.halves = cut.halves;
     p.n_split = cut.n_split;
     p.workspace_bytes = p.workspace_min + (p.n_split > 1 ? p.n_split * p.part_bytes : 0);
@@ -1395,11 +1400,19 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
     return FREQKV_OK;
 }
 
-// Parts that a workspace holds, and their tiles: one sized for a longer chunk may hold fewer parts than would be best, or none.
+// The cut that a workspace allows, and the tiles of its parts: one sized for a longer chunk may hold fewer parts than would be best, or
+// none.  Then the best of the cuts that it does hold, which may be one in halves where the planned one was in parts alone (201 queries on
+// 4505 rows, 8 KV heads of 8, planned 1 x 4, 57 us: with room for no parts 2 x 1, 71 us, where 1 x 1 takes 114; 272 on 6225, 8 of 4, planned 1 x
+// 6, with room for three 2 x 3, 57 us, where 1 x 3 takes 71).
 freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_tiles)
 {
     if (workspace_bytes < p->workspace_min) return FREQKV_E_WORKSPACE;
-    while (p->n_split > 1 && p->workspace_min + p->n_split * p->part_bytes > workspace_bytes) --p->n_split;
+    const size_t hold = (workspace_bytes - p->workspace_min) / p->part_bytes;
+    if (p->n_split > 1 && hold < (size_t)p->n_split) {
+        const PrefillCut cut = prefill_cut(p->units, p->a.G, p->a.cur_len, p->q_len, hold > 1 ? (int)hold : 1);
+        p->halves = cut.halves;
+        p->n_split = cut.n_split;
+    }
     *split_tiles = (p->key_tiles + p->n_split - 1) / p->n_split;
     p->n_split = (p->key_tiles + *split_tiles - 1) / *split_tiles;
     return FREQKV_OK;

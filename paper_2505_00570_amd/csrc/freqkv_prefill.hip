@@ -180,9 +180,9 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const SlabTable tab, const
 // vector registers).
 // HALVES == 2, for short calls: a workgroup has 4 tasks, and its first and last four waves (two to a SIMD) take the two halves of the
 // keys, each with rings of its own; the halves meet in LDS at the end.  So half as many states go through memory as with as many parts
-// of the key range more, or none, and no merging kernel.  (halves, parts) with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 35.0 us
-// (1, 1) -> 27.4 (2, 1); 100 on 1000 26.4 (1, 3) -> 23.9 (2, 3); 256 on 4000 50.8 -> 49.4.  A step of one tile of each half takes 0.985
-// us against 0.907 for a step of eight tasks (twice the copies).
+// of the key range more, or none, and no merging kernel.  With 8 KV heads of 4 query heads 1000 queries on 1000 rows 35.0 us in one stream,
+// 26.9 in halves; 100 on 1000 26.4 in 3 parts, 23.7 in 3 parts of halves; prefill_cut has more of them.  A step of one tile of each half takes 1.08
+// times that of eight tasks (twice the copies).
 template <int HALVES>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
 void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,

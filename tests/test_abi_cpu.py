@@ -420,3 +420,14 @@ def test_prefill_plan_time_hardly_depends_on_the_sizes():
     short = least(200, 100)
     for cur_len, q_len in [(5001, 301), (8192, 4094), (8192, 8192), (16384, 300)]:
         assert least(cur_len, q_len) <= 1.8 * short
+
+
+def test_prefill_cut_in_a_workspace_too_small_for_the_planned_parts():
+    """A call planned in parts alone falls back to the halves of a workgroup, not to one stream of keys in each."""
+    L = _layout(n_layers=1, cap=8192)
+    for hq, cur_len, q_len, planned, small in [(64, 4505, 201, (1, 4), [(2, 2), (2, 2), (2, 1), (2, 1)]),
+                                               (32, 6225, 272, (1, 6), [(2, 3), (2, 3), (2, 3), (2, 2), (2, 1), (2, 1)])]:
+        _, p = fk.attend_prefill_plan(L, hq, 8, 128, cur_len, q_len)
+        states = hq * ((q_len + 31) // 32) * 32 * (128 * 4 + 8)
+        assert fk.prefill_cut(L, hq, 8, 128, cur_len, q_len, p.workspace_bytes) == planned
+        assert [fk.prefill_cut(L, hq, 8, 128, cur_len, q_len, p.workspace_bytes - (i + 1) * states) for i in range(len(small))] == small
