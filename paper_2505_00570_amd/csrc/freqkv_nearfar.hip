@@ -1,5 +1,5 @@
 // Near/far form of the compression operator: any span n and any retained length Lc from n/5 up, bf16 caches.  Where n is 2 Lc or 4 Lc
-// most spans take the form by units instead (freqkv_nearfar_units.hip), for which figures at 8188 and 4092 rows below no longer hold.
+// most spans take the form by units instead (freqkv_nearfar_units.hip).
 //
 // The operator of Sec. 3.3 Eq. 2-3 with the transforms of Appendix A (n-point DCT-II, the Lc lowest
 // coefficients, Lc-point inverse, sqrt(Lc/n)) is, entry by entry,
@@ -16,22 +16,22 @@
 //     tile     32 result rows (32 n/Lc span rows): a window of NK leaves with exact entries, 8 local values from the
 //              leaves of the neighbouring blocks
 //     group    the GT tiles of one step: 8 local values from all the blocks further away
-// Per channel that is about 1.1 M multiply-adds at 8188 -> 4094 against 33.5 M for the dense operator, all of them on
+// Per channel that is about 1.3 M multiply-adds at 6083 -> 3041 against 18.5 M for the dense operator, all of them on
 // the matrix cores with bf16 operands: the cache values enter as they are (no scale, no conversion, no range guard),
 // the exact entries as the sum of two bf16 parts (16 significant bits; the second part only around the tile, where
 // entries are large).  The far part has two parts where they cost little, and one elsewhere: the moment tables (a product
 // of 8 moments has 16 result rows: the second parts take the other 8), the tables from local values to results (one more
 // product per tile) and, with windows of 3 leaves, the tiles' local values (the same product).  So the rms error stays
 // below that of a matrix of the operator in fp16, at every ratio: before the result is rounded, on white rows,
-// 8188 -> 4094 1.5e-4 of the RMS (fp16 matrix 1.6e-4), 8188 -> 2047 1.4e-4 (1.6e-4), 6083 -> 2737 1.6e-4 (1.8e-4); with
-// one part throughout the far field 1.8e-4, 2.0e-4 and 1.9e-4.  These second parts take 0.5 % of the time of 512 head-tensors
-// x 8188 rows at ratio 1/2, 1.7 % at 1/4 (two steps more of exact entries among them).
+// 6083 -> 2737 1.6e-4 of the RMS (fp16 matrix 1.8e-4; with one part throughout the far field 1.9e-4).  On channels of one frequency close to
+// the retained length, where the far rows add up in phase, what has one part shows: up to 9.2e-4 of the span's rms there (fp16 matrix
+// 1.8e-4), but for the long spans of which SPILL below speaks.
 //
 // One workgroup owns 32 channels (64 bytes of every row) of one head-tensor and streams the span twice through a ring
-// of LDS slots (a leaf each): first for the moments, then for the result rows.  What bounds it is moving the rows:
-// 512 head-tensors x 8188 rows take 0.35 ms for one read and one write of half and 0.45 ms with the second read (a bare
-// stream with the same ring, grid and stores), because 256 workgroups x 0.5 MB are still in the 256 MB memory-side
-// cache when they are read again: that is why a workgroup takes 32 channels and not a whole 256-byte row.  Ownership
+// of LDS slots (a leaf each): first for the moments, then for the result rows, which mostly come from the 256 MB memory-side
+// cache then, because 256 workgroups x 64 bytes of each row are still in it: that is why a workgroup takes 32 channels and not a whole
+// 256-byte row.  What bounds it: where entries repeat from tile to tile (SHIFTS) moving the rows; else the tables, 22 to 36 KB per tile
+// and workgroup against 4 KB of rows for each (6083 -> 3041 of 128 head-tensors 124 us, twice the time of its rows).  Ownership
 // by columns keeps the in-place write free of hazards: rows are written behind the rows still to be read.
 //
 // Four waves move data (global -> LDS copies, counted by vmcnt), four compute; apart, because the copies and the loads of
@@ -308,8 +308,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
 
     if (wave >= kCompute) {
         // ---- movers.  Leaves go out in the order in which they are used: last to first for the moments, then, since the
-        // first R of them are still in the ring, R, R+1, ... for the results (of 64 leaves at 8188 rows 13 stay in the
-        // ring, and 16 in registers, see below; of 32 at 4092 rows 15).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
+        // first R of them are still in the ring, R, R+1, ... for the results (of 48 leaves at 6083 rows 14 stay in the
+        // ring, and 16 in registers, see below).  A leaf may take its slot when the steps that used the slot's previous leaf are over, i.e. behind
         // the barrier after them.  Slots are taken in one direction round the ring on the way down and in the other on
         // the way up, so that leaf l and leaf l + R share one.
         // A mover issues little besides copies: its own instructions, branches above all, are what bounds the first reading when
@@ -319,9 +319,9 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         const int row0 = mv * 32 + (lane >> 2);                                               // its row in the first of its two copies
         const uint32_t part = (lane & 3) * 16;
         // Most of a mover's registers are free, and four movers hold 4 blocks in them: the first whole ones behind the leaves that stay
-        // in the ring are read from it on the way down (each mover its part) and written back on the way up.  8188 rows: 495 ->
-        // 482 us, 6083 rows: 127 -> 121 (5 or 6 blocks need more registers than there are); with less to read again than that and a
-        // half (spans up to some 4600 rows) the instructions cost what the copies did: 31.5 -> 32.3 us at 4092.
+        // in the ring are read from it on the way down (each mover its part) and written back on the way up.  6083 -> 3041 of 128
+        // head-tensors: 127 -> 121 us (5 or 6 blocks need more registers than there are); with less to read again than that and a
+        // half (spans up to some 4600 rows) the instructions cost what the copies did.
         const bool hold = g.NL - g.R >= 6 * kHeld;
         const int hold0 = hold ? (g.R + 3) / 4 * 4 : g.NL, hold1 = hold ? hold0 + 4 * kHeld : g.NL;
         u32x4 held[kHeld][4][2];
