@@ -444,10 +444,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0[i.value]), __float_as_uint(a1[i.value]), false, false);
             sum[i.value] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
         });
-        const int at = hw * 256 + vec16 + (g4 & 1) * 8;
         const u32x2 first = pack4(sum);
-        *(u32x2*)(vec + at) = first;
+        *(u32x2*)(vec + hw * 256 + vec16 + (g4 & 1) * 8) = first;
         if constexpr (SPILL) {
+            const int at = hw * 256 + vec16 + (g4 & 1) * 8;
             const u32x2 second = pack4(rest(sum, first));
             *(u32x2*)(vec + kVecB + at) = second;
             if (spill_at >= 0) {
@@ -459,10 +459,10 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     // all 16 result rows of a product: two vectors (SPILL: their second parts in memory)
     auto put16 = [&](char* vec, int h, f32x4 a, [[maybe_unused]] int spill_at) {
         NF_LANE();
-        const int at = (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8;
         const u32x2 first = pack4(a);
-        *(u32x2*)(vec + at) = first;
-        if constexpr (SPILL) __builtin_amdgcn_raw_buffer_store_b64(pack4(rest(a, first)), spill, at, spill_at, 0);
+        *(u32x2*)(vec + (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8) = first;
+        if constexpr (SPILL)
+            __builtin_amdgcn_raw_buffer_store_b64(pack4(rest(a, first)), spill, (g4 >> 1) * kVecB + h * 256 + vec16 + (g4 & 1) * 8, spill_at, 0);
     };
 
     // Tables that change from step to step are fetched one step ahead of their use, into registers: a load queues behind
@@ -486,8 +486,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     char* const local_out = loc + 2 * mt * kVecB + (lane >> 5) * kVecB + (TPW == 2 ? 0 : wave >> 1) * 256 + (lane & 15) * 16 + (lane >> 4 & 1) * 8;
     // part: of a block's moments (SPILL: the first parts meet both parts of the table, the second the first)
     auto locals_read = [&](int block0, auto u, auto k, auto part) {
-        const int block = block0 + k.value, at = SPILL ? block - block / kWin * kWin : block;
-        lf = *(const bf16x8*)(local_in + at * 4 * MV * kVecB + (TPW == 2 ? u.value * 256 : 0) + part.value * kVecB);
+        const int block = block0 + k.value, at = SPILL ? (block - block / kWin * kWin) * 4 * MV * kVecB : block0 * 4 * kVecB + k.value * 4 * kVecB;
+        lf = *(const bf16x8*)(local_in + at + (TPW == 2 ? u.value * 256 : 0) + part.value * kVecB);
     };
     auto locals_mac = [&](auto k, auto part) {
         constexpr int I = ROLL ? 0 : k.value;
@@ -639,8 +639,8 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                     else if (m0 + 4 < mts) fetch_far(m0 + 4, 0);
                 }
                 static_for<2>([&](auto j) {
-                    const int gr = 2 * (m0 + 2 * j.value);
-                    if (gr < g.NGp) put16(cloc + gr * kVecB, h, a[j.value], g.spill_cloc + gr * kVecB);
+                    const int m = m0 + 2 * j.value;
+                    if (m < mts) put16(cloc + 2 * m * kVecB, h, a[j.value], g.spill_cloc + 2 * m * kVecB);
                 });
             }
             if constexpr (SPILL) settle_memory();            // the groups' second parts are in memory
