@@ -79,8 +79,8 @@ typedef enum {
  *              to a result that is much smaller than its span (nearly all of it in the discarded band) it is larger.
  *              freqkv_plan says so in `runs` and keeps naming, as `variant`, the form that the shape would
  *              have otherwise, with that form's sizes and counts; of the workspace that it asks for
- *              workspace_min_bytes have to be there; spans from 9000 to 15000 rows up
- *              (by ratio) keep intermediate values in it, a share for each compute unit that works (with the least
+ *              workspace_min_bytes have to be there; spans from 8705 (ratio 0.2) to
+ *              15361 rows (0.45) up keep intermediate values in it, a share for each compute unit that works (with the least
  *              workspace fewer of them may), the others leave it unused.
  *   variant 6  the factored transform, head_dim not a multiple of 32, retain_ratio 0.5, spans n = 4pq with a compiled
  *              factorization (8188 = 4*23*89, 4092 = 4*11*93, 2044 = 4*7*73, 1020 = 4*3*85, and 1260, 140 for tests)

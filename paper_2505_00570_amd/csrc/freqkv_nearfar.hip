@@ -31,7 +31,8 @@
 // of LDS slots (a leaf each): first for the moments, then for the result rows, which mostly come from the 256 MB memory-side
 // cache then, because 256 workgroups x 64 bytes of each row are still in it: that is why a workgroup takes 32 channels and not a whole
 // 256-byte row.  What bounds it: where entries repeat from tile to tile (SHIFTS) moving the rows; else the tables, 22 to 36 KB per tile
-// and workgroup against 4 KB of rows for each (6083 -> 3041 of 128 head-tensors 124 us, twice the time of its rows).  Ownership
+// and workgroup against 4 KB of rows for each (6083 -> 3041 of 128 head-tensors 124 us where the rows come from HBM, as they do with several
+// caches in turn: twice the time of a copy; 100 to 104 us in calls on one cache, whose rows stay in the memory-side cache).  Ownership
 // by columns keeps the in-place write free of hazards: rows are written behind the rows still to be read.
 //
 // Four waves move data (global -> LDS copies, counted by vmcnt), four compute; apart, because the copies and the loads of
