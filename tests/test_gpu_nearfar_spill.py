@@ -20,10 +20,14 @@ def _workload(span, ratio, **kw):
     return synth.small(synth.WORKLOADS["llama2_7b_layer"], **args)
 
 
-def _spills(wl):
+def _kernel(wl):
     L = binding.Layout()
     L.dtype, L.n_layers, L.batch, L.token_capacity, L.stride_token = fk.BF16, 1, 1, wl.window, wl.head_dim
-    assert fk.compress_kernel(L, 1, wl.head_dim, wl.window, wl.n_sink, wl.retain_ratio) == "k_nearfar (workspace)"
+    return fk.compress_kernel(L, 1, wl.head_dim, wl.window, wl.n_sink, wl.retain_ratio)
+
+
+def _spills(wl):
+    assert _kernel(wl) == "k_nearfar (workspace)"
 
 
 @pytest.mark.parametrize("span,ratio", [
@@ -33,9 +37,19 @@ def _spills(wl):
     (8705, 0.2), (10300, 0.25), (11787, 0.21), (16384, 0.25),      # 3 leaves, 12 steps; the last with tables that repeat
 ])
 def test_spill_every_element(span, ratio):
+    _every_element(span, ratio, "k_nearfar (workspace)")
+
+
+@pytest.mark.parametrize("span,ratio", [(14801, 0.5), (14848, 0.5), (12800, 0.9), (13312, 0.4), (10237, 0.25), (8704, 0.21)])
+def test_longest_spans_without_the_workspace(span, ratio):
+    """Both kinds of window with the fewest ring slots, the last span before the workspace is used among them."""
+    _every_element(span, ratio, "k_nearfar")
+
+
+def _every_element(span, ratio, kernel):
     wl = _workload(span, ratio)
     _say(f"spill {span} {ratio}")
-    _spills(wl)
+    assert _kernel(wl) == kernel
     k, v = _mk(wl, seed=span, capacity=span + 20, cur_len=span + 9)
     k0, v0 = k.cpu().clone(), v.cpu().clone()
     rc, p, tap = _run(k, v, wl, span + 9)
