@@ -408,18 +408,18 @@ def test_prefill_plan_time_hardly_depends_on_the_sizes():
     with all of them worked out 2.5 times the time)."""
     import time
 
-    def least(cur_len, q_len):
-        L = _layout(n_layers=1, cap=cur_len)
-        best = 1.0
-        for _ in range(60):
+    sizes = [(200, 100), (5001, 301), (8192, 4094), (8192, 8192), (16384, 300)]
+    layouts = [_layout(n_layers=1, cap=cur_len) for cur_len, _ in sizes]
+    best = [1.0] * len(sizes)
+    for repeat in range(600):                           # in turn, so that a slow moment of the machine meets all of them
+        for i, (cur_len, q_len) in enumerate(sizes):
             t0 = time.perf_counter()
             for _ in range(100):
-                fk.attend_prefill_plan(L, 32, 8, 128, cur_len, q_len)
-            best = min(best, time.perf_counter() - t0)
-        return best
-    short = least(200, 100)
-    for cur_len, q_len in [(5001, 301), (8192, 4094), (8192, 8192), (16384, 300)]:
-        assert least(cur_len, q_len) <= 1.8 * short
+                fk.attend_prefill_plan(layouts[i], 32, 8, 128, cur_len, q_len)
+            best[i] = min(best[i], time.perf_counter() - t0)
+        if repeat >= 60 and max(best) <= 1.8 * best[0]:
+            break
+    assert max(best) <= 1.8 * best[0]
 
 
 def test_prefill_cut_in_a_workspace_too_small_for_the_planned_parts():
