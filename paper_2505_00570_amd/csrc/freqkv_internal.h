@@ -149,7 +149,7 @@ struct NfGeom {
     int R, NLr;              // ring slots; (NL - 1) mod R
     int shifts, PT, tlo, thi; // exact entries repeat every PT tiles for tiles tlo .. thi-1
     int TU, NU;              // the form by units (freqkv_nearfar_units.hip): tiles per unit, units; TU 0: not that form
-    int held, held0, held_every;  // ... blocks that its movers hold in registers: how many, the first, their distance
+    int held, held0, held_every;  // ... units of four leaves that its movers hold in registers: how many, the first one's first leaf, their distance in leaves
     int spills;              // the leaves' moments do not fit LDS: they go through spill, spill_bytes per workgroup
     int spill_bytes;         // (a multiple of 16)
     int spill_cloc;          // ... of these: where the second parts of the groups' local values begin

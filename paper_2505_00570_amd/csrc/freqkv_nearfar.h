@@ -88,18 +88,35 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed: one of 32 immediates, found
-// by halves.
-template <int LO = 0, int HI = 32>
+// A uniform x no smaller than lo and no larger than hi, in scalar registers (left alone the compiler takes v_med3 and moves it back).
+__device__ __forceinline__ int between(int x, int lo, int hi)
+{
+    int y = max(__builtin_amdgcn_readfirstlane(x), lo);
+    asm("" : "+s"(y));
+    return min(y, hi);
+}
+
+// Waits until all but the newest `leaves` leaf copies of this wave (2 instructions each) have landed.  The count is an immediate, so this
+// jumps to one of 32 waits: found by halves, the branches took a mover some 300 cycles of each step.
 __device__ __forceinline__ void wait_copies(int leaves)
 {
-    if constexpr (HI - LO == 1) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LO) : "memory");
-    } else {
-        constexpr int MID = (LO + HI) / 2;
-        if (leaves < MID) wait_copies<LO, MID>(leaves);
-        else wait_copies<MID, HI>(leaves);
-    }
+    // (the jump's base is the instruction behind s_getpc, the table 6 instructions of 4 bytes further on, 8 bytes to an entry)
+    leaves = between(leaves, 0, 31);
+    asm volatile("s_getpc_b64 s[90:91]\n\t"
+                 "s_lshl_b32 s92, %0, 3\n\t"
+                 "s_add_u32 s90, s90, s92\n\t"
+                 "s_addc_u32 s91, s91, 0\n\t"
+                 "s_add_u32 s90, s90, 24\n\t"
+                 "s_addc_u32 s91, s91, 0\n\t"
+                 "s_setpc_b64 s[90:91]\n\t"
+                 ".set nf_wait_n, 0\n\t"
+                 ".rept 32\n\t"
+                 "s_waitcnt vmcnt(nf_wait_n)\n\t"
+                 "s_branch .Lnf_waited_%=\n\t"
+                 ".set nf_wait_n, nf_wait_n + 2\n\t"
+                 ".endr\n"
+                 ".Lnf_waited_%=:"
+                 :: "s"(leaves) : "s90", "s91", "s92", "scc", "memory");
 }
 
 // A load that only some passes through a loop issue is awaited where it is issued: otherwise the compiler has to expect it in

@@ -79,7 +79,9 @@ __host__ __device__ inline int near_block0(const NfGeom& g, int c)      // first
 // to be taken with the blocks.
 __host__ __device__ inline bool end_group(const NfGeom& g, int c) { return c == 0 || c == g.NG - 1; }
 
-template <int TU> constexpr int kUnitHeld = TU == 2 ? 3 : 4;    // blocks that the movers hold at most (1 more of them: the same time or 1 % more)
+// Units of 4 leaves that the movers hold at most, each 32 KB of 1.1 MB that a task moves at 8188 rows: 3, 4 at ratio 1/2 448, 442 us, 4, 5, 6, 7 at
+// 1/4 384, 386, 379, 387.
+template <int TU> constexpr int kUnitHeld = TU == 2 ? 4 : 6;
 template <int TU> constexpr int GTiles = kCompute * TU;       // tiles of a group, and computing waves: each takes one
 
 // One thread per 16 bytes (lane) of a fragment.
@@ -226,20 +228,24 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         // first R of them are still in the ring, R, R+1, ... for the results.  A leaf may take its slot when the steps that used the
         // slot's previous leaf are over, i.e. behind the barrier after them.  Slots are taken in one direction round the ring on the
         // way down and in the other on the way up, so that leaf l and leaf l + R share one.
-        // A mover issues little besides copies: its own instructions, branches above all, are what bounds the first reading when
-        // rows come from the memory-side cache.  So leaves go out in runs (down, up), from a scalar base.
-        __builtin_amdgcn_s_setprio(3);                       // (the youngest wave of its SIMD, but what it issues all wait for: 1710 -> 1697 us at 4092 rows)
+        // A mover issues little besides copies: its own instructions, branches above all, hold up copies and steps, 600 of the 2600 cycles of a
+        // step of the results.  So leaves go out in runs (down, up), from a scalar base, held ones four at a time, and the waits are found
+        // by a jump (4092 -> 2046 of 16384 head-tensors 6890 -> 6790 us, of 64 29.6 -> 28.9; 8188 -> 2047 of 512 387 -> 382; with four units held, see
+        // kUnitHeld, instead of three 28.5, and 8188 -> 4094 of 512 449 -> 443).  With a raised priority they lose what they gain: then their bursts
+        // go ahead of what the computing waves read from LDS first (6790 -> 7010).
         const int mv = wave - kWaves;
         const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + mv * 32 * kRowB;
         const int row0 = mv * 32 + (lane >> 2);                                               // its row of a leaf in the first of its two copies
         const uint32_t part = (lane & 3) * 16, from0 = (uint32_t)row0 * rowb + part, from1 = from0 + 16 * rowb;
         char* const mine = ring + mv * 32 * kRowB + lane * 16;                                // where it lands, in slot 0
         const int zero0 = 2 * (g.n - (g.NL - 1) * kLeaf + kLead);                             // rows of the last leaf from here on hold nothing
-        // Most of a mover's registers are free, and four movers hold blocks in them: read from the ring on the way down (each mover its
-        // part) and written back on the way up.  The held blocks lie g.held_every apart, so that what comes from memory in between
-        // is asked for all the way up.
+        // Most of a mover's registers are free, and four movers hold units of four leaves in them: read from the ring on the way down (each
+        // mover its part) and written back on the way up.  The way up begins with leaf R and goes a unit at a time, so a unit held is one of
+        // those: where R is no multiple of 4 it lies in two blocks, and its leaf l is in place l & 3.  The held units lie g.held_every
+        // apart, so that what comes from memory in between is asked for all the way up.
         u32x4 held[HELD][4][2];
-        int held_at[HELD];
+        const int unit0 = g.R & 3;                           // place of a unit's first leaf
+        int held_at[HELD];                                   // first leaves
         static_for<HELD>([&](auto i) { held_at[i.value] = i.value < g.held ? g.held0 + i.value * g.held_every : 1 << 20; });
         int copies = 0;                                      // leaves that came from memory
         int issued = 0, slot = 0, dir = 1, vb = blockIdx.x, ht, c0;
@@ -247,55 +253,73 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         int leaf = g.NL - 1, left = g.NL;                                                     // next leaf, leaves left in the run
         int again = -1;                                      // slot of the last leaf, copied a second time and not yet cut
         const char* src = task_base(vb, &ht, &c0);
-        auto copy_leaf = [&]() {
-            const uint32_t to = ring_lds + slot * kSlotB;
-            if (leaf == 0 || leaf == g.NL - 1) {
-                static_for<2>([&](auto i) {                  // 16 rows each; beyond the ends of the span: their images
-                    int row = leaf * kLeaf - kLead + row0 + 16 * i.value;
-                    row = max(row, ~row);
-                    row = min(row, 2 * g.n - 1 - row);
-                    lds_dma16(to + i.value * 16 * kRowB, src, (uint32_t)row * rowb + part);
-                });
-            } else {
-                const char* const at = src + (uint32_t)(leaf * kLeaf - kLead) * rowb;
-                lds_dma16(to, at, from0);
-                lds_dma16(to + 16 * kRowB, at, from1);
+        const char* from = nullptr;                          // of the next leaf, if it is an inner one
+        const long long leaf_bytes = (long long)kLeaf * rowb;
+        auto set_from = [&]() { from = src + ((long long)leaf * kLeaf - kLead) * rowb; };
+        set_from();
+        // the next `count` leaves, none of them the first or the last, downwards (step -1) or upwards
+        auto copy_inner = [&](int count, auto step) {
+            for (; count > 0; --count) {
+                const uint32_t to = ring_lds + slot * kSlotB;
+                lds_dma16(to, from, from0);
+                lds_dma16(to + 16 * kRowB, from, from1);
+                from += step.value * leaf_bytes;
+                slot = wrap(slot + dir);
             }
+        };
+        auto copy_end = [&](int l) {                         // the first leaf or the last: beyond the ends of the span their images
+            static_for<2>([&](auto i) {                      // 16 rows each
+                int row = l * kLeaf - kLead + row0 + 16 * i.value;
+                row = max(row, ~row);
+                row = min(row, 2 * g.n - 1 - row);
+                lds_dma16(ring_lds + slot * kSlotB + i.value * 16 * kRowB, src, (uint32_t)row * rowb + part);
+            });
+            from += down ? -leaf_bytes : leaf_bytes;
+            slot = wrap(slot + dir);
         };
         auto issue_until = [&](int limit) {
             while (issued < limit && vb < tasks) {
-                const int count = min(limit - issued, left);
-                if (down) {
-                    for (int k = 0; k < count; ++k) {
-                        copy_leaf();
-                        slot = wrap(slot + dir);
-                        --leaf;
-                    }
-                    copies += count;
-                } else {
-                    for (int k = 0; k < count; ++k) {
-                        bool from_memory = true;
-                        static_for<HELD>([&](auto b) {
-                            if ((leaf >> 2) == held_at[b.value]) {
-                                from_memory = false;
-                                char* const p = mine + slot * kSlotB;
-                                dispatch<4>(leaf & 3, [&](auto l) {
-                                    static_for<2>([&](auto i) { *(u32x4*)(p + i.value * 16 * kRowB) = held[b.value][l.value][i.value]; });
-                                });
-                                asm volatile("; %0" :: "n"(b.value));
-                            }
-                        });
-                        if (from_memory) {
-                            copy_leaf();
-                            if (leaf == g.NL - 1) again = slot;
-                            ++copies;
-                        }
-                        slot = wrap(slot + dir);
-                        ++leaf;
-                    }
-                }
+                int count = min(limit - issued, left);
                 issued += count;
                 left -= count;
+                if (down) {
+                    copies += count;
+                    if (leaf == g.NL - 1) {
+                        copy_end(leaf);
+                        --leaf;
+                        --count;
+                    }
+                    const int inner = min(count, leaf);
+                    copy_inner(inner, IC<-1>{});
+                    leaf -= inner;
+                    if (count > inner) copy_end(0);
+                } else {
+                    for (int m; count > 0; count -= m) {
+                        m = min(count, 4 - ((leaf - g.R) & 3));
+                        int which = HELD;
+                        static_for<HELD>([&](auto b) { which = leaf == held_at[b.value] && m == 4 ? b.value : which; });
+                        if (which == HELD) {
+                            copies += m;
+                            const bool last = leaf + m == g.NL;
+                            copy_inner(last ? m - 1 : m, IC<1>{});
+                            if (last) {
+                                again = slot;
+                                copy_end(g.NL - 1);
+                            }
+                        } else {
+                            char* p[4];                      // of the leaf in place l
+                            static_for<4>([&](auto l) { p[l.value] = mine + wrap(slot + dir * ((l.value - unit0) & 3)) * kSlotB; });
+                            dispatch<HELD>(which, [&](auto b) {
+                                static_for<4>([&](auto l) {
+                                    static_for<2>([&](auto i) { *(u32x4*)(p[l.value] + i.value * 16 * kRowB) = held[b.value][l.value][i.value]; });
+                                });
+                            });
+                            slot = wrap(slot + 4 * dir);
+                            from += 4 * leaf_bytes;
+                        }
+                        leaf += m;
+                    }
+                }
                 if (left) break;
                 if (down && g.NL > g.R) {                    // turn round: leaf R goes where leaf 0 is
                     slot = wrap(slot - dir);
@@ -312,8 +336,9 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                     leaf = g.NL - 1;
                     left = g.NL;
                     vb += gridDim.x;
+                    if (vb < tasks) src = task_base(vb, &ht, &c0);
                 }
-                if (down && vb < tasks) src = task_base(vb, &ht, &c0);
+                set_from();
             }
         };
         // the last leaf's rows behind the images (there: this wave's copies of it have landed)
@@ -328,7 +353,7 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         int p0 = 0, d0 = 0, at0 = 0, at_dir = 1;
         auto copied = [&](int end) {
             int c = d0 + g.NL + max(0, end - g.R);
-            static_for<HELD>([&](auto i) { c -= min(max(end - 4 * held_at[i.value], 0), 4); });
+            static_for<HELD>([&](auto i) { c -= between(end - held_at[i.value], 0, 4); });
             return c;
         };
         for (int v = blockIdx.x; v < tasks; v += gridDim.x) {
@@ -337,11 +362,15 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
                 wait_copies(copies - (d0 + g.NL - 4 * i));
                 if (i == g.NC - 1) cut(at0);
                 lds_barrier();
+                // held units: this block's places from unit0 on belong to the unit that begins in it, the others to the one before
                 static_for<HELD>([&](auto b) {
-                    if (i == held_at[b.value]) {
+                    const int begins = 4 * i + unit0 - held_at[b.value];
+                    if (begins == 0 || (begins == 4 && unit0)) {
                         static_for<4>([&](auto l) {
-                            const char* const p = mine + wrap(at + at_dir * (3 - l.value)) * kSlotB;
-                            static_for<2>([&](auto k) { held[b.value][l.value][k.value] = *(const u32x4*)(p + k.value * 16 * kRowB); });
+                            if ((l.value >= unit0) == (begins == 0)) {
+                                const char* const p = mine + wrap(at + at_dir * (3 - l.value)) * kSlotB;
+                                static_for<2>([&](auto k) { held[b.value][l.value][k.value] = *(const u32x4*)(p + k.value * 16 * kRowB); });
+                            }
                         });
                         asm volatile("; %0" :: "n"(b.value));
                     }
@@ -430,12 +459,12 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
         *(u32x2*)p = first;
         if constexpr (TWO_LOC) *(u32x2*)(p + GT * kVecB) = pack4(rest(a, first));
     };
-    const int tile = wave % TU;                      // of the unit
+    const int own_wave = wave, own_tile = wave % TU;
     bf16x8 ft[kNB], rt, rt2, rt3;                    // local values of an inner group; results from local values: first, second and third product
     bf16x8 e[16], lo[LO];                            // exact entries, second parts
     static_for<kNB>([&](auto k) { ft[k.value] = local_table(1, k.value); });
-    static_for<16>([&](auto k) { e[k.value] = table((tile * 16 + k.value) * kFrag); });
-    static_for<LO>([&](auto k) { lo[k.value] = table((16 * TU + tile * LO + k.value) * kFrag); });
+    static_for<16>([&](auto k) { e[k.value] = table((own_tile * 16 + k.value) * kFrag); });
+    static_for<LO>([&](auto k) { lo[k.value] = table((16 * TU + own_tile * LO + k.value) * kFrag); });
     if constexpr (!LDS_TABS) {
         rt = table(g.off_t + wave * kFrag);
         rt2 = table(g.off_t + (GT + wave) * kFrag);
@@ -452,6 +481,9 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
     for (int vb = blockIdx.x; vb < tasks; vb += gridDim.x) {
         int ht, c0;
         char* const base = task_base(vb, &ht, &c0);
+        int wave = own_wave;                             // (opaque: what follows from it would be kept for all tasks, in lanes of registers that are short)
+        asm volatile("" : "+s"(wave));
+        const int tile = wave % TU;                      // of the unit
         // ---- moments, from the last leaf to the first: a step is one block, a wave takes one leaf, with eight waves half of its channels
         constexpr int H1 = 2 / TU;                       // halves that a wave takes
         const int in_block = wave & 3;
@@ -716,15 +748,14 @@ bool nf_unit_geometry(int n, int Lc, int head_dim, NfGeom* out)
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
     if (g.NL < g.R && g.R < g.NL + 4) g.R = g.NL;    // no slots over for part of the next task only
     g.NLr = (g.NL - 1) % g.R;
-    // blocks that the movers hold: whole ones behind the leaves that stay in the ring, spread over the rest of the span
-    const int first = (g.R + 3) / 4, held_of = g.NL / 4 - first;
+    // units of four leaves that the movers hold: of those from leaf R on, spread over the rest of the span
+    const int held_of = (g.NL - 1 - g.R) / 4;        // (whole ones, without the last leaf, whose rows are cut)
     if (held_of > 0) {
         const int most = g.TU == 2 ? kUnitHeld<2> : kUnitHeld<1>;
         g.held = held_of < most ? held_of : most;
-        g.held_every = held_of / g.held;
-        g.held0 = first + g.held_every - 1;
+        g.held_every = 4 * (held_of / g.held);
+        g.held0 = g.R + g.held_every - 4;
     }
-    if (!g.held_every) g.held_every = 1;
     *out = g;
     return true;
 }
