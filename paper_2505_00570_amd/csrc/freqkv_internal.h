@@ -154,7 +154,7 @@ struct NfGeom {
     int spill_bytes;         // (a multiple of 16)
     int spill_cloc;          // ... of these: where the second parts of the groups' local values begin
     char* spill;
-    int v_slots;             // moment tables: 2 (all leaves but the last | the last) or one per leaf
+    int v_slots;             // moment tables: 2 (all leaves but the last | the last), 3 (cosines | sines | the last) or one per leaf
     int off_v, off_m, off_c, off_f, off_t, off_w, table_bytes;
     int d;
     int S, n_heads, hts_per_slab, hts;

@@ -31,7 +31,7 @@
 // of LDS slots (a leaf each): first for the moments, then for the result rows, which mostly come from the 256 MB memory-side
 // cache then, because 256 workgroups x 64 bytes of each row are still in it: that is why a workgroup takes 32 channels and not a whole
 // 256-byte row.  What bounds it: where entries repeat from tile to tile (SHIFTS) moving the rows; else the tables, 22 to 36 KB per tile
-// and workgroup against 4 KB of rows for each (6083 -> 3041 of 128 head-tensors 124 us where the rows come from HBM, as they do with several
+// and workgroup against 4 KB of rows for each (6083 -> 3041 of 128 head-tensors 120 us where the rows come from HBM, as they do with several
 // caches in turn: twice the time of a copy; 100 to 104 us in calls on one cache, whose rows stay in the memory-side cache).  Ownership
 // by columns keeps the in-place write free of hazards: rows are written behind the rows still to be read.
 //
@@ -72,6 +72,9 @@ __host__ __device__ inline int tile_slot(const NfGeom& g, int t)
     if (!g.shifts) return t;
     return t < g.tlo ? g.PT + t : (t >= g.thi ? g.PT + g.tlo + (t - g.thi) : t % g.PT);
 }
+// Are the moments' tables the same for all leaves but the last?  cos(Lc b_j) is cos(phase of the leaf + angle within it), so the cosines and
+// sines of the angles within a leaf do for all, and the moments are their products' sum with the phase's cosine and (negative) sine.
+__host__ __device__ inline bool phased(const NfGeom& g) { return g.NK == 2 && !g.shifts; }
 // First block of the neighbourhood that group gr treats leaf by leaf.
 __host__ __device__ inline int group_block0(const NfGeom& g, int gr)
 {
@@ -151,6 +154,10 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
         u32x2* const words = (u32x2*)(out + g.off_w);
         if (w < g.NT) words[w] = tile_words(g, (int)w);
         else if (w == g.NT) words[w] = u32x2{(uint32_t)group_block0(g, 0), 0u};
+        else if (phased(g) && w <= g.NT + g.NL) {            // cosine and sine of the phase at which a leaf begins
+            const double t = (double)((256 * (w - g.NT - 1) * g.Lc) % (4LL * g.n)) / (2.0 * g.n);
+            words[w] = u32x2{__float_as_uint((float)cospi(t)), __float_as_uint((float)sinpi(t))};
+        }
         return;
     }
     const int lane = (int)(idx & 63);
@@ -177,14 +184,16 @@ __global__ void k_nf_tables(NfGeom g, char* __restrict__ out)
             x = g.out_scale * near_entry(g, slot, l32, 16 * k + 8 * hw + i);
             if (second) x -= first_part(x);
         } else if (byte < g.off_m) {
-            // moments: [slot][4 steps of 32 rows], 8 moments (then the second parts of their entries) x 32 rows
+            // moments: [slot][4 steps of 32 rows], 8 moments (then the second parts of their entries) x 32 rows.  Slots: one per leaf; all
+            // leaves but the last | the last; or (phased) cosines of all leaves but the last, from a phase of zero | their sines | the last
             const int f = (int)((byte - g.off_v) / kFrag), slot = f >> 2;
-            const int leaf = g.v_slots == 2 ? (slot ? g.NL - 1 : 0) : slot;
+            const int leaf = phased(g) ? (slot == 2 ? g.NL - 1 : 0) : g.v_slots == 2 ? (slot ? g.NL - 1 : 0) : slot;
             const long long j = 128LL * leaf + (f & 3) * 32 + 8 * g4 + i;
-            const Iv iv = leaf_iv(g, leaf);
-            if (j < g.n && iv.h > 0) {
+            const Iv iv = phased(g) && slot < 2 ? Iv{64.0, 64.0} : leaf_iv(g, leaf);
+            if (iv.h > 0 && (j < g.n || (phased(g) && slot < 2))) {
                 const long long ph = ((2 * j + 1) * (long long)g.Lc) % (4LL * g.n);      // cos(Lc b_j)
-                x = lagrange(l16 & 7, (j + 0.5 - iv.c) / iv.h) * cospi((double)ph / (2.0 * n)) / 128.0;
+                const double t = (double)ph / (2.0 * n);
+                x = lagrange(l16 & 7, (j + 0.5 - iv.c) / iv.h) * (phased(g) && slot == 1 ? sinpi(t) : cospi(t)) / 128.0;
                 if (l16 >= 8) x -= first_part(x);
             }
         } else if (byte < g.off_c) {
@@ -410,7 +419,13 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 const int end = (int)(words[min(t + kCompute, g.NT) - 1][0] & 255) + NK;
                 wait_copies(copies - copied(end));
                 lds_barrier();
-                issue_until(p0 + (whole ? g.R : g.NL + first));
+                // The next task's leaves come in one go in the last step: what the computing waves load of the next tile's tables waits behind
+                // every copy that is in flight, step after step, and without tables in flight the copies take what HBM gives (all as soon as their slots are
+                // free -> in the last two steps -> in the last one -> all after it: 2044 -> 1226 rows of 256 head-tensors 98.0, 96.4, 93.0, 93.4 us,
+                // 2044 -> 1839 124, 119, 116, 117, 4999 -> 2499 of 256 189.9, 186.6, 187.9, -, 6083 -> 3041 of 128 121.1, 119.8, 120.2, 120.3).
+                int limit = p0 + (whole ? g.R : g.NL + first);
+                if (!SHIFTS && t + kCompute < g.NT) limit = min(limit, p0 + g.NL + max(0, g.NL - g.R));
+                issue_until(limit);
             }
             p0 += g.NL + max(0, g.NL - g.R);
             d0 = copied(g.NL);
@@ -521,9 +536,14 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         });
         put_moments(cmom + b * (MV * kVecB), a[0], a[1], -1);
     };
-    bf16x8 vt[4];                                    // moments of the wave's next leaf
+    // PHASED: one pair of tables for all leaves but the last, the cosines' in LDS, the sines' in registers, as is the last leaf's own.  (A
+    // table per leaf, requested a step ahead, comes back behind the copies of all the leaves that are in flight, so that the ring did
+    // little to hide their way: 6083 -> 3041 of 128 head-tensors 50 000 -> 40 000 cycles for the first reading, 122.6 -> 120.9 us; 4092 -> 2455 of 512
+    // 342 -> 336; the errors are the same to four digits.  For windows of 3 leaves there are no registers left.)
+    constexpr bool PHASED = NK == 2 && !SHIFTS;
+    bf16x8 vt[4], vs[PHASED ? 4 : 1];                // moments of the wave's next leaf (PHASED: of the last leaf)
     auto fetch_moments = [&](int leaf) {
-        const int off = g.off_v + (SHIFTS ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
+        const int off = g.off_v + (PHASED ? 2 : SHIFTS ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
         static_for<4>([&](auto k) { vt[k.value] = table(off + k.value * kFrag); });
     };
     bf16x8 rt[TPW], rt2[TPW];                        // results from local values: first and second product
@@ -533,12 +553,13 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
             rt[u.value] = table(off);
             rt2[u.value] = table(off + 2 * GT * kFrag);
         });
-        static_for<TPW>([&](auto u) { pin(rt[u.value]); pin(rt2[u.value]); });
     };
+    auto pin_results = [&]() { static_for<TPW>([&](auto u) { pin(rt[u.value]); pin(rt2[u.value]); }); };
     const int top_leaf = 4 * (g.NC - 1) + wave < g.NL ? 4 * (g.NC - 1) + wave : 4 * (g.NC - 2) + wave;   // the wave's first
-    if constexpr (!ROLL) static_for<kNB>([&](auto k) { fetch_local(0, k); });
+    // (all of them in flight together, in the order in which they are used)
+    if constexpr (PHASED) static_for<4>([&](auto k) { vs[k.value] = table(g.off_v + (4 + k.value) * kFrag); });
     if (top_leaf >= 0) fetch_moments(top_leaf);
-    if (SHIFTS) static_for<4>([&](auto k) { pin(vt[k.value]); });
+    if constexpr (!ROLL) static_for<kNB>([&](auto k) { fetch_local(0, k); });
     fetch_results(g.NG == 1);
 
     // table of exact entries of the tile at hand, in registers; replaced step by step when the next tile has another
@@ -550,6 +571,9 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         cur_slot = (int)(words[wave][0] >> 16);
         fetch_entries(cur_slot);
     }
+    if constexpr (PHASED) static_for<4>([&](auto k) { pin(vs[k.value]); });
+    if (SHIFTS || PHASED) static_for<4>([&](auto k) { pin(vt[k.value]); });
+    pin_results();
     static_for<STEPS>([&](auto k) { pin(e[k.value]); });
 
     // parts of addresses that depend on the lane
@@ -569,6 +593,12 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                 const int leaf = 4 * i + wave;
                 if (SHIFTS && leaf != top_leaf)
                     static_for<4>([&](auto k) { vt[k.value] = lds_table(k.value); });
+                [[maybe_unused]] bf16x8 vc[4];
+                [[maybe_unused]] u32x2 phase;
+                if constexpr (PHASED) {
+                    static_for<4>([&](auto k) { vc[k.value] = lds_table(k.value); });
+                    phase = words[g.NT + 1 + min(leaf, g.NL - 1)];
+                }
                 lds_barrier();
                 if (leaf < g.NL) {
                     NF_LANE();
@@ -582,13 +612,25 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
                         });
                     });
                     __builtin_amdgcn_sched_barrier(0);
-                    static_for<4>([&](auto k) {
-                        static_for<2>([&](auto h) {
-                            a[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[k.value], xa[k.value][h.value], a[h.value], 0, 0, 0);
+                    auto products = [&](const bf16x8 (&t)[4], f32x4 (&to)[2]) {
+                        static_for<4>([&](auto k) {
+                            static_for<2>([&](auto h) {
+                                to[h.value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[k.value], xa[k.value][h.value], to[h.value], 0, 0, 0);
+                            });
                         });
-                    });
+                    };
+                    if (!PHASED || leaf == g.NL - 1) products(vt, a);
+                    if constexpr (PHASED) {
+                        if (leaf != g.NL - 1) {
+                            f32x4 b[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                            products(vc, a);
+                            products(vs, b);
+                            const float c = __uint_as_float(phase[0]), s = __uint_as_float(phase[1]);
+                            static_for<2>([&](auto h) { static_for<4>([&](auto r) { a[h.value][r.value] = c * a[h.value][r.value] - s * b[h.value][r.value]; }); });
+                        }
+                    }
                     put_moments(mom + (SPILL ? leaf & 7 : leaf) * (MV * kVecB), a[0], a[1], leaf * (MV * kVecB));
-                    if (!SHIFTS) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
+                    if (!SHIFTS && !PHASED) fetch_moments(leaf >= 4 ? leaf - 4 : top_leaf);
                 } else if constexpr (SPILL) {                // (a leaf that does not exist: see above)
                     const f32x4 none = {0.f, 0.f, 0.f, 0.f};
                     put_moments(mom + (leaf & 7) * (MV * kVecB), none, none, leaf * (MV * kVecB));
@@ -843,12 +885,12 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
         for (int i = 0; i < steps; i += 2) {
             const int c = TPW == 2 ? i / 2 : i;
             step(c, IC<0>{}, acc0, acc1);
-            if (TPW == 1 && g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+            if (TPW == 1 && g.NG > 1 && c >= g.NG - 2) { fetch_results(c == g.NG - 2); pin_results(); }
             if (i + 1 < steps) {
                 step(TPW == 2 ? c : c + 1, IC<TPW - 1>{}, acc1, acc0);
-                if (TPW == 1 && c + 1 >= g.NG - 2) fetch_results(c + 1 == g.NG - 2);
+                if (TPW == 1 && c + 1 >= g.NG - 2) { fetch_results(c + 1 == g.NG - 2); pin_results(); }
             }
-            if (TPW == 2 && g.NG > 1 && c >= g.NG - 2) fetch_results(c == g.NG - 2);
+            if (TPW == 2 && g.NG > 1 && c >= g.NG - 2) { fetch_results(c == g.NG - 2); pin_results(); }
         }
         if constexpr (LATE) {
             if (steps & 1) static_for<7>([&](auto p) { finish(acc0, before, p); });
@@ -930,14 +972,14 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
     // at 12284 -> 3071 of 64 head-tensors (matrix form 687).
     if (!g.spills && nf_unit_geometry(n, Lc, head_dim, out)) return true;
     const int slots = g.shifts ? g.PT + g.tlo + (g.NT - g.thi) : g.NT, parts = g.spills ? 2 : 1;
-    g.v_slots = g.shifts ? 2 : g.NL;
+    g.v_slots = phased(g) ? 3 : g.shifts ? 2 : g.NL;
     g.off_v = slots * (8 * g.NK + g.NLO) * kFrag;
     g.off_m = g.off_v + g.v_slots * 4 * kFrag;
     g.off_c = g.off_m + g.NC * kFrag;
     g.off_f = g.off_c + (g.NGp / 2) * (g.NCp / 4) * parts * kFrag;
     g.off_t = g.off_f + g.NG * (g.GT / 2) * g.NB * parts * kFrag;
     g.off_w = g.off_t + 4 * g.GT * kFrag;
-    g.table_bytes = g.off_w + (g.NT + 1) * 8;
+    g.table_bytes = g.off_w + (g.NT + 1 + (phased(g) ? g.NL : 0)) * 8;
     if (g.R > 19) g.R = 19;                          // more copies than that are never in flight
     if (g.NL < g.R && g.R < g.NL + 4) g.R = g.NL;    // no slots over for part of the next task only
     g.NLr = (g.NL - 1) % g.R;
@@ -948,7 +990,7 @@ bool nf_geometry(int n, int Lc, int head_dim, NfGeom* out)
 hipError_t launch_nf_tables(const NfGeom& g, char* out, hipStream_t st)
 {
     if (g.TU) return launch_nf_unit_tables(g, out, st);
-    const long long threads = g.off_w / 16 + g.NT + 1;
+    const long long threads = g.off_w / 16 + g.NT + 1 + g.NL;
     hipLaunchKernelGGL(k_nf_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, out);
     return hipGetLastError();
 }
