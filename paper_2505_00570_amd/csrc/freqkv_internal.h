@@ -29,6 +29,11 @@ constexpr int kMaxSlabs = 192;
 struct SlabTable {
     char* base[kMaxSlabs];
 };
+// ... of a launch of few slabs, see with_slabs
+constexpr int kFewSlabs = 8;
+struct FewSlabs {
+    char* base[kFewSlabs];
+};
 struct TailTable {
     int rows[kMaxSlabs];
 };
@@ -72,7 +77,8 @@ struct Geom {
 };
 
 // Byte address of (token 0, channel c) of the head-tensor that owns virtual column vcol.
-__device__ __forceinline__ char* column_base(const SlabTable& tab, const Geom& g, int vcol,
+template <class Slabs>
+__device__ __forceinline__ char* column_base(const Slabs& tab, const Geom& g, int vcol,
                                              int elem_bytes, int* ht_out)
 {
     int ht   = vcol / g.d;
@@ -92,7 +98,7 @@ enum Variant { kNone = 0, kFoldF16 = 1, kPlainF16 = 2, kF32 = 3, kDrop = 4, kFol
 // ---- basis construction (fp64 closed form, rounded once) -------------------------
 // G: [Kpad/8][Grows][8] fp16.  Folded: rows [0,Mpad) even part, rows [Mpad,2Mpad) odd part.
 hipError_t launch_basis_f16(_Float16* G, const Geom& g, int rescale, hipStream_t st);
-// Gt: [parity][Kh][Mpad] fp32 (plain: one parity).
+// Gt: [parity] of Kh x Mpad fp32 (plain: one parity), four consecutive k side by side (f32_at).
 hipError_t launch_basis_f32(float* Gt, const Geom& g, int rescale, hipStream_t st);
 
 // Power of two that brings a head-tensor whose largest bf16 magnitude has the bit pattern `amax` into

@@ -24,6 +24,8 @@
 // cores with fp32 accumulation, writing the Lc rows straight into the cache.
 #include "freqkv_internal.h"
 
+#include <type_traits>
+
 namespace freqkv {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -170,7 +172,15 @@ __global__ void k_basis_f16(_Float16* __restrict__ G, Geom g, double scale)
     *(half8*)(G + idx * 8) = out;
 }
 
-// fp32 operator, transposed for the contraction: [parity][Kh][Mpad] (plain: one parity), zero in the pad columns.
+// Where the fp32 path keeps element (k, x) of a matrix of `rows` contraction indices and `width` result rows or columns: four consecutive k of
+// one x side by side, [rows / 4][width][4], so that a lane takes four steps of the contraction with one load (which of its indices
+// come together in a step does not matter as long as both operands agree); the last 0 to 3 rows behind them as they are.
+__host__ __device__ inline size_t f32_at(int k, int x, int rows, int width)
+{
+    return k < (rows & ~3) ? ((size_t)(k >> 2) * width + x) * 4 + (k & 3) : (size_t)k * width + x;
+}
+
+// fp32 operator for the contraction: [parity] (plain: one parity) of Kh x Mpad, zero in the pad columns.
 __global__ void k_basis_f32(float* __restrict__ Gt, Geom g, double scale)
 {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -186,7 +196,7 @@ __global__ void k_basis_f32(float* __restrict__ Gt, Geom g, double scale)
             v = parity ? v - b : v + b;                               // the halves are in the span
         }
     }
-    Gt[idx] = (float)v;
+    Gt[(size_t)parity * g.Kh * g.Mpad + f32_at(j, m, g.Kh, g.Mpad)] = (float)v;
 }
 
 hipError_t launch_basis_f16(_Float16* G, const Geom& g, int rescale, hipStream_t st)
@@ -814,93 +824,118 @@ hipError_t launch_contract_f16(const SlabTable& tab, const Geom& g, const _Float
 
 // ------------------------------------------------------------------------------------------
 // fp32 cache: fold (or copy) the span out, then contract on the fp32 matrix instructions (fp32 products and sums)
-// workspace: xs[parity][Kh][ncolsf] fp32, ncolsf = ncols rounded up to 64 (pad columns are zero)
+// workspace: xs[parity] of Kh x ncolsf fp32 as f32_at has it, ncolsf = ncols rounded up to 64 (pad columns are zero)
 // ------------------------------------------------------------------------------------------
 
-__device__ __forceinline__ int f32_cols_padded(const Geom& g) { return (g.ncols + 63) & ~63; }
+__host__ __device__ inline int f32_cols_padded(const Geom& g) { return (g.ncols + 63) & ~63; }
 
-template <bool FOLD>
-__global__ __launch_bounds__(256) void k_prepare_f32(SlabTable tab, Geom g, float* __restrict__ ws)
+// A thread takes four consecutive rows (and their mirror images) of a column.
+constexpr int kPrepColsF32 = 64, kPrepGroupsF32 = 4;
+template <bool FOLD, class Slabs>
+__global__ __launch_bounds__(kPrepColsF32 * kPrepGroupsF32) void k_prepare_f32(Slabs tab, Geom g, float* __restrict__ ws)
 {
     const int ncp = f32_cols_padded(g);
-    const int vcol = blockIdx.x * 256 + threadIdx.x;
-    if (vcol >= ncp) return;
+    const int vcol = blockIdx.x * kPrepColsF32 + threadIdx.x;
     const char* base = vcol < g.ncols ? column_base(tab, g, vcol, 4, nullptr) + (long long)g.S * g.stride_token * 4 : nullptr;
-    for (int j = blockIdx.y; j < g.Kh; j += gridDim.y) {
-        float a = 0.f, b = 0.f;
-        if (base) a = *(const float*)(base + (long long)j * g.stride_token * 4);
-        if (FOLD && base) b = *(const float*)(base + (long long)(g.n - 1 - j) * g.stride_token * 4);
-        if (FOLD) a *= 0.5f, b *= 0.5f;                               // as large as the values themselves: no overflow
-        ws[(size_t)j * ncp + vcol] = FOLD ? a + b : a;
-        if (FOLD) ws[(size_t)(g.Kh + j) * ncp + vcol] = a - b;
+    const long long row_bytes = g.stride_token * 4;
+    for (int q = blockIdx.y * kPrepGroupsF32 + threadIdx.y; 4 * q < g.Kh; q += gridDim.y * kPrepGroupsF32) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+        if (base) {
+            static_for<4>([&](auto e) {
+                const int j = min(4 * q + e.value, g.Kh - 1);
+                a[e.value] = *(const float*)(base + j * row_bytes);
+                if (FOLD) b[e.value] = *(const float*)(base + (g.n - 1 - j) * row_bytes);
+            });
+        }
+        if (FOLD) {                                                   // as large as the values themselves: no overflow
+            static_for<4>([&](auto e) {
+                const float x = 0.5f * a[e.value], y = 0.5f * b[e.value];
+                a[e.value] = x + y;
+                b[e.value] = x - y;
+            });
+        }
+        static_for<FOLD ? 2 : 1>([&](auto p) {
+            float* const to = ws + (size_t)p.value * g.Kh * ncp;
+            const f32x4 x = p.value ? b : a;
+            if (4 * q + 4 <= g.Kh) *(f32x4*)(to + f32_at(4 * q, vcol, g.Kh, ncp)) = x;
+            else static_for<3>([&](auto e) { if (4 * q + e.value < g.Kh) to[f32_at(4 * q + e.value, vcol, g.Kh, ncp)] = x[e.value]; });
+        });
     }
 }
 
-// A workgroup owns 32 result rows (of each parity) x 32 columns; its four waves take a quarter of the contraction each, with
-// the operands straight from the L2 (32 consecutive rows or columns of two contraction indices in a 4-byte load per lane: at
-// 64 cycles per matrix instruction that is little traffic), and are added up in LDS.  The chain of one wave is what a small
-// cache costs: 254 x 508 on 64 columns of K and of V took 80 us as 8 workgroups of a 64 x 64 tile with vector multiply-adds
-// behind a barrier every 16 indices, and takes 5 us; 1022 x 2044 on 8192 columns took 810 us and takes 290 us.  Eight waves
-// to a tile lose 2 us on the former and 50 us on the latter, 32 x 64 tiles 5 us and 40 us, tiles of one wave 17 us and 12 us.
+// A workgroup owns TILE result rows (of each parity) x TILE columns; its four waves take a quarter of the contraction each, with
+// the operands straight from the L2, 16 bytes per lane for four steps, and are added up in LDS.
+// TILE 32: what bounds it is the loads, half of the 64 bytes per cycle that a compute unit takes: 2044 -> 1022 on 8192 columns 190 us per call, 89
+// TFLOP/s (with 4-byte loads, eight steps at a time, 303; as a 64 x 64 tile with vector multiply-adds 810), 1020 -> 510 on 4096 33.1 (47.8).
+// TILE 16, for few columns: a chain of loads, products and the sum is all that such a call consists of, so it is cut into four times as many
+// workgroups: 508 -> 254 rows of 64 columns of K and of V 7.1 us per call (10.3 with TILE 32, 11.9 with 4-byte loads as well), of which host work takes 6.
 constexpr int kWavesF32 = 4;
 
-template <bool FOLD>
+template <bool FOLD, int TILE, class Slabs>
 __global__ __launch_bounds__(kWavesF32 * 64)
-void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const float* __restrict__ ws, float* __restrict__ tap)
+void k_contract_f32(Slabs tab, Geom g, const float* __restrict__ Gt, const float* __restrict__ ws, float* __restrict__ tap)
 {
-    // U steps have their loads in flight together.  Without a fold half the matrix instructions stand behind a load, and one chain: there
-    // twice as many steps, and a second set requested ahead of the products of the first (8 steps in one set | 16 in two: 253 x 507 on
-    // 64 columns of K and of V 20.4 | 12.2 us, 510 x 2043 on 256 columns 72 | 27, 1021 x 2043 on 8192 508 | 493).  With a fold a second
-    // set loses (508 -> 254 12.1 -> 14.8, 2044 -> 1022 on 8192 columns 281 -> 304), and so do 16 steps in one (16.4, 330).
-    constexpr int P = FOLD ? 2 : 1, U = FOLD ? 8 : 16, SETS = FOLD ? 1 : 2;
-    __shared__ float red[kWavesF32][P][16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hw = lane >> 5;
-    const int ncp = f32_cols_padded(g), rtiles = g.Mpad / 32;
-    const int m0 = (int)(blockIdx.x % rtiles) * 32, c0 = (int)(blockIdx.x / rtiles) * 32;
-    const int steps = (g.Kh + 1) / 2;                                 // of two contraction indices each
-    const int per = (steps + kWavesF32 - 1) / kWavesF32, s0 = wave * per, s1 = min(s0 + per, steps);
-    f32x16 acc[P];
-    static_for<P>([&](auto p) { static_for<16>([&](auto r) { acc[p.value][r.value] = 0.f; }); });
-    const float* ga = Gt + m0 + l32;
-    const float* xb = ws + c0 + l32;
-    auto fetch = [&](float (&a)[U][P], float (&b)[U][P], int s) __attribute__((always_inline)) {
-        static_for<U>([&](auto u) {
-            const int k = min(2 * (s + u.value) + hw, g.Kh - 1);      // past the end: the last index again, times zero
+    // GR groups of four indices come together in a unit of four steps; U units have their loads in flight together, and U more while
+    // these are multiplied.
+    // (1, 2, 4 units in two sets, 2, 4 in one: 2044 -> 1022 on 8192 columns 190, 192, 210 | 193, 193 us, 896 -> 448 on 2048 27.0, 30.1, 33.4 |
+    // 30.1, 30.1; with TILE 16 2044 -> 1022 on 256 columns 13.1, 13.7, 14.8 | -, 14.1.)
+    constexpr int P = FOLD ? 2 : 1, GR = 64 / TILE, REGS = TILE * TILE / 64;
+    constexpr int U = TILE == 32 && !FOLD ? 2 : 1;
+    __shared__ float red[kWavesF32][P][REGS][64];
+    typedef float Acc __attribute__((ext_vector_type(REGS)));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, at = lane % TILE, group = lane / TILE;
+    const int ncp = f32_cols_padded(g), rtiles = (g.Mh + TILE - 1) / TILE;
+    const int m0 = (int)(blockIdx.x % rtiles) * TILE, c0 = (int)(blockIdx.x / rtiles) * TILE;
+    const int groups = g.Kh / 4, units = (groups + GR - 1) / GR;
+    const int per = (units + kWavesF32 - 1) / kWavesF32, u0 = wave * per, u1 = min(u0 + per, units);
+    Acc acc[P];
+    static_for<P>([&](auto p) { static_for<REGS>([&](auto r) { acc[p.value][r.value] = 0.f; }); });
+    const float* ga = Gt + m0 + at;
+    const float* xb = ws + c0 + at;
+    auto mac = [&](float a, float b, Acc& c) __attribute__((always_inline)) {
+        if constexpr (TILE == 32) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+        else c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    };
+    auto fetch = [&](f32x4 (&a)[U][P], f32x4 (&b)[U][P], int u) __attribute__((always_inline)) {
+        static_for<U>([&](auto i) {
+            const int q = min((u + i.value) * GR + group, groups - 1);       // past the end: the last group again, times zero
             static_for<P>([&](auto p) {
-                a[u.value][p.value] = ga[((size_t)p.value * g.Kh + k) * g.Mpad];
-                b[u.value][p.value] = xb[((size_t)p.value * g.Kh + k) * ncp];
+                a[i.value][p.value] = *(const f32x4*)(Gt + ((size_t)p.value * g.Kh * g.Mpad + ((size_t)q * g.Mpad + m0 + at) * 4));
+                b[i.value][p.value] = *(const f32x4*)(ws + ((size_t)p.value * g.Kh * ncp + ((size_t)q * ncp + c0 + at) * 4));
+            });
+        });
+        __builtin_amdgcn_sched_barrier(0);                            // (left alone the compiler has four loads in flight)
+    };
+    auto multiply = [&](const f32x4 (&a)[U][P], const f32x4 (&b)[U][P], int u) __attribute__((always_inline)) {
+        static_for<U>([&](auto i) {
+            const bool in = u + i.value < u1 && (u + i.value) * GR + group < groups;
+            static_for<4>([&](auto e) {
+                static_for<P>([&](auto p) { mac(in ? a[i.value][p.value][e.value] : 0.f, in ? b[i.value][p.value][e.value] : 0.f, acc[p.value]); });
             });
         });
     };
-    auto multiply = [&](const float (&a)[U][P], const float (&b)[U][P], int s) __attribute__((always_inline)) {
-        static_for<U>([&](auto u) {
-            const bool in = s + u.value < s1 && 2 * (s + u.value) + hw < g.Kh;
+    f32x4 a[2][U][P], b[2][U][P];
+    if (u0 < u1) fetch(a[0], b[0], u0);
+    for (int u = u0; u < u1; u += 2 * U) {
+        fetch(a[1], b[1], u + U);
+        multiply(a[0], b[0], u);
+        fetch(a[0], b[0], u + 2 * U);
+        multiply(a[1], b[1], u + U);
+    }
+    if (wave == kWavesF32 - 1) {                                      // (the wave with the least to do) the rows behind the last whole group
+        for (int k0 = 4 * groups; k0 < g.Kh; k0 += GR) {
+            const int k = min(k0 + group, g.Kh - 1);
+            const bool in = k0 + group < g.Kh;
             static_for<P>([&](auto p) {
-                acc[p.value] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[u.value][p.value] : 0.f, in ? b[u.value][p.value] : 0.f,
-                                                                    acc[p.value], 0, 0, 0);
+                const float x = ga[((size_t)p.value * g.Kh + k) * g.Mpad], y = xb[((size_t)p.value * g.Kh + k) * ncp];
+                mac(in ? x : 0.f, in ? y : 0.f, acc[p.value]);
             });
-        });
-    };
-    if constexpr (SETS == 2) {
-        float a[2][U][P], b[2][U][P];
-        fetch(a[0], b[0], s0);
-        for (int s = s0; s < s1; s += 2 * U) {
-            fetch(a[1], b[1], s + U);
-            multiply(a[0], b[0], s);
-            fetch(a[0], b[0], s + 2 * U);
-            multiply(a[1], b[1], s + U);
-        }
-    } else {
-        for (int s = s0; s < s1; s += U) {
-            float a[U][P], b[U][P];
-            fetch(a, b, s);
-            multiply(a, b, s);
         }
     }
-    static_for<P>([&](auto p) { static_for<16>([&](auto r) { red[wave][p.value][r.value][lane] = acc[p.value][r.value]; }); });
+    static_for<P>([&](auto p) { static_for<REGS>([&](auto r) { red[wave][p.value][r.value][lane] = acc[p.value][r.value]; }); });
     __syncthreads();
 
-    const int vcol = c0 + l32;
+    const int vcol = c0 + at;
     if (vcol >= g.ncols) return;
     int ht;
     char* base = column_base(tab, g, vcol, 4, &ht);
@@ -909,8 +944,8 @@ void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const f
         *(float*)(base + (long long)(g.S + row) * g.stride_token * 4) = v;
         if (tp) tp[(long long)row * g.d] = v;
     };
-    for (int r = wave; r < 16; r += kWavesF32) {
-        const int m = m0 + 8 * (r / 4) + 4 * hw + r % 4;              // row of result register r in this half of the wave
+    for (int r = wave; r < REGS; r += kWavesF32) {
+        const int m = m0 + 4 * GR * (r / 4) + 4 * group + r % 4;      // row of result register r in this group of lanes
         if (m >= g.Mh) continue;
         float v[P];
         static_for<P>([&](auto p) {
@@ -926,21 +961,51 @@ void k_contract_f32(SlabTable tab, Geom g, const float* __restrict__ Gt, const f
     }
 }
 
+// Calls f with the pass's slabs in a table of a few pointers if they fit: a launch copies its arguments to the device, 1.5 KB of pointers in
+// 0.7 us, which is a tenth of a short call.
+template <class F> static void with_slabs(const SlabTable& tab, const Geom& g, F&& f)
+{
+    const int slabs = g.ncols / (g.hts_per_slab * g.d);
+    if (slabs <= kFewSlabs) {
+        FewSlabs few;
+        for (int i = 0; i < kFewSlabs; ++i) few.base[i] = tab.base[i];
+        f(few);
+    } else {
+        f(tab);
+    }
+}
+
 hipError_t launch_prepare_f32(const SlabTable& tab, const Geom& g, float* ws, hipStream_t st)
 {
-    const int ncp = (g.ncols + 63) & ~63;
-    const dim3 grid((ncp + 255) / 256, g.Kh < 65535 ? g.Kh : 65535);
-    if (g.fold) hipLaunchKernelGGL(k_prepare_f32<true>, grid, dim3(256), 0, st, tab, g, ws);
-    else        hipLaunchKernelGGL(k_prepare_f32<false>, grid, dim3(256), 0, st, tab, g, ws);
+    const int groups = (g.Kh + 3) / 4, y = (groups + kPrepGroupsF32 - 1) / kPrepGroupsF32;
+    const dim3 grid(f32_cols_padded(g) / kPrepColsF32, y < 65535 ? y : 65535), block(kPrepColsF32, kPrepGroupsF32);
+    with_slabs(tab, g, [&](const auto& t) {
+        typedef std::decay_t<decltype(t)> Slabs;
+        if (g.fold) hipLaunchKernelGGL((k_prepare_f32<true, Slabs>), grid, block, 0, st, t, g, ws);
+        else        hipLaunchKernelGGL((k_prepare_f32<false, Slabs>), grid, block, 0, st, t, g, ws);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_contract_f32(const SlabTable& tab, const Geom& g, const float* Gt, const float* ws,
                                float* tap, hipStream_t st)
 {
-    const dim3 grid(g.Mpad / 32 * (((g.ncols + 63) & ~63) / 32));
-    if (g.fold) hipLaunchKernelGGL(k_contract_f32<true>, grid, dim3(kWavesF32 * 64), 0, st, tab, g, Gt, ws, tap);
-    else        hipLaunchKernelGGL(k_contract_f32<false>, grid, dim3(kWavesF32 * 64), 0, st, tab, g, Gt, ws, tap);
+    // Tiles of 16 up to 192 workgroups of 32 x 32 (tiles of 16 | of 32: 16 workgroups 7.1 | 10.3 us, 128 13.1 | 18.3, 10.7 | 13.2 and 9.5 | 11.0, 144
+    // 13.8 | 15.5, 192 12.5 | 12.5, 256 12.4 | 11.3 and 13.5 | 13.0): with more the compute units are busy, and smaller tiles load twice as much.
+    const int ncp = f32_cols_padded(g);
+    const bool small = (long long)((g.Mh + 31) / 32) * (ncp / 32) <= 192;
+    const int tile = small ? 16 : 32;
+    const dim3 grid((unsigned)((g.Mh + tile - 1) / tile * (ncp / tile))), block(kWavesF32 * 64);
+    with_slabs(tab, g, [&](const auto& t) {
+        typedef std::decay_t<decltype(t)> Slabs;
+        auto launch = [&](auto fold) {
+            constexpr bool FOLD = decltype(fold)::value;
+            if (small) hipLaunchKernelGGL((k_contract_f32<FOLD, 16, Slabs>), grid, block, 0, st, t, g, Gt, ws, tap);
+            else       hipLaunchKernelGGL((k_contract_f32<FOLD, 32, Slabs>), grid, block, 0, st, t, g, Gt, ws, tap);
+        };
+        if (g.fold) launch(std::true_type{});
+        else        launch(std::false_type{});
+    });
     return hipGetLastError();
 }
 
