@@ -7,8 +7,8 @@
 // appendix on key states with RoPE).  Rotary pairing is LLaMA's: channel i turns with channel i + d/2
 // by the angle pos * base^(-2i/d).
 //
-// The work is bound by reading K and V once from HBM, so it runs on the vector ALUs, not on the matrix
-// cores.  Two kernels:
+// The work is bound by reading K and V once from HBM, so scores are worked out on the vector ALUs; the weighted sums of four
+// heads go to the matrix cores, which leaves the vector ALUs half idle.  Two kernels:
 //   k_attend_partial  one workgroup per (KV head, chunk of rows, group of <= 4 query heads that share
 //                     the KV head); every lane owns 4 rotary pairs of a row (8 channels), D/8 lanes
 //                     share a row, and each such lane group walks its rows with a running
@@ -81,6 +81,39 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x)
     if constexpr (LPR >= 16) x += dpp<0x140>(x); // mirror inside the row of 16
     if constexpr (LPR >= 32) x += __shfl_xor(x, 16);
     return x;
+}
+
+// Barrier for what the workgroup keeps in LDS.  (The other one would wait for all loads as well, those of rows past the end of a chunk among
+// them, which nobody uses: 2000 cycles at the end of every workgroup.)
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Lane I of each quad, in all four lanes of it.
+template <int I> __device__ __forceinline__ float quad_lane(float x) { return dpp<I * 0x55>(x); }
+
+// Sums of four values over the LPR adjacent lanes that share a cache row: lane i of each quad gets that of x[i].  The first two steps
+// halve what is left to sum.
+template <int LPR> __device__ __forceinline__ float quad_sums(const float (&x)[4], int lane)
+{
+    const bool odd = lane & 1, high = lane & 2;
+    float a = odd ? x[1] : x[0], b = odd ? x[3] : x[2];
+    a += dpp<0xB1>(odd ? x[0] : x[1]);           // quad_perm [1,0,3,2]
+    b += dpp<0xB1>(odd ? x[2] : x[3]);
+    float s = high ? b : a;
+    s += dpp<0x4E>(high ? a : b);                // quad_perm [2,3,0,1]
+    if constexpr (LPR == 8) {
+        s += dpp<0x141>(dpp<0x1B>(s));           // the other quad of the half row: mirrored in the quad [3,2,1,0], then in the half row
+    } else {
+        static_assert(LPR >= 16);
+        s += dpp<0x124>(s);                      // the row of 16 turned by 4 and by 8
+        s += dpp<0x128>(s);
+        if constexpr (LPR >= 32) s += __shfl_xor(s, 16);
+    }
+    return s;
 }
 
 // x op (x of the lane O further or nearer), in every lane; O = 8, 16 or 32.  On the vector units: a shuffle goes through LDS, and
@@ -186,10 +219,11 @@ __global__ void k_rope_table(RopeEntry* rt, int d, double base, int step)
 // EXACT: no surplus loop step where a chunk has an odd number of them.
 template <typename T, int D, int GT, int P, bool ONE, bool EXACT>
 __global__ __launch_bounds__(kWaves * 64, attend_min_waves(sizeof(T), GT, P))
-void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict__ q,
+void k_attend_partial(const AttGeom, const T* __restrict__ q,
                       const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
-                      float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse)
+                      float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
+    const AttGeom g = first_argument<AttGeom, 4>();      // and those up to the first layers' slabs
     constexpr int LPR = D / (2 * P);       // lanes per cache row
     constexpr int RPW = 64 / LPR;          // rows per wave per load
     constexpr int STEP = kWaves * RPW;     // rows between two consecutive rows of one lane group
@@ -268,25 +302,36 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
         });
         next_off += (uint32_t)(U * STEP) * row_bytes;
     };
-    // the first rows are requested before anything else: the seeds below need no cache data
+    // Frequencies and queries, then the rows of the first two steps, all requested together ahead of the seeds: loads come back in order.
+    // (Left alone the compiler puts the rows behind the seeds.)
+    RopeEntry re[P];
+    RawT qrl[GT], qrh[GT];
+    static_for<P>([&](auto jj) { re[jj.value] = rt[P * l + jj.value]; });
+    static_for<GT>([&](auto gg) {
+        const T* qp = q + ((long long)unit * g.G + g0 + gg.value) * D;
+        load_raw(qp + P * l, qrl[gg.value]);
+        load_raw(qp + D / 2 + P * l, qrh[gg.value]);
+    });
     Rows ra, rb;
     issue(ra);
+    issue(rb);
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- rotary state of the P pairs this lane owns: pair j couples channels P*l+j and D/2+P*l+j.
     // (c, s) = cos/sin of (row position * theta_j); each processed row advances them by the fixed rotation
     // (cd, sd) of STEP rows, and every kReseed loop steps they are recomputed exactly.
     float c[P], s[P], cd[P], sd[P];
-    auto seed_rows = [&](int pos) {
+    auto seed_rows = [&](int pos, const RopeEntry (&entries)[P]) {
         static_for<P>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            RopeEntry e = rt[P * l + j];
+            const RopeEntry e = entries[j];
             CosSin k0 = seed_sincos(g.rope ? e.theta : 0.0, pos);   // no rotary embedding: every angle is zero
             c[j] = k0.c; s[j] = k0.s;
             cd[j] = g.rope ? e.cd : 1.f;
             sd[j] = g.rope ? e.sd : 0.f;
         });
     };
-    seed_rows(p0);
+    seed_rows(p0, re);
 
     // ---- queries: rotated at the query's position, scaled by log2(e)/sqrt(d) so that exp is exp2
     float ql[GT][P], qh[GT][P];
@@ -294,18 +339,14 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
         float qc[P], qs[P];
         static_for<P>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            CosSin q0 = seed_sincos(g.rope ? rt[P * l + j].theta : 0.0, q_pos);
+            CosSin q0 = seed_sincos(g.rope ? re[j].theta : 0.0, q_pos);
             qc[j] = q0.c; qs[j] = q0.s;
         });
         static_for<GT>([&](auto gg) {
             constexpr int gi = decltype(gg)::value;
-            const T* qp = q + ((long long)unit * g.G + g0 + gi) * D;
-            RawT rl, rh;
-            load_raw(qp + P * l, rl);
-            load_raw(qp + D / 2 + P * l, rh);
             float a[P], bb[P];
-            unpack(rl, a);
-            unpack(rh, bb);
+            unpack(qrl[gi], a);
+            unpack(qrh[gi], bb);
             static_for<P>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
                 ql[gi][j] = (a[j] * qc[j] - bb[j] * qs[j]) * g.qscale;
@@ -313,6 +354,18 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
             });
         });
     }
+
+    // Four heads: softmax of a row by quads of lanes, a head to each lane, and weighted sums on the matrix cores (v_mfma_f32_4x4x1, fp32 in and
+    // out: in each quad the product of 4 weights, one per lane, and 4 values, one per lane; a lane gets the 4 sums of its channel).  What
+    // bounds a chunk that has its compute unit to itself is vector issue, 4 cycles per instruction: a step of two rows took 440
+    // of them with every lane working out all heads, four exponentials at a quarter of the rate among them, and takes 280, so that rows are
+    // what it waits for (1 x 8 KV heads x 6147 rows 14.4 -> 13.2 us per call, with the arguments and the last barrier 12.5; x 16000 20.9 -> 17.9; 32 layers
+    // x 8 x 4000 rows with 8 query heads each 152 -> 138).
+    constexpr bool QUADS = GT == 4;
+    typedef float Acc4 __attribute__((ext_vector_type(4)));
+    [[maybe_unused]] float qm = kMinusBig, qsum = 0.f;   // of the lane's head
+    [[maybe_unused]] Acc4 qacc[2 * P];                   // [channel][head]
+    static_for<2 * P>([&](auto cc) { qacc[cc.value] = Acc4{0.f, 0.f, 0.f, 0.f}; });
 
     float m[GT], lsum[GT], acc[GT][2 * P];
     static_for<GT>([&](auto gg) {
@@ -325,10 +378,14 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
     // ---- main loop over the rows of this lane group: p0, p0+STEP, p0+2*STEP, ...
     // One step: the U rows in r (loaded a step ago) against the GT queries.
     auto consume = [&](const Rows& r, int it) {
-        if (it != 0 && (it & (kReseed - 1)) == 0) seed_rows(p0 + it * U * STEP);
+        if (it != 0 && (it & (kReseed - 1)) == 0) {
+            RopeEntry again[P];
+            static_for<P>([&](auto jj) { again[jj.value] = rt[P * l + jj.value]; });
+            seed_rows(p0 + it * U * STEP, again);
+        }
         const bool tail = row0 + (it + 1) * U * STEP > row_end;       // same for the whole workgroup
 
-        float sc[U][GT];
+        float sc[U][QUADS ? 1 : GT];
         static_for<U>([&](auto uu) {
             constexpr int u = decltype(uu)::value;
             float a[P], bb[P];
@@ -349,18 +406,47 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
                 s[j] = s[j] * cd[j] + c[j] * sd[j];
                 c[j] = cn;
             });
-            static_for<GT>([&](auto gg) {
-                constexpr int gi = decltype(gg)::value;
-                sc[u][gi] = group_sum<LPR>(part[gi]);
-            });
+            if constexpr (QUADS) sc[u][0] = quad_sums<LPR>(part, lane);
+            else static_for<GT>([&](auto gg) { sc[u][gg.value] = group_sum<LPR>(part[gg.value]); });
             if (tail) {                                        // only the last steps of a chunk can hold rows past its end
                 const bool valid = p0 + (it * U + u) * STEP < row_end;
-                static_for<GT>([&](auto gg) {
+                static_for<QUADS ? 1 : GT>([&](auto gg) {
                     constexpr int gi = decltype(gg)::value;
                     sc[u][gi] = valid ? sc[u][gi] : -INFINITY;
                 });
             }
         });
+
+        if constexpr (QUADS) {
+            // (the reference point as below)
+            float mx = sc[0][0];
+            static_for<U>([&](auto uu) { mx = fmaxf(mx, sc[uu.value][0]); });
+            const bool grow = mx > qm + kSlack;
+            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+                const float mn = grow ? mx : qm;
+                const float f = exp2_fast(qm - mn);
+                qm = mn;
+                qsum *= f;
+                static_for<GT>([&](auto gg) {
+                    const float fh = quad_lane<gg.value>(f);
+                    static_for<2 * P>([&](auto cc) { qacc[cc.value][gg.value] *= fh; });
+                });
+            }
+            static_for<U>([&](auto uu) {
+                constexpr int u = decltype(uu)::value;
+                const float pw = exp2_fast(sc[u][0] - qm);
+                qsum += pw;
+                float va[P], vb2[P];
+                unpack(r.vl[u], va);
+                unpack(r.vh[u], vb2);
+                static_for<P>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value;
+                    qacc[j] = __builtin_amdgcn_mfma_f32_4x4x1f32(pw, va[j], qacc[j], 0, 0, 0);
+                    qacc[P + j] = __builtin_amdgcn_mfma_f32_4x4x1f32(pw, vb2[j], qacc[P + j], 0, 0, 0);
+                });
+            });
+            return;
+        }
 
         static_for<GT>([&](auto gg) {
             constexpr int gi = decltype(gg)::value;
@@ -395,11 +481,20 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
     // Two register sets take turns: while one step is consumed the loads of the next are in flight.  Without EXACT the step
     // count is rounded up to even; a surplus step sees only rows past the end (weights exactly zero).
     for (int it = 0; it < nit; it += 2) {
-        issue(rb);
         consume(ra, it);
         if (EXACT && it + 1 >= nit) break;
         issue(ra);
         consume(rb, it + 1);
+        issue(rb);
+    }
+
+    if constexpr (QUADS) {
+        static_for<GT>([&](auto gg) {
+            constexpr int gi = decltype(gg)::value;
+            m[gi] = quad_lane<gi>(qm);
+            lsum[gi] = quad_lane<gi>(qsum);
+            static_for<2 * P>([&](auto cc) { acc[gi][cc.value] = qacc[cc.value][gi]; });
+        });
     }
 
     // ---- combine the lane groups of the workgroup
@@ -410,7 +505,7 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
         mx = fold_from<LPR>(mx, Max{});
         if (lane == 0) xm[gi][wave] = mx;
     });
-    __syncthreads();
+    lds_barrier();
     static_for<GT>([&](auto gg) {
         constexpr int gi = decltype(gg)::value;
         float M = xm[gi][0];
@@ -435,7 +530,7 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
             });
         }
     });
-    __syncthreads();
+    lds_barrier();
 
     // 2. sum over the parked lane groups; two channels of one query head per thread and pass
     auto group_ml = [&](int gi, float* M, float* L) {
@@ -476,9 +571,10 @@ void k_attend_partial(const SlabTable tab, const AttGeom g, const T* __restrict_
 constexpr int kMergeShare = 4;
 template <typename T, int D>
 __global__ __launch_bounds__(kMergeShare * D / 2)
-void k_attend_merge(const AttGeom g, const float* __restrict__ part_acc, const float* __restrict__ part_ml,
+void k_attend_merge(const AttGeom, const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                     T* __restrict__ out, float* __restrict__ lse)
 {
+    const AttGeom g = first_argument<AttGeom, 2>();
     constexpr int NT = kMergeShare * D / 2, NWV = NT / 64;
     __shared__ float wm[NWV], wl[NWV], sh_w[NT];
     __shared__ f32x2 sh_sum[kMergeShare][D / 2];
@@ -555,8 +651,8 @@ static void launch_partial_o(const SlabTable& tab, const AttGeom& g, const void*
 {
     const long long chunks = (long long)g.units * g.n_split, parts = g.G / g.GT;
     const dim3 grid = chunks * parts < 1 << 23 ? dim3((unsigned)(chunks * parts)) : dim3((unsigned)chunks, (unsigned)parts);   // (a launch has up to 2^32 threads per direction)
-    hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE, EXACT>), grid, dim3(kWaves * 64), 0, st, tab, g, (const T*)q, rt,
-                       part_acc, part_ml, (T*)out, lse);
+    hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE, EXACT>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
+                       part_acc, part_ml, (T*)out, lse, tab);
 }
 
 template <typename T, int D, int GT>

@@ -22,6 +22,25 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, const void* base, uint32
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(offset), "s"(base) : "memory");
 }
 
+// The first of the kernel's arguments (an A), behind a fetch of the first LINES x 64 bytes of all of them, all lines at once.  Read where they
+// are used, one line after the other comes from memory at the start of a kernel, 600 to 900 cycles each: so kernels of a few
+// microseconds have their small arguments first, the table of slabs behind them, and take the first from here.
+template <class A, int LINES> __device__ __forceinline__ A first_argument()
+{
+    A a = {};
+#ifdef __HIP_DEVICE_COMPILE__
+    auto* args = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile(".set fetch_line, 0\n\t"
+                 ".rept %1\n\t"
+                 "s_load_dword s90, %0, fetch_line\n\t"
+                 ".set fetch_line, fetch_line + 64\n\t"
+                 ".endr\n\t"
+                 "s_waitcnt lgkmcnt(0)" : "+s"(args) : "n"(LINES) : "s90");
+    __builtin_memcpy(&a, (const __attribute__((address_space(4))) A*)args, sizeof(A));
+#endif
+    return a;
+}
+
 // One launch group addresses at most this many (layer, K|V) slabs; their base
 // pointers travel by value in the kernel arguments.
 constexpr int kMaxSlabs = 192;
