@@ -101,9 +101,10 @@ __global__ void k_prefill_cs(float2* __restrict__ cs, int rows, int d, double ba
 // come from the same two 16-byte loads.  Kr tile layout (fp16): [group of 8 channels g8 = 0..15][key 0..31][8].
 // Values: the 32 x 128 bf16 block is read row by row with 16-byte loads, turned through LDS, and written as the Vt tile.
 // Vt tile layout (fp16): [channel block db = 0..3][k-step t = 0..1][half-wave hw = 0..1][channel 0..31][8 keys].
-__global__ __launch_bounds__(256) void k_prefill_prep(const SlabTable tab, const PrefillGeom g, const float2* __restrict__ cs,
-                                                      _Float16* __restrict__ Kr, _Float16* __restrict__ Vt)
+__global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const float2* __restrict__ cs, _Float16* __restrict__ Kr,
+                                                      _Float16* __restrict__ Vt, const SlabTable tab)
 {
+    const PrefillGeom g = first_argument<PrefillGeom, 4>();  // and those up to the first layers' slabs
     __shared__ uint32_t sm[kKeyTile][kD / 2 + 1];             // [key][pair of channels], one word of padding per row
     constexpr int half = kD / 2, pgn = half / 8;              // groups of 8 pairs per row
     const int tile = blockIdx.x % g.key_tiles;
@@ -185,10 +186,11 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const SlabTable tab, const
 // times that of eight tasks (twice the copies).
 template <int HALVES>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
-void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,
+void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,
                       const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
                       float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml)
 {
+    const PrefillGeom g = first_argument<PrefillGeom, 3>();
     constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
     __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
     __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];   // (two halves: and the slots not yet used)
@@ -534,10 +536,11 @@ void k_attend_prefill(const PrefillGeom g, const _Float16* __restrict__ Kr, cons
 }
 
 // Merges the parts of the key range (n_split > 1): one workgroup per task, a wave per block of 32 channels, the same lane layout.
-__global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom g, const float* __restrict__ part_acc,
+__global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const float* __restrict__ part_acc,
                                                        const float2* __restrict__ part_ml, uint16_t* __restrict__ out,
                                                        float* __restrict__ lse)
 {
+    const PrefillGeom g = first_argument<PrefillGeom, 3>();
     const int tasks_per_unit = g.G * g.q_blocks;
     const int unit = blockIdx.x / tasks_per_unit, task = blockIdx.x - unit * tasks_per_unit;
     const int db = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, hw = lane >> 5;
@@ -590,7 +593,7 @@ hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, co
 {
     if (g.d != kD || g.cur_len < 1 || g.q_len < 1 || g.q_len > g.cur_len) return hipErrorInvalidValue;
     if (g.key_tiles * kKeyTile < g.cur_len || g.q_pad < g.q_len || g.q_pad % kQPerWave) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, tab, g, cs, Kr, Vt);
+    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, g, cs, Kr, Vt, tab);
     return hipGetLastError();
 }
 
