@@ -193,7 +193,8 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     const PrefillGeom g = first_argument<PrefillGeom, 3>();
     constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
     __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
-    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];   // (two halves: and the slots not yet used)
+    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];
+    __shared__ __attribute__((aligned(16))) char origins[HALVES == 1 ? kPrefillWaves * (kD / 2) * 8 : 16];   // (two halves: a slot not yet used)
 
     static_assert(kTileBytes % (TASKS * 64 * 16) == 0, "whole 16-byte pieces of a tile per thread");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: the loop bounds below are per wave
@@ -296,61 +297,100 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     // Copies past the last tile are not branched around: they repeat the last tile into a slot that nobody
     // reads any more, which keeps the loop free of branches.
     const int last_tile = (t1 > t0 ? t1 : wg_tiles) - 1;
-    static_for<3>([&](auto i) {
-        dma_k(min(t0 + i.value, last_tile), t0 + i.value);
-        dma_v(min(t0 + i.value, last_tile), t0 + i.value);
-    });
     // ---- queries of this wave: second operand of S^T = Kr Qr^T, lane = query column, 8 channels per k-step half.
-    // Qr = rotate(q at its in-cache position) * log2(e)/sqrt(d), computed here once per wave: the lane's groups
-    // of 8 channels in the lower half (k-steps 0..3) and their rotary partners in the upper half (k-steps 4..7) are
-    // in its registers together.  A lane wants 16 bytes here and there of a query's row and of its row of cos and sin: asked for
-    // like that, 64 lines to a load, the start of a workgroup took 7 us.  So rows come in whole, all of them in flight at once, and
-    // turn through 8 KB of LDS per wave, three times: 16 pieces of 16 bytes of 32 rows, piece p of row r in place p ^ (r & 15).
-    // Rows of the block beyond q_len are zero (another row is loaded for them).  A wave without a task asks for nothing: the loads of
-    // seven such waves held up the eighth by 1 us (1 query of 4 heads on 200 rows: 13.8 -> 12.0 us).
+    // Qr = rotate(q at its in-cache position) * log2(e)/sqrt(d), computed here once: the lane's groups of 8 channels in the lower half
+    // (k-steps 0..3) and their rotary partners in the upper half (k-steps 4..7) are in its registers together.  A lane wants 16 bytes
+    // here and there of a query's row: asked for like that, 64 lines to a load, the start of a workgroup took 7 us.  So rows come in
+    // whole, all of them in flight at once, and turn through LDS.  Rows of the block beyond q_len are zero (another row is loaded for
+    // them).  A wave without a task asks for no queries: the loads of seven such waves held up the eighth by 1 us.
+    // What then bounded the start was cos and sin, 16 KB of them per wave, twice its queries, through the 64 bytes per cycle of a compute unit
+    // (128 of 240 to 288 KB), and the turning of them.  The angle of query r of a block that begins at position p is that of p plus that of
+    // r: one row of the table per wave (scaled) and its rows 0..31 once per workgroup, in slots of the rings that no copy uses yet, and
+    // a complex product per pair in fp32, 1e-7 beside the 5e-4 of the operands' fp16.  The tiles are requested behind the queries, so that
+    // they come while these are rotated.  In halves, the two waves of a task take half of the k-steps each and swap them in LDS.
+    // Start of a workgroup in halves: 301 queries over 5001 rows 10400 -> 8250 cycles, 300 over 300 9940 -> 7460; in one stream, 4094 over
+    // 8192, 12800 -> 12600 (all the queries of 256 workgroups come from memory at once).
+    constexpr int NP = 16 / HALVES, NL = 8 / HALVES, NS = 4 / HALVES;   // pieces of 16 bytes of a row, loads, k-steps of the lower half, per wave
+    char* const turn = qsm[0] + (tw * HALVES + half) * (32 * NP * 16);  // 32 rows, piece i of row r in place i ^ (r & 15), in halves i ^ (r / 2 & 7)
+    char* const table = ring[0][0][(part0 + 3) & 3];                     // rows 0..15 in this slot of the keys, 16..31 in that of the values
+    constexpr int TABLE_HALF = (int)sizeof(ring[0][0]);
+    char* const origin = (HALVES == 1 ? origins : ring[HALVES - 1][0][(part0 + steps + 3) & 3]) + wave * (kD / 2) * 8;
+    {
+        u32x4 rt[2], x[NL];
+        float2 o = {0.f, 0.f};
+        const int rrow = 4 * wave + (lane >> 5), rpiece = lane & 31;
+        static_for<2>([&](auto i) {
+            rt[i.value] = *(const u32x4*)(cs + (long long)min(rrow + 2 * i.value, g.cur_len - 1) * (kD / 2) + rpiece * 2);
+        });
+        const int r0 = lane / NP, pi = lane % NP;
+        if (active) {
+            o = cs[(long long)pos0 * (kD / 2) + lane];
+            const int piece = HALVES == 1 ? pi : (pi & 3) + 4 * half + 8 * (pi >> 2);
+            const uint16_t* const qrows = q + (head * g.q_len + q0) * kD + piece * 8;
+            const int most = g.q_len - 1 - q0;                    // last row of the block that there is
+            static_for<NL>([&](auto j) { x[j.value] = *(const u32x4*)(qrows + (long long)min(64 / NP * j.value + r0, most) * kD); });
+        }
+        static_for<2>([&](auto i) {
+            const int row = rrow + 2 * i.value;
+            *(u32x4*)(table + (row >> 4) * TABLE_HALF + (row & 15) * 512 + (rpiece ^ (row & 15)) * 16) = rt[i.value];
+        });
+        if (active) {
+            *(float2*)(origin + lane * 8) = {o.x * g.qscale, o.y * g.qscale};
+            static_for<NL>([&](auto j) {
+                const int row = 64 / NP * j.value + r0;
+                *(u32x4*)(turn + row * (NP * 16) + (pi ^ (HALVES == 1 ? row & 15 : row >> 1 & 7)) * 16) = x[j.value];
+            });
+        }
+    }
+    __syncthreads();
+    static_for<3>([&](auto i) { dma_k(min(t0 + i.value, last_tile), t0 + i.value); });
+    static_for<3>([&](auto i) { dma_v(min(t0 + i.value, last_tile), t0 + i.value); });
     half8 qf[8];
     static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
     if (active) {
-        char* const turn = HALVES == 1 ? qsm[wave % TASKS] : tw < 2 ? ring[half][tw][(t0 + 3) & 3] : qsm[half * 2 + tw - 2];
-        const int r0 = lane >> 4, piece = lane & 15;
-        auto put = [&](auto j, u32x4 x) { *(u32x4*)(turn + (4 * j.value + r0) * 256 + ((piece ^ (4 * j.value + r0)) & 15) * 16) = x; };
-        auto get = [&](int pc) { return *(const u32x4*)(turn + l32 * 256 + ((pc ^ l32) & 15) * 16); };
-        const uint16_t* const qrows = q + (head * g.q_len + q0) * kD + piece * 8;
-        const float2* const crows = cs + (long long)pos0 * (kD / 2) + piece * 2;
-        const int most = g.q_len - 1 - q0;                    // last row of the block that there is
-        u32x4 x[8], c[2][8];
-        static_for<8>([&](auto j) { x[j.value] = *(const u32x4*)(qrows + (long long)min(4 * j.value + r0, most) * kD); });
-        static_for<2>([&](auto h) {
-            static_for<8>([&](auto j) { c[h.value][j.value] = *(const u32x4*)(crows + (long long)min(4 * j.value + r0, most) * (kD / 2) + h.value * 32); });
-        });
-        u32x4 lo[4], up[4];
-        static_for<8>([&](auto j) { put(j, x[j.value]); });
-        static_for<4>([&](auto s) { lo[s.value] = get(2 * s.value + hw); up[s.value] = get(8 + 2 * s.value + hw); });
-        static_for<2>([&](auto h) {
-            static_for<8>([&](auto j) { put(j, c[h.value][j.value]); });
-            static_for<2>([&](auto s) {
-                constexpr int S = 2 * h.value + s.value;
-                half8 lo8, up8;
-                static_for<4>([&](auto ec) {
-                    constexpr int E = decltype(ec)::value;
-                    const u32x4 w = get(8 * s.value + 4 * hw + E);
-                    const float2 c0 = {__uint_as_float(w[0]), __uint_as_float(w[1])}, c1 = {__uint_as_float(w[2]), __uint_as_float(w[3])};
-                    const float a0 = bf16_lo(lo[S][E]), a1 = bf16_hi(lo[S][E]);
-                    const float b0 = bf16_lo(up[S][E]), b1 = bf16_hi(up[S][E]);
-                    // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
-                    lo8[2 * E]     = (_Float16)((a0 * c0.x - b0 * c0.y) * g.qscale);
-                    lo8[2 * E + 1] = (_Float16)((a1 * c1.x - b1 * c1.y) * g.qscale);
-                    up8[2 * E]     = (_Float16)((b0 * c0.x + a0 * c0.y) * g.qscale);
-                    up8[2 * E + 1] = (_Float16)((b1 * c1.x + a1 * c1.y) * g.qscale);
-                });
-                qf[S] = lo8;
-                qf[S + 4] = up8;
+        auto get = [&](int i) { return *(const u32x4*)(turn + l32 * (NP * 16) + (i ^ (HALVES == 1 ? l32 & 15 : l32 >> 1 & 7)) * 16); };
+        const char* const torigin = origin + (HALVES == 1 ? 0 : half * 256) + hw * 64;
+        const char* const trow = table + (l32 >> 4) * TABLE_HALF + (l32 & 15) * 512 + (HALVES == 1 ? 0 : half * 256);
+        const int tswap = (4 * hw ^ (l32 & 15)) * 16;
+        u32x4 lo[NS], up[NS];
+        static_for<NS>([&](auto s) { lo[s.value] = get(2 * s.value + hw); up[s.value] = get(NP / 2 + 2 * s.value + hw); });
+        half8 mine[2 * NS];
+        const bool there = l32 < g.q_len - q0;
+        static_for<NS>([&](auto s) {
+            constexpr int S = decltype(s)::value;
+            half8 lo8 = {}, up8 = {};
+            static_for<4>([&](auto ec) {
+                constexpr int E = decltype(ec)::value;
+                const f32x4 w = *(const f32x4*)(trow + S / 2 * 256 + ((8 * (S % 2) + E) * 16 ^ tswap)), v = *(const f32x4*)(torigin + S * 128 + E * 16);
+                const float2 c0 = {v[0] * w[0] - v[1] * w[1], v[1] * w[0] + v[0] * w[1]}, c1 = {v[2] * w[2] - v[3] * w[3], v[3] * w[2] + v[2] * w[3]};
+                const float a0 = bf16_lo(lo[S][E]), a1 = bf16_hi(lo[S][E]);
+                const float b0 = bf16_lo(up[S][E]), b1 = bf16_hi(up[S][E]);
+                // lower half: x_j cos - x_{j+d/2} sin;  upper half: x_{j+d/2} cos + x_j sin
+                lo8[2 * E]     = (_Float16)(a0 * c0.x - b0 * c0.y);
+                lo8[2 * E + 1] = (_Float16)(a1 * c1.x - b1 * c1.y);
+                up8[2 * E]     = (_Float16)(b0 * c0.x + a0 * c0.y);
+                up8[2 * E + 1] = (_Float16)(b1 * c1.x + a1 * c1.y);
             });
+            mine[S] = there ? lo8 : half8{};
+            mine[NS + S] = there ? up8 : half8{};
         });
-        if (l32 > most) static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
+        if constexpr (HALVES == 1) {
+            static_for<8>([&](auto s8) { qf[s8.value] = mine[s8.value]; });
+        } else {
+            static_for<4>([&](auto i) { *(half8*)(turn + (i.value * 64 + lane) * 16) = mine[i.value]; });   // (the wave's own rows: it has read them)
+        }
     }
-    __builtin_amdgcn_s_waitcnt(0x0f70);                // all loads and copies have landed (in a form that the compiler takes into account)
+    // the keys of three tiles and the values of the first have landed, which is what the first step reads; it ends with all of them there
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (PIECE / 1024)) : "memory");
     __syncthreads();
+    if constexpr (HALVES == 2) {
+        if (active) {
+            static_for<8>([&](auto s8) {
+                constexpr int S = decltype(s8)::value % 4;
+                qf[s8.value] = *(const half8*)(qsm[0] + (tw * 2 + S / 2) * 4096 + ((s8.value / 4 * 2 + S % 2) * 64 + lane) * 16);
+            });
+        }
+    }
 
     half8 kf[8], vf[8];         // fragments of Kr(t+1) and Vt(t), read from LDS a few matrix instructions ahead
     auto read_k = [&](auto s8, const char* kt) { kf[s8.value] = *(const half8*)(kt + s8.value * (2 * kKeyTile * 16)); };
@@ -471,32 +511,43 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
 
     // ---- normalise and store: lane = query, registers = channels 8*(r/4) + 4*hw + r%4 of each block
     lsum += __shfl_xor(lsum, 32);
-    if constexpr (HALVES == 2) {
+    constexpr int NB = 4 / HALVES;                     // channel blocks that a wave finishes
+    f32x16 fin[NB];
+    if constexpr (HALVES == 1) {
+        static_for<4>([&](auto db) { fin[db.value] = acc[db.value]; });
+    } else {
+        // The two waves of a task finish two channel blocks each, and hand each other the rest.
         // (behind the last step's barrier nobody reads or copies into the rings any more)
-        f32x4* const meet = (f32x4*)(&ring[0][0][0][0] + tw * 18 * 1024) + lane;
-        float2* const meet_ml = (float2*)(&ring[0][0][0][0] + tw * 18 * 1024 + 16 * 1024) + lane;
-        if (half == 1) {
-            static_for<4>([&](auto db) {
+        char* const area = &ring[0][0][0][0] + tw * 18 * 1024;
+        float2* const ml = (float2*)(area + 16 * 1024) + lane;
+        auto give = [&](auto first) {                  // the partner's two blocks
+            static_for<2>([&](auto db) {
                 static_for<4>([&](auto r4) {
-                    constexpr int R = 4 * decltype(r4)::value;
-                    meet[(db.value * 4 + r4.value) * 64] = f32x4{acc[db.value][R], acc[db.value][R + 1], acc[db.value][R + 2], acc[db.value][R + 3]};
+                    constexpr int R = 4 * decltype(r4)::value, B = decltype(first)::value + decltype(db)::value;
+                    ((f32x4*)(area + half * 8192))[(db.value * 4 + r4.value) * 64 + lane] = f32x4{acc[B][R], acc[B][R + 1], acc[B][R + 2], acc[B][R + 3]};
                 });
             });
-            *meet_ml = {m, lsum};
+        };
+        if (half == 0) {
+            give(IC<2>{});
+            fin[0] = acc[0], fin[1] = acc[1];
+        } else {
+            give(IC<0>{});
+            fin[0] = acc[2], fin[1] = acc[3];
         }
+        ml[half * 64] = {m, lsum};
         __syncthreads();
-        if (half == 1) return;
-        const float2 o = *meet_ml;
+        const float2 o = ml[(1 - half) * 64];
         const float m0 = lsum > 0.f ? m : -1e30f, m1 = o.y > 0.f ? o.x : -1e30f, M = fmaxf(m0, m1);
         const float f0 = exp2_fast(m0 - M), f1 = exp2_fast(m1 - M);
         m = M;
         lsum = lsum * f0 + o.y * f1;
-        static_for<4>([&](auto db) {
+        static_for<2>([&](auto db) {
             static_for<4>([&](auto r4) {
-                const f32x4 x = meet[(db.value * 4 + r4.value) * 64];
+                const f32x4 x = ((const f32x4*)(area + (1 - half) * 8192))[(db.value * 4 + r4.value) * 64 + lane];
                 static_for<4>([&](auto i) {
                     constexpr int R = 4 * decltype(r4)::value + decltype(i)::value;
-                    acc[db.value][R] = acc[db.value][R] * f0 + x[i.value] * f1;
+                    fin[db.value][R] = fin[db.value][R] * f0 + x[i.value] * f1;
                 });
             });
         });
@@ -505,33 +556,40 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         // the state as it is, in the order of the registers (1 KB per store): [task][part][channel block][register / 4][lane][4]
         if (seen) {
             const long long st = ((long long)unit * tasks_per_unit + task) * g.n_split + split;
-            f32x4* o = (f32x4*)part_acc + st * (16 * 64) + lane;
-            static_for<4>([&](auto db) {
+            f32x4* o = (f32x4*)part_acc + st * (16 * 64) + half * (NB * 4 * 64) + lane;
+            static_for<NB>([&](auto db) {
                 static_for<4>([&](auto r4) {
                     constexpr int R = 4 * decltype(r4)::value;
-                    o[(db.value * 4 + r4.value) * 64] = f32x4{acc[db.value][R], acc[db.value][R + 1], acc[db.value][R + 2], acc[db.value][R + 3]};
+                    o[(db.value * 4 + r4.value) * 64] = f32x4{fin[db.value][R], fin[db.value][R + 1], fin[db.value][R + 2], fin[db.value][R + 3]};
                 });
             });
-            if (hw == 0) part_ml[st * 32 + l32] = {lsum > 0.f ? m : -1e30f, lsum};
+            if (half == 0 && hw == 0) part_ml[st * 32 + l32] = {lsum > 0.f ? m : -1e30f, lsum};
         }
         return;
     }
-    const int qi = q0 + l32;
-    if (active && qi < g.q_len) {
+    if (active) {
+        // The results turn in LDS, where the queries did, and leave as whole rows (in halves, as half rows): 8 bytes here and there of 32
+        // rows to a store, as the registers have them, took longer: end of a workgroup in halves (300 over 300) 6460 -> 3410 cycles, in one stream 5130 -> 2950.
         const float inv = 1.0f / lsum;
-        uint16_t* orow = out + (head * g.q_len + qi) * kD;
-        static_for<4>([&](auto db) {
+        static_for<NB>([&](auto db) {
             static_for<4>([&](auto r4) {
-                constexpr int R = 4 * decltype(r4)::value;
-                f32x2 a = {acc[db.value][R] * inv, acc[db.value][R + 1] * inv};
-                f32x2 b = {acc[db.value][R + 2] * inv, acc[db.value][R + 3] * inv};
+                constexpr int R = 4 * decltype(r4)::value, I = decltype(db)::value * 4 + decltype(r4)::value;
+                f32x2 a = {fin[db.value][R] * inv, fin[db.value][R + 1] * inv};
+                f32x2 b = {fin[db.value][R + 2] * inv, fin[db.value][R + 3] * inv};
                 u32x2 w;
                 w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2));
                 w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(b, bf16x2));
-                *(u32x2*)(orow + db.value * 32 + 8 * r4.value + 4 * hw) = w;
+                *(u32x2*)(turn + l32 * (NP * 16) + (I ^ (HALVES == 1 ? l32 & 15 : l32 >> 1 & 7)) * 16 + hw * 8) = w;
             });
         });
-        if (lse && hw == 0) lse[head * g.q_len + qi] = 0.6931471805599453f * (m + log2f(lsum));
+        const int r0 = lane / NP, pi = lane % NP;
+        uint16_t* const orow = out + (head * g.q_len + q0) * kD + half * (NB * 32) + pi * 8;
+        static_for<NL>([&](auto j) {
+            const int row = 64 / NP * j.value + r0;
+            const u32x4 w = *(const u32x4*)(turn + row * (NP * 16) + (pi ^ (HALVES == 1 ? row & 15 : row >> 1 & 7)) * 16);
+            if (q0 + row < g.q_len) *(u32x4*)(orow + (long long)row * kD) = w;
+        });
+        if (lse && half == 0 && hw == 0 && q0 + l32 < g.q_len) lse[head * g.q_len + q0 + l32] = 0.6931471805599453f * (m + log2f(lsum));
     }
 }
 
@@ -549,18 +607,29 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const 
     const int parts = ((last + kKeyTile) / kKeyTile + g.split_tiles - 1) / g.split_tiles;     // parts that some query of the task sees
     const long long st = (long long)blockIdx.x * g.n_split;
     float M = -1e30f, L = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < parts; ++s) M = fmaxf(M, part_ml[(st + s) * 32 + l32].x);
     f32x4 o[4] = {};
-#pragma unroll 4
-    for (int s = 0; s < parts; ++s) {
-        const float2 ml = part_ml[(st + s) * 32 + l32];
-        const float f = exp2_fast(ml.x - M);
-        L = fmaf(ml.y, f, L);
-        const f32x4* a = (const f32x4*)part_acc + (st + s) * (16 * 64) + db * (4 * 64) + lane;
-        static_for<4>([&](auto r4) {
-            const f32x4 x = a[r4.value * 64];
-            static_for<4>([&](auto i) { o[r4.value][i.value] = fmaf(x[i.value], f, o[r4.value][i.value]); });
+    // Four parts at a time, all their loads in flight (past the last part its own again, with weight 0): one after the other, three parts
+    // waited six times for memory.
+    for (int s = 0; s < parts; s += 4) {
+        float2 ml[4];
+        f32x4 x[4][4];
+        static_for<4>([&](auto i) { ml[i.value] = part_ml[(st + min(s + i.value, parts - 1)) * 32 + l32]; });
+        static_for<4>([&](auto i) {
+            const f32x4* a = (const f32x4*)part_acc + (st + min(s + i.value, parts - 1)) * (16 * 64) + db * (4 * 64) + lane;
+            static_for<4>([&](auto r4) { x[i.value][r4.value] = a[r4.value * 64]; });
+        });
+        float Mn = M;
+        static_for<4>([&](auto i) { Mn = fmaxf(Mn, ml[i.value].x); });
+        const float old = exp2_fast(M - Mn);
+        M = Mn;
+        L *= old;
+        static_for<4>([&](auto r4) { o[r4.value] *= old; });
+        static_for<4>([&](auto i) {
+            const float f = s + i.value < parts ? exp2_fast(ml[i.value].x - M) : 0.f;
+            L = fmaf(ml[i.value].y, f, L);
+            static_for<4>([&](auto r4) {
+                static_for<4>([&](auto e) { o[r4.value][e.value] = fmaf(x[i.value][r4.value][e.value], f, o[r4.value][e.value]); });
+            });
         });
     }
     const int qi = q0 + l32;
