@@ -131,6 +131,19 @@ template <int O, class F> __device__ __forceinline__ float fold(float x, F&& op)
         return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
     }
 }
+// Sums of two values over lanes O apart: the lanes without O in their index get that of x, the others that of y.
+template <int O> __device__ __forceinline__ float fold_two(float x, float y, [[maybe_unused]] int lane)
+{
+    if constexpr (O == 8) {
+        const bool upper = lane & 8;
+        return (upper ? y : x) + dpp<0x128>(upper ? x : y);
+    } else {
+        static_assert(O == 16 || O == 32);
+        const auto s = O == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false)
+                               : __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+}
 // ... over the lanes O, 2 O, ... 32 apart
 template <int O, class F> __device__ __forceinline__ float fold_from(float x, F&& op)
 {
@@ -228,16 +241,17 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     constexpr int RPW = 64 / LPR;          // rows per wave per load
     constexpr int STEP = kWaves * RPW;     // rows between two consecutive rows of one lane group
     constexpr int U = kUnroll;
+    constexpr bool QUADS = GT == 4;        // see the main loop
     constexpr int HSLOTS = kWaves * RPW / 2;
     typedef Raw<T, P> RawT;
 
     __shared__ float red[HSLOTS * GT * D];
-    __shared__ float xm[GT][kWaves];
+    __shared__ __attribute__((aligned(16))) float xm[GT][kWaves];
     __shared__ float xl[GT][kWaves];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = lane % LPR;
     const int slot = lane / LPR;
 
@@ -302,7 +316,9 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         });
         next_off += (uint32_t)(U * STEP) * row_bytes;
     };
-    // Frequencies and queries, then the rows of the first two steps, all requested together ahead of the seeds: loads come back in order.
+    // Frequencies and queries, then the rows of the first step or (QUADS) two, all requested together ahead of the seeds: loads come back in
+    // order.  (With 1 or 2 heads more workgroups share a compute unit, and a step less in flight is faster: 32 x
+    // 4096 rows of 1 head 16.9 -> 16.0 us, 16 x 4096 of 2 12.6 -> 12.1, 32 x 1000 of 1 9.9 -> 9.3.)
     // (Left alone the compiler puts the rows behind the seeds.)
     RopeEntry re[P];
     RawT qrl[GT], qrh[GT];
@@ -314,7 +330,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     });
     Rows ra, rb;
     issue(ra);
-    issue(rb);
+    if constexpr (QUADS) issue(rb);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- rotary state of the P pairs this lane owns: pair j couples channels P*l+j and D/2+P*l+j.
@@ -361,7 +377,6 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     // of them with every lane working out all heads, four exponentials at a quarter of the rate among them, and takes 280, so that rows are
     // what it waits for (1 x 8 KV heads x 6147 rows 14.4 -> 13.2 us per call, with the arguments and the last barrier 12.5; x 16000 20.9 -> 17.9; 32 layers
     // x 8 x 4000 rows with 8 query heads each 152 -> 138).
-    constexpr bool QUADS = GT == 4;
     typedef float Acc4 __attribute__((ext_vector_type(4)));
     [[maybe_unused]] float qm = kMinusBig, qsum = 0.f;   // of the lane's head
     [[maybe_unused]] Acc4 qacc[2 * P];                   // [channel][head]
@@ -481,54 +496,60 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     // Two register sets take turns: while one step is consumed the loads of the next are in flight.  Without EXACT the step
     // count is rounded up to even; a surplus step sees only rows past the end (weights exactly zero).
     for (int it = 0; it < nit; it += 2) {
+        if constexpr (!QUADS) issue(rb);
         consume(ra, it);
         if (EXACT && it + 1 >= nit) break;
         issue(ra);
         consume(rb, it + 1);
-        issue(rb);
-    }
-
-    if constexpr (QUADS) {
-        static_for<GT>([&](auto gg) {
-            constexpr int gi = decltype(gg)::value;
-            m[gi] = quad_lane<gi>(qm);
-            lsum[gi] = quad_lane<gi>(qsum);
-            static_for<2 * P>([&](auto cc) { acc[gi][cc.value] = qacc[cc.value][gi]; });
-        });
+        if constexpr (QUADS) issue(rb);
     }
 
     // ---- combine the lane groups of the workgroup
-    // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS
-    static_for<GT>([&](auto gg) {
-        constexpr int gi = decltype(gg)::value;
-        float mx = m[gi];
-        mx = fold_from<LPR>(mx, Max{});
-        if (lane == 0) xm[gi][wave] = mx;
-    });
-    lds_barrier();
-    static_for<GT>([&](auto gg) {
-        constexpr int gi = decltype(gg)::value;
-        float M = xm[gi][0];
-        static_for<kWaves - 1>([&](auto w) { M = fmaxf(M, xm[gi][w.value + 1]); });
-        float f = exp2_fast(m[gi] - M);
-        m[gi] = M;
-        float ls = lsum[gi] * f;
-        ls = fold_from<LPR>(ls, Add{});
-        if (lane == 0) xl[gi][wave] = ls;
-        // rescale, fold the neighbouring lane group in, park the even groups' sums in LDS
-        static_for<2 * P>([&](auto cc) {
-            constexpr int ci = decltype(cc)::value;
-            acc[gi][ci] = fold<LPR>(acc[gi][ci] * f, Add{});
+    // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS; then sums, and accumulators
+    // rescaled.  (Four heads: still one to a lane of each quad, so once for all four.)
+    // (the lane's index is counted again: kept across the loop with what derives from it, it would not fit the registers of the longest kernel)
+    uint32_t none = 0;
+    asm volatile("" : "+v"(none));
+    const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
+    float scale[GT];
+    if constexpr (QUADS) {
+        const float mx = fold_from<LPR>(qm, Max{});
+        if (ln < 4) xm[ln][wave] = mx;
+        lds_barrier();
+        const f32x4 of_waves = *(const f32x4*)xm[ln & 3];
+        const float f = exp2_fast(qm - fmaxf(fmaxf(of_waves[0], of_waves[1]), fmaxf(of_waves[2], of_waves[3])));
+        const float ls = fold_from<LPR>(qsum * f, Add{});
+        if (ln < 4) xl[ln][wave] = ls;
+        static_for<GT>([&](auto gg) { scale[gg.value] = quad_lane<gg.value>(f); });
+    } else {
+        static_for<GT>([&](auto gg) {
+            constexpr int gi = decltype(gg)::value;
+            const float mx = fold_from<LPR>(m[gi], Max{});
+            if (ln == 0) xm[gi][wave] = mx;
         });
-        if ((slot & 1) == 0) {
-            float* dst = red + ((wave * (RPW / 2) + (slot >> 1)) * GT + gi) * D;
-            static_for<P / 4>([&](auto qq) {
-                constexpr int o = 4 * decltype(qq)::value;
-                *(f32x4*)(dst + P * l + o) = f32x4{acc[gi][o], acc[gi][o + 1], acc[gi][o + 2], acc[gi][o + 3]};
-                *(f32x4*)(dst + D / 2 + P * l + o) =
-                    f32x4{acc[gi][P + o], acc[gi][P + o + 1], acc[gi][P + o + 2], acc[gi][P + o + 3]};
-            });
-        }
+        lds_barrier();
+        static_for<GT>([&](auto gg) {
+            constexpr int gi = decltype(gg)::value;
+            float M = xm[gi][0];
+            static_for<kWaves - 1>([&](auto w) { M = fmaxf(M, xm[gi][w.value + 1]); });
+            const float f = exp2_fast(m[gi] - M);
+            const float ls = fold_from<LPR>(lsum[gi] * f, Add{});
+            if (ln == 0) xl[gi][wave] = ls;
+            scale[gi] = f;
+        });
+    }
+    // Two neighbouring lane groups are folded into one, the even one keeping the lower half of the channels and the odd one the upper,
+    // and park their sums in LDS.  (With the reference points and sums of four heads worked out at once, where every lane used to do all of
+    // them and the swaps folded each value for both groups: 64 rows of 8 KV heads 6.4 -> 5.8 us, 300 9.0 -> 8.4, 6147 13.3 -> 13.0.)
+    static_assert(P == 4);
+    static_for<GT>([&](auto gg) {
+        constexpr int gi = decltype(gg)::value;
+        f32x4 sum;
+        static_for<P>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            sum[j] = fold_two<LPR>((QUADS ? qacc[j][gi] : acc[gi][j]) * scale[gi], (QUADS ? qacc[P + j][gi] : acc[gi][P + j]) * scale[gi], ln);
+        });
+        *(f32x4*)(red + ((wave * (RPW / 2) + (ln / LPR >> 1)) * GT + gi) * D + (ln / LPR & 1) * (D / 2) + P * (ln % LPR)) = sum;
     });
     lds_barrier();
 
@@ -540,7 +561,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     };
     const long long head0 = (long long)unit * g.G + g0;                        // dense query head of gi = 0
     const long long pidx = head0 * g.n_split + split;                          // + gi * n_split below
-    for (int idx = tid; idx < GT * D / 2; idx += kWaves * 64) {
+    for (int idx = tid_end; idx < GT * D / 2; idx += kWaves * 64) {
         const int gi = idx / (D / 2), ch = 2 * (idx - gi * (D / 2));
         f32x2 sum = {0.f, 0.f};
 #pragma unroll
@@ -553,12 +574,12 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
             *(f32x2*)(part_acc + (pidx + (long long)gi * g.n_split) * D + ch) = sum;
         }
     }
-    if (tid < GT) {
+    if (tid_end < GT) {
         float M, L;
-        group_ml(tid, &M, &L);
-        f32x2* ml = (f32x2*)(part_ml + (pidx + (long long)tid * g.n_split) * 2);
+        group_ml(tid_end, &M, &L);
+        f32x2* ml = (f32x2*)(part_ml + (pidx + (long long)tid_end * g.n_split) * 2);
         if constexpr (ONE) {
-            if (lse) lse[head0 + tid] = 0.6931471805599453f * (M + log2f(L));
+            if (lse) lse[head0 + tid_end] = 0.6931471805599453f * (M + log2f(L));
         } else {
             *ml = f32x2{M, L};
         }
