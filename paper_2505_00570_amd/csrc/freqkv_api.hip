@@ -382,21 +382,24 @@ freqkv_status_t get_nf_tables(const Shape& sh, int rescale, hipStream_t st, cons
 
 // ---------------------------------------------------------------- attention: shape, plan, rotary table
 // Row chunks per KV head.  All workgroups of a launch are resident at once (up to 3 or 4 per compute unit), so what counts is
-// how many sit on the busiest of the 256 compute units.  Measured (bf16, d = 128, 4 query heads per workgroup): one
-// workgroup alone on its compute unit takes 0.0239 us per row, several of them 0.020 each; 0.013 with 2 heads, 0.0095 with
-// 1, in proportion to d; a workgroup's set-up adds 1 us for each on the compute unit, merging 1.5 us and 0.04 for each
-// chunk; nothing runs faster than the rows come from memory (6 TB/s).  Tried are the chunk counts that fill 1, 2, 3 or 4
-// workgroups per compute unit; the fewest chunks within 1 us of the best are taken.  8 KV heads x 6147 rows: 28 chunks 15.1
-// us (22 chunks 16.5, 16 19.5); 128 x 8192: 4 chunks 86 us (6: 97); 32 heads of 1 query head x 4096: 8 chunks 16.1 us (22: 17.5).
+// how many sit on the busiest of the 256 compute units.  The constants rank the cuts (they are what a row took before the softmax by quads:
+// 0.0239 us alone on a compute unit, several workgroups 0.020 each, now 0.017 alone; 0.013 with 2 heads, 0.0095 with 1, in proportion to d; a
+// workgroup's set-up 1 us for each on the compute unit, merging 1.5 us and 0.04 per chunk; nothing faster than rows come from memory, 6
+// TB/s); in a sweep of 45 shapes they pick the best cut or one within 3 %.  Tried are the counts that fill a quarter, a half, 1, 2, 3 or 4
+// workgroups per compute unit; the fewest chunks within 1 us of the best are taken.  8 KV heads x 6147 rows: 28 chunks 13.3 us (22: 14.2, 15:
+// 16.2, 39: 16.1); 128 x 8000: 4 chunks 100 us (1: 153); 32 heads of 1 query head x 4096: 8 chunks 16.6 us (4: 18.7, 22: 18.0).  The quarter
+// and the half are for few KV heads, of whose chunks the merging is the larger part: 1 x 8000 rows 250 chunks 16.5 -> 63 10.9 us, 1 x
+// 16000 of d = 64 13.6 -> 9.3, 2 x 8000 125 13.8 -> 63 11.5.
 int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int rows, int min_rows)
 {
-    constexpr int kCus = 256, kMost = 4;
+    constexpr int kCus = 256, kCuts = 7;
+    constexpr double kFill[kCuts] = {0.0, 0.25, 0.5, 1.0, 2.0, 3.0, 4.0};
     const double per_row = (GT == 4 ? 0.0239 : GT == 2 ? 0.013 : 0.0095) * d / 128.0 * (elem == 4 ? 1.3 : 1.0);
     const double floor_us = 2.0 * units * rows * d * elem / 6e6;
-    int ns_of[kMost + 1];
-    double cost[kMost + 1], best = 1e30;
-    for (int r = 0; r <= kMost; ++r) {
-        long long ns = r ? (long long)kCus * r / wgs : 1;
+    int ns_of[kCuts];
+    double cost[kCuts], best = 1e30;
+    for (int r = 0; r < kCuts; ++r) {
+        long long ns = (long long)(kCus * kFill[r]) / wgs;
         if (ns > rows / min_rows) ns = rows / min_rows;
         if (ns < 1) ns = 1;
         const double chunk = (double)rows / ns;
@@ -409,7 +412,7 @@ int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int r
         cost[r] = us + deep + (ns > 1 ? 1.5 + 0.04 * ns : 0.0);
         if (cost[r] < best) best = cost[r];
     }
-    for (int r = 0; r <= kMost; ++r)
+    for (int r = 0; r < kCuts; ++r)
         if (cost[r] <= best + 1.0) return ns_of[r];
     return 1;
 }
