@@ -74,7 +74,8 @@ __host__ __device__ inline int tile_slot(const NfGeom& g, int t)
 }
 // Are the moments' tables the same for all leaves but the last?  cos(Lc b_j) is cos(phase of the leaf + angle within it), so the cosines and
 // sines of the angles within a leaf do for all, and the moments are their products' sum with the phase's cosine and (negative) sine.
-__host__ __device__ inline bool phased(const NfGeom& g) { return g.NK == 2 && !g.shifts; }
+// (Not for spans of up to 3 blocks: the second product costs more than the tables' way does, 251 -> 125 rows of 1728 head-tensors 75.5 -> 78.3 us.)
+__host__ __device__ inline bool phased(const NfGeom& g) { return g.NK == 2 && !g.shifts && g.NC > g.NB; }
 // First block of the neighbourhood that group gr treats leaf by leaf.
 __host__ __device__ inline int group_block0(const NfGeom& g, int gr)
 {
@@ -540,7 +541,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     // table per leaf, requested a step ahead, comes back behind the copies of all the leaves that are in flight, so that the ring did
     // little to hide their way: 6083 -> 3041 of 128 head-tensors 50 000 -> 40 000 cycles for the first reading, 122.6 -> 120.9 us; 4092 -> 2455 of 512
     // 342 -> 336; the errors are the same to four digits.  For windows of 3 leaves there are no registers left.)
-    constexpr bool PHASED = NK == 2 && !SHIFTS;
+    constexpr bool PHASED = NK == 2 && !SHIFTS && !ALL_NEAR;
     bf16x8 vt[4], vs[PHASED ? 4 : 1];                // moments of the wave's next leaf (PHASED: of the last leaf)
     auto fetch_moments = [&](int leaf) {
         const int off = g.off_v + (PHASED ? 2 : SHIFTS ? (leaf == g.NL - 1) : leaf) * 4 * kFrag;
