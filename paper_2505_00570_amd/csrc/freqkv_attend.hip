@@ -236,7 +236,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
                       const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
                       float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
-    const AttGeom g = first_argument<AttGeom, 4>();      // and those up to the first layers' slabs
+    const AttGeom g = first_argument<decltype(k_attend_partial<T, D, GT, P, ONE, EXACT>)>();
     constexpr int LPR = D / (2 * P);       // lanes per cache row
     constexpr int RPW = 64 / LPR;          // rows per wave per load
     constexpr int STEP = kWaves * RPW;     // rows between two consecutive rows of one lane group
@@ -463,7 +463,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
             return;
         }
 
-        static_for<GT>([&](auto gg) {
+        static_for<QUADS ? 0 : GT>([&](auto gg) {
             constexpr int gi = decltype(gg)::value;
             // The reference point m of the running softmax only moves when a score exceeds it by more than
             // 2^kSlack; until then weights up to 2^kSlack are accumulated as they are (any reference point
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(kMergeShare * D / 2)
 void k_attend_merge(const AttGeom, const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                     T* __restrict__ out, float* __restrict__ lse)
 {
-    const AttGeom g = first_argument<AttGeom, 2>();
+    const AttGeom g = first_argument<decltype(k_attend_merge<T, D>)>();
     constexpr int NT = kMergeShare * D / 2, NWV = NT / 64;
     __shared__ float wm[NWV], wl[NWV], sh_w[NT];
     __shared__ f32x2 sh_sum[kMergeShare][D / 2];

@@ -22,11 +22,22 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, const void* base, uint32
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(offset), "s"(base) : "memory");
 }
 
-// The first of the kernel's arguments (an A), behind a fetch of the first LINES x 64 bytes of all of them, all lines at once.  Read where they
-// are used, one line after the other comes from memory at the start of a kernel, 600 to 900 cycles each: so kernels of a few
-// microseconds have their small arguments first, the table of slabs behind them, and take the first from here.
-template <class A, int LINES> __device__ __forceinline__ A first_argument()
+// What a kernel's arguments take, from its type.
+template <class Kernel> struct Arguments;
+template <class A, class... More> struct Arguments<void(A, More...)> {
+    static_assert(sizeof(A) % 8 == 0 && ((sizeof(More) % 8 == 0) && ...), "sizes add up without gaps");
+    typedef A First;
+    static constexpr int bytes = (int)(sizeof(A) + (sizeof(More) + ... + 0));
+};
+
+// The kernel's first argument, behind a fetch of the cache lines that hold its arguments (the first 256 bytes of them), all lines at once.  Read
+// where they are used, one line after the other comes from memory at the start of a kernel, 600 to 900 cycles each: so kernels of a few
+// microseconds have their small arguments first, the table of slabs behind them, and take the first from here.  A line is touched at its
+// start, which has to lie within the arguments: hence their size from the kernel's type.
+template <class Kernel> __device__ __forceinline__ typename Arguments<Kernel>::First first_argument()
 {
+    typedef typename Arguments<Kernel>::First A;
+    constexpr int bytes = Arguments<Kernel>::bytes, lines = ((bytes < 256 ? bytes : 256) + 63) / 64;
     A a = {};
 #ifdef __HIP_DEVICE_COMPILE__
     auto* args = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -35,7 +46,7 @@ template <class A, int LINES> __device__ __forceinline__ A first_argument()
                  "s_load_dword s90, %0, fetch_line\n\t"
                  ".set fetch_line, fetch_line + 64\n\t"
                  ".endr\n\t"
-                 "s_waitcnt lgkmcnt(0)" : "+s"(args) : "n"(LINES) : "s90");
+                 "s_waitcnt lgkmcnt(0)" : "+s"(args) : "n"(lines) : "s90");
     __builtin_memcpy(&a, (const __attribute__((address_space(4))) A*)args, sizeof(A));
 #endif
     return a;

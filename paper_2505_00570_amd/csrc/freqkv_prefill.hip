@@ -104,7 +104,7 @@ __global__ void k_prefill_cs(float2* __restrict__ cs, int rows, int d, double ba
 __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const float2* __restrict__ cs, _Float16* __restrict__ Kr,
                                                       _Float16* __restrict__ Vt, const SlabTable tab)
 {
-    const PrefillGeom g = first_argument<PrefillGeom, 4>();  // and those up to the first layers' slabs
+    const PrefillGeom g = first_argument<decltype(k_prefill_prep)>();
     __shared__ uint32_t sm[kKeyTile][kD / 2 + 1];             // [key][pair of channels], one word of padding per row
     constexpr int half = kD / 2, pgn = half / 8;              // groups of 8 pairs per row
     const int tile = blockIdx.x % g.key_tiles;
@@ -190,7 +190,7 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
                       const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
                       float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml)
 {
-    const PrefillGeom g = first_argument<PrefillGeom, 3>();
+    const PrefillGeom g = first_argument<decltype(k_attend_prefill<HALVES>)>();
     constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
     __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
     __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const 
                                                        const float2* __restrict__ part_ml, uint16_t* __restrict__ out,
                                                        float* __restrict__ lse)
 {
-    const PrefillGeom g = first_argument<PrefillGeom, 3>();
+    const PrefillGeom g = first_argument<decltype(k_prefill_merge)>();
     const int tasks_per_unit = g.G * g.q_blocks;
     const int unit = blockIdx.x / tasks_per_unit, task = blockIdx.x - unit * tasks_per_unit;
     const int db = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, hw = lane >> 5;
