@@ -29,11 +29,11 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * (5.244e5 + 9.187e5) + 1.0 * (2.62e5 + 5.24e5)) * 1024}
 TRAFFIC_BYTES_SINGLE_FOLD = {"llama3_8b_128k": (2.0 * 2.622e6 + 1.0 * 5.24e5) * 1024}
 # the same for the near/far form's single kernel (profiles/compress_llama3_8b_128k_pmc.txt)
-NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.635e5 + 1.0 * 5.24e5) * 1024}
+NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.286e5 + 1.0 * 5.24e5) * 1024}
 # the same for k_attend_partial (profiles/attend_llama3_8b_128k_pmc.txt)
-ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.267e5 + 1.0 * 1056) * 1024}
+ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.288e5 + 1.0 * 1056) * 1024}
 # the same for k_attend_prefill (profiles/prefill_llama3_8b_128k.txt)
-PREFILL_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 1.705e6 + 1.0 * 1.049e6) * 1024}
+PREFILL_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 1.448e6 + 1.0 * 1.049e6) * 1024}
 
 
 def cpu_baseline(wl, k_cache, cores):
