@@ -608,7 +608,7 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const 
     const long long st = (long long)blockIdx.x * g.n_split;
     float M = -1e30f, L = 0.f;
     f32x4 o[4] = {};
-    // Four parts at a time, all their loads in flight (past the last part its own again, with weight 0): one after the other, three parts
+    // Four parts at a time, all their loads in flight (past the last part its own again, and then not used): one after the other, three parts
     // waited six times for memory.
     for (int s = 0; s < parts; s += 4) {
         float2 ml[4];
@@ -618,6 +618,7 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const 
             const f32x4* a = (const f32x4*)part_acc + (st + min(s + i.value, parts - 1)) * (16 * 64) + db * (4 * 64) + lane;
             static_for<4>([&](auto r4) { x[i.value][r4.value] = a[r4.value * 64]; });
         });
+        __builtin_amdgcn_sched_barrier(0);                            // (left alone the compiler has four to six of them in flight)
         float Mn = M;
         static_for<4>([&](auto i) { Mn = fmaxf(Mn, ml[i.value].x); });
         const float old = exp2_fast(M - Mn);
@@ -625,10 +626,15 @@ __global__ __launch_bounds__(256) void k_prefill_merge(const PrefillGeom, const 
         L *= old;
         static_for<4>([&](auto r4) { o[r4.value] *= old; });
         static_for<4>([&](auto i) {
-            const float f = s + i.value < parts ? exp2_fast(ml[i.value].x - M) : 0.f;
-            L = fmaf(ml[i.value].y, f, L);
+            // (not by a weight of 0, which would make an infinite sum NaN)
+            const bool there = s + i.value < parts;
+            const float f = exp2_fast(ml[i.value].x - M);
+            L = there ? fmaf(ml[i.value].y, f, L) : L;
             static_for<4>([&](auto r4) {
-                static_for<4>([&](auto e) { o[r4.value][e.value] = fmaf(x[i.value][r4.value][e.value], f, o[r4.value][e.value]); });
+                static_for<4>([&](auto e) {
+                    const float sum = fmaf(x[i.value][r4.value][e.value], f, o[r4.value][e.value]);
+                    o[r4.value][e.value] = there ? sum : o[r4.value][e.value];
+                });
             });
         });
     }
