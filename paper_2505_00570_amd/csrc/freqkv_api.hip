@@ -3,6 +3,7 @@
 #include "freqkv.h"
 #include "freqkv_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -382,38 +383,42 @@ freqkv_status_t get_nf_tables(const Shape& sh, int rescale, hipStream_t st, cons
 
 // ---------------------------------------------------------------- attention: shape, plan, rotary table
 // Row chunks per KV head.  All workgroups of a launch are resident at once (up to 3 or 4 per compute unit), so what counts is
-// how many sit on the busiest of the 256 compute units.  The constants rank the cuts (they are what a row took before the softmax by quads:
-// 0.0239 us alone on a compute unit, several workgroups 0.020 each, now 0.017 alone; 0.013 with 2 heads, 0.0095 with 1, in proportion to d; a
-// workgroup's set-up 1 us for each on the compute unit, merging 1.5 us and 0.04 per chunk; nothing faster than rows come from memory, 6
-// TB/s); in a sweep of 45 shapes they pick the best cut or one within 3 %.  Tried are the counts that fill a quarter, a half, 1, 2, 3 or 4
-// workgroups per compute unit; the fewest chunks within 1 us of the best are taken.  8 KV heads x 6147 rows: 28 chunks 13.3 us (22: 14.2, 15:
-// 16.2, 39: 16.1); 128 x 8000: 4 chunks 100 us (1: 153); 32 heads of 1 query head x 4096: 8 chunks 16.6 us (4: 18.7, 22: 18.0).  The quarter
-// and the half are for few KV heads, of whose chunks the merging is the larger part: 1 x 8000 rows 250 chunks 16.5 -> 63 10.9 us, 1 x
-// 16000 of d = 64 13.6 -> 9.3, 2 x 8000 125 13.8 -> 63 11.5.
+// how many sit on the busiest of the 256 compute units.  The constants rank the cuts, they are no times of the present kernel (0.0239 us per row alone on a
+// compute unit, several workgroups 0.020 each, is what it took with every lane working out the softmax of all heads; 0.013 with 2 heads, 0.0095 with
+// 1, in proportion to d; a workgroup's set-up 1 us for each on the compute unit, merging 1.5 us and 0.04 per chunk; nothing faster than rows
+// come from memory, 6 TB/s).  Tried are the counts that fill 1, 2, 3 or 4 workgroups per compute unit; the fewest chunks within 1 us of the
+// best are taken.  (8 KV heads x 6147 rows: 28 chunks 11.4 us of device time, 22: 12.3, 15: 14.6, 33: 14.6.)
+// Few KV heads over long caches would have up to 256 chunks each, and the merge reads 32 of them at a time: 64 and 128 are tried too where
+// the compute units would take more than half as many again (1 KV head x 8000 rows 250 chunks 14.9 us, 63 10.1; 2 x 8192 of d = 64
+// 128 10.0, 64 8.2; 1 x 16000 of d = 256 250 17.5, 125 15.6).  With fewer than that, leaving compute units idle takes longer than
+// the chunks that it saves: a quarter or half of them 12 x 1500 rows of d = 64 12 chunks 7.2, 5 8.6; 8 x 8000 of d = 64 32 8.6, 16 10.1; 24 x 300 5
+// 7.2, 2 8.5; 3 x 16357 74 12.2, 40 13.8.  Over 230 other shapes 1.2 % above the best cut with rows from HBM, 15 % at worst (1.8 % and 20 % with
+// a quarter and half of the compute units for all, 1.6 % and 20 % with neither): profiles/decode_chunks.txt.
 int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int rows, int min_rows)
 {
     constexpr int kCus = 256, kCuts = 7;
-    constexpr double kFill[kCuts] = {0.0, 0.25, 0.5, 1.0, 2.0, 3.0, 4.0};
     const double per_row = (GT == 4 ? 0.0239 : GT == 2 ? 0.013 : 0.0095) * d / 128.0 * (elem == 4 ? 1.3 : 1.0);
     const double floor_us = 2.0 * units * rows * d * elem / 6e6;
-    int ns_of[kCuts];
+    auto filling = [&](int per_cu) -> long long {
+        const long long ns = std::min((long long)kCus * per_cu / wgs, (long long)rows / min_rows);
+        return ns < 1 ? 1 : ns;
+    };
+    const long long full = filling(1);
+    const long long cuts[kCuts] = {1, 2 * full > 3 * 64 ? 64 : full, 2 * full > 3 * 128 ? 128 : full, full, filling(2), filling(3), filling(4)};
     double cost[kCuts], best = 1e30;
     for (int r = 0; r < kCuts; ++r) {
-        long long ns = (long long)(kCus * kFill[r]) / wgs;
-        if (ns > rows / min_rows) ns = rows / min_rows;
-        if (ns < 1) ns = 1;
+        const long long ns = cuts[r];
         const double chunk = (double)rows / ns;
         const double deep = std::ceil((double)wgs * ns / kCus);
         double us = chunk * deep * per_row * (deep > 1 ? 0.83 : 1.0);
         // compute units with fewer workgroups than the busiest leave half of their share of the bandwidth unused
         const double least = floor_us * (0.5 + 0.5 * deep * kCus / ((double)wgs * ns));
         if (us < least) us = least;
-        ns_of[r] = (int)ns;
         cost[r] = us + deep + (ns > 1 ? 1.5 + 0.04 * ns : 0.0);
         if (cost[r] < best) best = cost[r];
     }
     for (int r = 0; r < kCuts; ++r)
-        if (cost[r] <= best + 1.0) return ns_of[r];
+        if (cost[r] <= best + 1.0) return (int)cuts[r];
     return 1;
 }
 
