@@ -967,8 +967,8 @@ template <class F> static void with_slabs(const SlabTable& tab, const Geom& g, F
 {
     const int slabs = g.ncols / (g.hts_per_slab * g.d);
     if (slabs <= kFewSlabs) {
-        FewSlabs few;
-        for (int i = 0; i < kFewSlabs; ++i) few.base[i] = tab.base[i];
+        FewSlabs few = {};
+        for (int i = 0; i < slabs; ++i) few.base[i] = tab.base[i];        // (the table holds no more)
         f(few);
     } else {
         f(tab);
