@@ -193,8 +193,9 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     const PrefillGeom g = first_argument<decltype(k_attend_prefill<HALVES>)>();
     constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
     __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
-    __shared__ __attribute__((aligned(1024))) char qsm[kPrefillWaves / HALVES][32 * 256];
-    __shared__ __attribute__((aligned(16))) char origins[HALVES == 1 ? kPrefillWaves * (kD / 2) * 8 : 16];   // (two halves: a slot not yet used)
+    constexpr int QUERIES = 32 * kD * 2, ORIGIN = HALVES == 1 ? (kD / 2) * 8 : 0;
+    __shared__ __attribute__((aligned(1024))) char qsm[TASKS][QUERIES + ORIGIN];     // of each task: its queries, and the angles at its first one (in halves: those in a slot not yet used)
+    static_assert(sizeof(ring) + sizeof(qsm) <= 160 * 1024, "a compute unit's LDS, all of it in halves");
 
     static_assert(kTileBytes % (TASKS * 64 * 16) == 0, "whole 16-byte pieces of a tile per thread");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: the loop bounds below are per wave
@@ -311,10 +312,10 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     // Start of a workgroup in halves: 301 queries over 5001 rows 10400 -> 8250 cycles, 300 over 300 9940 -> 7460; in one stream, 4094 over
     // 8192, 12800 -> 12600 (all the queries of 256 workgroups come from memory at once).
     constexpr int NP = 16 / HALVES, NL = 8 / HALVES, NS = 4 / HALVES;   // pieces of 16 bytes of a row, loads, k-steps of the lower half, per wave
-    char* const turn = qsm[0] + (tw * HALVES + half) * (32 * NP * 16);  // 32 rows, piece i of row r in place i ^ (r & 15), in halves i ^ (r / 2 & 7)
+    char* const turn = qsm[tw] + half * (32 * NP * 16);                  // 32 rows, piece i of row r in place i ^ (r & 15), in halves i ^ (r / 2 & 7)
     char* const table = ring[0][0][(part0 + 3) & 3];                     // rows 0..15 in this slot of the keys, 16..31 in that of the values
     constexpr int TABLE_HALF = (int)sizeof(ring[0][0]);
-    char* const origin = (HALVES == 1 ? origins : ring[HALVES - 1][0][(part0 + steps + 3) & 3]) + wave * (kD / 2) * 8;
+    char* const origin = HALVES == 1 ? qsm[tw] + QUERIES : ring[HALVES - 1][0][(part0 + steps + 3) & 3] + wave * (kD / 2) * 8;
     {
         u32x4 rt[2], x[NL];
         float2 o = {0.f, 0.f};
@@ -387,7 +388,7 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         if (active) {
             static_for<8>([&](auto s8) {
                 constexpr int S = decltype(s8)::value % 4;
-                qf[s8.value] = *(const half8*)(qsm[0] + (tw * 2 + S / 2) * 4096 + ((s8.value / 4 * 2 + S % 2) * 64 + lane) * 16);
+                qf[s8.value] = *(const half8*)(qsm[tw] + S / 2 * 4096 + ((s8.value / 4 * 2 + S % 2) * 64 + lane) * 16);
             });
         }
     }
