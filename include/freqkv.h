@@ -371,16 +371,22 @@ FREQKV_API freqkv_status_t freqkv_debug_fast_stage(void* k, void* v, const freqk
                                         size_t dump_bytes, void* stream);
 
 /*
- * Which kernel the spans of a trigger go through, and how a chunk-wise call shares out its keys: for tests, profiles and benchmarks.
+ * Which kernel the spans of a trigger go through, what k_nearfar_units keeps of them, and how a chunk-wise call shares out its keys: for
+ * tests, profiles and benchmarks.
  * HOST only, like the plans; the answers follow measurements and may change from version to version.
  *   freqkv_debug_compress_kernel   a static string: "k_nearfar_units", "k_nearfar" or, where moments go through the workspace, "k_nearfar
  *       (workspace)" (near/far form), "k_fast" (variant 6), "k_contract_f16" (1, 2, 5), "k_contract_f32" (3), "k_move_rows" (4), "none" (0);
  *       NULL for invalid arguments
+ *   freqkv_debug_compress_ring   leaves (64 rows) that its ring in LDS holds, units of four leaves that it holds in registers besides, the
+ *       first leaf of the first of these, and from each to the next, in leaves (FREQKV_E_UNSUPPORTED: another kernel's span)
  *   freqkv_debug_prefill_cut   halves: 2 where the waves of a workgroup share out the keys, else 1; parts: of the key range, as a
  *       workspace of workspace_bytes allows (FREQKV_E_WORKSPACE: too small for the call)
  */
 FREQKV_API const char* freqkv_debug_compress_kernel(const freqkv_layout_t* layout, int n_heads, int head_dim, int window, int n_sink,
                                          double retain_ratio);
+FREQKV_API freqkv_status_t freqkv_debug_compress_ring(const freqkv_layout_t* layout, int n_heads, int head_dim, int window, int n_sink,
+                                         double retain_ratio, int32_t* slots /* host */, int32_t* held /* host */,
+                                         int32_t* first /* host */, int32_t* every /* host */);
 FREQKV_API freqkv_status_t freqkv_debug_prefill_cut(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads, int head_dim,
                                          int cur_len, int q_len, size_t workspace_bytes, int32_t* halves /* host */,
                                          int32_t* parts /* host */);

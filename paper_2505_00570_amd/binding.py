@@ -126,6 +126,8 @@ def load() -> C.CDLL:
     lib.freqkv_prepare.restype = C.c_int
     lib.freqkv_debug_compress_kernel.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double]
     lib.freqkv_debug_compress_kernel.restype = C.c_char_p
+    lib.freqkv_debug_compress_ring.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_double] + 4 * [C.POINTER(C.c_int32)]
+    lib.freqkv_debug_compress_ring.restype = C.c_int
     lib.freqkv_debug_prefill_cut.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int32),
                                              C.POINTER(C.c_int32)]
     lib.freqkv_debug_prefill_cut.restype = C.c_int
@@ -263,6 +265,14 @@ def compress_kernel(layout: Layout, n_heads: int, head_dim: int, window: int, n_
     """freqkv_debug_compress_kernel: name of the kernel that the spans go through; None for invalid arguments."""
     name = load().freqkv_debug_compress_kernel(C.byref(layout), n_heads, head_dim, window, n_sink, float(retain_ratio))
     return name.decode() if name is not None else None
+
+
+def compress_ring(layout: Layout, n_heads: int, head_dim: int, window: int, n_sink: int, retain_ratio: float):
+    """freqkv_debug_compress_ring: (ring slots, held units, first leaf of the first, leaves from each to the next) of k_nearfar_units."""
+    out = [C.c_int32() for _ in range(4)]
+    _check(load().freqkv_debug_compress_ring(C.byref(layout), n_heads, head_dim, window, n_sink, float(retain_ratio),
+                                             *[C.byref(x) for x in out]))
+    return tuple(x.value for x in out)
 
 
 def prefill_cut(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, cur_len: int, q_len: int, workspace_bytes: int):

@@ -724,6 +724,21 @@ const char* freqkv_debug_compress_kernel(const freqkv_layout_t* layout, int n_he
     }
 }
 
+freqkv_status_t freqkv_debug_compress_ring(const freqkv_layout_t* layout, int n_heads, int head_dim, int window, int n_sink,
+                                           double retain_ratio, int32_t* slots, int32_t* held, int32_t* first, int32_t* every)
+{
+    if (!slots || !held || !first || !every) return FREQKV_E_INVALID;
+    Shape sh;
+    freqkv_status_t rc = check_shape(layout, n_heads, head_dim, 0, window, n_sink, retain_ratio, &sh);
+    if (rc < 0) return rc;
+    if (!sh.nearfar || !sh.nf.TU) return FREQKV_E_UNSUPPORTED;
+    *slots = sh.nf.R;
+    *held = sh.nf.held;
+    *first = sh.nf.held0;
+    *every = sh.nf.held_every;
+    return FREQKV_OK;
+}
+
 freqkv_status_t freqkv_prepare(int dtype, uint32_t flags, int window, int n_sink, double retain_ratio,
                                void* stream)
 {

@@ -388,6 +388,20 @@ def test_kernel_names():
     assert fk.compress_kernel(_layout(), 8, 128, 8192, 4, 1.5) is None
 
 
+def test_compress_ring():
+    """freqkv_debug_compress_ring: what k_nearfar_units keeps of a span; an error for spans of other kernels."""
+    def ring(span, ratio):
+        return fk.compress_ring(_layout(cap=span + 4), 8, 128, span + 4, 4, ratio)
+    assert ring(8188, 0.5) == (11, 4, 19, 12) and ring(1020, 0.5)[1] == 0
+    for span, ratio in ((6083, 0.5), (900, 0.5), (508, 1.0)):
+        with pytest.raises(fk.FreqKVError) as e:
+            ring(span, ratio)
+        assert e.value.status == -2
+    with pytest.raises(fk.FreqKVError) as e:
+        ring(8188, 1.5)
+    assert e.value.status == -1
+
+
 def test_prefill_cut_follows_the_workspace():
     """freqkv_debug_prefill_cut: the planned cut in the planned workspace, fewer parts in less, an error without room for the operands."""
     L = _layout(n_layers=1, cap=8192)
