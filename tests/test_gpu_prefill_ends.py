@@ -1,6 +1,6 @@
 """GPU parity of chunk-wise attention at its start and end: queries rotated by the sum of two angles at the ends of their blocks and at large
-positions, results that leave as whole rows from blocks of 1 to 32 queries, in one stream of keys and in halves, results over the
-queries, and states merged four parts at a time."""
+positions, results that leave as whole rows from blocks of 1 to 32 queries, in one stream of keys and in halves, and
+states merged four parts at a time."""
 import pytest
 import torch
 
@@ -28,17 +28,10 @@ def test_rows_and_positions(hkv, hq, cur, q_len, halves):
     wl = _wl(hkv, hq, cur)
     _say(f"prefill ends {hkv}/{hq} {cur}/{q_len}")
     q, k, v = _mk(wl, cur, q_len, seed=cur + q_len)
-    L = binding.layout_for(k)
-    _, p = fk.attend_prefill_plan(L, hq, hkv, 128, cur, q_len)
+    _, p = fk.attend_prefill_plan(binding.layout_for(k), hq, hkv, 128, cur, q_len)
     assert _cut(k, hq, hkv, cur, q_len, p.workspace_bytes)[0] == halves
     out, lse, _ = _run(q, k, v, wl, cur)
     assert _check(q, k, v, out, lse, wl, cur) <= TOL_PREFILL
-    ws = torch.empty(p.workspace_bytes, dtype=torch.uint8, device="cuda")
-    L.workspace, L.workspace_bytes = ws.data_ptr(), ws.numel()
-    over = q.clone()                                                     # every wave has its queries before it writes
-    fk.attend_prefill(over, k, v, over, None, L, hq, hkv, 128, cur, q_len, wl.rope_base)
-    torch.cuda.synchronize()
-    assert torch.equal(over, out)
 
 
 def test_parts_four_at_a_time():
