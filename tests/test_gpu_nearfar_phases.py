@@ -27,7 +27,8 @@ WITH_OWN_TABLES = [(257, 0.5, 0.870e-4), (511, 0.6, 1.028e-4), (769, 0.5, 1.254e
 
 @pytest.mark.parametrize("span,ratio,own", WITH_OWN_TABLES)
 def test_error_is_that_of_a_table_per_leaf(span, ratio, own):
-    """2 % over it at most: the sums are rounded at other places (0.1 % is what the rounding of 64 channels moves it by)."""
+    """Sums are rounded at other places.  The rms of N independent errors drawn anew moves by 1 / sqrt(2 N) of itself: twice that over it at most, and 0.1 % for
+    the digits of the figures above."""
     rows = torch.from_numpy(np.random.default_rng(span).standard_normal((2, span, 64))).to(torch.bfloat16)
     k, v = (rows[i].to("cuda").reshape(1, 1, 1, span, 64).clone() for i in range(2))
     rc, p, tap = _run(k, v, _workload(span, ratio, head_dim=64), span)
@@ -35,7 +36,7 @@ def test_error_is_that_of_a_table_per_leaf(span, ratio, own):
     ref = np.stack([orc.compress_span(f64(rows[i]), p.retained_len) for i in range(2)])
     err = np.sqrt(((f64(tap).reshape(ref.shape) - ref) ** 2).mean() / (ref ** 2).mean())
     _say(f"phases {span} {ratio}: rms error {err:.3e} of {own:.3e}")
-    assert err <= 1.02 * own
+    assert err <= (1.001 + 2.0 / np.sqrt(2.0 * ref.size)) * own
 
 
 @pytest.mark.parametrize("span,ratio", [(129, 0.6), (255, 0.9), (256, 0.6), (1281, 0.6), (1407, 0.6), (1600, 0.7), (3073, 0.45), (3199, 0.95)])
