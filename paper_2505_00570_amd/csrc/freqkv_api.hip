@@ -1348,11 +1348,12 @@ struct PrefillShape {
 // streams of copies); 7 more for each further round, whose workgroups start from nothing; for parts, 3, 1 per part, and a
 // write and a read of their states (16.6 KB per task) at 7 TB/s.  The halves' own meeting, in LDS, is next to nothing; with up to 4 tasks
 // they would only give work to waves that are idle in a workgroup of one stream, and parts alone measure the same.  The
-// constants are fitted: those that choose best over 36 shapes timed in every cut (0.5 % above the best cut on average, no bound for others).
-// Measured, as (halves x parts), with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 35.0 us (1x1), 26.9 (2x1), 41.5 (2x2); 300
-// on 300 18.8 (1x1), 16.3 (2x1); 100 on 1000 26.4 (1x3), 23.7 (2x3); 301 on 5001 123 (1x1), 51.4 (1x6), 50.3 (2x3), 66 (1x8 and 2x4: a
-// second round); 1 on 8192 134 (1x1), 41.6 (1x10), 40.7 (2x10), 43.4 (1x16); 600 on 2 x 4096 109 (1x1), 128 (2x1); 2000 on 8192 238
-// (1x1), 246 (2x1), 250 (1x2); 363 on 727 in 4 layers 36.8 (1x1), 42.8 (2x1).
+// constants are fitted to 36 shapes timed in every cut, before the kernels' starts, ends and merge were made shorter: 1.7 % above the best cut on average
+// and 15 % at worst over 79 other shapes as the kernels are (profiles/prefill_cuts.txt).
+// Device time, as (halves x parts), with 8 KV heads of 4 query heads: 1000 queries on 1000 rows 34.2 us (1x1), 24.2 (2x1), 36.1 (2x2); 300
+// on 300 16.1 (1x1), 13.2 (2x1); 100 on 1000 25.2 (1x3), 21.8 (2x3); 301 on 5001 120 (1x1), 50.1 (1x6), 48.2 (2x3), 65 (1x8), 61 (2x4: a
+// second round); 1 on 8192 135 (1x1), 39.0 (1x10), 36.4 (1x16); 600 on 2 x 4096 114 (1x1), 123 (2x1); 2000 on 8192 238
+// (1x1), 240 (2x1), 257 (1x2); 363 on 727 in 4 layers 35.0 (1x1), 38.6 (2x1).
 struct PrefillCut { int halves, n_split; };
 PrefillCut prefill_cut(long long units, int G, int cur_len, int q_len, int most_parts)
 {
@@ -1425,8 +1426,8 @@ freqkv_status_t check_prefill(const freqkv_layout_t* L, int n_q, int n_kv, int d
 
 // The cut that a workspace allows, and the tiles of its parts: one sized for a longer chunk may hold fewer parts than would be best, or
 // none.  Then the best of the cuts that it does hold, which may be one in halves where the planned one was in parts alone (201 queries on
-// 4505 rows, 8 KV heads of 8, planned 1 x 4, 57 us: with room for no parts 2 x 1, 71 us, where 1 x 1 takes 114; 272 on 6225, 8 of 4, planned 1 x
-// 6, with room for three 2 x 3, 57 us, where 1 x 3 takes 71).
+// 4505 rows, 8 KV heads of 8, planned 1 x 4, 54 us: with room for no parts 2 x 1, 69 us, where 1 x 1 takes 109; 272 on 6225, 8 of 4, planned 1 x
+// 6, with room for three 2 x 3, 55 us, where 1 x 3 takes 71).
 freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_tiles)
 {
     if (workspace_bytes < p->workspace_min) return FREQKV_E_WORKSPACE;

@@ -74,7 +74,10 @@ __host__ __device__ inline int tile_slot(const NfGeom& g, int t)
 }
 // Are the moments' tables the same for all leaves but the last?  cos(Lc b_j) is cos(phase of the leaf + angle within it), so the cosines and
 // sines of the angles within a leaf do for all, and the moments are their products' sum with the phase's cosine and (negative) sine.
-// (Not for spans of up to 3 blocks: the second product costs more than the tables' way does, 251 -> 125 rows of 1728 head-tensors 75.5 -> 78.3 us.)
+// (Not for spans of up to 3 blocks: the second product costs more than the tables' way does, 251 -> 125 rows of 1728 head-tensors 75.5 -> 78.3 us.
+// On longer spans it depends on how many copies are in flight: a table per leaf -> shared, rows from HBM, ratio 0.6: 1600 rows of 16, 32, 128, 512
+// head-tensors 16.2 -> 16.8, 16.9 -> 17.8, 40.6 -> 40.1, 143.7 -> 142.0 us; 2600 of 16, 32, 64, 256 23.2 -> 24.0, 26.2 -> 26.7, 34.0 -> 33.5, 123.1 -> 119.9; 4092
+// of the same 36.1 -> 36.6, 42.1 -> 41.1, 52.2 -> 50.5, 181.9 -> 178.7.  A choice by the size of the call would make its bits depend on it.)
 __host__ __device__ inline bool phased(const NfGeom& g) { return g.NK == 2 && !g.shifts && g.NC > g.NB; }
 // First block of the neighbourhood that group gr treats leaf by leaf.
 __host__ __device__ inline int group_block0(const NfGeom& g, int gr)
@@ -274,7 +277,7 @@ void k_nearfar(SlabTable tab, NfGeom g, const char* __restrict__ tables, float* 
     char* const cloc = mom + g.NLm * kVecB;          // [group]...
     char* const loc = cloc + g.NGp * kVecB;          // [2][tile of the group]..., with TWO_LOC the second parts behind them
     char* const cmom = loc;                          // [block]..., gone before the first local values of tiles come (SPILL: two parts each)
-    char* const ltab = loc + g.NX * kVecB;           // moments of an inner leaf (SHIFTS) | of an inner block | of the last block
+    char* const ltab = loc + g.NX * kVecB;           // moments of an inner leaf (SHIFTS; PHASED: their cosines) | of an inner block | of the last block
     constexpr int GT = kCompute * TPW;
     char* const win = loc + 4 * GT * kVecB;          // SPILL: moments of kWin blocks [block mod kWin][leaf]..., in the place of cmom as well
     constexpr bool TWO_LOC = NK == 3 || SPILL;       // local values of tiles in two parts

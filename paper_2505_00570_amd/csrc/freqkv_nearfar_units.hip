@@ -179,7 +179,7 @@ void k_nearfar_units(SlabTable tab, NfGeom g, const char* __restrict__ tables, f
     constexpr int GT = GTiles<TU>, LO = kLo<TU>, kWaves = GT, kThreads = (kWaves + kMovers) * 64;
     constexpr bool TWO_LOC = TU == 1;                // local values of tiles in two parts
     constexpr bool LDS_TABS = TU == 2;               // (three waves to a SIMD: 168 registers)
-    constexpr int HELD = kUnitHeld<TU>;            // blocks that the movers hold
+    constexpr int HELD = kUnitHeld<TU>;              // units of four leaves that the movers hold
     constexpr int LOCB = 8 * kVecB;                  // local values of a group: 8 tiles, or 4 in two parts
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

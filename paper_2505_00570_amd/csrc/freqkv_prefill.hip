@@ -181,8 +181,8 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
 // vector registers).
 // HALVES == 2, for short calls: a workgroup has 4 tasks, and its first and last four waves (two to a SIMD) take the two halves of the
 // keys, each with rings of its own; the halves meet in LDS at the end.  So half as many states go through memory as with as many parts
-// of the key range more, or none, and no merging kernel.  With 8 KV heads of 4 query heads 1000 queries on 1000 rows 35.0 us in one stream,
-// 26.9 in halves; 100 on 1000 26.4 in 3 parts, 23.7 in 3 parts of halves; prefill_cut has more of them.  A step of one tile of each half takes 1.08
+// of the key range more, or none, and no merging kernel.  With 8 KV heads of 4 query heads 1000 queries on 1000 rows 34.2 us in one stream,
+// 24.2 in halves; 100 on 1000 25.2 in 3 parts, 21.8 in 3 parts of halves; prefill_cut has more of them.  A step of one tile of each half takes 1.08
 // times that of eight tasks (twice the copies).
 template <int HALVES>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
