@@ -875,18 +875,23 @@ template <bool FOLD, int TILE, class Slabs>
 __global__ __launch_bounds__(kWavesF32 * 64)
 void k_contract_f32(Slabs tab, Geom g, const float* __restrict__ Gt, const float* __restrict__ ws, float* __restrict__ tap)
 {
-    // GR groups of four indices come together in a unit of four steps; U units have their loads in flight together, and U more while
-    // these are multiplied.
-    // (1, 2, 4 units in two sets, 2, 4 in one: 2044 -> 1022 on 8192 columns 190, 192, 210 | 193, 193 us, 896 -> 448 on 2048 27.0, 30.1, 33.4 |
-    // 30.1, 30.1; with TILE 16 2044 -> 1022 on 256 columns 13.1, 13.7, 14.8 | -, 14.1.)
-    constexpr int P = FOLD ? 2 : 1, GR = 64 / TILE, REGS = TILE * TILE / 64;
+    // Eight indices, two groups of four, make a unit.  AT units come in one load and U such loads are in flight together, and U more while these are
+    // multiplied.
+    // (TILE 32, units in flight 1, 2, 4 in two sets, 2, 4 in one: 2044 -> 1022 on 8192 columns 190, 192, 210 | 193, 193 us, 896 -> 448 on 2048 27.0, 30.1,
+    // 33.4 | 30.1, 30.1.)
+    // Both tiles add up in the same order, wave by wave and index by index, so that a column's bits do not depend on how many there are in the pass:
+    // groups q0, q1 of a unit go q0[0], q1[0], q0[2], q1[2], q0[1], q1[1], q0[3], q1[3], two to a matrix instruction or four, which adds them up in the order
+    // of the lanes.  With TILE 16 the lanes' lower half loads a unit and the upper half the next; then they swap halves of their groups, which makes
+    // four instructions' operands of it.  (8 bytes per lane of one unit after the other: 3 to 14 % more time.  An order of its own, without the swap, would save
+    // 1 to 5 %, 0.1 us of 508 -> 254 rows of 64 columns, 0.4 of 896 -> 448 of 512.)
+    constexpr int P = FOLD ? 2 : 1, GR = 64 / TILE, AT = GR / 2, REGS = TILE * TILE / 64;
     constexpr int U = TILE == 32 && !FOLD ? 2 : 1;
     __shared__ float red[kWavesF32][P][REGS][64];
     typedef float Acc __attribute__((ext_vector_type(REGS)));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, at = lane % TILE, group = lane / TILE;
     const int ncp = f32_cols_padded(g), rtiles = (g.Mh + TILE - 1) / TILE;
     const int m0 = (int)(blockIdx.x % rtiles) * TILE, c0 = (int)(blockIdx.x / rtiles) * TILE;
-    const int groups = g.Kh / 4, units = (groups + GR - 1) / GR;
+    const int groups = g.Kh / 4, units = (groups + 1) / 2;
     const int per = (units + kWavesF32 - 1) / kWavesF32, u0 = wave * per, u1 = min(u0 + per, units);
     Acc acc[P];
     static_for<P>([&](auto p) { static_for<REGS>([&](auto r) { acc[p.value][r.value] = 0.f; }); });
@@ -898,7 +903,7 @@ void k_contract_f32(Slabs tab, Geom g, const float* __restrict__ Gt, const float
     };
     auto fetch = [&](f32x4 (&a)[U][P], f32x4 (&b)[U][P], int u) __attribute__((always_inline)) {
         static_for<U>([&](auto i) {
-            const int q = min((u + i.value) * GR + group, groups - 1);       // past the end: the last group again, times zero
+            const int q = min(2 * (u + i.value * AT) + group, groups - 1);   // past the end: the last group again, not used
             static_for<P>([&](auto p) {
                 a[i.value][p.value] = *(const f32x4*)(Gt + ((size_t)p.value * g.Kh * g.Mpad + ((size_t)q * g.Mpad + m0 + at) * 4));
                 b[i.value][p.value] = *(const f32x4*)(ws + ((size_t)p.value * g.Kh * ncp + ((size_t)q * ncp + c0 + at) * 4));
@@ -906,21 +911,36 @@ void k_contract_f32(Slabs tab, Geom g, const float* __restrict__ Gt, const float
         });
         __builtin_amdgcn_sched_barrier(0);                            // (left alone the compiler has four loads in flight)
     };
+    // operands of four instructions in their order from what the lanes loaded
+    auto operands = [&](f32x4 x) __attribute__((always_inline)) {
+        if constexpr (TILE == 32) return f32x4{x[0], x[2], x[1], x[3]};
+        static_for<2>([&](auto e) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[e.value]), __float_as_uint(x[e.value + 2]), false, false);
+            x[e.value] = __uint_as_float(s[0]);
+            x[e.value + 2] = __uint_as_float(s[1]);
+        });
+        return x;
+    };
     auto multiply = [&](const f32x4 (&a)[U][P], const f32x4 (&b)[U][P], int u) __attribute__((always_inline)) {
         static_for<U>([&](auto i) {
-            const bool in = u + i.value < u1 && (u + i.value) * GR + group < groups;
-            static_for<4>([&](auto e) {
-                static_for<P>([&](auto p) { mac(in ? a[i.value][p.value][e.value] : 0.f, in ? b[i.value][p.value][e.value] : 0.f, acc[p.value]); });
+            const int q = 2 * (u + i.value * AT) + group;
+            const bool in = q < 2 * u1 && q < groups;                 // (else zero; the table's entries are finite as they are)
+            f32x4 x[P], y[P];
+            static_for<P>([&](auto p) {
+                f32x4 column;
+                static_for<4>([&](auto e) { column[e.value] = in ? b[i.value][p.value][e.value] : 0.f; });
+                x[p.value] = operands(a[i.value][p.value]), y[p.value] = operands(column);
             });
+            static_for<4>([&](auto e) { static_for<P>([&](auto p) { mac(x[p.value][e.value], y[p.value][e.value], acc[p.value]); }); });
         });
     };
     f32x4 a[2][U][P], b[2][U][P];
     if (u0 < u1) fetch(a[0], b[0], u0);
-    for (int u = u0; u < u1; u += 2 * U) {
-        fetch(a[1], b[1], u + U);
+    for (int u = u0; u < u1; u += 2 * U * AT) {
+        fetch(a[1], b[1], u + U * AT);
         multiply(a[0], b[0], u);
-        fetch(a[0], b[0], u + 2 * U);
-        multiply(a[1], b[1], u + U);
+        fetch(a[0], b[0], u + 2 * U * AT);
+        multiply(a[1], b[1], u + U * AT);
     }
     if (wave == kWavesF32 - 1) {                                      // (the wave with the least to do) the rows behind the last whole group
         for (int k0 = 4 * groups; k0 < g.Kh; k0 += GR) {

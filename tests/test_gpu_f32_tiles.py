@@ -1,7 +1,8 @@
 """GPU parity of the fp32 contraction in tiles of 16 and of 32, against the fp64 CPU oracle, every element: contraction lengths of every
 remainder to 4 and shorter than 4, shares of a wave that end within a unit of loads, both sides of the rule between the tiles, more slabs
-than fit the short table of pointers."""
+than fit the short table of pointers; and the same bits from both."""
 import pytest
+import torch
 
 from paper_2505_00570_amd import synth
 
@@ -35,3 +36,25 @@ def test_f32_tiles_every_element(case):
     rc, p, tap = _run(k, v, wl, span + 4)
     assert rc == 0
     _check_all_heads(wl, k0, v0, k.cpu(), v.cpu(), tap.cpu(), p, span + 4, TOL_F32)
+
+
+@pytest.mark.parametrize("span,ratio", [(508, 0.5), (510, 0.5), (512, 0.5), (514, 0.5), (2044, 0.5), (1500, 0.3),      # folded, every remainder to 4
+                                        (509, 0.5), (511, 0.7), (510, 0.9), (512, 0.3), (1023, 0.5)])                  # plain
+def test_bits_do_not_depend_on_the_columns_of_a_pass(span, ratio):
+    """All heads in one call, one at a time, and a slab to a pass in the smallest workspace: different tiles, the same bits."""
+    heads = 20
+    wl = synth.small(synth.WORKLOADS["tiny"], n_layers=1, batch=1, n_heads=heads, head_dim=64, window=span + 1, n_sink=1, retain_ratio=ratio,
+                     total_tokens=span + 1)
+    one = synth.small(wl, n_heads=1)
+    k, v = _mk(wl, seed=span)
+    ka, va, kb, vb = (t.clone() for t in (k, v, k, v))
+    rc, p, _ = _run(ka, va, wl, span + 1, tap=False)
+    assert rc == 0 and p.variant == 3
+    rows = -(-p.retained_len // (64 if p.retained_len % 2 == 0 and span % 2 == 0 else 32))
+    assert rows * (2 * heads * 64 // 32) > 192 >= rows * (2 * 64 // 32)              # tiles of 32 and of 16
+    assert _run(kb, vb, wl, span + 1, tap=False, ws_bytes=p.workspace_min_bytes)[0] == 0
+    for h in range(heads):
+        kh, vh = k[:, :, h:h + 1].clone(), v[:, :, h:h + 1].clone()
+        assert _run(kh, vh, one, span + 1, tap=False)[0] == 0
+        assert torch.equal(ka[:, :, h], kh[:, :, 0]) and torch.equal(va[:, :, h], vh[:, :, 0]), h
+    assert torch.equal(ka, kb) and torch.equal(va, vb)
