@@ -490,7 +490,7 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
     auto it = g_rope.find(key);
     if (it == g_rope.end()) {
         BasisEntry e;
-        e.bytes = (size_t)(d / 2) * sizeof(RopeEntry);
+        e.bytes = (size_t)d * sizeof(RopeEntry);
         hipError_t err = hipMalloc(&e.ptr, e.bytes);
         if (err != hipSuccess) {
             set_error("hipMalloc(rotary table)", err);
@@ -576,7 +576,7 @@ freqkv_status_t get_cs_table(int rows, int d, double base, hipStream_t st, float
 // device address is looked up once per device, with that device current, and only that pointer is ever
 // handed to a kernel.
 constexpr size_t kScratchBytes = (size_t)8 << 20;
-constexpr size_t kScratchRopeBytes = 4096;            // rotary table of up to 256 channels (128 entries x 16 B)
+constexpr size_t kScratchRopeBytes = 4096;            // rotary table of up to 256 channels (256 entries x 16 B)
 constexpr int kScratchMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 void* g_scratch_ptr[kScratchMaxDevices] = {};
@@ -1190,7 +1190,6 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         }
     }
     hipStream_t st = (hipStream_t)stream;
-    const int rope = rope_base > 0.0;
     RopeEntry* rt = nullptr;
     char* ws = (char*)L.workspace;
     if (use_static) {
@@ -1206,7 +1205,7 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         // the table is rebuilt by every call (a few hundred bytes, one tiny kernel on the caller's stream),
         // so that calls on different streams never depend on each other's table
         rt = (RopeEntry*)sp;
-        HIP_TRY(launch_rope_table(rt, a.d, rope ? rope_base : 1.0, st));
+        HIP_TRY(launch_rope_table(rt, a.d, rope_base, st));
         ws = (char*)sp + kScratchRopeBytes;
     } else {
         // The best chunk count is not monotone in cur_len, so a workspace planned at another length (a longer one, as a loop over
@@ -1214,7 +1213,7 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         while (a.n_split > 1 && a.workspace_bytes > L.workspace_bytes) a.cut(a.n_split - 1);
         if (!L.workspace || ((uintptr_t)L.workspace & 255) || L.workspace_bytes < a.workspace_bytes)
             return FREQKV_E_WORKSPACE;
-        rc = get_rope_table(a.d, rope ? rope_base : 1.0, st, &rt);
+        rc = get_rope_table(a.d, rope_base, st, &rt);
         if (rc < 0) return rc;
     }
 
@@ -1231,8 +1230,9 @@ freqkv_status_t attend_impl(const void* q, const void* k, const void* v, void* o
         memset(&g, 0, sizeof(g));
         g.d = a.d; g.G = a.G; g.GT = a.GT; g.n_kv = a.n_kv; g.P = attend_pairs_per_lane(a.d);
         g.units = layers * upl; g.units_per_layer = upl;
-        g.cur_len = cur_len; g.q_pos = q_pos; g.cur_lens = cur_lens; g.rope = rope;
+        g.cur_len = cur_len; g.q_pos = q_pos; g.cur_lens = cur_lens;
         g.n_split = a.n_split; g.chunk = a.chunk;
+        g.by_split = divisor(a.n_split); g.by_layer = divisor(upl); g.by_kv = divisor(a.n_kv);
         g.stride_batch = L.stride_batch; g.stride_head = L.stride_head; g.stride_token = L.stride_token;
         g.qscale = (float)(1.4426950408889634 / std::sqrt((double)a.d));
         const long long head0 = (long long)l0 * upl * a.G;                 // first query head of this pass

@@ -7,14 +7,15 @@
 // appendix on key states with RoPE).  Rotary pairing is LLaMA's: channel i turns with channel i + d/2
 // by the angle pos * base^(-2i/d).
 //
-// The work is bound by reading K and V once from HBM, so scores are worked out on the vector ALUs; the weighted sums of four
-// heads go to the matrix cores, which leaves the vector ALUs half idle.  Two kernels:
-//   k_attend_partial  one workgroup per (KV head, chunk of rows, group of <= 4 query heads that share
+// The work is bound by reading K and V once from HBM, so one or two heads are worked out on the vector ALUs; four
+// heads go to the matrix cores, which leaves the vector ALUs half idle.  The kernels:
+//   k_attend_partial  one workgroup per (KV head, chunk of rows, group of 1 or 2 query heads that share
 //                     the KV head); every lane owns 4 rotary pairs of a row (8 channels), D/8 lanes
 //                     share a row, and each such lane group walks its rows with a running
 //                     max / sum / weighted-V state (online softmax).  cos/sin of the row position are
 //                     advanced by a fixed rotation per step from seeds computed with an fp64 range
 //                     reduction, so no table is read in the loop.
+//   k_attend_quads    the same for groups of four query heads.
 //   k_attend_merge    combines the per-chunk states of a query head and writes the output row (not needed for one chunk).
 #include "freqkv_internal.h"
 
@@ -48,9 +49,13 @@ __device__ __forceinline__ void static_for(F&& f)
 template <typename T, int P> struct Raw;
 template <> struct Raw<uint16_t, 4> { u32x2 a; };
 template <> struct Raw<float, 4>    { f32x4 a; };
+template <> struct Raw<uint16_t, 8> { u32x4 a; };
+template <> struct Raw<float, 8>    { f32x4 a, b; };
 
 __device__ __forceinline__ void load_raw(const uint16_t* p, Raw<uint16_t, 4>& r) { r.a = *(const u32x2*)p; }
 __device__ __forceinline__ void load_raw(const float* p, Raw<float, 4>& r) { r.a = *(const f32x4*)p; }
+__device__ __forceinline__ void load_raw(const uint16_t* p, Raw<uint16_t, 8>& r) { r.a = *(const u32x4*)p; }
+__device__ __forceinline__ void load_raw(const float* p, Raw<float, 8>& r) { r.a = *(const f32x4*)p; r.b = *(const f32x4*)(p + 4); }
 
 template <int P> __device__ __forceinline__ void unpack(const Raw<uint16_t, P>& r, float (&f)[P])
 {
@@ -63,6 +68,34 @@ template <int P> __device__ __forceinline__ void unpack(const Raw<uint16_t, P>& 
 __device__ __forceinline__ void unpack(const Raw<float, 4>& r, float (&f)[4])
 {
     static_for<4>([&](auto i) { f[decltype(i)::value] = r.a[decltype(i)::value]; });
+}
+__device__ __forceinline__ void unpack(const Raw<float, 8>& r, float (&f)[8])
+{
+    static_for<4>([&](auto i) { f[i.value] = r.a[i.value]; f[4 + i.value] = r.b[i.value]; });
+}
+
+// The upper half-wave of x and the lower of y change places.
+__device__ __forceinline__ void swap_halves(u32x4& x, u32x4& y)
+{
+    static_for<4>([&](auto i) {
+        const uint32_t a = x[i.value], b = y[i.value];
+        const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        x[i.value] = s[0];
+        y[i.value] = s[1];
+    });
+}
+__device__ __forceinline__ void swap_halves(f32x4& x, f32x4& y)
+{
+    u32x4 a = __builtin_bit_cast(u32x4, x), b = __builtin_bit_cast(u32x4, y);
+    swap_halves(a, b);
+    x = __builtin_bit_cast(f32x4, a);
+    y = __builtin_bit_cast(f32x4, b);
+}
+__device__ __forceinline__ void swap_halves(Raw<uint16_t, 8>& x, Raw<uint16_t, 8>& y) { swap_halves(x.a, y.a); }
+__device__ __forceinline__ void swap_halves(Raw<float, 8>& x, Raw<float, 8>& y)
+{
+    swap_halves(x.a, y.a);
+    swap_halves(x.b, y.b);
 }
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -95,34 +128,13 @@ __device__ __forceinline__ void lds_barrier()
 // Lane I of each quad, in all four lanes of it.
 template <int I> __device__ __forceinline__ float quad_lane(float x) { return dpp<I * 0x55>(x); }
 
-// Sums of four values over the LPR adjacent lanes that share a cache row: lane i of each quad gets that of x[i].  The first two steps
-// halve what is left to sum.  All quads get the same bits: with S0..S3 the sums of the quads of a row of 16, turned by 8 first each has S0 + S2 or S1 + S3,
-// and then the sum of both.  (By 4 first, they would have (S0 + S3) + (S2 + S1) or (S1 + S0) + (S3 + S2), and a quad's weights would not
-// be those whose sum divides its results: 2e-5 off for scores of 30.)
-template <int LPR> __device__ __forceinline__ float quad_sums(const float (&x)[4], int lane)
-{
-    const bool odd = lane & 1, high = lane & 2;
-    float a = odd ? x[1] : x[0], b = odd ? x[3] : x[2];
-    a += dpp<0xB1>(odd ? x[0] : x[1]);           // quad_perm [1,0,3,2]
-    b += dpp<0xB1>(odd ? x[2] : x[3]);
-    float s = high ? b : a;
-    s += dpp<0x4E>(high ? a : b);                // quad_perm [2,3,0,1]
-    if constexpr (LPR == 8) {
-        s += dpp<0x141>(dpp<0x1B>(s));           // the other quad of the half row: mirrored in the quad [3,2,1,0], then in the half row
-    } else {
-        static_assert(LPR >= 16);
-        s += dpp<0x128>(s);                      // the row of 16 turned by 8 and by 4
-        s += dpp<0x124>(s);
-        if constexpr (LPR >= 32) s += __shfl_xor(s, 16);
-    }
-    return s;
-}
-
-// x op (x of the lane O further or nearer), in every lane; O = 8, 16 or 32.  On the vector units: a shuffle goes through LDS, and
+// x op (x of the lane O further or nearer), in every lane; O = 4, 8, 16 or 32.  On the vector units: a shuffle goes through LDS, and
 // a chain of them is what the end of a short call waits for.
 template <int O, class F> __device__ __forceinline__ float fold(float x, F&& op)
 {
-    if constexpr (O == 8) {
+    if constexpr (O == 4) {
+        return op(x, dpp<0x141>(dpp<0x1B>(x)));  // mirrored in the quad [3,2,1,0], then in the half row
+    } else if constexpr (O == 8) {
         return op(x, dpp<0x128>(x));             // the row of 16 turned by 8
     } else if constexpr (O == 16) {
         const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -136,7 +148,10 @@ template <int O, class F> __device__ __forceinline__ float fold(float x, F&& op)
 // Sums of two values over lanes O apart: the lanes without O in their index get that of x, the others that of y.
 template <int O> __device__ __forceinline__ float fold_two(float x, float y, [[maybe_unused]] int lane)
 {
-    if constexpr (O == 8) {
+    if constexpr (O == 4) {
+        const bool upper = lane & 4;
+        return (upper ? y : x) + dpp<0x141>(dpp<0x1B>(upper ? x : y));
+    } else if constexpr (O == 8) {
         const bool upper = lane & 8;
         return (upper ? y : x) + dpp<0x128>(upper ? x : y);
     } else {
@@ -144,6 +159,22 @@ template <int O> __device__ __forceinline__ float fold_two(float x, float y, [[m
         const auto s = O == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false)
                                : __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
         return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+}
+// x of the lane without O in its index and of the one with it, for the two lanes O apart.
+struct Pair { float of[2]; };
+template <int O> __device__ __forceinline__ Pair both(float x)
+{
+    if constexpr (O == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return Pair{{__uint_as_float(s[0]), __uint_as_float(s[1])}};
+    } else {
+        static_assert(O == 4 || O == 8);
+        // moved O lanes up into the quads that have O in their index, and down into those that have not
+        constexpr int upper = O == 4 ? 0xa : 0xc;
+        const int i = __builtin_bit_cast(int, x);
+        return Pair{{__builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x110 + O, 0xf, upper, false)),
+                     __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x100 + O, 0xf, 0xf ^ upper, false))}};
     }
 }
 // ... over the lanes O, 2 O, ... 32 apart
@@ -164,6 +195,23 @@ template <class F> __device__ __forceinline__ float wave_fold(float x, F&& op)
 struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
+// Four heads: the score of the row lane / (D / 16) and the head that the lane's place in its quad names, from the products of four rows with the
+// channels of its quad.  All quads that share a row get the same bits: where each keeps what it has, two lanes add up the same two
+// values.  (D = 256, with S0..S3 the sums of the quads of 16 lanes: turned by 8 first S0 + S2 and S1 + S3.  By 4 first, they would have
+// (S0 + S3) + (S2 + S1) or (S1 + S0) + (S3 + S2), and a quad's weights would not be those whose sum divides its results: 2e-5 off for scores of 30.)
+template <int D> __device__ __forceinline__ float row_score(f32x4 x, int lane)
+{
+    if constexpr (D == 64) {
+        return fold_two<4>(fold_two<8>(x[0], x[2], lane), fold_two<8>(x[1], x[3], lane), lane);
+    } else if constexpr (D == 128) {
+        return fold<4>(fold_two<8>(fold_two<16>(x[0], x[2], lane), fold_two<16>(x[1], x[3], lane), lane), Add{});
+    } else {
+        const float s = fold_two<16>(fold_two<32>(x[0], x[2], lane), fold_two<32>(x[1], x[3], lane), lane);
+        const float t = s + dpp<0x128>(s);
+        return t + dpp<0x124>(t);
+    }
+}
+
 // Two adjacent results, rounded once.
 __device__ __forceinline__ void store2(uint16_t* p, float a, float b)
 {
@@ -175,6 +223,8 @@ __device__ __forceinline__ void store2(float* p, float a, float b) { *(f32x2*)p 
 // cos and sin of pos * theta.  The product, its reduction to [-pi/4, pi/4] plus a quadrant and the two
 // short Taylor sums (truncation below 2e-9 on that interval) are all in fp64; the results are rounded once.
 struct CosSin { float c, s; };
+// x is worked out where this stands.
+__device__ __forceinline__ void here(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ CosSin seed_sincos(double theta, int pos)
 {
     double x = (double)pos * theta;
@@ -209,19 +259,73 @@ __device__ __forceinline__ CosSin seed_sincos(double theta, int pos)
 
 }  // namespace
 
-// theta_j = base^(-2j/d) and the rotation that advances a row position by `step` rows.
+// theta_j = base^(-2j/d) and the rotation that advances a row position by `step` rows; then the same for twice as many.
 __global__ void k_rope_table(RopeEntry* rt, int d, double base, int step)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= d / 2) return;
-    double theta = pow(base, -2.0 * (double)j / (double)d);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, j = i < d / 2 ? i : i - d / 2;
+    if (i >= d) return;
+    if (i >= d / 2) step *= 2;
+    double theta = base > 0.0 ? pow(base, -2.0 * (double)j / (double)d) : 0.0;       // no rotary embedding: every angle is zero
     double sd, cd;
     sincos((double)step * theta, &sd, &cd);
     RopeEntry e;
     e.theta = theta;
     e.cd = (float)cd;
     e.sd = (float)sd;
-    rt[j] = e;
+    rt[i] = e;
+}
+
+// Workgroups that read the same rows, for query heads beyond those of one, follow each other on one XCD (they are dealt round-robin to 8) and
+// find them in its L2 (8 query heads to each of 4 KV heads x 8192 rows x 32 layers 181 -> 159 us, of 8 x 4000 x 32 167 -> 155; with all
+// first parts ahead of all second ones, rows came from memory again).
+__device__ __forceinline__ void share_out(int parts, int& chunk_id, int& part)
+{
+    const int chunks = (int)gridDim.x / parts, whole = chunks & ~7, at = chunk_id - whole * parts;
+    if (at < 0) {
+        const int grp = chunk_id / (8 * parts), local = chunk_id - grp * 8 * parts;
+        part = local >> 3;
+        chunk_id = grp * 8 + (local & 7);
+    } else {
+        part = at / (chunks - whole);
+        chunk_id = whole + at - part * (chunks - whole);
+    }
+}
+
+// The end of a chunk, from the states of its lane groups in LDS (red: HSLOTS of them; largest scores and sums of each wave): sums, and the chunk's
+// state in memory or (ONE) the results.
+template <typename T, int D, int GT, int W, int HSLOTS, bool ONE>
+__device__ __forceinline__ void finish_chunk(const float* red, const float (&xm)[GT][W], const float (&xl)[GT][W], int tid, long long head0,
+                                             int split, int n_split, float* __restrict__ part_acc, float* __restrict__ part_ml,
+                                             T* __restrict__ out, float* __restrict__ lse)
+{
+    auto group_ml = [&](int gi, float* M, float* L) {
+        *M = xm[gi][0];
+        *L = xl[gi][0];
+        static_for<W - 1>([&](auto w) { *M = fmaxf(*M, xm[gi][w.value + 1]); *L += xl[gi][w.value + 1]; });
+    };
+    const long long pidx = head0 * n_split + split;                            // + gi * n_split below
+    for (int idx = tid; idx < GT * D / 2; idx += W * 64) {
+        const int gi = idx / (D / 2), ch = 2 * (idx - gi * (D / 2));
+        f32x2 sum = {0.f, 0.f};
+#pragma unroll
+        for (int hs = 0; hs < HSLOTS; ++hs) sum += *(const f32x2*)(red + (hs * GT + gi) * D + ch);
+        if constexpr (ONE) {
+            float M, L;
+            group_ml(gi, &M, &L);
+            store2(out + (head0 + gi) * D + ch, sum[0] / L, sum[1] / L);
+        } else {
+            *(f32x2*)(part_acc + (pidx + (long long)gi * n_split) * D + ch) = sum;
+        }
+    }
+    if (tid < GT) {
+        float M, L;
+        group_ml(tid, &M, &L);
+        if constexpr (ONE) {
+            if (lse) lse[head0 + tid] = 0.6931471805599453f * (M + log2f(L));
+        } else {
+            *(f32x2*)(part_ml + (pidx + (long long)tid * n_split) * 2) = f32x2{M, L};
+        }
+    }
 }
 
 // T: storage type of the cache, the query and the output (uint16_t = bfloat16 bits, or float).
@@ -243,7 +347,6 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     constexpr int RPW = 64 / LPR;          // rows per wave per load
     constexpr int STEP = kWaves * RPW;     // rows between two consecutive rows of one lane group
     constexpr int U = kUnroll;
-    constexpr bool QUADS = GT == 4;        // see the main loop
     constexpr int HSLOTS = kWaves * RPW / 2;
     typedef Raw<T, P> RawT;
 
@@ -257,27 +360,14 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     const int l = lane % LPR;
     const int slot = lane / LPR;
 
-    // Workgroups that read the same rows, for query heads beyond GT, follow each other on one XCD (they are dealt round-robin to 8) and
-    // find them in its L2 (8 query heads to each of 4 KV heads x 8192 rows x 32 layers 181 -> 159 us, of 8 x 4000 x 32 167 -> 155; with all
-    // first parts ahead of all second ones, rows came from memory again).
     int chunk_id = blockIdx.x, part = blockIdx.y;
-    if (g.G != GT && gridDim.y == 1) {
-        const int parts = g.G / GT, chunks = (int)gridDim.x / parts, whole = chunks & ~7, at = chunk_id - whole * parts;
-        if (at < 0) {
-            const int grp = chunk_id / (8 * parts), local = chunk_id - grp * 8 * parts;
-            part = local >> 3;
-            chunk_id = grp * 8 + (local & 7);
-        } else {
-            part = at / (chunks - whole);
-            chunk_id = whole + at - part * (chunks - whole);
-        }
-    }
-    const int unit = chunk_id / g.n_split;
+    if (g.G != GT && gridDim.y == 1) share_out(g.G / GT, chunk_id, part);
+    const int unit = g.by_split.quotient(chunk_id);
     const int split = chunk_id - unit * g.n_split;
     const int g0 = part * GT;                         // first query head of this workgroup inside the KV group
-    const int layer = unit / g.units_per_layer;
+    const int layer = g.by_layer.quotient(unit);
     const int rem = unit - layer * g.units_per_layer;
-    const int b = rem / g.n_kv;
+    const int b = g.by_kv.quotient(rem);
     const int kvh = rem - b * g.n_kv;
     const long long head_off = (long long)b * g.stride_batch + (long long)kvh * g.stride_head;
     const T* kbase = (const T*)tab.base[2 * layer] + head_off;
@@ -318,9 +408,9 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         });
         next_off += (uint32_t)(U * STEP) * row_bytes;
     };
-    // Frequencies and queries, then the rows of the first step or (QUADS) two, all requested together ahead of the seeds: loads come back in
-    // order.  (With 1 or 2 heads more workgroups share a compute unit, and a step less in flight is faster: 32 x
-    // 4096 rows of 1 head 16.9 -> 16.0 us, 16 x 4096 of 2 12.6 -> 12.1, 32 x 1000 of 1 9.9 -> 9.3.)
+    // Frequencies and queries, then the rows of the first step, all requested together ahead of the seeds: loads come back in
+    // order.  (A second step of rows is slower, as several workgroups share a compute unit: 32 x
+    // 4096 rows of 1 head 16.0 -> 16.9 us, 16 x 4096 of 2 12.1 -> 12.6, 32 x 1000 of 1 9.3 -> 9.9.)
     // (Left alone the compiler puts the rows behind the seeds.)
     RopeEntry re[P];
     RawT qrl[GT], qrh[GT];
@@ -332,7 +422,6 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     });
     Rows ra, rb;
     issue(ra);
-    if constexpr (QUADS) issue(rb);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- rotary state of the P pairs this lane owns: pair j couples channels P*l+j and D/2+P*l+j.
@@ -343,10 +432,10 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         static_for<P>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
             const RopeEntry e = entries[j];
-            CosSin k0 = seed_sincos(g.rope ? e.theta : 0.0, pos);   // no rotary embedding: every angle is zero
+            CosSin k0 = seed_sincos(e.theta, pos);
             c[j] = k0.c; s[j] = k0.s;
-            cd[j] = g.rope ? e.cd : 1.f;
-            sd[j] = g.rope ? e.sd : 0.f;
+            cd[j] = e.cd;
+            sd[j] = e.sd;
         });
     };
     seed_rows(p0, re);
@@ -357,7 +446,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         float qc[P], qs[P];
         static_for<P>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            CosSin q0 = seed_sincos(g.rope ? re[j].theta : 0.0, q_pos);
+            CosSin q0 = seed_sincos(re[j].theta, q_pos);
             qc[j] = q0.c; qs[j] = q0.s;
         });
         static_for<GT>([&](auto gg) {
@@ -372,17 +461,6 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
             });
         });
     }
-
-    // Four heads: softmax of a row by quads of lanes, a head to each lane, and weighted sums on the matrix cores (v_mfma_f32_4x4x1, fp32 in and
-    // out: in each quad the product of 4 weights, one per lane, and 4 values, one per lane; a lane gets the 4 sums of its channel).  What
-    // bounds a chunk that has its compute unit to itself is vector issue, 4 cycles per instruction: a step of two rows took 440
-    // of them with every lane working out all heads, four exponentials at a quarter of the rate among them, and takes 280, so that rows are
-    // what it waits for (1 x 8 KV heads x 6147 rows 14.4 -> 13.2 us per call, with the arguments and the last barrier 12.5; x 16000 20.9 -> 17.9; 32 layers
-    // x 8 x 4000 rows with 8 query heads each 152 -> 138).
-    typedef float Acc4 __attribute__((ext_vector_type(4)));
-    [[maybe_unused]] float qm = kMinusBig, qsum = 0.f;   // of the lane's head
-    [[maybe_unused]] Acc4 qacc[2 * P];                   // [channel][head]
-    static_for<2 * P>([&](auto cc) { qacc[cc.value] = Acc4{0.f, 0.f, 0.f, 0.f}; });
 
     float m[GT], lsum[GT], acc[GT][2 * P];
     static_for<GT>([&](auto gg) {
@@ -402,7 +480,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         }
         const bool tail = row0 + (it + 1) * U * STEP > row_end;       // same for the whole workgroup
 
-        float sc[U][QUADS ? 1 : GT];
+        float sc[U][GT];
         static_for<U>([&](auto uu) {
             constexpr int u = decltype(uu)::value;
             float a[P], bb[P];
@@ -423,49 +501,17 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
                 s[j] = s[j] * cd[j] + c[j] * sd[j];
                 c[j] = cn;
             });
-            if constexpr (QUADS) sc[u][0] = quad_sums<LPR>(part, lane);
-            else static_for<GT>([&](auto gg) { sc[u][gg.value] = group_sum<LPR>(part[gg.value]); });
+            static_for<GT>([&](auto gg) { sc[u][gg.value] = group_sum<LPR>(part[gg.value]); });
             if (tail) {                                        // only the last steps of a chunk can hold rows past its end
                 const bool valid = p0 + (it * U + u) * STEP < row_end;
-                static_for<QUADS ? 1 : GT>([&](auto gg) {
+                static_for<GT>([&](auto gg) {
                     constexpr int gi = decltype(gg)::value;
                     sc[u][gi] = valid ? sc[u][gi] : -INFINITY;
                 });
             }
         });
 
-        if constexpr (QUADS) {
-            // (the reference point as below)
-            float mx = sc[0][0];
-            static_for<U>([&](auto uu) { mx = fmaxf(mx, sc[uu.value][0]); });
-            const bool grow = mx > qm + kSlack;
-            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-                const float mn = grow ? mx : qm;
-                const float f = exp2_fast(qm - mn);
-                qm = mn;
-                qsum *= f;
-                static_for<GT>([&](auto gg) {
-                    const float fh = quad_lane<gg.value>(f);
-                    static_for<2 * P>([&](auto cc) { qacc[cc.value][gg.value] *= fh; });
-                });
-            }
-            static_for<U>([&](auto uu) {
-                constexpr int u = decltype(uu)::value;
-                const float pw = exp2_fast(sc[u][0] - qm);
-                qsum += pw;
-                float va[P], vb2[P];
-                unpack(r.vl[u], va);
-                unpack(r.vh[u], vb2);
-                static_for<P>([&](auto jj) {
-                    constexpr int j = decltype(jj)::value;
-                    qacc[j] = __builtin_amdgcn_mfma_f32_4x4x1f32(pw, va[j], qacc[j], 0, 0, 0);
-                    qacc[P + j] = __builtin_amdgcn_mfma_f32_4x4x1f32(pw, vb2[j], qacc[P + j], 0, 0, 0);
-                });
-            });
-            return;
-        }
-
-        static_for<QUADS ? 0 : GT>([&](auto gg) {
+        static_for<GT>([&](auto gg) {
             constexpr int gi = decltype(gg)::value;
             // The reference point m of the running softmax only moves when a score exceeds it by more than
             // 2^kSlack; until then weights up to 2^kSlack are accumulated as they are (any reference point
@@ -498,32 +544,22 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     // Two register sets take turns: while one step is consumed the loads of the next are in flight.  Without EXACT the step
     // count is rounded up to even; a surplus step sees only rows past the end (weights exactly zero).
     for (int it = 0; it < nit; it += 2) {
-        if constexpr (!QUADS) issue(rb);
+        issue(rb);
         consume(ra, it);
         if (EXACT && it + 1 >= nit) break;
         issue(ra);
         consume(rb, it + 1);
-        if constexpr (QUADS) issue(rb);
     }
 
     // ---- combine the lane groups of the workgroup
     // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS; then sums, and accumulators
-    // rescaled.  (Four heads: still one to a lane of each quad, so once for all four.)
+    // rescaled.
     // (the lane's index is counted again: kept across the loop with what derives from it, it would not fit the registers of the longest kernel)
     uint32_t none = 0;
     asm volatile("" : "+v"(none));
     const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
     float scale[GT];
-    if constexpr (QUADS) {
-        const float mx = fold_from<LPR>(qm, Max{});
-        if (ln < 4) xm[ln][wave] = mx;
-        lds_barrier();
-        const f32x4 of_waves = *(const f32x4*)xm[ln & 3];
-        const float f = exp2_fast(qm - fmaxf(fmaxf(of_waves[0], of_waves[1]), fmaxf(of_waves[2], of_waves[3])));
-        const float ls = fold_from<LPR>(qsum * f, Add{});
-        if (ln < 4) xl[ln][wave] = ls;
-        static_for<GT>([&](auto gg) { scale[gg.value] = quad_lane<gg.value>(f); });
-    } else {
+    {
         static_for<GT>([&](auto gg) {
             constexpr int gi = decltype(gg)::value;
             const float mx = fold_from<LPR>(m[gi], Max{});
@@ -541,51 +577,273 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
         });
     }
     // Two neighbouring lane groups are folded into one, the even one keeping the lower half of the channels and the odd one the upper,
-    // and park their sums in LDS.  (With the reference points and sums of four heads worked out at once, where every lane used to do all of
-    // them and the swaps folded each value for both groups: 64 rows of 8 KV heads 6.4 -> 5.8 us, 300 9.0 -> 8.4, 6147 13.3 -> 13.0.)
+    // and park their sums in LDS.
     static_assert(P == 4);
     static_for<GT>([&](auto gg) {
         constexpr int gi = decltype(gg)::value;
         f32x4 sum;
         static_for<P>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            sum[j] = fold_two<LPR>((QUADS ? qacc[j][gi] : acc[gi][j]) * scale[gi], (QUADS ? qacc[P + j][gi] : acc[gi][P + j]) * scale[gi], ln);
+            sum[j] = fold_two<LPR>(acc[gi][j] * scale[gi], acc[gi][P + j] * scale[gi], ln);
         });
         *(f32x4*)(red + ((wave * (RPW / 2) + (ln / LPR >> 1)) * GT + gi) * D + (ln / LPR & 1) * (D / 2) + P * (ln % LPR)) = sum;
     });
     lds_barrier();
 
     // 2. sum over the parked lane groups; two channels of one query head per thread and pass
-    auto group_ml = [&](int gi, float* M, float* L) {
-        *M = xm[gi][0];
-        *L = xl[gi][0];
-        static_for<kWaves - 1>([&](auto w) { *M = fmaxf(*M, xm[gi][w.value + 1]); *L += xl[gi][w.value + 1]; });
+    finish_chunk<T, D, GT, kWaves, HSLOTS, ONE>(red, xm, xl, tid_end, (long long)unit * g.G + g0, split, g.n_split, part_acc, part_ml, out, lse);
+}
+
+// The same for four query heads that share a KV head, scores and weighted sums on the matrix cores (v_mfma_f32_4x4x1_16b_f32: fp32 products and
+// sums; in each quad of lanes the product of 4 values, one per lane, and 4 others, a lane getting the 4 that its own value has part in).
+//   keys     a quad of lanes has four rows, each lane 8 rotary pairs of its row; times the head that the lane's place in the quad names they give
+//            the lane four scores' shares, summed over the quads by lane exchanges that halve what is left, so that a lane ends with one
+//            score and one exponential for every 8 rows of 128 channels.
+//   values   a lane has 8 adjacent channels of two rows.
+// A key turns by the position of its row less that of the query, which so stays as it is.
+// What bounds it: rows; with a workgroup to a compute unit also the time until the first come (4000 cycles) and, one wave to a SIMD hiding nothing, the 1400
+// cycles of a step.  Rows asked for 16 bytes a lane, 170 vector instructions instead of 280 per 8 rows, frequencies and queries by whole lines, no rows
+// beyond a chunk's end (with keys shared out like values, each lane 4 pairs, dot products on the vector units and a head's softmax to a lane ->
+// this, graphs of calls, rows from HBM): 8 KV heads x 6147 rows 13.2 -> 12.4 us, x 3000 10.9 -> 9.9, x 16000 19.9 -> 18.7, 64 x 1000
+// 14.2 -> 13.3, 128 x 4096 53.6 -> 51.5; d = 64, 8 x 4000, 9.9 -> 8.6; d = 256 14.8 -> 13.5; fp32 14.7 -> 12.2.  Where a call has the memory to itself for longer the
+// sum is what it was: 256 x 8192 183 us, 5.9 TB/s.  Tried: copies into a ring in LDS, no registers for rows in flight (8 x 6147 12.5,
+// 256 x 8192 196); waves that take rows apart from each other's (256 x 8192 198); 8 waves (8 x 6147 12.0, as these 11.2 in calls one after the
+// other); the same for 1 and 2 heads (8 x 6147 of 1 head 9.1 -> 10.6 on rows in the memory-side cache, 11.5 -> 11.7 from HBM).
+// SHORT: chunks of up to 2 kReseed steps.
+template <typename T, int D, bool ONE, bool SHORT>
+__global__ __launch_bounds__(kWaves * 64, 2)
+void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
+                    float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
+{
+    const AttGeom g = first_argument<decltype(k_attend_quads<T, D, ONE, SHORT>)>();
+    constexpr int GT = 4, W = kWaves;
+    constexpr int N = 8;                          // channels of a value, and pairs of a key, that a lane has
+    constexpr int LPR = D / N, RPW = 64 / LPR;    // lanes that share a value, rows that a wave's lanes have one value of each
+    constexpr int SR = 2 * RPW;                   // rows of a wave's step
+    constexpr int HSLOTS = W * RPW / 2;
+    constexpr int kReseedSteps = 2 * kReseed;
+    typedef Raw<T, N> RawN;
+
+    constexpr int EB = D / 2 * (int)sizeof(RopeEntry), QB = GT * D * (int)sizeof(T), SB = 1024, TABLE = EB < SB ? SB : EB, QUERY = QB < SB ? SB : QB;
+    constexpr int ENDS = HSLOTS * GT * D * 4, STARTS = W * (TABLE + QUERY);
+    __shared__ __attribute__((aligned(16))) float red[(ENDS > STARTS ? ENDS : STARTS) / 4];
+    __shared__ __attribute__((aligned(16))) float xm[GT][W];
+    __shared__ float xl[GT][W];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    // (neighbours read the same rows, see k_attend_partial)
+    int chunk_id = blockIdx.x, part = blockIdx.y;
+    if (g.G != GT && gridDim.y == 1) share_out(g.G / GT, chunk_id, part);
+    const int unit = g.by_split.quotient(chunk_id);
+    const int split = chunk_id - unit * g.n_split;
+    const int g0 = part * GT;                         // first query head of this workgroup inside the KV group
+    const int layer = g.by_layer.quotient(unit);
+    const int rem = unit - layer * g.units_per_layer;
+    const int b = g.by_kv.quotient(rem);
+    const int kvh = rem - b * g.n_kv;
+    const long long head_off = ((long long)b * g.stride_batch + (long long)kvh * g.stride_head) * (long long)sizeof(T);
+    const char* const kb = tab.base[2 * layer] + head_off;
+    const char* const vb = tab.base[2 * layer + 1] + head_off;
+    const long long head0 = (long long)unit * g.G + g0;                        // dense query head
+
+    int cur_len = g.cur_len, q_pos = g.q_pos;
+    if (g.cur_lens) {
+        cur_len = max(1, min(g.cur_lens[b], g.cur_len));
+        q_pos = cur_len - 1;
+    }
+    const int row0 = split * g.chunk;
+    const int row_end = min(row0 + g.chunk, cur_len);   // <= row0 for a chunk beyond a short sequence: no rows
+    const int wave_row0 = row0 + wave * SR;
+    const int nit = row_end > row0 ? (row_end - row0 + W * SR - 1) / (W * SR) : 0;
+
+    // ---- what a lane has.  Keys: 8 pairs, 8 piece .. +7, of the row krow of a step; of values 8 channels of the rows vrow and vrow + 1; and the score of
+    // row srow.  Keys are requested in pieces of 16 bytes (fp32: 32), a quad of lanes having the same piece of four rows (asked for 8 bytes each,
+    // they come at 4.7 TB/s instead of 6.1).  With 64 or 128 channels the lower half-wave has the lower channels of the first half of a step's rows and the upper
+    // the upper ones; the next load has the other rows, and the half-waves trade.
+    // Rows are addressed by 32-bit byte offsets inside the head's slab (the host checks the range); rows past the end of the chunk are
+    // its last row again, and masked: no load is conditional, so the loads in flight can be counted exactly.
+    const int piece = D == 256 ? lane >> 2 : D == 128 ? lane >> 2 & 7 : lane >> 2 & 3;
+    const int krow = lane / (D / 4) * 4 + (lane & 3), srow = lane / (LPR / 2), vrow = 2 * (lane / LPR);
+    const uint32_t row_bytes = (uint32_t)g.stride_token * (uint32_t)sizeof(T);
+    const uint32_t last_off = (uint32_t)max(row_end - 1, 0) * row_bytes;
+    const uint32_t kfrom = (uint32_t)(D < 256 ? krow & (SR / 2 - 1) : krow) * row_bytes, vfrom = (uint32_t)vrow * row_bytes;
+    const uint32_t kpart = (uint32_t)(N * piece + (D < 256 && lane >= 32 ? D / 2 : 0)) * (uint32_t)sizeof(T), vpart = (uint32_t)(N * (lane % LPR)) * (uint32_t)sizeof(T);
+    uint32_t next_at = (uint32_t)wave_row0 * row_bytes;
+    struct Rows { RawN kl, kh, v[2]; };
+    auto issue = [&](Rows& r) {
+        const uint32_t o = min(next_at + kfrom, last_off) + kpart;
+        load_raw((const T*)(kb + o), r.kl);
+        if constexpr (D == 256) load_raw((const T*)(kb + o) + D / 2, r.kh);
+        else                    load_raw((const T*)(kb + (min(next_at + SR / 2 * row_bytes + kfrom, last_off) + kpart)), r.kh);
+        static_for<2>([&](auto u) { load_raw((const T*)(vb + (min(next_at + u.value * row_bytes + vfrom, last_off) + vpart)), r.v[u.value]); });
+        next_at += (uint32_t)(W * SR) * row_bytes;
     };
-    const long long head0 = (long long)unit * g.G + g0;                        // dense query head of gi = 0
-    const long long pidx = head0 * g.n_split + split;                          // + gi * n_split below
-    for (int idx = tid_end; idx < GT * D / 2; idx += kWaves * 64) {
-        const int gi = idx / (D / 2), ch = 2 * (idx - gi * (D / 2));
-        f32x2 sum = {0.f, 0.f};
-#pragma unroll
-        for (int hs = 0; hs < HSLOTS; ++hs) sum += *(const f32x2*)(red + (hs * GT + gi) * D + ch);
-        if constexpr (ONE) {
-            float M, L;
-            group_ml(gi, &M, &L);
-            store2(out + (head0 + gi) * D + ch, sum[0] / L, sum[1] / L);
-        } else {
-            *(f32x2*)(part_acc + (pidx + (long long)gi * g.n_split) * D + ch) = sum;
+    // Frequencies and queries, then the rows of two steps, all requested together ahead of the seeds: loads come back in order.  Each wave asks for
+    // whole lines, once, and hands them out through LDS: every lane asking for its own entries, the few lines of the table were
+    // what all waves of the device waited for.
+    char* const own = (char*)red + wave * (TABLE + QUERY);
+    u32x4 line[(TABLE + QUERY) / SB];
+    static_for<TABLE / SB>([&](auto j) { line[j.value] = *(const u32x4*)((const char*)(rt + D / 2) + min(j.value * SB + 16 * lane, EB - 16)); });
+    static_for<QUERY / SB>([&](auto j) { line[TABLE / SB + j.value] = *(const u32x4*)((const char*)(q + head0 * D) + min(j.value * SB + 16 * lane, QB - 16)); });
+    Rows ra, rb;
+    issue(ra);
+    issue(rb);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<(TABLE + QUERY) / SB>([&](auto j) { *(u32x4*)(own + j.value * SB + 16 * lane) = line[j.value]; });
+    asm volatile("" ::: "memory");                    // (a wave's LDS instructions take effect in order)
+
+    // ---- the lane's query, scaled by log2(e)/sqrt(d) so that exp is exp2, and the rotary state of its pairs: a pair couples channels j and D/2 + j.
+    // (c, s) = cos/sin of ((row position - query position) * theta_j), so that the query stays as it is; each step advances them by the
+    // fixed rotation (cd, sd) of its W SR rows, and every kReseedSteps they are recomputed exactly.
+    float c[N], s[N], cd[N], sd[N], ql[N], qh[N];
+    RawN qa, qb;
+    load_raw((const T*)(own + TABLE) + (lane & 3) * D + N * piece, qa);
+    load_raw((const T*)(own + TABLE) + (lane & 3) * D + D / 2 + N * piece, qb);
+    RopeEntry entries[N];
+    static_for<N>([&](auto j) { entries[j.value] = ((const RopeEntry*)own)[N * piece + j.value]; });
+    unpack(qa, ql);
+    unpack(qb, qh);
+    static_for<N>([&](auto j) { ql[j.value] *= g.qscale; qh[j.value] *= g.qscale; });
+    const int kp0 = wave_row0 + krow - q_pos;           // of the lane's key in the first step
+    auto seed = [&](const RopeEntry (&entries)[N], int pos) {
+        static_for<N>([&](auto j) {
+            const CosSin k0 = seed_sincos(entries[j.value].theta, pos);
+            c[j.value] = k0.c;
+            s[j.value] = k0.s;
+        });
+    };
+    static_for<N>([&](auto j) {
+        cd[j.value] = entries[j.value].cd;
+        sd[j.value] = entries[j.value].sd;
+    });
+    seed(entries, kp0);
+    // (all of it ahead of the rows: moved into the loop's branch, frequencies and query would be awaited there, behind the rows)
+    static_for<N>([&](auto j) {
+        constexpr int J = j.value;
+        here(c[J]); here(s[J]); here(cd[J]); here(sd[J]); here(ql[J]); here(qh[J]);
+    });
+
+    typedef float Acc4 __attribute__((ext_vector_type(4)));
+    float qm = kMinusBig, qsum = 0.f;                 // of the lane's head
+    Acc4 qacc[N];                                     // [channel][head]
+    static_for<N>([&](auto cc) { qacc[cc.value] = Acc4{0.f, 0.f, 0.f, 0.f}; });
+
+    auto consume = [&](Rows& r, int it) {
+        if constexpr (D < 256) swap_halves(r.kl, r.kh);
+        float a[N], bb[N];
+        unpack(r.kl, a);
+        unpack(r.kh, bb);
+        // four rows, one to each lane of a quad, times four queries: [row] for the query of the lane
+        f32x4 of_rows = {0.f, 0.f, 0.f, 0.f};
+        static_for<N>([&](auto jj) {
+            constexpr int j = jj.value;
+            of_rows = __builtin_amdgcn_mfma_f32_4x4x1f32(a[j] * c[j] - bb[j] * s[j], ql[j], of_rows, 0, 0, 0);
+            of_rows = __builtin_amdgcn_mfma_f32_4x4x1f32(bb[j] * c[j] + a[j] * s[j], qh[j], of_rows, 0, 0, 0);
+            const float cn = c[j] * cd[j] - s[j] * sd[j];
+            s[j] = s[j] * cd[j] + c[j] * sd[j];
+            c[j] = cn;
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        float sc = row_score<D>(of_rows, lane);
+        if (row0 + (it + 1) * (W * SR) > row_end && wave_row0 + it * (W * SR) + srow >= row_end) sc = -INFINITY;
+        // The reference point m of the running softmax only moves when a score exceeds it by more than 2^kSlack, see k_attend_partial.  It is
+        // common to the two rows whose values a lane has.
+        const float mx = fold<LPR / 2>(sc, Max{});
+        const bool grow = mx > qm + kSlack;
+        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+            const float mn = grow ? mx : qm;
+            const float f = exp2_fast(qm - mn);
+            qm = mn;
+            qsum *= f;
+            static_for<GT>([&](auto gg) {
+                const float fh = quad_lane<gg.value>(f);
+                static_for<N>([&](auto cc) { qacc[cc.value][gg.value] *= fh; });
+            });
+        }
+        const float pw = exp2_fast(sc - qm);
+        qsum += pw;
+        const Pair weights = both<LPR / 2>(pw);
+        static_for<2>([&](auto u) {
+            float va[N];
+            unpack(r.v[u.value], va);
+            static_for<N>([&](auto cc) {
+                qacc[cc.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(weights.of[u.value], va[cc.value], qacc[cc.value], 0, 0, 0);
+            });
+        });
+    };
+    // Two register sets take turns: while one step is consumed the loads of the next are in flight.  A long chunk has its steps
+    // rounded up to an even number; a surplus step sees only rows past the end (weights exactly zero).
+    if constexpr (SHORT) {
+        for (int it = 0; it < nit; it += 2) {
+            consume(ra, it);
+            if (it + 1 >= nit) break;
+            __builtin_amdgcn_sched_barrier(0);
+            issue(ra);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(rb, it + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(rb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        int it = 0;
+        while (true) {
+            for (const int end = min(nit, it + kReseedSteps); it < end; it += 2) {
+                consume(ra, it);
+                __builtin_amdgcn_sched_barrier(0);
+                issue(ra);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(rb, it + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                issue(rb);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (it >= nit) break;
+            RopeEntry again[N];
+            static_for<N>([&](auto j) { again[j.value] = rt[D / 2 + N * piece + j.value]; });
+            seed(again, kp0 + it * (W * SR));
         }
     }
-    if (tid_end < GT) {
-        float M, L;
-        group_ml(tid_end, &M, &L);
-        f32x2* ml = (f32x2*)(part_ml + (pidx + (long long)tid_end * g.n_split) * 2);
-        if constexpr (ONE) {
-            if (lse) lse[head0 + tid_end] = 0.6931471805599453f * (M + log2f(L));
-        } else {
-            *ml = f32x2{M, L};
-        }
+
+    // ---- combine the lane groups of the workgroup
+    // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS; then sums, and accumulators
+    // rescaled, one head to a lane of each quad.
+    // (the lane's index is counted again: kept across the loop with what derives from it, it would not fit the registers)
+    uint32_t none = 0;
+    asm volatile("" : "+v"(none));
+    const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
+    float scale[GT];
+    {
+        const float mx = fold_from<LPR>(qm, Max{});
+        if (ln < GT) xm[ln][wave] = mx;
+        lds_barrier();
+        float M = kMinusBig;
+        static_for<W / 4>([&](auto w) {
+            const f32x4 of_waves = *(const f32x4*)&xm[ln & 3][4 * w.value];
+            M = fmaxf(M, fmaxf(fmaxf(of_waves[0], of_waves[1]), fmaxf(of_waves[2], of_waves[3])));
+        });
+        const float f = exp2_fast(qm - M);
+        const float ls = fold_from<LPR / 2>(qsum * f, Add{});
+        if (ln < GT) xl[ln][wave] = ls;
+        static_for<GT>([&](auto gg) { scale[gg.value] = quad_lane<gg.value>(f); });
     }
+    // Two neighbouring lane groups are folded into one, the even one keeping the lower half of the lanes' channels and the odd one the upper,
+    // and park their sums in LDS.
+    static_for<GT>([&](auto gg) {
+        constexpr int gi = decltype(gg)::value;
+        f32x4 sum;
+        static_for<4>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            sum[j] = fold_two<LPR>(qacc[j][gi] * scale[gi], qacc[4 + j][gi] * scale[gi], ln);
+        });
+        *(f32x4*)(red + ((wave * (RPW / 2) + (ln / LPR >> 1)) * GT + gi) * D + N * (ln % LPR) + (ln / LPR & 1) * 4) = sum;
+    });
+    lds_barrier();
+
+    // 2. sum over the parked lane groups; two channels of one query head per thread and pass
+    finish_chunk<T, D, GT, W, HSLOTS, ONE>(red, xm, xl, tid_end, head0, split, g.n_split, part_acc, part_ml, out, lse);
 }
 
 // One workgroup per query head merges the chunk states, normalises, stores.  D/2 threads cover the channels (two each), and
@@ -664,16 +922,21 @@ void k_attend_merge(const AttGeom, const float* __restrict__ part_acc, const flo
 hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st)
 {
     int step = attend_row_step(d);
-    hipLaunchKernelGGL(k_rope_table, dim3((d / 2 + 63) / 64), dim3(64), 0, st, rt, d, base, step);
+    hipLaunchKernelGGL(k_rope_table, dim3((d + 63) / 64), dim3(64), 0, st, rt, d, base, step);
     return hipGetLastError();
+}
+
+static dim3 partial_grid(const AttGeom& g)
+{
+    const long long chunks = (long long)g.units * g.n_split, parts = g.G / g.GT;
+    return chunks * parts < 1 << 23 ? dim3((unsigned)(chunks * parts)) : dim3((unsigned)chunks, (unsigned)parts);   // (a launch has up to 2^32 threads per direction)
 }
 
 template <typename T, int D, int GT, bool ONE, bool EXACT>
 static void launch_partial_o(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
                              float* part_ml, void* out, float* lse, hipStream_t st)
 {
-    const long long chunks = (long long)g.units * g.n_split, parts = g.G / g.GT;
-    const dim3 grid = chunks * parts < 1 << 23 ? dim3((unsigned)(chunks * parts)) : dim3((unsigned)chunks, (unsigned)parts);   // (a launch has up to 2^32 threads per direction)
+    const dim3 grid = partial_grid(g);
     hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE, EXACT>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
                        part_acc, part_ml, (T*)out, lse, tab);
 }
@@ -693,11 +956,25 @@ static void launch_partial_g(const SlabTable& tab, const AttGeom& g, const void*
 }
 
 template <typename T, int D>
+static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc, float* part_ml, void* out,
+                         float* lse, hipStream_t st)
+{
+    const dim3 grid = partial_grid(g);
+    const bool brief = g.chunk <= 2 * kReseed * kUnroll * attend_row_step(D);
+    auto launch = [&](auto one, auto is_short) {
+        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
+                           part_acc, part_ml, (T*)out, lse, tab);
+    };
+    if (g.n_split == 1) brief ? launch(IC<1>{}, IC<1>{}) : launch(IC<1>{}, IC<0>{});
+    else                brief ? launch(IC<0>{}, IC<1>{}) : launch(IC<0>{}, IC<0>{});
+}
+
+template <typename T, int D>
 static hipError_t launch_partial_d(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
                                    float* part_ml, void* out, float* lse, hipStream_t st)
 {
     switch (g.GT) {
-        case 4: launch_partial_g<T, D, 4>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
+        case 4: launch_quads<T, D>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 2: launch_partial_g<T, D, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 1: launch_partial_g<T, D, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         default: return hipErrorInvalidValue;

@@ -219,6 +219,23 @@ hipError_t launch_calib_mfma(float* out, int blocks, int iters, hipStream_t st);
 
 // ---- decode attention over the compacted cache ---------------------------------------------------
 // Geometry of one attention pass (by-value kernel argument).  A "unit" is one (layer, batch, KV head).
+// Division of 0 .. 2^31 - 1 by a fixed d, which a kernel would spend some 150 cycles on at its start.  With 2^s < d <= 2^(s+1), factor =
+// ceil(2^(32+s) / d) has 32 bits and is less than 2^(s+1) / d too large, which a quotient's floor does not notice: n 2^(s+1) < 2^(32+s).
+struct Divisor {
+    uint32_t factor, shift;            // factor 0: d is 1
+    __host__ __device__ int quotient(int n) const
+    {
+        return factor ? (int)((uint32_t)(((uint64_t)(uint32_t)n * factor) >> 32) >> shift) : n;
+    }
+};
+inline Divisor divisor(int d)
+{
+    if (d <= 1) return Divisor{0, 0};
+    uint32_t s = 0;
+    while ((2u << s) < (uint32_t)d) ++s;
+    return Divisor{(uint32_t)((((uint64_t)1 << (32 + s)) + d - 1) / d), s};
+}
+
 struct AttGeom {
     int d;                 // head_dim: 64, 128 or 256
     int G;                 // query heads per KV head
@@ -230,14 +247,15 @@ struct AttGeom {
     int q_pos;             // in-cache position of the query (with cur_lens: each sequence's last row)
     const int* cur_lens;   // optional device array [batch] of per-sequence cached rows, or null
     int P;                 // rotary pairs per lane, attend_pairs_per_lane(d)
-    int rope;              // 1: rotate query and keys at read time, 0: plain dot products
     int n_split;           // row chunks per unit
     int chunk;             // rows per chunk, a multiple of 2 * attend_row_step(d)
     long long stride_batch, stride_head, stride_token;   // elements
+    Divisor by_split, by_layer, by_kv;   // n_split, units_per_layer, n_kv
     float qscale;          // log2(e) / sqrt(d)
 };
 
-// One rotary pair: its frequency and the rotation that advances the position by attend_row_step(d) rows.
+// One rotary pair: its frequency and the rotation that advances the position by attend_row_step(d) rows (the second d/2 entries of a table:
+// by twice as many).
 struct RopeEntry {
     double theta;
     float cd, sd;

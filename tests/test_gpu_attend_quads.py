@@ -70,3 +70,19 @@ def test_quads_keep_channels_and_heads_apart(d):
     out, _, _ = _run(q2, k, v, wl, 500)
     others = [h for h in range(8) if h != 2]
     assert torch.isnan(out[0, 0, 2].float()).all() and torch.equal(out[0, 0, others], clean[0, 0, others])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,cur_len", [(64, 4097), (64, 4225), (128, 2047), (128, 2049), (128, 2113), (256, 1025), (256, 2081)])
+def test_quads_long_chunks(d, cur_len, dtype):
+    """Whole sequences in one chunk each, below and beyond the 64 steps between exact angles: an odd and an even number of steps, a last step of one row."""
+    batch = 256
+    wl = _wl(d=d, hkv=2, hq=8, batch=batch, cap=cur_len, dtype=dtype)
+    q, k, v = _mk(wl, cur_len, seed=cur_len + d)
+    _ramp(q, k, cur_len)
+    out, lse, p = _run(q, k, v, wl, cur_len)
+    _say(f"quads, long chunks {cur_len} {d} {dtype}: n_split {p.n_split}")
+    assert p.n_split == 1
+    q, k, v, out, lse = (t[:, [0, 255]].cpu() for t in (q, k, v, out, lse))
+    for b in range(2):
+        _check_heads(q, k, v, out, lse, wl, b, cur_len)
