@@ -294,7 +294,7 @@ __device__ __forceinline__ void share_out(int parts, int& chunk_id, int& part)
 // The end of a chunk, from the states of its lane groups in LDS (red: HSLOTS of them; largest scores and sums of each wave): sums, and the chunk's
 // state in memory or (ONE) the results.
 template <typename T, int D, int GT, int W, int HSLOTS, bool ONE>
-__device__ __forceinline__ void finish_chunk(const float* red, const float (&xm)[GT][W], const float (&xl)[GT][W], int tid, long long head0,
+__device__ __forceinline__ void finish_chunk(const float* red, const float (&xm)[GT][W], const float (&xl)[GT][W], int tid, int heads, long long head0,
                                              int split, int n_split, float* __restrict__ part_acc, float* __restrict__ part_ml,
                                              T* __restrict__ out, float* __restrict__ lse)
 {
@@ -304,7 +304,7 @@ __device__ __forceinline__ void finish_chunk(const float* red, const float (&xm)
         static_for<W - 1>([&](auto w) { *M = fmaxf(*M, xm[gi][w.value + 1]); *L += xl[gi][w.value + 1]; });
     };
     const long long pidx = head0 * n_split + split;                            // + gi * n_split below
-    for (int idx = tid; idx < GT * D / 2; idx += W * 64) {
+    for (int idx = tid; idx < heads * (D / 2); idx += W * 64) {
         const int gi = idx / (D / 2), ch = 2 * (idx - gi * (D / 2));
         f32x2 sum = {0.f, 0.f};
 #pragma unroll
@@ -317,7 +317,7 @@ __device__ __forceinline__ void finish_chunk(const float* red, const float (&xm)
             *(f32x2*)(part_acc + (pidx + (long long)gi * n_split) * D + ch) = sum;
         }
     }
-    if (tid < GT) {
+    if (tid < heads) {
         float M, L;
         group_ml(tid, &M, &L);
         if constexpr (ONE) {
@@ -591,7 +591,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     lds_barrier();
 
     // 2. sum over the parked lane groups; two channels of one query head per thread and pass
-    finish_chunk<T, D, GT, kWaves, HSLOTS, ONE>(red, xm, xl, tid_end, (long long)unit * g.G + g0, split, g.n_split, part_acc, part_ml, out, lse);
+    finish_chunk<T, D, GT, kWaves, HSLOTS, ONE>(red, xm, xl, tid_end, GT, (long long)unit * g.G + g0, split, g.n_split, part_acc, part_ml, out, lse);
 }
 
 // The same for four query heads that share a KV head, scores and weighted sums on the matrix cores (v_mfma_f32_4x4x1_16b_f32: fp32 products and
@@ -610,12 +610,14 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
 // 256 x 8192 196); waves that take rows apart from each other's (256 x 8192 198); 8 waves (8 x 6147 12.0, as these 11.2 in calls one after the
 // other); the same for 1 and 2 heads (8 x 6147 of 1 head 9.1 -> 10.6 on rows in the memory-side cache, 11.5 -> 11.7 from HBM).
 // SHORT: chunks of up to 2 kReseed steps.
-template <typename T, int D, bool ONE, bool SHORT>
+// MANY: the heads are the queries of a chunk of g.q_len that has just been appended, g.G in all (for each head that shares the KV head all of the chunk), not
+// always a multiple of four; each has its own position, by which it is turned, and its own number of rows.
+template <typename T, int D, bool ONE, bool SHORT, bool MANY>
 __global__ __launch_bounds__(kWaves * 64, 2)
 void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
                     float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
-    const AttGeom g = first_argument<decltype(k_attend_quads<T, D, ONE, SHORT>)>();
+    const AttGeom g = first_argument<decltype(k_attend_quads<T, D, ONE, SHORT, MANY>)>();
     constexpr int GT = 4, W = kWaves;
     constexpr int N = 8;                          // channels of a value, and pairs of a key, that a lane has
     constexpr int LPR = D / N, RPW = 64 / LPR;    // lanes that share a value, rows that a wave's lanes have one value of each
@@ -635,7 +637,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
 
     // (neighbours read the same rows, see k_attend_partial)
     int chunk_id = blockIdx.x, part = blockIdx.y;
-    if (g.G != GT && gridDim.y == 1) share_out(g.G / GT, chunk_id, part);
+    if (g.G != GT && gridDim.y == 1) share_out(MANY ? (g.G + GT - 1) / GT : g.G / GT, chunk_id, part);
     const int unit = g.by_split.quotient(chunk_id);
     const int split = chunk_id - unit * g.n_split;
     const int g0 = part * GT;                         // first query head of this workgroup inside the KV group
@@ -647,6 +649,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     const char* const kb = tab.base[2 * layer] + head_off;
     const char* const vb = tab.base[2 * layer + 1] + head_off;
     const long long head0 = (long long)unit * g.G + g0;                        // dense query head
+    const int heads = MANY ? min(GT, g.G - g0) : GT;
 
     int cur_len = g.cur_len, q_pos = g.q_pos;
     if (g.cur_lens) {
@@ -656,6 +659,9 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     const int row0 = split * g.chunk;
     const int row_end = min(row0 + g.chunk, cur_len);   // <= row0 for a chunk beyond a short sequence: no rows
     const int wave_row0 = row0 + wave * SR;
+    // MANY: of the lane's query, its place in the chunk of queries, and the rows that it sees; what all see
+    const int place = MANY ? g0 + (lane & 3) - g.by_q.quotient(g0 + (lane & 3)) * g.q_len : 0;
+    const int limit = MANY ? min(row_end, cur_len - g.q_len + 1 + place) : row_end, seen = MANY ? min(row_end, cur_len - g.q_len + 1) : row_end;
     const int nit = row_end > row0 ? (row_end - row0 + W * SR - 1) / (W * SR) : 0;
 
     // ---- what a lane has.  Keys: 8 pairs, 8 piece .. +7, of the row krow of a step; of values 8 channels of the rows vrow and vrow + 1; and the score of
@@ -686,7 +692,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     char* const own = (char*)red + wave * (TABLE + QUERY);
     u32x4 line[(TABLE + QUERY) / SB];
     static_for<TABLE / SB>([&](auto j) { line[j.value] = *(const u32x4*)((const char*)(rt + D / 2) + min(j.value * SB + 16 * lane, EB - 16)); });
-    static_for<QUERY / SB>([&](auto j) { line[TABLE / SB + j.value] = *(const u32x4*)((const char*)(q + head0 * D) + min(j.value * SB + 16 * lane, QB - 16)); });
+    static_for<QUERY / SB>([&](auto j) { line[TABLE / SB + j.value] = *(const u32x4*)((const char*)(q + head0 * D) + min(j.value * SB + 16 * lane, (MANY ? heads * (QB / GT) : QB) - 16)); });
     Rows ra, rb;
     issue(ra);
     issue(rb);
@@ -705,7 +711,12 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     static_for<N>([&](auto j) { entries[j.value] = ((const RopeEntry*)own)[N * piece + j.value]; });
     unpack(qa, ql);
     unpack(qb, qh);
-    static_for<N>([&](auto j) { ql[j.value] *= g.qscale; qh[j.value] *= g.qscale; });
+    static_for<N>([&](auto j) {
+        const float x = ql[j.value] * g.qscale, y = qh[j.value] * g.qscale;
+        const CosSin k0 = MANY ? seed_sincos(entries[j.value].theta, place + 1 - g.q_len) : CosSin{1.f, 0.f};
+        ql[j.value] = MANY ? x * k0.c - y * k0.s : x;
+        qh[j.value] = MANY ? y * k0.c + x * k0.s : y;
+    });
     const int kp0 = wave_row0 + krow - q_pos;           // of the lane's key in the first step
     auto seed = [&](const RopeEntry (&entries)[N], int pos) {
         static_for<N>([&](auto j) {
@@ -747,7 +758,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
         });
         __builtin_amdgcn_sched_barrier(0);
         float sc = row_score<D>(of_rows, lane);
-        if (row0 + (it + 1) * (W * SR) > row_end && wave_row0 + it * (W * SR) + srow >= row_end) sc = -INFINITY;
+        if (row0 + (it + 1) * (W * SR) > seen && wave_row0 + it * (W * SR) + srow >= limit) sc = -INFINITY;
         // The reference point m of the running softmax only moves when a score exceeds it by more than 2^kSlack, see k_attend_partial.  It is
         // common to the two rows whose values a lane has.
         const float mx = fold<LPR / 2>(sc, Max{});
@@ -843,7 +854,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     lds_barrier();
 
     // 2. sum over the parked lane groups; two channels of one query head per thread and pass
-    finish_chunk<T, D, GT, W, HSLOTS, ONE>(red, xm, xl, tid_end, head0, split, g.n_split, part_acc, part_ml, out, lse);
+    finish_chunk<T, D, GT, W, HSLOTS, ONE>(red, xm, xl, tid_end, heads, head0, split, g.n_split, part_acc, part_ml, out, lse);
 }
 
 // One workgroup per query head merges the chunk states, normalises, stores.  D/2 threads cover the channels (two each), and
@@ -928,7 +939,7 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st)
 
 static dim3 partial_grid(const AttGeom& g)
 {
-    const long long chunks = (long long)g.units * g.n_split, parts = g.G / g.GT;
+    const long long chunks = (long long)g.units * g.n_split, parts = (g.G + g.GT - 1) / g.GT;
     return chunks * parts < 1 << 23 ? dim3((unsigned)(chunks * parts)) : dim3((unsigned)chunks, (unsigned)parts);   // (a launch has up to 2^32 threads per direction)
 }
 
@@ -955,14 +966,14 @@ static void launch_partial_g(const SlabTable& tab, const AttGeom& g, const void*
                               : launch_partial_o<T, D, GT, false, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
 }
 
-template <typename T, int D>
+template <typename T, int D, bool MANY>
 static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc, float* part_ml, void* out,
                          float* lse, hipStream_t st)
 {
     const dim3 grid = partial_grid(g);
     const bool brief = g.chunk <= 2 * kReseed * kUnroll * attend_row_step(D);
     auto launch = [&](auto one, auto is_short) {
-        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
+        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
                            part_acc, part_ml, (T*)out, lse, tab);
     };
     if (g.n_split == 1) brief ? launch(IC<1>{}, IC<1>{}) : launch(IC<1>{}, IC<0>{});
@@ -974,7 +985,7 @@ static hipError_t launch_partial_d(const SlabTable& tab, const AttGeom& g, const
                                    float* part_ml, void* out, float* lse, hipStream_t st)
 {
     switch (g.GT) {
-        case 4: launch_quads<T, D>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
+        case 4: launch_quads<T, D, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 2: launch_partial_g<T, D, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 1: launch_partial_g<T, D, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         default: return hipErrorInvalidValue;
@@ -1005,6 +1016,16 @@ hipError_t launch_attend_partial(const SlabTable& tab, const AttGeom& g, int ele
     if (g.chunk % (kUnroll * attend_row_step(g.d))) return hipErrorInvalidValue;
     return elem_bytes == 2 ? launch_partial_t<uint16_t>(tab, g, q, rt, part_acc, part_ml, out, lse, st)
                            : launch_partial_t<float>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+}
+
+hipError_t launch_attend_many(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc, float* part_ml, void* out,
+                              float* lse, hipStream_t st)
+{
+    if (g.units < 1 || g.n_split < 1 || g.chunk < 1 || g.q_len < 1 || g.q_len > g.cur_len || g.G % g.q_len) return hipErrorInvalidValue;
+    if ((long long)(g.n_split - 1) * g.chunk >= g.cur_len || (long long)g.n_split * g.chunk < g.cur_len) return hipErrorInvalidValue;
+    if (g.d != 128 || g.GT != 4 || g.cur_lens || g.chunk % (kUnroll * attend_row_step(g.d))) return hipErrorInvalidValue;
+    launch_quads<uint16_t, 128, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_attend_merge(const AttGeom& g, int elem_bytes, const float* part_acc, const float* part_ml,

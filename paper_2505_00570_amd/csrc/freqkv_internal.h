@@ -250,7 +250,8 @@ struct AttGeom {
     int n_split;           // row chunks per unit
     int chunk;             // rows per chunk, a multiple of 2 * attend_row_step(d)
     long long stride_batch, stride_head, stride_token;   // elements
-    Divisor by_split, by_layer, by_kv;   // n_split, units_per_layer, n_kv
+    Divisor by_split, by_layer, by_kv, by_q;   // n_split, units_per_layer, n_kv, q_len
+    int q_len;             // launch_attend_many: queries of a head, G being that of all heads; else 0
     float qscale;          // log2(e) / sqrt(d)
 };
 
@@ -273,6 +274,9 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st);
 // part_ml: [units*G][n_split][2] fp32 (running maximum in the exp2 domain, sum of weights).
 hipError_t launch_attend_partial(const SlabTable& tab, const AttGeom& g, int elem_bytes, const void* q,
                                  const RopeEntry* rt, float* part_acc, float* part_ml, void* out, float* lse, hipStream_t st);
+// Several queries of each head, the last q_len rows, bf16 and d = 128: g.G = query heads per KV head * q_len, q and out dense [units][g.G][d].
+hipError_t launch_attend_many(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc, float* part_ml, void* out,
+                              float* lse, hipStream_t st);
 hipError_t launch_attend_merge(const AttGeom& g, int elem_bytes, const float* part_acc, const float* part_ml,
                                void* out, float* lse, hipStream_t st);
 
