@@ -344,8 +344,8 @@ FREQKV_API freqkv_status_t freqkv_attend_prefill_plan(const freqkv_layout_t* lay
  *                     fewer parts (few queries are then slower), down to what the operands alone need
  * head_dim 128 and bfloat16 caches only (FREQKV_E_UNSUPPORTED otherwise).  Operands of the matrix cores are
  * fp16 (cache values are exact in fp16; rotated keys and queries keep 11 significant bits), accumulation,
- * softmax and the running sums are fp32; with up to 16 queries in all heads of a KV head (up to 64 over short caches) everything
- * is fp32, as in freqkv_attend_decode.  The call only enqueues work on `stream`.  The cos/sin of the row positions is
+ * softmax and the running sums are fp32; with up to 4 queries in all heads of a KV head, and with up to 64 where that is
+ * faster, everything is fp32, as in freqkv_attend_decode.  The call only enqueues work on `stream`.  The cos/sin of the row positions is
  * kept per (device, rope_base), 512 bytes per row, up to 65536 rows and 16 tables per device; calls beyond that, and
  * first calls inside a stream capture, compute it into their workspace (some 5 us more).
  */

@@ -1449,16 +1449,38 @@ freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_
     p->n_split = (p->key_tiles + *split_tiles - 1) / *split_tiles;
     return FREQKV_OK;
 }
-// Few queries go as so many heads of a decode call, by fours, which reads keys and values where they are and works in fp32; the other way writes all
-// cached rows as operands first, 0.26 ns for each.  Up to 16 queries in all heads of a KV head are always faster so (one query 1.3 to 3.4 times, 16
+
+// Calls whose tiles are used by few workgroups read the cached rows as they are: there is no pass that writes them as operands first (7 ns per KV head
+// and tile of 32 keys, and its launch), but each workgroup turns every tile that it uses, 0.21 us more per tile, 0.475 per tile of each half.  The
+// constants are a least-squares fit to 300 shapes drawn over 1 to 32 KV heads, 1 to 8 query heads each, 1 to 4 layers, 1 to 4 sequences, 256 to 8192 rows
+// and 13 of them to all as queries, each timed both ways in graphs of calls, with 1 us to spare: 93 of them go this way, the longest 1.003 times as long as the
+// other way, the shortest a third.  Operands first -> rows as they are, us: 32 KV heads of one query head each, 4 sequences, 4046 rows, 20 queries 186 ->
+// 62; 2 layers, 2 sequences, 1693, 267 97 -> 61; 385, 385, 4 layers 33 -> 22; 794, 794, 2 sequences 41 -> 31; 8 KV heads of 4, 2 sequences, 5082, 121
+// 56 -> 45.  Not taken: 8 of 4, 5001, 301 52.1 -> 52.1; 1000, 1000 25.0 -> 29.8; 8192, 4094 385 -> 453; 32 of 1, 4261, 4261, 2 layers 382 -> 398.
+bool prefill_direct(const PrefillShape& p, int split_tiles, long long stride_token)
+{
+    if (!prefill_direct_fits(p.a.cur_len, stride_token)) return false;
+    const int tasks_per_unit = p.a.G * (p.q_pad / 32), first = (p.a.cur_len - p.q_len) / 32 + 1;
+    const double wgs = (double)p.units * ((tasks_per_unit * p.halves + 7) / 8);
+    const double steps = std::max((double)split_tiles, wgs * 0.5 * (p.key_tiles + first) / 256.0) / p.halves;     // of a compute unit
+    return 0.007 * (double)p.units * p.key_tiles > (p.halves == 2 ? 0.475 : 0.21) * steps + 0.2;
+}
+
+// Few queries go as so many heads of a decode call, by fours, which reads keys and values where they are and works in fp32.
+// Against operands written first: up to 16 queries in all heads of a KV head are always faster so (one query 1.3 to 3.4 times, 16
 // 1.04 to 2.3; 8 KV heads of 2 query heads each, 4 layers, 6000 rows, 8 queries 62 -> 55 us).  Of more than that each further four take 0.066 ns per row on a device that is full,
 // against some 6 us that a call has less to do, rows of short caches counting as 256: 2 KV heads of 8, 1500 rows, 8 queries 17.5 -> 11.2,
 // 8 of 4, 1500, 8 20.4 -> 15.2; not taken 8 of 2 in 4 layers, 6000, 16 62 -> 102, 2 of 8, 7922, 7 30.3 -> 23.5.  Over 240 shapes in both ways 1.5 % above the better one on
 // average; where this way was taken never more than 2 % above the other.
-bool prefill_as_decode(long long units, int G, int cur_len, int q_len)
+// Against rows as they are (direct): four queries, which only read, are always faster so; each further four take 0.06 ns per row, and the other way 0.5 us per
+// tile of a part.  Over 165 shapes in both ways 0.4 % above the better one on average.  32 KV heads of 1, 1631 rows, 17 queries: operands first 24.2, so 25.2, rows as
+// they are 16.6; 32 of 1, 4 layers, 7323, 5 336, 123, 104; 16 of 4, 2 layers, 5330, 4 75, 49, 35; taken 4 of 1, 2 layers, 5075, 6 28.7, 14.2, 20.7.
+bool prefill_as_decode(const PrefillShape& p, bool direct, int split_tiles)
 {
-    const long long groups = ((long long)G * q_len + 3) / 4;
-    return groups <= 4 || (groups <= 16 && units * std::max(cur_len, 256) * (groups - 4) < 75000);
+    const long long groups = ((long long)p.a.G * p.q_len + 3) / 4, units = p.units;
+    if (groups > 16) return false;
+    if (direct) return groups == 1 || 0.5 + 0.5 * split_tiles > 1e-3 * (double)(units * std::max(p.a.cur_len, 320)) * (0.06 * (double)groups - 0.03);
+    return groups <= 4 || units * std::max(p.a.cur_len, 256) * (groups - 4) < 75000;
 }
 
 // A call of few queries.  Its states take less than the operands of the other way, which the workspace has room for.
@@ -1567,7 +1589,8 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
     int split_tiles = 0;
     rc = fit_prefill(&p, L.workspace_bytes, &split_tiles);
     if (rc < 0) return rc;
-    if (prefill_as_decode(p.units, a.G, cur_len, q_len)) return attend_many(p, bases.data(), q, out, lse, L, rope_base, (hipStream_t)stream);
+    const bool direct = prefill_direct(p, split_tiles, L.stride_token);
+    if (prefill_as_decode(p, direct, split_tiles)) return attend_many(p, bases.data(), q, out, lse, L, rope_base, (hipStream_t)stream);
     const int n_split = p.n_split;
 
     hipStream_t st = (hipStream_t)stream;
@@ -1593,14 +1616,16 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
         const char* qp = (const char*)q + head0 * q_len * a.d * a.elem;
         char* op = (char*)out + head0 * q_len * a.d * a.elem;
         ProfSpan sp;
-        HIP_TRY(prof_begin(st, 0, &sp));
-        HIP_TRY(launch_prefill_prepare(tab, g, cs, (_Float16*)(ws + p.off_kr), (_Float16*)(ws + p.off_vt), st));
-        HIP_TRY(prof_end(st, &sp));
+        if (!direct) {
+            HIP_TRY(prof_begin(st, 0, &sp));
+            HIP_TRY(launch_prefill_prepare(tab, g, cs, (_Float16*)(ws + p.off_kr), (_Float16*)(ws + p.off_vt), st));
+            HIP_TRY(prof_end(st, &sp));
+        }
         HIP_TRY(prof_begin(st, 3, &sp));
         const long long tasks = (long long)g.units * a.G * g.q_blocks;
         float* part_acc = n_split > 1 ? (float*)(ws + p.off_part) : nullptr;
         float2* part_ml = n_split > 1 ? (float2*)(part_acc + tasks * n_split * 32 * a.d) : nullptr;
-        HIP_TRY(launch_attend_prefill(g, (const _Float16*)(ws + p.off_kr), (const _Float16*)(ws + p.off_vt), qp, cs, op,
+        HIP_TRY(launch_attend_prefill(g, direct ? &tab : nullptr, (const _Float16*)(ws + p.off_kr), (const _Float16*)(ws + p.off_vt), qp, cs, op,
                                       lse ? lse + head0 * q_len : nullptr, part_acc, part_ml, st));
         HIP_TRY(prof_end(st, &sp));
     }

@@ -312,9 +312,15 @@ __host__ __device__ inline int prefill_first_wg(int cur_len, int q_len, int G, i
 hipError_t launch_prefill_cs(float2* cs, int rows, int d, double rope_base, int rope, hipStream_t st);
 // Kr, Vt: [units][key_tiles] tiles of 32 keys x d fp16 in fragment order.
 hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, const float2* cs, _Float16* Kr, _Float16* Vt, hipStream_t st);
+// Offsets of a head's rows and of their cos/sin, a tile beyond the last, are within 31 bits (the attention kernel reads the cached rows as a buffer).
+inline bool prefill_direct_fits(int cur_len, long long stride_token)
+{
+    return stride_token < (1LL << 30) && ((long long)cur_len + 32) * (stride_token > 256 ? stride_token : 256) * 2 < (1LL << 31);
+}
+// With tab, keys and values come from the cached rows, without it from Kr and Vt.
 // q: dense [units*G][q_len][d] bf16, rotated inside the attention kernel.  part_acc, part_ml (n_split > 1): per (task, part)
 // 32 x d fp32 and 32 x (reference point, sum).
-hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
+hipError_t launch_attend_prefill(const PrefillGeom& g, const SlabTable* tab, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
                                  void* out, float* lse, float* part_acc, float2* part_ml, hipStream_t st);
 
 }  // namespace freqkv

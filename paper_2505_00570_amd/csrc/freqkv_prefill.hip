@@ -17,7 +17,8 @@
 // and k_attend_prefill first builds, per wave, Qr = rotate(q) * log2(e)/sqrt(d) for its 32 queries in
 // registers (once), then computes S^T = Kr Qr^T for 32 keys x 32 queries at a time, the running softmax per
 // query (a query is a column, so its sum is an in-lane reduction plus one exchange between the two
-// half-waves at the end), and O^T += Vt P^T.
+// half-waves at the end), and O^T += Vt P^T.  Where few workgroups use a tile there is no such pass: k_attend_prefill<.., true> reads the cached
+// rows and makes the tiles of them itself, in LDS.
 #include "freqkv_internal.h"
 
 namespace freqkv {
@@ -48,6 +49,8 @@ constexpr int kKeyTile = 32;       // keys per tile
 constexpr int kQPerWave = 32;      // queries per wave
 constexpr int kPrefillWaves = 8;   // waves per workgroup of the attention kernel
 constexpr int kTileBytes = kKeyTile * kD * 2;   // one Kr or Vt tile, fp16
+constexpr int kAnchor = 8;         // tiles
+constexpr int kBufferFlags = 0x00020000;        // fourth word of a buffer's descriptor: raw, 32-bit elements
 constexpr float kSlack = 14.0f;    // log2 of the largest un-rescaled softmax weight (an fp16 operand: < 2^16)
 constexpr float kWeightLimit = 16384.0f;   // 2^kSlack
 
@@ -60,6 +63,10 @@ __device__ __forceinline__ half2v pack_half2(float a, float b)
     f32x2 v = {a, b};
     return __builtin_convertvector(v, half2v);          // round to nearest even, one packed conversion
 }
+
+// What the attention kernel reads keys and values from: the operands that k_prefill_prep wrote, or the cached rows themselves.
+template <bool DIRECT> struct KeysAndValues { const _Float16 *Kr, *Vt; };
+template <> struct KeysAndValues<true> { SlabTable tab; };
 
 // Position of the key that sits at storage index s (0..31) of a Vt tile: the matrix core leaves a
 // 32x32 result with register r of a lane in half-wave hw at row 8*(r/4) + 4*hw + r%4; k-step t of the
@@ -184,13 +191,17 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
 // of the key range more, or none, and no merging kernel.  With 8 KV heads of 4 query heads 1000 queries on 1000 rows 34.2 us in one stream,
 // 24.2 in halves; 100 on 1000 25.2 in 3 parts, 21.8 in 3 parts of halves; prefill_cut has more of them.  A step of one tile of each half takes 1.08
 // times that of eight tasks (twice the copies).
-template <int HALVES>
+// DIRECT: keys and values come from the cached rows; a tile is asked for a step and a half ahead of its use, into registers, and rotated, turned and
+// written to LDS between the matrix instructions of the weighted sum.  That is 50 (in halves 110) vector instructions per thread and step beside some 80,
+// and 16 KB (in halves 4) of cos and sin through the 64 bytes per cycle of a compute unit beside 16 (32) of keys and values: 0.21 us per step,
+// 0.475 in halves (0.53 with cos and sin from the table for every tile, as in one stream, where turning them on instead makes 0.23).  Rows touched
+// ahead of time, so that they come from the L2, changed nothing.  prefill_direct says which calls gain by it.
+template <int HALVES, bool DIRECT>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
-void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const _Float16* __restrict__ Vt,
-                      const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
-                      float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml)
+void k_attend_prefill(const PrefillGeom, const uint16_t* __restrict__ q, const float2* __restrict__ cs, uint16_t* __restrict__ out,
+                      float* __restrict__ lse, float* __restrict__ part_acc, float2* __restrict__ part_ml, const KeysAndValues<DIRECT> kv)
 {
-    const PrefillGeom g = first_argument<decltype(k_attend_prefill<HALVES>)>();
+    const PrefillGeom g = first_argument<decltype(k_attend_prefill<HALVES, DIRECT>)>();
     constexpr int TASKS = kPrefillWaves / HALVES;                        // of a workgroup
     __shared__ __attribute__((aligned(1024))) char ring[HALVES][2][4][kTileBytes];   // of each half: Kr tiles t+1, t+2, t+3 of step t, Vt tiles t .. t+3
     constexpr int QUERIES = 32 * kD * 2, ORIGIN = HALVES == 1 ? (kD / 2) * 8 : 0;
@@ -271,11 +282,16 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     f32x16 negm;                // -m in every register: the accumulator input of the first score instruction of a tile
     static_for<16>([&](auto r) { negm[r.value] = 0.f; });
 
-    const char* ksrc = (const char*)(Kr + (long long)unit * g.key_tiles * (kKeyTile * kD));
-    const char* vsrc = (const char*)(Vt + (long long)unit * g.key_tiles * (kKeyTile * kD));
+    const char *ksrc = nullptr, *vsrc = nullptr;
+    if constexpr (!DIRECT) {
+        ksrc = (const char*)(kv.Kr + (long long)unit * g.key_tiles * (kKeyTile * kD));
+        vsrc = (const char*)(kv.Vt + (long long)unit * g.key_tiles * (kKeyTile * kD));
+    }
     constexpr int PIECE = kTileBytes / TASKS;          // of a tile, per wave
     const int tid16 = tw * PIECE + lane * 16;
-    const int frag = (hw * kKeyTile + l32) * 16;       // this lane's 16 bytes inside a k-step of a tile
+    // this lane's 16 bytes inside a k-step of a tile (keys in even and odd k-steps; values)
+    const int frag[2] = {(hw * kKeyTile + (DIRECT ? l32 ^ 4 * hw : l32)) * 16, (hw * kKeyTile + (DIRECT ? l32 ^ (8 + 4 * hw) : l32)) * 16};
+    const int vfrag = (hw * kKeyTile + (DIRECT ? l32 >> 1 | (l32 & 1) << 4 : l32)) * 16;
 
     // Step t consumes tile t: it computes S(t+1) = Kr(t+1) Qr^T while the softmax of S(t) runs, then
     // O^T += Vt(t) P(t)^T.  Kr(t+3) and Vt(t+3) are requested at the start of step t, straight into their ring
@@ -298,6 +314,94 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     // Copies past the last tile are not branched around: they repeat the last tile into a slot that nobody
     // reads any more, which keeps the loop free of branches.
     const int last_tile = (t1 > t0 ? t1 : wg_tiles) - 1;
+    // DIRECT: a thread has its piece of a tile in registers, asked for a step ahead: 4 pairs of a key (in halves of two, 16 rows apart), which it
+    // rotates, and 4 (8) keys of two channels, which it turns.  Rows beyond cur_len are read as zero, past the end of the buffer.  Keys lie in LDS at
+    // place key ^ 4 (group of 8 channels & 3) of their group, channels at place c / 2 + 16 (c & 1) of their block, so that the writes of
+    // a wave go to different banks, as do the reads.  The cos and sin of a thread's pairs turn on by 32 (16) rows with each key, and
+    // come from the table again every kAnchor tiles (1e-6 by then, beside the 5e-4 of the operands' fp16).
+    constexpr int NK = HALVES, P = 4, NV = 4 * HALVES;       // keys, pairs, values per channel of a thread
+    struct Staged { u32x2 lo[NK], up[NK]; f32x4 angle[2]; uint32_t v[NV]; } sg;            // angle: (cos, sin) of 4 pairs at the first key
+    f32x4 turn_by[2];                                  // of the 16 rows between keys
+    __amdgpu_buffer_rsrc_t kbuf, vbuf, cbuf;
+    uint32_t koff = 0, voff = 0, coff = 0, row_bytes = 0;
+    char *kput = nullptr, *vput = nullptr;             // in slot 0
+    if constexpr (DIRECT) {
+        const int layer = unit / g.units_per_layer, rem = unit - layer * g.units_per_layer;
+        const int b = rem / g.n_kv, kvh = rem - b * g.n_kv;
+        const long long at = (long long)b * g.stride_batch + (long long)kvh * g.stride_head;
+        const int size = (int)(((long long)(g.cur_len - 1) * g.stride_token + kD) * 2);
+        kbuf = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint16_t*)kv.tab.base[2 * layer] + at), 0, size, kBufferFlags);
+        vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint16_t*)kv.tab.base[2 * layer + 1] + at), 0, size, kBufferFlags);
+        cbuf = __builtin_amdgcn_make_buffer_rsrc((void*)cs, 0, g.cur_len * (kD / 2) * 8, kBufferFlags);
+        row_bytes = (uint32_t)g.stride_token * 2;
+        constexpr int KW = 4 / HALVES;                 // waves, of 8 keys each
+        const int key = (lane >> 3) + 8 * (tw % KW), j0 = tw / KW * 32 + (lane & 7) * P, g8 = j0 / 8;
+        koff = key * row_bytes + j0 * 2;
+        coff = key * (kD / 2 * 8) + j0 * 8;
+        kput = ksm[0] + g8 * (kKeyTile * 16) + (key ^ 4 * (g8 & 3)) * 16 + j0 % 8 * 2;
+        const int oct = HALVES == 1 ? tw >> 1 : tw, first = HALVES == 1 ? tw & 1 : 0;      // 8 keys of the tile (k-step, half-wave); which 4 of them
+        voff = vt_key(8 * oct + 4 * first) * row_bytes + lane * 4;
+        vput = vsm[0] + (((lane >> 4) * 4 + oct) * kKeyTile + (lane & 15)) * 16 + first * 8;
+    }
+    auto cs_at = [&](uint32_t at, f32x4 (&x)[2]) {
+        static_for<2>([&](auto i) { x[i.value] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(cbuf, at + i.value * 16, 0, 0)); });
+    };
+    auto ask_k = [&](Staged& x, int tile) {
+        if (HALVES == 1 || ((tile - t0) & (kAnchor - 1)) == 0) cs_at(coff + tile * (kKeyTile * kD / 2 * 8), x.angle);
+        static_for<NK>([&](auto k) {
+            const uint32_t at = koff + (tile * kKeyTile + k.value * 16) * row_bytes;
+            x.lo[k.value] = __builtin_amdgcn_raw_buffer_load_b64(kbuf, at, 0, 0);
+            x.up[k.value] = __builtin_amdgcn_raw_buffer_load_b64(kbuf, at + kD, 0, 0);
+        });
+    };
+    auto ask_v = [&](Staged& x, int tile) {
+        static_for<NV>([&](auto e) {
+            x.v[e.value] = __builtin_amdgcn_raw_buffer_load_b32(vbuf, voff + (tile * kKeyTile + (e.value / 4 * 8 + e.value % 4)) * row_bytes, 0, 0);
+        });
+    };
+    // (the empty assembly keeps what follows where it stands, behind the matrix instruction before it)
+    u32x2 hk[2];                                       // what goes to LDS: lower and upper half of the channels of a key
+    uint32_t hv[2][NV / 2];                            // both channels
+    auto turn_k = [&](Staged& x, auto k, auto i) {     // two pairs of a key
+        constexpr int K = decltype(k)::value, I = decltype(i)::value;
+        uint32_t lo = x.lo[K][I], up = x.up[K][I];
+        asm volatile("" : "+v"(lo), "+v"(up));
+        const float a0 = bf16_lo(lo), a1 = bf16_hi(lo), b0 = bf16_lo(up), b1 = bf16_hi(up);
+        const f32x4 c = x.angle[I];
+        hk[0][I] = __builtin_bit_cast(uint32_t, pack_half2(a0 * c[0] - b0 * c[1], a1 * c[2] - b1 * c[3]));
+        hk[1][I] = __builtin_bit_cast(uint32_t, pack_half2(b0 * c[0] + a0 * c[1], b1 * c[2] + a1 * c[3]));
+        if constexpr (HALVES == 2) {
+            const f32x4 r = turn_by[I];
+            x.angle[I] = f32x4{c[0] * r[0] - c[1] * r[1], c[1] * r[0] + c[0] * r[1], c[2] * r[2] - c[3] * r[3], c[3] * r[2] + c[2] * r[3]};
+        }
+    };
+    auto turn_v = [&](Staged& x, auto i) {             // two keys
+        asm volatile("" : "+v"(x.v[2 * i.value]), "+v"(x.v[2 * i.value + 1]));
+        const uint32_t w0 = x.v[2 * i.value], w1 = x.v[2 * i.value + 1];
+        hv[0][i.value] = __builtin_bit_cast(uint32_t, pack_half2(bf16_lo(w0), bf16_lo(w1)));
+        hv[1][i.value] = __builtin_bit_cast(uint32_t, pack_half2(bf16_hi(w0), bf16_hi(w1)));
+    };
+    auto put_k = [&](int slot, auto k) {
+        char* const to = kput + (slot & 3) * kTileBytes + k.value * 256;               // (16 keys on: bit 4 of the place is no part of the exchange)
+        *(u32x2*)to = hk[0];
+        *(u32x2*)(to + kD / 16 * kKeyTile * 16) = hk[1];
+    };
+    auto put_v = [&](int slot) {
+        typedef uint32_t piece_t __attribute__((ext_vector_type(NV / 2)));
+        static_for<2>([&](auto c) {
+            piece_t w;
+            static_for<NV / 2>([&](auto i) { w[i.value] = hv[c.value][i.value]; });
+            *(piece_t*)(vput + (slot & 3) * kTileBytes + c.value * 256) = w;
+        });
+    };
+    auto take = [&](Staged& x, int slot) {
+        static_for<NK>([&](auto k) {
+            static_for<2>([&](auto i) { turn_k(x, k, i); });
+            put_k(slot, k);
+        });
+        static_for<NV / 2>([&](auto i) { turn_v(x, i); });
+        put_v(slot);
+    };
     // ---- queries of this wave: second operand of S^T = Kr Qr^T, lane = query column, 8 channels per k-step half.
     // Qr = rotate(q at its in-cache position) * log2(e)/sqrt(d), computed here once: the lane's groups of 8 channels in the lower half
     // (k-steps 0..3) and their rotary partners in the upper half (k-steps 4..7) are in its registers together.  A lane wants 16 bytes
@@ -344,8 +448,17 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         }
     }
     __syncthreads();
-    static_for<3>([&](auto i) { dma_k(min(t0 + i.value, last_tile), t0 + i.value); });
-    static_for<3>([&](auto i) { dma_v(min(t0 + i.value, last_tile), t0 + i.value); });
+    Staged early[3];
+    if constexpr (DIRECT) {
+        if constexpr (HALVES == 2) cs_at(16 * (kD / 2 * 8) + coff % (kD / 2 * 8), turn_by);
+        static_for<3>([&](auto i) {
+            ask_k(early[i.value], min(t0 + i.value, last_tile));
+            ask_v(early[i.value], min(t0 + i.value, last_tile));
+        });
+    } else {
+        static_for<3>([&](auto i) { dma_k(min(t0 + i.value, last_tile), t0 + i.value); });
+        static_for<3>([&](auto i) { dma_v(min(t0 + i.value, last_tile), t0 + i.value); });
+    }
     half8 qf[8];
     static_for<8>([&](auto s8) { qf[s8.value] = half8{}; });
     if (active) {
@@ -381,8 +494,18 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
             static_for<4>([&](auto i) { *(half8*)(turn + (i.value * 64 + lane) * 16) = mine[i.value]; });   // (the wave's own rows: it has read them)
         }
     }
-    // the keys of three tiles and the values of the first have landed, which is what the first step reads; it ends with all of them there
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (PIECE / 1024)) : "memory");
+    if constexpr (DIRECT) {
+        static_for<3>([&](auto i) {
+            if constexpr (HALVES == 2 && decltype(i)::value > 0) static_for<2>([&](auto j) { early[i.value].angle[j.value] = early[i.value - 1].angle[j.value]; });
+            take(early[i.value], t0 + i.value);
+        });
+        static_for<2>([&](auto j) { sg.angle[j.value] = early[2].angle[j.value]; });
+        ask_k(sg, min(t0 + 3, last_tile));
+        ask_v(sg, min(t0 + 3, last_tile));
+    } else {
+        // the keys of three tiles and the values of the first have landed, which is what the first step reads; it ends with all of them there
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (PIECE / 1024)) : "memory");
+    }
     __syncthreads();
     if constexpr (HALVES == 2) {
         if (active) {
@@ -394,19 +517,19 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     }
 
     half8 kf[8], vf[8];         // fragments of Kr(t+1) and Vt(t), read from LDS a few matrix instructions ahead
-    auto read_k = [&](auto s8, const char* kt) { kf[s8.value] = *(const half8*)(kt + s8.value * (2 * kKeyTile * 16)); };
+    auto read_k = [&](auto s8, const char* kt) { kf[s8.value] = *(const half8*)(kt + frag[s8.value % 2] + s8.value * (2 * kKeyTile * 16)); };
 
     // cur holds S(t) - m: the accumulators of the scores start at minus the query's reference point, so the
     // exponent needs no subtraction; nxt receives S(t+1) - m during step t; the two swap roles every step.
     f32x16 cur, nxt;
     static_for<16>([&](auto r) { cur[r.value] = 0.f; });
     if (my_tiles > t0) {
-        const char* kt = ksm[t0 & 3] + frag;
+        const char* kt = ksm[t0 & 3];
         static_for<8>([&](auto s8) {
             read_k(s8, kt);
             cur = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s8.value], qf[s8.value], cur, 0, 0, 0);
         });
-        static_for<2>([&](auto s8) { read_k(s8, ksm[(t0 + 1) & 3] + frag); });
+        static_for<2>([&](auto s8) { read_k(s8, ksm[(t0 + 1) & 3]); });
     }
 
     // Causal mask of a tile that reaches past the first query of the wave.
@@ -442,17 +565,19 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     // One step: tile t, whose scores minus m are in s, is consumed while the scores of tile t+1 go to n.
     bool first = true;          // the first tile sets the reference points whatever the scores are
     auto step = [&](int t, f32x16& s, f32x16& n) {
-        const bool mine = t < my_tiles;
+        const bool mine = DIRECT || t < my_tiles;
         if (mine) {
             if (t >= full_tiles) mask_tile(t, s);
             if (first) move_refs(s, true);
             first = false;
         }
-        dma_k(min(t + 3, last_tile), t + 3);
-        dma_v(min(t + 3, last_tile), t + 3);
+        if constexpr (!DIRECT) {
+            dma_k(min(t + 3, last_tile), t + 3);
+            dma_v(min(t + 3, last_tile), t + 3);
+        }
         if (mine) {
-            const char* kt = ksm[(t + 1) & 3] + frag;     // past the wave's last tile a stale slot: result unused
-            const char* vt = vsm[t & 3] + frag;
+            const char* kt = ksm[(t + 1) & 3];            // past the wave's last tile a stale slot: result unused
+            const char* vt = vsm[t & 3] + vfrag;
             auto read_v = [&](auto i) { vf[i.value] = *(const half8*)(vt + i.value * (2 * kKeyTile * 16)); };
             // ---- scores of the next tile on the matrix cores, dealt out between the exponentials of this tile
             // on the vector units: per 16-channel step one matrix instruction and two weights, packed to fp16
@@ -496,18 +621,51 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
                 const half8 pf = __builtin_bit_cast(half8, pw[k2.value]);
                 static_for<4>([&](auto db) {
                     if constexpr (decltype(k2)::value == 0) read_v(IC<decltype(db)::value * 2 + 1>{});   // second k-step
-                    else if constexpr (decltype(db)::value < 2) read_k(db, ksm[(t + 2) & 3] + frag);   // first fragments of the step after
+                    else if constexpr (decltype(db)::value < 2) read_k(db, ksm[(t + 2) & 3]);   // first fragments of the step after
                     acc[db.value] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[db.value * 2 + k2.value], pf, acc[db.value], 0, 0, 0);
+                    // tile t+3 goes to LDS between the matrix instructions, and tile t+4 is asked for
+                    if constexpr (DIRECT) {
+                        constexpr int S = decltype(k2)::value * 4 + decltype(db)::value;
+                        if constexpr (HALVES == 1 ? S % 2 == 0 && S < 4 : S < 4) turn_k(sg, IC<S / 2 % HALVES>{}, IC<HALVES == 1 ? S / 2 : S % 2>{});
+                        if constexpr (HALVES == 2 && S == 1) put_k(t + 3, IC<0>{});
+                        if constexpr (S == 3) {
+                            put_k(t + 3, IC<HALVES - 1>{});
+                            ask_k(sg, min(t + 4, last_tile));
+                        }
+                        if constexpr (S >= 4 && S % (2 / HALVES) == 0) turn_v(sg, IC<(S - 4) / (2 / HALVES)>{});
+                        if constexpr (S == 7) {
+                            put_v(t + 3);
+                            ask_v(sg, min(t + 4, last_tile));
+                        }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (!DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
-    for (int t = t0; t < t0 + steps; t += 2) {
-        step(t, cur, nxt);
-        if (t + 1 < t0 + steps) step(t + 1, nxt, cur);
+    if constexpr (DIRECT) {
+        // the steps that the wave has keys of, then those of the others' alone: in one loop, with a way for either, the compiler moves
+        // the registers of the loads in flight about and waits for them
+        int t = t0;
+        for (; t < my_tiles; t += 2) {
+            step(t, cur, nxt);
+            if (t + 1 >= my_tiles) { ++t; break; }
+            step(t + 1, nxt, cur);
+        }
+#pragma unroll 1
+        for (; t < t0 + steps; ++t) {
+            take(sg, t + 3);
+            ask_k(sg, min(t + 4, last_tile));
+            ask_v(sg, min(t + 4, last_tile));
+            __syncthreads();
+        }
+    } else {
+        for (int t = t0; t < t0 + steps; t += 2) {
+            step(t, cur, nxt);
+            if (t + 1 < t0 + steps) step(t + 1, nxt, cur);
+        }
     }
 
     // ---- normalise and store: lane = query, registers = channels 8*(r/4) + 4*hw + r%4 of each block
@@ -673,19 +831,28 @@ hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, co
     return hipGetLastError();
 }
 
-hipError_t launch_attend_prefill(const PrefillGeom& g, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
+hipError_t launch_attend_prefill(const PrefillGeom& g, const SlabTable* tab, const _Float16* Kr, const _Float16* Vt, const void* q, const float2* cs,
                                  void* out, float* lse, float* part_acc, float2* part_ml, hipStream_t st)
 {
     if (g.d != kD || g.q_blocks * kQPerWave != g.q_pad) return hipErrorInvalidValue;
     if (g.halves != 1 && g.halves != 2) return hipErrorInvalidValue;
+    if (tab ? !prefill_direct_fits(g.cur_len, g.stride_token) : !Kr || !Vt) return hipErrorInvalidValue;
     if (g.n_split < 1 || (g.n_split > 1 && (!part_acc || !part_ml || (long long)g.n_split * g.split_tiles < g.key_tiles))) return hipErrorInvalidValue;
     const int tasks = kPrefillWaves / g.halves, wgs_per_unit = (g.G * g.q_blocks + tasks - 1) / tasks;
     PrefillGeom gw = g;
     gw.wgs = 0;
     for (int s = 0; s < g.n_split; ++s) gw.wgs += wgs_per_unit - prefill_first_wg(g.cur_len, g.q_len, g.G, wgs_per_unit, tasks, s * g.split_tiles);
     const dim3 grid((unsigned)((long long)g.units * gw.wgs)), block(kPrefillWaves * 64);
-    if (g.halves == 2) hipLaunchKernelGGL(k_attend_prefill<2>, grid, block, 0, st, gw, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
-    else               hipLaunchKernelGGL(k_attend_prefill<1>, grid, block, 0, st, gw, Kr, Vt, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml);
+    auto launch = [&](auto kernel, const auto& kv) { hipLaunchKernelGGL(kernel, grid, block, 0, st, gw, (const uint16_t*)q, cs, (uint16_t*)out, lse, part_acc, part_ml, kv); };
+    if (tab) {
+        const KeysAndValues<true> kv = {*tab};
+        if (g.halves == 2) launch(k_attend_prefill<2, true>, kv);
+        else               launch(k_attend_prefill<1, true>, kv);
+    } else {
+        const KeysAndValues<false> kv = {Kr, Vt};
+        if (g.halves == 2) launch(k_attend_prefill<2, false>, kv);
+        else               launch(k_attend_prefill<1, false>, kv);
+    }
     if (g.n_split > 1)
         hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)((long long)g.units * g.G * g.q_blocks)), dim3(256), 0, st, g, part_acc, part_ml,
                            (uint16_t*)out, lse);
