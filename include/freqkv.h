@@ -156,7 +156,7 @@ typedef struct freqkv_profile {
 typedef struct freqkv_attend_plan {
     int32_t n_split;            /* row chunks each KV head's cache is cut into                       */
     int32_t chunk_rows;         /* rows per chunk                                                    */
-    int32_t heads_together;     /* query heads of one KV group that one workgroup serves (1, 2 or 4) */
+    int32_t heads_together;     /* query heads of one KV group that are worked out as one set (1, 2 or 4) */
     int32_t reserved;
     size_t  workspace_bytes;    /* scratch for the per-chunk softmax states; a longer cache may need less (fewer
                                    chunks suit it better)                                            */

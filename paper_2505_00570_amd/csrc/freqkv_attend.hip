@@ -612,12 +612,16 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
 // SHORT: chunks of up to 2 kReseed steps.
 // MANY: the heads are the queries of a chunk of g.q_len that has just been appended, g.G in all (for each head that shares the KV head all of the chunk), not
 // always a multiple of four; each has its own position, by which it is turned, and its own number of rows.
-template <typename T, int D, bool ONE, bool SHORT, bool MANY>
+// SETS: sets of four heads that a workgroup has.  Two of them share the rows' loads, unpacking and turning, 120 of 180 vector instructions per 8 rows; the
+// results are the same to the bit.  Calls with 8 query heads to a KV head, a set to a workgroup -> two, graphs of calls, rows from HBM: 8 layers x 20 x
+// 8 KV heads x 2143 rows 363 -> 291 us, 32 layers x 5 x 4 x 3806 322 -> 278, 5 x 16 x 310 of d = 256 217 -> 182, 8 x 56 x 8 x 488 of d = 64
+// 141 -> 117, fp32 56 x 8 x 1476 150 -> 120; two_sets has the others.
+template <typename T, int D, bool ONE, bool SHORT, bool MANY, int SETS>
 __global__ __launch_bounds__(kWaves * 64, 2)
 void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
                     float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
-    const AttGeom g = first_argument<decltype(k_attend_quads<T, D, ONE, SHORT, MANY>)>();
+    const AttGeom g = first_argument<decltype(k_attend_quads<T, D, ONE, SHORT, MANY, SETS>)>();
     constexpr int GT = 4, W = kWaves;
     constexpr int N = 8;                          // channels of a value, and pairs of a key, that a lane has
     constexpr int LPR = D / N, RPW = 64 / LPR;    // lanes that share a value, rows that a wave's lanes have one value of each
@@ -626,7 +630,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     constexpr int kReseedSteps = 2 * kReseed;
     typedef Raw<T, N> RawN;
 
-    constexpr int EB = D / 2 * (int)sizeof(RopeEntry), QB = GT * D * (int)sizeof(T), SB = 1024, TABLE = EB < SB ? SB : EB, QUERY = QB < SB ? SB : QB;
+    constexpr int EB = D / 2 * (int)sizeof(RopeEntry), QB = SETS * GT * D * (int)sizeof(T), SB = 1024, TABLE = EB < SB ? SB : EB, QUERY = QB < SB ? SB : QB;
     constexpr int ENDS = HSLOTS * GT * D * 4, STARTS = W * (TABLE + QUERY);
     __shared__ __attribute__((aligned(16))) float red[(ENDS > STARTS ? ENDS : STARTS) / 4];
     __shared__ __attribute__((aligned(16))) float xm[GT][W];
@@ -637,10 +641,10 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
 
     // (neighbours read the same rows, see k_attend_partial)
     int chunk_id = blockIdx.x, part = blockIdx.y;
-    if (g.G != GT && gridDim.y == 1) share_out(MANY ? (g.G + GT - 1) / GT : g.G / GT, chunk_id, part);
+    if (g.G != SETS * GT && gridDim.y == 1) share_out(MANY ? (g.G + GT - 1) / GT : g.G / (SETS * GT), chunk_id, part);
     const int unit = g.by_split.quotient(chunk_id);
     const int split = chunk_id - unit * g.n_split;
-    const int g0 = part * GT;                         // first query head of this workgroup inside the KV group
+    const int g0 = part * (SETS * GT);                // first query head of this workgroup inside the KV group
     const int layer = g.by_layer.quotient(unit);
     const int rem = unit - layer * g.units_per_layer;
     const int b = g.by_kv.quotient(rem);
@@ -703,19 +707,23 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     // ---- the lane's query, scaled by log2(e)/sqrt(d) so that exp is exp2, and the rotary state of its pairs: a pair couples channels j and D/2 + j.
     // (c, s) = cos/sin of ((row position - query position) * theta_j), so that the query stays as it is; each step advances them by the
     // fixed rotation (cd, sd) of its W SR rows, and every kReseedSteps they are recomputed exactly.
-    float c[N], s[N], cd[N], sd[N], ql[N], qh[N];
-    RawN qa, qb;
-    load_raw((const T*)(own + TABLE) + (lane & 3) * D + N * piece, qa);
-    load_raw((const T*)(own + TABLE) + (lane & 3) * D + D / 2 + N * piece, qb);
+    float c[N], s[N], cd[N], sd[N], ql[SETS][N], qh[SETS][N];
+    RawN qa[SETS], qb[SETS];
+    static_for<SETS>([&](auto h) {
+        load_raw((const T*)(own + TABLE) + (h.value * GT + (lane & 3)) * D + N * piece, qa[h.value]);
+        load_raw((const T*)(own + TABLE) + (h.value * GT + (lane & 3)) * D + D / 2 + N * piece, qb[h.value]);
+    });
     RopeEntry entries[N];
     static_for<N>([&](auto j) { entries[j.value] = ((const RopeEntry*)own)[N * piece + j.value]; });
-    unpack(qa, ql);
-    unpack(qb, qh);
-    static_for<N>([&](auto j) {
-        const float x = ql[j.value] * g.qscale, y = qh[j.value] * g.qscale;
-        const CosSin k0 = MANY ? seed_sincos(entries[j.value].theta, place + 1 - g.q_len) : CosSin{1.f, 0.f};
-        ql[j.value] = MANY ? x * k0.c - y * k0.s : x;
-        qh[j.value] = MANY ? y * k0.c + x * k0.s : y;
+    static_for<SETS>([&](auto h) {
+        unpack(qa[h.value], ql[h.value]);
+        unpack(qb[h.value], qh[h.value]);
+        static_for<N>([&](auto j) {
+            const float x = ql[h.value][j.value] * g.qscale, y = qh[h.value][j.value] * g.qscale;
+            const CosSin k0 = MANY ? seed_sincos(entries[j.value].theta, place + 1 - g.q_len) : CosSin{1.f, 0.f};
+            ql[h.value][j.value] = MANY ? x * k0.c - y * k0.s : x;
+            qh[h.value][j.value] = MANY ? y * k0.c + x * k0.s : y;
+        });
     });
     const int kp0 = wave_row0 + krow - q_pos;           // of the lane's key in the first step
     auto seed = [&](const RopeEntry (&entries)[N], int pos) {
@@ -733,13 +741,18 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     // (all of it ahead of the rows: moved into the loop's branch, frequencies and query would be awaited there, behind the rows)
     static_for<N>([&](auto j) {
         constexpr int J = j.value;
-        here(c[J]); here(s[J]); here(cd[J]); here(sd[J]); here(ql[J]); here(qh[J]);
+        here(c[J]); here(s[J]); here(cd[J]); here(sd[J]);
+        static_for<SETS>([&](auto h) { here(ql[h.value][J]); here(qh[h.value][J]); });
     });
 
     typedef float Acc4 __attribute__((ext_vector_type(4)));
-    float qm = kMinusBig, qsum = 0.f;                 // of the lane's head
-    Acc4 qacc[N];                                     // [channel][head]
-    static_for<N>([&](auto cc) { qacc[cc.value] = Acc4{0.f, 0.f, 0.f, 0.f}; });
+    float qm[SETS], qsum[SETS];                       // of the lane's head in each set
+    Acc4 qacc[SETS][N];                               // [channel][head]
+    static_for<SETS>([&](auto h) {
+        qm[h.value] = kMinusBig;
+        qsum[h.value] = 0.f;
+        static_for<N>([&](auto cc) { qacc[h.value][cc.value] = Acc4{0.f, 0.f, 0.f, 0.f}; });
+    });
 
     auto consume = [&](Rows& r, int it) {
         if constexpr (D < 256) swap_halves(r.kl, r.kh);
@@ -747,40 +760,49 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
         unpack(r.kl, a);
         unpack(r.kh, bb);
         // four rows, one to each lane of a quad, times four queries: [row] for the query of the lane
-        f32x4 of_rows = {0.f, 0.f, 0.f, 0.f};
+        f32x4 of_rows[SETS];
+        static_for<SETS>([&](auto h) { of_rows[h.value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
         static_for<N>([&](auto jj) {
             constexpr int j = jj.value;
-            of_rows = __builtin_amdgcn_mfma_f32_4x4x1f32(a[j] * c[j] - bb[j] * s[j], ql[j], of_rows, 0, 0, 0);
-            of_rows = __builtin_amdgcn_mfma_f32_4x4x1f32(bb[j] * c[j] + a[j] * s[j], qh[j], of_rows, 0, 0, 0);
+            const float lo = a[j] * c[j] - bb[j] * s[j], up = bb[j] * c[j] + a[j] * s[j];
+            static_for<SETS>([&](auto h) { of_rows[h.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(lo, ql[h.value][j], of_rows[h.value], 0, 0, 0); });
+            static_for<SETS>([&](auto h) { of_rows[h.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(up, qh[h.value][j], of_rows[h.value], 0, 0, 0); });
             const float cn = c[j] * cd[j] - s[j] * sd[j];
             s[j] = s[j] * cd[j] + c[j] * sd[j];
             c[j] = cn;
         });
         __builtin_amdgcn_sched_barrier(0);
-        float sc = row_score<D>(of_rows, lane);
-        if (row0 + (it + 1) * (W * SR) > seen && wave_row0 + it * (W * SR) + srow >= limit) sc = -INFINITY;
-        // The reference point m of the running softmax only moves when a score exceeds it by more than 2^kSlack, see k_attend_partial.  It is
-        // common to the two rows whose values a lane has.
-        const float mx = fold<LPR / 2>(sc, Max{});
-        const bool grow = mx > qm + kSlack;
-        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-            const float mn = grow ? mx : qm;
-            const float f = exp2_fast(qm - mn);
-            qm = mn;
-            qsum *= f;
-            static_for<GT>([&](auto gg) {
-                const float fh = quad_lane<gg.value>(f);
-                static_for<N>([&](auto cc) { qacc[cc.value][gg.value] *= fh; });
-            });
-        }
-        const float pw = exp2_fast(sc - qm);
-        qsum += pw;
-        const Pair weights = both<LPR / 2>(pw);
+        const bool masked = row0 + (it + 1) * (W * SR) > seen && wave_row0 + it * (W * SR) + srow >= limit;
+        Pair weights[SETS];
+        static_for<SETS>([&](auto h) {
+            float sc = row_score<D>(of_rows[h.value], lane);
+            if (masked) sc = -INFINITY;
+            // The reference point m of the running softmax only moves when a score exceeds it by more than 2^kSlack, see k_attend_partial.  It is
+            // common to the two rows whose values a lane has.
+            float& m = qm[h.value];
+            const float mx = fold<LPR / 2>(sc, Max{});
+            const bool grow = mx > m + kSlack;
+            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+                const float mn = grow ? mx : m;
+                const float f = exp2_fast(m - mn);
+                m = mn;
+                qsum[h.value] *= f;
+                static_for<GT>([&](auto gg) {
+                    const float fh = quad_lane<gg.value>(f);
+                    static_for<N>([&](auto cc) { qacc[h.value][cc.value][gg.value] *= fh; });
+                });
+            }
+            const float pw = exp2_fast(sc - m);
+            qsum[h.value] += pw;
+            weights[h.value] = both<LPR / 2>(pw);
+        });
         static_for<2>([&](auto u) {
             float va[N];
             unpack(r.v[u.value], va);
-            static_for<N>([&](auto cc) {
-                qacc[cc.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(weights.of[u.value], va[cc.value], qacc[cc.value], 0, 0, 0);
+            static_for<SETS>([&](auto h) {
+                static_for<N>([&](auto cc) {
+                    qacc[h.value][cc.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(weights[h.value].of[u.value], va[cc.value], qacc[h.value][cc.value], 0, 0, 0);
+                });
             });
         });
     };
@@ -825,36 +847,39 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     uint32_t none = 0;
     asm volatile("" : "+v"(none));
     const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
-    float scale[GT];
-    {
-        const float mx = fold_from<LPR>(qm, Max{});
-        if (ln < GT) xm[ln][wave] = mx;
+    static_for<SETS>([&](auto h) {
+        if constexpr (h.value > 0) lds_barrier();         // (the set before has been read)
+        float scale[GT];
+        {
+            const float mx = fold_from<LPR>(qm[h.value], Max{});
+            if (ln < GT) xm[ln][wave] = mx;
+            lds_barrier();
+            float M = kMinusBig;
+            static_for<W / 4>([&](auto w) {
+                const f32x4 of_waves = *(const f32x4*)&xm[ln & 3][4 * w.value];
+                M = fmaxf(M, fmaxf(fmaxf(of_waves[0], of_waves[1]), fmaxf(of_waves[2], of_waves[3])));
+            });
+            const float f = exp2_fast(qm[h.value] - M);
+            const float ls = fold_from<LPR / 2>(qsum[h.value] * f, Add{});
+            if (ln < GT) xl[ln][wave] = ls;
+            static_for<GT>([&](auto gg) { scale[gg.value] = quad_lane<gg.value>(f); });
+        }
+        // Two neighbouring lane groups are folded into one, the even one keeping the lower half of the lanes' channels and the odd one the upper,
+        // and park their sums in LDS.
+        static_for<GT>([&](auto gg) {
+            constexpr int gi = decltype(gg)::value;
+            f32x4 sum;
+            static_for<4>([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                sum[j] = fold_two<LPR>(qacc[h.value][j][gi] * scale[gi], qacc[h.value][4 + j][gi] * scale[gi], ln);
+            });
+            *(f32x4*)(red + ((wave * (RPW / 2) + (ln / LPR >> 1)) * GT + gi) * D + N * (ln % LPR) + (ln / LPR & 1) * 4) = sum;
+        });
         lds_barrier();
-        float M = kMinusBig;
-        static_for<W / 4>([&](auto w) {
-            const f32x4 of_waves = *(const f32x4*)&xm[ln & 3][4 * w.value];
-            M = fmaxf(M, fmaxf(fmaxf(of_waves[0], of_waves[1]), fmaxf(of_waves[2], of_waves[3])));
-        });
-        const float f = exp2_fast(qm - M);
-        const float ls = fold_from<LPR / 2>(qsum * f, Add{});
-        if (ln < GT) xl[ln][wave] = ls;
-        static_for<GT>([&](auto gg) { scale[gg.value] = quad_lane<gg.value>(f); });
-    }
-    // Two neighbouring lane groups are folded into one, the even one keeping the lower half of the lanes' channels and the odd one the upper,
-    // and park their sums in LDS.
-    static_for<GT>([&](auto gg) {
-        constexpr int gi = decltype(gg)::value;
-        f32x4 sum;
-        static_for<4>([&](auto jj) {
-            constexpr int j = decltype(jj)::value;
-            sum[j] = fold_two<LPR>(qacc[j][gi] * scale[gi], qacc[4 + j][gi] * scale[gi], ln);
-        });
-        *(f32x4*)(red + ((wave * (RPW / 2) + (ln / LPR >> 1)) * GT + gi) * D + N * (ln % LPR) + (ln / LPR & 1) * 4) = sum;
-    });
-    lds_barrier();
 
-    // 2. sum over the parked lane groups; two channels of one query head per thread and pass
-    finish_chunk<T, D, GT, W, HSLOTS, ONE>(red, xm, xl, tid_end, heads, head0, split, g.n_split, part_acc, part_ml, out, lse);
+        // 2. sum over the parked lane groups; two channels of one query head per thread and pass
+        finish_chunk<T, D, GT, W, HSLOTS, ONE>(red, xm, xl, tid_end, heads, head0 + h.value * GT, split, g.n_split, part_acc, part_ml, out, lse);
+    });
 }
 
 // One workgroup per query head merges the chunk states, normalises, stores.  D/2 threads cover the channels (two each), and
@@ -937,9 +962,9 @@ hipError_t launch_rope_table(RopeEntry* rt, int d, double base, hipStream_t st)
     return hipGetLastError();
 }
 
-static dim3 partial_grid(const AttGeom& g)
+static dim3 partial_grid(const AttGeom& g, int together)
 {
-    const long long chunks = (long long)g.units * g.n_split, parts = (g.G + g.GT - 1) / g.GT;
+    const long long chunks = (long long)g.units * g.n_split, parts = (g.G + together - 1) / together;
     return chunks * parts < 1 << 23 ? dim3((unsigned)(chunks * parts)) : dim3((unsigned)chunks, (unsigned)parts);   // (a launch has up to 2^32 threads per direction)
 }
 
@@ -947,7 +972,7 @@ template <typename T, int D, int GT, bool ONE, bool EXACT>
 static void launch_partial_o(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc,
                              float* part_ml, void* out, float* lse, hipStream_t st)
 {
-    const dim3 grid = partial_grid(g);
+    const dim3 grid = partial_grid(g, GT);
     hipLaunchKernelGGL((k_attend_partial<T, D, GT, attend_pairs_per_lane(D), ONE, EXACT>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
                        part_acc, part_ml, (T*)out, lse, tab);
 }
@@ -966,18 +991,35 @@ static void launch_partial_g(const SlabTable& tab, const AttGeom& g, const void*
                               : launch_partial_o<T, D, GT, false, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
 }
 
-template <typename T, int D, bool MANY>
+template <typename T, int D, bool MANY, int SETS>
 static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, const RopeEntry* rt, float* part_acc, float* part_ml, void* out,
                          float* lse, hipStream_t st)
 {
-    const dim3 grid = partial_grid(g);
+    const dim3 grid = partial_grid(g, 4 * SETS);
     const bool brief = g.chunk <= 2 * kReseed * kUnroll * attend_row_step(D);
     auto launch = [&](auto one, auto is_short) {
-        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
+        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY, SETS>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
                            part_acc, part_ml, (T*)out, lse, tab);
     };
-    if (g.n_split == 1) brief ? launch(IC<1>{}, IC<1>{}) : launch(IC<1>{}, IC<0>{});
-    else                brief ? launch(IC<0>{}, IC<1>{}) : launch(IC<0>{}, IC<0>{});
+    if constexpr (SETS > 1) {
+        // (left early, as SHORT leaves its loop at an odd step, the loop takes more registers than there are)
+        g.n_split == 1 ? launch(IC<1>{}, IC<0>{}) : launch(IC<0>{}, IC<0>{});
+    } else if (g.n_split == 1) {
+        brief ? launch(IC<1>{}, IC<1>{}) : launch(IC<1>{}, IC<0>{});
+    } else {
+        brief ? launch(IC<0>{}, IC<1>{}) : launch(IC<0>{}, IC<0>{});
+    }
+}
+
+// Two sets of four heads to a workgroup where it does not leave compute units idle: a workgroup takes 1.2 to 1.4 times as long, and there are half as
+// many.  Up to 128 of them would take every second compute unit (128 8.3 us for 6.8 at 8 KV heads of 8 x 100 rows, 16.5 for 12.6 at 400); 129 to 256 are one
+// to a compute unit instead of two of the others (152 8.2 for 9.2; 256 28.3 for 34.4 at 1500 rows); 257 to 384 two instead of three, which is as
+// long (0.94 to 1.13 times); more are faster again (392 12.4 for 15.4, 77 for 94 at 1500 rows).
+static bool two_sets(const AttGeom& g)
+{
+    if (g.G % 8) return false;
+    const long long wgs = (long long)g.units * g.n_split * (g.G / 8);
+    return wgs > 384 || (wgs > 128 && wgs <= 256);
 }
 
 template <typename T, int D>
@@ -985,7 +1027,10 @@ static hipError_t launch_partial_d(const SlabTable& tab, const AttGeom& g, const
                                    float* part_ml, void* out, float* lse, hipStream_t st)
 {
     switch (g.GT) {
-        case 4: launch_quads<T, D, false>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
+        case 4:
+            if (two_sets(g)) launch_quads<T, D, false, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+            else             launch_quads<T, D, false, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+            break;
         case 2: launch_partial_g<T, D, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 1: launch_partial_g<T, D, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         default: return hipErrorInvalidValue;
@@ -1024,7 +1069,7 @@ hipError_t launch_attend_many(const SlabTable& tab, const AttGeom& g, const void
     if (g.units < 1 || g.n_split < 1 || g.chunk < 1 || g.q_len < 1 || g.q_len > g.cur_len || g.G % g.q_len) return hipErrorInvalidValue;
     if ((long long)(g.n_split - 1) * g.chunk >= g.cur_len || (long long)g.n_split * g.chunk < g.cur_len) return hipErrorInvalidValue;
     if (g.d != 128 || g.GT != 4 || g.cur_lens || g.chunk % (kUnroll * attend_row_step(g.d))) return hipErrorInvalidValue;
-    launch_quads<uint16_t, 128, true>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+    launch_quads<uint16_t, 128, true, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
     return hipGetLastError();
 }
 
