@@ -1452,9 +1452,10 @@ freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_
 
 // Calls whose tiles are used by few workgroups read the cached rows as they are: there is no pass that writes them as operands first (7 ns per KV head
 // and tile of 32 keys, and its launch), but each workgroup turns every tile that it uses, 0.21 us more per tile, 0.475 per tile of each half.  The
-// constants are a least-squares fit to 300 shapes drawn over 1 to 32 KV heads, 1 to 8 query heads each, 1 to 4 layers, 1 to 4 sequences, 256 to 8192 rows
-// and 13 of them to all as queries, each timed both ways in graphs of calls, with 1 us to spare: 93 of them go this way, the longest 1.003 times as long as the
-// other way, the shortest a third.  Operands first -> rows as they are, us: 32 KV heads of one query head each, 4 sequences, 4046 rows, 20 queries 186 ->
+// figures are a least-squares fit to 300 shapes drawn over 1 to 32 KV heads, 1 to 8 query heads each, 1 to 4 layers, 1 to 4 sequences, 256 to 8192 rows
+// and 13 of them to all as queries, each timed both ways in graphs of calls.  With them as they are, 93 of these go this way, and of others near the line some
+// were 3 to 6 % slower (888 over 888, 2 layers, 2 sequences, 8 of 4: 57.5 -> 60); with the margin below it is 76, none of them slower, the shortest a third as
+// long.  Operands first -> rows as they are, us: 32 KV heads of one query head each, 4 sequences, 4046 rows, 20 queries 186 ->
 // 62; 2 layers, 2 sequences, 1693, 267 97 -> 61; 385, 385, 4 layers 33 -> 22; 794, 794, 2 sequences 41 -> 31; 8 KV heads of 4, 2 sequences, 5082, 121
 // 56 -> 45.  Not taken: 8 of 4, 5001, 301 52.1 -> 52.1; 1000, 1000 25.0 -> 29.8; 8192, 4094 385 -> 453; 32 of 1, 4261, 4261, 2 layers 382 -> 398.
 bool prefill_direct(const PrefillShape& p, int split_tiles, long long stride_token)
@@ -1463,7 +1464,7 @@ bool prefill_direct(const PrefillShape& p, int split_tiles, long long stride_tok
     const int tasks_per_unit = p.a.G * (p.q_pad / 32), first = (p.a.cur_len - p.q_len) / 32 + 1;
     const double wgs = (double)p.units * ((tasks_per_unit * p.halves + 7) / 8);
     const double steps = std::max((double)split_tiles, wgs * 0.5 * (p.key_tiles + first) / 256.0) / p.halves;     // of a compute unit
-    return 0.007 * (double)p.units * p.key_tiles > (p.halves == 2 ? 0.475 : 0.21) * steps + 0.2;
+    return 0.007 * (double)p.units * p.key_tiles > (p.halves == 2 ? 0.52 : 0.26) * steps + 0.6;
 }
 
 // Few queries go as so many heads of a decode call, by fours, which reads keys and values where they are and works in fp32.
