@@ -30,8 +30,8 @@ TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * (5.244e5 + 9.187e5) + 1.0 *
 TRAFFIC_BYTES_SINGLE_FOLD = {"llama3_8b_128k": (2.0 * 2.622e6 + 1.0 * 5.24e5) * 1024}
 # the same for the near/far form's single kernel (profiles/compress_llama3_8b_128k_pmc.txt)
 NEARFAR_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 8.286e5 + 1.0 * 5.24e5) * 1024}
-# the same for k_attend_partial (profiles/attend_llama3_8b_128k_pmc.txt)
-ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.288e5 + 1.0 * 1056) * 1024}
+# the same for the row-chunk kernel, k_attend_quads (profiles/attend_llama3_8b_128k_pmc.txt)
+ATTEND_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 5.247e5 + 1.0 * 1056) * 1024}
 # the same for k_attend_prefill (profiles/prefill_llama3_8b_128k.txt)
 PREFILL_TRAFFIC_BYTES_PER_LAUNCH = {"llama3_8b_128k": (2.0 * 1.448e6 + 1.0 * 1.049e6) * 1024}
 
@@ -133,7 +133,7 @@ def bench_attend(args, wl, dev):
         "gflops": p.flops / (dt / args.steps) / 1e9,
         "ms_partial_kernel": ms_kernel,
         "measured_copy_gbs": copy_gbs,
-        "roofline": {"bound": "hbm", "kernel": "k_attend_partial", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "hbm", "kernel": "k_attend_quads" if p.heads_together == 4 else "k_attend_partial", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": ATTEND_TRAFFIC_BYTES_PER_LAUNCH.get(args.workload),
                      "ms_per_launch": ms_kernel, "bytes_per_launch": bytes_launch, "measured_copy_gbs": copy_gbs,
                      "frac_of_measured_copy": gbs / copy_gbs},

@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
 // DIRECT: keys and values come from the cached rows; a tile is asked for a step and a half ahead of its use, into registers, and rotated, turned and
 // written to LDS between the matrix instructions of the weighted sum.  That is 50 (in halves 110) vector instructions per thread and step beside some 80,
 // and 16 KB (in halves 4) of cos and sin through the 64 bytes per cycle of a compute unit beside 16 (32) of keys and values: 0.21 us per step,
-// 0.475 in halves (0.53 with cos and sin from the table for every tile, as in one stream, where turning them on instead makes 0.23).  Rows touched
+// 0.475 in halves.  (In halves cos and sin turn on from key to key: whole calls 5 to 14 % faster than with the table for every tile, 39 queries over 8 x 6222 rows
+// 35.6 -> 30.7 us; in one stream, which has half as many bytes of them to load, 1 to 3 % slower so, 4 x 32 x 1302 86.8 -> 89.5.)  Rows touched
 // ahead of time, so that they come from the L2, changed nothing.  prefill_direct says which calls gain by it.
 template <int HALVES, bool DIRECT>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
