@@ -661,11 +661,13 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
         q_pos = cur_len - 1;
     }
     const int row0 = split * g.chunk;
-    const int row_end = min(row0 + g.chunk, cur_len);   // <= row0 for a chunk beyond a short sequence: no rows
     const int wave_row0 = row0 + wave * SR;
-    // MANY: of the lane's query, its place in the chunk of queries, and the rows that it sees; what all see
+    // MANY: places of the queries in their chunk, of the lane's and the least and the last of the set's, which may go on from the end of one head's
+    // chunk to the next head's; the rows that the lane's query sees, and that all of the set see.  No others than a query of the set sees are read.
     const int place = MANY ? g0 + (lane & 3) - g.by_q.quotient(g0 + (lane & 3)) * g.q_len : 0;
-    const int limit = MANY ? min(row_end, cur_len - g.q_len + 1 + place) : row_end, seen = MANY ? min(row_end, cur_len - g.q_len + 1) : row_end;
+    const int place0 = MANY ? g0 - g.by_q.quotient(g0) * g.q_len : 0, past = cur_len - g.q_len + 1;
+    const int row_end = min(row0 + g.chunk, MANY ? past + min(place0 + heads, g.q_len) - 1 : cur_len);   // <= row0 for a chunk beyond a short sequence: no rows
+    const int limit = MANY ? min(row_end, past + place) : row_end, seen = MANY ? min(row_end, past + (place0 + heads > g.q_len ? 0 : place0)) : row_end;
     const int nit = row_end > row0 ? (row_end - row0 + W * SR - 1) / (W * SR) : 0;
 
     // ---- what a lane has.  Keys: 8 pairs, 8 piece .. +7, of the row krow of a step; of values 8 channels of the rows vrow and vrow + 1; and the score of
@@ -772,7 +774,8 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
             c[j] = cn;
         });
         __builtin_amdgcn_sched_barrier(0);
-        const bool masked = row0 + (it + 1) * (W * SR) > seen && wave_row0 + it * (W * SR) + srow >= limit;
+        const bool tail = row0 + (it + 1) * (W * SR) > seen;
+        const bool masked = tail && wave_row0 + it * (W * SR) + srow >= limit;
         Pair weights[SETS];
         static_for<SETS>([&](auto h) {
             float sc = row_score<D>(of_rows[h.value], lane);
@@ -796,6 +799,35 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
             qsum[h.value] += pw;
             weights[h.value] = both<LPR / 2>(pw);
         });
+        if constexpr (MANY) {
+            // A value that is infinite or NaN is kept from the queries that do not see its row, whose weight of 0 would make it NaN.
+            if (tail) {
+                float none[2] = {0.f, 0.f};
+                static_for<2>([&](auto u) {
+                    float va[N];
+                    unpack(r.v[u.value], va);
+                    static_for<N>([&](auto cc) { none[u.value] = fmaf(va[cc.value], 0.f, none[u.value]); });
+                });
+                if (__builtin_amdgcn_ballot_w64(!(none[0] + none[1] == 0.f)) != 0) {
+                    static_for<2>([&](auto u) {
+                        const int row = wave_row0 + it * (W * SR) + vrow + u.value;
+                        float va[N];
+                        unpack(r.v[u.value], va);
+                        static_for<SETS>([&](auto h) {
+                            static_for<GT>([&](auto gg) {
+                                const float w = quad_lane<gg.value>(weights[h.value].of[u.value]);
+                                const bool sees = row < __float_as_int(quad_lane<gg.value>(__int_as_float(limit)));
+                                static_for<N>([&](auto cc) {
+                                    const float sum = qacc[h.value][cc.value][gg.value];
+                                    qacc[h.value][cc.value][gg.value] = sees ? fmaf(w, va[cc.value], sum) : sum;
+                                });
+                            });
+                        });
+                    });
+                    return;
+                }
+            }
+        }
         static_for<2>([&](auto u) {
             float va[N];
             unpack(r.v[u.value], va);
