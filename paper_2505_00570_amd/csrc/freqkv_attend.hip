@@ -57,6 +57,19 @@ __device__ __forceinline__ void load_raw(const float* p, Raw<float, 4>& r) { r.a
 __device__ __forceinline__ void load_raw(const uint16_t* p, Raw<uint16_t, 8>& r) { r.a = *(const u32x4*)p; }
 __device__ __forceinline__ void load_raw(const float* p, Raw<float, 8>& r) { r.a = *(const f32x4*)p; r.b = *(const f32x4*)(p + 4); }
 
+// ... of a buffer, which reads as zero past its end
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t b, uint32_t at, Raw<uint16_t, 4>& r) { r.a = __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, 0); }
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t b, uint32_t at, Raw<float, 4>& r)
+{
+    r.a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, 0));
+}
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t b, uint32_t at, Raw<uint16_t, 8>& r) { r.a = __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, 0); }
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t b, uint32_t at, Raw<float, 8>& r)
+{
+    r.a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, 0));
+    r.b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 16, 0));
+}
+
 template <int P> __device__ __forceinline__ void unpack(const Raw<uint16_t, P>& r, float (&f)[P])
 {
     static_for<P / 2>([&](auto i) {
@@ -388,23 +401,24 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     const int nit = row_end > row0 ? (row_end - row0 + STEP * U - 1) / (STEP * U) : 0;
     const int last = cur_len - 1;
     // Rows are addressed by 32-bit byte offsets inside the head's slab (uniform base + per-lane offset; the host
-    // checks the range).  Rows past the end re-read the last row: no load is conditional, so the loads in
-    // flight can be counted exactly; such rows are masked in the steps that can contain them.
+    // checks the range).  Of rows past the end of the chunk the values are zero, from past the end of a buffer (times a weight of 0 an infinite
+    // value would be NaN), and the keys those of other rows, the last one's at most, and masked in the steps that can contain them: no load is
+    // conditional, so the loads in flight can be counted exactly.
     const char* kb = (const char*)kbase;
-    const char* vb = (const char*)vbase;
     const uint32_t row_bytes = (uint32_t)g.stride_token * (uint32_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)(P * l) * (uint32_t)sizeof(T);
     const uint32_t last_off = (uint32_t)last * row_bytes + lane_off;
+    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)vbase, 0, (int)((uint32_t)max(row_end - 1, 0) * row_bytes + (uint32_t)(D * sizeof(T))), kBufferFlags);
     uint32_t next_off = (uint32_t)p0 * row_bytes + lane_off;      // first row of the step to be loaded next
     struct Rows { RawT kl[U], kh[U], vl[U], vh[U]; };
     auto issue = [&](Rows& r) {
         static_for<U>([&](auto uu) {
             constexpr int u = decltype(uu)::value;
-            const uint32_t o = min(next_off + (uint32_t)(u * STEP) * row_bytes, last_off);
+            const uint32_t at = next_off + (uint32_t)(u * STEP) * row_bytes, o = min(at, last_off);
             load_raw((const T*)(kb + o), r.kl[u]);
             load_raw((const T*)(kb + o) + D / 2, r.kh[u]);
-            load_raw((const T*)(vb + o), r.vl[u]);
-            load_raw((const T*)(vb + o) + D / 2, r.vh[u]);
+            load_raw(vbuf, at, r.vl[u]);
+            load_raw(vbuf, at + D / 2 * (uint32_t)sizeof(T), r.vh[u]);
         });
         next_off += (uint32_t)(U * STEP) * row_bytes;
     };
@@ -674,14 +688,16 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     // row srow.  Keys are requested in pieces of 16 bytes (fp32: 32), a quad of lanes having the same piece of four rows (asked for 8 bytes each,
     // they come at 4.7 TB/s instead of 6.1).  With 64 or 128 channels the lower half-wave has the lower channels of the first half of a step's rows and the upper
     // the upper ones; the next load has the other rows, and the half-waves trade.
-    // Rows are addressed by 32-bit byte offsets inside the head's slab (the host checks the range); rows past the end of the chunk are
-    // its last row again, and masked: no load is conditional, so the loads in flight can be counted exactly.
+    // Rows are addressed by 32-bit byte offsets inside the head's slab (the host checks the range).  Of rows past the end of the chunk the keys are its
+    // last row's again, and masked, and the values zero, from past the end of a buffer (times a weight of 0 an infinite value would be NaN): no load is
+    // conditional, so the loads in flight can be counted exactly.
     const int piece = D == 256 ? lane >> 2 : D == 128 ? lane >> 2 & 7 : lane >> 2 & 3;
     const int krow = lane / (D / 4) * 4 + (lane & 3), srow = lane / (LPR / 2), vrow = 2 * (lane / LPR);
     const uint32_t row_bytes = (uint32_t)g.stride_token * (uint32_t)sizeof(T);
     const uint32_t last_off = (uint32_t)max(row_end - 1, 0) * row_bytes;
-    const uint32_t kfrom = (uint32_t)(D < 256 ? krow & (SR / 2 - 1) : krow) * row_bytes, vfrom = (uint32_t)vrow * row_bytes;
-    const uint32_t kpart = (uint32_t)(N * piece + (D < 256 && lane >= 32 ? D / 2 : 0)) * (uint32_t)sizeof(T), vpart = (uint32_t)(N * (lane % LPR)) * (uint32_t)sizeof(T);
+    const uint32_t kfrom = (uint32_t)(D < 256 ? krow & (SR / 2 - 1) : krow) * row_bytes, vfrom = (uint32_t)vrow * row_bytes + (uint32_t)(N * (lane % LPR)) * (uint32_t)sizeof(T);
+    const uint32_t kpart = (uint32_t)(N * piece + (D < 256 && lane >= 32 ? D / 2 : 0)) * (uint32_t)sizeof(T);
+    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)vb, 0, (int)(last_off + (uint32_t)(D * sizeof(T))), kBufferFlags);
     uint32_t next_at = (uint32_t)wave_row0 * row_bytes;
     struct Rows { RawN kl, kh, v[2]; };
     auto issue = [&](Rows& r) {
@@ -689,7 +705,7 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
         load_raw((const T*)(kb + o), r.kl);
         if constexpr (D == 256) load_raw((const T*)(kb + o) + D / 2, r.kh);
         else                    load_raw((const T*)(kb + (min(next_at + SR / 2 * row_bytes + kfrom, last_off) + kpart)), r.kh);
-        static_for<2>([&](auto u) { load_raw((const T*)(vb + (min(next_at + u.value * row_bytes + vfrom, last_off) + vpart)), r.v[u.value]); });
+        static_for<2>([&](auto u) { load_raw(vbuf, next_at + u.value * row_bytes + vfrom, r.v[u.value]); });
         next_at += (uint32_t)(W * SR) * row_bytes;
     };
     // Frequencies and queries, then the rows of two steps, all requested together ahead of the seeds: loads come back in order.  Each wave asks for

@@ -22,6 +22,8 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, const void* base, uint32
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(offset), "s"(base) : "memory");
 }
 
+constexpr int kBufferFlags = 0x00020000;        // fourth word of a buffer's descriptor: raw, 32-bit elements
+
 // What a kernel's arguments take, from its type.
 template <class Kernel> struct Arguments;
 template <class A, class... More> struct Arguments<void(A, More...)> {

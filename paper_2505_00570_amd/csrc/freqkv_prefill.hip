@@ -51,7 +51,6 @@ constexpr int kPrefillWaves = 8;   // waves per workgroup of the attention kerne
 constexpr int kTileBytes = kKeyTile * kD * 2;   // one Kr or Vt tile, fp16
 constexpr int kAnchor = 8;         // tiles
 constexpr int kTilesByRows = 32;   // from so many on, k_prefill_prep's workgroups stand by rows
-constexpr int kBufferFlags = 0x00020000;        // fourth word of a buffer's descriptor: raw, 32-bit elements
 constexpr float kSlack = 14.0f;    // log2 of the largest un-rescaled softmax weight (an fp16 operand: < 2^16)
 constexpr float kWeightLimit = 16384.0f;   // 2^kSlack
 
