@@ -288,6 +288,14 @@ __global__ void k_rope_table(RopeEntry* rt, int d, double base, int step)
     rt[i] = e;
 }
 
+// The lane's index, counted again: kept across a loop, with what derives from it, it would not fit the registers of the longest kernels.
+__device__ __forceinline__ int lane_index()
+{
+    uint32_t none = 0;
+    asm volatile("" : "+v"(none));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+}
+
 // Workgroups that read the same rows, for query heads beyond those of one, follow each other on one XCD (they are dealt round-robin to 8) and
 // find them in its L2 (8 query heads to each of 4 KV heads x 8192 rows x 32 layers 181 -> 159 us, of 8 x 4000 x 32 167 -> 155; with all
 // first parts ahead of all second ones, rows came from memory again).
@@ -568,10 +576,7 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
     // ---- combine the lane groups of the workgroup
     // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS; then sums, and accumulators
     // rescaled.
-    // (the lane's index is counted again: kept across the loop with what derives from it, it would not fit the registers of the longest kernel)
-    uint32_t none = 0;
-    asm volatile("" : "+v"(none));
-    const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
+    const int ln = lane_index(), tid_end = wave * 64 + ln;
     float scale[GT];
     {
         static_for<GT>([&](auto gg) {
@@ -630,8 +635,10 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
 // results are the same to the bit.  Calls with 8 query heads to a KV head, a set to a workgroup -> two, graphs of calls, rows from HBM: 8 layers x 20 x
 // 8 KV heads x 2143 rows 363 -> 291 us, 32 layers x 5 x 4 x 3806 322 -> 278, 5 x 16 x 310 of d = 256 217 -> 182, 8 x 56 x 8 x 488 of d = 64
 // 141 -> 117, fp32 56 x 8 x 1476 150 -> 120; two_sets has the others.
+// Of bf16 workgroups of one set three fit a compute unit, which is what 513 to 768 of them want (the loop for long chunks had two registers too many: 576
+// workgroups of 4400 rows 267 us, 259 by threes).
 template <typename T, int D, bool ONE, bool SHORT, bool MANY, int SETS>
-__global__ __launch_bounds__(kWaves * 64, 2)
+__global__ __launch_bounds__(kWaves * 64, sizeof(T) == 2 && SETS == 1 && !MANY ? 3 : 2)
 void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
                     float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
@@ -691,8 +698,9 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     // Rows are addressed by 32-bit byte offsets inside the head's slab (the host checks the range).  Of rows past the end of the chunk the keys are its
     // last row's again, and masked, and the values zero, from past the end of a buffer (times a weight of 0 an infinite value would be NaN): no load is
     // conditional, so the loads in flight can be counted exactly.
-    const int piece = D == 256 ? lane >> 2 : D == 128 ? lane >> 2 & 7 : lane >> 2 & 3;
-    const int krow = lane / (D / 4) * 4 + (lane & 3), srow = lane / (LPR / 2), vrow = 2 * (lane / LPR);
+    auto piece_of = [](int lane) { return D == 256 ? lane >> 2 : D == 128 ? lane >> 2 & 7 : lane >> 2 & 3; };
+    auto krow_of = [](int lane) { return lane / (D / 4) * 4 + (lane & 3); };
+    const int piece = piece_of(lane), krow = krow_of(lane), srow = lane / (LPR / 2), vrow = 2 * (lane / LPR);
     const uint32_t row_bytes = (uint32_t)g.stride_token * (uint32_t)sizeof(T);
     const uint32_t last_off = (uint32_t)max(row_end - 1, 0) * row_bytes;
     const uint32_t kfrom = (uint32_t)(D < 256 ? krow & (SR / 2 - 1) : krow) * row_bytes, vfrom = (uint32_t)vrow * row_bytes + (uint32_t)(N * (lane % LPR)) * (uint32_t)sizeof(T);
@@ -882,19 +890,17 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (it >= nit) break;
+            const int ln = lane_index();
             RopeEntry again[N];
-            static_for<N>([&](auto j) { again[j.value] = rt[D / 2 + N * piece + j.value]; });
-            seed(again, kp0 + it * (W * SR));
+            static_for<N>([&](auto j) { again[j.value] = rt[D / 2 + N * piece_of(ln) + j.value]; });
+            seed(again, wave_row0 + krow_of(ln) - q_pos + it * (W * SR));
         }
     }
 
     // ---- combine the lane groups of the workgroup
     // 1. common maximum per query head: over the lane groups of a wave by lane swaps, over waves through LDS; then sums, and accumulators
     // rescaled, one head to a lane of each quad.
-    // (the lane's index is counted again: kept across the loop with what derives from it, it would not fit the registers)
-    uint32_t none = 0;
-    asm volatile("" : "+v"(none));
-    const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)), tid_end = wave * 64 + ln;
+    const int ln = lane_index(), tid_end = wave * 64 + ln;
     static_for<SETS>([&](auto h) {
         if constexpr (h.value > 0) lds_barrier();         // (the set before has been read)
         float scale[GT];
@@ -1044,10 +1050,14 @@ static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, 
                          float* lse, hipStream_t st)
 {
     const dim3 grid = partial_grid(g, 4 * SETS);
+    // Long chunks: more workgroups than three to each compute unit go by twos, held apart by LDS that they do not use, so that the last
+    // round has more of them (4400 rows, by threes -> by twos: 800 workgroups 353 -> 328 us, 896 371 -> 362, 1024 397 -> 395, 1280 496 -> 495, 2048 787 -> 780; up to three
+    // all are there at once, and 576 of them take 259 instead of 266).
+    const unsigned apart = (long long)grid.x * grid.y > 3 * 256 ? 40 << 10 : 0;
     const bool brief = g.chunk <= 2 * kReseed * kUnroll * attend_row_step(D);
     auto launch = [&](auto one, auto is_short) {
-        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY, SETS>), grid, dim3(kWaves * 64), 0, st, g, (const T*)q, rt,
-                           part_acc, part_ml, (T*)out, lse, tab);
+        hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY, SETS>), grid, dim3(kWaves * 64),
+                           decltype(is_short)::value ? 0 : apart, st, g, (const T*)q, rt, part_acc, part_ml, (T*)out, lse, tab);
     };
     if constexpr (SETS > 1) {
         // (left early, as SHORT leaves its loop at an odd step, the loop takes more registers than there are)
