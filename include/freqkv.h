@@ -346,8 +346,9 @@ FREQKV_API freqkv_status_t freqkv_attend_prefill_plan(const freqkv_layout_t* lay
  * fp16 (cache values are exact in fp16; rotated keys and queries keep 11 significant bits), accumulation,
  * softmax and the running sums are fp32; with up to 4 queries in all heads of a KV head, and with up to 64 where that is
  * faster, everything is fp32, as in freqkv_attend_decode.  The call only enqueues work on `stream`.  The cos/sin of the row positions is
- * kept per (device, rope_base), 512 bytes per row, up to 65536 rows and 16 tables per device; calls beyond that, and
- * first calls inside a stream capture, compute it into their workspace (some 5 us more).
+ * kept per (device, rope_base), 512 bytes per row, up to 65536 rows and 16 tables per device, and for calls in fp32 the frequencies,
+ * 2 KB, up to 16 tables per device with those of freqkv_attend_decode; calls beyond that, first calls inside a stream capture, and calls
+ * that there is no memory for, compute it into their workspace (some 5 us more).
  */
 FREQKV_API freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* v, void* out,
                                       float* lse, const freqkv_layout_t* layout, int n_q_heads,

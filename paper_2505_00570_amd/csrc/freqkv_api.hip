@@ -480,8 +480,11 @@ struct RopeKey {
     bool operator<(const RopeKey& o) const { return std::tie(device, d, base) < std::tie(o.device, o.d, o.base); }
 };
 std::map<RopeKey, BasisEntry> g_rope;
+// What chunk-wise calls keep per device at most: of these tables (those of decode calls count, which are kept whatever their number), and of the cos/sin below.
+constexpr int kMostTables = 16;
 
-// ws: where a call whose stream is being captured has its table if there is none yet (nothing is allocated then); null: a caller that may allocate.
+// ws: where a call has its table if there is none yet and none is to be allocated, as its stream is being captured or there are kMostTables, or if there is no
+// memory for it; null: a caller that allocates.
 freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** out, void* ws = nullptr)
 {
     int dev = 0;
@@ -490,19 +493,25 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
     std::lock_guard<std::mutex> lock(g_mu);
     auto it = g_rope.find(key);
     if (it == g_rope.end()) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (ws) HIP_TRY(hipStreamIsCapturing(st, &cap));
-        if (cap != hipStreamCaptureStatusNone) {
-            HIP_TRY(launch_rope_table((RopeEntry*)ws, d, base, st));
-            *out = (RopeEntry*)ws;
-            return FREQKV_OK;
+        bool keep = true;
+        if (ws) {
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            HIP_TRY(hipStreamIsCapturing(st, &cap));
+            int held = 0;                                 // tables of this device
+            for (const auto& t : g_rope) held += t.first.device == dev;
+            keep = cap == hipStreamCaptureStatusNone && held < kMostTables;
         }
         BasisEntry e;
         e.bytes = (size_t)d * sizeof(RopeEntry);
-        hipError_t err = hipMalloc(&e.ptr, e.bytes);
+        hipError_t err = keep ? hipMalloc(&e.ptr, e.bytes) : hipErrorOutOfMemory;
         if (err != hipSuccess) {
+            if (keep) (void)hipGetLastError();
+            if (ws) {
+                HIP_TRY(launch_rope_table((RopeEntry*)ws, d, base, st));
+                *out = (RopeEntry*)ws;
+                return FREQKV_OK;
+            }
             set_error("hipMalloc(rotary table)", err);
-            (void)hipGetLastError();
             return FREQKV_E_ALLOC;
         }
         err = launch_rope_table((RopeEntry*)e.ptr, d, base, st);
@@ -524,11 +533,10 @@ freqkv_status_t get_rope_table(int d, double base, hipStream_t st, RopeEntry** o
 // Cos/sin of every row position for chunk-wise attention (512 bytes per row at d = 128), cached per (device, d, base) like the
 // other tables: 5 us of every short call otherwise.  A call that needs more rows than the table has gets a new one of the next
 // power of two; the old one stays until shutdown, since enqueued work and captured graphs may still read it.  While a
-// stream is being captured nothing is allocated, and neither are tables beyond kCsMaxRows rows or kCsMaxTables per device
+// stream is being captured nothing is allocated, and neither are tables beyond kCsMaxRows rows or kMostTables per device
 // (three rotary bases that grow from 4096 to kCsMaxRows rows, 64 MB each in all, and one more): such calls fill the table into
-// their own workspace.
+// their own workspace.  Without one (ws null) a table is made ready for longer chunks, where one may be kept.
 constexpr int kCsMaxRows = 1 << 16;
-constexpr int kCsMaxTables = 16;
 struct CsTable { RopeKey key; int rows; BasisEntry e; };
 std::vector<CsTable> g_cs;
 
@@ -544,14 +552,14 @@ freqkv_status_t get_cs_table(int rows, int d, double base, hipStream_t st, float
             if (t.key.device != dev) continue;
             ++held;
             if (t.key.d == d && t.key.base == base && t.rows >= rows) {
-                HIP_TRY(order_after(t.e, st));
+                if (ws) HIP_TRY(order_after(t.e, st));
                 *out = (const float2*)t.e.ptr;
                 return FREQKV_OK;
             }
         }
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         HIP_TRY(hipStreamIsCapturing(st, &cap));
-        if (cap == hipStreamCaptureStatusNone && rows <= kCsMaxRows && held < kCsMaxTables) {
+        if (cap == hipStreamCaptureStatusNone && rows <= kCsMaxRows && held < kMostTables) {
             CsTable t{RopeKey{dev, d, base}, 4096, BasisEntry()};
             while (t.rows < rows) t.rows *= 2;
             t.e.bytes = (size_t)t.rows * (d / 2) * sizeof(float2);
@@ -572,7 +580,7 @@ freqkv_status_t get_cs_table(int rows, int d, double base, hipStream_t st, float
             (void)hipGetLastError();                      // no memory for it: as above, in the workspace
         }
     }
-    HIP_TRY(launch_prefill_cs(ws, rows, d, rope ? base : 1.0, rope, st));
+    if (ws) HIP_TRY(launch_prefill_cs(ws, rows, d, rope ? base : 1.0, rope, st));
     *out = ws;
     return FREQKV_OK;
 }
@@ -1498,6 +1506,9 @@ freqkv_status_t attend_many(const PrefillShape& p, char* const* bases, const voi
     char* const ws = (char*)L.workspace;
     RopeEntry* rt = nullptr;
     freqkv_status_t rc = get_rope_table(a.d, rope_base, st, &rt, ws);
+    if (rc < 0) return rc;
+    const float2* longer = nullptr;                   // (a program may go on with a longer chunk, in a capture)
+    rc = get_cs_table(a.cur_len, a.d, rope_base, st, nullptr, &longer);
     if (rc < 0) return rc;
     float* const part_acc = (float*)(ws + kScratchRopeBytes);
     float* const part_ml = (float*)(ws + kScratchRopeBytes + a.ml_offset);
