@@ -50,7 +50,6 @@ constexpr int kQPerWave = 32;      // queries per wave
 constexpr int kPrefillWaves = 8;   // waves per workgroup of the attention kernel
 constexpr int kTileBytes = kKeyTile * kD * 2;   // one Kr or Vt tile, fp16
 constexpr int kAnchor = 8;         // tiles
-constexpr int kTilesByRows = 32;   // from so many on, k_prefill_prep's workgroups stand by rows
 constexpr float kSlack = 14.0f;    // log2 of the largest un-rescaled softmax weight (an fp16 operand: < 2^16)
 constexpr float kWeightLimit = 16384.0f;   // 2^kSlack
 
@@ -114,20 +113,11 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
     const PrefillGeom g = first_argument<decltype(k_prefill_prep)>();
     __shared__ uint32_t sm[kKeyTile][kD / 2 + 1];             // [key][pair of channels], one word of padding per row
     constexpr int half = kD / 2, pgn = half / 8;              // groups of 8 pairs per row
-    // Workgroups are dealt round-robin to the 8 XCDs: all units' tiles of the same rows go to one, so that their cos and sin, as many bytes as a unit's keys
-    // and values, come to one L2 instead of all (unit by unit -> this, whole calls: 301 queries over 5001 rows of 8 KV heads 52.5 -> 51.2 us, 4190
-    // over 4190 of 32 210 -> 206).  Two or four units to a workgroup, for cos and sin in registers: no faster over long caches, 0.5 to 1.7 us slower over short ones.
-    // Short caches go unit by unit: there the tiles beyond the last 8 of them would leave some XCDs with half the work (16 KV heads x 385 rows, 13 tiles, 16.0 -> 16.3).
-    int unit, tile;
-    if (g.key_tiles < kTilesByRows) {
-        unit = blockIdx.x / g.key_tiles;
-        tile = blockIdx.x - unit * g.key_tiles;
-    } else {
-        const int turn = (blockIdx.x >> 3) / g.units;
-        unit = (blockIdx.x >> 3) - turn * g.units;
-        tile = 8 * turn + (blockIdx.x & 7);
-        if (tile >= g.key_tiles) return;
-    }
+    // Unit by unit: with all units' tiles of the same rows on one XCD, whose L2 then has their cos and sin once, 301 queries over 5001 rows of 8 KV heads take 48.7
+    // instead of 49.4 us, but heads that lie 2 MB apart, and numbers of tiles that are no multiple of 8, lose by it (4 sequences x 8 KV heads x 8192 rows, 2000
+    // queries, 874 -> 906; 2 layers, 4000 queries, 735 -> 754; 4 x 8 x 1891, 945 queries, 70.4 -> 72.7).
+    const int tile = blockIdx.x % g.key_tiles;
+    const int unit = blockIdx.x / g.key_tiles;
     const int layer = unit / g.units_per_layer;
     const int rem = unit - layer * g.units_per_layer;
     const int b = rem / g.n_kv, kvh = rem - b * g.n_kv;
@@ -840,7 +830,7 @@ hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, co
 {
     if (g.d != kD || g.cur_len < 1 || g.q_len < 1 || g.q_len > g.cur_len) return hipErrorInvalidValue;
     if (g.key_tiles * kKeyTile < g.cur_len || g.q_pad < g.q_len || g.q_pad % kQPerWave) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * (g.key_tiles < kTilesByRows ? g.key_tiles : (g.key_tiles + 7) / 8 * 8))), dim3(256), 0, st, g, cs, Kr, Vt, tab);
+    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, g, cs, Kr, Vt, tab);
     return hipGetLastError();
 }
 
