@@ -1458,14 +1458,14 @@ freqkv_status_t fit_prefill(PrefillShape* p, size_t workspace_bytes, int* split_
     return FREQKV_OK;
 }
 
-// Calls whose tiles are used by few workgroups read the cached rows as they are: there is no pass that writes them as operands first (7 ns per KV head
-// and tile of 32 keys, and its launch), but each workgroup turns every tile that it uses, 0.21 us more per tile, 0.475 per tile of each half.  The
-// figures are a least-squares fit to 300 shapes drawn over 1 to 32 KV heads, 1 to 8 query heads each, 1 to 4 layers, 1 to 4 sequences, 256 to 8192 rows
-// and 13 of them to all as queries, each timed both ways in graphs of calls.  With them as they are, 93 of these go this way, and of others near the line some
-// were 3 to 6 % slower (888 over 888, 2 layers, 2 sequences, 8 of 4: 57.5 -> 60); with the margin below it is 76, none of them slower, the shortest a third as
-// long.  Operands first -> rows as they are, us: 32 KV heads of one query head each, 4 sequences, 4046 rows, 20 queries 186 ->
-// 62; 2 layers, 2 sequences, 1693, 267 97 -> 61; 385, 385, 4 layers 33 -> 22; 794, 794, 2 sequences 41 -> 31; 8 KV heads of 4, 2 sequences, 5082, 121
-// 56 -> 45.  Not taken: 8 of 4, 5001, 301 52.1 -> 52.1; 1000, 1000 25.0 -> 29.8; 8192, 4094 385 -> 453; 32 of 1, 4261, 4261, 2 layers 382 -> 398.
+// Calls whose tiles are used by few workgroups read the cached rows as they are: there is no pass that writes them as operands first (some 7 ns per KV head
+// and tile of 32 keys, and its launch), but each workgroup turns every tile that it uses, some 0.24 us more per tile, 0.52 per tile of each half.  Over 460
+// shapes drawn over 1 to 32 KV heads, 1 to 8 query heads each, 1 to 4 layers, 1 to 4 sequences, 256 to 8192 rows
+// and 13 of them to all as queries, each timed both ways in graphs of calls, a least-squares fit gives 6.6 ns, 0.24 us and 1.35 us for the launch, in halves 5.9 ns,
+// 0.52 us and 0.98.  With the line below 81 of them go this way, one of them slower so (583 over 1167, 2 layers, 2 sequences, 16 of 1 55.1 -> 55.9 to 56.9), the shortest a third as
+// long; of the others 11 would be 3 to 10 % faster.  The cut is the one that is best with operands written first.  Operands first -> rows as they are, us: 32 KV heads of one query head each, 4 sequences, 4046 rows, 20 queries 188 ->
+// 62; 2 layers, 2 sequences, 1693, 267 97 -> 60; 385, 385, 4 layers 31.7 -> 21.1; 794, 794, 2 sequences 39.1 -> 30.9; 8 KV heads of 4, 2 sequences, 5082, 121
+// 54.0 -> 46.3.  Not taken: 8 of 4, 5001, 301 48.9 -> 50.9; 1000, 1000 23.1 -> 28.6; 8192, 4094 375 -> 441; 888, 888, 2 layers, 2 sequences 54.2 -> 56.5; 32 of 1, 4261, 4261, 2 layers 373 -> 390.
 bool prefill_direct(const PrefillShape& p, int split_tiles, long long stride_token)
 {
     if (!prefill_direct_fits(p.a.cur_len, stride_token)) return false;

@@ -49,7 +49,6 @@ constexpr int kKeyTile = 32;       // keys per tile
 constexpr int kQPerWave = 32;      // queries per wave
 constexpr int kPrefillWaves = 8;   // waves per workgroup of the attention kernel
 constexpr int kTileBytes = kKeyTile * kD * 2;   // one Kr or Vt tile, fp16
-constexpr int kAnchor = 8;         // tiles
 constexpr float kSlack = 14.0f;    // log2 of the largest un-rescaled softmax weight (an fp16 operand: < 2^16)
 constexpr float kWeightLimit = 16384.0f;   // 2^kSlack
 
@@ -195,10 +194,10 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
 // 24.2 in halves; 100 on 1000 25.2 in 3 parts, 21.8 in 3 parts of halves; prefill_cut has more of them.  A step of one tile of each half takes 1.08
 // times that of eight tasks (twice the copies).
 // DIRECT: keys and values come from the cached rows; a tile is asked for a step and a half ahead of its use, into registers, and rotated, turned and
-// written to LDS between the matrix instructions of the weighted sum.  That is 50 (in halves 110) vector instructions per thread and step beside some 80,
-// and 16 KB (in halves 4) of cos and sin through the 64 bytes per cycle of a compute unit beside 16 (32) of keys and values: 0.21 us per step,
-// 0.475 in halves.  (In halves cos and sin turn on from key to key: whole calls 5 to 14 % faster than with the table for every tile, 39 queries over 8 x 6222 rows
-// 35.6 -> 30.7 us; in one stream, which has half as many bytes of them to load, 1 to 3 % slower so, 4 x 32 x 1302 86.8 -> 89.5.)  Rows touched
+// written to LDS between the matrix instructions of the weighted sum.  That is some 50 (in halves 100) vector instructions per thread and step beside some 80,
+// and 16 KB (in halves 32) of cos and sin through the 64 bytes per cycle of a compute unit beside 16 (32) of keys and values: 0.24 us per step,
+// 0.52 in halves.  (In halves cos and sin that turn on from key to key, from the table every eighth tile, made whole calls up to 9 % shorter, 128 queries over
+// 4 x 4 x 6431 rows 41.5 -> 37.8 us, but are up to 7e-7 off where the table's are 3e-8.)  Rows touched
 // ahead of time, so that they come from the L2, changed nothing.  prefill_direct says which calls gain by it.
 template <int HALVES, bool DIRECT>
 __global__ __launch_bounds__(kPrefillWaves * 64, 2)
@@ -322,11 +321,9 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     // DIRECT: a thread has its piece of a tile in registers, asked for a step ahead: 4 pairs of a key (in halves of two, 16 rows apart), which it
     // rotates, and 4 (8) keys of two channels, which it turns.  Rows beyond cur_len are read as zero, past the end of the buffer.  Keys lie in LDS at
     // place key ^ 4 (group of 8 channels & 3) of their group, channels at place c / 2 + 16 (c & 1) of their block, so that the writes of
-    // a wave go to different banks, as do the reads.  The cos and sin of a thread's pairs turn on by 32 (16) rows with each key, and
-    // come from the table again every kAnchor tiles (1e-6 by then, beside the 5e-4 of the operands' fp16).
+    // a wave go to different banks, as do the reads.
     constexpr int NK = HALVES, P = 4, NV = 4 * HALVES;       // keys, pairs, values per channel of a thread
-    struct Staged { u32x2 lo[NK], up[NK]; f32x4 angle[2]; uint32_t v[NV]; } sg;            // angle: (cos, sin) of 4 pairs at the first key
-    f32x4 turn_by[2];                                  // of the 16 rows between keys
+    struct Staged { u32x2 lo[NK], up[NK]; f32x4 angle[NK][2]; uint32_t v[NV]; } sg;        // angle: (cos, sin) of 4 pairs
     __amdgpu_buffer_rsrc_t kbuf, vbuf, cbuf;
     uint32_t koff = 0, voff = 0, coff = 0, row_bytes = 0;
     char *kput = nullptr, *vput = nullptr;             // in slot 0
@@ -352,7 +349,7 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         static_for<2>([&](auto i) { x[i.value] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(cbuf, at + i.value * 16, 0, 0)); });
     };
     auto ask_k = [&](Staged& x, int tile) {
-        if (HALVES == 1 || ((tile - t0) & (kAnchor - 1)) == 0) cs_at(coff + tile * (kKeyTile * kD / 2 * 8), x.angle);
+        static_for<NK>([&](auto k) { cs_at(coff + (tile * kKeyTile + k.value * 16) * (kD / 2 * 8), x.angle[k.value]); });
         static_for<NK>([&](auto k) {
             const uint32_t at = koff + (tile * kKeyTile + k.value * 16) * row_bytes;
             x.lo[k.value] = __builtin_amdgcn_raw_buffer_load_b64(kbuf, at, 0, 0);
@@ -372,13 +369,9 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         uint32_t lo = x.lo[K][I], up = x.up[K][I];
         asm volatile("" : "+v"(lo), "+v"(up));
         const float a0 = bf16_lo(lo), a1 = bf16_hi(lo), b0 = bf16_lo(up), b1 = bf16_hi(up);
-        const f32x4 c = x.angle[I];
+        const f32x4 c = x.angle[K][I];
         hk[0][I] = __builtin_bit_cast(uint32_t, pack_half2(a0 * c[0] - b0 * c[1], a1 * c[2] - b1 * c[3]));
         hk[1][I] = __builtin_bit_cast(uint32_t, pack_half2(b0 * c[0] + a0 * c[1], b1 * c[2] + a1 * c[3]));
-        if constexpr (HALVES == 2) {
-            const f32x4 r = turn_by[I];
-            x.angle[I] = f32x4{c[0] * r[0] - c[1] * r[1], c[1] * r[0] + c[0] * r[1], c[2] * r[2] - c[3] * r[3], c[3] * r[2] + c[2] * r[3]};
-        }
     };
     auto turn_v = [&](Staged& x, auto i) {             // two keys
         asm volatile("" : "+v"(x.v[2 * i.value]), "+v"(x.v[2 * i.value + 1]));
@@ -455,7 +448,6 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
     __syncthreads();
     Staged early[3];
     if constexpr (DIRECT) {
-        if constexpr (HALVES == 2) cs_at(16 * (kD / 2 * 8) + coff % (kD / 2 * 8), turn_by);
         static_for<3>([&](auto i) {
             ask_k(early[i.value], min(t0 + i.value, last_tile));
             ask_v(early[i.value], min(t0 + i.value, last_tile));
@@ -500,11 +492,7 @@ void k_attend_prefill(const PrefillGeom, const _Float16* __restrict__ Kr, const 
         }
     }
     if constexpr (DIRECT) {
-        static_for<3>([&](auto i) {
-            if constexpr (HALVES == 2 && decltype(i)::value > 0) static_for<2>([&](auto j) { early[i.value].angle[j.value] = early[i.value - 1].angle[j.value]; });
-            take(early[i.value], t0 + i.value);
-        });
-        static_for<2>([&](auto j) { sg.angle[j.value] = early[2].angle[j.value]; });
+        static_for<3>([&](auto i) { take(early[i.value], t0 + i.value); });
         ask_k(sg, min(t0 + 3, last_tile));
         ask_v(sg, min(t0 + 3, last_tile));
     } else {
