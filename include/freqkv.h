@@ -382,7 +382,9 @@ FREQKV_API freqkv_status_t freqkv_debug_fast_stage(void* k, void* v, const freqk
  *   freqkv_debug_compress_ring   leaves (64 rows) that its ring in LDS holds, units of four leaves that it holds in registers besides, the
  *       first leaf of the first of these, and from each to the next, in leaves (FREQKV_E_UNSUPPORTED: another kernel's span)
  *   freqkv_debug_prefill_cut   halves: 2 where the waves of a workgroup share out the keys, else 1; parts: of the key range, as a
- *       workspace of workspace_bytes allows (FREQKV_E_WORKSPACE: too small for the call)
+ *       workspace of workspace_bytes allows (FREQKV_E_WORKSPACE: too small for the call); of k_attend_prefill, whether the call goes there or not
+ *   freqkv_debug_prefill_kernel   a static string: "k_attend_prefill (operands)", after the pass that writes them, "k_attend_prefill (rows)", on the
+ *       cached rows, or "k_attend_quads", few queries as heads of a decode call; NULL for calls that are refused
  */
 FREQKV_API const char* freqkv_debug_compress_kernel(const freqkv_layout_t* layout, int n_heads, int head_dim, int window, int n_sink,
                                          double retain_ratio);
@@ -392,6 +394,8 @@ FREQKV_API freqkv_status_t freqkv_debug_compress_ring(const freqkv_layout_t* lay
 FREQKV_API freqkv_status_t freqkv_debug_prefill_cut(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads, int head_dim,
                                          int cur_len, int q_len, size_t workspace_bytes, int32_t* halves /* host */,
                                          int32_t* parts /* host */);
+FREQKV_API const char* freqkv_debug_prefill_kernel(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads, int head_dim,
+                                         int cur_len, int q_len, size_t workspace_bytes);
 
 /* Human-readable name of a status code (static string, host). */
 FREQKV_API const char* freqkv_status_string(freqkv_status_t status);

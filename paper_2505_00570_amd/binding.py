@@ -131,6 +131,8 @@ def load() -> C.CDLL:
     lib.freqkv_debug_prefill_cut.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int32),
                                              C.POINTER(C.c_int32)]
     lib.freqkv_debug_prefill_cut.restype = C.c_int
+    lib.freqkv_debug_prefill_kernel.argtypes = [LP, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t]
+    lib.freqkv_debug_prefill_kernel.restype = C.c_char_p
     lib.freqkv_status_string.argtypes = [C.c_int]
     lib.freqkv_status_string.restype = C.c_char_p
     lib.freqkv_last_error.argtypes = []
@@ -281,6 +283,12 @@ def prefill_cut(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, 
     _check(load().freqkv_debug_prefill_cut(C.byref(layout), n_q_heads, n_kv_heads, head_dim, cur_len, q_len, workspace_bytes,
                                            C.byref(halves), C.byref(parts)))
     return halves.value, parts.value
+
+
+def prefill_kernel(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, cur_len: int, q_len: int, workspace_bytes: int):
+    """freqkv_debug_prefill_kernel: the way a chunk-wise call with such a workspace takes; None where it is refused."""
+    name = load().freqkv_debug_prefill_kernel(C.byref(layout), n_q_heads, n_kv_heads, head_dim, cur_len, q_len, workspace_bytes)
+    return name.decode() if name is not None else None
 
 
 def attend_prefill_plan(layout: Layout, n_q_heads: int, n_kv_heads: int, head_dim: int, cur_len: int, q_len: int,

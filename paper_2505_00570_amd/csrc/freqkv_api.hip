@@ -1492,6 +1492,14 @@ bool prefill_as_decode(const PrefillShape& p, bool direct, int split_tiles)
     return groups <= 4 || units * std::max(p.a.cur_len, 256) * (groups - 4) < 75000;
 }
 
+// The way of a call whose parts fit_prefill has settled.
+enum PrefillWay { kOperands, kRows, kAsDecode };
+PrefillWay prefill_way(const PrefillShape& p, int split_tiles, long long stride_token)
+{
+    const bool direct = prefill_direct(p, split_tiles, stride_token);
+    return prefill_as_decode(p, direct, split_tiles) ? kAsDecode : direct ? kRows : kOperands;
+}
+
 // A call of few queries.  Its states take less than the operands of the other way, which the workspace has room for.
 freqkv_status_t attend_many(const PrefillShape& p, char* const* bases, const void* q, void* out, float* lse, const freqkv_layout_t& L,
                             double rope_base, hipStream_t st)
@@ -1502,7 +1510,7 @@ freqkv_status_t attend_many(const PrefillShape& p, char* const* bases, const voi
     a.GT = 4;
     a.units_all = p.units;                            // of a pass
     a.cut(attend_chunks(p.units * parts, p.units, 4, a.d, a.elem, a.cur_len, 2 * attend_row_step(a.d)));
-    while (a.n_split > 1 && kScratchRopeBytes + a.workspace_bytes > L.workspace_bytes) a.cut(a.n_split - 1);
+    while (a.n_split > 1 && kScratchRopeBytes + a.workspace_bytes > L.workspace_bytes) a.cut(a.n_split - 1);   // (a guard: no known call comes here)
     char* const ws = (char*)L.workspace;
     RopeEntry* rt = nullptr;
     freqkv_status_t rc = get_rope_table(a.d, rope_base, st, &rt, ws);
@@ -1555,6 +1563,21 @@ freqkv_status_t freqkv_debug_prefill_cut(const freqkv_layout_t* layout, int n_q_
     return FREQKV_OK;
 }
 
+const char* freqkv_debug_prefill_kernel(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads, int head_dim, int cur_len, int q_len,
+                                        size_t workspace_bytes)
+{
+    PrefillShape p;
+    int split_tiles = 0;
+    freqkv_status_t rc = check_prefill(layout, n_q_heads, n_kv_heads, head_dim, cur_len, q_len, &p);
+    if (rc == FREQKV_OK) rc = fit_prefill(&p, workspace_bytes, &split_tiles);
+    if (rc < 0) return nullptr;
+    switch (prefill_way(p, split_tiles, layout->stride_token)) {
+        case kRows: return "k_attend_prefill (rows)";
+        case kAsDecode: return "k_attend_quads";
+        default: return "k_attend_prefill (operands)";
+    }
+}
+
 freqkv_status_t freqkv_attend_prefill_plan(const freqkv_layout_t* layout, int n_q_heads, int n_kv_heads,
                                            int head_dim, int cur_len, int q_len, freqkv_prefill_plan_t* out)
 {
@@ -1601,8 +1624,9 @@ freqkv_status_t freqkv_attend_prefill(const void* q, const void* k, const void* 
     int split_tiles = 0;
     rc = fit_prefill(&p, L.workspace_bytes, &split_tiles);
     if (rc < 0) return rc;
-    const bool direct = prefill_direct(p, split_tiles, L.stride_token);
-    if (prefill_as_decode(p, direct, split_tiles)) return attend_many(p, bases.data(), q, out, lse, L, rope_base, (hipStream_t)stream);
+    const PrefillWay way = prefill_way(p, split_tiles, L.stride_token);
+    const bool direct = way == kRows;
+    if (way == kAsDecode) return attend_many(p, bases.data(), q, out, lse, L, rope_base, (hipStream_t)stream);
     const int n_split = p.n_split;
 
     hipStream_t st = (hipStream_t)stream;
