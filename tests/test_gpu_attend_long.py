@@ -31,3 +31,19 @@ def _check_ends(d, hkv, group, batch, cur_len, dtype):
 ])
 def test_long_chunks_of_one_set(d, hkv, batch, cur_len, dtype):
     _check_ends(d, hkv, 4, batch, cur_len, dtype)
+
+
+@pytest.mark.parametrize("d,hkv,group,batch,cur_len,dtype", [
+    (128, 1, 8, 385, 2113, torch.bfloat16),    # two sets of four heads to a workgroup, three steps beyond the exact angles, the last of a row
+    (128, 2, 8, 128, 2050, torch.bfloat16),    # 256 workgroups
+    (256, 2, 8, 256, 1025, torch.bfloat16),
+    (256, 2, 8, 256, 2081, torch.bfloat16),    # exact angles twice
+    (64, 2, 8, 200, 4100, torch.bfloat16),
+    (64, 1, 16, 200, 4161, torch.float32),     # two workgroups to the same rows
+    (256, 1, 8, 400, 1089, torch.float32),
+    (128, 1, 8, 400, 2081, torch.float32),
+])
+def test_long_chunks_of_two_sets(d, hkv, group, batch, cur_len, dtype):
+    workgroups = batch * hkv * group // 8
+    assert workgroups > 384 or 128 < workgroups <= 256
+    _check_ends(d, hkv, group, batch, cur_len, dtype)
