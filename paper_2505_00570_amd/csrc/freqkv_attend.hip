@@ -635,10 +635,11 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
 // results are the same to the bit.  Calls with 8 query heads to a KV head, a set to a workgroup -> two, graphs of calls, rows from HBM: 8 layers x 20 x
 // 8 KV heads x 2143 rows 363 -> 291 us, 32 layers x 5 x 4 x 3806 322 -> 278, 5 x 16 x 310 of d = 256 217 -> 182, 8 x 56 x 8 x 488 of d = 64
 // 141 -> 117, fp32 56 x 8 x 1476 150 -> 120; two_sets has the others.
-// Of bf16 workgroups of one set three fit a compute unit, which is what 513 to 768 of them want (the loop for long chunks had two registers too many: 576
-// workgroups of 4400 rows 267 us, 259 by threes).
+// Of bf16 workgroups of one set three fit a compute unit, of the others two.  513 to 768 of them want three (the loop for long chunks had two registers too
+// many: 576 workgroups of 4400 rows 267 us, 259 by threes).
+template <typename T, bool MANY, int SETS> constexpr bool by_threes() { return sizeof(T) == 2 && SETS == 1 && !MANY; }
 template <typename T, int D, bool ONE, bool SHORT, bool MANY, int SETS>
-__global__ __launch_bounds__(kWaves * 64, sizeof(T) == 2 && SETS == 1 && !MANY ? 3 : 2)
+__global__ __launch_bounds__(kWaves * 64, (by_threes<T, MANY, SETS>() ? 3 : 2))
 void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __restrict__ rt, float* __restrict__ part_acc,
                     float* __restrict__ part_ml, T* __restrict__ out, float* __restrict__ lse, const SlabTable tab)
 {
@@ -1069,7 +1070,7 @@ static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, 
     // Long chunks: more workgroups than three to each compute unit go by twos, held apart by LDS that they do not use, so that the last
     // round has more of them (4400 rows, by threes -> by twos: 800 workgroups 353 -> 328 us, 896 371 -> 362, 1024 397 -> 395, 1280 496 -> 495, 2048 787 -> 780; up to three
     // all are there at once, and 576 of them take 259 instead of 266).
-    const unsigned apart = (long long)grid.x * grid.y > 3 * 256 ? 40 << 10 : 0;
+    const unsigned apart = by_threes<T, MANY, SETS>() && (long long)grid.x * grid.y > 3 * 256 ? 40 << 10 : 0;
     const bool brief = g.chunk <= 2 * kReseed * kUnroll * attend_row_step(D);
     auto launch = [&](auto one, auto is_short) {
         hipLaunchKernelGGL((k_attend_quads<T, D, decltype(one)::value != 0, decltype(is_short)::value != 0, MANY, SETS>), grid, dim3(kWaves * 64),

@@ -1,5 +1,5 @@
-"""Decode attention with two sets of four query heads to a workgroup: caches with other strides and behind pointer tables, a given position of the query, and
-no rotary embedding."""
+"""Decode attention with two sets of four query heads to a workgroup: caches with other strides and behind pointer tables, a given position of the query,
+no rotary embedding, and more workgroups than are there at once."""
 import ctypes as C
 
 import pytest
@@ -60,3 +60,15 @@ def test_no_rotary_embedding(d):
     wl, q, k, v = _case(d)
     out, lse, _ = _run(q, k, v, wl, CUR, base=0.0)
     _check_some(q, k, v, out, lse, wl, base=0.0)
+
+
+@pytest.mark.parametrize("d,group,batch,dtype", [(128, 8, 260, torch.bfloat16), (256, 8, 260, torch.bfloat16), (256, 8, 260, torch.float32), (64, 16, 140, torch.float32)])
+def test_more_workgroups_than_three_to_a_compute_unit(d, group, batch, dtype):
+    wl = _wl(d=d, hkv=3, hq=3 * group, batch=batch, cap=70, dtype=dtype)
+    q, k, v = _mk(wl, 70, seed=9)
+    out, lse, p = _run(q, k, v, wl, 70)
+    assert batch * 3 * group // 8 * p.n_split > 768
+    one = _wl(d=d, hkv=3, hq=3 * group, batch=1, cap=70, dtype=dtype)
+    for b in (0, batch - 1):
+        at = slice(b, b + 1)
+        _check(q[:, at], k[:, at], v[:, at], out[:, at], lse[:, at], one, 70)
