@@ -393,7 +393,9 @@ freqkv_status_t get_nf_tables(const Shape& sh, int rescale, hipStream_t st, cons
 // 128 10.0, 64 8.2; 1 x 16000 of d = 256 250 17.5, 125 15.6).  With fewer than that, leaving compute units idle takes longer than
 // the chunks that it saves: a quarter or half of them 12 x 1500 rows of d = 64 12 chunks 7.2, 5 8.6; 8 x 8000 of d = 64 32 8.6, 16 10.1; 24 x 300 5
 // 7.2, 2 8.5; 3 x 16357 74 12.2, 40 13.8.  Over 230 other shapes 1.2 % above the best cut with rows from HBM, 15 % at worst (1.8 % and 20 % with
-// a quarter and half of the compute units for all, 1.6 % and 20 % with neither): profiles/decode_chunks.txt.
+// a quarter and half of the compute units for all, 1.6 % and 20 % with neither): profiles/decode_chunks.txt.  That was with the four-head kernel before this one; with
+// the present one 1.3 % above the best cut over 200 shapes with groups of four, 26 % at worst (96 KV heads of 16 in fp32 x 791 rows), 1.0 and 15 % in bf16:
+// profiles/decode_chunks_quads.txt.
 int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int rows, int min_rows)
 {
     constexpr int kCus = 256, kCuts = 7;

@@ -67,6 +67,9 @@ __device__ __forceinline__ half2v pack_half2(float a, float b)
 template <bool DIRECT> struct Rows { void* none; };
 template <> struct Rows<true> { SlabTable tab; };
 
+// Workgroups of k_prefill_prep to a unit, some of which may have no tile.
+__host__ __device__ inline int prep_tiles(int key_tiles) { return key_tiles < 64 || (-key_tiles & 7) * 14 > key_tiles ? key_tiles : (key_tiles + 7) & ~7; }
+
 // Position of the key that sits at storage index s (0..31) of a Vt tile: the matrix core leaves a
 // 32x32 result with register r of a lane in half-wave hw at row 8*(r/4) + 4*hw + r%4; k-step t of the
 // weighted sum takes registers 8t .. 8t+7, so storage index s = 16t + 8hw + e holds key
@@ -113,11 +116,13 @@ __global__ __launch_bounds__(256) void k_prefill_prep(const PrefillGeom, const f
     const PrefillGeom g = first_argument<decltype(k_prefill_prep)>();
     __shared__ uint32_t sm[kKeyTile][kD / 2 + 1];             // [key][pair of channels], one word of padding per row
     constexpr int half = kD / 2, pgn = half / 8;              // groups of 8 pairs per row
-    // Unit by unit: with all units' tiles of the same rows on one XCD, whose L2 then has their cos and sin once, 301 queries over 5001 rows of 8 KV heads take 48.7
-    // instead of 49.4 us, but heads that lie 2 MB apart, and numbers of tiles that are no multiple of 8, lose by it (4 sequences x 8 KV heads x 8192 rows, 2000
-    // queries, 874 -> 906; 2 layers, 4000 queries, 735 -> 754; 4 x 8 x 1891, 945 queries, 70.4 -> 72.7).
-    const int tile = blockIdx.x % g.key_tiles;
-    const int unit = blockIdx.x / g.key_tiles;
+    // Workgroups are dealt round-robin to the 8 XCDs: unit by unit, in multiples of 8, so that the tiles of the same rows of all units go to one, and their cos and
+    // sin, as many bytes as a unit's keys and values, come to one L2 instead of all (without the multiples -> with them, whole calls: 301 queries over 5001 rows of 8 KV
+    // heads 49.8 -> 48.9 us, 945 over 8 x 2375 27.8 -> 26.7, 300 over 8 x 2500 32.5 -> 31.6, 4190 over 4190 of 32 207.6 -> 204.8).  From 64 tiles on, and with up to a fourteenth of them without a tile:
+    // some XCDs have more work than others then (4 layers x 4 x 8 x 1056 rows, 33 tiles, 166 -> 170; 2 x 4 x 8 x 1120 102 -> 104; 2 x 2 x 8 x 2110, 66 tiles, 177.8 -> 179.5).  Row by row, with the units of
+    // the same rows next to each other, heads that lie 2 MB apart lose (4 x 8 x 8192 rows, 2000 queries, 874 -> 906; 2 layers, 4000 queries, 735 -> 754).
+    const int tiles = prep_tiles(g.key_tiles), tile = blockIdx.x % tiles, unit = blockIdx.x / tiles;
+    if (tile >= g.key_tiles) return;
     const int layer = unit / g.units_per_layer;
     const int rem = unit - layer * g.units_per_layer;
     const int b = rem / g.n_kv, kvh = rem - b * g.n_kv;
@@ -820,7 +825,7 @@ hipError_t launch_prefill_prepare(const SlabTable& tab, const PrefillGeom& g, co
 {
     if (g.d != kD || g.cur_len < 1 || g.q_len < 1 || g.q_len > g.cur_len) return hipErrorInvalidValue;
     if (g.key_tiles * kKeyTile < g.cur_len || g.q_pad < g.q_len || g.q_pad % kQPerWave) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * g.key_tiles)), dim3(256), 0, st, g, cs, Kr, Vt, tab);
+    hipLaunchKernelGGL(k_prefill_prep, dim3((unsigned)((long long)g.units * prep_tiles(g.key_tiles))), dim3(256), 0, st, g, cs, Kr, Vt, tab);
     return hipGetLastError();
 }
 
