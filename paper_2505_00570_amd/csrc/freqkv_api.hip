@@ -1479,19 +1479,26 @@ bool prefill_direct(const PrefillShape& p, int split_tiles, long long stride_tok
 
 // Few queries go as so many heads of a decode call, by fours, which reads keys and values where they are and works in fp32.
 // Against operands written first: up to 16 queries in all heads of a KV head are always faster so (one query 1.3 to 3.4 times, 16
-// 1.04 to 2.3; 8 KV heads of 2 query heads each, 4 layers, 6000 rows, 8 queries 62 -> 55 us).  Of more than that each further four take 0.066 ns per row on a device that is full,
-// against some 6 us that a call has less to do, rows of short caches counting as 256: 2 KV heads of 8, 1500 rows, 8 queries 17.5 -> 11.2,
-// 8 of 4, 1500, 8 20.4 -> 15.2; not taken 8 of 2 in 4 layers, 6000, 16 62 -> 102, 2 of 8, 7922, 7 30.3 -> 23.5.  Over 240 shapes in both ways 1.5 % above the better one on
-// average; where this way was taken never more than 2 % above the other.
+// 1.04 to 2.3).  Of more than that each further four take 0.066 ns per row on a device that is full, against some 6 us that a call has less to do, rows of short
+// caches counting as 256.  Where they make more workgroups than a third of the compute units, which then have half of the rows, one after the other, up to 640 rows;
+// than half, which have all of them, 512; than all, so that some have two, 112; more than two for each go the other way.  2 KV heads of 8, 1500 rows, 8 queries
+// 17.5 -> 11.2 us; 8 of 4, 1500, 8 20.4 -> 15.2; 16 workgroups for each of 16 KV heads, 317 rows 13.8 -> 11.4; 9 for each of 32, 92 rows 10.5 -> 9.6.  Not taken 2 of 8, 7922, 7
+// 30.3 -> 23.5; 13 for each of 8, 984 rows 15.6 -> 17.9; 12 for each of 16, 564 15.2 -> 19.8; 9 for each of 32, 301 14.2 -> 16.5, 361 15.1 -> 20.8; 16 for each of 32, 176 12.4 -> 13.0.  Of
+// 902 shapes that have operands otherwise 779 go this way, none of them slower.
 // Against rows as they are (direct): four queries, which only read, are always faster so; each further four take 0.06 ns per row, and the other way 0.5 us per
-// tile of a part.  Over 165 shapes in both ways 0.4 % above the better one on average.  32 KV heads of 1, 1631 rows, 17 queries: operands first 24.2, so 25.2, rows as
-// they are 16.6; 32 of 1, 4 layers, 7323, 5 336, 123, 104; 16 of 4, 2 layers, 5330, 4 75, 49, 35; taken 4 of 1, 2 layers, 5075, 6 28.7, 14.2, 20.7.
+// tile of a part; more workgroups than compute units over short caches only, as above (5 for each of 64 KV heads, 361 rows: operands first 16.6, so 20.1, rows as they are 13.4).
+// Of 448 such shapes 54 go this way, one of them 2.4 % slower so.  32 KV heads of 1, 1631 rows, 17 queries 24.2, 25.2, 16.6; 32 of 1, 4 layers, 7323, 5
+// 336, 123, 104; 16 of 4, 2 layers, 5330, 4 75, 49, 35; taken 4 of 1, 2 layers, 5075, 6 28.7, 14.2, 20.7.  Over all 1350 0.2 % above the better of the two.
 bool prefill_as_decode(const PrefillShape& p, bool direct, int split_tiles)
 {
-    const long long groups = ((long long)p.a.G * p.q_len + 3) / 4, units = p.units;
+    const long long groups = ((long long)p.a.G * p.q_len + 3) / 4, units = p.units, wgs = units * groups;
+    const int rows = p.a.cur_len;
     if (groups > 16) return false;
-    if (direct) return groups == 1 || 0.5 + 0.5 * split_tiles > 1e-3 * (double)(units * std::max(p.a.cur_len, 320)) * (0.06 * (double)groups - 0.03);
-    return groups <= 4 || units * std::max(p.a.cur_len, 256) * (groups - 4) < 75000;
+    if (groups == 1 || (!direct && groups <= 4)) return true;
+    if (wgs > 256 && rows > (wgs > 512 ? 0 : 112)) return false;
+    if (direct) return 0.5 + 0.5 * split_tiles > 1e-3 * (double)(units * std::max(rows, 320)) * (0.06 * (double)groups - 0.03);
+    if (wgs > 85 && rows > (wgs > 128 ? 512 : 640)) return false;
+    return units * std::max(rows, 256) * (groups - 4) < 75000;
 }
 
 // The way of a call whose parts fit_prefill has settled.

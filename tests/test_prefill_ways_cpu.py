@@ -64,3 +64,14 @@ def test_refused_calls_have_no_way():
     assert fk.prefill_kernel(L, 32, 8, 128, 1000, 1001, 1 << 40) is None
     assert fk.prefill_kernel(L, 32, 8, 128, 1000, 10, 1000) is None
     assert fk.prefill_kernel(L, 32, 8, 64, 1000, 10, 1 << 40) is None
+
+
+def test_more_workgroups_than_compute_units_go_as_decode_over_short_caches_only():
+    """As decode 38 and 36, 16, 10, 10, 5, 4, 4, 14 and 30 % slower than with operands written first (20.8 us against 15.1 and so on)."""
+    assert _way(16, 2, 361, 18, layers=2) == _way(32, 1, 439, 33) == _way(2, 4, 301, 9, layers=4, batch=4) == OPERANDS
+    assert _way(8, 1, 213, 40, layers=4) == _way(8, 4, 208, 10, batch=4) == _way(1, 4, 667, 10, layers=4, batch=4) == OPERANDS
+    assert _way(8, 2, 152, 20, layers=4) == _way(8, 4, 180, 9, layers=2, batch=2) == OPERANDS
+    assert _way(2, 1, 984, 51, layers=2, batch=2) == _way(2, 2, 564, 23, layers=4, batch=2) == OPERANDS
+    assert _way(8, 2, 361, 10, layers=2, batch=4) == ROWS            # (as decode 53 % slower)
+    # 8, 9, 17, 20 and 17 % faster
+    assert _way(16, 2, 92, 11, batch=4) == _way(32, 1, 63, 41) == _way(16, 4, 317, 16) == _way(16, 4, 243, 16) == _way(4, 8, 531, 4, layers=2, batch=2) == DECODE
