@@ -407,24 +407,23 @@ void k_attend_partial(const AttGeom, const T* __restrict__ q,
 
     // ---- rows of this lane group: p0, p0+STEP, p0+2*STEP, ...
     const int nit = row_end > row0 ? (row_end - row0 + STEP * U - 1) / (STEP * U) : 0;
-    const int last = cur_len - 1;
     // Rows are addressed by 32-bit byte offsets inside the head's slab (uniform base + per-lane offset; the host
     // checks the range).  Of rows past the end of the chunk the values are zero, from past the end of a buffer (times a weight of 0 an infinite
     // value would be NaN), and the keys those of other rows, the last one's at most, and masked in the steps that can contain them: no load is
     // conditional, so the loads in flight can be counted exactly.
-    const char* kb = (const char*)kbase;
     const uint32_t row_bytes = (uint32_t)g.stride_token * (uint32_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)(P * l) * (uint32_t)sizeof(T);
-    const uint32_t last_off = (uint32_t)last * row_bytes + lane_off;
-    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)vbase, 0, (int)((uint32_t)max(row_end - 1, 0) * row_bytes + (uint32_t)(D * sizeof(T))), kBufferFlags);
+    const int size = (int)((uint32_t)max(row_end - 1, 0) * row_bytes + (uint32_t)(D * sizeof(T)));
+    const __amdgpu_buffer_rsrc_t kbuf = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, size, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)vbase, 0, size, kBufferFlags);
     uint32_t next_off = (uint32_t)p0 * row_bytes + lane_off;      // first row of the step to be loaded next
     struct Rows { RawT kl[U], kh[U], vl[U], vh[U]; };
     auto issue = [&](Rows& r) {
         static_for<U>([&](auto uu) {
             constexpr int u = decltype(uu)::value;
-            const uint32_t at = next_off + (uint32_t)(u * STEP) * row_bytes, o = min(at, last_off);
-            load_raw((const T*)(kb + o), r.kl[u]);
-            load_raw((const T*)(kb + o) + D / 2, r.kh[u]);
+            const uint32_t at = next_off + (uint32_t)(u * STEP) * row_bytes;
+            load_raw(kbuf, at, r.kl[u]);
+            load_raw(kbuf, at + D / 2 * (uint32_t)sizeof(T), r.kh[u]);
             load_raw(vbuf, at, r.vl[u]);
             load_raw(vbuf, at + D / 2 * (uint32_t)sizeof(T), r.vh[u]);
         });
@@ -795,11 +794,12 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
         static_for<SETS>([&](auto h) { of_rows[h.value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
         static_for<N>([&](auto jj) {
             constexpr int j = jj.value;
-            const float lo = a[j] * c[j] - bb[j] * s[j], up = bb[j] * c[j] + a[j] * s[j];
+            // (which product is rounded by itself is said here: left to the compiler, it is not the same for one set of heads and for two)
+            const float lo = fmaf(a[j], c[j], -(bb[j] * s[j])), up = fmaf(bb[j], c[j], a[j] * s[j]);
             static_for<SETS>([&](auto h) { of_rows[h.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(lo, ql[h.value][j], of_rows[h.value], 0, 0, 0); });
             static_for<SETS>([&](auto h) { of_rows[h.value] = __builtin_amdgcn_mfma_f32_4x4x1f32(up, qh[h.value][j], of_rows[h.value], 0, 0, 0); });
-            const float cn = c[j] * cd[j] - s[j] * sd[j];
-            s[j] = s[j] * cd[j] + c[j] * sd[j];
+            const float cn = fmaf(c[j], cd[j], -(s[j] * sd[j]));
+            s[j] = fmaf(s[j], cd[j], c[j] * sd[j]);
             c[j] = cn;
         });
         __builtin_amdgcn_sched_barrier(0);
@@ -864,38 +864,35 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
     };
     // Two register sets take turns: while one step is consumed the loads of the next are in flight.  A long chunk has its steps
     // rounded up to an even number; a surplus step sees only rows past the end (weights exactly zero).
-    auto walk = [&](auto apart) {
-        if constexpr (SHORT) {
-            for (int it = 0; it < nit; it += 2) {
-                consume(apart, ra, it);
-                if (it + 1 >= nit) break;
+    if constexpr (SHORT) {
+        for (int it = 0; it < nit; it += 2) {
+            consume(IC<0>{}, ra, it);
+            if (it + 1 >= nit) break;
+            __builtin_amdgcn_sched_barrier(0);
+            issue(ra);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(IC<0>{}, rb, it + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(rb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        int it = 0;
+        while (true) {
+            for (const int end = min(nit, it + kReseedSteps); it < end; it += 2) {
+                consume(IC<0>{}, ra, it);
                 __builtin_amdgcn_sched_barrier(0);
                 issue(ra);
                 __builtin_amdgcn_sched_barrier(0);
-                consume(apart, rb, it + 1);
+                consume(IC<0>{}, rb, it + 1);
                 __builtin_amdgcn_sched_barrier(0);
                 issue(rb);
                 __builtin_amdgcn_sched_barrier(0);
             }
-        } else {
-            int it = 0;
-            while (true) {
-                for (const int end = min(nit, it + kReseedSteps); it < end; it += 2) {
-                    consume(apart, ra, it);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue(ra);
-                    __builtin_amdgcn_sched_barrier(0);
-                    consume(apart, rb, it + 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue(rb);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (it >= nit) break;
-                seed_again(it);
-            }
+            if (it >= nit) break;
+            seed_again(it);
         }
-    };
-    walk(IC<0>{});
+    }
     if constexpr (MANY) {
         // A value that is infinite or NaN, in a row that not all queries of the set see, has made the sums of the others NaN, by their weight of 0: sums that are
         // not finite are worked out again, with those rows left out where they are not seen.  (26 queries of 2 heads to each of 2 x 8 KV heads over 335 rows take 10.85 us,
@@ -905,11 +902,12 @@ void k_attend_quads(const AttGeom, const T* __restrict__ q, const RopeEntry* __r
             static_for<N>([&](auto cc) { static_for<GT>([&](auto gg) { none[gg.value] = fmaf(qacc[0][cc.value][gg.value], 0.f, none[gg.value]); }); });
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(none[0] + none[1] + none[2] + none[3] == 0.f)) != 0, 0)) {
                 next_at = (uint32_t)wave_row0 * row_bytes;
-                issue(ra);
-                issue(rb);
-                seed_again(0);
                 start();
-                walk(IC<1>{});
+                for (int it = 0; it < nit; ++it) {
+                    if (it % kReseedSteps == 0) seed_again(it);
+                    issue(ra);
+                    consume(IC<1>{}, ra, it);
+                }
             }
         }
     }
