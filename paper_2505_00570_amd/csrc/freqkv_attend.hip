@@ -1084,15 +1084,30 @@ static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, 
     }
 }
 
-// Two sets of four heads to a workgroup where it does not leave compute units idle: a workgroup takes 1.2 to 1.4 times as long, and there are half as
-// many.  Up to 128 of them would take every second compute unit (128 8.3 us for 6.8 at 8 KV heads of 8 x 100 rows, 16.5 for 12.6 at 400); 129 to 256 are one
-// to a compute unit instead of two of the others (152 8.2 for 9.2; 256 28.3 for 34.4 at 1500 rows); 257 to 384 two instead of three, which is as
-// long (0.94 to 1.13 times); more are faster again (392 12.4 for 15.4, 77 for 94 at 1500 rows).
-static bool two_sets(const AttGeom& g)
+// Two sets of four heads to a workgroup: a workgroup takes 1.2 to 1.4 times as long, and there are half as many; an odd number of steps is rounded up.
+// Time of one set to a workgroup over that of two (above 1 two are faster; 1 to 11 steps of 2 * attend_row_step(d) rows, much the same for d = 64, 128, 256):
+//   workgroups of two sets                      bf16: 1 step   3     5    even   9, 11      fp32: 1 step   3     5    even   7    9, 11
+//   up to 128 (every second compute unit idle; 128 8.3 us for 6.8 at 8 KV heads of 8 x 100 rows)
+//   136 to 256 (one to a compute unit)                 0.91  1.00  1.03  1.11  1.06               0.91  0.94  0.93  1.04  1.02  1.09
+//   300, 384 (two; of the others three, in fp32 two)   0.83  0.86  0.86  0.97  0.89               0.95  0.91  0.95  1.05  0.98  1.00 (long ones 1.03 to 1.27)
+//   400, 500                                           1.02  1.06  1.07  1.21  1.12               1.11  1.06  1.13  1.22  1.16  1.18
+//   520, 600 (a few for the second time)               0.85  0.90  0.91  1.03  0.97               0.95  0.98  1.04  1.11  1.07  1.06
+//   700; 1000 and 1200                                 0.96  1.04  1.04  1.17  1.09               1.09  1.11  1.17  1.26  1.19  1.19
+//   800                                                0.88  0.93  0.96  1.08  0.99               1.02  1.03  1.08  1.17  1.10  1.09
+static bool two_sets(const AttGeom& g, int elem_bytes)
 {
     if (g.G % 8) return false;
     const long long wgs = (long long)g.units * g.n_split * (g.G / 8);
-    return wgs > 384 || (wgs > 128 && wgs <= 256);
+    const bool f32 = elem_bytes == 4;
+    int one = 0;                               // odd numbers of steps up to this have one set
+    if (wgs <= 128) return false;
+    else if (wgs <= 256) one = f32 ? 5 : 1;
+    else if (wgs <= 384) { if (!f32) return false; one = 11; }
+    else if (wgs <= 512) one = 0;
+    else if (wgs <= 640) one = f32 ? 3 : 9;
+    else if (!f32) one = wgs > 768 && wgs <= 896 ? 9 : 1;
+    const int rows = kUnroll * attend_row_step(g.d), steps = ((g.chunk < g.cur_len ? g.chunk : g.cur_len) + rows - 1) / rows;
+    return steps % 2 == 0 || steps > one;
 }
 
 template <typename T, int D>
@@ -1101,8 +1116,8 @@ static hipError_t launch_partial_d(const SlabTable& tab, const AttGeom& g, const
 {
     switch (g.GT) {
         case 4:
-            if (two_sets(g)) launch_quads<T, D, false, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
-            else             launch_quads<T, D, false, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+            if (two_sets(g, sizeof(T))) launch_quads<T, D, false, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
+            else                        launch_quads<T, D, false, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st);
             break;
         case 2: launch_partial_g<T, D, 2>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
         case 1: launch_partial_g<T, D, 1>(tab, g, q, rt, part_acc, part_ml, out, lse, st); break;
