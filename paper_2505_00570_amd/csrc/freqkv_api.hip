@@ -387,14 +387,14 @@ freqkv_status_t get_nf_tables(const Shape& sh, int rescale, hipStream_t st, cons
 // compute unit, several workgroups 0.020 each, is what it took with every lane working out the softmax of all heads; 0.013 with 2 heads, 0.0095 with
 // 1, in proportion to d; a workgroup's set-up 1 us for each on the compute unit, merging 1.5 us and 0.04 per chunk; nothing faster than rows
 // come from memory, 6 TB/s).  Tried are the counts that fill 1, 2, 3 or 4 workgroups per compute unit; the fewest chunks within 1 us of the
-// best are taken.  (8 KV heads x 6147 rows: 28 chunks 11.4 us of device time, 22: 12.3, 15: 14.6, 33: 14.6.)
+// best are taken.  (8 KV heads x 6147 rows: 28 chunks 11.6 us of device time, 22: 12.7, 15: 14.7, 33: 14.4.)
 // Few KV heads over long caches would have up to 256 chunks each, and the merge reads 32 of them at a time: 64 and 128 are tried too where
-// the compute units would take more than half as many again (1 KV head x 8000 rows 250 chunks 14.9 us, 63 10.1; 2 x 8192 of d = 64
-// 128 10.0, 64 8.2; 1 x 16000 of d = 256 250 17.5, 125 15.6).  With fewer than that, leaving compute units idle takes longer than
+// the compute units would take more than half as many again (1 KV head x 8000 rows 250 chunks 14.8 us, 63 10.2; 2 x 8192 of d = 64
+// 128 10.3, 64 9.0; 1 x 16000 of d = 256 250 17.1, 125 15.1).  With fewer than that, leaving compute units idle takes longer than
 // the chunks that it saves: a quarter or half of them 12 x 1500 rows of d = 64 12 chunks 7.2, 5 8.6; 8 x 8000 of d = 64 32 8.6, 16 10.1; 24 x 300 5
 // 7.2, 2 8.5; 3 x 16357 74 12.2, 40 13.8.  Over 230 other shapes 1.2 % above the best cut with rows from HBM, 15 % at worst (1.8 % and 20 % with
 // a quarter and half of the compute units for all, 1.6 % and 20 % with neither): profiles/decode_chunks.txt.  That was with the four-head kernel before this one; with
-// the present one 1.3 % above the best cut over 200 shapes with groups of four, 26 % at worst (96 KV heads of 16 in fp32 x 791 rows), 1.0 and 15 % in bf16:
+// the present one 1.3 % above the best cut over 200 shapes with groups of four, 17 % at worst (96 KV heads of 8 in fp32 x 2746 rows of d = 64), 1.0 and 15 % in bf16:
 // profiles/decode_chunks_quads.txt.
 int attend_chunks(long long wgs, long long units, int GT, int d, int elem, int rows, int min_rows)
 {

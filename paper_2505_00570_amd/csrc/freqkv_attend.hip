@@ -1086,6 +1086,7 @@ static void launch_quads(const SlabTable& tab, const AttGeom& g, const void* q, 
 
 // Two sets of four heads to a workgroup: a workgroup takes 1.2 to 1.4 times as long, and there are half as many; an odd number of steps is rounded up.
 // Time of one set to a workgroup over that of two (above 1 two are faster; 1 to 11 steps of 2 * attend_row_step(d) rows, much the same for d = 64, 128, 256):
+// (profiles/decode_sets.txt)
 //   workgroups of two sets                      bf16: 1 step   3     5    even   9, 11      fp32: 1 step   3     5    even   7    9, 11
 //   up to 128 (every second compute unit idle; 128 8.3 us for 6.8 at 8 KV heads of 8 x 100 rows)
 //   136 to 256 (one to a compute unit)                 0.91  1.00  1.03  1.11  1.06               0.91  0.94  0.93  1.04  1.02  1.09

@@ -823,7 +823,8 @@ hipError_t launch_contract_f16(const SlabTable& tab, const Geom& g, const _Float
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 cache: fold (or copy) the span out, then contract on the fp32 matrix instructions (fp32 products and sums)
+// fp32 cache: fold (or copy) the span out, then contract on the fp32 matrix instructions (fp32 products and sums); two launches, as each result needs all
+// rows of its column and goes over rows of the span
 // workspace: xs[parity] of Kh x ncolsf fp32 as f32_at has it, ncolsf = ncols rounded up to 64 (pad columns are zero)
 // ------------------------------------------------------------------------------------------
 
